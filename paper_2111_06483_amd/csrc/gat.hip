@@ -23,6 +23,7 @@
 
 #include "gather_common.h"
 #include "gat_f256.h"
+#include "gat_slots.h"
 #include "sar_internal.h"
 
 namespace {
@@ -540,49 +541,120 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict
 
 // ---------------------------------------------------------------- node-wise
 
-// score[v,h] = <a[h], Z[v,h]>; one lane group per node.  A second vector / output pair may ride
-// along (the two halves of the attention score from one pass over Z); avec2 = null: only the first.
-template <typename T, int G>
+// Lanes of the node-wise kernels: a head is LPH lanes of VEC values (the power of two that covers
+// it; lanes behind its end idle), a node is the launch's H heads, a wavefront takes as many nodes
+// (slots) as fit.  RAG: head widths that are no multiple of 4, with the last lane of a head on the
+// head's last four values as in gat_slots.h (`dup` of them are the lane before it's), and heads of
+// fewer than 4 values moved one by one.
+template <typename T, int VEC, int LPH, bool RAG>
+struct NodeLanes {
+    int lane, k_pos, slot, n_slots, h, foff, dup, width;
+    bool on;
+    __device__ inline NodeLanes(int H, int D)
+    {
+        lane = threadIdx.x & (kWave - 1);
+        k_pos = lane % LPH;
+        const int grp = lane / LPH;
+        n_slots = (kWave / LPH) / H;
+        slot = grp / H;
+        h = grp - slot * H;
+        width = D;
+        on = slot < n_slots && VEC * k_pos < D;
+        const int off = RAG ? max(0, min(VEC * k_pos, D - VEC)) : VEC * k_pos;
+        dup = (RAG && on) ? VEC * k_pos - off : 0;
+        foff = h * D + off;
+    }
+    __device__ inline void load(const T* row, float (&v)[VEC]) const
+    {
+        if constexpr (!RAG) {
+            if constexpr (VEC == Vec<T>::N)
+                Vec<T>::unpack(Vec<T>::load(row + foff), v);
+            else
+                f256::Row4<T>::unpack(f256::load_raw<T, false>(row + foff), v);
+        } else {
+            if (width >= VEC) {
+                f256::Row4<T>::unpack(f256::load_raw<T, true>(row + foff), v);
+            } else {
+#pragma unroll
+                for (int x = 0; x < VEC; ++x) v[x] = x < width ? widen(row[foff + x]) : 0.f;
+            }
+        }
+    }
+    __device__ inline void store(T* row, const float (&v)[VEC]) const
+    {
+        if constexpr (!RAG) {
+            if constexpr (VEC == Vec<T>::N)
+                Vec<T>::store(row + foff, v);
+            else
+                f256::store4<T, false>(row + foff, v);
+        } else {
+            if (width >= VEC) {
+                f256::store4<T, true>(row + foff, v);
+            } else {
+#pragma unroll
+                for (int x = 0; x < VEC; ++x)
+                    if (x < width) narrow(row + foff + x, v[x]);
+            }
+        }
+    }
+    __device__ inline void load_vec(const float* p, float (&v)[VEC]) const     // fp32 rows
+    {
+#pragma unroll
+        for (int x = 0; x < VEC; ++x) v[x] = x < width ? p[foff + x] : 0.f;
+    }
+    // whether this lane (and not the one before it) speaks for its value x
+    __device__ inline bool owns(int x) const { return !RAG || (x >= dup && x < width); }
+    __device__ inline float head_sum(float v) const { return f256::group_all<LPH, f256::OpSum>(v); }
+    static __device__ inline float widen(float x) { return x; }
+    static __device__ inline float widen(bf16_t x) { return __uint_as_float((uint32_t)x.bits << 16); }
+    static __device__ inline void narrow(float* p, float v) { *p = v; }
+    static __device__ inline void narrow(bf16_t* p, float v) { p->bits = (uint16_t)f32_to_bf16_rne(v); }
+};
+
+// score[v,h] = <a[h], Z[v,h]>; one lane group per (node, head).  A second vector / output pair may
+// ride along (the two halves of the attention score from one pass over Z); avec2 = null: only the first.
+template <typename T, int VEC, int LPH, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__ Z, int64_t n, int H, int D,
-                                                           int F, int ldz, int ldh,
+                                                           int ldz, int ldh,
                                                            const float* __restrict__ avec,
                                                            float* __restrict__ score,
                                                            const float* __restrict__ avec2,
                                                            float* __restrict__ score2)
 {
-    constexpr int VEC = Vec<T>::N;
-    constexpr int SLOTS = kWave / G;
-    const LaneMap<T, G> lm(F, H, D);
-    const bool pow2 = is_pow2(lm.lph);
-    float av[VEC], av2[VEC];
+    const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
+    float av[VEC] = {}, av2[VEC] = {};
+    if (lm.on) {
+        lm.load_vec(avec, av);
+        if (avec2) lm.load_vec(avec2, av2);
 #pragma unroll
-    for (int x = 0; x < VEC; ++x) {
-        av[x] = lm.on ? avec[lm.gl * VEC + x] : 0.f;
-        av2[x] = (lm.on && avec2) ? avec2[lm.gl * VEC + x] : 0.f;
+        for (int x = 0; x < VEC; ++x) {
+            av[x] = lm.owns(x) ? av[x] : 0.f;
+            av2[x] = lm.owns(x) ? av2[x] : 0.f;
+        }
     }
     const int64_t wave_id = ((int64_t)blockIdx.x * kGatherThreads + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t v0 = wave_id * SLOTS; v0 < n; v0 += n_waves * SLOTS) {
+    for (int64_t v0 = wave_id * lm.n_slots; v0 < n; v0 += n_waves * lm.n_slots) {
         const int64_t v = v0 + lm.slot;
         float z[VEC] = {};
-        if (v < n && lm.on) Vec<T>::unpack(Vec<T>::load(Z + v * ldz + lm.gl * VEC), z);
+        if (v < n && lm.on) lm.load(Z + v * ldz, z);
         float c = 0.f, c2 = 0.f;
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
             c = fmaf(av[x], z[x], c);
             c2 = fmaf(av2[x], z[x], c2);
         }
-        c = pow2 ? group_sum_pow2(c, lm.lph) : group_sum_any(c, lm.head_first, lm.lph);
-        if (avec2) c2 = pow2 ? group_sum_pow2(c2, lm.lph) : group_sum_any(c2, lm.head_first, lm.lph);
-        if (v < n && lm.on && (lm.gl % lm.lph) == 0) {
+        c = lm.head_sum(c);
+        if (avec2) c2 = lm.head_sum(c2);
+        if (v < n && lm.on && lm.k_pos == 0) {
             score[v * ldh + lm.h] = c;
             if (avec2) score2[v * ldh + lm.h] = c2;
         }
     }
 }
 
-// The same for head widths that do not fill whole 16-byte lane pieces: one thread per
-// (node, head), element-wise reads.  Scores only; the aggregation kernels do not take such rows.
+// The same for heads that no wavefront covers: one thread per (node, head), element-wise reads.
+// Scores only; the aggregation kernels do not take such rows.
 template <typename T>
 __global__ __launch_bounds__(256) void k_scores_any(const T* __restrict__ Z, int64_t n, int H, int D,
                                                     const float* __restrict__ avec, float* __restrict__ score,
@@ -594,11 +666,7 @@ __global__ __launch_bounds__(256) void k_scores_any(const T* __restrict__ Z, int
         const T* z = Z + k * D;
         float c = 0.f, c2 = 0.f;
         for (int d = 0; d < D; ++d) {
-            float v;
-            if constexpr (sizeof(T) == 2)
-                v = __uint_as_float((uint32_t)z[d].bits << 16);
-            else
-                v = z[d];
+            const float v = NodeLanes<T, 4, 4, true>::widen(z[d]);
             c = fmaf(avec[h * D + d], v, c);
             if (avec2) c2 = fmaf(avec2[h * D + d], v, c2);
         }
@@ -619,32 +687,33 @@ __global__ __launch_bounds__(256) void k_fwd_begin(float* __restrict__ m, float*
     }
 }
 
-template <typename T, int G>
+template <typename T, int VEC, int LPH, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_fwd_end(const float* __restrict__ m,
                                                             const float* __restrict__ l,
                                                             const float* __restrict__ acc, T* __restrict__ out,
-                                                            float* __restrict__ L, int64_t n, int H, int D, int F,
+                                                            float* __restrict__ L, int64_t n, int H, int D,
                                                             int ldz, int ldh, int act)
 {
-    constexpr int VEC = Vec<T>::N;
-    constexpr int SLOTS = kWave / G;
-    const LaneMap<T, G> lm(F, H, D);
+    const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
     const int64_t wave_id = ((int64_t)blockIdx.x * kGatherThreads + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t v0 = wave_id * SLOTS; v0 < n; v0 += n_waves * SLOTS) {
+    for (int64_t v0 = wave_id * lm.n_slots; v0 < n; v0 += n_waves * lm.n_slots) {
         const int64_t v = v0 + lm.slot;
         if (v >= n || !lm.on) continue;
         const float lv = l[v * ldh + lm.h];
         const float inv = lv > 0.f ? 1.f / lv : 0.f;
         float a[VEC];
-        load_f32<VEC>(acc + v * ldz + lm.gl * VEC, a);
+        if constexpr (RAG)
+            lm.load_vec(acc + v * ldz, a);
+        else
+            load_f32<VEC>(acc + v * ldz + lm.foff, a);
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
             a[x] *= inv;
             if (act == SAR_ACT_RELU) a[x] = fmaxf(a[x], 0.f);
         }
-        Vec<T>::store(out + v * ldz + lm.gl * VEC, a);
-        if ((lm.gl % lm.lph) == 0)
+        lm.store(out + v * ldz, a);
+        if (lm.k_pos == 0)
             L[v * ldh + lm.h] = lv > 0.f ? m[v * ldh + lm.h] + fast_log2(lv) * kLn2 : -INFINITY;
     }
 }
@@ -652,37 +721,36 @@ __global__ __launch_bounds__(kGatherThreads) void k_fwd_end(const float* __restr
 // rec[i,h] = (s log2e, L log2e, <G_i, out_i>, 0) and ds = 0.  With a non-linearity, `out` holds
 // h = act(aggregate) and Gr the error of h: the error of the aggregate, Gr * act'(.), is formed
 // here from h alone (ReLU: h > 0 exactly where the aggregate is, and there they are equal, so
-// <G_i, out_i> is unchanged) and written to Gact for the block kernels to gather.
-template <typename T, int G>
+// <G_i, out_i> is unchanged) and written to Gact for the block kernels to gather.  (Gact may be Gr
+// itself: lanes that share values of a ragged head read them before either writes, in one
+// instruction each, and write the same bits.)
+template <typename T, int VEC, int LPH, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_bwd_begin(const T* Gr, const T* __restrict__ out,
                                                               const float* __restrict__ s,
                                                               const float* __restrict__ L, float4* __restrict__ rec,
-                                                              float* __restrict__ ds, int64_t n, int H, int D, int F,
+                                                              float* __restrict__ ds, int64_t n, int H, int D,
                                                               int ldz, int ldh, int act, T* Gact)
 {
-    constexpr int VEC = Vec<T>::N;
-    constexpr int SLOTS = kWave / G;
-    const LaneMap<T, G> lm(F, H, D);
-    const bool pow2 = is_pow2(lm.lph);
+    const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
     const int64_t wave_id = ((int64_t)blockIdx.x * kGatherThreads + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t v0 = wave_id * SLOTS; v0 < n; v0 += n_waves * SLOTS) {
+    for (int64_t v0 = wave_id * lm.n_slots; v0 < n; v0 += n_waves * lm.n_slots) {
         const int64_t v = v0 + lm.slot;
         float g[VEC] = {}, o[VEC] = {};
         if (v < n && lm.on) {
-            Vec<T>::unpack(Vec<T>::load(Gr + v * ldz + lm.gl * VEC), g);
-            Vec<T>::unpack(Vec<T>::load(out + v * ldz + lm.gl * VEC), o);
+            lm.load(Gr + v * ldz, g);
+            lm.load(out + v * ldz, o);
             if (act == SAR_ACT_RELU) {
 #pragma unroll
                 for (int x = 0; x < VEC; ++x) g[x] = o[x] > 0.f ? g[x] : 0.f;
-                Vec<T>::store(Gact + v * ldz + lm.gl * VEC, g);
+                lm.store(Gact + v * ldz, g);
             }
         }
         float c = 0.f;
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) c = fmaf(g[x], o[x], c);
-        c = pow2 ? group_sum_pow2(c, lm.lph) : group_sum_any(c, lm.head_first, lm.lph);
-        if (v < n && lm.on && (lm.gl % lm.lph) == 0) {
+        for (int x = 0; x < VEC; ++x) c = lm.owns(x) ? fmaf(g[x], o[x], c) : c;
+        c = lm.head_sum(c);
+        if (v < n && lm.on && lm.k_pos == 0) {
             const int64_t k = v * ldh + lm.h;
             rec[k] = make_float4(s[k] * kLog2e, L[k] * kLog2e, c, 0.f);
             ds[k] = 0.f;
@@ -691,64 +759,51 @@ __global__ __launch_bounds__(kGatherThreads) void k_bwd_begin(const T* Gr, const
 }
 
 // dZdst[i] = ds[i] a_r (+ dZadd[i]) ; per-workgroup partial of da_r = sum_i ds[i] Zdst[i]
-template <typename T, int G>
+template <typename T, int VEC, int LPH, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_bwd_end(const T* __restrict__ Zdst, const float* __restrict__ ds,
                                                             const float* __restrict__ a_r, const T* dZadd,
                                                             const int32_t* __restrict__ add_rank, T* dZdst,
                                                             float* __restrict__ partial, int64_t n, int H, int D,
-                                                            int F, int ldz, int ldh)
+                                                            int ldz, int ldh)
 {
-    constexpr int VEC = Vec<T>::N;
-    constexpr int SLOTS = kWave / G;
     __shared__ float part[kWavesPerWG][kWave][VEC];
-    const LaneMap<T, G> lm(F, H, D);
+    const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
     const int wave = threadIdx.x / kWave;
-    float ar[VEC], dar[VEC];
-#pragma unroll
-    for (int x = 0; x < VEC; ++x) {
-        ar[x] = lm.on ? a_r[lm.gl * VEC + x] : 0.f;
-        dar[x] = 0.f;
-    }
+    float ar[VEC] = {}, dar[VEC] = {};
+    if (lm.on) lm.load_vec(a_r, ar);
     const int64_t wave_id = (int64_t)blockIdx.x * kWavesPerWG + wave;
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t v0 = wave_id * SLOTS; v0 < n; v0 += n_waves * SLOTS) {
+    for (int64_t v0 = wave_id * lm.n_slots; v0 < n; v0 += n_waves * lm.n_slots) {
         const int64_t v = v0 + lm.slot;
         if (v >= n || !lm.on) continue;
         const float d = ds[v * ldh + lm.h];
-        float z[VEC], o[VEC];
-        Vec<T>::unpack(Vec<T>::load(Zdst + v * ldz + lm.gl * VEC), z);
+        float z[VEC], o[VEC] = {};
+        lm.load(Zdst + v * ldz, z);
         int64_t va = v;
         bool add = dZadd != nullptr && dZdst != nullptr;
         if (add && add_rank) {
             va = add_rank[v];
             add = add_rank[v + 1] > (int32_t)va;
         }
-        if (add) {
-            Vec<T>::unpack(Vec<T>::load(dZadd + va * ldz + lm.gl * VEC), o);
-        } else {
-#pragma unroll
-            for (int x = 0; x < VEC; ++x) o[x] = 0.f;
-        }
+        if (add) lm.load(dZadd + va * ldz, o);
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
             o[x] = fmaf(d, ar[x], o[x]);
             dar[x] = fmaf(d, z[x], dar[x]);
         }
-        if (dZdst) Vec<T>::store(dZdst + v * ldz + lm.gl * VEC, o);     // null: only da_r is wanted
+        if (dZdst) lm.store(dZdst + v * ldz, o);     // null: only da_r is wanted
     }
 #pragma unroll
     for (int x = 0; x < VEC; ++x) part[wave][lm.lane][x] = dar[x];
     __syncthreads();
     if (wave == 0 && lm.slot == 0 && lm.on) {
-        float v[VEC];
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
             float s = 0.f;
             for (int w = 0; w < kWavesPerWG; ++w)
-                for (int sl = 0; sl < SLOTS; ++sl) s += part[w][sl * G + lm.gl][x];
-            v[x] = s;
+                for (int sl = 0; sl < lm.n_slots; ++sl) s += part[w][sl * H * LPH + lm.lane][x];
+            if (lm.owns(x)) partial[(int64_t)blockIdx.x * (H * D) + lm.foff + x] = s;
         }
-        store_f32<VEC>(partial + (int64_t)blockIdx.x * F + lm.gl * VEC, v);
     }
 }
 
@@ -776,86 +831,130 @@ int check_shape(int dtype, int H, int D)
     return SAR_OK;
 }
 
-// Heads are independent in Eq. 3, so a layer whose rows exceed what one wavefront covers
-// (64 lane pieces: 1024 bytes when the head width is a whole number of 16-byte pieces) is
-// processed as several launches over groups of heads, each launch seeing its slice of every
-// row through the row stride.
+int pow2_at_least(int x)
+{
+    int p = 1;
+    while (p < x) p *= 2;
+    return p;
+}
+
+// Which gather kernels take a launch.  All but the generic ones give a head LPH lanes of 4 values,
+// the power of two >= D/4, which makes 64/LPH lane groups in a wavefront.
+//   exact   rows of 256 contiguous values, every lane busy (gat_f256.h);
+//   padded  the launch's heads need more than half of the lane groups (gat_f256.h; D a multiple of 4,
+//           LPH 8..64): lanes behind a head's end and groups without a head idle.  The gathers are
+//           bound by memory, not by lanes, so they cost little;
+//   slots   they need half of the groups or fewer, or the head width is no multiple of 4, or a head
+//           is four lanes (gat_slots.h): the groups left over take other edges.
+//   generic heads of 1 to 3 values and bf16 heads of more than 256.
+// Measured on shares of the products-sized graph, padded -> slots, forward and backward kernels
+// together where half of the lane groups were idle: see gat_slots.h.
+enum class Gather { kGeneric, kExact, kPadded, kSlots };
+struct LaunchGeo {
+    Gather kind;
+    int lph, n_slots;
+    bool ragged;
+};
+
+LaunchGeo launch_geo(int Hg, int D, int ldz)
+{
+    if (D < 4 || D > 256) return LaunchGeo{Gather::kGeneric, 0, 0, false};
+    const int lph = std::max(4, pow2_at_least((D + 3) / 4)), groups = 64 / lph;
+    if (Hg * lph == 64 && D == 4 * lph && ldz == f256::kF) return LaunchGeo{Gather::kExact, lph, 1, false};
+    int slots = 1;
+    while (slots * 2 * Hg <= groups) slots *= 2;
+    if (slots == 1 && lph >= 8 && D % 4 == 0) return LaunchGeo{Gather::kPadded, lph, 1, false};
+    return LaunchGeo{Gather::kSlots, lph, slots, D % 4 != 0};
+}
+
+// Heads are independent in Eq. 3, so a layer of more heads than a wavefront has lane groups for is
+// processed as several launches over groups of heads, as even as they come, each launch seeing its
+// slice of every row through the row stride.
 struct HeadGroups {
-    int n, Hg, Fg;       // groups, heads per group, values per group
+    int n, most, H;      // launches, heads of a launch at most, heads of the layer
     size_t fb;           // bytes per feature value
-    int piece;           // values per lane of the generic and node-wise kernels (divides D)
-    bool fast_fwd;       // the specialised forward / backward gather kernels take a group (they use the
-    bool fast_bwd;       // full row type)
-    int full;            // values per lane of the full row type: 4 (fp32) or 8 (bf16)
+    int first(int g) const { return g * most; }
+    int count(int g) const { return std::min(most, H - g * most); }
 };
-
-// Lanes per head of the specialised kernels for head width D: the power of two >= D/4 (4..64), or 0.
-int lanes_per_head(int D)
-{
-    if (D % 4 != 0 || D > 256) return 0;
-    int lph = 4;
-    while (lph * 4 < D) lph *= 2;
-    return lph;
-}
-
-// The specialised kernels give every head LPH lanes of 4 values.  Exact geometry: contiguous rows
-// of 256 values, LPH = D/4 (4..64), 64/LPH heads.  Padded geometry (built for LPH = 8, 16, 32, 64):
-// heads of any width that is a multiple of 4 up to 4 LPH, rows of any stride, up to 64/LPH heads per
-// launch; lanes a head does not need, and head groups the launch has no head for, stay idle, and a
-// layer of more heads runs as several launches over groups of heads.  The gathers are bound by
-// memory, not by lanes, so idle lanes cost little:
-//   at least 3/8 of the 64 lanes busy: faster than the generic kernels in both passes, also over
-//     several launches (4 x 32, 5.96 -> 3.8 ms per step of the products-sized share; 16 x 32 in
-//     rows of 512, 19.2 -> 14.9 ms; 1 x 100, 11.5 -> 5.3 ms; 3 x 64 and 6 x 32 on 48 lanes);
-//   fewer ("sparse"): only the backward pass gains, and only when the whole layer is ONE launch
-//     (the generic backward gives every source a wavefront however few its edges: 4 x 16,
-//     3.43 -> 1.83 ms; its forward stays ahead, 0.69 against 0.94 ms; over several launches the
-//     repeated index traffic costs more than it saves).
-// Lanes per head of the padded geometry for head width D, or 0.
-int padded_lanes(int D)
-{
-    const int need = lanes_per_head(D);
-    return need == 0 ? 0 : std::max(8, need);
-}
-// Whether a launch of Hg heads of width D would leave more than 5/8 of the lanes idle.
-bool sparse_launch(int Hg, int D) { return Hg * (D / 4) * 8 < 3 * 64; }
-
-struct FastGeo {
-    int lph;     // 0: not applicable
-    bool pad;
-    bool sparse; // fewer than 3/8 of the lanes carry values: backward pass only
-};
-FastGeo fast_geo(int H, int D, int ldz);
 
 HeadGroups head_groups(int dtype, int H, int D)
 {
     HeadGroups g;
+    g.H = H;
     g.fb = dtype == SAR_F32 ? 4 : 2;
-    g.full = dtype == SAR_F32 ? 4 : 8;
-    g.piece = piece_for(dtype == SAR_F32, D);
-    int hg = std::max<int>(1, 64 * g.piece / D);
-    hg = std::min(hg, H);
-    while (H % hg != 0) --hg;
-    // heads per launch of the specialised kernels, where they apply (see padded_lanes): the largest
-    // divisor of H that fits a wavefront
-    const int lph = lanes_per_head(D);
-    if (lph > 0 && H * lph == 64 && H * D == f256::kF) {
-        hg = H;                                   // the exact geometry: all heads in one launch
-    } else if (lph > 0) {
-        for (int cand = std::min(H, 64 / padded_lanes(D)); cand >= 1; --cand) {
-            if (H % cand != 0) continue;
-            if (!sparse_launch(cand, D) || cand == H) hg = cand;
-            break;
-        }
-    }
-    g.Hg = hg;
-    g.n = H / hg;
-    g.Fg = hg * D;
-    const FastGeo geo = fast_geo(hg, D, H * D);
-    g.fast_bwd = geo.lph != 0;
-    g.fast_fwd = geo.lph != 0 && !geo.sparse;
+    const int groups = (D < 4 || D > 256) ? std::max(1, 64 * piece_for(dtype == SAR_F32, D) / D)
+                                          : 64 / std::max(4, pow2_at_least((D + 3) / 4));
+    g.n = (H + groups - 1) / groups;
+    g.most = (H + g.n - 1) / g.n;
+    g.n = (H + g.most - 1) / g.most;
     return g;
 }
+
+// Geometry of the node-wise kernels (NodeLanes): 16 bytes per lane where the head width is whole
+// 16-byte pieces, else 4 values.
+struct NodeGeo {
+    int vec, lph;
+    bool ragged;
+    HeadGroups hg;
+    int slots(int g) const { return (kWave / lph) / hg.count(g); }
+};
+
+NodeGeo node_geo(int dtype, int H, int D)
+{
+    NodeGeo g;
+    const int full = dtype == SAR_F32 ? 4 : 8;
+    g.vec = D % full == 0 ? full : 4;
+    g.ragged = D % 4 != 0;
+    g.lph = pow2_at_least((D + g.vec - 1) / g.vec);
+    g.hg.H = H;
+    g.hg.fb = dtype == SAR_F32 ? 4 : 2;
+    const int groups = 64 / g.lph;
+    g.hg.n = (H + groups - 1) / groups;
+    g.hg.most = (H + g.hg.n - 1) / g.hg.n;
+    g.hg.n = (H + g.hg.most - 1) / g.hg.most;
+    return g;
+}
+
+#define SAR_NODE_LPH(geo, ...)                                          \
+    switch ((geo).lph) {                                                \
+        case 1: { constexpr int kL = 1; __VA_ARGS__; } break;           \
+        case 2: { constexpr int kL = 2; __VA_ARGS__; } break;           \
+        case 4: { constexpr int kL = 4; __VA_ARGS__; } break;           \
+        case 8: { constexpr int kL = 8; __VA_ARGS__; } break;           \
+        case 16: { constexpr int kL = 16; __VA_ARGS__; } break;         \
+        case 32: { constexpr int kL = 32; __VA_ARGS__; } break;         \
+        default: { constexpr int kL = 64; __VA_ARGS__; } break;         \
+    }
+// Runs `...` with T, kV, kL, kR bound to the row type, VEC, LPH and RAG of `geo`.
+#define SAR_DISPATCH_NODE(dtype, geo, ...)                              \
+    do {                                                                \
+        if ((dtype) == SAR_F32) {                                       \
+            using T = float;                                            \
+            constexpr int kV = 4;                                       \
+            if ((geo).ragged) {                                         \
+                constexpr bool kR = true;                               \
+                SAR_NODE_LPH(geo, __VA_ARGS__);                         \
+            } else {                                                    \
+                constexpr bool kR = false;                              \
+                SAR_NODE_LPH(geo, __VA_ARGS__);                         \
+            }                                                           \
+        } else {                                                        \
+            using T = bf16_t;                                           \
+            if ((geo).vec == 8) {                                       \
+                constexpr int kV = 8;                                   \
+                constexpr bool kR = false;                              \
+                SAR_NODE_LPH(geo, __VA_ARGS__);                         \
+            } else if ((geo).ragged) {                                  \
+                constexpr int kV = 4;                                   \
+                constexpr bool kR = true;                               \
+                SAR_NODE_LPH(geo, __VA_ARGS__);                         \
+            } else {                                                    \
+                constexpr int kV = 4;                                   \
+                constexpr bool kR = false;                              \
+                SAR_NODE_LPH(geo, __VA_ARGS__);                         \
+            }                                                           \
+        }                                                               \
+    } while (0)
 
 template <typename P>
 P* shift(P* p, size_t bytes)
@@ -908,20 +1007,25 @@ unsigned persistent_grid_for(int64_t n_rows, int64_t n_long, int resident)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, resident));
 }
 
-// Whether the specialised kernels take a launch of H heads of width D in rows of stride ldz, and
-// in which geometry: exact (contiguous rows of 256 values, power-of-two head width) or padded
-// (64/LPH heads of any width up to 4*LPH that is a multiple of 4, any row stride; built for
-// LPH = 8, 16, 32, 64).  Lanes move 4 values (16 bytes of fp32, 8 bytes of bf16) either way.
-FastGeo fast_geo(int H, int D, int ldz)
+f256::FwdP fwd_params(const FwdArgs& a)
 {
-    const int lph = lanes_per_head(D);
-    if (lph == 0) return FastGeo{0, false, false};
-    if (H * lph == 64 && D == 4 * lph && ldz == f256::kF) return FastGeo{lph, false, false};
-    const int lanes = padded_lanes(D);
-    if (H < 1 || H * lanes > 64) return FastGeo{0, false, false};
-    const bool sparse = sparse_launch(H, D);
-    if (sparse && H * D != ldz) return FastGeo{0, false, false};   // sparse launches pay only as the single one
-    return FastGeo{lanes, true, sparse};
+    f256::FwdP p{};
+    p.indptr = a.indptr; p.indices = a.indices; p.rows = a.rows;
+    p.n_rows = a.n_rows; p.n_long = a.n_long;
+    p.Z = a.Z; p.t = a.t; p.a_l = a.a_l; p.s = a.s; p.m = a.m; p.l = a.l; p.acc = a.acc; p.out = a.out; p.L = a.L;
+    p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope; p.act = a.act;
+    p.ld = a.ldz; p.ldh = a.ldh; p.D = a.D;
+    return p;
+}
+
+f256::Tabs fwd_tabs(const PtrTab& zt, const PtrTab& tt)
+{
+    f256::Tabs tabs{};
+    for (int q = 0; q < SAR_MAX_BLOCKS; ++q) {
+        tabs.Z[q] = zt.p[q];
+        tabs.t[q] = static_cast<const float*>(tt.p[q]);
+    }
+    return tabs;
 }
 
 template <typename T, int LPH, bool ALL, bool FLY, bool PAD>
@@ -930,55 +1034,27 @@ int launch_fwd_f256(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, hipStr
     constexpr int B = LPH >= 8 ? 8 : 4;
     auto fn = f256::k_gat_fwd_f256<T, LPH, B, ALL, FLY, PAD>;
     static const int resident = resident_workgroups(fn);
-    f256::FwdP p{};
-    p.indptr = a.indptr; p.indices = a.indices; p.rows = a.rows;
-    p.n_rows = a.n_rows; p.n_long = a.n_long;
-    p.Z = a.Z; p.t = a.t; p.a_l = a.a_l; p.s = a.s; p.m = a.m; p.l = a.l; p.acc = a.acc; p.out = a.out; p.L = a.L;
-    p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope; p.act = a.act;
-    p.ld = a.ldz; p.ldh = a.ldh; p.D = a.D;
-    f256::Tabs tabs{};
-    for (int q = 0; q < SAR_MAX_BLOCKS; ++q) {
-        tabs.Z[q] = zt.p[q];
-        tabs.t[q] = static_cast<const float*>(tt.p[q]);
-    }
-    fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(p, tabs);
+    fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt));
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
 
-template <typename T, bool ALL>
-int launch_fwd(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
+template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
+int launch_fwd_slots(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int n_slots, hipStream_t st)
 {
-    if (a.n_rows == 0) return SAR_OK;
-    if constexpr (is_full_row<T>::value) {
-#define SAR_FWD_F256(LPH, PAD)                                                             \
-    return a.a_l ? launch_fwd_f256<T, LPH, ALL, true, PAD>(a, zt, tt, st)                  \
-                 : launch_fwd_f256<T, LPH, ALL, false, PAD>(a, zt, tt, st)
-        const FastGeo geo = fast_geo(a.H, a.D, a.ldz);
-        if (geo.sparse) {
-            // the generic forward kernel is the faster one here
-        } else if (geo.pad) {
-            switch (geo.lph) {
-                case 8: SAR_FWD_F256(8, true);
-                case 16: SAR_FWD_F256(16, true);
-                case 32: SAR_FWD_F256(32, true);
-                case 64: SAR_FWD_F256(64, true);
-                default: break;
-            }
-        } else {
-            switch (geo.lph) {
-                case 4: SAR_FWD_F256(4, false);
-                case 8: SAR_FWD_F256(8, false);
-                case 16: SAR_FWD_F256(16, false);
-                case 32: SAR_FWD_F256(32, false);
-                case 64: SAR_FWD_F256(64, false);
-                default: break;
-            }
-        }
-#undef SAR_FWD_F256
-        if (a.D % Vec<T>::N != 0)
-            return sar::fail(SAR_ERR_STATE, "head width %d reached the generic kernel with %d-value pieces", a.D, Vec<T>::N);
-    }
+    auto fn = slots::k_gat_fwd_slots<T, LPH, ALL, FLY, RAG>;
+    static const int resident = resident_workgroups(fn);
+    fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt),
+                                                                                     n_slots);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
+// The generic kernels' launch: heads of 1 to 3 values (T a narrow row type) or bf16 heads of more
+// than 256 (T = bf16_t).
+template <typename T, bool ALL>
+int launch_fwd_generic(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
+{
     const unsigned grid = persistent_grid(a.n_rows, a.n_long);
     if constexpr (ALL) {
         if (a.act == SAR_ACT_RELU) {
@@ -992,70 +1068,186 @@ int launch_fwd(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipS
     return SAR_OK;
 }
 
-// The same pair of kernels in the padded geometry.  The few-edges kernel also takes the sources
-// without an edge at the end of the list (it writes their zero rows).
-template <typename T, int LPH, bool ALL>
-int launch_bwd_f256_padded(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out, hipStream_t st)
+// Runs `...` with T bound to the generic kernels' row type.
+#define SAR_DISPATCH_GENERIC(dtype, D, ...)              \
+    do {                                                 \
+        if ((dtype) == SAR_F32) {                        \
+            if ((D) == 2) {                              \
+                using T = f32x2_t;                       \
+                __VA_ARGS__;                             \
+            } else {                                     \
+                using T = f32x1_t;                       \
+                __VA_ARGS__;                             \
+            }                                            \
+        } else if ((D) > 256) {                          \
+            using T = bf16_t;                            \
+            __VA_ARGS__;                                 \
+        } else if ((D) == 2) {                           \
+            using T = bf16x2_t;                          \
+            __VA_ARGS__;                                 \
+        } else {                                         \
+            using T = bf16x1_t;                          \
+            __VA_ARGS__;                                 \
+        }                                                \
+    } while (0)
+
+#define SAR_FWD_CASE(LAUNCH, LPH, FLAG, ...)                                                          \
+    case LPH:                                                                                         \
+        return a.a_l ? LAUNCH<T, LPH, ALL, true, FLAG>(a, zt, tt __VA_ARGS__, st)                     \
+                     : LAUNCH<T, LPH, ALL, false, FLAG>(a, zt, tt __VA_ARGS__, st)
+
+template <typename T, bool ALL>
+int launch_fwd_fast(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, const LaunchGeo& geo, hipStream_t st)
 {
-    constexpr int B = 8;
-    auto wide = f256::k_gat_bwd_f256<T, LPH, B, ALL, true>;
-    auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
-    auto single = f256::k_gat_bwd_single<T, LPH, true>;
-    static const int resident_wide = resident_workgroups(wide);
-    static const int resident_few = resident_workgroups(few);
-    static const int resident_single = resident_workgroups(single);
+    const int ns = geo.n_slots;
+    if (geo.kind == Gather::kExact) {
+        switch (geo.lph) {
+            SAR_FWD_CASE(launch_fwd_f256, 4, false);
+            SAR_FWD_CASE(launch_fwd_f256, 8, false);
+            SAR_FWD_CASE(launch_fwd_f256, 16, false);
+            SAR_FWD_CASE(launch_fwd_f256, 32, false);
+            SAR_FWD_CASE(launch_fwd_f256, 64, false);
+            default: break;
+        }
+    } else if (geo.kind == Gather::kPadded) {
+        switch (geo.lph) {
+            SAR_FWD_CASE(launch_fwd_f256, 8, true);
+            SAR_FWD_CASE(launch_fwd_f256, 16, true);
+            SAR_FWD_CASE(launch_fwd_f256, 32, true);
+            SAR_FWD_CASE(launch_fwd_f256, 64, true);
+            default: break;
+        }
+    } else if (geo.ragged) {
+        switch (geo.lph) {
+            SAR_FWD_CASE(launch_fwd_slots, 4, true, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 8, true, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 16, true, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 32, true, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 64, true, , ns);
+            default: break;
+        }
+    } else {
+        switch (geo.lph) {
+            SAR_FWD_CASE(launch_fwd_slots, 4, false, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 8, false, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 16, false, , ns);
+            SAR_FWD_CASE(launch_fwd_slots, 32, false, , ns);
+            default: break;
+        }
+    }
+    return sar::fail(SAR_ERR_STATE, "no forward kernel for %d heads of %d values", a.H, a.D);
+}
+
+template <bool ALL>
+int launch_fwd(int dtype, const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
+{
+    if (a.n_rows == 0) return SAR_OK;
+    const LaunchGeo geo = launch_geo(a.H, a.D, a.ldz);
+    if (geo.kind == Gather::kGeneric)
+        SAR_DISPATCH_GENERIC(dtype, a.D, return (launch_fwd_generic<T, ALL>(a, zt, tt, P, st)));
+    if (dtype == SAR_F32) return launch_fwd_fast<float, ALL>(a, zt, tt, geo, st);
+    return launch_fwd_fast<bf16_t, ALL>(a, zt, tt, geo, st);
+}
+
+// Work of a backward launch in the padded geometry or with slots: kernels, and what they need
+// besides BwdTabs and BwdP.
+f256::BwdTabs bwd_tabs(const BwdArgs& tabs)
+{
     f256::BwdTabs t{};
     for (int q = 0; q < SAR_MAX_BLOCKS; ++q) {
         t.t_indptr[q] = tabs.t_indptr[q]; t.t_indices[q] = tabs.t_indices[q];
         t.Z[q] = tabs.Z[q]; t.t[q] = tabs.t[q]; t.dZ[q] = tabs.dZ[q]; t.dt[q] = tabs.dt[q];
         t.rank[q] = tabs.rank[q];
     }
+    return t;
+}
+
+f256::BwdP bwd_params(const BwdScalars& a)
+{
     f256::BwdP p{};
     p.rows = a.rows; p.n_rows = a.n_wide; p.n_long = std::min(a.n_long, a.n_wide);
     p.G = a.G; p.rec = a.rec; p.a_l = a.a_l; p.ds = a.ds; p.partial = a.partial;
     p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope;
     p.ld = a.ldz; p.ldh = a.ldh; p.D = a.D;
+    return p;
+}
+
+unsigned grid_of(int64_t items, int64_t per_wg, int resident)
+{
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + per_wg - 1) / per_wg, resident));
+}
+
+// The padded and the slots kernels.  The few-edges kernels also take the sources without an edge
+// at the end of the list (they write their zero rows).
+template <typename T, int LPH, bool ALL, bool SLOTS, bool RAG>
+int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, unsigned* grid_out, hipStream_t st)
+{
+    constexpr int B = LPH >= 8 ? 8 : 4;
+    const f256::BwdTabs t = bwd_tabs(tabs);
+    const f256::BwdP p = bwd_params(a);
     unsigned g_wide = 0, g_few = 0, g_single = 0;
     if (a.n_wide > 0) {
-        g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
-        wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
+        if constexpr (SLOTS) {
+            auto wide = slots::k_gat_bwd_slots<T, LPH, ALL, RAG>;
+            static const int resident = resident_workgroups(wide);
+            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
+            wide<<<g_wide, kGatherThreads, 0, st>>>(t, p, n_slots);
+        } else {
+            auto wide = f256::k_gat_bwd_f256<T, LPH, B, ALL, true>;
+            static const int resident = resident_workgroups(wide);
+            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
+            wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
+        }
         SAR_LAUNCH_CHECK();
     }
     // The sources of one edge go destination-major where the handle lists them that way.  In the
     // work list they sit between the other few-edge sources and the ones without an edge, so the
     // few-edges kernel takes the list in two pieces around them.
     const int64_t n_edged = std::max(a.n_wide, std::min(a.n_rows, a.n_touched));
-    const int64_t n_pulled = (ALL && a.s_dst && a.n_single <= n_edged - a.n_wide) ? a.n_single : 0;
-    const int64_t per_wg = (int64_t)(B / 2) * kWavesPerWG;
+    const int64_t n_pulled = (!RAG && ALL && a.s_dst && a.n_single <= n_edged - a.n_wide) ? a.n_single : 0;
     const int64_t piece[2][2] = {{a.n_wide, n_pulled ? n_edged - n_pulled : a.n_rows}, {n_edged, n_pulled ? a.n_rows : n_edged}};
     for (int k = 0; k < 2; ++k) {
         const int64_t n = piece[k][1] - piece[k][0];
         if (n <= 0) continue;
-        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per_wg - 1) / per_wg, resident_few));
-        few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few));
+        unsigned g = 0;
+        if constexpr (SLOTS) {
+            auto few = slots::k_gat_bwd_few_slots<T, LPH, ALL, RAG>;
+            static const int resident = resident_workgroups(few);
+            g = grid_of(n, (int64_t)n_slots * kWavesPerWG, resident);
+            few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few), n_slots);
+        } else {
+            auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
+            static const int resident = resident_workgroups(few);
+            g = grid_of(n, (int64_t)(B / 2) * kWavesPerWG, resident);
+            few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few));
+        }
         SAR_LAUNCH_CHECK();
         g_few += g;
     }
-    if (n_pulled > 0) {
-        const f256::SingleP sp{a.s_dst, a.s_src, a.s_row, n_pulled};
-        const int64_t per_wg_s = (int64_t)kWave * kWavesPerWG;
-        g_single = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_pulled + per_wg_s - 1) / per_wg_s, resident_single));
-        single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
-        SAR_LAUNCH_CHECK();
+    if constexpr (!RAG && ALL) {
+        if (n_pulled > 0) {
+            auto single = f256::k_gat_bwd_single<T, LPH, true>;
+            static const int resident = resident_workgroups(single);
+            const f256::SingleP sp{a.s_dst, a.s_src, a.s_row, n_pulled};
+            g_single = grid_of(n_pulled, (int64_t)kWave * kWavesPerWG, resident);
+            single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
+            SAR_LAUNCH_CHECK();
+        }
     }
     *grid_out = g_wide + g_few + g_single;
     return SAR_OK;
 }
 
-// da_l[h*D + 4k + x] += sum_w partial[w][(h*LPH + k)*4 + x]: the padded kernels leave their
-// partial sums in lane order (256 slots per workgroup)
+// da_l[h*D + off(k) + x] += sum_w partial[w][(h*LPH + k)*4 + x]: the padded and the slots kernels
+// leave their partial sums in lane order (256 per workgroup).  off(k) = 4k, or D - 4 for the last
+// lane of a ragged head; the values such a lane shares with the one before it are that one's.
 __global__ __launch_bounds__(256) void k_reduce_partials_padded(const float* __restrict__ partial, int n_part,
                                                                 int lph, int H, int D, float* __restrict__ out)
 {
     __shared__ float red[256];
     const int slot = blockIdx.x, lane = slot >> 2, x = slot & 3;
-    const int h = lane / lph, k = lane % lph;
-    if (h >= H || 4 * k >= D) return;
+    const int h = lane / lph, k = lane % lph, off = min(4 * k, D - 4);
+    if (h >= H || 4 * k >= D || off + x < 4 * k) return;
     float s = 0.f;
     for (int w = threadIdx.x; w < n_part; w += 256) s += partial[(int64_t)w * 256 + slot];
     red[threadIdx.x] = s;
@@ -1064,7 +1256,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials_padded(const float* __r
         if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[h * D + 4 * k + x] += red[0];
+    if (threadIdx.x == 0) out[h * D + off + x] += red[0];
 }
 
 // The sources without an edge in their block (the tail of the work list): their rows of dZ_q and
@@ -1109,16 +1301,8 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
     static const int resident_wide = resident_workgroups(wide);
     static const int resident_few = resident_workgroups(few);
     static const int resident_single = resident_workgroups(single);
-    f256::BwdTabs t{};
-    for (int q = 0; q < SAR_MAX_BLOCKS; ++q) {
-        t.t_indptr[q] = tabs.t_indptr[q]; t.t_indices[q] = tabs.t_indices[q];
-        t.Z[q] = tabs.Z[q]; t.t[q] = tabs.t[q]; t.dZ[q] = tabs.dZ[q]; t.dt[q] = tabs.dt[q];
-        t.rank[q] = tabs.rank[q];
-    }
-    f256::BwdP p{};
-    p.rows = a.rows; p.n_rows = a.n_wide; p.n_long = std::min(a.n_long, a.n_wide);
-    p.G = a.G; p.rec = a.rec; p.a_l = a.a_l; p.ds = a.ds; p.partial = a.partial;
-    p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope;
+    const f256::BwdTabs t = bwd_tabs(tabs);
+    const f256::BwdP p = bwd_params(a);
     unsigned g_wide = 0, g_few = 0, g_single = 0;
     const int64_t n_edged = std::max(a.n_wide, std::min(a.n_rows, a.n_touched));
     // the sources of one edge (the end of the edged part of the list) go destination-major where
@@ -1169,44 +1353,76 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
     return SAR_OK;
 }
 
+#define SAR_BWD_CASE(LPH, SLOTS, RAG)                                                                     \
+    case LPH: SAR_TRY((launch_bwd_padded<T, LPH, ALL, SLOTS, RAG>(tabs, a, geo.n_slots, &grid, st))); break
+
 template <typename T, bool ALL>
-int launch_bwd(const BwdArgs& tabs, BwdScalars& a, float* da_l, hipStream_t st)
+int launch_bwd_fast(const BwdArgs& tabs, const BwdScalars& a, const LaunchGeo& geo, float* da_l, hipStream_t st)
 {
-    if (a.n_rows == 0) return SAR_OK;
-    unsigned grid = persistent_grid(a.n_rows, a.n_long);
-    bool done = false;
-    if constexpr (is_full_row<T>::value) {
-        const FastGeo geo = fast_geo(a.H, a.D, a.ldz);
-        if (geo.pad) {
-            switch (geo.lph) {
-                case 8: SAR_TRY((launch_bwd_f256_padded<T, 8, ALL>(tabs, a, &grid, st))); break;
-                case 16: SAR_TRY((launch_bwd_f256_padded<T, 16, ALL>(tabs, a, &grid, st))); break;
-                case 32: SAR_TRY((launch_bwd_f256_padded<T, 32, ALL>(tabs, a, &grid, st))); break;
-                default: SAR_TRY((launch_bwd_f256_padded<T, 64, ALL>(tabs, a, &grid, st))); break;
-            }
-            k_reduce_partials_padded<<<256, 256, 0, st>>>(a.partial, (int)grid, geo.lph, a.H, a.D, da_l);
-            SAR_LAUNCH_CHECK();
-            return SAR_OK;
-        }
-        done = true;
+    unsigned grid = 0;
+    if (geo.kind == Gather::kExact) {
         switch (geo.lph) {
             case 4: SAR_TRY((launch_bwd_f256<T, 4, ALL>(tabs, a, &grid, st))); break;
             case 8: SAR_TRY((launch_bwd_f256<T, 8, ALL>(tabs, a, &grid, st))); break;
             case 16: SAR_TRY((launch_bwd_f256<T, 16, ALL>(tabs, a, &grid, st))); break;
             case 32: SAR_TRY((launch_bwd_f256<T, 32, ALL>(tabs, a, &grid, st))); break;
-            case 64: SAR_TRY((launch_bwd_f256<T, 64, ALL>(tabs, a, &grid, st))); break;
-            default: done = false; break;
+            default: SAR_TRY((launch_bwd_f256<T, 64, ALL>(tabs, a, &grid, st))); break;
         }
-        if (!done && a.D % Vec<T>::N != 0)
-            return sar::fail(SAR_ERR_STATE, "head width %d reached the generic kernel with %d-value pieces", a.D, Vec<T>::N);
-    }
-    if (!done) {
-        SAR_DISPATCH_G(T, a.F, (k_gat_bwd<T, kG, ALL><<<grid, kGatherThreads, 0, st>>>(tabs, a)));
+        k_reduce_partials<<<a.F, 256, 0, st>>>(a.partial, (int)grid, a.F, da_l);
         SAR_LAUNCH_CHECK();
+        return SAR_OK;
     }
+    if (geo.kind == Gather::kPadded) {
+        switch (geo.lph) {
+            SAR_BWD_CASE(8, false, false);
+            SAR_BWD_CASE(16, false, false);
+            SAR_BWD_CASE(32, false, false);
+            SAR_BWD_CASE(64, false, false);
+            default: return sar::fail(SAR_ERR_STATE, "no backward kernel for %d heads of %d values", a.H, a.D);
+        }
+    } else if (geo.ragged) {
+        switch (geo.lph) {
+            SAR_BWD_CASE(4, true, true);
+            SAR_BWD_CASE(8, true, true);
+            SAR_BWD_CASE(16, true, true);
+            SAR_BWD_CASE(32, true, true);
+            SAR_BWD_CASE(64, true, true);
+            default: return sar::fail(SAR_ERR_STATE, "no backward kernel for %d heads of %d values", a.H, a.D);
+        }
+    } else {
+        switch (geo.lph) {
+            SAR_BWD_CASE(4, true, false);
+            SAR_BWD_CASE(8, true, false);
+            SAR_BWD_CASE(16, true, false);
+            SAR_BWD_CASE(32, true, false);
+            default: return sar::fail(SAR_ERR_STATE, "no backward kernel for %d heads of %d values", a.H, a.D);
+        }
+    }
+    k_reduce_partials_padded<<<256, 256, 0, st>>>(a.partial, (int)grid, geo.lph, a.H, a.D, da_l);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
+template <typename T, bool ALL>
+int launch_bwd_generic(const BwdArgs& tabs, const BwdScalars& a, float* da_l, hipStream_t st)
+{
+    const unsigned grid = persistent_grid(a.n_rows, a.n_long);
+    SAR_DISPATCH_G(T, a.F, (k_gat_bwd<T, kG, ALL><<<grid, kGatherThreads, 0, st>>>(tabs, a)));
+    SAR_LAUNCH_CHECK();
     k_reduce_partials<<<a.F, 256, 0, st>>>(a.partial, (int)grid, a.F, da_l);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
+}
+
+template <bool ALL>
+int launch_bwd(int dtype, const BwdArgs& tabs, const BwdScalars& a, float* da_l, hipStream_t st)
+{
+    if (a.n_rows == 0) return SAR_OK;
+    const LaunchGeo geo = launch_geo(a.H, a.D, a.ldz);
+    if (geo.kind == Gather::kGeneric)
+        SAR_DISPATCH_GENERIC(dtype, a.D, return (launch_bwd_generic<T, ALL>(tabs, a, da_l, st)));
+    if (dtype == SAR_F32) return launch_bwd_fast<float, ALL>(tabs, a, geo, da_l, st);
+    return launch_bwd_fast<bf16_t, ALL>(tabs, a, geo, da_l, st);
 }
 
 // room for one row of 256 partial sums per workgroup of the (up to) four backward launches of a call
@@ -1243,18 +1459,15 @@ int sar::gat_scores2(const void* Z, int dtype, int64_t n, int H, int D, const fl
     if (n == 0) return SAR_OK;
     SAR_CHECK_ARG(Z && a && score, "Z, a or score is null");
     SAR_CHECK_ARG(aligned16(Z), "Z must be 16-byte aligned");
-    const int F = H * D;
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const NodeGeo geo = node_geo(dtype, H, D);
     hipStream_t st = sar::as_stream(stream);
-    for (int g = 0; g < hg.n; ++g) {
-        const void* Zg = shift(Z, (size_t)g * hg.Fg * hg.fb);
-        const float* ag = a + (size_t)g * hg.Fg;
-        float* sg = score + (size_t)g * hg.Hg;
-        const float* ag2 = a2 ? a2 + (size_t)g * hg.Fg : nullptr;
-        float* sg2 = score2 ? score2 + (size_t)g * hg.Hg : nullptr;
-        SAR_DISPATCH_ROW(dtype, hg.piece,
-                         SAR_DISPATCH_G(T, hg.Fg, (k_scores<T, kG><<<nodewise_grid(n, kWave / kG), kGatherThreads, 0, st>>>(
-                                                      static_cast<const T*>(Zg), n, hg.Hg, D, hg.Fg, F, H, ag, sg, ag2, sg2))));
+    for (int g = 0; g < geo.hg.n; ++g) {
+        const size_t h0 = (size_t)geo.hg.first(g), f0 = h0 * D;
+        const void* Zg = shift(Z, f0 * geo.hg.fb);
+        const unsigned grid = nodewise_grid(n, geo.slots(g));
+        SAR_DISPATCH_NODE(dtype, geo, (k_scores<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
+                                          static_cast<const T*>(Zg), n, geo.hg.count(g), D, H * D, H, a + f0, score + h0,
+                                          a2 ? a2 + f0 : nullptr, score2 ? score2 + h0 : nullptr)));
         SAR_LAUNCH_CHECK();
     }
     return SAR_OK;
@@ -1292,7 +1505,7 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     SAR_CHECK_ARG(aligned16(Zq) && aligned16(acc) && aligned16(a_l), "Zq, acc and a_l must be 16-byte aligned");
     const HeadGroups hg = head_groups(dtype, H, D);
     for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
+        const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         FwdArgs a{};
         a.indptr = k.indptr;
         a.indices = reinterpret_cast<const uint32_t*>(k.indices);
@@ -1306,15 +1519,14 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.m = m + h0;
         a.l = l + h0;
         a.acc = acc + f0;
-        a.H = hg.Hg;
+        a.H = hg.count(g);
         a.D = D;
-        a.F = hg.Fg;
+        a.F = a.H * D;
         a.ldz = H * D;
         a.ldh = H;
         a.slope = slope;
         PtrTab none{};
-        SAR_DISPATCH_ROW(dtype, hg.fast_fwd ? hg.full : hg.piece,
-                         SAR_TRY((launch_fwd<T, false>(a, none, none, 0, sar::as_stream(stream)))));
+        SAR_TRY(launch_fwd<false>(dtype, a, none, none, 0, sar::as_stream(stream)));
     }
     return SAR_OK;
 }
@@ -1328,15 +1540,14 @@ extern "C" int sar_gat_fwd_end(const float* m, const float* l, const float* acc,
     if (n_dst == 0) return SAR_OK;
     SAR_CHECK_ARG(m && l && acc && out && L, "a tensor argument is null");
     SAR_CHECK_ARG(aligned16(acc) && aligned16(out), "acc and out must be 16-byte aligned");
-    const int F = H * D;
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const NodeGeo geo = node_geo(dtype, H, D);
     hipStream_t st = sar::as_stream(stream);
-    for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
-        SAR_DISPATCH_ROW(dtype, hg.piece,
-                         SAR_DISPATCH_G(T, hg.Fg, (k_fwd_end<T, kG><<<nodewise_grid(n_dst, kWave / kG), kGatherThreads, 0, st>>>(
-                                                      m + h0, l + h0, acc + f0, static_cast<T*>(out) + f0, L + h0, n_dst,
-                                                      hg.Hg, D, hg.Fg, F, H, act))));
+    for (int g = 0; g < geo.hg.n; ++g) {
+        const size_t h0 = (size_t)geo.hg.first(g), f0 = h0 * D;
+        const unsigned grid = nodewise_grid(n_dst, geo.slots(g));
+        SAR_DISPATCH_NODE(dtype, geo, (k_fwd_end<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
+                                          m + h0, l + h0, acc + f0, static_cast<T*>(out) + f0, L + h0, n_dst,
+                                          geo.hg.count(g), D, H * D, H, act)));
         SAR_LAUNCH_CHECK();
     }
     return SAR_OK;
@@ -1361,7 +1572,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
     hipStream_t st = sar::as_stream(stream);
     const HeadGroups hg = head_groups(dtype, H, D);
     for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
+        const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         PtrTab zt{}, tt{};
         for (int q = 0; q < b->P; ++q) {
             zt.p[q] = shift(Zq[q], f0 * hg.fb);
@@ -1377,15 +1588,15 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.a_l = tq ? nullptr : a_l + f0;
         a.out = shift(out, f0 * hg.fb);
         a.L = L + h0;
-        a.H = hg.Hg;
+        a.H = hg.count(g);
         a.D = D;
-        a.F = hg.Fg;
+        a.F = a.H * D;
         a.ldz = H * D;
         a.ldh = H;
         a.tag_shift = b->tag_shift;
         a.slope = slope;
         a.act = act;
-        SAR_DISPATCH_ROW(dtype, hg.fast_fwd ? hg.full : hg.piece, SAR_TRY((launch_fwd<T, true>(a, zt, tt, b->P, st))));
+        SAR_TRY(launch_fwd<true>(dtype, a, zt, tt, b->P, st));
     }
     return SAR_OK;
 }
@@ -1409,19 +1620,18 @@ extern "C" int sar_gat_bwd_begin(const void* G, const void* out, const float* s,
     SAR_CHECK_ARG(G && out && s && L && rec && ds, "a tensor argument is null");
     SAR_CHECK_ARG(aligned16(G) && aligned16(out) && aligned16(rec), "G, out and rec must be 16-byte aligned");
     SAR_CHECK_ARG(act == SAR_ACT_NONE || (Gact && aligned16(Gact)), "a non-linearity needs Gact (16-byte aligned)");
-    const int F = H * D;
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const NodeGeo geo = node_geo(dtype, H, D);
     hipStream_t st = sar::as_stream(stream);
-    for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
-        const void* Gg = shift(G, f0 * hg.fb);
-        const void* og = shift(out, f0 * hg.fb);
+    for (int g = 0; g < geo.hg.n; ++g) {
+        const size_t h0 = (size_t)geo.hg.first(g), f0 = h0 * D;
+        const void* Gg = shift(G, f0 * geo.hg.fb);
+        const void* og = shift(out, f0 * geo.hg.fb);
         float4* recg = reinterpret_cast<float4*>(rec) + h0;
-        SAR_DISPATCH_ROW(dtype, hg.piece,
-                         SAR_DISPATCH_G(T, hg.Fg, (k_bwd_begin<T, kG><<<nodewise_grid(n_dst, kWave / kG), kGatherThreads, 0, st>>>(
-                                                      static_cast<const T*>(Gg), static_cast<const T*>(og), s + h0, L + h0,
-                                                      recg, ds + h0, n_dst, hg.Hg, D, hg.Fg, F, H, act,
-                                                      static_cast<T*>(shift(Gact, f0 * hg.fb))))));
+        const unsigned grid = nodewise_grid(n_dst, geo.slots(g));
+        SAR_DISPATCH_NODE(dtype, geo, (k_bwd_begin<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
+                                          static_cast<const T*>(Gg), static_cast<const T*>(og), s + h0, L + h0, recg,
+                                          ds + h0, n_dst, geo.hg.count(g), D, H * D, H, act,
+                                          static_cast<T*>(shift(Gact, f0 * geo.hg.fb)))));
         SAR_LAUNCH_CHECK();
     }
     return SAR_OK;
@@ -1450,15 +1660,15 @@ int bwd_common_checks(const sar_blocks_t* b, int dtype, int H, int D, const void
 void fill_bwd_group(BwdScalars& a, const HeadGroups& hg, int g, int H, int D, const void* G, const float* rec,
                     const float* a_l, float* ds, void* work, float slope)
 {
-    const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
+    const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
     a.G = shift(G, f0 * hg.fb);
     a.rec = reinterpret_cast<const float4*>(rec) + h0;
     a.a_l = a_l + f0;
     a.ds = ds + h0;
     a.partial = static_cast<float*>(work);
-    a.H = hg.Hg;
+    a.H = hg.count(g);
     a.D = D;
-    a.F = hg.Fg;
+    a.F = a.H * D;
     a.ldz = H * D;
     a.ldh = H;
     a.slope = slope;
@@ -1480,7 +1690,7 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     hipStream_t st = sar::as_stream(stream);
     const HeadGroups hg = head_groups(dtype, H, D);
     for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
+        const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         BwdArgs tabs{};
         tabs.t_indptr[0] = k.t_indptr;
         tabs.t_indices[0] = k.t_indices;
@@ -1499,7 +1709,7 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.n_src_host = &k.n_src;
         a.n_blocks = 1;
         fill_bwd_group(a, hg, g, H, D, G, rec, a_l, ds, work, slope);
-        SAR_DISPATCH_ROW(dtype, hg.fast_bwd ? hg.full : hg.piece, SAR_TRY((launch_bwd<T, false>(tabs, a, da_l + f0, st))));
+        SAR_TRY(launch_bwd<false>(dtype, tabs, a, da_l + f0, st));
     }
     return SAR_OK;
 }
@@ -1524,7 +1734,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
     int64_t n_src_all[SAR_MAX_BLOCKS];
     for (int q = 0; q < b->P; ++q) n_src_all[q] = b->blk[q].n_src;
     for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
+        const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         BwdArgs tabs{};
         for (int q = 0; q < b->P; ++q) {
             const sar::Block& k = b->blk[q];
@@ -1553,7 +1763,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.n_long = b->n_ft_long;
         a.tag_shift = b->tag_shift;
         fill_bwd_group(a, hg, g, H, D, G, rec, a_l, ds, work, slope);
-        SAR_DISPATCH_ROW(dtype, hg.fast_bwd ? hg.full : hg.piece, SAR_TRY((launch_bwd<T, true>(tabs, a, da_l + f0, st))));
+        SAR_TRY(launch_bwd<true>(dtype, tabs, a, da_l + f0, st));
     }
     return SAR_OK;
 }
@@ -1588,29 +1798,25 @@ int scratch_of(float** out)
     return SAR_OK;
 }
 
-// partial: room for one row of hg.Fg sums per workgroup; partial_floats = its size in values.
+// partial: room for one row of sums (the launch's heads) per workgroup; partial_floats = its size in values.
 int bwd_end_impl(const void* Zdst, const float* ds, const float* a_r, const void* dZadd,
                  const int32_t* dZadd_rank, void* dZdst, float* da_r, int dtype, int64_t n_dst, int H, int D, float* partial, size_t partial_floats,
                  hipStream_t st)
 {
-    const int F = H * D;
-    const HeadGroups hg = head_groups(dtype, H, D);
-    for (int g = 0; g < hg.n; ++g) {
-        const size_t f0 = (size_t)g * hg.Fg, h0 = (size_t)g * hg.Hg;
-        unsigned grid = 1;
-        const int slots = kWave / lanes_for(hg.Fg, hg.piece);
-        grid = nodewise_grid(n_dst, slots);
-        if ((size_t)grid * hg.Fg > partial_floats)
+    const NodeGeo geo = node_geo(dtype, H, D);
+    for (int g = 0; g < geo.hg.n; ++g) {
+        const int Hg = geo.hg.count(g), Fg = Hg * D;
+        const size_t h0 = (size_t)geo.hg.first(g), f0 = h0 * D;
+        const unsigned grid = nodewise_grid(n_dst, geo.slots(g));
+        if ((size_t)grid * Fg > partial_floats)
             return sar::fail(SAR_ERR_UNSUPPORTED, "%u workgroups x %d partial sums exceed the %zu values of scratch",
-                             grid, hg.Fg, partial_floats);
-        SAR_DISPATCH_ROW(dtype, hg.piece,
-                         SAR_DISPATCH_G(T, hg.Fg, (k_bwd_end<T, kG><<<grid, kGatherThreads, 0, st>>>(
-                                                      static_cast<const T*>(Zdst) + f0, ds + h0, a_r + f0,
-                                                      dZadd ? static_cast<const T*>(dZadd) + f0 : nullptr, dZadd_rank,
-                                                      dZdst ? static_cast<T*>(dZdst) + f0 : nullptr, partial, n_dst,
-                                                      hg.Hg, D, hg.Fg, F, H))));
+                             grid, Fg, partial_floats);
+        SAR_DISPATCH_NODE(dtype, geo, (k_bwd_end<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
+                                          static_cast<const T*>(Zdst) + f0, ds + h0, a_r + f0,
+                                          dZadd ? static_cast<const T*>(dZadd) + f0 : nullptr, dZadd_rank,
+                                          dZdst ? static_cast<T*>(dZdst) + f0 : nullptr, partial, n_dst, Hg, D, H * D, H)));
         SAR_LAUNCH_CHECK();
-        k_reduce_partials<<<hg.Fg, 256, 0, st>>>(partial, (int)grid, hg.Fg, da_r + f0);
+        k_reduce_partials<<<Fg, 256, 0, st>>>(partial, (int)grid, Fg, da_r + f0);
         SAR_LAUNCH_CHECK();
     }
     return SAR_OK;

@@ -17,7 +17,9 @@
 // lanes [h*LPH, (h+1)*LPH), lane k of it owns features h*D + 4k.. while 4k < D
 // and is idle otherwise (it still takes its turn at the per-edge scalars).  That
 // brings head widths such as 100 and rows wider than one wavefront (several
-// launches over groups of heads) onto these kernels.
+// launches over groups of heads) onto these kernels.  Layers whose heads leave
+// half of the lanes or more, and head widths that are no multiple of 4, have
+// kernels of their own (gat_slots.h).
 #pragma once
 
 #include <type_traits>
@@ -173,6 +175,37 @@ struct Row4<bf16_t> {
         reinterpret_cast<uint2*>(row)[lane] = r;
     }
 };
+
+// Accesses of 4 values at any value's alignment (gfx950 takes unaligned vector accesses).
+struct __attribute__((packed, aligned(4))) F32x4Any {
+    float x, y, z, w;
+};
+struct __attribute__((packed, aligned(2))) Bf16x4Any {
+    uint32_t x, y;
+};
+template <typename T, bool ANY>
+__device__ inline typename Row4<T>::Raw load_raw(const T* p)
+{
+    if constexpr (!ANY) {
+        return *reinterpret_cast<const typename Row4<T>::Raw*>(p);
+    } else if constexpr (sizeof(T) == 4) {
+        const F32x4Any r = *reinterpret_cast<const F32x4Any*>(p);
+        return make_float4(r.x, r.y, r.z, r.w);
+    } else {
+        const Bf16x4Any r = *reinterpret_cast<const Bf16x4Any*>(p);
+        return make_uint2(r.x, r.y);
+    }
+}
+template <typename T, bool ANY>
+__device__ inline void store4(T* p, const float (&v)[4])
+{
+    if constexpr (!ANY)
+        Row4<T>::store(p, 0, v);
+    else if constexpr (sizeof(T) == 4)
+        *reinterpret_cast<F32x4Any*>(p) = F32x4Any{v[0], v[1], v[2], v[3]};
+    else
+        *reinterpret_cast<Bf16x4Any*>(p) = Bf16x4Any{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+}
 
 // The lane's 4 values of a row (zeros for an idle lane of the padded geometry).
 template <typename T, bool PAD>

@@ -1,0 +1,599 @@
+// Attention kernels for layers whose heads leave room in a wavefront: narrow layers (one head of
+// 47 values, 4 heads of 16, 4 of 32 ...) and layers whose head width is no multiple of 4.
+//
+// A head is covered by LPH lanes of 4 values (the power of two >= D/4), as in the padded geometry
+// of gat_f256.h, and the 64/LPH lane groups of a wavefront that the heads do not need are not left
+// idle: they form further SLOTS, group g speaking for head g % H of slot g / H.  In the forward
+// kernel and in the backward kernel for sources of 8 and more edges the slots take different edges
+// of the same row (each with its own running softmax, merged at the end of the row); in the
+// backward kernel for the other sources every slot takes a source of its own.  A row of 188 bytes
+// then costs a quarter of a wave-wide load instead of a whole one.
+//
+// Head widths that are no multiple of 4 (template flag RAG): the last lane of a head takes the LAST
+// four values of the head instead of a piece that would end behind it, so every access is one
+// (unaligned) 16- or 8-byte access inside the row.  The values it shares with the lane before it
+// are left out of its dot products; where it accumulates or stores them it has the same bits as
+// that lane.
+//
+// What bounds them: the bytes of the gathered rows (whole cache lines: a 188-byte row touches
+// four 64-byte sectors), like the kernels of gat_f256.h.  Measured on a worker's share of 7.4M edges, 1 x 47 fp32:
+// the kernels these replace moved one value per lane and reduced a head of 47 lanes by 47
+// shuffles per edge: forward 5.77 ms, backward 6.56 ms.
+#pragma once
+
+#include "gat_f256.h"
+
+namespace sar {
+namespace slots {
+
+using f256::BwdAcc4;
+using f256::BwdP;
+using f256::BwdTabs;
+using f256::FwdP;
+using f256::group_all;
+using f256::group_bcast;
+using f256::leaky2;
+using f256::OpMax;
+using f256::OpSum;
+using f256::Row4;
+using f256::static_for;
+using f256::Tabs;
+
+// Edges of one row (or of one source) a lane group has in flight.
+template <int LPH>
+constexpr int kBatch = LPH >= 8 ? 8 : 4;
+
+// Where this lane stands.
+template <int LPH, bool RAG>
+struct Place {
+    int lane, k_pos;   // lane of the wavefront, lane of the head group
+    int slot, h;       // slot and head of the lane group
+    bool live;         // the group has a slot (64/LPH need not be a multiple of H)
+    bool on;           // the lane carries values
+    int foff;          // first of the lane's 4 values inside the launch's row
+    int dup;           // how many of them the lane before it carries as well (RAG only)
+    __device__ inline Place(int H, int D, int n_slots)
+    {
+        lane = threadIdx.x & (kWave - 1);
+        k_pos = lane % LPH;
+        const int grp = lane / LPH;
+        slot = grp / H;
+        h = grp - slot * H;
+        live = slot < n_slots;
+        on = live && 4 * k_pos < D;
+        const int off = RAG ? min(4 * k_pos, D - 4) : 4 * k_pos;
+        dup = (RAG && on) ? 4 * k_pos - off : 0;
+        foff = h * D + off;
+    }
+    // v without the values the lane before it carries as well
+    __device__ inline void own_only(float (&v)[4]) const
+    {
+        if constexpr (RAG) {
+#pragma unroll
+            for (int x = 0; x < 3; ++x) v[x] = x >= dup ? v[x] : 0.f;
+        }
+    }
+};
+
+using f256::load_raw;
+using f256::store4;
+template <bool ANY>
+__device__ inline void load4_f32(const float* p, float (&v)[4])
+{
+    Row4<float>::unpack(load_raw<float, ANY>(p), v);
+}
+
+// Value of lane K of the caller's head group.
+template <int LPH, int K>
+__device__ inline int bcast_i(int v)
+{
+    return __float_as_int(group_bcast<LPH, K>(__int_as_float(v)));
+}
+
+// Adds the slots' values to slot 0 (n_slots a power of two; the other slots are left with junk).
+__device__ inline float sum_slots(float v, int lane, int n_slots, int width)
+{
+    for (int o = n_slots >> 1; o > 0; o >>= 1) v += __shfl(v, lane + o * width);
+    return v;
+}
+
+// ------------------------------------------------------------------ forward
+
+struct State {
+    float m2, l, acc[4];   // running maximum (log2 units), this lane's share of the denominator, numerator
+};
+
+template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
+__device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_Z, const float* const* s_t,
+                                 uint32_t mine, int cnt, int n_slots, const Place<LPH, RAG>& p, float s2,
+                                 const float (&al)[4])
+{
+    constexpr int B = kBatch<LPH>;
+    const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {
+        typename Row4<T>::Raw raw[B];
+        static_for<B>([&](auto kk) {
+            constexpr int K = decltype(kk)::value;
+            raw[K] = typename Row4<T>::Raw{};
+            if (k0 + K * n_slots < cnt) {          // uniform: some slot has an edge here
+                const uint32_t id = (uint32_t)__shfl((int)mine, min(k0 + K * n_slots + p.slot, cnt - 1));
+                const T* zb = static_cast<const T*>(ALL ? s_Z[id >> a.tag_shift] : a.Z);
+                if (p.on) raw[K] = load_raw<T, RAG>(zb + (int64_t)(id & mask) * a.ld + p.foff);
+            }
+        });
+        // lane k of a head group speaks for the k-th edge of its slot
+        const int my_e = k0 + p.k_pos * n_slots + p.slot;
+        const bool valid = p.live && p.k_pos < B && my_e < cnt;
+        float tv = 0.f;
+        if constexpr (FLY) {
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                float v[4];
+                Row4<T>::unpack(raw[K], v);
+                float c = al[0] * v[0];
+#pragma unroll
+                for (int x = 1; x < 4; ++x) c = fmaf(al[x], v[x], c);
+                c = group_all<LPH, OpSum>(c);
+                tv = (p.k_pos == K) ? c : tv;
+            });
+        } else {
+            const uint32_t my = (uint32_t)__shfl((int)mine, valid ? my_e : 0);
+            const float* tb = ALL ? s_t[my >> a.tag_shift] : a.t;
+            tv = tb[(int64_t)(my & mask) * a.ldh + p.h];
+        }
+        const float e2 = valid ? leaky2(fmaf(tv, kLog2e, s2), a.slope) : -INFINITY;
+        const float cmax = group_all<LPH, OpMax>(e2);
+        if (__builtin_amdgcn_ballot_w64(cmax > st.m2)) {
+            const float mn = fmaxf(st.m2, cmax);
+            const float c = fast_exp2(st.m2 - (mn == -INFINITY ? 0.f : mn));   // no edge yet: exp2(-inf) = 0
+            st.l *= c;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) st.acc[x] *= c;
+            st.m2 = mn;
+        }
+        const float pe = fast_exp2(e2 - (st.m2 == -INFINITY ? 0.f : st.m2));   // 0 for the lanes without an edge
+        st.l += pe;
+        static_for<B>([&](auto kk) {
+            constexpr int K = decltype(kk)::value;
+            const float pk = group_bcast<LPH, K>(pe);
+            float v[4];
+            Row4<T>::unpack(raw[K], v);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) st.acc[x] = fmaf(pk, v[x], st.acc[x]);
+        });
+    }
+}
+
+__device__ inline void merge_into(State& st, float om, float ol, const float (&oacc)[4])
+{
+    const float mn = fmaxf(st.m2, om), ref = (mn == -INFINITY) ? 0.f : mn;
+    const float ca = fast_exp2(st.m2 - ref), cb = fast_exp2(om - ref);
+    st.l = st.l * ca + ol * cb;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) st.acc[x] = st.acc[x] * ca + oacc[x] * cb;
+    st.m2 = mn;
+}
+
+template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_slots(FwdP a, Tabs tabs, int n_slots)
+{
+    __shared__ float part[kWavesPerWG][kWave][6];
+    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
+    __shared__ const float* s_t[SAR_MAX_BLOCKS];
+    if constexpr (ALL) {
+        if (threadIdx.x < SAR_MAX_BLOCKS) {
+            s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
+            s_t[threadIdx.x] = tabs.t[threadIdx.x];
+        }
+        __syncthreads();
+    }
+    const Place<LPH, RAG> p(a.H, a.D, n_slots);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int width = a.H * LPH;                       // lanes of a slot
+    const bool first = p.slot == 0;
+    T* outp = static_cast<T*>(a.out);
+    float al[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (FLY) {
+        if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
+        p.own_only(al);
+    }
+    auto init = [&](State& st, int i, bool carry) {
+        st.m2 = -INFINITY;
+        st.l = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) st.acc[x] = 0.f;
+        if constexpr (!ALL) {
+            if (carry && first) {   // the state carried from the blocks already aggregated enters through slot 0
+                st.m2 = a.m[(int64_t)i * a.ldh + p.h] * kLog2e;
+                st.l = (p.k_pos == 0) ? a.l[(int64_t)i * a.ldh + p.h] : 0.f;
+                if (p.on) load4_f32<RAG>(a.acc + (int64_t)i * a.ld + p.foff, st.acc);
+            }
+        }
+    };
+    auto edges = [&](State& st, int i, int chunk0, int stride) {
+        const float s2 = a.s[(int64_t)i * a.ldh + p.h] * kLog2e;
+        const int beg = a.indptr[i], end = a.indptr[i + 1];
+        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+            const int cnt = min(kWave, end - cb);
+            const uint32_t mine = (p.lane < cnt) ? a.indices[cb + p.lane] : 0u;
+            fwd_chunk<T, LPH, ALL, FLY, RAG>(st, a, s_Z, s_t, mine, cnt, n_slots, p, s2, al);
+        }
+        // one state per head out of the slots' states; the denominator becomes the group's total
+        st.l = group_all<LPH, OpSum>(st.l);
+        for (int o = n_slots >> 1; o > 0; o >>= 1) {
+            const int from = p.lane + o * width;
+            const float om = __shfl(st.m2, from), ol = __shfl(st.l, from);
+            float oacc[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) oacc[x] = __shfl(st.acc[x], from);
+            merge_into(st, om, ol, oacc);
+        }
+    };
+    auto finish = [&](const State& st, int i) {
+        if (!first || !p.live) return;
+        const float l = st.l;
+        if constexpr (ALL) {
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            float v[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                v[x] = st.acc[x] * inv;
+                if (a.act == SAR_ACT_RELU) v[x] = fmaxf(v[x], 0.f);
+            }
+            if (p.on) store4<T, RAG>(outp + (int64_t)i * a.ld + p.foff, v);
+            if (p.k_pos == 0) a.L[(int64_t)i * a.ldh + p.h] = l > 0.f ? (st.m2 + fast_log2(l)) * kLn2 : -INFINITY;
+        } else {
+            if (p.on) store4<float, RAG>(a.acc + (int64_t)i * a.ld + p.foff, st.acc);
+            if (p.k_pos == 0) {
+                a.m[(int64_t)i * a.ldh + p.h] = st.m2 * kLn2;
+                a.l[(int64_t)i * a.ldh + p.h] = l;
+            }
+        }
+    };
+
+    // the long rows at the head of the list: the four wavefronts share the row
+    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+        const int i = (int)a.rows[r];
+        State st;
+        init(st, i, wave == 0);
+        edges(st, i, wave, kWavesPerWG);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) part[wave][p.lane][x] = st.acc[x];
+        part[wave][p.lane][4] = st.m2;
+        part[wave][p.lane][5] = st.l;
+        __syncthreads();
+        if (wave == 0) {
+            for (int w = 1; w < kWavesPerWG; ++w) {
+                float oacc[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) oacc[x] = part[w][p.lane][x];
+                merge_into(st, part[w][p.lane][4], part[w][p.lane][5], oacc);
+            }
+            finish(st, i);
+        }
+        __syncthreads();
+    }
+    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
+    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+        const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
+        State st;
+        init(st, i, true);
+        edges(st, i, 0, 1);
+        finish(st, i);
+    }
+}
+
+// ----------------------------------------------------------------- backward
+
+// This workgroup's share of da_l = sum_j dt_j z_j, one row of 256 lane values per workgroup.
+template <int LPH, bool RAG>
+__device__ inline void store_partial(float (&dal)[4], float (*part)[kWave][4], const Place<LPH, RAG>& p, int wave,
+                                     int n_slots, int width, float* row)
+{
+#pragma unroll
+    for (int x = 0; x < 4; ++x) part[wave][p.lane][x] = sum_slots(dal[x], p.lane, n_slots, width);
+    __syncthreads();
+    if (wave == 0) {
+        float v[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            float s = 0.f;
+            for (int w = 0; w < kWavesPerWG; ++w) s += part[w][p.lane][x];
+            v[x] = s;
+        }
+        store_f32<4>(row + p.lane * 4, v);
+    }
+}
+
+// Sources of at least 8 edges: one wavefront each (a workgroup for the long ones), its slots taking
+// different edges.
+template <typename T, int LPH, bool ALL, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, BwdP a, int n_slots)
+{
+    constexpr int B = kBatch<LPH>;
+    __shared__ float part[kWavesPerWG][kWave][4];
+    __shared__ float part_dt[kWavesPerWG][kWave];
+    const Place<LPH, RAG> p(a.H, a.D, n_slots);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int width = a.H * LPH;
+    const bool first = p.slot == 0;
+    const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    const T* Gp = static_cast<const T*>(a.G);
+    float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
+    if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) dal[x] = 0.f;
+
+    auto edges = [&](BwdAcc4& ac, int q, int j, int chunk0, int stride, float (&zj)[4]) {
+        typename Row4<T>::Raw zr{};
+        if (p.on) zr = load_raw<T, RAG>(static_cast<const T*>(tabs.Z[q]) + (int64_t)j * a.ld + p.foff);
+        Row4<T>::unpack(zr, zj);
+        p.own_only(zj);
+        float t2;
+        if (tabs.t[q]) {
+            t2 = tabs.t[q][(int64_t)j * a.ldh + p.h] * kLog2e;
+        } else {   // t_j = <a_l, z_j>
+            float c = al[0] * zj[0];
+#pragma unroll
+            for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
+            t2 = group_all<LPH, OpSum>(c) * kLog2e;
+        }
+        const int32_t* idx = tabs.t_indices[q];
+        const int beg = tabs.t_indptr[q][j], end = tabs.t_indptr[q][j + 1];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) ac.dz[x] = 0.f;
+        ac.dt = 0.f;
+        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+            const int cnt = min(kWave, end - cb);
+            const int mine = (p.lane < cnt) ? idx[cb + p.lane] : 0;
+            for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {
+                typename Row4<T>::Raw raw[B];
+                static_for<B>([&](auto kk) {
+                    constexpr int K = decltype(kk)::value;
+                    raw[K] = typename Row4<T>::Raw{};
+                    if (k0 + K * n_slots < cnt) {
+                        const int i = __shfl(mine, min(k0 + K * n_slots + p.slot, cnt - 1));
+                        if (p.on) raw[K] = load_raw<T, RAG>(Gp + (int64_t)i * a.ld + p.foff);
+                    }
+                });
+                const int my_e = k0 + p.k_pos * n_slots + p.slot;
+                const bool valid = p.live && p.k_pos < B && my_e < cnt;
+                const int my_i = __shfl(mine, valid ? my_e : 0);
+                const float4 rec = a.rec[(int64_t)my_i * a.ldh + p.h];
+                float c_mine = 0.f;
+                static_for<B>([&](auto kk) {
+                    constexpr int K = decltype(kk)::value;
+                    float g[4];
+                    Row4<T>::unpack(raw[K], g);
+                    float c = g[0] * zj[0];
+#pragma unroll
+                    for (int x = 1; x < 4; ++x) c = fmaf(g[x], zj[x], c);
+                    c = group_all<LPH, OpSum>(c);
+                    c_mine = (p.k_pos == K) ? c : c_mine;
+                });
+                const float u2 = rec.x + t2;
+                const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
+                const float de = alpha * (c_mine - rec.z);
+                const float du = u2 > 0.f ? de : a.slope * de;
+                ac.dt += du;
+                if (valid) unsafeAtomicAdd(a.ds + (int64_t)my_i * a.ldh + p.h, du);
+                static_for<B>([&](auto kk) {
+                    constexpr int K = decltype(kk)::value;
+                    const float ak = group_bcast<LPH, K>(alpha);
+                    float g[4];
+                    Row4<T>::unpack(raw[K], g);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) ac.dz[x] = fmaf(ak, g[x], ac.dz[x]);
+                });
+            }
+        }
+        ac.dt = sum_slots(group_all<LPH, OpSum>(ac.dt), p.lane, n_slots, width);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) ac.dz[x] = sum_slots(ac.dz[x], p.lane, n_slots, width);
+    };
+    // dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j (slot 0 holds the sums)
+    auto outputs = [&](const BwdAcc4& ac, int q, int j, const float (&zj)[4]) {
+        if (!first || !p.live) return;
+        float v[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            v[x] = fmaf(ac.dt, al[x], ac.dz[x]);
+            dal[x] = fmaf(ac.dt, zj[x], dal[x]);
+        }
+        const int64_t jo = tabs.rank[q] ? tabs.rank[q][j] : j;
+        if (p.on) store4<T, RAG>(static_cast<T*>(tabs.dZ[q]) + jo * a.ld + p.foff, v);
+        if (p.k_pos == 0 && tabs.dt[q]) tabs.dt[q][jo * a.ldh + p.h] = ac.dt;
+    };
+
+    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+        const uint32_t id = a.rows[r];
+        const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
+        BwdAcc4 ac;
+        float zj[4];
+        edges(ac, q, j, wave, kWavesPerWG, zj);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) part[wave][p.lane][x] = ac.dz[x];
+        part_dt[wave][p.lane] = ac.dt;
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                float s = 0.f;
+                for (int w = 0; w < kWavesPerWG; ++w) s += part[w][p.lane][x];
+                ac.dz[x] = s;
+            }
+            float s = 0.f;
+            for (int w = 0; w < kWavesPerWG; ++w) s += part_dt[w][p.lane];
+            ac.dt = s;
+            outputs(ac, q, j, zj);
+        }
+        __syncthreads();
+    }
+    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
+    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+        const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.rows[r]);
+        const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
+        BwdAcc4 ac;
+        float zj[4];
+        edges(ac, q, j, 0, 1, zj);
+        outputs(ac, q, j, zj);
+    }
+    __syncthreads();
+    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width, a.partial + (int64_t)blockIdx.x * f256::kF);
+}
+
+// The other sources of the list (fewer than 8 edges, or none): every slot takes a source of its
+// own, lane k of each of its head groups speaking for the source's edge k, so a source is one
+// round of gathers (two of four where a head has only four lanes).  List entries are read three
+// rounds ahead, ranges and output rows two, destinations one.
+template <typename T, int LPH, bool ALL, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs tabs, BwdP a, int64_t r_begin,
+                                                                      int64_t r_end, int partial_row0, int n_slots)
+{
+    constexpr int B = kBatch<LPH>;
+    constexpr int kMost = 1 << kNarrowMaxClass;          // this kernel's sources have fewer edges
+    constexpr int kRounds = (kMost - 1 + B - 1) / B;
+    __shared__ float part[kWavesPerWG][kWave][4];
+    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
+    __shared__ const float* s_t[SAR_MAX_BLOCKS];
+    __shared__ void* s_dZ[SAR_MAX_BLOCKS];
+    __shared__ float* s_dt[SAR_MAX_BLOCKS];
+    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
+    __shared__ const int32_t* s_ix[SAR_MAX_BLOCKS];
+    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    if (threadIdx.x < SAR_MAX_BLOCKS) {
+        s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
+        s_t[threadIdx.x] = tabs.t[threadIdx.x];
+        s_dZ[threadIdx.x] = tabs.dZ[threadIdx.x];
+        s_dt[threadIdx.x] = tabs.dt[threadIdx.x];
+        s_ip[threadIdx.x] = tabs.t_indptr[threadIdx.x];
+        s_ix[threadIdx.x] = tabs.t_indices[threadIdx.x];
+        s_rank[threadIdx.x] = tabs.rank[threadIdx.x];
+    }
+    __syncthreads();
+    const Place<LPH, RAG> p(a.H, a.D, n_slots);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int width = a.H * LPH;
+    const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    const T* Gp = static_cast<const T*>(a.G);
+    float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
+    if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) dal[x] = 0.f;
+
+    struct Meta { int q, j, beg, cnt, jo; };
+    struct Dst { int i[kRounds]; };
+    const int64_t stride = (int64_t)gridDim.x * kWavesPerWG * n_slots;
+    const int64_t w0 = r_begin + ((int64_t)blockIdx.x * kWavesPerWG + wave) * n_slots;   // slot 0's list position
+    auto have = [&](int64_t w) { return p.live && w + p.slot < r_end; };
+    auto load_id = [&](int64_t w) -> uint32_t { return have(w) ? a.rows[w + p.slot] : 0u; };
+    auto load_meta = [&](uint32_t id, int64_t w) {
+        Meta m{0, 0, 0, 0, 0};
+        if (have(w)) {
+            m.q = ALL ? (int)(id >> a.tag_shift) : 0;
+            m.j = (int)(id & mask);
+            const int32_t* ip = s_ip[m.q];
+            m.beg = ip[m.j];
+            m.cnt = ip[m.j + 1] - m.beg;
+            m.jo = s_rank[m.q] ? s_rank[m.q][m.j] : m.j;
+        }
+        return m;
+    };
+    auto load_dst = [&](const Meta& m) {
+        Dst d;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int e = r * B + p.k_pos;
+            d.i[r] = (p.k_pos < B && e < m.cnt) ? s_ix[m.q][m.beg + e] : 0;
+        }
+        return d;
+    };
+    uint32_t id2 = load_id(w0 + 2 * stride);
+    Meta m0 = load_meta(load_id(w0), w0), m1 = load_meta(load_id(w0 + stride), w0 + stride);
+    Dst d0 = load_dst(m0);
+
+    for (int64_t w = w0; w < r_end; w += stride) {
+        const Dst d1 = load_dst(m1);
+        const Meta m2 = load_meta(id2, w + 2 * stride);
+        const uint32_t id3 = load_id(w + 3 * stride);
+        const bool mine = have(w);
+        float zj[4];
+        {
+            typename Row4<T>::Raw zr{};
+            if (mine && p.on) zr = load_raw<T, RAG>(static_cast<const T*>(s_Z[m0.q]) + (int64_t)m0.j * a.ld + p.foff);
+            Row4<T>::unpack(zr, zj);
+            p.own_only(zj);
+        }
+        float dz[4] = {0.f, 0.f, 0.f, 0.f}, dt = 0.f, t2 = 0.f;
+        bool have_t = false;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            if (__builtin_amdgcn_ballot_w64(m0.cnt > r * B) == 0) break;
+            typename Row4<T>::Raw raw[B];
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                raw[K] = typename Row4<T>::Raw{};
+                const int i = bcast_i<LPH, K>(d0.i[r]);
+                if (p.on && r * B + K < m0.cnt) raw[K] = load_raw<T, RAG>(Gp + (int64_t)i * a.ld + p.foff);
+            });
+            const bool valid = p.live && p.k_pos < B && r * B + p.k_pos < m0.cnt;
+            const int my_i = d0.i[r];
+            float4 rec = make_float4(0.f, INFINITY, 0.f, 0.f);   // L = +inf gives alpha = 0
+            if (valid) rec = a.rec[(int64_t)my_i * a.ldh + p.h];
+            if (!have_t) {
+                have_t = true;
+                float c = al[0] * zj[0];
+#pragma unroll
+                for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
+                c = group_all<LPH, OpSum>(c);
+                if (mine && s_t[m0.q]) c = s_t[m0.q][(int64_t)m0.j * a.ldh + p.h];
+                t2 = c * kLog2e;
+            }
+            float c_mine = 0.f;
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                float g[4];
+                Row4<T>::unpack(raw[K], g);
+                float c = g[0] * zj[0];
+#pragma unroll
+                for (int x = 1; x < 4; ++x) c = fmaf(g[x], zj[x], c);
+                c = group_all<LPH, OpSum>(c);
+                c_mine = (p.k_pos == K) ? c : c_mine;
+            });
+            const float u2 = rec.x + t2;
+            const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
+            const float de = alpha * (c_mine - rec.z);
+            const float du = u2 > 0.f ? de : a.slope * de;
+            dt += du;
+            if (valid) unsafeAtomicAdd(a.ds + (int64_t)my_i * a.ldh + p.h, du);
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                const float ak = group_bcast<LPH, K>(alpha);
+                float g[4];
+                Row4<T>::unpack(raw[K], g);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) dz[x] = fmaf(ak, g[x], dz[x]);
+            });
+        }
+        dt = group_all<LPH, OpSum>(dt);
+        if (mine) {
+            float v[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                v[x] = fmaf(dt, al[x], dz[x]);
+                dal[x] = fmaf(dt, zj[x], dal[x]);
+            }
+            if (p.on) store4<T, RAG>(static_cast<T*>(s_dZ[m0.q]) + (int64_t)m0.jo * a.ld + p.foff, v);
+            if (p.k_pos == 0 && s_dt[m0.q]) s_dt[m0.q][(int64_t)m0.jo * a.ldh + p.h] = dt;
+        }
+        m0 = m1;
+        d0 = d1;
+        m1 = m2;
+        id2 = id3;
+    }
+    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width,
+                            a.partial + ((int64_t)partial_row0 + blockIdx.x) * f256::kF);
+}
+
+}  // namespace slots
+}  // namespace sar

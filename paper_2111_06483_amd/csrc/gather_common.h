@@ -316,19 +316,6 @@ inline int piece_for(int dtype_is_f32, int w)
         }                                                    \
     } while (0)
 
-template <typename T>
-struct is_full_row {
-    static constexpr bool value = false;
-};
-template <>
-struct is_full_row<float> {
-    static constexpr bool value = true;
-};
-template <>
-struct is_full_row<bf16_t> {
-    static constexpr bool value = true;
-};
-
 inline int lanes_for(int F, int vec)
 {
     int need = (F + vec - 1) / vec, g = 4;
