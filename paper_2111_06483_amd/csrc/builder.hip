@@ -695,6 +695,8 @@ int derive(sar_blocks* h, hipStream_t st)
         h->blk[q].n_rows = L.n_rows;
         h->blk[q].n_long = L.n_long;
         h->blk[q].n_rows_wide = L.n_wide;
+        for (int c = 1; c < sar::kNumClasses; ++c)
+            if (hist[q * sar::kNumClasses + c]) h->blk[q].hub = (int64_t)1 << (c - 1);
         memcpy(&cursors[q * sar::kNumClasses], L.start, sizeof(L.start));
         rows_base[q] = rows_total;
         rows_total += L.n_rows;

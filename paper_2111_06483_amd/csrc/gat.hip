@@ -318,7 +318,9 @@ struct BwdScalars {
     const void* G;              // [n_dst,H,D]
     const float4* rec;          // [n_dst,H]: (s*log2e, L*log2e, delta, unused)
     const float* a_l;           // [H,D]
-    float* ds;                  // [n_dst,H], atomically accumulated
+    float* ds;                  // [n_dst,H], atomically accumulated: the array or the first of ds_copies copies
+    int64_t ds_stride;          // values between copies
+    int ds_copies;              // a power of two
     float* partial;             // [gridDim.x][F] per-workgroup da_l partial sums
     int H, D, F;
     int ldz, ldh;               // node strides of feature rows / per-head arrays
@@ -402,6 +404,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd(BwdArgs tabs, BwdSca
     const int wave = threadIdx.x / kWave;
     const bool pow2 = is_pow2(lm.lph);
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    a.ds += (int64_t)(blockIdx.x & (unsigned)(a.ds_copies - 1)) * a.ds_stride;
 
     float al[VEC], dal[VEC];
 #pragma unroll
@@ -846,9 +849,15 @@ int pow2_at_least(int x)
 //           bound by memory, not by lanes, so they cost little;
 //   slots   they need half of the groups or fewer, or the head width is no multiple of 4, or a head
 //           is four lanes (gat_slots.h): the groups left over take other edges.
-//   generic heads of 1 to 3 values and bf16 heads of more than 256.
-// Measured on shares of the products-sized graph, padded -> slots, forward and backward kernels
-// together where half of the lane groups were idle: see gat_slots.h.
+//   generic heads of 1 to 3 values, bf16 heads of more than 256, and in the forward pass heads of 4 or 8
+//           values (one or two lanes of 16 bytes: 8 x 8 bf16 229 us against 391 with the four lanes of a
+//           slots head; the slots' batches pay again in the backward pass, 703 us against 834) and bf16
+//           layers whose heads would fall into launches of different sizes (5 x 40 as 3 + 2: 965 us
+//           against 819 in one generic launch).
+// In the forward pass the padded kernel also takes launches that leave up to 5/8 of the lanes idle:
+// it waits for memory there either way (4 x 32 fp32 on 7.4M edges: 603 us padded, 608 us with two
+// slots), while the backward pass gains from the slots (4 x 32: 1.9 and 6.5% of the whole step in
+// fp32 and bf16).
 enum class Gather { kGeneric, kExact, kPadded, kSlots };
 struct LaunchGeo {
     Gather kind;
@@ -856,14 +865,30 @@ struct LaunchGeo {
     bool ragged;
 };
 
-LaunchGeo launch_geo(int Hg, int D, int ldz)
+// Heads of width D a wavefront of the slots kernels (and of the padded ones) has lane groups for.
+int lane_groups(int D) { return 64 / std::max(4, pow2_at_least((D + 3) / 4)); }
+
+bool generic_layer(int dtype, int H, int D, bool forward)
 {
-    if (D < 4 || D > 256) return LaunchGeo{Gather::kGeneric, 0, 0, false};
+    if (D < 4 || D > 256) return true;
+    if (!forward) return false;
+    if (D == 4 || D == 8) return true;
+    const int n = (H + lane_groups(D) - 1) / lane_groups(D);
+    return dtype == SAR_BF16 && D % 8 == 0 && H % n != 0 && H * D <= 512;
+}
+
+LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, bool forward)
+{
+    if (generic_layer(dtype, ldz / D, D, forward)) return LaunchGeo{Gather::kGeneric, 0, 0, false};
     const int lph = std::max(4, pow2_at_least((D + 3) / 4)), groups = 64 / lph;
     if (Hg * lph == 64 && D == 4 * lph && ldz == f256::kF) return LaunchGeo{Gather::kExact, lph, 1, false};
     int slots = 1;
     while (slots * 2 * Hg <= groups) slots *= 2;
-    if (slots == 1 && lph >= 8 && D % 4 == 0) return LaunchGeo{Gather::kPadded, lph, 1, false};
+    if (D % 4 == 0) {
+        const int padded = std::max(8, lph);
+        if (slots == 1 && lph >= 8) return LaunchGeo{Gather::kPadded, lph, 1, false};
+        if (forward && Hg * padded <= 64 && Hg * (D / 4) * 8 >= 3 * 64) return LaunchGeo{Gather::kPadded, padded, 1, false};
+    }
     return LaunchGeo{Gather::kSlots, lph, slots, D % 4 != 0};
 }
 
@@ -877,13 +902,13 @@ struct HeadGroups {
     int count(int g) const { return std::min(most, H - g * most); }
 };
 
-HeadGroups head_groups(int dtype, int H, int D)
+HeadGroups head_groups(int dtype, int H, int D, bool forward)
 {
     HeadGroups g;
     g.H = H;
     g.fb = dtype == SAR_F32 ? 4 : 2;
-    const int groups = (D < 4 || D > 256) ? std::max(1, 64 * piece_for(dtype == SAR_F32, D) / D)
-                                          : 64 / std::max(4, pow2_at_least((D + 3) / 4));
+    const int groups = generic_layer(dtype, H, D, forward) ? std::max(1, 64 * piece_for(dtype == SAR_F32, D) / D)
+                                                           : lane_groups(D);
     g.n = (H + groups - 1) / groups;
     g.most = (H + g.n - 1) / g.n;
     g.n = (H + g.most - 1) / g.most;
@@ -1050,8 +1075,7 @@ int launch_fwd_slots(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int n
     return SAR_OK;
 }
 
-// The generic kernels' launch: heads of 1 to 3 values (T a narrow row type) or bf16 heads of more
-// than 256 (T = bf16_t).
+// The generic kernels' launch.
 template <typename T, bool ALL>
 int launch_fwd_generic(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
 {
@@ -1068,27 +1092,35 @@ int launch_fwd_generic(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int
     return SAR_OK;
 }
 
-// Runs `...` with T bound to the generic kernels' row type.
-#define SAR_DISPATCH_GENERIC(dtype, D, ...)              \
-    do {                                                 \
-        if ((dtype) == SAR_F32) {                        \
-            if ((D) == 2) {                              \
-                using T = f32x2_t;                       \
-                __VA_ARGS__;                             \
-            } else {                                     \
-                using T = f32x1_t;                       \
-                __VA_ARGS__;                             \
-            }                                            \
-        } else if ((D) > 256) {                          \
-            using T = bf16_t;                            \
-            __VA_ARGS__;                                 \
-        } else if ((D) == 2) {                           \
-            using T = bf16x2_t;                          \
-            __VA_ARGS__;                                 \
-        } else {                                         \
-            using T = bf16x1_t;                          \
-            __VA_ARGS__;                                 \
-        }                                                \
+// Runs `...` with T bound to the generic kernels' row type: whole 16-byte pieces (bf16 heads of more
+// than 256 values, and what the forward pass keeps there) or, below 4 values, one or two of them.
+#define SAR_DISPATCH_GENERIC(dtype, D, ...)                             \
+    do {                                                                \
+        const int piece_ = piece_for((dtype) == SAR_F32, D);            \
+        if ((dtype) == SAR_F32) {                                       \
+            if (piece_ == 4) {                                          \
+                using T = float;                                        \
+                __VA_ARGS__;                                            \
+            } else if (piece_ == 2) {                                   \
+                using T = f32x2_t;                                      \
+                __VA_ARGS__;                                            \
+            } else {                                                    \
+                using T = f32x1_t;                                      \
+                __VA_ARGS__;                                            \
+            }                                                           \
+        } else if (piece_ == 8) {                                       \
+            using T = bf16_t;                                           \
+            __VA_ARGS__;                                                \
+        } else if (piece_ == 4) {                                       \
+            using T = bf16x4_t;                                         \
+            __VA_ARGS__;                                                \
+        } else if (piece_ == 2) {                                       \
+            using T = bf16x2_t;                                         \
+            __VA_ARGS__;                                                \
+        } else {                                                        \
+            using T = bf16x1_t;                                         \
+            __VA_ARGS__;                                                \
+        }                                                               \
     } while (0)
 
 #define SAR_FWD_CASE(LAUNCH, LPH, FLAG, ...)                                                          \
@@ -1142,7 +1174,7 @@ template <bool ALL>
 int launch_fwd(int dtype, const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const LaunchGeo geo = launch_geo(a.H, a.D, a.ldz);
+    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, true);
     if (geo.kind == Gather::kGeneric)
         SAR_DISPATCH_GENERIC(dtype, a.D, return (launch_fwd_generic<T, ALL>(a, zt, tt, P, st)));
     if (dtype == SAR_F32) return launch_fwd_fast<float, ALL>(a, zt, tt, geo, st);
@@ -1166,7 +1198,8 @@ f256::BwdP bwd_params(const BwdScalars& a)
 {
     f256::BwdP p{};
     p.rows = a.rows; p.n_rows = a.n_wide; p.n_long = std::min(a.n_long, a.n_wide);
-    p.G = a.G; p.rec = a.rec; p.a_l = a.a_l; p.ds = a.ds; p.partial = a.partial;
+    p.G = a.G; p.rec = a.rec; p.a_l = a.a_l; p.ds = a.ds;
+    p.ds_stride = a.ds_stride; p.ds_copies = a.ds_copies; p.partial = a.partial;
     p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope;
     p.ld = a.ldz; p.ldh = a.ldh; p.D = a.D;
     return p;
@@ -1414,19 +1447,116 @@ int launch_bwd_generic(const BwdArgs& tabs, const BwdScalars& a, float* da_l, hi
     return SAR_OK;
 }
 
+// The generic backward kernel's row types: heads of 1 to 3 values, bf16 heads of more than 256.
+#define SAR_DISPATCH_GENERIC_BWD(dtype, D, ...)          \
+    do {                                                 \
+        if ((dtype) == SAR_F32) {                        \
+            if ((D) == 2) {                              \
+                using T = f32x2_t;                       \
+                __VA_ARGS__;                             \
+            } else {                                     \
+                using T = f32x1_t;                       \
+                __VA_ARGS__;                             \
+            }                                            \
+        } else if ((D) > 256) {                          \
+            using T = bf16_t;                            \
+            __VA_ARGS__;                                 \
+        } else if ((D) == 2) {                           \
+            using T = bf16x2_t;                          \
+            __VA_ARGS__;                                 \
+        } else {                                         \
+            using T = bf16x1_t;                          \
+            __VA_ARGS__;                                 \
+        }                                                \
+    } while (0)
+
 template <bool ALL>
 int launch_bwd(int dtype, const BwdArgs& tabs, const BwdScalars& a, float* da_l, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const LaunchGeo geo = launch_geo(a.H, a.D, a.ldz);
+    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, false);
     if (geo.kind == Gather::kGeneric)
-        SAR_DISPATCH_GENERIC(dtype, a.D, return (launch_bwd_generic<T, ALL>(tabs, a, da_l, st)));
+        SAR_DISPATCH_GENERIC_BWD(dtype, a.D, return (launch_bwd_generic<T, ALL>(tabs, a, da_l, st)));
     if (dtype == SAR_F32) return launch_bwd_fast<float, ALL>(tabs, a, geo, da_l, st);
     return launch_bwd_fast<bf16_t, ALL>(tabs, a, geo, da_l, st);
 }
 
 // room for one row of 256 partial sums per workgroup of the (up to) four backward launches of a call
 size_t workspace_bytes(int F) { return (size_t)4 * kMaxPersistentWGs * F * sizeof(float); }
+
+// The backward kernels add every edge's du to ds with atomics.  ds is small (4H bytes a destination),
+// so the frequent destinations of a power-law graph share few cache lines (32/H of them a line), and
+// additions to one line are served one after the other, some 4 ns each: on a share of 7.4M edges and
+// 150k destinations, 1 x 47, the two backward kernels took 1019 + 688 us with and 255 + 183 us without
+// the additions.  Where that is what a call would wait for, the workgroups add to several copies of ds
+// (copy = workgroup modulo their number, so with 8 or more an XCD's workgroups have theirs to
+// themselves), summed at the end: 399 + 250 us with 8 copies, 344 + 231 with 16; bf16 4 x 64 on 31k
+// destinations 230 + 293 -> 72 + 91.  Copies are kept small (up to 1.25 MB 16 of them, to 2.5 MB 8:
+// zeroing and summing them is 10 to 15 us): ds of 4.9 MB (4 x 64 on 306k destinations) is spread
+// over enough lines, 1530 + 1324 us as it is and 1535 + 1364 with 8 copies.
+constexpr size_t kDsSmall = 5 << 18;
+int ds_copies_for(int64_t n_dst, int H)
+{
+    const size_t bytes = (size_t)n_dst * H * sizeof(float);
+    return bytes == 0 || bytes > 2 * kDsSmall ? 1 : bytes > kDsSmall ? 8 : 16;
+}
+// Whether a call of nnz edges, hub of them into its most frequent destination, waits for the line that
+// destination is on: its additions (as if the line's other destinations were as frequent) against the
+// two extra launches and against the time the call's rows take at 6 TB/s.
+bool ds_contended(int64_t hub, int64_t nnz, int H, int D, size_t fb)
+{
+    const double line_us = 0.004 * (double)hub * std::max(1, 32 / H);
+    const double rows_us = (double)nnz * H * D * fb / 6e6;
+    return line_us > 20.0 && line_us > 0.15 * rows_us;
+}
+size_t ds_copy_bytes(int64_t n_dst, int H) { return ((size_t)n_dst * H * sizeof(float) + 255) / 256 * 256; }
+
+// ds[i] += sum of the copies' ds[i] (COPIES = 8 or 16: their loads travel together)
+template <int COPIES>
+__global__ __launch_bounds__(256) void k_ds_sum(const float* __restrict__ copies, int64_t stride,
+                                                float* __restrict__ ds, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        float v[COPIES], s = 0.f;
+#pragma unroll
+        for (int c = 0; c < COPIES; ++c) v[c] = copies[c * stride + i];
+#pragma unroll
+        for (int c = 0; c < COPIES; ++c) s += v[c];
+        ds[i] += s;
+    }
+}
+
+// Where a backward call's atomics go: ds itself or zeroed copies of it in the caller's scratch.
+struct DsTarget {
+    float* base;
+    int64_t stride, n;
+    int copies;
+};
+int ds_begin(DsTarget& d, int64_t n_dst, bool contended, int H, float* ds, void* work, size_t work_bytes, hipStream_t st)
+{
+    d = DsTarget{ds, 0, n_dst * H, 1};
+    const int c = ds_copies_for(n_dst, H);
+    const size_t each = ds_copy_bytes(n_dst, H);
+    if (c == 1 || !contended || work_bytes < workspace_bytes(256) + c * each) return SAR_OK;
+    d.base = reinterpret_cast<float*>(static_cast<char*>(work) + workspace_bytes(256));
+    d.stride = (int64_t)(each / sizeof(float));
+    d.copies = c;
+    const int64_t n = d.stride * c;
+    k_zero_f32<<<(unsigned)std::min<int64_t>((n + 255) / 256, kMaxPersistentWGs), 256, 0, st>>>(d.base, n);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+int ds_end(const DsTarget& d, float* ds, hipStream_t st)
+{
+    if (d.copies == 1) return SAR_OK;
+    const unsigned grid = (unsigned)std::min<int64_t>((d.n + 255) / 256, kMaxPersistentWGs);
+    if (d.copies == 16)
+        k_ds_sum<16><<<grid, 256, 0, st>>>(d.base, d.stride, ds, d.n);
+    else
+        k_ds_sum<8><<<grid, 256, 0, st>>>(d.base, d.stride, ds, d.n);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
 
 }  // namespace
 
@@ -1503,7 +1633,7 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     SAR_CHECK_ARG(Zq && s && m && l && acc, "a tensor argument is null");
     SAR_CHECK_ARG(tq || a_l, "either tq or a_l must be given");
     SAR_CHECK_ARG(aligned16(Zq) && aligned16(acc) && aligned16(a_l), "Zq, acc and a_l must be 16-byte aligned");
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const HeadGroups hg = head_groups(dtype, H, D, true);
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         FwdArgs a{};
@@ -1570,7 +1700,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(aligned16(Zq[q]), "Zq[%d] must be 16-byte aligned", q);
     }
     hipStream_t st = sar::as_stream(stream);
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const HeadGroups hg = head_groups(dtype, H, D, true);
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         PtrTab zt{}, tt{};
@@ -1605,7 +1735,8 @@ extern "C" int sar_gat_workspace_bytes(int64_t n_dst, int64_t n_src_max, int H, 
 {
     SAR_CHECK_ARG(bytes != nullptr, "bytes is null");
     SAR_CHECK_ARG(n_dst >= 0 && n_src_max >= 0 && H > 0 && D > 0, "sizes must be non-negative, H and D positive");
-    *bytes = workspace_bytes(256);
+    const int copies = ds_copies_for(n_dst, H);
+    *bytes = workspace_bytes(256) + (copies > 1 ? (size_t)copies * ds_copy_bytes(n_dst, H) : 0);
     return SAR_OK;
 }
 
@@ -1658,13 +1789,15 @@ int bwd_common_checks(const sar_blocks_t* b, int dtype, int H, int D, const void
 
 // Fields that do not depend on the block(s) or on the head group.
 void fill_bwd_group(BwdScalars& a, const HeadGroups& hg, int g, int H, int D, const void* G, const float* rec,
-                    const float* a_l, float* ds, void* work, float slope)
+                    const float* a_l, const DsTarget& ds, void* work, float slope)
 {
     const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
     a.G = shift(G, f0 * hg.fb);
     a.rec = reinterpret_cast<const float4*>(rec) + h0;
     a.a_l = a_l + f0;
-    a.ds = ds + h0;
+    a.ds = ds.base + h0;
+    a.ds_stride = ds.stride;
+    a.ds_copies = ds.copies;
     a.partial = static_cast<float*>(work);
     a.H = hg.count(g);
     a.D = D;
@@ -1688,7 +1821,9 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     SAR_CHECK_ARG(Zq && dZq, "a tensor argument is null");
     SAR_CHECK_ARG(aligned16(Zq) && aligned16(dZq), "Zq and dZq must be 16-byte aligned");
     hipStream_t st = sar::as_stream(stream);
-    const HeadGroups hg = head_groups(dtype, H, D);
+    DsTarget dst;
+    const HeadGroups hg = head_groups(dtype, H, D, false);
+    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(k.hub, k.nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         BwdArgs tabs{};
@@ -1708,10 +1843,10 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.n_touched = k.n_t_rows;
         a.n_src_host = &k.n_src;
         a.n_blocks = 1;
-        fill_bwd_group(a, hg, g, H, D, G, rec, a_l, ds, work, slope);
+        fill_bwd_group(a, hg, g, H, D, G, rec, a_l, dst, work, slope);
         SAR_TRY(launch_bwd<false>(dtype, tabs, a, da_l + f0, st));
     }
-    return SAR_OK;
+    return ds_end(dst, ds, st);
 }
 
 extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, const void* G,
@@ -1730,7 +1865,14 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(Zq[q] && (!tq || tq[q]) && dZq[q] && (!dtq || dtq[q]), "a tensor of block %d is null", q);
         SAR_CHECK_ARG(aligned16(Zq[q]) && aligned16(dZq[q]), "Zq[%d] and dZq[%d] must be 16-byte aligned", q, q);
     }
-    const HeadGroups hg = head_groups(dtype, H, D);
+    const HeadGroups hg = head_groups(dtype, H, D, false);
+    DsTarget dst;
+    int64_t nnz = 0, hub = 0;     // a frequent destination is frequent in every block
+    for (int q = 0; q < b->P; ++q) {
+        nnz += b->blk[q].nnz;
+        hub += b->blk[q].hub;
+    }
+    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(hub, nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
     int64_t n_src_all[SAR_MAX_BLOCKS];
     for (int q = 0; q < b->P; ++q) n_src_all[q] = b->blk[q].n_src;
     for (int g = 0; g < hg.n; ++g) {
@@ -1762,10 +1904,10 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.n_blocks = b->P;
         a.n_long = b->n_ft_long;
         a.tag_shift = b->tag_shift;
-        fill_bwd_group(a, hg, g, H, D, G, rec, a_l, ds, work, slope);
+        fill_bwd_group(a, hg, g, H, D, G, rec, a_l, dst, work, slope);
         SAR_TRY(launch_bwd<true>(dtype, tabs, a, da_l + f0, st));
     }
-    return SAR_OK;
+    return ds_end(dst, ds, st);
 }
 
 namespace {

@@ -452,7 +452,9 @@ struct BwdP {
     const void* G;
     const float4* rec;
     const float* a_l;
-    float* ds;
+    float* ds;           // score gradients of the destinations: the array itself or the first of ds_copies copies
+    int64_t ds_stride;   // values between copies
+    int ds_copies;       // a power of two; workgroup w adds to copy w % ds_copies
     float* partial;
     int H;
     int tag_shift;
@@ -460,13 +462,19 @@ struct BwdP {
     int ld, ldh, D;      // padded geometry, as in FwdP
 };
 
+// The copy of ds this workgroup adds to.
+__device__ inline float* ds_of(const BwdP& a)
+{
+    return a.ds + (int64_t)(blockIdx.x & (unsigned)(a.ds_copies - 1)) * a.ds_stride;
+}
+
 struct BwdAcc4 {
     float dz[4];   // sum_i alpha G_i for the lane's 4 features
     float dt;      // this lane's share of sum_i du
 };
 
 template <typename T, int LPH, int B, bool PAD>
-__device__ inline void bwd_chunk(BwdAcc4& ac, const BwdP& a, int mine, int cnt, int foff, bool on, int h, int k,
+__device__ inline void bwd_chunk(BwdAcc4& ac, const BwdP& a, float* ds, int mine, int cnt, int foff, bool on, int h, int k,
                                  const float (&zj)[4], float t2)
 {
     const int ld = PAD ? a.ld : kF, ldh = PAD ? a.ldh : a.H;
@@ -506,7 +514,7 @@ __device__ inline void bwd_chunk(BwdAcc4& ac, const BwdP& a, int mine, int cnt, 
         const float de = alpha * (c_mine - rec.z);
         const float du = u2 > 0.f ? de : a.slope * de;
         ac.dt += du;
-        if (valid) unsafeAtomicAdd(a.ds + (int64_t)my_i * ldh + h, du);
+        if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, du);
         static_for<B>([&](auto kk) {
             const float ak = group_bcast<LPH, decltype(kk)::value>(alpha);
             float g[4];
@@ -535,6 +543,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
     const bool on = PAD ? head_ok && 4 * k_pos < a.D : true;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
 
+    float* const ds = ds_of(a);
     float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
     if (on) load_f32<4>(a.a_l + foff, al);
 #pragma unroll
@@ -560,7 +569,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
             const int cnt = min(kWave, end - cb);
             const int mine = (lane < cnt) ? idx[cb + lane] : 0;
-            bwd_chunk<T, LPH, B, PAD>(ac, a, mine, cnt, foff, on, h, k, zj, t2);
+            bwd_chunk<T, LPH, B, PAD>(ac, a, ds, mine, cnt, foff, on, h, k, zj, t2);
         }
     };
     // dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j
@@ -684,6 +693,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
     const T* Gp = static_cast<const T*>(a.G);
 
+    float* const ds = ds_of(a);
     float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
     if (on) load_f32<4>(a.a_l + foff, al);
 #pragma unroll
@@ -812,7 +822,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
             const float de = alpha * (c_mine - rec.z);
             const float du = u2 > 0.f ? de : a.slope * de;
             dt_mine += du;
-            if (my_ok) unsafeAtomicAdd(a.ds + (int64_t)my_i * ldh + h, du);
+            if (my_ok) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, du);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 const float ak = group_bcast<LPH, K>(alpha);
@@ -910,6 +920,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
     const uint32_t mask = (1u << a.tag_shift) - 1u;
     const T* Gp = static_cast<const T*>(a.G);
 
+    float* const ds = ds_of(a);
     float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
     if (on) load_f32<4>(a.a_l + foff, al);
 #pragma unroll
@@ -1001,7 +1012,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
                     }
                 });
                 const int next = dpp_i<kRowShl + 1>(seg);
-                if (valid && (k == B - 1 || next != seg)) unsafeAtomicAdd(a.ds + (int64_t)my_i * ldh + h, run);
+                if (valid && (k == B - 1 || next != seg)) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, run);
             }
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;

@@ -319,6 +319,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
     const bool first = p.slot == 0;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
     const T* Gp = static_cast<const T*>(a.G);
+    float* const ds = f256::ds_of(a);
     float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
     if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
 #pragma unroll
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
                 const float de = alpha * (c_mine - rec.z);
                 const float du = u2 > 0.f ? de : a.slope * de;
                 ac.dt += du;
-                if (valid) unsafeAtomicAdd(a.ds + (int64_t)my_i * a.ldh + p.h, du);
+                if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
                 static_for<B>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     const float ak = group_bcast<LPH, K>(alpha);
@@ -476,6 +477,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs ta
     const int width = a.H * LPH;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
     const T* Gp = static_cast<const T*>(a.G);
+    float* const ds = f256::ds_of(a);
     float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4];
     if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
 #pragma unroll
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs ta
             const float de = alpha * (c_mine - rec.z);
             const float du = u2 > 0.f ? de : a.slope * de;
             dt += du;
-            if (valid) unsafeAtomicAdd(a.ds + (int64_t)my_i * a.ldh + p.h, du);
+            if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 const float ak = group_bcast<LPH, K>(alpha);
