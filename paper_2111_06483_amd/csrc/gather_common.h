@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace sar {
 
 struct bf16_t {
@@ -321,6 +323,30 @@ inline int lanes_for(int F, int vec)
     int need = (F + vec - 1) / vec, g = 4;
     while (g < need) g <<= 1;
     return g;
+}
+
+// Workgroups that can be resident at once for kernel `fn` (persistent grids are
+// sized to this, so that every workgroup starts immediately).
+template <typename Fn>
+inline int resident_workgroups(Fn fn)
+{
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return kMaxPersistentWGs;
+        n_cu = prop.multiProcessorCount;
+    }
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kGatherThreads, 0) != hipSuccess || per_cu <= 0)
+        return kMaxPersistentWGs;
+    return std::min(kMaxPersistentWGs, n_cu * per_cu);
+}
+
+inline unsigned persistent_grid_for(int64_t n_rows, int64_t n_long, int resident)
+{
+    const int64_t want = n_long + (n_rows - n_long + kWavesPerWG - 1) / kWavesPerWG;
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, resident));
 }
 
 }  // namespace sar

@@ -8,6 +8,14 @@
 // in fp32 registers.  The long rows at the head of a list are shared by the four
 // wavefronts of a workgroup and merged through LDS.  The grid is persistent:
 // workgroups stride over the degree-ordered row list, longest rows first.
+//
+// Rows of fewer than 512 bytes leave room for several lane groups in a wavefront: they take
+// different edges of a row, or, for rows of fewer than 8 edges, a row each (k_rows_few).  Row widths
+// that are no whole number of 16-byte pieces (template flag RAG): the last lane of a row takes the
+// row's last 16 bytes, so every access is one unaligned 16-byte access inside the row; the values
+// it shares with the lane before it get the same bits from both.  Measured on a worker's 6.2M edges
+// of bf16 rows of 47 values (one worker of eight on 1M nodes), which used to be moved 2 bytes per lane:
+// see launch_spmm.
 #include <algorithm>
 
 #include "gather_common.h"
@@ -17,7 +25,7 @@ namespace {
 
 using namespace sar;
 
-constexpr int kU = 4;   // rows in flight per lane group
+constexpr int kU = 4;   // rows in flight per lane group, twice as many where a row has them
 
 struct PtrTab {
     const void* p[SAR_MAX_BLOCKS];
@@ -43,54 +51,122 @@ struct SpmmArgs {
 
 enum class Mode { kBlock, kAll, kBackward };
 
-// Adds the rows listed in idx[beg,end) into acc.  The wavefront takes the
-// 64-edge chunks chunk0, chunk0+stride, ...
-template <typename T, int G, Mode M>
-__device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab,
-                                int beg, int end, int chunk0, int stride, const LaneMap<T, G>& lm)
+// The lane's place in a row: the first of its VEC values and whether it carries any.
+template <typename T, int G, bool RAG>
+struct RowLanes {
+    static constexpr int VEC = Vec<T>::N;
+    int lane, gl, slot, off;
+    bool on;
+    __device__ inline explicit RowLanes(int F)
+    {
+        lane = threadIdx.x & (kWave - 1);
+        gl = lane & (G - 1);
+        slot = lane / G;
+        on = gl * VEC < F;
+        off = RAG ? min(gl * VEC, F - VEC) : gl * VEC;
+    }
+    static __device__ inline typename Vec<T>::Raw load(const T* p)
+    {
+        if constexpr (RAG) {
+            typename Vec<T>::Raw r;
+            __builtin_memcpy(&r, p, sizeof(r));
+            return r;
+        } else {
+            return Vec<T>::load(p);
+        }
+    }
+    static __device__ inline void store(T* p, const float (&v)[VEC])
+    {
+        if constexpr (RAG) {
+            alignas(16) T tmp[VEC];
+            Vec<T>::store(tmp, v);
+            __builtin_memcpy(p, tmp, sizeof(tmp));
+        } else {
+            Vec<T>::store(p, v);
+        }
+    }
+    static __device__ inline void load_acc(const float* p, float (&v)[VEC])
+    {
+        if constexpr (RAG)
+            __builtin_memcpy(v, p, sizeof(v));
+        else
+            load_f32<VEC>(p, v);
+    }
+    static __device__ inline void store_acc(float* p, const float (&v)[VEC])
+    {
+        if constexpr (RAG)
+            __builtin_memcpy(p, v, sizeof(v));
+        else
+            store_f32<VEC>(p, v);
+    }
+};
+
+// Adds the rows of KU edges per lane group into acc: edges k0 + k SLOTS + slot of the chunk whose
+// ids the lanes hold in `mine`.  FULL: all of them are below cnt.
+template <typename T, int G, Mode M, bool RAG, int KU, bool FULL>
+__device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab, uint32_t mine,
+                                 int k0, int cnt, const RowLanes<T, G, RAG>& lm)
 {
     constexpr int VEC = Vec<T>::N;
     constexpr int SLOTS = kWave / G;
     const uint32_t mask = (M == Mode::kAll) ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    typename Vec<T>::Raw raw[KU];
+    int deg[KU];        // the weights are formed after all loads have been issued
+#pragma unroll
+    for (int k = 0; k < KU; ++k) {
+        const int ek = k0 + k * SLOTS + lm.slot;
+        const uint32_t id = __shfl(mine, ek & (kWave - 1));
+        const bool ok = (FULL || ek < cnt) && lm.on;
+        raw[k] = Vec<T>::zero();
+        deg[k] = 1;
+        if (ok) {
+            const uint32_t j = id & mask;
+            const T* base;
+            if constexpr (M == Mode::kAll)
+                base = static_cast<const T*>(ztab[id >> a.tag_shift]);
+            else
+                base = static_cast<const T*>(a.Z);
+            raw[k] = lm.load(base + (int64_t)j * a.ld + lm.off);
+            if constexpr (M == Mode::kBackward) {
+                if (a.mean) deg[k] = a.deg[j];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KU; ++k) {
+        float v[VEC];
+        Vec<T>::unpack(raw[k], v);
+        const float w = 1.f / (float)max(deg[k], 1);
+#pragma unroll
+        for (int x = 0; x < VEC; ++x) {
+            if constexpr (M == Mode::kBackward)
+                acc[x] = fmaf(w, v[x], acc[x]);
+            else
+                acc[x] += v[x];
+        }
+    }
+}
+
+// Adds the rows listed in idx[beg,end) into acc.  The wavefront takes the
+// 64-edge chunks chunk0, chunk0+stride, ...  Eight edges per lane group are in flight while there are
+// as many (forward, 7.4M edges: bf16 rows of 512 values 1208 us with four, 1099 with eight), then four.
+// The backward pass over wide rows stays with four: a source has 12 edges on average and its wavefront
+// waits for the chain in front of them, so what counts is how many wavefronts are resident (the same
+// rows: 1149 us with four, 1257 with eight and their registers).
+template <typename T, int G, Mode M, bool RAG>
+__device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab,
+                                int beg, int end, int chunk0, int stride, const RowLanes<T, G, RAG>& lm)
+{
+    constexpr int SLOTS = kWave / G;
     for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
         const int cnt = min(kWave, end - cb);
         const uint32_t mine = (lm.lane < cnt) ? a.indices[cb + lm.lane] : 0u;
-        for (int k0 = 0; k0 < cnt; k0 += SLOTS * kU) {
-            typename Vec<T>::Raw raw[kU];
-            float w[kU];
-#pragma unroll
-            for (int k = 0; k < kU; ++k) {
-                const int ek = k0 + k * SLOTS + lm.slot;
-                const uint32_t id = __shfl(mine, ek & (kWave - 1));
-                const bool ok = (ek < cnt) && lm.on;
-                raw[k] = Vec<T>::zero();
-                w[k] = 1.f;
-                if (ok) {
-                    const uint32_t j = id & mask;
-                    const T* base;
-                    if constexpr (M == Mode::kAll)
-                        base = static_cast<const T*>(ztab[id >> a.tag_shift]);
-                    else
-                        base = static_cast<const T*>(a.Z);
-                    raw[k] = Vec<T>::load(base + (int64_t)j * a.ld + lm.gl * VEC);
-                    if constexpr (M == Mode::kBackward) {
-                        if (a.mean) w[k] = 1.f / (float)max(a.deg[j], 1);
-                    }
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kU; ++k) {
-                float v[VEC];
-                Vec<T>::unpack(raw[k], v);
-#pragma unroll
-                for (int x = 0; x < VEC; ++x) {
-                    if constexpr (M == Mode::kBackward)
-                        acc[x] = fmaf(w[k], v[x], acc[x]);
-                    else
-                        acc[x] += v[x];
-                }
-            }
+        int k0 = 0;
+        if constexpr (M != Mode::kBackward || G <= 16) {
+            for (; k0 + 2 * kU * SLOTS <= cnt; k0 += 2 * kU * SLOTS)
+                add_batch<T, G, M, RAG, 2 * kU, true>(acc, a, ztab, mine, k0, cnt, lm);
         }
+        for (; k0 < cnt; k0 += kU * SLOTS) add_batch<T, G, M, RAG, kU, false>(acc, a, ztab, mine, k0, cnt, lm);
     }
 }
 
@@ -103,9 +179,9 @@ __device__ inline void merge_slots(float (&acc)[Vec<T>::N])
         for (int x = 0; x < Vec<T>::N; ++x) acc[x] += __shfl_xor(acc[x], o);
 }
 
-template <typename T, int G, Mode M>
+template <typename T, int G, Mode M, bool RAG>
 __device__ inline void finish_row(const float (&acc)[Vec<T>::N], const SpmmArgs& a, int i,
-                                  const LaneMap<T, G>& lm)
+                                  const RowLanes<T, G, RAG>& lm)
 {
     constexpr int VEC = Vec<T>::N;
     if (lm.slot != 0 || !lm.on) return;
@@ -113,13 +189,13 @@ __device__ inline void finish_row(const float (&acc)[Vec<T>::N], const SpmmArgs&
     if constexpr (M == Mode::kBackward) {
         if (a.out_rank) row = a.out_rank[i];
     }
-    const int64_t o = row * a.ld + lm.gl * VEC;
+    const int64_t o = row * a.ld + lm.off;
     if constexpr (M == Mode::kBlock) {
         float cur[VEC];
-        load_f32<VEC>(a.acc + o, cur);
+        lm.load_acc(a.acc + o, cur);
 #pragma unroll
         for (int x = 0; x < VEC; ++x) cur[x] += acc[x];
-        store_f32<VEC>(a.acc + o, cur);
+        lm.store_acc(a.acc + o, cur);
     } else {
         float v[VEC];
         float sc = 1.f;
@@ -131,7 +207,7 @@ __device__ inline void finish_row(const float (&acc)[Vec<T>::N], const SpmmArgs&
         if constexpr (M == Mode::kAll) {
             if (a.res) {
                 float r[VEC];
-                Vec<T>::unpack(Vec<T>::load(static_cast<const T*>(a.res) + o), r);
+                Vec<T>::unpack(lm.load(static_cast<const T*>(a.res) + o), r);
 #pragma unroll
                 for (int x = 0; x < VEC; ++x) v[x] += r[x];
             }
@@ -140,11 +216,11 @@ __device__ inline void finish_row(const float (&acc)[Vec<T>::N], const SpmmArgs&
                 for (int x = 0; x < VEC; ++x) v[x] = fmaxf(v[x], 0.f);
             }
         }
-        Vec<T>::store(static_cast<T*>(a.out) + o, v);
+        lm.store(static_cast<T*>(a.out) + o, v);
     }
 }
 
-template <typename T, int G, Mode M>
+template <typename T, int G, Mode M, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab, int P)
 {
     constexpr int VEC = Vec<T>::N;
@@ -154,14 +230,14 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab,
         if ((int)threadIdx.x < P) ztab[threadIdx.x] = tab.p[threadIdx.x];
         __syncthreads();
     }
-    const LaneMap<T, G> lm(a.F, 1, a.F);
+    const RowLanes<T, G, RAG> lm(a.F);
     const int wave = threadIdx.x / kWave;
 
     // long rows: one workgroup each
     for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
         const int i = (int)a.rows[r];
         float acc[VEC] = {};
-        add_rows<T, G, M>(acc, a, ztab, a.indptr[i], a.indptr[i + 1], wave, kWavesPerWG, lm);
+        add_rows<T, G, M, RAG>(acc, a, ztab, a.indptr[i], a.indptr[i + 1], wave, kWavesPerWG, lm);
         merge_slots<T, G>(acc);
         if (lm.slot == 0)
 #pragma unroll
@@ -174,7 +250,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab,
                 for (int w = 0; w < kWavesPerWG; ++w) t += part[w][lm.gl][x];
                 acc[x] = t;
             }
-            finish_row<T, G, M>(acc, a, i, lm);
+            finish_row<T, G, M, RAG>(acc, a, i, lm);
         }
         __syncthreads();
     }
@@ -183,9 +259,9 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab,
     for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = (int)a.rows[r];
         float acc[VEC] = {};
-        add_rows<T, G, M>(acc, a, ztab, a.indptr[i], a.indptr[i + 1], 0, 1, lm);
+        add_rows<T, G, M, RAG>(acc, a, ztab, a.indptr[i], a.indptr[i + 1], 0, 1, lm);
         merge_slots<T, G>(acc);
-        finish_row<T, G, M>(acc, a, i, lm);
+        finish_row<T, G, M, RAG>(acc, a, i, lm);
     }
 }
 
@@ -247,13 +323,13 @@ struct BwdAllTabs {
     const int32_t* rank[SAR_MAX_BLOCKS];
 };
 
-template <typename T, int G>
+template <typename T, int G, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_spmm_bwd_all(SpmmArgs a, BwdAllTabs tabs)
 {
     constexpr int VEC = Vec<T>::N;
     constexpr Mode M = Mode::kBackward;
     __shared__ float part[kWavesPerWG][G][VEC];
-    const LaneMap<T, G> lm(a.F, 1, a.F);
+    const RowLanes<T, G, RAG> lm(a.F);
     const int wave = threadIdx.x / kWave;
     const uint32_t mask = (1u << a.tag_shift) - 1u;
     auto locate = [&](int64_t r, SpmmArgs& la) -> int {
@@ -270,7 +346,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm_bwd_all(SpmmArgs a, Bwd
         SpmmArgs la = a;
         const int j = locate(r, la);
         float acc[VEC] = {};
-        add_rows<T, G, M>(acc, la, nullptr, la.indptr[j], la.indptr[j + 1], wave, kWavesPerWG, lm);
+        add_rows<T, G, M, RAG>(acc, la, nullptr, la.indptr[j], la.indptr[j + 1], wave, kWavesPerWG, lm);
         merge_slots<T, G>(acc);
         if (lm.slot == 0)
 #pragma unroll
@@ -283,7 +359,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm_bwd_all(SpmmArgs a, Bwd
                 for (int w = 0; w < kWavesPerWG; ++w) t += part[w][lm.gl][x];
                 acc[x] = t;
             }
-            finish_row<T, G, M>(acc, la, j, lm);
+            finish_row<T, G, M, RAG>(acc, la, j, lm);
         }
         __syncthreads();
     }
@@ -292,9 +368,115 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm_bwd_all(SpmmArgs a, Bwd
         SpmmArgs la = a;
         const int j = locate(r, la);
         float acc[VEC] = {};
-        add_rows<T, G, M>(acc, la, nullptr, la.indptr[j], la.indptr[j + 1], 0, 1, lm);
+        add_rows<T, G, M, RAG>(acc, la, nullptr, la.indptr[j], la.indptr[j + 1], 0, 1, lm);
         merge_slots<T, G>(acc);
-        finish_row<T, G, M>(acc, la, j, lm);
+        finish_row<T, G, M, RAG>(acc, la, j, lm);
+    }
+}
+
+// Rows of fewer than 8 edges and rows without any (list entries [r_begin, r_end)): a lane group
+// each, all of a row's edges in flight at once.  One wavefront per such row left the memory system
+// waiting for a chain of four dependent loads; list entries are read three rounds ahead here, ranges
+// and output rows two, ids one.  ALLB: entries tagged with their block, as in k_spmm_bwd_all.
+template <typename T, int G, Mode M, bool ALLB, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllTabs tabs, int64_t r_begin, int64_t r_end)
+{
+    static_assert(M != Mode::kAll, "the all-blocks forward pass walks rows of all blocks together");
+    constexpr int VEC = Vec<T>::N;
+    constexpr int SLOTS = kWave / G;
+    constexpr int kMost = (1 << sar::kNarrowMaxClass) - 1;
+    constexpr int kHold = (kMost + G - 1) / G;          // ids a lane holds
+    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
+    __shared__ const uint32_t* s_ix[SAR_MAX_BLOCKS];
+    __shared__ void* s_out[SAR_MAX_BLOCKS];
+    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    if constexpr (ALLB) {
+        if (threadIdx.x < SAR_MAX_BLOCKS) {
+            s_ip[threadIdx.x] = tabs.t_indptr[threadIdx.x];
+            s_ix[threadIdx.x] = tabs.t_indices[threadIdx.x];
+            s_out[threadIdx.x] = tabs.dZ[threadIdx.x];
+            s_rank[threadIdx.x] = tabs.rank[threadIdx.x];
+        }
+        __syncthreads();
+    }
+    const RowLanes<T, G, RAG> lm(a.F);
+    const uint32_t mask = ALLB ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
+    struct Meta { int q, j, beg, cnt, jo; };
+    struct Ids { uint32_t v[kHold]; };
+    const int64_t stride = (int64_t)gridDim.x * kWavesPerWG * SLOTS;
+    const int64_t r0 = r_begin + ((int64_t)blockIdx.x * kWavesPerWG + threadIdx.x / kWave) * SLOTS + lm.slot;
+    auto load_id = [&](int64_t r) -> uint32_t { return r < r_end ? a.rows[r] : 0u; };
+    auto load_meta = [&](uint32_t id, int64_t r) {
+        Meta m{0, 0, 0, 0, 0};
+        if (r < r_end) {
+            m.q = ALLB ? (int)(id >> a.tag_shift) : 0;
+            m.j = (int)(id & mask);
+            const int32_t* ip = ALLB ? s_ip[m.q] : a.indptr;
+            m.beg = ip[m.j];
+            m.cnt = ip[m.j + 1] - m.beg;
+            m.jo = m.j;
+            if constexpr (M == Mode::kBackward) {
+                const int32_t* rank = ALLB ? s_rank[m.q] : a.out_rank;
+                if (rank) m.jo = rank[m.j];
+            }
+        }
+        return m;
+    };
+    auto load_ids = [&](const Meta& m) {
+        Ids d;
+#pragma unroll
+        for (int k = 0; k < kHold; ++k) {
+            const int e = k * G + lm.gl;
+            d.v[k] = e < m.cnt ? (ALLB ? s_ix[m.q] : a.indices)[m.beg + e] : 0u;
+        }
+        return d;
+    };
+    uint32_t id2 = load_id(r0 + 2 * stride);
+    Meta m0 = load_meta(load_id(r0), r0), m1 = load_meta(load_id(r0 + stride), r0 + stride);
+    Ids d0 = load_ids(m0);
+    for (int64_t r = r0; r - lm.slot < r_end; r += stride) {       // uniform over the wavefront
+        const Ids d1 = load_ids(m1);
+        const Meta m2 = load_meta(id2, r + 2 * stride);
+        const uint32_t id3 = load_id(r + 3 * stride);
+        typename Vec<T>::Raw raw[kMost];
+        int deg[kMost];
+#pragma unroll
+        for (int e = 0; e < kMost; ++e) {
+            raw[e] = Vec<T>::zero();
+            deg[e] = 1;
+            const uint32_t j = __shfl(d0.v[e / G], lm.slot * G + e % G);
+            if (e < m0.cnt && lm.on) {
+                raw[e] = lm.load(static_cast<const T*>(a.Z) + (int64_t)j * a.ld + lm.off);
+                if constexpr (M == Mode::kBackward) {
+                    if (a.mean) deg[e] = a.deg[j];
+                }
+            }
+        }
+        if (r < r_end && lm.on) {
+            float acc[VEC] = {};
+#pragma unroll
+            for (int e = 0; e < kMost; ++e) {
+                float v[VEC];
+                Vec<T>::unpack(raw[e], v);
+                const float w = 1.f / (float)max(deg[e], 1);
+#pragma unroll
+                for (int x = 0; x < VEC; ++x) acc[x] = M == Mode::kBackward ? fmaf(w, v[x], acc[x]) : acc[x] + v[x];
+            }
+            const int64_t o = (int64_t)m0.jo * a.ld + lm.off;
+            if constexpr (M == Mode::kBlock) {
+                float cur[VEC];
+                lm.load_acc(a.acc + o, cur);
+#pragma unroll
+                for (int x = 0; x < VEC; ++x) cur[x] += acc[x];
+                lm.store_acc(a.acc + o, cur);
+            } else {
+                lm.store(static_cast<T*>(ALLB ? s_out[m0.q] : a.out) + o, acc);
+            }
+        }
+        m0 = m1;
+        d0 = d1;
+        m1 = m2;
+        id2 = id3;
     }
 }
 
@@ -326,42 +508,93 @@ __global__ __launch_bounds__(256) void k_error_add(const T* __restrict__ Eq, con
     }
 }
 
-unsigned persistent_grid(int64_t n_rows, int64_t n_long)
+// Runs `...` with kG bound to the lanes of a row and kR to whether its last lane is shifted back.
+#define SAR_DISPATCH_LANES(T, F, ...)                                                          \
+    do {                                                                                       \
+        const bool ragged_ = (F) % Vec<T>::N != 0;                                             \
+        switch (lanes_for((F), Vec<T>::N)) {                                                   \
+            case 4: { constexpr int kG = 4; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;         \
+            case 8: { constexpr int kG = 8; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;         \
+            case 16: { constexpr int kG = 16; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;       \
+            case 32: { constexpr int kG = 32; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;       \
+            default: { constexpr int kG = 64; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;       \
+        }                                                                                      \
+    } while (0)
+#define SAR_RAGGED_OR_NOT(T, ...)                  \
+    if (ragged_) {                                       \
+        constexpr bool kR = Vec<T>::N * sizeof(T) == 16; \
+        __VA_ARGS__;                               \
+    } else {                                       \
+        constexpr bool kR = false;                 \
+        __VA_ARGS__;                               \
+    }
+
+// Rows of the list's tail with fewer than 8 edges go to k_rows_few where a wavefront has room for
+// at least four of them (backward on 7.4M edges, alone -> with it: bf16 47 values 595 -> 318 us, fp32 64
+// values 415 -> 371; with two to a wavefront it lost, fp32 128 values 603 -> 657).
+template <typename T>
+int64_t first_few(const SpmmArgs& a, int64_t n_wide)
 {
-    const int64_t want = n_long + (n_rows - n_long + kWavesPerWG - 1) / kWavesPerWG;
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, kMaxPersistentWGs));
+    return lanes_for(a.F, Vec<T>::N) <= 16 ? std::min(n_wide, a.n_rows) : a.n_rows;
+}
+template <typename T>
+unsigned few_grid(const SpmmArgs& a, int64_t n, int resident)
+{
+    const int64_t per_wg = (int64_t)kWavesPerWG * (kWave / lanes_for(a.F, Vec<T>::N));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per_wg - 1) / per_wg, resident));
 }
 
+// n_wide: list entries before it have at least 8 edges.
 template <typename T, Mode M>
-int launch_spmm(const SpmmArgs& a, const PtrTab& tab, int P, hipStream_t st)
+int launch_spmm(SpmmArgs a, const PtrTab& tab, int P, int64_t n_wide, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const unsigned grid = persistent_grid(a.n_rows, a.n_long);
-    switch (lanes_for(a.F, Vec<T>::N)) {
-        case 4: k_spmm<T, 4, M><<<grid, kGatherThreads, 0, st>>>(a, tab, P); break;
-        case 8: k_spmm<T, 8, M><<<grid, kGatherThreads, 0, st>>>(a, tab, P); break;
-        case 16: k_spmm<T, 16, M><<<grid, kGatherThreads, 0, st>>>(a, tab, P); break;
-        case 32: k_spmm<T, 32, M><<<grid, kGatherThreads, 0, st>>>(a, tab, P); break;
-        case 64: k_spmm<T, 64, M><<<grid, kGatherThreads, 0, st>>>(a, tab, P); break;
-        default: return sar::fail(SAR_ERR_UNSUPPORTED, "row of F=%d values is wider than 1024 bytes", a.F);
+    if constexpr (M != Mode::kAll) {
+        const int64_t few = first_few<T>(a, n_wide), n = a.n_rows - few;
+        if (n > 0) {
+            SAR_DISPATCH_LANES(T, a.F, {
+                auto fn = k_rows_few<T, (kG <= 16 ? kG : 16), M, false, kR>;
+                static const int resident = resident_workgroups(fn);
+                fn<<<few_grid<T>(a, n, resident), kGatherThreads, 0, st>>>(a, BwdAllTabs{}, few, a.n_rows);
+            });
+            SAR_LAUNCH_CHECK();
+            a.n_rows = few;
+            a.n_long = std::min(a.n_long, few);
+            if (few == 0) return SAR_OK;
+        }
     }
+    // every workgroup of the persistent grid has to start at once: with 2048 of them and room for 1792,
+    // the backward pass over rows of 512 bf16 values took 1580 us instead of 1149
+    SAR_DISPATCH_LANES(T, a.F, {
+        auto fn = k_spmm<T, kG, M, kR>;
+        static const int resident = resident_workgroups(fn);
+        fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(a, tab, P);
+    });
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
 
 template <typename T>
-int launch_spmm_bwd_all(const SpmmArgs& a, const BwdAllTabs& tabs, hipStream_t st)
+int launch_spmm_bwd_all(SpmmArgs a, const BwdAllTabs& tabs, int64_t n_wide, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const unsigned grid = persistent_grid(a.n_rows, a.n_long);
-    switch (lanes_for(a.F, Vec<T>::N)) {
-        case 4: k_spmm_bwd_all<T, 4><<<grid, kGatherThreads, 0, st>>>(a, tabs); break;
-        case 8: k_spmm_bwd_all<T, 8><<<grid, kGatherThreads, 0, st>>>(a, tabs); break;
-        case 16: k_spmm_bwd_all<T, 16><<<grid, kGatherThreads, 0, st>>>(a, tabs); break;
-        case 32: k_spmm_bwd_all<T, 32><<<grid, kGatherThreads, 0, st>>>(a, tabs); break;
-        case 64: k_spmm_bwd_all<T, 64><<<grid, kGatherThreads, 0, st>>>(a, tabs); break;
-        default: return sar::fail(SAR_ERR_UNSUPPORTED, "row of F=%d values is wider than 1024 bytes", a.F);
+    const int64_t few = first_few<T>(a, n_wide), n = a.n_rows - few;
+    if (n > 0) {
+        SAR_DISPATCH_LANES(T, a.F, {
+            auto fn = k_rows_few<T, (kG <= 16 ? kG : 16), Mode::kBackward, true, kR>;
+            static const int resident = resident_workgroups(fn);
+            fn<<<few_grid<T>(a, n, resident), kGatherThreads, 0, st>>>(a, tabs, few, a.n_rows);
+        });
+        SAR_LAUNCH_CHECK();
+        a.n_rows = few;
+        a.n_long = std::min(a.n_long, few);
+        if (few == 0) return SAR_OK;
     }
+    SAR_DISPATCH_LANES(T, a.F, {
+        auto fn = k_spmm_bwd_all<T, kG, kR>;
+        static const int resident = resident_workgroups(fn);
+        fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(a, tabs);
+    });
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
@@ -374,21 +607,25 @@ int check_row_shape(int dtype, int F)
     return SAR_OK;
 }
 
-// A wavefront covers 64 lane pieces of a row (1024 bytes when the row width is a whole number of
-// 16-byte pieces, less when lanes have to move 8, 4 or 2 bytes); wider rows are processed as
-// several launches over column ranges, each seeing its slice of every row through the row stride.
+// A wavefront covers 64 lane pieces of a row (1024 bytes; less where the row is so narrow that
+// lanes have to move 8, 4 or 2 bytes); wider rows are processed as several launches over column
+// ranges of about the same width, each seeing its slice of every row through the row stride.
 struct ColumnChunks {
     int n, width;   // launches and values per launch (the last launch may be narrower)
     size_t fb;
-    int piece;      // values per lane: the largest of 16, 8, 4, 2 bytes' worth that divides F
+    int piece;      // values per lane: 16 bytes' worth; rows that are narrower, the largest piece that divides them
+    int first(int c) const { return c * width; }
+    int count(int c, int F) const { return std::min(width, F - c * width); }
 };
 
 ColumnChunks column_chunks(int dtype, int F)
 {
     ColumnChunks c;
     c.fb = dtype == SAR_F32 ? 4 : 2;
-    c.piece = piece_for(dtype == SAR_F32, F);
-    c.width = 64 * c.piece;
+    const int full = dtype == SAR_F32 ? 4 : 8;
+    c.piece = F >= full ? full : piece_for(dtype == SAR_F32, F);
+    c.n = (F + 64 * c.piece - 1) / (64 * c.piece);
+    c.width = ((F + c.n - 1) / c.n + c.piece - 1) / c.piece * c.piece;
     c.n = (F + c.width - 1) / c.width;
     return c;
 }
@@ -423,11 +660,11 @@ extern "C" int sar_spmm_block(const sar_blocks_t* b, int q, const void* Zq, int 
     PtrTab tab{};
     const ColumnChunks cc = column_chunks(dtype, F);
     for (int c = 0; c < cc.n; ++c) {
-        const size_t f0 = (size_t)c * cc.width;
+        const size_t f0 = (size_t)cc.first(c);
         a.Z = shift(Zq, f0 * cc.fb);
         a.acc = acc + f0;
-        a.F = std::min<int>(cc.width, F - (int)f0);
-        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kBlock>(a, tab, 0, sar::as_stream(stream)))));
+        a.F = cc.count(c, F);
+        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kBlock>(a, tab, 0, k.n_rows_wide, sar::as_stream(stream)))));
     }
     return SAR_OK;
 }
@@ -512,14 +749,14 @@ extern "C" int sar_spmm_all(const sar_blocks_t* b, const void* const* Zq, int dt
     a.mean = mean;
     const ColumnChunks cc = column_chunks(dtype, F);
     for (int c = 0; c < cc.n; ++c) {
-        const size_t f0 = (size_t)c * cc.width;
+        const size_t f0 = (size_t)cc.first(c);
         PtrTab tab{};
         for (int q = 0; q < b->P; ++q) tab.p[q] = shift(Zq[q], f0 * cc.fb);
         a.out = shift(out, f0 * cc.fb);
         a.res = residual ? shift(residual, f0 * cc.fb) : nullptr;
         a.act = act;
-        a.F = std::min<int>(cc.width, F - (int)f0);
-        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kAll>(a, tab, b->P, st))));
+        a.F = cc.count(c, F);
+        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kAll>(a, tab, b->P, 0, st))));
     }
     return SAR_OK;
 }
@@ -550,11 +787,11 @@ extern "C" int sar_spmm_bwd_block(const sar_blocks_t* b, int q, const void* G, i
     PtrTab tab{};
     const ColumnChunks cc = column_chunks(dtype, F);
     for (int c = 0; c < cc.n; ++c) {
-        const size_t f0 = (size_t)c * cc.width;
+        const size_t f0 = (size_t)cc.first(c);
         a.Z = shift(G, f0 * cc.fb);
         a.out = shift(dZq, f0 * cc.fb);
-        a.F = std::min<int>(cc.width, F - (int)f0);
-        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kBackward>(a, tab, 0, st))));
+        a.F = cc.count(c, F);
+        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY((launch_spmm<T, Mode::kBackward>(a, tab, 0, k.n_t_wide, st))));
     }
     return SAR_OK;
 }
@@ -588,7 +825,7 @@ extern "C" int sar_spmm_bwd_all(const sar_blocks_t* b, const void* G, int mean, 
     a.tag_shift = b->tag_shift;
     const ColumnChunks cc = column_chunks(dtype, F);
     for (int c = 0; c < cc.n; ++c) {
-        const size_t f0 = (size_t)c * cc.width;
+        const size_t f0 = (size_t)cc.first(c);
         BwdAllTabs tabs{};
         for (int q = 0; q < b->P; ++q) {
             const sar::Block& k = b->blk[q];
@@ -599,8 +836,8 @@ extern "C" int sar_spmm_bwd_all(const sar_blocks_t* b, const void* G, int mean, 
             tabs.rank[q] = (b->flags & SAR_BUILD_COMPACT) ? k.t_rank : nullptr;
         }
         a.Z = shift(G, f0 * cc.fb);
-        a.F = std::min<int>(cc.width, F - (int)f0);
-        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY(launch_spmm_bwd_all<T>(a, tabs, st)));
+        a.F = cc.count(c, F);
+        SAR_DISPATCH_ROW(dtype, cc.piece, SAR_TRY(launch_spmm_bwd_all<T>(a, tabs, b->n_ft_wide, st)));
     }
     return SAR_OK;
 }
