@@ -11,7 +11,12 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
+#include <mutex>
 #include <new>
+#include <type_traits>
+#include <utility>
+#include <vector>
 
 #include "sar_internal.h"
 
@@ -40,7 +45,6 @@ using sar::Block;
 constexpr int kThreads = 256;
 constexpr int kScanTile = 2048;   // 256 threads x 8 values
 constexpr int kPartTile = 1024;   // nodes per workgroup when ranking nodes in partitions
-constexpr int kShortSort = 32;    // rows up to this length are insertion-sorted by one thread
 constexpr int kLdsSort = 8192;    // longer rows up to this length are sorted in LDS
 
 // ---------------------------------------------------------------- scan
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_reduce(const int32_t* __restr
 
 __global__ __launch_bounds__(kThreads) void k_tile_scan(const int32_t* in, int64_t n,
                                                         const int32_t* __restrict__ tile_offsets,
-                                                        int32_t* out)
+                                                        int32_t first, int32_t* out)
 {
     __shared__ int lds4[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * 8;
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(const int32_t* in, int64
         s += v[k];
     }
     int total;
-    int run = block_exclusive_scan(s, lds4, &total) + (tile_offsets ? tile_offsets[blockIdx.x] : 0);
+    int run = block_exclusive_scan(s, lds4, &total) + (tile_offsets ? tile_offsets[blockIdx.x] : 0) + first;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         if (base + k < n) out[base + k] = run;
@@ -98,30 +102,114 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(const int32_t* in, int64
     }
 }
 
+// Device memory of handles and of builder calls.  A handle is some ten arrays of a few to a few
+// hundred MB, and a program that rebuilds its handles (a graph that changes, restricted handles batch
+// by batch) would pay the driver for mapping and clearing them every time: up to 20 ms of a 25 ms
+// call where much memory had been freed before.  What a builder call or sar_blocks_free gives up is
+// therefore kept for the next call, at most kPoolMost bytes per device and nothing larger than a
+// quarter of that, and all of it is given back when the last handle on the device is freed (or
+// when the device runs out of memory).  Nothing enters the pool before the work that used it is done.
+class Pool {
+public:
+    static constexpr size_t kPoolMost = (size_t)1 << 30;
+    static size_t round(size_t bytes)
+    {
+        size_t unit = 4096;
+        while (unit * 16 < bytes) unit *= 2;         // at most an eighth more than asked for
+        return (std::max<size_t>(bytes, 1) + unit - 1) / unit * unit;
+    }
+    int take(int dev, void** out, size_t size)       // dev: the current device; size as round() gives it
+    {
+        std::lock_guard<std::mutex> lock(m_);
+        auto& d = devices_[dev];
+        auto it = d.idle.lower_bound(size);
+        if (it != d.idle.end() && it->first == size) {
+            *out = it->second;
+            d.bytes -= it->first;
+            d.idle.erase(it);
+            return SAR_OK;
+        }
+        if (hipMalloc(out, size) == hipSuccess) return SAR_OK;
+        (void)hipGetLastError();
+        release(d);
+        SAR_HIP(hipMalloc(out, size));
+        return SAR_OK;
+    }
+    void give(int dev, void* p, size_t size)         // memory of `dev` that nothing in flight uses any more
+    {
+        if (size <= kPoolMost / 4) {
+            std::lock_guard<std::mutex> lock(m_);
+            auto& d = devices_[dev];
+            if (d.bytes + size <= kPoolMost) {
+                d.idle.emplace(size, p);
+                d.bytes += size;
+                return;
+            }
+        }
+        (void)hipFree(p);
+    }
+    void count_handle(int dev, int by)
+    {
+        std::lock_guard<std::mutex> lock(m_);
+        auto& d = devices_[dev];
+        d.handles += by;
+        if (d.handles <= 0) release(d);
+    }
+
+private:
+    struct Device {
+        std::multimap<size_t, void*> idle;
+        size_t bytes = 0;
+        int64_t handles = 0;
+    };
+    void release(Device& d)
+    {
+        for (auto& e : d.idle) (void)hipFree(e.second);
+        d.idle.clear();
+        d.bytes = 0;
+    }
+    std::mutex m_;
+    std::map<int, Device> devices_;
+};
+
+Pool& pool()
+{
+    static Pool* p = new Pool();     // never destroyed: handles may be freed while the process ends
+    return *p;
+}
+
+// Scratch of one builder call on one stream.
 struct DeviceTemps {
-    std::vector<void*> ptrs;
+    explicit DeviceTemps(hipStream_t s, int device) : st(s), dev(device) {}
+    DeviceTemps(const DeviceTemps&) = delete;
     ~DeviceTemps()
     {
-        for (void* p : ptrs) (void)hipFree(p);
+        if (ptrs.empty()) return;
+        (void)hipStreamSynchronize(st);
+        for (auto& p : ptrs) pool().give(dev, p.first, p.second);
     }
     template <typename T>
     int alloc(T** out, int64_t count)
     {
         void* p = nullptr;
-        SAR_HIP(hipMalloc(&p, std::max<int64_t>(count, 1) * sizeof(T)));
-        ptrs.push_back(p);
+        const size_t size = Pool::round(std::max<int64_t>(count, 1) * sizeof(T));
+        SAR_TRY(pool().take(dev, &p, size));
+        ptrs.emplace_back(p, size);
         *out = static_cast<T*>(p);
         return SAR_OK;
     }
+    hipStream_t st;
+    int dev;
+    std::vector<std::pair<void*, size_t>> ptrs;
 };
 
-// out[k] = sum of in[0..k) for k in [0,n); in may equal out.
-int exclusive_scan(const int32_t* in, int32_t* out, int64_t n, hipStream_t st, DeviceTemps& tmp)
+// out[k] = base + sum of in[0..k) for k in [0,n); in may equal out.
+int exclusive_scan(const int32_t* in, int32_t* out, int64_t n, hipStream_t st, DeviceTemps& tmp, int32_t base = 0)
 {
     if (n <= 0) return SAR_OK;
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
     if (tiles == 1) {
-        k_tile_scan<<<1, kThreads, 0, st>>>(in, n, nullptr, out);
+        k_tile_scan<<<1, kThreads, 0, st>>>(in, n, nullptr, base, out);
         SAR_LAUNCH_CHECK();
         return SAR_OK;
     }
@@ -130,7 +218,7 @@ int exclusive_scan(const int32_t* in, int32_t* out, int64_t n, hipStream_t st, D
     k_tile_reduce<<<(unsigned)tiles, kThreads, 0, st>>>(in, n, sums);
     SAR_LAUNCH_CHECK();
     SAR_TRY(exclusive_scan(sums, sums, tiles, st, tmp));
-    k_tile_scan<<<(unsigned)tiles, kThreads, 0, st>>>(in, n, sums, out);
+    k_tile_scan<<<(unsigned)tiles, kThreads, 0, st>>>(in, n, sums, base, out);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
@@ -160,11 +248,11 @@ __global__ __launch_bounds__(kThreads) void k_part_tile_count(const int32_t* __r
     if ((int)threadIdx.x < P) tile_counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = hist[threadIdx.x];
 }
 
-// lid[v] = number of nodes u < v in the same partition as v.
+// code[v] = (partition of v << tag_shift) | number of nodes u < v in the same partition.
 __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restrict__ part, int64_t N,
                                                         int P, int64_t n_tiles,
-                                                        const int32_t* __restrict__ tile_base,
-                                                        int32_t* __restrict__ lid)
+                                                        const int32_t* __restrict__ tile_base, int tag_shift,
+                                                        uint32_t* __restrict__ code)
 {
     constexpr int kRounds = kPartTile / kThreads;
     constexpr int kChunks = kPartTile / 64;
@@ -206,61 +294,546 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
         int pre = 0;
         for (int c = 0; c < chunk; ++c) pre += cnt[c][pv[r]];
         const int64_t col = (int64_t)pv[r] * n_tiles;
-        lid[v] = tile_base[col + blockIdx.x] - tile_base[col] + pre + rank[r];
+        code[v] = ((uint32_t)pv[r] << tag_shift) | (uint32_t)(tile_base[col + blockIdx.x] - tile_base[col] + pre + rank[r]);
     }
 }
 
-// ------------------------------------------------------ edges -> blocks
+// ------------------------------------------------------ buckets of keys
+//
+// Both indexes of a block are (key, value) pairs grouped by key with every group ascending: the CSR
+// has key = row (block q, destination) and value = source, its transpose key = source and value =
+// destination.  Counters in memory, one atomic per pair, serialise on the frequent keys of a
+// power-law graph (15.2M edges: count 3.2 ms, scatter 2.1 ms for the CSR, 1.9 + 2.2 ms for the
+// transposes, and as many passes again through cursors).  Here the pairs first go to buckets of up to
+// 2^w keys and 4 thousand pairs on average: every tile of the input counts its pairs per bucket in
+// LDS, one scan over the [bucket][tile] counts gives each tile its place in each bucket, and the
+// tile's pairs are written there.  Then a workgroup takes a bucket: counts its keys in LDS; and, with
+// the offsets of all keys scanned, places its values in LDS, sorts the groups there and writes them
+// out in order.  No atomic leaves the LDS, and what is written does not depend on scheduling.
+// The keys are dealt to the buckets in runs of four: neighbouring keys are often frequent together
+// (ids in the order of degree), and a bucket of the 1024 most frequent rows of that graph holds half a
+// million pairs (641 us for one workgroup, and 14 ms to sort its rows).
+// What the kernels now take on those 15.2M edges: pairs to buckets 218 + 222 us from the edge list (the
+// gathers of the nodes' codes) and 30 + 196 us from the CSR, keys 31, finish 374 each; of the last,
+// 140 us are the few hundred rows of more than 256 values and the rest the stores of short runs.
 
-template <typename IdxT>
-__global__ __launch_bounds__(kThreads) void k_edge_count(const IdxT* __restrict__ src,
-                                                         const IdxT* __restrict__ dst, int64_t E,
-                                                         const int32_t* __restrict__ part, int64_t N,
-                                                         int p, const int32_t* __restrict__ lid,
-                                                         int64_t n_dst, int32_t* __restrict__ row_cnt,
-                                                         unsigned long long* __restrict__ kept,
-                                                         int* __restrict__ err)
+constexpr int kBucketThreads = 512;
+constexpr int kRunBits = 2;             // runs of four keys
+constexpr int kBucketSub = 2048;         // input is taken 2048 pairs at a time
+constexpr int kMaxBucketBits = 13;       // keys of a bucket: LDS counters of 32 KB at most
+constexpr int kBucketCap = 10240;        // values of a bucket that are placed and sorted in LDS
+constexpr int kRankLanes = 16;           // groups up to this length are sorted by 16 lanes
+constexpr int kWaveSort = 256;           //            up to this length by one wavefront
+constexpr int64_t kKeysPerPass = (int64_t)1 << 28;      // at most 32768 buckets at once
+constexpr int64_t kMaxBucketCounts = (int64_t)1 << 25;  // entries of the [bucket][tile] counts
+
+struct BucketPlan {
+    int w;                   // log2 of the keys a bucket has room for
+    int nb;                  // log2 of the buckets
+    int64_t tile, n_tiles;   // pairs (input elements) per tile, a multiple of kBucketSub
+    int n_buckets() const { return 1 << nb; }
+};
+
+// Key k of a pass sits in bucket `bucket` at place `place`; key_at is the inverse.
+struct Deal {
+    int nb;
+    __device__ inline int bucket(int64_t key) const { return (int)(key >> kRunBits) & ((1 << nb) - 1); }
+    __device__ inline int place(int64_t key) const
+    {
+        return ((int)(key >> (kRunBits + nb)) << kRunBits) | (int)(key & ((1 << kRunBits) - 1));
+    }
+    __device__ inline int64_t key_at(int bucket, int place) const
+    {
+        return ((((int64_t)(place >> kRunBits) << nb) | bucket) << kRunBits) | (place & ((1 << kRunBits) - 1));
+    }
+};
+
+// n_keys <= kKeysPerPass.
+BucketPlan plan_buckets(int64_t n_keys, int64_t n_items)
 {
-    unsigned long long mine = 0;
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < E;
-         e += (int64_t)gridDim.x * kThreads) {
+    BucketPlan b;
+    const int64_t per = std::min<int64_t>(4096, std::max<int64_t>(256, n_items / 1024));
+    const int64_t want = n_items / per + 1;
+    b.nb = 0;
+    // as many buckets as wanted, while each has a run; more where a bucket could not count its keys
+    while (((int64_t)1 << b.nb) < want && ((int64_t)1 << (b.nb + kRunBits)) < n_keys && b.nb < 15) ++b.nb;
+    while (((int64_t)1 << (b.nb + kMaxBucketBits)) < n_keys) ++b.nb;
+    b.w = kRunBits;
+    while (((int64_t)1 << (b.nb + b.w)) < n_keys) ++b.w;
+    // about a thousand tiles, fewer where the counts would not fit
+    const int64_t tiles = std::min<int64_t>(1024, std::max<int64_t>(1, kMaxBucketCounts >> b.nb));
+    b.tile = std::max<int64_t>(1, (n_items + tiles - 1) / tiles);
+    b.tile = (b.tile + kBucketSub - 1) / kBucketSub * kBucketSub;
+    b.n_tiles = std::max<int64_t>(1, (n_items + b.tile - 1) / b.tile);
+    return b;
+}
+
+// A pair as it travels: the key's place in its bucket above `vbits` bits of value; 32 bits where
+// that fits, else 64.
+template <typename PairT>
+__device__ inline PairT make_pair(int key_in_bucket, uint32_t value, int vbits)
+{
+    return ((PairT)(uint32_t)key_in_bucket << vbits) | (PairT)value;
+}
+
+// The edges of worker p as pairs (q n_dst + destination, source), both local ids.  code[v] =
+// (partition << tag_shift) | local id.
+template <typename IdxT>
+struct EdgeSource {
+    const IdxT* src;
+    const IdxT* dst;
+    const uint32_t* code;
+    int64_t E, N, n_dst;
+    int p, tag_shift;
+    int* err;
+    __device__ inline bool get(int64_t e, int64_t& key, uint32_t& value) const
+    {
         const int64_t d = (int64_t)dst[e], s = (int64_t)src[e];
         if (d < 0 || d >= N || s < 0 || s >= N) {
             atomicOr(err, 2);
-            continue;
+            return false;
         }
-        if (part[d] != p) continue;
-        atomicAdd(&row_cnt[(int64_t)part[s] * n_dst + lid[d]], 1);
-        ++mine;
+        const uint32_t cd = code[d];
+        if ((int)(cd >> tag_shift) != p) return false;
+        const uint32_t cs = code[s], mask = (1u << tag_shift) - 1u;
+        key = (int64_t)(cs >> tag_shift) * n_dst + (int64_t)(cd & mask);
+        value = cs & mask;
+        return true;
     }
-    // edges kept for this worker, in 64 bits: the 32-bit offsets that follow must not wrap
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(kept, mine);
-}
+};
 
-// Uses row_cnt as a countdown cursor: slot order inside a row is arbitrary
-// here and fixed by the sort that follows.
-template <typename IdxT>
-__global__ __launch_bounds__(kThreads) void k_edge_scatter(const IdxT* __restrict__ src,
-                                                           const IdxT* __restrict__ dst, int64_t E,
-                                                           const int32_t* __restrict__ part,
-                                                           int64_t N, int p,
-                                                           const int32_t* __restrict__ lid,
-                                                           int64_t n_dst, int32_t* __restrict__ row_cnt,
-                                                           const int32_t* __restrict__ row_off,
-                                                           int32_t* __restrict__ indices_all)
+template <typename Src>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t tile, int64_t n_tiles, int64_t key0,
+                                                                 int64_t n_keys, Deal deal,
+                                                                 int32_t* __restrict__ counts,
+                                                                 unsigned long long* __restrict__ kept)
 {
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < E;
-         e += (int64_t)gridDim.x * kThreads) {
-        const int64_t d = (int64_t)dst[e], s = (int64_t)src[e];
-        if (d < 0 || d >= N || s < 0 || s >= N) continue;
-        if (part[d] != p) continue;
-        const int64_t r = (int64_t)part[s] * n_dst + lid[d];
-        const int pos = atomicSub(&row_cnt[r], 1) - 1;
-        indices_all[(int64_t)row_off[r] + pos] = lid[s];
+    extern __shared__ int bucket_hist[];
+    const int n_buckets = 1 << deal.nb;
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) bucket_hist[b] = 0;
+    __syncthreads();
+    const int64_t beg = (int64_t)blockIdx.x * tile, end = min(in.E, beg + tile);
+    unsigned long long mine = 0;
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
+        int64_t key;
+        uint32_t value;
+        if (!in.get(e, key, value)) continue;
+        ++mine;
+        key -= key0;
+        if (key >= 0 && key < n_keys) atomicAdd(&bucket_hist[deal.bucket(key)], 1);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
+    // edges kept for this worker, in 64 bits: the 32-bit offsets that follow must not wrap
+    if (kept) {
+        for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+        if ((threadIdx.x & 63) == 0 && mine) atomicAdd(kept, mine);
     }
 }
 
+template <typename Src, typename PairT>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Src in, int64_t tile, int64_t n_tiles, int64_t key0,
+                                                                   int64_t n_keys, Deal deal, int vbits,
+                                                                   const int32_t* __restrict__ offsets,
+                                                                   PairT* __restrict__ pairs)
+{
+    extern __shared__ int bucket_cursor[];
+    const int n_buckets = 1 << deal.nb;
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads)
+        bucket_cursor[b] = offsets[(int64_t)b * n_tiles + blockIdx.x];
+    __syncthreads();
+    const int64_t beg = (int64_t)blockIdx.x * tile, end = min(in.E, beg + tile);
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
+        int64_t key;
+        uint32_t value;
+        if (!in.get(e, key, value)) continue;
+        key -= key0;
+        if (key < 0 || key >= n_keys) continue;
+        pairs[atomicAdd(&bucket_cursor[deal.bucket(key)], 1)] = make_pair<PairT>(deal.place(key), value, vbits);
+    }
+}
+
+// What the builder's kernels need of every block, in device memory.
+struct BlkDev {
+    const int32_t* indptr;
+    const int32_t* indices;
+    int64_t n_src, coff;     // sources of the block, and of the blocks before it
+    int64_t nnz, nnz0;       // edges of the block, and of the blocks before it
+    int64_t tile0;           // first tile of the block (k_block_count / k_block_scatter)
+    uint32_t* rows;          // launch lists
+    uint32_t* t_rows;
+    int32_t* t_indptr;
+    int32_t* t_rank;
+};
+
+// The edges of all blocks as pairs (coff[q] + source, destination): a tile lies inside one block.
+__device__ inline int block_of_tile(const BlkDev* blk, int P, int64_t tile)
+{
+    int lo = 0, hi = P - 1;      // the last block that starts at or before the tile and has tiles
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (blk[mid].tile0 <= tile)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kBucketThreads) void k_block_count(const BlkDev* __restrict__ blk, int P, int64_t tile,
+                                                                int64_t n_tiles, int64_t key0, int64_t n_keys, Deal deal,
+                                                                int32_t* __restrict__ counts)
+{
+    extern __shared__ int bucket_hist[];
+    const int n_buckets = 1 << deal.nb;
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) bucket_hist[b] = 0;
+    __syncthreads();
+    const BlkDev& B = blk[block_of_tile(blk, P, blockIdx.x)];
+    const int64_t beg = ((int64_t)blockIdx.x - B.tile0) * tile, end = min(B.nnz, beg + tile);
+    const int64_t first = B.coff - key0;
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
+        const int64_t key = first + B.indices[e];
+        if (key >= 0 && key < n_keys) atomicAdd(&bucket_hist[deal.bucket(key)], 1);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
+}
+
+// The destination of an edge is the row whose range holds it: the rows that start inside the 2048
+// edges at hand mark their first edge, and a running maximum over the marks names every edge's row.
+template <typename PairT>
+__global__ __launch_bounds__(kBucketThreads) void k_block_scatter(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
+                                                                  int64_t tile, int64_t n_tiles, int64_t key0,
+                                                                  int64_t n_keys, Deal deal, int vbits,
+                                                                  const int32_t* __restrict__ offsets,
+                                                                  PairT* __restrict__ pairs)
+{
+    constexpr int kPer = kBucketSub / kBucketThreads;
+    constexpr int kWaves = kBucketThreads / 64;
+    extern __shared__ int bucket_cursor[];
+    __shared__ int mark[kBucketSub];
+    __shared__ int wave_max[kWaves];
+    __shared__ int first_row;
+    const int n_buckets = 1 << deal.nb;
+    for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads)
+        bucket_cursor[b] = offsets[(int64_t)b * n_tiles + blockIdx.x];
+    const BlkDev& B = blk[block_of_tile(blk, P, blockIdx.x)];
+    const int64_t t_beg = ((int64_t)blockIdx.x - B.tile0) * tile, t_end = min(B.nnz, t_beg + tile);
+    const int64_t first = B.coff - key0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int64_t beg = t_beg; beg < t_end; beg += kBucketSub) {
+        const int n = (int)min((int64_t)kBucketSub, t_end - beg);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int64_t lo = 0, hi = n_dst - 1;      // the last row that starts at or before `beg`
+            while (lo < hi) {
+                const int64_t mid = (lo + hi + 1) / 2;
+                if (B.indptr[mid] <= beg)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            first_row = (int)lo;
+        }
+        for (int k = threadIdx.x; k < kBucketSub; k += kBucketThreads) mark[k] = 0;
+        __syncthreads();
+        const int r0 = first_row;
+        for (int64_t r = r0 + 1 + threadIdx.x; r < n_dst; r += kBucketThreads) {
+            const int64_t at = B.indptr[r] - beg;
+            if (at >= n) break;
+            atomicMax(&mark[at], (int)(r - r0));
+        }
+        __syncthreads();
+        int v[kPer], run = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            run = max(run, mark[threadIdx.x * kPer + k]);
+            v[k] = run;
+        }
+        int incl = run;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(incl, o);
+            if (lane >= o) incl = max(incl, x);
+        }
+        if (lane == 63) wave_max[wave] = incl;
+        __syncthreads();
+        int before = __shfl_up(incl, 1);
+        if (lane == 0) before = 0;
+        for (int k = 0; k < wave; ++k) before = max(before, wave_max[k]);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) mark[threadIdx.x * kPer + k] = max(before, v[k]);
+        __syncthreads();
+        for (int k = threadIdx.x; k < n; k += kBucketThreads) {
+            const int64_t key = first + B.indices[beg + k];
+            if (key < 0 || key >= n_keys) continue;
+            pairs[atomicAdd(&bucket_cursor[deal.bucket(key)], 1)] =
+                make_pair<PairT>(deal.place(key), (uint32_t)(r0 + mark[k]), vbits);
+        }
+    }
+}
+
+// Ascending sort of a[0, len) by the threads `tid` of `nt`: a bitonic network in which every
+// comparator is ascending, so the virtual +inf padding behind the end never moves.
+template <typename Sync>
+__device__ inline void bitonic(int32_t* a, int len, int tid, int nt, Sync&& sync)
+{
+    int n2 = 1;
+    while (n2 < len) n2 <<= 1;
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const bool flip = j == (k >> 1);
+            for (int t = tid; t < n2; t += nt) {
+                const int partner = flip ? (t ^ (k - 1)) : (t ^ j);
+                if (partner > t && partner < len) {
+                    const int32_t x = a[t], y = a[partner];
+                    if (x > y) {
+                        a[t] = y;
+                        a[partner] = x;
+                    }
+                }
+            }
+            sync();
+        }
+    }
+}
+
+// Values among the 16 of a DPP row that sort before this lane's (equal ones by lane).
+template <int J>
+__device__ inline int rank16_step(int32_t x, int l)
+{
+    if constexpr (J == 0) {
+        return 0;
+    } else {
+        const int32_t y = __builtin_amdgcn_update_dpp(0, x, 0x120 + J, 0xf, 0xf, false);   // row_ror:J
+        const int from = (l - J) & 15;
+        return rank16_step<J - 1>(x, l) + ((y < x || (y == x && from < l)) ? 1 : 0);
+    }
+}
+__device__ inline int rank16(int32_t x, int l) { return rank16_step<15>(x, l); }
+
+// Ascending order of a[0, len), len <= 64 N, by one wavefront: every value goes to the place that the
+// count of the values before it gives it -- smaller ones, and equal ones at lower indexes: for values
+// x at index i and y at j, y goes first if y < x + (j < i).
+template <int N>
+__device__ inline void rank_sort_wave(int32_t* a, int len, int lane)
+{
+    int32_t x[N];
+    int rank[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        x[r] = a[min(r * 64 + lane, len - 1)];
+        rank[r] = 0;
+    }
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+        const int n = min(64, len - b * 64);
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) {
+            const int32_t y = a[b * 64 + j];
+#pragma unroll
+            for (int r = 0; r < N; ++r) {
+                const int32_t bound = b < r ? x[r] + 1 : b > r ? x[r] : x[r] + (j < lane ? 1 : 0);
+                rank[r] += y < bound ? 1 : 0;
+            }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reads stay ahead of the writes
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+        if (r * 64 + lane < len) a[rank[r]] = x[r];
+}
+
+// Ascending order of a[0, len) in LDS by a workgroup of THREADS, len <= kMergeSort: wavefronts sort
+// pieces of 256, then pairs of sorted runs are merged in place, every value finding its place by a
+// search in the other run.  (A bitonic network spends most of its time in barriers.)
+constexpr int kMergeSort = 4096;
+template <int THREADS>
+__device__ inline void merge_sort(int32_t* a, int len)
+{
+    constexpr int kPer = kMergeSort / THREADS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int c = wave * kWaveSort; c < len; c += THREADS / 64 * kWaveSort)
+        rank_sort_wave<kWaveSort / 64>(a + c, min(kWaveSort, len - c), lane);
+    __syncthreads();
+    for (int width = kWaveSort; width < len; width *= 2) {
+        int32_t x[kPer];
+        int to[kPer];
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            const int e = r * THREADS + threadIdx.x;
+            to[r] = -1;
+            x[r] = 0;
+            if (e >= len) continue;
+            x[r] = a[e];
+            const int run = e / width, other = (run ^ 1) * width;
+            int lo = 0, hi = min(width, max(0, len - other));
+            const int32_t bound = x[r] + (run & 1);          // of equal values the first run's go first
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (a[other + mid] < bound)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
+            to[r] = (run & ~1) * width + (e - run * width) + lo;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPer; ++r)
+            if (to[r] >= 0) a[to[r]] = x[r];
+        __syncthreads();
+    }
+}
+
+// off[key] = pairs of the key, for every key of the pass: a workgroup per bucket.
+template <typename PairT>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_keys(const PairT* __restrict__ pairs,
+                                                                const int32_t* __restrict__ offsets, int64_t n_tiles,
+                                                                int w, Deal deal, int64_t n_keys, int vbits,
+                                                                int32_t* __restrict__ off)
+{
+    extern __shared__ int bucket_lds[];
+    const int n_slots = 1 << w, b = blockIdx.x;
+    for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) bucket_lds[k] = 0;
+    __syncthreads();
+    const int beg = offsets[(int64_t)b * n_tiles], end = offsets[(int64_t)(b + 1) * n_tiles];
+    for (int e = beg + threadIdx.x; e < end; e += kBucketThreads) atomicAdd(&bucket_lds[(int)(pairs[e] >> vbits)], 1);
+    __syncthreads();
+    for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) {
+        const int64_t key = deal.key_at(b, k);
+        if (key < n_keys) off[key] = bucket_lds[k];
+    }
+}
+
+// One bucket per workgroup: its values in order at off[key], each group ascending.  A bucket of more
+// than kBucketCap pairs is placed in memory directly and listed for k_sort_buckets.
+template <typename PairT>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_finish(const PairT* __restrict__ pairs,
+                                                                  const int32_t* __restrict__ offsets, int64_t n_tiles,
+                                                                  int w, Deal deal, int64_t n_keys, int vbits,
+                                                                  const int32_t* __restrict__ off,
+                                                                  int32_t* __restrict__ values,
+                                                                  int32_t* __restrict__ big_list,
+                                                                  int* __restrict__ big_count)
+{
+    constexpr int kWaves = kBucketThreads / 64;
+    constexpr int kRunLanes = 16;
+    extern __shared__ int bucket_lds[];
+    __shared__ int wave_sum[kWaves];
+    __shared__ int n_listed, n_big;
+    __shared__ uint16_t listed[kBucketCap / kRankLanes];
+    __shared__ uint16_t big[kBucketCap / kWaveSort];
+    const int n_slots = 1 << w;
+    int* cnt = bucket_lds;
+    int32_t* vals = bucket_lds + n_slots;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int beg = offsets[(int64_t)b * n_tiles], end = offsets[(int64_t)(b + 1) * n_tiles], n = end - beg;
+    const PairT vmask = (PairT)(((uint64_t)1 << vbits) - 1u);
+    if (n == 0) return;
+    if (n > kBucketCap) {
+        for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) {
+            const int64_t key = deal.key_at(b, k);
+            cnt[k] = key < n_keys ? off[key] : 0;
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < n; e += kBucketThreads) {
+            const PairT x = pairs[beg + e];
+            values[atomicAdd(&cnt[(int)(x >> vbits)], 1)] = (int32_t)(x & vmask);
+        }
+        if (threadIdx.x == 0) big_list[atomicAdd(big_count, 1)] = b;
+        return;
+    }
+    if (threadIdx.x == 0) n_listed = n_big = 0;
+    for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) {
+        const int64_t key = deal.key_at(b, k);
+        cnt[k] = key < n_keys ? off[key + 1] - off[key] : 0;
+    }
+    __syncthreads();
+    const int per = (n_slots + kBucketThreads - 1) / kBucketThreads;
+    int sum = 0;
+    for (int k = 0; k < per; ++k) {
+        const int at = threadIdx.x * per + k;
+        if (at < n_slots) sum += cnt[at];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int k = 0; k < wave; ++k) run += wave_sum[k];
+    for (int k = 0; k < per; ++k) {
+        const int at = threadIdx.x * per + k;
+        if (at < n_slots) {
+            const int c = cnt[at];
+            cnt[at] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    // each group's start is its cursor; afterwards it is the group's end
+    for (int e = threadIdx.x; e < n; e += kBucketThreads) {
+        const PairT x = pairs[beg + e];
+        vals[atomicAdd(&cnt[(int)(x >> vbits)], 1)] = (int32_t)(x & vmask);
+    }
+    __syncthreads();
+    // Groups of up to 16 values: a DPP row of 16 lanes each, a lane's value goes to the place that the
+    // count of smaller ones gives it; the others' values come by rotation, without LDS.
+    for (int k0 = threadIdx.x / kRankLanes; k0 < n_slots; k0 += kBucketThreads / kRankLanes) {
+        const int s = k0 ? cnt[k0 - 1] : 0, len = cnt[k0] - s, l = threadIdx.x % kRankLanes;
+        if (len > kWaveSort) {
+            if (l == 0) big[atomicAdd(&n_big, 1)] = (uint16_t)k0;
+        } else if (len > kRankLanes) {
+            if (l == 0) listed[atomicAdd(&n_listed, 1)] = (uint16_t)k0;
+        } else if (len > 1) {
+            const int32_t x = l < len ? vals[s + l] : 0x7fffffff;
+            const int rank = rank16(x, l);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reads stay ahead of the writes
+            if (l < len) vals[s + rank] = x;
+        }
+    }
+    __syncthreads();
+    // up to 256: a wavefront each, one to four values to a lane
+    for (int i = wave; i < n_listed; i += kWaves) {
+        const int k = __builtin_amdgcn_readfirstlane(listed[i]);
+        const int s = k ? cnt[k - 1] : 0, len = __builtin_amdgcn_readfirstlane(cnt[k] - s);
+        if (len <= 64)
+            rank_sort_wave<1>(vals + s, len, lane);
+        else if (len <= 128)
+            rank_sort_wave<2>(vals + s, len, lane);
+        else
+            rank_sort_wave<4>(vals + s, len, lane);
+    }
+    __syncthreads();
+    for (int i = 0; i < n_big; ++i) {
+        const int k = big[i], s = k ? cnt[k - 1] : 0, len = cnt[k] - s;
+        if (len <= kMergeSort)
+            merge_sort<kBucketThreads>(vals + s, len);
+        else
+            bitonic(vals + s, len, threadIdx.x, kBucketThreads, [] { __syncthreads(); });
+    }
+    __syncthreads();
+    // a run of keys is contiguous here and there
+    for (int r = threadIdx.x / kRunLanes; r < n_slots >> kRunBits; r += kBucketThreads / kRunLanes) {
+        const int k0 = r << kRunBits, s = k0 ? cnt[k0 - 1] : 0, len = cnt[k0 + (1 << kRunBits) - 1] - s;
+        if (len == 0) continue;
+        int32_t* const out = values + off[deal.key_at(b, k0)];
+        for (int e = threadIdx.x % kRunLanes; e < len; e += kRunLanes) out[e] = vals[s + e];
+    }
+}
+
+// out[k] = in[k * step] for k in [0, n]
+__global__ __launch_bounds__(kThreads) void k_every(const int32_t* __restrict__ in, int64_t step, int n,
+                                                    int32_t* __restrict__ out)
+{
+    for (int k = threadIdx.x; k <= n; k += kThreads) out[k] = in[k * step];
+}
+
+// indptr of block q out of the offsets of all blocks' rows
 __global__ __launch_bounds__(kThreads) void k_make_indptr(const int32_t* __restrict__ row_off,
                                                           int64_t n_dst, int P,
                                                           int32_t* __restrict__ indptr_all)
@@ -273,137 +846,119 @@ __global__ __launch_bounds__(kThreads) void k_make_indptr(const int32_t* __restr
     }
 }
 
-// ------------------------------------------------------------ row sorting
-
-__global__ __launch_bounds__(kThreads) void k_sort_short(const int32_t* __restrict__ off,
-                                                         int64_t n_rows, int32_t* __restrict__ data,
-                                                         int32_t* __restrict__ long_list,
-                                                         int* __restrict__ long_count)
-{
-    for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r < n_rows;
-         r += (int64_t)gridDim.x * kThreads) {
-        const int beg = off[r], len = off[r + 1] - beg;
-        if (len <= 1) continue;
-        if (len > kShortSort) {
-            long_list[atomicAdd(long_count, 1)] = (int32_t)r;
-            continue;
-        }
-        int32_t* a = data + beg;
-        for (int k = 1; k < len; ++k) {
-            const int32_t x = a[k];
-            int m = k - 1;
-            while (m >= 0 && a[m] > x) {
-                a[m + 1] = a[m];
-                --m;
-            }
-            a[m + 1] = x;
-        }
-    }
-}
-
-// One workgroup per listed row: bitonic network in which every comparator is
-// ascending, so the virtual +inf padding behind the row never moves.
-__global__ __launch_bounds__(kThreads) void k_sort_long(const int32_t* __restrict__ off,
-                                                        int32_t* __restrict__ data,
-                                                        const int32_t* __restrict__ long_list,
-                                                        const int* __restrict__ long_count)
+// The groups of the listed buckets (those too large for k_bucket_finish), gridDim.y workgroups a bucket.
+__global__ __launch_bounds__(kThreads) void k_sort_buckets(const int32_t* __restrict__ off, int32_t* __restrict__ data,
+                                                           int w, Deal deal, int64_t n_keys,
+                                                           const int32_t* __restrict__ big_list,
+                                                           const int* __restrict__ big_count)
 {
     __shared__ int32_t buf[kLdsSort];
-    const int n_list = *long_count;
-    for (int w = blockIdx.x; w < n_list; w += gridDim.x) {
-        const int64_t r = long_list[w];
-        const int beg = off[r], len = off[r + 1] - beg;
-        int32_t* g = data + beg;
-        const bool in_lds = len <= kLdsSort;
-        int32_t* a = in_lds ? buf : g;
-        if (in_lds) {
-            for (int t = threadIdx.x; t < len; t += kThreads) buf[t] = g[t];
-        }
-        __syncthreads();
-        int n2 = 1;
-        while (n2 < len) n2 <<= 1;
-        for (int k = 2; k <= n2; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const bool flip = (j == (k >> 1));
-                for (int t = threadIdx.x; t < n2; t += kThreads) {
-                    const int partner = flip ? (t ^ (k - 1)) : (t ^ j);
-                    if (partner > t && partner < len) {
-                        const int32_t x = a[t], y = a[partner];
-                        if (x > y) {
-                            a[t] = y;
-                            a[partner] = x;
-                        }
-                    }
-                }
-                __syncthreads();
+    const int n_list = *big_count;
+    for (int i = blockIdx.x; i < n_list; i += gridDim.x) {
+        for (int k = blockIdx.y; k < (1 << w); k += gridDim.y) {
+            const int64_t key = deal.key_at(big_list[i], k);
+            if (key >= n_keys) continue;
+            const int beg = off[key], len = off[key + 1] - beg;
+            if (len <= 1) continue;
+            int32_t* g = data + beg;
+            const bool in_lds = len <= kLdsSort;
+            __syncthreads();
+            if (in_lds) {
+                for (int t = threadIdx.x; t < len; t += kThreads) buf[t] = g[t];
+            }
+            __syncthreads();
+            if (len <= kMergeSort)
+                merge_sort<kThreads>(buf, len);
+            else
+                bitonic(in_lds ? buf : g, len, threadIdx.x, kThreads, [] { __syncthreads(); });
+            if (in_lds) {
+                for (int t = threadIdx.x; t < len; t += kThreads) g[t] = buf[t];
             }
         }
-        if (in_lds) {
-            for (int t = threadIdx.x; t < len; t += kThreads) g[t] = buf[t];
-        }
-        __syncthreads();
     }
-}
-
-int sort_rows(const int32_t* off, int64_t n_rows, int32_t* data, int64_t nnz, hipStream_t st,
-              DeviceTemps& tmp)
-{
-    if (n_rows <= 0 || nnz <= 1) return SAR_OK;
-    const int64_t cap = nnz / (kShortSort + 1) + 1;
-    int32_t* list = nullptr;
-    int* count = nullptr;
-    SAR_TRY(tmp.alloc(&list, cap));
-    SAR_TRY(tmp.alloc(&count, 1));
-    SAR_HIP(hipMemsetAsync(count, 0, sizeof(int), st));
-    const unsigned g1 = (unsigned)std::min<int64_t>((n_rows + kThreads - 1) / kThreads, 1 << 20);
-    k_sort_short<<<g1, kThreads, 0, st>>>(off, n_rows, data, list, count);
-    SAR_LAUNCH_CHECK();
-    const unsigned g2 = (unsigned)std::min<int64_t>(cap, 16384);
-    k_sort_long<<<g2, kThreads, 0, st>>>(off, data, list, count);
-    SAR_LAUNCH_CHECK();
-    return SAR_OK;
 }
 
 // ------------------------------------------------- degree-class row lists
 
 __device__ inline int degree_class(int len) { return len <= 0 ? 0 : 32 - __clz(len); }
 
-__global__ __launch_bounds__(kThreads) void k_class_hist(const int32_t* __restrict__ off, int64_t n,
-                                                         int* __restrict__ hist)
+// hist[y][class] over the rows of offset array y: the blocks' own, their transposes', or one given array.
+enum class Lists { kRows, kSources, kAllRows, kAllSources };
+struct ListIn {
+    const BlkDev* blk;
+    const int32_t* off;      // kAllRows: the all-blocks row offsets
+    int64_t n_dst;
+    __device__ inline const int32_t* offsets(Lists l, int y, int64_t& n) const
+    {
+        const bool sources = l == Lists::kSources || l == Lists::kAllSources;
+        n = sources ? blk[y].n_src : n_dst;
+        return l == Lists::kAllRows ? off : sources ? blk[y].t_indptr : blk[y].indptr;
+    }
+};
+
+__global__ __launch_bounds__(kThreads) void k_class_hist(ListIn in, Lists l, int* __restrict__ hist_all)
 {
     __shared__ int h[sar::kNumClasses];
     if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
     __syncthreads();
-    for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r < n;
-         r += (int64_t)gridDim.x * kThreads) {
-        atomicAdd(&h[degree_class(off[r + 1] - off[r])], 1);
+    int64_t n;
+    const int32_t* off = in.offsets(l, blockIdx.y, n);
+    // most rows of a block fall into a few classes: the lanes of a class count themselves together
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t r0 = (int64_t)blockIdx.x * kThreads; r0 < n; r0 += stride) {
+        const int64_t r = r0 + threadIdx.x;
+        const int c = r < n ? degree_class(off[r + 1] - off[r]) : -1;
+        unsigned long long todo = __ballot(c >= 0);
+        while (todo) {
+            const int first = __ffsll((long long)todo) - 1;
+            const unsigned long long same = __ballot(c == __shfl(c, first));
+            if ((int)(threadIdx.x & 63) == first) atomicAdd(&h[c], __popcll(same));
+            todo &= ~same;
+        }
     }
     __syncthreads();
+    int* hist = hist_all + blockIdx.y * sar::kNumClasses;
     if (threadIdx.x < sar::kNumClasses && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
 // cursor[c] starts at the first slot of class c; value written = r | tag.
-// Rows without edges (class 0) are listed last, and only if with_empty.
-__global__ __launch_bounds__(kThreads) void k_class_place(const int32_t* __restrict__ off, int64_t n,
-                                                          int* __restrict__ cursor, uint32_t tag,
-                                                          bool with_empty, uint32_t* __restrict__ out)
+// Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.
+__global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, int tag_shift, int* __restrict__ cursors,
+                                                          uint32_t* __restrict__ out_all)
 {
     __shared__ int h[sar::kNumClasses];
     __shared__ int base[sar::kNumClasses];
-    const int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
-    __syncthreads();
-    int c = -1, local = 0;
-    if (r < n) {
-        c = degree_class(off[r + 1] - off[r]);
-        if (c == 0 && !with_empty) c = -1;
-        if (c >= 0) local = atomicAdd(&h[c], 1);
+    int64_t n;
+    const int32_t* off = in.offsets(l, blockIdx.y, n);
+    int* cursor = cursors + (l == Lists::kRows || l == Lists::kSources ? blockIdx.y * sar::kNumClasses : 0);
+    uint32_t* out = l == Lists::kRows ? in.blk[blockIdx.y].rows : l == Lists::kSources ? in.blk[blockIdx.y].t_rows : out_all;
+    const uint32_t tag = l == Lists::kAllSources ? (uint32_t)blockIdx.y << tag_shift : 0u;
+    const int lane = threadIdx.x & 63;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t r0 = (int64_t)blockIdx.x * kThreads; r0 < n; r0 += stride) {
+        if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
+        __syncthreads();
+        const int64_t r = r0 + threadIdx.x;
+        int c = r < n ? degree_class(off[r + 1] - off[r]) : -1;
+        if (c == 0 && l == Lists::kRows) c = -1;
+        int local = 0;
+        unsigned long long todo = __ballot(c >= 0);
+        while (todo) {
+            const int first = __ffsll((long long)todo) - 1;
+            const unsigned long long same = __ballot(c == __shfl(c, first));
+            int start = 0;
+            if (lane == first) start = atomicAdd(&h[c], __popcll(same));
+            start = __shfl(start, first);
+            if ((same >> lane) & 1) local = start + __popcll(same & ((1ull << lane) - 1ull));
+            todo &= ~same;
+        }
+        __syncthreads();
+        if (threadIdx.x < sar::kNumClasses && h[threadIdx.x])
+            base[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]);
+        __syncthreads();
+        if (c >= 0) out[base[c] + local] = (uint32_t)r | tag;
+        __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x < sar::kNumClasses && h[threadIdx.x])
-        base[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]);
-    __syncthreads();
-    if (c >= 0) out[base[c] + local] = (uint32_t)r | tag;
 }
 
 struct ClassLayout {
@@ -459,8 +1014,8 @@ __global__ __launch_bounds__(kThreads) void k_single_list(SingleTabs tabs, const
                                                           const uint32_t* __restrict__ f_indices, int64_t n_dst,
                                                           int tag_shift, int32_t* __restrict__ cnt,
                                                           const int32_t* __restrict__ off,
-                                                          int32_t* __restrict__ s_dst, uint32_t* __restrict__ s_src,
-                                                          int32_t* __restrict__ s_row)
+                                                          int64_t n_single, int32_t* __restrict__ s_dst,
+                                                          uint32_t* __restrict__ s_src, int32_t* __restrict__ s_row)
 {
     __shared__ const int32_t* ip[SAR_MAX_BLOCKS];
     __shared__ const int32_t* rk[SAR_MAX_BLOCKS];
@@ -488,9 +1043,11 @@ __global__ __launch_bounds__(kThreads) void k_single_list(SingleTabs tabs, const
             const unsigned long long votes = __ballot(single);
             if (FILL && single) {
                 const int mine = at + __popcll(votes & ((1ull << lane) - 1ull));
-                s_dst[mine] = (int32_t)r;
-                s_src[mine] = id;
-                s_row[mine] = rk[q] ? rk[q][j] : j;
+                if (mine < n_single) {
+                    s_dst[mine] = (int32_t)r;
+                    s_src[mine] = id;
+                    s_row[mine] = rk[q] ? rk[q][j] : j;
+                }
             }
             at += __popcll(votes);
         }
@@ -498,126 +1055,107 @@ __global__ __launch_bounds__(kThreads) void k_single_list(SingleTabs tabs, const
     }
 }
 
-// --------------------------------------------------- transpose of a block
+// ------------------------------------------- source side of the blocks
 
-// One wavefront per listed destination row.
-// col_cnt[j] = number of edges of the block whose source is j: one thread per edge
-__global__ __launch_bounds__(kThreads) void k_t_count(const int32_t* __restrict__ indices, int64_t nnz,
-                                                      int32_t* __restrict__ col_cnt)
+// t_indptr of every block (its sources' offsets, from 0) and flags[j] = 1 if a source has an edge
+__global__ __launch_bounds__(kThreads) void k_source_offsets(const BlkDev* __restrict__ blk, const int32_t* __restrict__ off,
+                                                             int32_t* __restrict__ flags)
 {
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * kThreads)
-        atomicAdd(&col_cnt[indices[e]], 1);
-}
-
-// Destination i of every edge goes into its source's slot range.  LANES lanes share a row of the
-// launch list: a whole wavefront for the rows of at least 8 edges at the head of the list, 8 lanes
-// for the short rows behind them (most rows of a P-way split have a handful of edges per block).
-template <int LANES>
-__global__ __launch_bounds__(kThreads) void k_t_scatter(const int32_t* __restrict__ indptr,
-                                                        const int32_t* __restrict__ indices,
-                                                        const uint32_t* __restrict__ rows,
-                                                        int64_t n_rows, int32_t* __restrict__ col_cnt,
-                                                        const int32_t* __restrict__ col_off,
-                                                        int32_t* __restrict__ t_indices_all)
-{
-    const int lane = threadIdx.x & (LANES - 1);
-    for (int64_t w = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / LANES; w < n_rows;
-         w += ((int64_t)gridDim.x * kThreads) / LANES) {
-        const int i = (int)rows[w];
-        const int beg = indptr[i], end = indptr[i + 1];
-        for (int e = beg + lane; e < end; e += LANES) {
-            const int j = indices[e];
-            const int pos = atomicSub(&col_cnt[j], 1) - 1;
-            t_indices_all[(int64_t)col_off[j] + pos] = i;
-        }
+    const BlkDev& B = blk[blockIdx.y];
+    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k <= B.n_src; k += (int64_t)gridDim.x * kThreads) {
+        const int32_t o = off[B.coff + k];
+        B.t_indptr[k] = o - (int32_t)B.nnz0;
+        if (k < B.n_src) flags[B.coff + k] = off[B.coff + k + 1] > o ? 1 : 0;
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_rebase(const int32_t* __restrict__ off, int64_t n_plus_1,
-                                                     int32_t* __restrict__ out)
+// t_rank[j] = touched sources of the block below j (pos: of all blocks), and the ascending touched list
+__global__ __launch_bounds__(kThreads) void k_source_ranks(const BlkDev* __restrict__ blk, const int32_t* __restrict__ pos,
+                                                           int32_t* __restrict__ touched_all)
 {
-    const int32_t base = off[0];
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n_plus_1;
-         k += (int64_t)gridDim.x * kThreads)
-        out[k] = off[k] - base;
-}
-
-// flags[j] = 1 if source j has an edge (from global offsets)
-__global__ __launch_bounds__(kThreads) void k_nonempty_flags(const int32_t* __restrict__ off, int64_t n,
-                                                             int32_t* __restrict__ flags)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * kThreads)
-        flags[k] = off[k + 1] > off[k] ? 1 : 0;
-}
-
-__global__ __launch_bounds__(kThreads) void k_compact(const int32_t* __restrict__ off,
-                                                      const int32_t* __restrict__ pos, int64_t n,
-                                                      int32_t base_pos, int32_t* __restrict__ out)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * kThreads)
-        if (off[k + 1] > off[k]) out[pos[k] - base_pos] = (int32_t)k;
+    const BlkDev& B = blk[blockIdx.y];
+    const int32_t base = pos[B.coff];
+    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k <= B.n_src; k += (int64_t)gridDim.x * kThreads) {
+        const int32_t at = pos[B.coff + k];
+        B.t_rank[k] = at - base;
+        if (k < B.n_src && pos[B.coff + k + 1] > at) touched_all[at] = (int32_t)k;
+    }
 }
 
 // ------------------------------------------------- all-blocks (fused) index
 
-struct PtrTable {
-    const int32_t* indptr[SAR_MAX_PARTS];     // every handle's blocks (the degree pass), 2 KB of kernel arguments
-};
-
-__global__ __launch_bounds__(kThreads) void k_total_degree(PtrTable t, int P, int64_t n_dst,
+__global__ __launch_bounds__(kThreads) void k_total_degree(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
                                                            int32_t* __restrict__ deg)
 {
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i <= n_dst;
          i += (int64_t)gridDim.x * kThreads) {
         int d = 0;
         if (i < n_dst)
-            for (int q = 0; q < P; ++q) d += t.indptr[q][i + 1] - t.indptr[q][i];
+            for (int q = 0; q < P; ++q) d += blk[q].indptr[i + 1] - blk[q].indptr[i];
         deg[i] = d;   // deg[n_dst] = 0 closes the scan
     }
 }
 
-struct IdxTable {
-    const int32_t* indices[SAR_MAX_BLOCKS];
-};
-
 // Row i of the all-blocks index: its sources block after block, tagged with the block.  A
-// wavefront takes a row: lane q reads block q's range of the row, then the blocks are copied
-// in turn (8 lanes per block range when the blocks are many and the ranges short).
-__global__ __launch_bounds__(kThreads) void k_fused_copy(PtrTable t, IdxTable x, int P, int64_t n_dst,
+// wavefront takes a row: lane q reads block q's range of the row, then 8 lanes copy a block's
+// (usually short) range, eight blocks at a time.
+__global__ __launch_bounds__(kThreads) void k_fused_copy(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
                                                          const int32_t* __restrict__ f_indptr, int tag_shift,
                                                          uint32_t* __restrict__ f_indices)
 {
-    const int lane = threadIdx.x & 63;
+    __shared__ const int32_t* s_indices[SAR_MAX_BLOCKS];
+    __shared__ const int32_t* s_indptr[SAR_MAX_BLOCKS];
+    if ((int)threadIdx.x < P) {
+        s_indices[threadIdx.x] = blk[threadIdx.x].indices;
+        s_indptr[threadIdx.x] = blk[threadIdx.x].indptr;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
     for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6; i < n_dst;
          i += ((int64_t)gridDim.x * kThreads) >> 6) {
         int beg = 0, len = 0;
         if (lane < P) {
-            beg = t.indptr[lane][i];
-            len = t.indptr[lane][i + 1] - beg;
+            beg = s_indptr[lane][i];
+            len = s_indptr[lane][i + 1] - beg;
         }
-        int64_t pos = f_indptr[i];
-        for (int q = 0; q < P; ++q) {
-            const int b = __shfl(beg, q), n = __shfl(len, q);
-            for (int e = lane; e < n; e += 64)
-                f_indices[pos + e] = (uint32_t)x.indices[q][b + e] | ((uint32_t)q << tag_shift);
-            pos += n;
+        int at = len;                          // exclusive sum of the blocks' lengths
+        for (int o = 1; o < P; o <<= 1) {
+            const int x = __shfl_up(at, o);
+            if (lane >= o) at += x;
+        }
+        at -= len;
+        const int64_t pos = f_indptr[i];
+        for (int q0 = 0; q0 < P; q0 += 8) {
+            const int q = q0 + grp;            // P <= 64: a lane of the wavefront
+            const int b = __shfl(beg, q), n = __shfl(len, q), a = __shfl(at, q);
+            if (q < P)
+                for (int e = sub; e < n; e += 8)
+                    f_indices[pos + a + e] = (uint32_t)s_indices[q][b + e] | ((uint32_t)q << tag_shift);
         }
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_check_columns(const int32_t* __restrict__ indptr,
-                                                            const int32_t* __restrict__ indices,
-                                                            int64_t n_dst, int64_t nnz, int64_t n_src,
+// ends[2q], ends[2q+1] = first and last offset of block q
+__global__ __launch_bounds__(kThreads) void k_block_ends(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
+                                                         int32_t* __restrict__ ends)
+{
+    const int q = threadIdx.x;
+    if (q < P) {
+        ends[2 * q] = blk[q].indptr[0];
+        ends[2 * q + 1] = blk[q].indptr[n_dst];
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_check_columns(const BlkDev* __restrict__ blk, int64_t n_dst,
                                                             int* __restrict__ err)
 {
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < nnz;
+    const BlkDev& B = blk[blockIdx.y];
+    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < B.nnz;
          k += (int64_t)gridDim.x * kThreads)
-        if (indices[k] < 0 || indices[k] >= n_src) atomicOr(err, 4);
+        if (B.indices[k] < 0 || B.indices[k] >= B.n_src) atomicOr(err, 4);
     for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n_dst;
          k += (int64_t)gridDim.x * kThreads)
-        if (indptr[k + 1] < indptr[k]) atomicOr(err, 8);
+        if (B.indptr[k + 1] < B.indptr[k]) atomicOr(err, 8);
 }
 
 unsigned grid_for(int64_t items, int per_block = kThreads, int64_t cap = 1 << 20)
@@ -629,8 +1167,9 @@ template <typename T>
 int own(sar_blocks* h, T** out, int64_t count)
 {
     void* p = nullptr;
-    SAR_HIP(hipMalloc(&p, std::max<int64_t>(count, 1) * sizeof(T)));
-    h->owned.push_back(p);
+    const size_t size = Pool::round(std::max<int64_t>(count, 1) * sizeof(T));
+    SAR_TRY(pool().take(h->device, &p, size));
+    h->owned.emplace_back(p, size);
     *out = static_cast<T*>(p);
     return SAR_OK;
 }
@@ -642,239 +1181,288 @@ int bits_for(int64_t n)
     return b;
 }
 
+// Bits by which a source's block is tagged above its local id.
+int set_tag_shift(sar_blocks* h, int64_t n_src_max)
+{
+    h->tag_shift = std::max(1, bits_for(std::max<int64_t>(n_src_max, 2)));
+    if (h->tag_shift + bits_for(h->P) > 32)
+        return sar::fail(SAR_ERR_UNSUPPORTED, "P=%d blocks of up to %lld sources do not fit a 32-bit tagged index",
+                         h->P, (long long)n_src_max);
+    return SAR_OK;
+}
+
+template <typename Fn>
+int allow_lds(Fn fn, size_t bytes)
+{
+    SAR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    return SAR_OK;
+}
+
+// host[k] = in[k * step] for k in [0, P]; the stream has to be waited for before they are read.
+int read_every(const int32_t* in, int64_t step, int P, int32_t* host, DeviceTemps& tmp, hipStream_t st)
+{
+    int32_t* dev = nullptr;
+    SAR_TRY(tmp.alloc(&dev, P + 1));
+    k_every<<<1, kThreads, 0, st>>>(in, step, P, dev);
+    SAR_LAUNCH_CHECK();
+    SAR_HIP(hipMemcpyAsync(host, dev, (P + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    return SAR_OK;
+}
+
+// Scratch of a builder call that its two groupings share.
+struct PairScratch {
+    void* pairs = nullptr;
+    size_t bytes = 0;
+    int take(DeviceTemps& tmp, size_t want)
+    {
+        if (want <= bytes) return SAR_OK;
+        char* p = nullptr;
+        SAR_TRY(tmp.alloc(&p, (int64_t)want));
+        pairs = p;
+        bytes = want;
+        return SAR_OK;
+    }
+};
+
+// The pairs of the n_keys keys of a pass are in their buckets: off[0..n_keys] their offsets (from `base`
+// on), and their values in order.
+template <typename PairT>
+int finish_buckets(const BucketPlan& plan, const PairT* pairs, const int32_t* counts, int64_t n_keys, int vbits,
+                   int32_t base, int32_t* off, int32_t* values, DeviceTemps& tmp, hipStream_t st)
+{
+    int32_t* list = nullptr;
+    SAR_TRY(tmp.alloc(&list, plan.n_buckets() + 1));
+    int* count = list + plan.n_buckets();
+    SAR_HIP(hipMemsetAsync(count, 0, sizeof(int), st));
+    SAR_HIP(hipMemsetAsync(off + n_keys, 0, sizeof(int32_t), st));
+    const size_t slots = ((size_t)1 << plan.w) * sizeof(int), lds = slots + kBucketCap * sizeof(int32_t);
+    const Deal deal{plan.nb};
+    k_bucket_keys<PairT><<<(unsigned)plan.n_buckets(), kBucketThreads, slots, st>>>(pairs, counts, plan.n_tiles, plan.w,
+                                                                                   deal, n_keys, vbits, off);
+    SAR_LAUNCH_CHECK();
+    SAR_TRY(exclusive_scan(off, off, n_keys + 1, st, tmp, base));
+    SAR_TRY(allow_lds(k_bucket_finish<PairT>, lds));
+    k_bucket_finish<PairT><<<(unsigned)plan.n_buckets(), kBucketThreads, lds, st>>>(
+        pairs, counts, plan.n_tiles, plan.w, deal, n_keys, vbits, off, values, list, count);
+    SAR_LAUNCH_CHECK();
+    k_sort_buckets<<<dim3((unsigned)std::min(plan.n_buckets(), 32), 16), kThreads, 0, st>>>(off, values, plan.w, deal, n_keys,
+                                                                                            list, count);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
 // Builds what `flags` asks for on top of per-block CSR arrays already in h->blk.
-int derive(sar_blocks* h, hipStream_t st)
+int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st)
 {
     const int P = h->P;
     const int64_t n_dst = h->n_dst;
-    DeviceTemps tmp;
     if ((h->flags & SAR_BUILD_COMPACT) && !(h->flags & SAR_BUILD_TRANSPOSE))
         return sar::fail(SAR_ERR_INVALID_ARG, "SAR_BUILD_COMPACT needs SAR_BUILD_TRANSPOSE");
+    const bool transpose = (h->flags & SAR_BUILD_TRANSPOSE) != 0, fused = (h->flags & SAR_BUILD_FUSED) != 0;
 
-    int64_t nnz_total = 0, n_src_total = 0, n_src_max = 0;
+    int64_t nnz_total = 0, n_src_total = 0, n_src_max = 0, nnz_max = 0;
     for (auto& b : h->blk) {
         nnz_total += b.nnz;
         n_src_total += b.n_src;
         n_src_max = std::max(n_src_max, b.n_src);
+        nnz_max = std::max(nnz_max, b.nnz);
     }
     if (n_src_total >= ((int64_t)1 << 31))
         return sar::fail(SAR_ERR_UNSUPPORTED, "the %d source partitions hold %lld nodes in total; a handle's work "
                          "lists index fewer than 2^31", P, (long long)n_src_total);
-    h->tag_shift = std::max(1, bits_for(std::max<int64_t>(n_src_max, 2)));
-    if (h->tag_shift + bits_for(P) > 32)
-        return sar::fail(SAR_ERR_UNSUPPORTED, "P=%d blocks of up to %lld sources do not fit a 32-bit tagged index",
-                         P, (long long)n_src_max);
+    SAR_TRY(set_tag_shift(h, n_src_max));
+    if (fused && nnz_total >= ((int64_t)1 << 31))
+        return sar::fail(SAR_ERR_UNSUPPORTED, "all-blocks index needs fewer than 2^31 edges, got %lld",
+                         (long long)nnz_total);
+    if (transpose && nnz_total >= ((int64_t)1 << 31))
+        return sar::fail(SAR_ERR_UNSUPPORTED, "transpose needs fewer than 2^31 edges in total, got %lld",
+                         (long long)nnz_total);
 
-    PtrTable tab;
-    memset(&tab, 0, sizeof(tab));
-    for (int q = 0; q < P; ++q) tab.indptr[q] = h->blk[q].indptr;
-
-    // total in-degree |N(i)|
+    // ---- arrays whose sizes are known; the launch lists at the most they can hold
+    const int64_t rows_most = std::min<int64_t>(nnz_total, (int64_t)P * n_dst);
+    int32_t *rows_all = nullptr, *t_indices_all = nullptr, *t_indptr_all = nullptr, *t_rank_all = nullptr;
+    int32_t *t_rows_all = nullptr, *touched_all = nullptr;
     SAR_TRY(own(h, &h->deg, n_dst + 1));
-    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(tab, P, n_dst, h->deg);
-    SAR_LAUNCH_CHECK();
-
-    // ---- destination-row launch lists, one per block, longest class first
-    int* hist_d = nullptr;
-    const int n_hist = (P + 2) * sar::kNumClasses;
-    SAR_TRY(tmp.alloc(&hist_d, n_hist));
-    SAR_HIP(hipMemsetAsync(hist_d, 0, n_hist * sizeof(int), st));
-    for (int q = 0; q < P; ++q) {
-        k_class_hist<<<grid_for(n_dst, kThreads, 4096), kThreads, 0, st>>>(h->blk[q].indptr, n_dst,
-                                                                           hist_d + q * sar::kNumClasses);
-        SAR_LAUNCH_CHECK();
-    }
-    std::vector<int> hist(n_hist);
-    SAR_HIP(hipMemcpyAsync(hist.data(), hist_d, n_hist * sizeof(int), hipMemcpyDeviceToHost, st));
-    SAR_HIP(hipStreamSynchronize(st));
-    std::vector<int> cursors(n_hist, 0);
-    int64_t rows_total = 0;
-    std::vector<int64_t> rows_base(P);
-    for (int q = 0; q < P; ++q) {
-        ClassLayout L = layout_from_hist(&hist[q * sar::kNumClasses], 0, sar::kLongClassBlock);
-        h->blk[q].n_rows = L.n_rows;
-        h->blk[q].n_long = L.n_long;
-        h->blk[q].n_rows_wide = L.n_wide;
-        for (int c = 1; c < sar::kNumClasses; ++c)
-            if (hist[q * sar::kNumClasses + c]) h->blk[q].hub = (int64_t)1 << (c - 1);
-        memcpy(&cursors[q * sar::kNumClasses], L.start, sizeof(L.start));
-        rows_base[q] = rows_total;
-        rows_total += L.n_rows;
-    }
-    int32_t* rows_all = nullptr;
-    SAR_TRY(own(h, &rows_all, rows_total));
-    SAR_HIP(hipMemcpyAsync(hist_d, cursors.data(), n_hist * sizeof(int), hipMemcpyHostToDevice, st));
-    for (int q = 0; q < P; ++q) {
-        h->blk[q].rows = rows_all + rows_base[q];
-        k_class_place<<<grid_for(n_dst, kThreads, 1 << 23), kThreads, 0, st>>>(h->blk[q].indptr, n_dst,
-                                                            hist_d + q * sar::kNumClasses, 0u, false,
-                                                            reinterpret_cast<uint32_t*>(h->blk[q].rows));
-        SAR_LAUNCH_CHECK();
-    }
-    SAR_HIP(hipStreamSynchronize(st));   // cursors (host vector) must outlive the copy
-
-    // ---- all-blocks destination-major index
-    if (h->flags & SAR_BUILD_FUSED) {
-        if (nnz_total >= ((int64_t)1 << 31))
-            return sar::fail(SAR_ERR_UNSUPPORTED, "all-blocks index needs fewer than 2^31 edges, got %lld",
-                             (long long)nnz_total);
+    SAR_TRY(own(h, &rows_all, rows_most));
+    if (fused) {
         SAR_TRY(own(h, &h->f_indptr, n_dst + 1));
-        SAR_TRY(exclusive_scan(h->deg, h->f_indptr, n_dst + 1, st, tmp));
         SAR_TRY(own(h, &h->f_indices, nnz_total));
-        {
-            IdxTable idx;
-            memset(&idx, 0, sizeof(idx));
-            for (int q = 0; q < P; ++q) idx.indices[q] = h->blk[q].indices;
-            k_fused_copy<<<grid_for(n_dst * 64), kThreads, 0, st>>>(tab, idx, P, n_dst, h->f_indptr, h->tag_shift,
-                                                                    h->f_indices);
-            SAR_LAUNCH_CHECK();
-        }
-        int* fh = hist_d + P * sar::kNumClasses;
-        SAR_HIP(hipMemsetAsync(fh, 0, sar::kNumClasses * sizeof(int), st));
-        k_class_hist<<<grid_for(n_dst, kThreads, 4096), kThreads, 0, st>>>(h->f_indptr, n_dst, fh);
-        SAR_LAUNCH_CHECK();
-        int fhist[sar::kNumClasses];
-        SAR_HIP(hipMemcpyAsync(fhist, fh, sizeof(fhist), hipMemcpyDeviceToHost, st));
-        SAR_HIP(hipStreamSynchronize(st));
-        ClassLayout L = layout_from_hist(fhist, 0, sar::kLongClassBlock);
-        h->n_f_rows = L.n_rows;
-        h->n_f_long = L.n_long;
         SAR_TRY(own(h, &h->f_rows, n_dst));
-        SAR_HIP(hipMemcpyAsync(fh, L.start, sizeof(L.start), hipMemcpyHostToDevice, st));
-        k_class_place<<<grid_for(n_dst, kThreads, 1 << 23), kThreads, 0, st>>>(h->f_indptr, n_dst, fh, 0u, true,
-                                                            reinterpret_cast<uint32_t*>(h->f_rows));
-        SAR_LAUNCH_CHECK();
-        SAR_HIP(hipStreamSynchronize(st));
     }
-
-    // ---- source-major transpose of every block
-    if (h->flags & SAR_BUILD_TRANSPOSE) {
-        if (nnz_total >= ((int64_t)1 << 31))
-            return sar::fail(SAR_ERR_UNSUPPORTED, "transpose needs fewer than 2^31 edges in total, got %lld",
-                             (long long)nnz_total);
-        // counts of all blocks in one array [sum n_src + 1], block q at coff[q]
-        std::vector<int64_t> coff(P + 1, 0);
-        for (int q = 0; q < P; ++q) coff[q + 1] = coff[q] + h->blk[q].n_src;
-        int32_t *col_cnt = nullptr, *col_off = nullptr, *t_indices_all = nullptr, *t_indptr_all = nullptr;
-        SAR_TRY(tmp.alloc(&col_cnt, n_src_total + 1));
-        SAR_TRY(tmp.alloc(&col_off, n_src_total + 1));
-        SAR_HIP(hipMemsetAsync(col_cnt, 0, (n_src_total + 1) * sizeof(int32_t), st));
-        for (int q = 0; q < P; ++q) {
-            const Block& b = h->blk[q];
-            if (b.n_rows == 0) continue;
-            k_t_count<<<grid_for(b.nnz, kThreads, 1 << 16), kThreads, 0, st>>>(b.indices, b.nnz, col_cnt + coff[q]);
-            SAR_LAUNCH_CHECK();
-        }
-        SAR_TRY(exclusive_scan(col_cnt, col_off, n_src_total + 1, st, tmp));
+    if (transpose) {
         SAR_TRY(own(h, &t_indices_all, nnz_total));
-        for (int q = 0; q < P; ++q) {
-            const Block& b = h->blk[q];
-            if (b.n_rows == 0) continue;
-            const uint32_t* rows = reinterpret_cast<const uint32_t*>(b.rows);
-            if (b.n_rows_wide > 0) {
-                k_t_scatter<64><<<grid_for(b.n_rows_wide * 64), kThreads, 0, st>>>(
-                    b.indptr, b.indices, rows, b.n_rows_wide, col_cnt + coff[q], col_off + coff[q], t_indices_all);
-                SAR_LAUNCH_CHECK();
-            }
-            if (b.n_rows > b.n_rows_wide) {
-                k_t_scatter<8><<<grid_for((b.n_rows - b.n_rows_wide) * 8), kThreads, 0, st>>>(
-                    b.indptr, b.indices, rows + b.n_rows_wide, b.n_rows - b.n_rows_wide, col_cnt + coff[q],
-                    col_off + coff[q], t_indices_all);
-                SAR_LAUNCH_CHECK();
-            }
-        }
-        SAR_TRY(sort_rows(col_off, n_src_total, t_indices_all, nnz_total, st, tmp));
-
-        // per-block views: own indptr (rebased to the block) and a slice of the indices
         SAR_TRY(own(h, &t_indptr_all, n_src_total + P));
-        std::vector<int32_t> block_first(P + 1, 0);
-        for (int q = 0; q <= P; ++q)
-            SAR_HIP(hipMemcpyAsync(&block_first[q], col_off + coff[q], sizeof(int32_t),
-                                   hipMemcpyDeviceToHost, st));
-        SAR_HIP(hipStreamSynchronize(st));
-        for (int q = 0; q < P; ++q) {
-            Block& b = h->blk[q];
-            b.t_indptr = t_indptr_all + coff[q] + q;
-            b.t_indices = t_indices_all + block_first[q];
-            k_rebase<<<grid_for(b.n_src + 1), kThreads, 0, st>>>(col_off + coff[q], b.n_src + 1, b.t_indptr);
-            SAR_LAUNCH_CHECK();
-        }
-
-        // source launch lists per block + one for all blocks, and the touched lists
-        SAR_HIP(hipMemsetAsync(hist_d, 0, n_hist * sizeof(int), st));
-        for (int q = 0; q < P; ++q) {
-            k_class_hist<<<grid_for(h->blk[q].n_src, kThreads, 4096), kThreads, 0, st>>>(
-                h->blk[q].t_indptr, h->blk[q].n_src, hist_d + q * sar::kNumClasses);
-            SAR_LAUNCH_CHECK();
-        }
-        SAR_HIP(hipMemcpyAsync(hist.data(), hist_d, n_hist * sizeof(int), hipMemcpyDeviceToHost, st));
-        SAR_HIP(hipStreamSynchronize(st));
-        int all_hist[sar::kNumClasses] = {0};
-        int64_t t_rows_total = 0;
-        std::vector<int64_t> t_base(P);
-        for (int q = 0; q < P; ++q) {
-            ClassLayout L = layout_from_hist(&hist[q * sar::kNumClasses], 0, sar::kLongClassBlock);
-            h->blk[q].n_t_rows = L.n_rows;
-            h->blk[q].n_t_long = L.n_long;
-            h->blk[q].n_t_wide = L.n_wide;
-            memcpy(&cursors[q * sar::kNumClasses], L.start, sizeof(L.start));
-            t_base[q] = t_rows_total;
-            t_rows_total += L.n_rows;
-            for (int c = 0; c < sar::kNumClasses; ++c) all_hist[c] += hist[q * sar::kNumClasses + c];
-        }
-        ClassLayout LA = layout_from_hist(all_hist, 0, sar::kLongClassBlock);
-        h->n_ft_rows = LA.n_rows;
-        h->n_ft_long = LA.n_long;
-        h->n_ft_wide = LA.n_wide;
-        memcpy(&cursors[P * sar::kNumClasses], LA.start, sizeof(LA.start));
-        int32_t *t_rows_all = nullptr, *touched_all = nullptr;
+        SAR_TRY(own(h, &t_rank_all, n_src_total + P));
         // the launch lists also carry the sources without edges (last), so that the
         // backward kernels write every row of dZ_q; `touched` holds only the others
         SAR_TRY(own(h, &t_rows_all, n_src_total));
-        SAR_TRY(own(h, &touched_all, t_rows_total));
         SAR_TRY(own(h, &h->ft_rows, n_src_total));
-        SAR_HIP(hipMemcpyAsync(hist_d, cursors.data(), n_hist * sizeof(int), hipMemcpyHostToDevice, st));
-        for (int q = 0; q < P; ++q) {
-            Block& b = h->blk[q];
-            b.t_rows = t_rows_all + coff[q];
-            b.touched = touched_all + t_base[q];
-            k_class_place<<<grid_for(b.n_src, kThreads, 1 << 23), kThreads, 0, st>>>(b.t_indptr, b.n_src,
-                                                                  hist_d + q * sar::kNumClasses, 0u, true,
-                                                                  reinterpret_cast<uint32_t*>(b.t_rows));
-            SAR_LAUNCH_CHECK();
-            k_class_place<<<grid_for(b.n_src, kThreads, 1 << 23), kThreads, 0, st>>>(b.t_indptr, b.n_src,
-                                                                  hist_d + P * sar::kNumClasses,
-                                                                  (uint32_t)q << h->tag_shift, true, h->ft_rows);
-            SAR_LAUNCH_CHECK();
+        SAR_TRY(own(h, &touched_all, std::min(n_src_total, nnz_total)));
+    }
+
+    const BucketPlan plan = plan_buckets(std::min(kKeysPerPass, std::max<int64_t>(n_src_total, 1)), nnz_total);
+    std::vector<BlkDev> blk(P);
+    int64_t coff = 0, nnz0 = 0, tiles = 0;
+    for (int q = 0; q < P; ++q) {
+        Block& b = h->blk[q];
+        if (transpose) {
+            b.t_indptr = t_indptr_all + coff + q;
+            b.t_rank = t_rank_all + coff + q;
+            b.t_indices = t_indices_all + nnz0;
+            b.t_rows = t_rows_all + coff;
         }
-        // touched = ascending ids of the sources with an edge: compaction by scan
-        int32_t* pos = nullptr;
-        SAR_TRY(tmp.alloc(&pos, n_src_total + 1));
-        k_nonempty_flags<<<grid_for(n_src_total), kThreads, 0, st>>>(col_off, n_src_total, pos);
+        blk[q] = BlkDev{b.indptr, b.indices, b.n_src, coff, b.nnz, nnz0, tiles, nullptr,
+                        reinterpret_cast<uint32_t*>(b.t_rows), b.t_indptr, b.t_rank};
+        coff += b.n_src;
+        nnz0 += b.nnz;
+        tiles += (b.nnz + plan.tile - 1) / plan.tile;
+    }
+    BlkDev* blk_d = nullptr;
+    SAR_TRY(tmp.alloc(&blk_d, P));
+    SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+
+    // total in-degree |N(i)|, and its class histograms: the blocks' rows, their sources, all rows
+    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg);
+    SAR_LAUNCH_CHECK();
+    int* hist_d = nullptr;
+    const int C = sar::kNumClasses, n_hist = (2 * P + 2) * C;
+    SAR_TRY(tmp.alloc(&hist_d, n_hist));
+    SAR_HIP(hipMemsetAsync(hist_d, 0, n_hist * sizeof(int), st));
+    int *rows_hist = hist_d, *src_hist = hist_d + P * C, *all_rows_hist = hist_d + 2 * P * C;
+    ListIn in{blk_d, h->f_indptr, n_dst};
+    const dim3 g_rows(grid_for(n_dst, kThreads, std::max(1, 4096 / P)), P), g_all(grid_for(n_dst, kThreads, 4096), 1);
+    const dim3 g_src(grid_for(n_src_max + 1, kThreads, std::max(1, 4096 / P)), P);
+    k_class_hist<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, rows_hist);
+    SAR_LAUNCH_CHECK();
+
+    // ---- all-blocks destination-major index
+    if (fused) {
+        SAR_TRY(exclusive_scan(h->deg, h->f_indptr, n_dst + 1, st, tmp));
+        k_fused_copy<<<grid_for(n_dst * 64), kThreads, 0, st>>>(blk_d, P, n_dst, h->f_indptr, h->tag_shift, h->f_indices);
         SAR_LAUNCH_CHECK();
-        SAR_HIP(hipMemsetAsync(pos + n_src_total, 0, sizeof(int32_t), st));
-        SAR_TRY(exclusive_scan(pos, pos, n_src_total + 1, st, tmp));
-        // t_rank[j] = number of touched sources below j, per block (the same scan, rebased)
-        int32_t* t_rank_all = nullptr;
-        SAR_TRY(own(h, &t_rank_all, n_src_total + P));
-        for (int q = 0; q < P; ++q) {
-            Block& b = h->blk[q];
-            b.t_rank = t_rank_all + coff[q] + q;
-            k_rebase<<<grid_for(b.n_src + 1), kThreads, 0, st>>>(pos + coff[q], b.n_src + 1, b.t_rank);
+        k_class_hist<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, all_rows_hist);
+        SAR_LAUNCH_CHECK();
+    }
+
+    // ---- source-major transpose of every block
+    int32_t* pos = nullptr;
+    if (transpose) {
+        int32_t *col_off = nullptr, *counts = nullptr;
+        SAR_TRY(tmp.alloc(&col_off, n_src_total + 1));
+        SAR_TRY(tmp.alloc(&counts, (int64_t)plan.n_buckets() * std::max<int64_t>(tiles, 1) + 1));
+        const int vbits = bits_for(std::max<int64_t>(n_dst, 1));
+        const bool narrow = plan.w + vbits <= 32;
+        SAR_TRY(scratch.take(tmp, (size_t)nnz_total * (narrow ? 4 : 8)));
+        BucketPlan pass = plan;
+        pass.n_tiles = tiles;
+        int32_t base = 0;
+        if (nnz_total == 0) SAR_HIP(hipMemsetAsync(col_off, 0, (n_src_total + 1) * sizeof(int32_t), st));
+        for (int64_t key0 = 0; key0 < n_src_total && nnz_total > 0; key0 += kKeysPerPass) {
+            const int64_t nk = std::min(kKeysPerPass, n_src_total - key0);
+            const bool last = key0 + nk == n_src_total;
+            const int64_t n_counts = (int64_t)pass.n_buckets() * tiles + 1;
+            const size_t lds = pass.n_buckets() * sizeof(int);
+            const Deal deal{pass.nb};
+            SAR_HIP(hipMemsetAsync(counts + n_counts - 1, 0, sizeof(int32_t), st));
+            SAR_TRY(allow_lds(k_block_count, lds));
+            k_block_count<<<(unsigned)tiles, kBucketThreads, lds, st>>>(blk_d, P, pass.tile, tiles, key0, nk, deal,
+                                                                        counts);
             SAR_LAUNCH_CHECK();
-            if (b.n_t_rows == 0) continue;
-            k_compact<<<grid_for(b.n_src), kThreads, 0, st>>>(b.t_indptr, pos + coff[q], b.n_src,
-                                                              (int32_t)t_base[q], b.touched);
-            SAR_LAUNCH_CHECK();
+            SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
+            auto place = [&](auto* pairs) -> int {
+                using PairT = std::remove_pointer_t<decltype(pairs)>;
+                SAR_TRY(allow_lds(k_block_scatter<PairT>, lds));
+                k_block_scatter<PairT><<<(unsigned)tiles, kBucketThreads, lds, st>>>(
+                    blk_d, P, n_dst, pass.tile, tiles, key0, nk, deal, vbits, counts, pairs);
+                SAR_LAUNCH_CHECK();
+                return finish_buckets<PairT>(pass, pairs, counts, nk, vbits, base, col_off + key0, t_indices_all, tmp, st);
+            };
+            SAR_TRY(narrow ? place(static_cast<uint32_t*>(scratch.pairs)) : place(static_cast<uint64_t*>(scratch.pairs)));
+            if (!last) {
+                int32_t in_pass = 0;
+                SAR_HIP(hipMemcpyAsync(&in_pass, counts + n_counts - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+                SAR_HIP(hipStreamSynchronize(st));
+                base += in_pass;
+            }
         }
-        SAR_HIP(hipStreamSynchronize(st));
+        // per-block offsets (from 0), the classes of the sources, ranks of the touched ones
+        SAR_TRY(tmp.alloc(&pos, n_src_total + 1));
+        SAR_HIP(hipMemsetAsync(pos + n_src_total, 0, sizeof(int32_t), st));
+        k_source_offsets<<<g_src, kThreads, 0, st>>>(blk_d, col_off, pos);
+        SAR_LAUNCH_CHECK();
+        k_class_hist<<<g_src, kThreads, 0, st>>>(in, Lists::kSources, src_hist);
+        SAR_LAUNCH_CHECK();
+        SAR_TRY(exclusive_scan(pos, pos, n_src_total + 1, st, tmp));
+        k_source_ranks<<<g_src, kThreads, 0, st>>>(blk_d, pos, touched_all);
+        SAR_LAUNCH_CHECK();
+    }
+
+    // ---- launch lists, longest class first
+    std::vector<int> hist(n_hist), cursors(n_hist, 0);
+    SAR_HIP(hipMemcpyAsync(hist.data(), hist_d, n_hist * sizeof(int), hipMemcpyDeviceToHost, st));
+    SAR_HIP(hipStreamSynchronize(st));
+    int64_t rows_at = 0, t_rows_at = 0;
+    int all_hist[sar::kNumClasses] = {0};
+    for (int q = 0; q < P; ++q) {
+        Block& b = h->blk[q];
+        const int* row_hist = &hist[q * C];
+        ClassLayout L = layout_from_hist(row_hist, 0, sar::kLongClassBlock);
+        b.n_rows = L.n_rows;
+        b.n_long = L.n_long;
+        b.n_rows_wide = L.n_wide;
+        for (int c = 1; c < C; ++c)
+            if (row_hist[c]) b.hub = (int64_t)1 << (c - 1);
+        memcpy(&cursors[q * C], L.start, sizeof(L.start));
+        b.rows = rows_all + rows_at;
+        blk[q].rows = reinterpret_cast<uint32_t*>(b.rows);
+        rows_at += L.n_rows;
+        if (transpose) {
+            const int* s_hist = &hist[(P + q) * C];
+            ClassLayout S = layout_from_hist(s_hist, 0, sar::kLongClassBlock);
+            b.n_t_rows = S.n_rows;
+            b.n_t_long = S.n_long;
+            b.n_t_wide = S.n_wide;
+            memcpy(&cursors[(P + q) * C], S.start, sizeof(S.start));
+            b.touched = touched_all + t_rows_at;
+            t_rows_at += S.n_rows;
+            for (int c = 0; c < C; ++c) all_hist[c] += s_hist[c];
+        }
+    }
+    if (fused) {
+        ClassLayout L = layout_from_hist(&hist[2 * P * C], 0, sar::kLongClassBlock);
+        h->n_f_rows = L.n_rows;
+        h->n_f_long = L.n_long;
+        memcpy(&cursors[2 * P * C], L.start, sizeof(L.start));
+    }
+    if (transpose) {
+        ClassLayout L = layout_from_hist(all_hist, 0, sar::kLongClassBlock);
+        h->n_ft_rows = L.n_rows;
+        h->n_ft_long = L.n_long;
+        h->n_ft_wide = L.n_wide;
+        memcpy(&cursors[(2 * P + 1) * C], L.start, sizeof(L.start));
+    }
+    SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+    SAR_HIP(hipMemcpyAsync(hist_d, cursors.data(), n_hist * sizeof(int), hipMemcpyHostToDevice, st));
+    k_class_place<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, rows_hist, nullptr);
+    SAR_LAUNCH_CHECK();
+    if (fused) {
+        k_class_place<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, 0, all_rows_hist,
+                                                  reinterpret_cast<uint32_t*>(h->f_rows));
+        SAR_LAUNCH_CHECK();
+    }
+    int32_t placed = 0;
+    if (transpose) {
+        k_class_place<<<g_src, kThreads, 0, st>>>(in, Lists::kSources, 0, src_hist, nullptr);
+        SAR_LAUNCH_CHECK();
+        k_class_place<<<g_src, kThreads, 0, st>>>(in, Lists::kAllSources, h->tag_shift, hist_d + (2 * P + 1) * C, h->ft_rows);
+        SAR_LAUNCH_CHECK();
 
         // ---- the sources of one edge, listed from their destinations' side (all-blocks backward):
         // built where they carry at least an eighth of the edges, or on request
         const int64_t n_single = all_hist[1];
         const bool want_singles = (h->flags & SAR_BUILD_SINGLES) ||
                                   (!(h->flags & SAR_BUILD_NO_SINGLES) && n_single * 8 >= nnz_total);
-        if ((h->flags & SAR_BUILD_FUSED) && want_singles && n_single > 0) {
+        if (fused && want_singles && n_single > 0) {
             SAR_TRY(own(h, &h->s_dst, n_single));
             SAR_TRY(own(h, &h->s_src, n_single));
             SAR_TRY(own(h, &h->s_row, n_single));
@@ -890,22 +1478,20 @@ int derive(sar_blocks* h, hipStream_t st)
             SAR_HIP(hipMemsetAsync(s_cnt + n_dst, 0, sizeof(int32_t), st));
             const unsigned g_list = grid_for(n_dst * 64, kThreads, 1 << 16);
             k_single_list<false><<<g_list, kThreads, 0, st>>>(stabs, h->f_indptr, h->f_indices, n_dst, h->tag_shift,
-                                                              s_cnt, nullptr, nullptr, nullptr, nullptr);
+                                                              s_cnt, nullptr, 0, nullptr, nullptr, nullptr);
             SAR_LAUNCH_CHECK();
             SAR_TRY(exclusive_scan(s_cnt, s_off, n_dst + 1, st, tmp));
-            int32_t placed = 0;
             SAR_HIP(hipMemcpyAsync(&placed, s_off + n_dst, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            SAR_HIP(hipStreamSynchronize(st));
-            if (placed != n_single)
-                return sar::fail(SAR_ERR_STATE, "the all-blocks index lists %d sources of one edge, the transposes %lld",
-                                 placed, (long long)n_single);
             k_single_list<true><<<g_list, kThreads, 0, st>>>(stabs, h->f_indptr, h->f_indices, n_dst, h->tag_shift,
-                                                             nullptr, s_off, h->s_dst, h->s_src, h->s_row);
+                                                             nullptr, s_off, n_single, h->s_dst, h->s_src, h->s_row);
             SAR_LAUNCH_CHECK();
             h->n_single = n_single;
         }
     }
     SAR_HIP(hipStreamSynchronize(st));
+    if (h->n_single > 0 && placed != h->n_single)
+        return sar::fail(SAR_ERR_STATE, "the all-blocks index lists %d sources of one edge, the transposes %lld", placed,
+                         (long long)h->n_single);
     return SAR_OK;
 }
 
@@ -923,139 +1509,183 @@ int check_err_flag(int* err_d, hipStream_t st)
 }
 
 int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_bytes, int64_t E,
-                     const int32_t* part, int64_t N, int P, int p, hipStream_t st)
+                     const int32_t* part, int64_t N, int P, int p, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st)
 {
-    DeviceTemps tmp;
     int* err_d = nullptr;
-    SAR_TRY(tmp.alloc(&err_d, 1));
-    SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
+    SAR_TRY(tmp.alloc(&err_d, 4));
+    unsigned long long* kept_d = reinterpret_cast<unsigned long long*>(err_d + 2);
+    SAR_HIP(hipMemsetAsync(err_d, 0, 4 * sizeof(int), st));
 
     // 1. rank of every node inside its partition
     const int64_t n_tiles = std::max<int64_t>(1, (N + kPartTile - 1) / kPartTile);
-    int32_t *tile_counts = nullptr, *lid = nullptr;
+    int32_t* tile_counts = nullptr;
+    uint32_t* code = nullptr;
     SAR_TRY(tmp.alloc(&tile_counts, (int64_t)P * n_tiles + 1));
-    SAR_TRY(tmp.alloc(&lid, N));
-    SAR_HIP(hipMemsetAsync(tile_counts, 0, ((int64_t)P * n_tiles + 1) * sizeof(int32_t), st));
+    SAR_TRY(tmp.alloc(&code, N));
+    SAR_HIP(hipMemsetAsync(tile_counts + (int64_t)P * n_tiles, 0, sizeof(int32_t), st));
     k_part_tile_count<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, err_d);
     SAR_LAUNCH_CHECK();
-    SAR_TRY(check_err_flag(err_d, st));
     SAR_TRY(exclusive_scan(tile_counts, tile_counts, (int64_t)P * n_tiles + 1, st, tmp));
     std::vector<int32_t> part_first(P + 1);
-    for (int q = 0; q <= P; ++q)
-        SAR_HIP(hipMemcpyAsync(&part_first[q], tile_counts + (int64_t)q * n_tiles, sizeof(int32_t),
-                               hipMemcpyDeviceToHost, st));
-    SAR_HIP(hipStreamSynchronize(st));
-    k_local_ids<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, lid);
-    SAR_LAUNCH_CHECK();
+    SAR_TRY(read_every(tile_counts, n_tiles, P, part_first.data(), tmp, st));
+    SAR_TRY(check_err_flag(err_d, st));
     const int64_t n_dst = part_first[p + 1] - part_first[p];
     h->n_dst = n_dst;
     h->blk.resize(P);
+    int64_t n_src_max = 0;
     for (int q = 0; q < P; ++q) {
         h->blk[q].n_dst = n_dst;
         h->blk[q].n_src = part_first[q + 1] - part_first[q];
+        n_src_max = std::max(n_src_max, h->blk[q].n_src);
     }
+    SAR_TRY(set_tag_shift(h, n_src_max));
+    k_local_ids<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, h->tag_shift, code);
+    SAR_LAUNCH_CHECK();
 
-    // 2. count, scan, scatter, sort
+    // 2. the kept edges grouped by (block, destination)
     const int64_t n_rows_all = (int64_t)P * n_dst;
-    int32_t *row_cnt = nullptr, *row_off = nullptr;
-    SAR_TRY(tmp.alloc(&row_cnt, n_rows_all + 1));
+    int32_t *row_off = nullptr, *indices_all = nullptr, *indptr_all = nullptr;
     SAR_TRY(tmp.alloc(&row_off, n_rows_all + 1));
-    SAR_HIP(hipMemsetAsync(row_cnt, 0, (n_rows_all + 1) * sizeof(int32_t), st));
-    const unsigned ge = grid_for(E, kThreads, 1 << 16);
-    if (E > 0) {
-        unsigned long long* kept_d = nullptr;
-        SAR_TRY(tmp.alloc(&kept_d, 1));
-        SAR_HIP(hipMemsetAsync(kept_d, 0, sizeof(unsigned long long), st));
-        if (idx_bytes == 4)
-            k_edge_count<int32_t><<<ge, kThreads, 0, st>>>((const int32_t*)src, (const int32_t*)dst, E, part,
-                                                           N, p, lid, n_dst, row_cnt, kept_d, err_d);
-        else
-            k_edge_count<int64_t><<<ge, kThreads, 0, st>>>((const int64_t*)src, (const int64_t*)dst, E, part,
-                                                           N, p, lid, n_dst, row_cnt, kept_d, err_d);
-        SAR_LAUNCH_CHECK();
-        SAR_TRY(check_err_flag(err_d, st));
-        unsigned long long kept = 0;
-        SAR_HIP(hipMemcpyAsync(&kept, kept_d, sizeof(kept), hipMemcpyDeviceToHost, st));
-        SAR_HIP(hipStreamSynchronize(st));
-        if (kept >= (1ull << 31))
-            return sar::fail(SAR_ERR_UNSUPPORTED, "worker %d's share holds %llu in-edges; a handle holds fewer than 2^31",
-                             p, kept);
-    }
-    SAR_TRY(exclusive_scan(row_cnt, row_off, n_rows_all + 1, st, tmp));
-    std::vector<int32_t> block_first(P + 1);
-    for (int q = 0; q <= P; ++q)
-        SAR_HIP(hipMemcpyAsync(&block_first[q], row_off + (int64_t)q * n_dst, sizeof(int32_t),
-                               hipMemcpyDeviceToHost, st));
-    SAR_HIP(hipStreamSynchronize(st));
-    const int64_t nnz_total = block_first[P];
-    int32_t *indices_all = nullptr, *indptr_all = nullptr;
-    SAR_TRY(own(h, &indices_all, nnz_total));
     SAR_TRY(own(h, &indptr_all, (int64_t)P * (n_dst + 1)));
+    int64_t nnz_total = 0;
+    auto group = [&](auto in) -> int {
+        const int vbits = h->tag_shift;
+        BucketPlan plan = plan_buckets(std::min(kKeysPerPass, std::max<int64_t>(n_rows_all, 1)), E);
+        const bool narrow = plan.w + vbits <= 32;
+        int32_t* counts = nullptr;
+        SAR_TRY(tmp.alloc(&counts, (int64_t)plan.n_buckets() * plan.n_tiles + 1));
+        int32_t base = 0;
+        for (int64_t key0 = 0; key0 < std::max<int64_t>(n_rows_all, 1); key0 += kKeysPerPass) {
+            const int64_t nk = std::min(kKeysPerPass, n_rows_all - key0);
+            const bool first = key0 == 0, last = key0 + nk >= n_rows_all;
+            const int64_t n_counts = (int64_t)plan.n_buckets() * plan.n_tiles + 1;
+            const size_t lds = plan.n_buckets() * sizeof(int);
+            const Deal deal{plan.nb};
+            SAR_HIP(hipMemsetAsync(counts + n_counts - 1, 0, sizeof(int32_t), st));
+            SAR_TRY(allow_lds(k_bucket_count<decltype(in)>, lds));
+            k_bucket_count<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(in, plan.tile, plan.n_tiles, key0, nk, deal,
+                                                                                counts, first ? kept_d : nullptr);
+            SAR_LAUNCH_CHECK();
+            SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
+            if (first) {
+                unsigned long long kept = 0;
+                SAR_HIP(hipMemcpyAsync(&kept, kept_d, sizeof(kept), hipMemcpyDeviceToHost, st));
+                SAR_TRY(check_err_flag(err_d, st));
+                if (kept >= (1ull << 31))
+                    return sar::fail(SAR_ERR_UNSUPPORTED,
+                                     "worker %d's share holds %llu in-edges; a handle holds fewer than 2^31", p, kept);
+                nnz_total = (int64_t)kept;
+                SAR_TRY(own(h, &indices_all, nnz_total));
+                SAR_TRY(scratch.take(tmp, (size_t)nnz_total * (narrow ? 4 : 8)));
+                if (n_rows_all == 0) break;
+            }
+            auto place = [&](auto* pairs) -> int {
+                using PairT = std::remove_pointer_t<decltype(pairs)>;
+                SAR_TRY(allow_lds(k_bucket_scatter<decltype(in), PairT>, lds));
+                k_bucket_scatter<decltype(in), PairT><<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(
+                    in, plan.tile, plan.n_tiles, key0, nk, deal, vbits, counts, pairs);
+                SAR_LAUNCH_CHECK();
+                return finish_buckets<PairT>(plan, pairs, counts, nk, vbits, base, row_off + key0, indices_all, tmp, st);
+            };
+            SAR_TRY(narrow ? place(static_cast<uint32_t*>(scratch.pairs)) : place(static_cast<uint64_t*>(scratch.pairs)));
+            if (!last) {
+                int32_t in_pass = 0;
+                SAR_HIP(hipMemcpyAsync(&in_pass, counts + n_counts - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+                SAR_HIP(hipStreamSynchronize(st));
+                base += in_pass;
+            }
+        }
+        return SAR_OK;
+    };
     if (E > 0) {
         if (idx_bytes == 4)
-            k_edge_scatter<int32_t><<<ge, kThreads, 0, st>>>((const int32_t*)src, (const int32_t*)dst, E,
-                                                             part, N, p, lid, n_dst, row_cnt, row_off,
-                                                             indices_all);
+            SAR_TRY(group(EdgeSource<int32_t>{(const int32_t*)src, (const int32_t*)dst, code, E, N, n_dst, p, h->tag_shift, err_d}));
         else
-            k_edge_scatter<int64_t><<<ge, kThreads, 0, st>>>((const int64_t*)src, (const int64_t*)dst, E,
-                                                             part, N, p, lid, n_dst, row_cnt, row_off,
-                                                             indices_all);
-        SAR_LAUNCH_CHECK();
+            SAR_TRY(group(EdgeSource<int64_t>{(const int64_t*)src, (const int64_t*)dst, code, E, N, n_dst, p, h->tag_shift, err_d}));
     }
-    SAR_TRY(sort_rows(row_off, n_rows_all, indices_all, nnz_total, st, tmp));
+    if (E == 0 || n_rows_all == 0) {
+        SAR_HIP(hipMemsetAsync(row_off, 0, (n_rows_all + 1) * sizeof(int32_t), st));
+        if (!indices_all) SAR_TRY(own(h, &indices_all, 0));
+    }
     k_make_indptr<<<grid_for((int64_t)P * (n_dst + 1)), kThreads, 0, st>>>(row_off, n_dst, P, indptr_all);
     SAR_LAUNCH_CHECK();
+    std::vector<int32_t> block_first(P + 1, 0);
+    if (n_dst > 0) {
+        SAR_TRY(read_every(row_off, n_dst, P, block_first.data(), tmp, st));
+        SAR_HIP(hipStreamSynchronize(st));
+    }
     for (int q = 0; q < P; ++q) {
         h->blk[q].nnz = block_first[q + 1] - block_first[q];
         h->blk[q].indptr = indptr_all + (int64_t)q * (n_dst + 1);
         h->blk[q].indices = indices_all + block_first[q];
     }
-    SAR_HIP(hipStreamSynchronize(st));
     return SAR_OK;
 }
 
 // ------------------------------------------------ destination subsets
 
-// cnt[r] = length of row ids[r] (0 and an error flag for an id out of range); cnt[n_sub] = 0
-__global__ __launch_bounds__(kThreads) void k_subset_count(const int32_t* __restrict__ indptr,
-                                                           const int32_t* __restrict__ ids, int64_t n_sub,
-                                                           int64_t n_dst, int32_t* __restrict__ cnt, int* err)
+// cnt[q n_sub + r] = length of row ids[r] of block q (0 and an error flag for an id out of range)
+__global__ __launch_bounds__(kThreads) void k_subset_count(const BlkDev* __restrict__ from, const int32_t* __restrict__ ids,
+                                                           int64_t n_sub, int64_t n_dst, int32_t* __restrict__ cnt, int* err)
 {
-    for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r <= n_sub; r += (int64_t)gridDim.x * kThreads) {
+    const int32_t* indptr = from[blockIdx.y].indptr;
+    for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r < n_sub; r += (int64_t)gridDim.x * kThreads) {
         int c = 0;
-        if (r < n_sub) {
-            const int i = ids[r];
-            if (i < 0 || i >= n_dst)
-                atomicOr(err, 16);
-            else
-                c = indptr[i + 1] - indptr[i];
-        }
-        cnt[r] = c;
+        const int i = ids[r];
+        if (i < 0 || i >= n_dst)
+            atomicOr(err, 16);
+        else
+            c = indptr[i + 1] - indptr[i];
+        cnt[(int64_t)blockIdx.y * n_sub + r] = c;
     }
 }
 
-// new row r = old row ids[r], one wavefront per row
-__global__ __launch_bounds__(kThreads) void k_subset_copy(const int32_t* __restrict__ indptr,
-                                                          const int32_t* __restrict__ indices,
+// new row r of block q = its old row ids[r], 16 lanes per row
+__global__ __launch_bounds__(kThreads) void k_subset_copy(const BlkDev* __restrict__ from,
                                                           const int32_t* __restrict__ ids, int64_t n_sub,
-                                                          const int32_t* __restrict__ new_indptr,
+                                                          const int32_t* __restrict__ row_off,
                                                           int32_t* __restrict__ new_indices)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
-    const int64_t n_waves = ((int64_t)gridDim.x * kThreads) >> 6;
-    for (int64_t r = wave; r < n_sub; r += n_waves) {
+    constexpr int kLanes = 16;
+    const int32_t* indptr = from[blockIdx.y].indptr;
+    const int32_t* indices = from[blockIdx.y].indices;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int64_t first = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kLanes;
+    const int64_t step = ((int64_t)gridDim.x * kThreads) / kLanes;
+    for (int64_t r = first; r < n_sub; r += step) {
         const int i = ids[r];
-        const int beg = indptr[i], len = indptr[i + 1] - beg, at = new_indptr[r];
-        for (int k = lane; k < len; k += 64) new_indices[at + k] = indices[beg + k];
+        const int beg = indptr[i], len = indptr[i + 1] - beg, at = row_off[(int64_t)blockIdx.y * n_sub + r];
+        for (int k = lane; k < len; k += kLanes) new_indices[at + k] = indices[beg + k];
     }
 }
 
+// Frees the handle's arrays once nothing on its device uses them any more.
 void destroy(sar_blocks* h)
 {
     if (!h) return;
-    for (void* p : h->owned) (void)hipFree(p);
+    int current = h->device;
+    (void)hipGetDevice(&current);
+    if (current != h->device) (void)hipSetDevice(h->device);
+    if (!h->owned.empty()) (void)hipDeviceSynchronize();
+    for (auto& p : h->owned) pool().give(h->device, p.first, p.second);
+    pool().count_handle(h->device, -1);
+    if (current != h->device) (void)hipSetDevice(current);
     delete h;
+}
+
+// A handle on the current device.
+int new_handle(sar_blocks** out)
+{
+    sar_blocks* h = new (std::nothrow) sar_blocks();
+    if (!h) return sar::fail(SAR_ERR_HIP, "out of host memory");
+    const hipError_t e = hipGetDevice(&h->device);
+    if (e != hipSuccess) {
+        delete h;
+        return sar::fail(SAR_ERR_HIP, "hipGetDevice failed: %s", hipGetErrorString(e));
+    }
+    pool().count_handle(h->device, +1);
+    *out = h;
+    return SAR_OK;
 }
 
 }  // namespace
@@ -1085,13 +1715,15 @@ extern "C" int sar_blocks_build(const void* src, const void* dst, int idx_bytes,
                          "SAR_BUILD_FUSED and use the per-block calls", P, SAR_MAX_BLOCKS);
     if (N >= ((int64_t)1 << 31))
         return sar::fail(SAR_ERR_UNSUPPORTED, "N must be below 2^31 (32-bit node ids inside the handle)");
-    sar_blocks* h = new (std::nothrow) sar_blocks();
-    if (!h) return sar::fail(SAR_ERR_HIP, "out of host memory");
+    sar_blocks* h = nullptr;
+    SAR_TRY(new_handle(&h));
     h->P = P;
     h->flags = flags;
     hipStream_t st = sar::as_stream(stream);
-    int rc = build_from_edges(h, src, dst, idx_bytes, E, part, N, P, p, st);
-    if (rc == SAR_OK) rc = derive(h, st);
+    DeviceTemps tmp(st, h->device);
+    PairScratch scratch;
+    int rc = build_from_edges(h, src, dst, idx_bytes, E, part, N, P, p, tmp, scratch, st);
+    if (rc == SAR_OK) rc = derive(h, tmp, scratch, st);
     if (rc != SAR_OK) {
         destroy(h);
         return rc;
@@ -1120,36 +1752,49 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
     }
     SAR_CHECK_ARG(n_dst < ((int64_t)1 << 31), "n_dst must be below 2^31");
     hipStream_t st = sar::as_stream(stream);
-    sar_blocks* h = new (std::nothrow) sar_blocks();
-    if (!h) return sar::fail(SAR_ERR_HIP, "out of host memory");
+    sar_blocks* h = nullptr;
+    SAR_TRY(new_handle(&h));
     h->P = P;
     h->n_dst = n_dst;
     h->flags = flags;
     h->blk.resize(P);
     auto body = [&]() -> int {
-        DeviceTemps tmp;
+        DeviceTemps tmp(st, h->device);
+        PairScratch scratch;
         int* err_d = nullptr;
+        int32_t* ends_d = nullptr;
+        BlkDev* blk_d = nullptr;
         SAR_TRY(tmp.alloc(&err_d, 1));
+        SAR_TRY(tmp.alloc(&ends_d, 2 * P));
+        SAR_TRY(tmp.alloc(&blk_d, P));
         SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
+        std::vector<BlkDev> blk(P);
+        std::vector<int32_t> ends(2 * P);
         for (int q = 0; q < P; ++q) {
             Block& b = h->blk[q];
             b.n_dst = n_dst;
             b.n_src = n_src[q];
             b.indptr = indptr[q];
             b.indices = indices[q];
-            int32_t ends[2] = {0, 0};
-            SAR_HIP(hipMemcpyAsync(&ends[0], indptr[q], sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            SAR_HIP(hipMemcpyAsync(&ends[1], indptr[q] + n_dst, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            SAR_HIP(hipStreamSynchronize(st));
-            SAR_CHECK_ARG(ends[0] == 0 && ends[1] >= 0, "indptr[%d] must start at 0 and end >= 0", q);
-            b.nnz = ends[1];
-            SAR_CHECK_ARG(b.nnz == 0 || indices[q] != nullptr, "indices[%d] is null", q);
-            k_check_columns<<<grid_for(std::max(b.nnz, n_dst), kThreads, 4096), kThreads, 0, st>>>(
-                b.indptr, b.indices, n_dst, b.nnz, b.n_src, err_d);
-            SAR_LAUNCH_CHECK();
+            blk[q] = BlkDev{indptr[q], indices[q], n_src[q], 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
         }
+        SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+        k_block_ends<<<1, kThreads, 0, st>>>(blk_d, P, n_dst, ends_d);
+        SAR_LAUNCH_CHECK();
+        SAR_HIP(hipMemcpyAsync(ends.data(), ends_d, 2 * P * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        SAR_HIP(hipStreamSynchronize(st));
+        int64_t most = n_dst;
+        for (int q = 0; q < P; ++q) {
+            SAR_CHECK_ARG(ends[2 * q] == 0 && ends[2 * q + 1] >= 0, "indptr[%d] must start at 0 and end >= 0", q);
+            blk[q].nnz = h->blk[q].nnz = ends[2 * q + 1];
+            SAR_CHECK_ARG(blk[q].nnz == 0 || indices[q] != nullptr, "indices[%d] is null", q);
+            most = std::max(most, blk[q].nnz);
+        }
+        SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+        k_check_columns<<<dim3(grid_for(most, kThreads, std::max(1, 4096 / P)), P), kThreads, 0, st>>>(blk_d, n_dst, err_d);
+        SAR_LAUNCH_CHECK();
         SAR_TRY(check_err_flag(err_d, st));
-        return derive(h, st);
+        return derive(h, tmp, scratch, st);
     };
     int rc = body();
     if (rc != SAR_OK) {
@@ -1226,44 +1871,61 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
     SAR_CHECK_ARG(n_sub == 0 || dst_ids != nullptr, "dst_ids is null");
     SAR_CHECK_ARG((flags & ~kKnownFlags) == 0, "unknown flags 0x%x", flags);
     hipStream_t st = sar::as_stream(stream);
-    sar_blocks* h = new (std::nothrow) sar_blocks();
-    if (!h) return sar::fail(SAR_ERR_HIP, "out of host memory");
+    sar_blocks* h = nullptr;
+    SAR_TRY(new_handle(&h));
     h->P = b->P;
     h->n_dst = n_sub;
     h->flags = flags;
     h->blk.resize(b->P);
     auto body = [&]() -> int {
-        DeviceTemps tmp;
+        DeviceTemps tmp(st, h->device);
+        PairScratch scratch;
+        const int P = b->P;
+        const int64_t n_rows_all = (int64_t)P * n_sub;
         int* err_d = nullptr;
+        BlkDev* blk_d = nullptr;
+        int32_t *row_off = nullptr, *indptr_all = nullptr, *indices_all = nullptr;
         SAR_TRY(tmp.alloc(&err_d, 1));
-        SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
-        for (int q = 0; q < b->P; ++q) {
+        SAR_TRY(tmp.alloc(&blk_d, P));
+        SAR_TRY(tmp.alloc(&row_off, n_rows_all + 1));
+        SAR_TRY(own(h, &indptr_all, (int64_t)P * (n_sub + 1)));
+        std::vector<BlkDev> blk(P);
+        for (int q = 0; q < P; ++q) {
             const Block& from = b->blk[q];
-            Block& to = h->blk[q];
-            to.n_dst = n_sub;
-            to.n_src = from.n_src;
-            int32_t* indptr = nullptr;
-            SAR_TRY(own(h, &indptr, n_sub + 1));
-            k_subset_count<<<grid_for(n_sub + 1, kThreads, 4096), kThreads, 0, st>>>(from.indptr, dst_ids, n_sub,
-                                                                                    b->n_dst, indptr, err_d);
-            SAR_LAUNCH_CHECK();
-            SAR_TRY(exclusive_scan(indptr, indptr, n_sub + 1, st, tmp));
-            int32_t nnz = 0;
-            SAR_HIP(hipMemcpyAsync(&nnz, indptr + n_sub, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            SAR_TRY(check_err_flag(err_d, st));      // synchronises; ids are in range beyond this point
-            if (nnz < 0) return sar::fail(SAR_ERR_UNSUPPORTED, "block %d of the subset holds 2^31 edges or more", q);
-            int32_t* indices = nullptr;
-            SAR_TRY(own(h, &indices, nnz));
-            if (nnz > 0) {
-                k_subset_copy<<<grid_for(n_sub * 64, kThreads, 1 << 16), kThreads, 0, st>>>(
-                    from.indptr, from.indices, dst_ids, n_sub, indptr, indices);
-                SAR_LAUNCH_CHECK();
-            }
-            to.indptr = indptr;
-            to.indices = indices;
-            to.nnz = nnz;
+            h->blk[q].n_dst = n_sub;
+            h->blk[q].n_src = from.n_src;
+            blk[q] = BlkDev{from.indptr, from.indices, from.n_src, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
         }
-        return derive(h, st);
+        SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+        SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
+        SAR_HIP(hipMemsetAsync(row_off + n_rows_all, 0, sizeof(int32_t), st));
+        std::vector<int32_t> block_first(P + 1, 0);
+        if (n_sub > 0) {
+            k_subset_count<<<dim3(grid_for(n_sub, kThreads, std::max(1, 4096 / P)), P), kThreads, 0, st>>>(
+                blk_d, dst_ids, n_sub, b->n_dst, row_off, err_d);
+            SAR_LAUNCH_CHECK();
+            SAR_TRY(exclusive_scan(row_off, row_off, n_rows_all + 1, st, tmp));
+            SAR_TRY(read_every(row_off, n_sub, P, block_first.data(), tmp, st));
+        }
+        SAR_TRY(check_err_flag(err_d, st));      // synchronises; ids are in range beyond this point
+        // the offsets are 32-bit: repeated ids may list more edges than the handle they come from
+        for (int q = 0; q < P; ++q)
+            if (block_first[q + 1] < block_first[q])
+                return sar::fail(SAR_ERR_UNSUPPORTED, "the subset holds 2^31 edges or more");
+        SAR_TRY(own(h, &indices_all, block_first[P]));
+        if (block_first[P] > 0) {
+            k_subset_copy<<<dim3(grid_for(n_sub * 16, kThreads, std::max(1, (1 << 16) / P)), P), kThreads, 0, st>>>(
+                blk_d, dst_ids, n_sub, row_off, indices_all);
+            SAR_LAUNCH_CHECK();
+        }
+        k_make_indptr<<<grid_for((int64_t)P * (n_sub + 1)), kThreads, 0, st>>>(row_off, n_sub, P, indptr_all);
+        SAR_LAUNCH_CHECK();
+        for (int q = 0; q < P; ++q) {
+            h->blk[q].nnz = block_first[q + 1] - block_first[q];
+            h->blk[q].indptr = indptr_all + (int64_t)q * (n_sub + 1);
+            h->blk[q].indices = indices_all + block_first[q];
+        }
+        return derive(h, tmp, scratch, st);
     };
     int rc = body();
     if (rc != SAR_OK) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
 #include <vector>
 
 #include "../../include/sar_mi355x.h"
@@ -82,6 +83,7 @@ int gat_scores2(const void* Z, int dtype, int64_t n, int H, int D, const float* 
 }  // namespace sar
 
 struct sar_blocks {
+    int device = 0;                // where its arrays are
     int P = 0;
     int64_t n_dst = 0;
     int flags = 0;
@@ -105,5 +107,5 @@ struct sar_blocks {
     uint32_t* s_src = nullptr;
     int32_t* s_row = nullptr;
     int64_t n_single = 0;
-    std::vector<void*> owned;      // device allocations freed with the handle
+    std::vector<std::pair<void*, size_t>> owned;   // device allocations (and their sizes) freed with the handle
 };
