@@ -74,11 +74,9 @@ struct GemmArgs {
     int64_t M;        // rows of C
     int N;            // cols of C
     int64_t Kd;       // contraction length
-    int64_t lda;      // A_K_FAST: A(i,k) = A[i*lda + k]   else A(i,k) = A[k*lda + i]
+    int64_t lda;      // A(i,k) = A[i*lda + k]
     int64_t ldb;      // B_K_FAST: B(k,j) = B[j*ldb + k]   else B(k,j) = B[k*ldb + j]
     int64_t ldc;
-    int64_t k_slab;   // contraction range per blockIdx.z (split-K); C advances by c_split per slab
-    int64_t c_split;
     int vec_a, vec_b; // 4-element groups of A / B are aligned and in one row
 };
 
@@ -132,8 +130,8 @@ struct Stage {
 
 static_assert(BM == BN, "operand staging assumes square workgroup tiles");
 
-// A_K_FAST: A is contiguous along the contraction; B_K_FAST: same for B.
-template <typename TA, typename TB, typename TC, bool A_K_FAST, bool B_K_FAST>
+// A is contiguous along the contraction; B_K_FAST: so is B.
+template <typename TA, typename TB, typename TC, bool B_K_FAST>
 __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g)
 {
     __shared__ __attribute__((aligned(16))) float As[BK][BM + kPad];
@@ -144,8 +142,7 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g)
     const int wm = wave >> 1, wn = wave & 1;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int64_t n0 = (int64_t)blockIdx.y * BN;
-    const int64_t k_beg = (int64_t)blockIdx.z * g.k_slab;
-    const int64_t k_end = std::min<int64_t>(g.Kd, k_beg + g.k_slab);
+    const int64_t k_beg = 0, k_end = g.Kd;
 
     float16_t acc[2][2];
 #pragma unroll
@@ -155,7 +152,7 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-    Stage<TA, A_K_FAST> sa;
+    Stage<TA, true> sa;
     Stage<TB, B_K_FAST> sb;
     if (k_beg < k_end) {
         sa.fetch(A, g.lda, m0, g.M, k_beg, k_end, g.vec_a, tid);
@@ -189,7 +186,7 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g)
     }
 
     // lane holds column (lane % 32); register r holds row 8*(r/4) + 4*(lane/32) + r%4
-    TC* C = static_cast<TC*>(g.C) + (int64_t)blockIdx.z * g.c_split;
+    TC* C = static_cast<TC*>(g.C);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -245,20 +242,19 @@ __device__ inline void commit_bf16(const float (&v)[kPerThread][4], uint16_t (*h
     }
 }
 
-template <typename TA, typename TB, typename TC, bool A_K_FAST, bool B_K_FAST, bool SPLIT_B>
+template <typename TA, typename TB, typename TC, bool B_K_FAST>
 __global__ __launch_bounds__(kGemmThreads) void k_gemm_bf16(GemmArgs g)
 {
     __shared__ __attribute__((aligned(16))) uint16_t As[BM][BK + kPadH];
     __shared__ __attribute__((aligned(16))) uint16_t Bh[BN][BK + kPadH];
-    __shared__ __attribute__((aligned(16))) uint16_t Bl[SPLIT_B ? BN : 1][BK + kPadH];
+    __shared__ __attribute__((aligned(16))) uint16_t Bl[BN][BK + kPadH];
     const TA* A = static_cast<const TA*>(g.A);
     const TB* B = static_cast<const TB*>(g.B);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int64_t n0 = (int64_t)blockIdx.y * BN;
-    const int64_t k_beg = (int64_t)blockIdx.z * g.k_slab;
-    const int64_t k_end = std::min<int64_t>(g.Kd, k_beg + g.k_slab);
+    const int64_t k_beg = 0, k_end = g.Kd;
 
     float16_t acc[2][2];
 #pragma unroll
@@ -268,15 +264,15 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_bf16(GemmArgs g)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-    Stage<TA, A_K_FAST> sa;
+    Stage<TA, true> sa;
     Stage<TB, B_K_FAST> sb;
     if (k_beg < k_end) {
         sa.fetch(A, g.lda, m0, g.M, k_beg, k_end, g.vec_a, tid);
         sb.fetch(B, g.ldb, n0, g.N, k_beg, k_end, g.vec_b, tid);
     }
     for (int64_t k0 = k_beg; k0 < k_end; k0 += BK) {
-        commit_bf16<A_K_FAST>(sa.v, As, nullptr, tid);
-        commit_bf16<B_K_FAST>(sb.v, Bh, SPLIT_B ? Bl : nullptr, tid);
+        commit_bf16<true>(sa.v, As, nullptr, tid);
+        commit_bf16<B_K_FAST>(sb.v, Bh, Bl, tid);
         __syncthreads();
         if (k0 + BK < k_end) {
             sa.fetch(A, g.lda, m0, g.M, k0 + BK, k_end, g.vec_a, tid);
@@ -290,20 +286,20 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_bf16(GemmArgs g)
             for (int x = 0; x < 2; ++x) {
                 a[x] = *reinterpret_cast<const bf16x8_t*>(&As[wm * 64 + x * 32 + (lane & 31)][kk]);
                 bh[x] = *reinterpret_cast<const bf16x8_t*>(&Bh[wn * 64 + x * 32 + (lane & 31)][kk]);
-                if (SPLIT_B) bl[x] = *reinterpret_cast<const bf16x8_t*>(&Bl[wn * 64 + x * 32 + (lane & 31)][kk]);
+                bl[x] = *reinterpret_cast<const bf16x8_t*>(&Bl[wn * 64 + x * 32 + (lane & 31)][kk]);
             }
 #pragma unroll
             for (int x = 0; x < 2; ++x)
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
                     acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bh[y], acc[x][y], 0, 0, 0);
-                    if (SPLIT_B) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bl[y], acc[x][y], 0, 0, 0);
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bl[y], acc[x][y], 0, 0, 0);
                 }
         }
         __syncthreads();
     }
 
-    TC* C = static_cast<TC*>(g.C) + (int64_t)blockIdx.z * g.c_split;
+    TC* C = static_cast<TC*>(g.C);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -384,6 +380,17 @@ constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = 64 * kSkinnyWaves;
 constexpr size_t kSkinnyMaxLds = 160 * 1024;   // all of a CU's LDS: one workgroup per CU then
 
+// Any alignment (gfx950 takes unaligned vector accesses).
+struct __attribute__((packed, aligned(2))) U4Any {
+    uint32_t x, y, z, w;
+};
+__device__ inline uint4 load16(const void* p)
+{
+    const U4Any r = *static_cast<const U4Any*>(p);
+    return make_uint4(r.x, r.y, r.z, r.w);
+}
+__device__ inline void store16(void* p, const uint4& v) { *static_cast<U4Any*>(p) = U4Any{v.x, v.y, v.z, v.w}; }
+
 struct SkinnyArgs {
     const void* A;     // [M, K], row stride lda, contraction index contiguous
     int64_t lda, M;
@@ -406,6 +413,31 @@ struct SkinnyArgs {
     RowsOp op;         // FUSE only: how the rows of A are formed
 };
 
+
+// The last `rest` values of a 16-byte piece, moved to its front, zeros behind them.
+template <typename T>
+__device__ inline uint4 front_of_piece(const uint4& v, int rest);
+template <>
+__device__ inline uint4 front_of_piece<float>(const uint4& v, int rest)
+{
+    return rest == 3 ? make_uint4(v.y, v.z, v.w, 0u) : rest == 2 ? make_uint4(v.z, v.w, 0u, 0u) : make_uint4(v.w, 0u, 0u, 0u);
+}
+template <>
+__device__ inline uint4 front_of_piece<bf16_t>(const uint4& v, int rest)
+{
+    // down by 8 - rest halves: whole words first, then half a word
+    const int words = (8 - rest) >> 1;
+    uint32_t w[5] = {v.x, v.y, v.z, v.w, 0u}, o[4];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const bool shift = s < words;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = shift ? w[k + 1] : w[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = (rest & 1) ? (w[k] >> 16) | (w[k + 1] << 16) : w[k];
+    return make_uint4(o[0], o[1], o[2], o[3]);
+}
 
 // FUSE: the rows of A are not stored; each piece is formed where it is multiplied (RowsOp, K <= 256).
 // Between the epilogues a wavefront's staging tile is idle, so it holds what the pieces need: the
@@ -512,20 +544,23 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
 
     const TA* A = static_cast<const TA*>(g.A);
     const int64_t n_tiles = (g.M + 31) / 32;
+    // a few tiles spread over the workgroups before they fill one
     const int64_t stride = (int64_t)gridDim.x * kSkinnyWaves;
-    int64_t tile = (int64_t)blockIdx.x * kSkinnyWaves + wave;
+    int64_t tile = (int64_t)blockIdx.x + (int64_t)gridDim.x * wave;
     if (tile >= n_tiles) return;
 
-    // K is a multiple of the lane's piece, so a piece is inside the row or beyond it.  Loads are
-    // unconditional (a piece beyond the row is read from the row's last piece, and zeroed where it
-    // is used) and the main loop below is straight-line code, so that the compiler can count the
+    // Loads are unconditional (a piece that would end beyond the row is read from the row's last 16
+    // bytes; what of it is beyond, or the piece before it carries as well, is zeroed where it is used)
+    // and the main loop below is straight-line code, so that the compiler can count the
     // loads in flight and wait for the oldest only; with branches around them it waits for all of
     // them at every chunk, which leaves the ring no depth.
     const int k_last = g.K - kChunk / 2;
     auto load_piece = [&](const TA* rowp, int t) -> uint4 {
         const int k = t * kChunk + gq * (kChunk / 2);
-        return *reinterpret_cast<const uint4*>(rowp + min(k, k_last));
+        return load16(rowp + min(k, k_last));
     };
+    // a piece that starts at k_first < K and was read from k_last < k_first: its values move to the front
+    const int rest = g.K % (kChunk / 2);
     auto row_ptr = [&](int64_t tl) { return A + std::min<int64_t>(tl * 32 + c, g.M - 1) * g.lda; };
 
     // FUSE: where this lane's row of the stored part is (row 0, and `has` false, where there is none:
@@ -613,6 +648,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
             const bool beyond = k_first >= g.K;
             uint4 av = make_uint4(beyond ? 0u : piece.x, beyond ? 0u : piece.y, beyond ? 0u : piece.z,
                                   beyond ? 0u : piece.w);
+            if (rest != 0 && k_first <= g.K && k_first > k_last) av = front_of_piece<TA>(av, rest);
             if constexpr (FUSE) {
                 if (!has) av = make_uint4(0u, 0u, 0u, 0u);
                 // a_r is zero beyond K, so a piece beyond the row stays zero
@@ -725,7 +761,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
                     const int64_t i = row0 + row, n = n0 + nt * 32 + piece * kPer;
                     if (i < g.M) {
                         if (n + kPer <= g.N) {
-                            *reinterpret_cast<uint4*>(C + i * g.ldc + n) = *reinterpret_cast<const uint4*>(from);
+                            store16(C + i * g.ldc + n, *reinterpret_cast<const uint4*>(from));
                         } else {
                             for (int e = 0; e < kPer && n + e < g.N; ++e) C[i * g.ldc + n + e] = from[e];
                         }
@@ -767,24 +803,23 @@ struct SkinnyPlan {
     int stage_off = 0;   // see SkinnyArgs
 };
 
-// Whether the skinny kernel applies: 16-byte pieces of A rows must be aligned
-// and whole, and the small operand must fit in LDS in at most four column slabs.
-bool plan_skinny(const void* A, int64_t lda, const void* C, int64_t ldc, int K, int N, int dtype, int extra_tiles,
-                 SkinnyPlan* p)
+// Whether the skinny kernel applies: the contraction must be at least a 16-byte piece long, and the
+// small operand must fit in LDS in at most four column slabs.
+bool plan_skinny(int K, int N, int dtype, int extra_tiles, SkinnyPlan* p)
 {
     const int elem = dtype == SAR_F32 ? 4 : 2, piece = 16 / elem;
-    if (reinterpret_cast<uintptr_t>(A) % 16 != 0 || (lda * elem) % 16 != 0 || K % piece != 0) return false;
+    if (K < piece) return false;
     const int chunk = 2 * piece;
     p->chunks = (K + chunk - 1) / chunk;
     const size_t unit = dtype == SAR_F32 ? 1024 : 2048;
     const int need = (N + 31) / 32;
     int nt = 1;
     while (nt < need && nt < 8) nt *= 2;
-    // Outputs go through staging tiles when their 16-byte pieces are aligned: always for 2-byte
+    // Outputs go through staging tiles: always for 2-byte
     // outputs (stored directly they are scattered 2-byte writes), for 4-byte outputs when the
     // tiles fit beside the small operand without narrowing the slab
-    bool stage = reinterpret_cast<uintptr_t>(C) % 16 == 0 && (ldc * elem) % 16 == 0;
-    size_t stage_bytes = stage ? (size_t)kSkinnyWaves * 32 * 32 * elem : 0;
+    bool stage = true;
+    size_t stage_bytes = (size_t)kSkinnyWaves * 32 * 32 * elem;
     auto fits = [&](int t, size_t extra) {
         return (size_t)p->chunks * (t + extra_tiles) * unit + extra <= kSkinnyMaxLds;
     };
@@ -816,11 +851,10 @@ int launch_skinny_nt(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
     SAR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_skinny<TA, TC, NT, SC, FUSE>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds));
     const int64_t tiles = (g.M + 31) / 32;
-    const int64_t want = (tiles + kSkinnyWaves - 1) / kSkinnyWaves;
     // one workgroup per CU; two where registers (NT <= 4) and LDS leave room
     const int per_cu = (NT <= 4 && 2 * p.lds <= 150 * 1024) ? 2 : 1;
     const int64_t resident = std::max<int64_t>(1, (int64_t)n_cu * per_cu / p.slabs);
-    dim3 grid((unsigned)std::max<int64_t>(1, std::min(want, resident)), p.slabs, 1);
+    dim3 grid((unsigned)std::max<int64_t>(1, std::min(tiles, resident)), p.slabs, 1);
     k_gemm_skinny<TA, TC, NT, SC, FUSE><<<grid, kSkinnyThreads, p.lds, st>>>(g);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
@@ -855,58 +889,97 @@ bool plan_takes_rows_op(const SkinnyPlan& p, int K, int H, int dtype)
 // buffered, one barrier per chunk) and the wavefronts read their fragments
 // column-wise from there: one element per lane and row, which costs LDS
 // instructions but no bank conflicts (row strides put the two lane groups of
-// a fragment on different banks).  The output tile is 128 x 256: four kf-tiles
-// by two n-tiles per wavefront, 128 accumulator registers.  Rows are split
-// into slabs over the grid; each slab writes its partial tile, summed below.
+// a fragment on different banks).  The output tile is 128 x NW, two n-tiles and
+// four kf-tiles per wavefront (128 accumulator registers); tiles beyond K or N
+// are skipped.  NW = 256: the four wavefronts side by side.  NW = 128: two by
+// two, the pairs taking every other row step of a chunk and adding up through
+// LDS at the end.  NW = 64: the same with the kf-tiles dealt to the halves of
+// a pair.  Rows are split into slabs over the grid; each slab writes its
+// partial tile, summed below.  Rows of any width and alignment: the last unit
+// of a row that is no whole number of them is read where the row ends and moved
+// to its front (RAG).
+//
+// What this measured, before (one 128 x 256 shape, no slab below 128 rows, a general tiled kernel for
+// other widths) and now: 64 x 64 over 4096 rows 31 -> 9.7 us, where every wavefront's four by two
+// tiles were multiplied though one in eight existed; bf16 254 x 200 over 30000 rows and other widths
+// off 16 bytes 28..59 -> 10..25 us.  The large products (fp32, 256 x 256 over 157000 rows, 404 us)
+// are as they were: bound by the fp32 matrix rate.  Two wavefronts per SIMD have to be asked for: with
+// the guarded and the unguarded row step both in it the compiler takes one (366 -> 415 us).
 
-constexpr int kDwKf = 128, kDwN = 256;
+constexpr int kDwKf = 128;
 
 template <typename T>
 struct DwShape;
 template <>
 struct DwShape<float> {
     static constexpr int kRows = 16;          // rows per chunk
-    static constexpr int kXs = kDwKf + 32;    // LDS row strides in elements: consecutive rows
-    static constexpr int kDs = kDwN + 32;     // (the two lane groups) 32 banks apart
+    static constexpr int kPad = 32;           // LDS row strides: consecutive rows (the two lane groups)
+                                              // 32 banks apart
     static constexpr int kVec = 4;            // elements per 16 bytes
 };
 template <>
 struct DwShape<bf16_t> {
     static constexpr int kRows = 32;
-    static constexpr int kXs = kDwKf + 8;     // rows 8 apart (the two lane groups) 32 banks apart
-    static constexpr int kDs = kDwN + 8;
+    static constexpr int kPad = 8;            // rows 8 apart (the two lane groups) 32 banks apart
     static constexpr int kVec = 8;
 };
 
-template <typename T, bool FUSE>
-__global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __restrict__ dZ, RowsOp op,
+template <typename T, bool FUSE, int NW, bool RAG>
+__global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T* __restrict__ dZ, RowsOp op,
                                             float* __restrict__ partial, int64_t M, int K, int N,
                                             int64_t rows_per_slab)
 {
     using S = DwShape<T>;
     constexpr bool BF = sizeof(T) == 2;
     constexpr int kXUnits = S::kRows * kDwKf / S::kVec / 256;   // 16-byte units per thread and chunk
-    constexpr int kDUnits = S::kRows * kDwN / S::kVec / 256;
-    __shared__ __attribute__((aligned(16))) T Xs[2][S::kRows][S::kXs];
-    __shared__ __attribute__((aligned(16))) T Ds[2][S::kRows][S::kDs];
+    constexpr int kDUnits = S::kRows * NW / S::kVec / 256;
+    constexpr int kXs = kDwKf + S::kPad, kDs = NW + S::kPad;
+    constexpr int kCols = NW / 64, kParts = NW == 256 ? 1 : 2, kKg = 4 / kCols / kParts, kKt = 4 / kKg;
+    __shared__ __attribute__((aligned(16))) T Xs[2][S::kRows][kXs];
+    __shared__ __attribute__((aligned(16))) T Ds[2][S::kRows][kDs];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, gq = lane >> 5;
-    const int kf0 = blockIdx.z * kDwKf, n0 = blockIdx.y * kDwN;
+    const int kf0 = blockIdx.z * kDwKf, n0 = blockIdx.y * NW;
     const int64_t m_beg = (int64_t)blockIdx.x * rows_per_slab;
     const int64_t m_end = std::min<int64_t>(M, m_beg + rows_per_slab);
+    const int cw = wave % kCols, part = (wave / kCols) % kParts, kg = wave / (kCols * kParts);
+    // this wavefront's tiles that exist (its kf-tile kt is the workgroup's kt * kKg + kg)
+    const int kt_n = min(kKt, ((K - kf0 + 31) / 32 + kKg - 1 - kg) / kKg);
+    const int nt_n = max(0, min(2, (N - n0 - 64 * cw + 31) / 32));
 
+    // RAG: the unit in which a row ends is read from the row's last 16 bytes and moved to its front
+    // where it is stored (commit); rows shorter than a unit are read value by value
+    auto unit = [](const T* row, int col, int width) -> uint4 {
+        if constexpr (RAG) {
+            if (width < S::kVec) {
+                T v[S::kVec] = {};
+#pragma unroll
+                for (int x = 0; x < S::kVec; ++x)
+                    if (x < width) v[x] = row[x];
+                return __builtin_bit_cast(uint4, v);
+            }
+            col = min(col, width - S::kVec);
+        }
+        return load16(row + col);
+    };
+    auto placed = [](const uint4& v, int col, int width) -> uint4 {
+        if constexpr (RAG) {
+            if (width > S::kVec && col < width && col + S::kVec > width) return front_of_piece<T>(v, width % S::kVec);
+        }
+        return v;
+    };
     uint4 gx[kXUnits], gd[kDUnits];
     // FUSE: the rows of dZ are formed here (see RowsOp).  A thread's units keep their column, so its
     // pieces of a_r and its heads are fixed; the row map of a chunk is read one chunk ahead of the
     // rows themselves, which keeps a single level of loads in flight.
-    __shared__ __attribute__((aligned(16))) float ars[FUSE ? kDwN : 4];   // this tile's columns of a_r
+    __shared__ __attribute__((aligned(16))) float ars[FUSE ? NW : 4];   // this tile's columns of a_r
     float dsv[FUSE ? kDUnits : 1];
     int hq[FUSE ? kDUnits : 1], rk0[FUSE ? kDUnits : 1], rk1[FUSE ? kDUnits : 1];
     auto fetch_rank = [&](int64_t m0) {
         if constexpr (FUSE) {
 #pragma unroll
             for (int q = 0; q < kDUnits; ++q) {
-                const int u = tid + 256 * q, row = u / (kDwN / S::kVec);
+                const int u = tid + 256 * q, row = u / (NW / S::kVec);
                 const bool ok = op.rank != nullptr && m0 + row < m_end;
                 rk0[q] = ok ? op.rank[m0 + row] : 0;
                 rk1[q] = ok ? op.rank[m0 + row + 1] : 0;
@@ -916,13 +989,13 @@ __global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __
     if constexpr (FUSE) {
         // a piece's values four by four: the first four of every piece, then (8-value pieces) the
         // last four, so that neighbouring lanes read neighbouring 16 bytes (no bank conflicts)
-        for (int f = tid; f < kDwN; f += 256) {
+        for (int f = tid; f < NW; f += 256) {
             const int piece = f / S::kVec, x = f % S::kVec;
-            ars[(x / 4) * (kDwN / 2) + piece * 4 + (x % 4)] = (op.ds && n0 + f < N) ? op.a_r[n0 + f] : 0.f;
+            ars[(x / 4) * (NW / 2) + piece * 4 + (x % 4)] = (op.ds && n0 + f < N) ? op.a_r[n0 + f] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, col = (u % (kDwN / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, col = (u % (NW / S::kVec)) * S::kVec;
             hq[q] = n0 + col < N ? (n0 + col) / op.D : 0;
             dsv[q] = 0.f;
         }
@@ -934,11 +1007,11 @@ __global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __
         for (int q = 0; q < kXUnits; ++q) {
             const int u = tid + 256 * q, row = u / (kDwKf / S::kVec), col = (u % (kDwKf / S::kVec)) * S::kVec;
             const bool ok = m0 + row < m_end && kf0 + col < K;
-            gx[q] = ok ? *reinterpret_cast<const uint4*>(X + (m0 + row) * K + kf0 + col) : make_uint4(0u, 0u, 0u, 0u);
+            gx[q] = ok ? unit(X + (m0 + row) * K, kf0 + col, K) : make_uint4(0u, 0u, 0u, 0u);
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (kDwN / S::kVec), col = (u % (kDwN / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (NW / S::kVec), col = (u % (NW / S::kVec)) * S::kVec;
             const bool ok = m0 + row < m_end && n0 + col < N;
             if constexpr (FUSE) {
                 int64_t from = m0 + row;
@@ -950,7 +1023,7 @@ __global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __
                 gd[q] = has ? *reinterpret_cast<const uint4*>(dZ + from * N + n0 + col) : make_uint4(0u, 0u, 0u, 0u);
                 dsv[q] = (ok && op.ds) ? op.ds[(m0 + row) * op.H + hq[q]] : 0.f;
             } else {
-                gd[q] = ok ? *reinterpret_cast<const uint4*>(dZ + (m0 + row) * N + n0 + col) : make_uint4(0u, 0u, 0u, 0u);
+                gd[q] = ok ? unit(dZ + (m0 + row) * N, n0 + col, N) : make_uint4(0u, 0u, 0u, 0u);
             }
         }
         fetch_rank(m0 + S::kRows);
@@ -959,31 +1032,78 @@ __global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __
 #pragma unroll
         for (int q = 0; q < kXUnits; ++q) {
             const int u = tid + 256 * q, row = u / (kDwKf / S::kVec), col = (u % (kDwKf / S::kVec)) * S::kVec;
-            *reinterpret_cast<uint4*>(&Xs[buf][row][col]) = gx[q];
+            *reinterpret_cast<uint4*>(&Xs[buf][row][col]) = placed(gx[q], kf0 + col, K);
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (kDwN / S::kVec), col = (u % (kDwN / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (NW / S::kVec), col = (u % (NW / S::kVec)) * S::kVec;
             if constexpr (FUSE) {
                 float arv[S::kVec];
 #pragma unroll
                 for (int x = 0; x < S::kVec; x += 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(ars + (x / 4) * (kDwN / 2) + (col / S::kVec) * 4);
+                    const float4 v = *reinterpret_cast<const float4*>(ars + (x / 4) * (NW / 2) + (col / S::kVec) * 4);
                     arv[x] = v.x; arv[x + 1] = v.y; arv[x + 2] = v.z; arv[x + 3] = v.w;
                 }
                 *reinterpret_cast<uint4*>(&Ds[buf][row][col]) = fuse_piece<T>(gd[q], dsv[q], arv);
             } else
-                *reinterpret_cast<uint4*>(&Ds[buf][row][col]) = gd[q];
+                *reinterpret_cast<uint4*>(&Ds[buf][row][col]) = placed(gd[q], n0 + col, N);
         }
     };
 
-    float16_t acc[4][2];
+    float16_t acc[kKt][2];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < kKt; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+
+    constexpr int kStep = BF ? 16 : 2;   // rows per matrix instruction
+    // one row step; ALL: every tile of this wavefront exists
+    auto step = [&](int buf, int s, auto all) {
+        constexpr bool ALL = decltype(all)::value;
+        if constexpr (BF) {
+            const uint16_t(*xs)[kXs] = reinterpret_cast<const uint16_t(*)[kXs]>(Xs[buf]);
+            const uint16_t(*ds)[kDs] = reinterpret_cast<const uint16_t(*)[kDs]>(Ds[buf]);
+            const int r0 = kStep * s + 8 * gq;
+            auto column = [&](auto tile, int col) -> bf16x8_t {
+                uint32_t w[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w[e] = (uint32_t)tile[r0 + 2 * e][col] | ((uint32_t)tile[r0 + 2 * e + 1][col] << 16);
+                return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+            };
+            bf16x8_t b[2];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                if (ALL || nt < nt_n) b[nt] = column(ds, 64 * cw + 32 * nt + c);
+#pragma unroll
+            for (int kt = 0; kt < kKt; ++kt)
+                if (ALL || kt < kt_n) {
+                    const bf16x8_t a = column(xs, 32 * (kt * kKg + kg) + c);
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt)
+                        if (ALL || nt < nt_n)
+                            acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[nt], acc[kt][nt], 0, 0, 0);
+                }
+        } else {
+            const float(*xs)[kXs] = reinterpret_cast<const float(*)[kXs]>(Xs[buf]);
+            const float(*ds)[kDs] = reinterpret_cast<const float(*)[kDs]>(Ds[buf]);
+            const int r0 = kStep * s + gq;
+            float a[kKt], b[2];
+#pragma unroll
+            for (int kt = 0; kt < kKt; ++kt) a[kt] = xs[r0][32 * (kt * kKg + kg) + c];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) b[nt] = ds[r0][64 * cw + 32 * nt + c];
+#pragma unroll
+            for (int kt = 0; kt < kKt; ++kt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    if (ALL || (kt < kt_n && nt < nt_n))
+                        acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kt], b[nt], acc[kt][nt], 0, 0, 0);
+        }
+    };
+    const bool all = kt_n == kKt && nt_n == 2;
 
     if (m_beg < m_end) {
         fetch(m_beg);
@@ -994,69 +1114,45 @@ __global__ __launch_bounds__(256) void k_dw(const T* __restrict__ X, const T* __
     for (int64_t m0 = m_beg; m0 < m_end; m0 += S::kRows, buf ^= 1) {
         const bool more = m0 + S::kRows < m_end;
         if (more) fetch(m0 + S::kRows);
-        if (BF) {
-            const uint16_t(*xs)[S::kXs] = reinterpret_cast<const uint16_t(*)[S::kXs]>(Xs[buf]);
-            const uint16_t(*ds)[S::kDs] = reinterpret_cast<const uint16_t(*)[S::kDs]>(Ds[buf]);
+        if (all) {
 #pragma unroll
-            for (int s = 0; s < S::kRows / 16; ++s) {
-                const int r0 = 16 * s + 8 * gq;
-                bf16x8_t a[4], b[2];
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    uint32_t w[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        w[e] = (uint32_t)xs[r0 + 2 * e][32 * kt + c] | ((uint32_t)xs[r0 + 2 * e + 1][32 * kt + c] << 16);
-                    a[kt] = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-                }
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    uint32_t w[4];
-                    const int col = 64 * wave + 32 * nt + c;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        w[e] = (uint32_t)ds[r0 + 2 * e][col] | ((uint32_t)ds[r0 + 2 * e + 1][col] << 16);
-                    b[nt] = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-                }
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt)
-                        acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kt], b[nt], acc[kt][nt], 0, 0, 0);
-            }
+            for (int s = 0; s < S::kRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::true_type{});
         } else {
-            const float(*xs)[S::kXs] = reinterpret_cast<const float(*)[S::kXs]>(Xs[buf]);
-            const float(*ds)[S::kDs] = reinterpret_cast<const float(*)[S::kDs]>(Ds[buf]);
 #pragma unroll
-            for (int s = 0; s < S::kRows / 2; ++s) {
-                const int r0 = 2 * s + gq;
-                float a[4], b[2];
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt) a[kt] = xs[r0][32 * kt + c];
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) b[nt] = ds[r0][64 * wave + 32 * nt + c];
-#pragma unroll
-                for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt)
-                        acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kt], b[nt], acc[kt][nt], 0, 0, 0);
-            }
+            for (int s = 0; s < S::kRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::false_type{});
         }
         if (more) commit(buf ^ 1);
         __syncthreads();
+    }
+    if constexpr (kParts == 2) {
+        // the second half's sums through LDS, a kf-tile at a time (the operand buffers are free now)
+        static_assert(2 * 2 * 16 * 64 * sizeof(float) <= sizeof(Xs), "two wavefronts' kf-tiles");
+        float* mine = reinterpret_cast<float*>(&Xs[0][0][0]) + (kg * kCols + cw) * 2 * 16 * 64 + lane;
+#pragma unroll
+        for (int kt = 0; kt < kKt; ++kt) {
+            if (part == 1)
+#pragma unroll
+                for (int q = 0; q < 32; ++q) mine[q * 64] = acc[kt][q / 16][q % 16];
+            __syncthreads();
+            if (part == 0)
+#pragma unroll
+                for (int q = 0; q < 32; ++q) acc[kt][q / 16][q % 16] += mine[q * 64];
+            __syncthreads();
+        }
+        if (part == 1) return;
     }
 
     // lane holds column c; register r holds row 8*(r/4) + 4*(lane/32) + r%4
     float* out = partial + (int64_t)blockIdx.x * K * N;
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+    for (int kt = 0; kt < kKt; ++kt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            const int n = n0 + 64 * wave + 32 * nt + c;
+            const int n = n0 + 64 * cw + 32 * nt + c;
             if (n >= N) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int kf = kf0 + 32 * kt + 8 * (r / 4) + 4 * gq + (r % 4);
+                const int kf = kf0 + 32 * (kt * kKg + kg) + 8 * (r / 4) + 4 * gq + (r % 4);
                 if (kf < K) out[(int64_t)kf * N + n] = acc[kt][nt][r];
             }
         }
@@ -1089,13 +1185,15 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const float* __restrict__ par
 
 constexpr int kMaxSlabs = 512;
 
+// How many slabs of rows dW is split into: as many as fill the chip (1024 workgroups), each of at
+// least 128 rows.  Where the partial tiles written and read again stay below the operands' own
+// bytes, down to 32 rows: a step of few nodes would otherwise wait for a handful of workgroups.
 int slabs_for(int64_t n, int K, int F)
 {
     const int64_t tiles = (int64_t)((K + BM - 1) / BM) * ((F + BN - 1) / BN);
-    int64_t want = std::max<int64_t>(1, (1024 + tiles - 1) / tiles);
-    want = std::min<int64_t>(want, kMaxSlabs);
-    const int64_t by_rows = std::max<int64_t>(1, n / (4 * BK));
-    return (int)std::min(want, by_rows);
+    const int64_t want = std::min<int64_t>(kMaxSlabs, std::max<int64_t>(1, (1024 + tiles - 1) / tiles));
+    const int64_t cheap = std::min(n / 32, n * (K + F) / (2 * (int64_t)K * F));
+    return (int)std::max<int64_t>(1, std::min(want, std::max(n / (4 * BK), cheap)));
 }
 
 // groups of 4 consecutive elements can be moved with one access: rows start aligned
@@ -1137,24 +1235,25 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     g.lda = K;
     g.ldb = F;
     g.ldc = F;
-    g.k_slab = K;
-    g.c_split = 0;
     g.vec_a = vec_ok(X, K, dtype == SAR_F32 ? 4 : 2);
     g.vec_b = vec_ok(W, F, 4);
     SkinnyPlan plan;
     const bool want_scores = a_score || a_score2;
+    // fp32 rows that are no whole number of pieces stay with the tiled kernel: the two take the
+    // contraction in different orders, and the scores' signs decide slopes
+    const bool rows_whole = dtype == SAR_BF16 || K % 4 == 0;
     // With fp32 rows the scores are two more columns of the product (z_h . a_h = x . (W_h a_h)),
     // equal to the scores of the stored rows up to fp32 rounding.  With bf16 rows they are taken
     // from the STORED (rounded) rows in one pass afterwards: every later step reads those rows,
     // and a score of the unrounded sums differs from theirs by up to the storage rounding, which
     // is enough to move LeakyReLU's kink for about one edge in a thousand.
-    if (want_scores && dtype == SAR_F32 && 2 * H <= 32 && plan_skinny(X, K, Z, F, K, F, dtype, 1, &plan)) {
+    if (want_scores && dtype == SAR_F32 && 2 * H <= 32 && rows_whole && plan_skinny(K, F, dtype, 1, &plan)) {
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, a_score, a_score2, score, score2, H, D,
                       plan.stage_off};
         SAR_TRY((launch_skinny<float, float, true>(sk, plan, st)));
         return SAR_OK;
     }
-    if (plan_skinny(X, K, Z, F, K, F, dtype, 0, &plan)) {
+    if (rows_whole && plan_skinny(K, F, dtype, 0, &plan)) {
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                       plan.stage_off};
         if (dtype == SAR_F32)
@@ -1164,9 +1263,9 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     } else {
         dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((F + BN - 1) / BN), 1);
         if (dtype == SAR_F32)
-            k_gemm<float, float, float, true, false><<<grid, kGemmThreads, 0, st>>>(g);
+            k_gemm<float, float, float, false><<<grid, kGemmThreads, 0, st>>>(g);
         else
-            k_gemm_bf16<bf16_t, float, bf16_t, true, false, true><<<grid, kGemmThreads, 0, st>>>(g);
+            k_gemm_bf16<bf16_t, float, bf16_t, false><<<grid, kGemmThreads, 0, st>>>(g);
         SAR_LAUNCH_CHECK();
     }
     // (one pass over the stored rows; with one vector the same vector rides along twice)
@@ -1192,7 +1291,7 @@ bool rows_op_fusable(const void* X, const void* dZ, const RowsOp& op, void* dX, 
     if (reinterpret_cast<uintptr_t>(X) % 16 != 0 || reinterpret_cast<uintptr_t>(dZ) % 16 != 0) return false;
     if (op.ds && reinterpret_cast<uintptr_t>(op.a_r) % 16 != 0) return false;
     SkinnyPlan plan;
-    if (dX && !(plan_skinny(dZ, F, dX, K, F, K, dtype, 0, &plan) && plan_takes_rows_op(plan, F, op.H, dtype)))
+    if (dX && !(plan_skinny(F, K, dtype, 0, &plan) && plan_takes_rows_op(plan, F, op.H, dtype)))
         return false;
     return true;
 }
@@ -1234,54 +1333,40 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
 {
     if (dW) {
         const int slabs = slabs_for(n, K, F);
-        const size_t need = (size_t)slabs * K * F * sizeof(float);
+        const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
         SAR_CHECK_ARG(work != nullptr && work_bytes >= need, "work_bytes=%zu is below the %zu bytes required",
                       work_bytes, need);
         // dW[K,F] = X^T dZ, contraction over the n rows, split into slabs
-        const int elem = dtype == SAR_F32 ? 4 : 2, vec = 16 / elem;
-        if (K % vec == 0 && F % vec == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
-            reinterpret_cast<uintptr_t>(dZ) % 16 == 0) {
-            const int chunk = dtype == SAR_F32 ? DwShape<float>::kRows : DwShape<bf16_t>::kRows;
-            const int64_t rows_per_slab = ((n + slabs - 1) / slabs + chunk - 1) / chunk * chunk;
-            dim3 grid((unsigned)slabs, (unsigned)((F + kDwN - 1) / kDwN), (unsigned)((K + kDwKf - 1) / kDwKf));
-            if (op && dtype == SAR_F32)
-                k_dw<float, true><<<grid, 256, 0, st>>>(static_cast<const float*>(X), static_cast<const float*>(dZ),
-                                                        *op, static_cast<float*>(work), n, K, F, rows_per_slab);
-            else if (op)
-                k_dw<bf16_t, true><<<grid, 256, 0, st>>>(static_cast<const bf16_t*>(X),
-                                                         static_cast<const bf16_t*>(dZ), *op,
-                                                         static_cast<float*>(work), n, K, F, rows_per_slab);
-            else if (dtype == SAR_F32)
-                k_dw<float, false><<<grid, 256, 0, st>>>(static_cast<const float*>(X), static_cast<const float*>(dZ),
-                                                         RowsOp{}, static_cast<float*>(work), n, K, F, rows_per_slab);
+        const int chunk = dtype == SAR_F32 ? DwShape<float>::kRows : DwShape<bf16_t>::kRows;
+        const int64_t rows_per_slab = ((n + slabs - 1) / slabs + chunk - 1) / chunk * chunk;
+        auto launch = [&](auto kernel, int nw, const auto* x, const auto* dz) {
+            const dim3 grid((unsigned)slabs, (unsigned)((F + nw - 1) / nw), (unsigned)((K + kDwKf - 1) / kDwKf));
+            kernel<<<grid, 256, 0, st>>>(x, dz, op ? *op : RowsOp{}, static_cast<float*>(work), n, K, F,
+                                         rows_per_slab);
+        };
+        auto with = [&](auto fuse, auto ragged, const auto* x, const auto* dz) {
+            using T = std::remove_cv_t<std::remove_reference_t<decltype(*x)>>;
+            constexpr bool FUSE = decltype(fuse)::value, RAG = decltype(ragged)::value;
+            if (F <= 64)
+                launch(k_dw<T, FUSE, 64, RAG>, 64, x, dz);
+            else if (F <= 128)
+                launch(k_dw<T, FUSE, 128, RAG>, 128, x, dz);
             else
-                k_dw<bf16_t, false><<<grid, 256, 0, st>>>(static_cast<const bf16_t*>(X),
-                                                          static_cast<const bf16_t*>(dZ), RowsOp{},
-                                                          static_cast<float*>(work), n, K, F, rows_per_slab);
-            SAR_LAUNCH_CHECK();
-        } else {
-            if (op) return sar::fail(SAR_ERR_STATE, "rows formed on the fly need the aligned dW kernel");
-            GemmArgs g{};
-            g.A = X;
-            g.B = dZ;
-            g.C = work;
-            g.M = K;
-            g.N = F;
-            g.Kd = n;
-            g.lda = K;
-            g.ldb = F;
-            g.ldc = F;
-            g.k_slab = ((n + slabs - 1) / slabs + BK - 1) / BK * BK;
-            g.c_split = (int64_t)K * F;
-            g.vec_a = vec_ok(X, K, elem);
-            g.vec_b = vec_ok(dZ, F, elem);
-            dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)((F + BN - 1) / BN), (unsigned)slabs);
-            if (dtype == SAR_F32)
-                k_gemm<float, float, float, false, false><<<grid, kGemmThreads, 0, st>>>(g);
+                launch(k_dw<T, FUSE, 256, RAG>, 256, x, dz);
+        };
+        auto typed = [&](const auto* x, const auto* dz, int vec) {
+            if (op)   // (rows_op_fusable: whole units)
+                with(std::true_type{}, std::false_type{}, x, dz);
+            else if (K % vec == 0 && F % vec == 0)
+                with(std::false_type{}, std::false_type{}, x, dz);
             else
-                k_gemm_bf16<bf16_t, bf16_t, float, false, false, false><<<grid, kGemmThreads, 0, st>>>(g);
-            SAR_LAUNCH_CHECK();
-        }
+                with(std::false_type{}, std::true_type{}, x, dz);
+        };
+        if (dtype == SAR_F32)
+            typed(static_cast<const float*>(X), static_cast<const float*>(dZ), 4);
+        else
+            typed(static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(dZ), 8);
+        SAR_LAUNCH_CHECK();
         const int64_t count = (int64_t)K * F;
         k_sum_slabs<<<(unsigned)std::min<int64_t>((count + 31) / 32, 8192), 256, 0, st>>>(
             static_cast<const float*>(work), slabs, count, dW);
@@ -1299,12 +1384,10 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
         g.lda = F;
         g.ldb = F;
         g.ldc = K;
-        g.k_slab = F;
-        g.c_split = 0;
         g.vec_a = vec_ok(dZ, F, dtype == SAR_F32 ? 4 : 2);
         g.vec_b = vec_ok(W, F, 4);
         SkinnyPlan plan;
-        if (plan_skinny(dZ, F, dX, K, F, K, dtype, 0, &plan)) {
+        if (plan_skinny(F, K, dtype, 0, &plan)) {
             // B(k = f, n = kcol) = W[kcol * F + f]
             SkinnyArgs sk{dZ, F, n, W, 1, F, dX, K, F, K, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                           plan.stage_off};
@@ -1323,9 +1406,9 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
             if (op) return sar::fail(SAR_ERR_STATE, "rows formed on the fly need the skinny dX kernel");
             dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((K + BN - 1) / BN), 1);
             if (dtype == SAR_F32)
-                k_gemm<float, float, float, true, true><<<grid, kGemmThreads, 0, st>>>(g);
+                k_gemm<float, float, float, true><<<grid, kGemmThreads, 0, st>>>(g);
             else
-                k_gemm_bf16<bf16_t, float, bf16_t, true, true, true><<<grid, kGemmThreads, 0, st>>>(g);
+                k_gemm_bf16<bf16_t, float, bf16_t, true><<<grid, kGemmThreads, 0, st>>>(g);
             SAR_LAUNCH_CHECK();
         }
     }
