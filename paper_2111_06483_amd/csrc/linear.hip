@@ -445,10 +445,12 @@ __device__ inline uint4 front_of_piece<bf16_t>(const uint4& v, int rest)
 // tile ahead (the map two), like the first pieces of its rows.
 constexpr int kDsRegs = 8;   // 32 rows x H <= 16 heads of ds, 64 lanes
 
-template <typename TA, typename TC, int NT, bool SC, bool FUSE = false>
+// RAG: K is no whole number of pieces.
+template <typename TA, typename TC, int NT, bool SC, bool FUSE, bool RAG>
 __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
 {
     static_assert(!(SC && FUSE), "the fused operand is that of dX = E W^T, which has no score columns");
+    static_assert(!(RAG && (FUSE || SC)), "");
     constexpr int NA = NT + (SC ? 1 : 0);   // accumulator tiles: NT of the product, one of scores
     extern __shared__ __attribute__((aligned(16))) unsigned char skinny_lds[];
     constexpr bool BF = sizeof(TA) == 2;
@@ -459,96 +461,14 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
     const int64_t n0 = (int64_t)blockIdx.y * (NT * 32);
     uint4* frag = reinterpret_cast<uint4*>(skinny_lds);
 
-    const int units = g.chunks * NA * kFragsPerTile * 64;
-    auto make_frag = [&](int u) -> uint4 {
-        const int l = u & 63;
-        int f = u >> 6, half = 0;
-        if (BF) {
-            half = f & 1;
-            f >>= 1;
-        }
-        const int nt = f % NA, t = f / NA;
-        // the score tile starts as zeros; its entries are written below
-        const int64_t n = (SC && nt == NT) ? g.N : n0 + nt * 32 + (l & 31);
-        const int kb = t * kChunk + (l >> 5) * (kChunk / 2);
-        uint32_t w[4];
-        if (!BF) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                w[j] = (kb + j < g.K && n < g.N) ? __float_as_uint(g.B[(int64_t)(kb + j) * g.sbk + n * g.sbn]) : 0u;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t part[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int k = kb + 2 * j + e;
-                    const float v = (k < g.K && n < g.N) ? g.B[(int64_t)k * g.sbk + n * g.sbn] : 0.f;
-                    const uint32_t hi = f32_to_bf16_rne(v);
-                    part[e] = half ? f32_to_bf16_rne(v - __uint_as_float(hi << 16)) : hi;
-                }
-                w[j] = part[0] | (part[1] << 16);
-            }
-        }
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    };
-    // four fragments per thread and round, so that their 16 loads travel together
-    for (int u0 = tid; u0 < units; u0 += 4 * kSkinnyThreads) {
-        uint4 val[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) val[x] = make_frag(min(u0 + x * kSkinnyThreads, units - 1));
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-            if (u0 + x * kSkinnyThreads < units) frag[u0 + x * kSkinnyThreads] = val[x];
-    }
-    if (SC) {
-        // (W a)[k][h] = sum_d W[k][h*D + d] a[h][d]: z_h . a_h = x . (W_h a_h), so the scores
-        // are 2H more output columns of the same product, taken from the unrounded sums
-        __syncthreads();
-        // a head's two score columns belong to the column slab that holds the head's first
-        // column; the other slabs leave them at zero and do not store them
-        const int cols = 2 * g.H;
-        for (int p = tid; p < g.K * cols; p += kSkinnyThreads) {
-            const int k = p / cols, col = p % cols;
-            const int h = col < g.H ? col : col - g.H;
-            const float* av = col < g.H ? g.a1 : g.a2;
-            const int t = k / kChunk, gk = (k / (kChunk / 2)) & 1, e = k % (kChunk / 2);
-            float v = 0.f;
-            if (av && (h * g.D) / (NT * 32) == (int)blockIdx.y) {
-                if (!BF && (int64_t)(h + 1) * g.D <= n0 + NT * 32) {
-                    // this head's part of row k of W is in LDS already (exact fp32 values, fragment
-                    // order): D strided reads of global memory per product would cost more than
-                    // the whole staging
-                    const float* wk = reinterpret_cast<const float*>(frag) + ((size_t)t * NA * 64 + gk * 32) * 4 + e;
-                    for (int d = 0; d < g.D; ++d) {
-                        const int n = h * g.D + d - (int)n0;
-                        v = fmaf(wk[((n >> 5) * 64 + (n & 31)) * 4], av[h * g.D + d], v);
-                    }
-                } else {
-                    const float* wrow = g.B + (int64_t)k * g.sbk + (int64_t)h * g.D * g.sbn;
-                    for (int d = 0; d < g.D; ++d) v = fmaf(wrow[d * g.sbn], av[h * g.D + d], v);
-                }
-            }
-            if (!BF) {
-                reinterpret_cast<float*>(frag)[(((size_t)t * NA + NT) * 64 + gk * 32 + col) * 4 + e] = v;
-            } else {
-                uint16_t* fh = reinterpret_cast<uint16_t*>(frag);
-                const uint32_t hi = f32_to_bf16_rne(v);
-                const size_t at = ((size_t)t * NA + NT) * 2 * 64 + gk * 32 + col;
-                fh[at * 8 + e] = (uint16_t)hi;
-                fh[(at + 64) * 8 + e] = (uint16_t)f32_to_bf16_rne(v - __uint_as_float(hi << 16));
-            }
-        }
-    }
-    __syncthreads();
-
     const TA* A = static_cast<const TA*>(g.A);
     const int64_t n_tiles = (g.M + 31) / 32;
     // a few tiles spread over the workgroups before they fill one
     const int64_t stride = (int64_t)gridDim.x * kSkinnyWaves;
     int64_t tile = (int64_t)blockIdx.x + (int64_t)gridDim.x * wave;
-    if (tile >= n_tiles) return;
 
+    // The first pieces of the first tile travel while the small operand is staged.
+    //
     // Loads are unconditional (a piece that would end beyond the row is read from the row's last 16
     // bytes; what of it is beyond, or the piece before it carries as well, is zeroed where it is used)
     // and the main loop below is straight-line code, so that the compiler can count the
@@ -601,8 +521,6 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
     if constexpr (FUSE) {
         dsl = reinterpret_cast<float*>(skinny_lds + g.stage_off + wave * (32 * 32 * (int)sizeof(TC)));
         arl = dsl + 32 * g.op.H;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) arreg[x] = (g.op.ds && lane * 4 + x < g.K) ? g.op.a_r[lane * 4 + x] : 0.f;
     }
 
     // Two sets of pieces: while the chunks of one set are multiplied, the other set travels.
@@ -616,14 +534,127 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
     if constexpr (FUSE) {
         rank_of(tile, nrk0, nrk1);
         rowp = row_ptr_fused(tile, nrk0, nrk1, has);
-        load_ds(tile);
+        if (tile < n_tiles) load_ds(tile);
         rank_of(tile + stride, nrk0, nrk1);
     } else {
         rowp = row_ptr(tile);
     }
 #pragma unroll
     for (int u = 0; u < PS; ++u) a[u] = load_piece(rowp, u);
-    const int full = g.chunks / (2 * PS) * (2 * PS);
+    // Staging is one long wait of a step of few nodes, so its loads travel together, eight units'
+    // worth per thread and round: unconditional (values beyond K or N are read from the last row or
+    // column and dropped), and along the contraction by 16 bytes where that is the contiguous direction.
+    // bf16: a thread makes the hi and the lo unit of the same eight values.  (bf16, whole kernel, before:
+    // loads behind a branch each, and every value twice: 254 x 200 over 30000 rows 46 -> 19..25 us, 219 x 36
+    // over 14000 rows 32 -> 13 us.)
+    const int units = g.chunks * NA * 64;
+    constexpr int kVals = kChunk / 2, kRound = 32 / kVals;
+    for (int u0 = tid; u0 < units; u0 += kRound * kSkinnyThreads) {
+        float val[kRound][kVals];
+        auto where = [&](int u, int& kb, int64_t& n) {
+            const int f = u >> 6, nt = f % NA, t = f / NA;
+            // the score tile starts as zeros; its entries are written below
+            n = (SC && nt == NT) ? g.N : n0 + nt * 32 + (u & 31);
+            kb = t * kChunk + ((u & 63) >> 5) * kVals;
+        };
+#pragma unroll
+        for (int x = 0; x < kRound; ++x) {
+            int kb;
+            int64_t n;
+            where(min(u0 + x * kSkinnyThreads, units - 1), kb, n);
+            const float* from = g.B + std::min<int64_t>(n, g.N - 1) * g.sbn;
+            if (!RAG && g.sbk == 1) {
+                // (K is a whole number of pieces, so a piece lies inside the row or beyond it)
+#pragma unroll
+                for (int j = 0; j < kVals; j += 4) {
+                    const uint4 v = load16(from + min(kb, g.K - kVals) + j);
+                    val[x][j] = __uint_as_float(v.x);
+                    val[x][j + 1] = __uint_as_float(v.y);
+                    val[x][j + 2] = __uint_as_float(v.z);
+                    val[x][j + 3] = __uint_as_float(v.w);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < kVals; ++j) val[x][j] = from[(int64_t)min(kb + j, g.K - 1) * g.sbk];
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < kRound; ++x) {
+            const int u = u0 + x * kSkinnyThreads;
+            if (u >= units) break;
+            int kb;
+            int64_t n;
+            where(u, kb, n);
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < kVals; ++j) {
+                const float v = (kb + j < g.K && n < g.N) ? val[x][j] : 0.f;
+                if (!BF) {
+                    hi[j % 4] = __float_as_uint(v);
+                } else {
+                    const uint32_t h = f32_to_bf16_rne(v), l = f32_to_bf16_rne(v - __uint_as_float(h << 16));
+                    hi[j / 2] = (j & 1) ? hi[j / 2] | (h << 16) : h;
+                    lo[j / 2] = (j & 1) ? lo[j / 2] | (l << 16) : l;
+                }
+            }
+            if (!BF) {
+                frag[u] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            } else {
+                uint4* at = frag + (u >> 6) * 128 + (u & 63);
+                at[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+                at[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            }
+        }
+    }
+    if (SC) {
+        // (W a)[k][h] = sum_d W[k][h*D + d] a[h][d]: z_h . a_h = x . (W_h a_h), so the scores
+        // are 2H more output columns of the same product, taken from the unrounded sums
+        __syncthreads();
+        // a head's two score columns belong to the column slab that holds the head's first
+        // column; the other slabs leave them at zero and do not store them
+        const int cols = 2 * g.H;
+        for (int p = tid; p < g.K * cols; p += kSkinnyThreads) {
+            const int k = p / cols, col = p % cols;
+            const int h = col < g.H ? col : col - g.H;
+            const float* av = col < g.H ? g.a1 : g.a2;
+            const int t = k / kChunk, gk = (k / (kChunk / 2)) & 1, e = k % (kChunk / 2);
+            float v = 0.f;
+            if (av && (h * g.D) / (NT * 32) == (int)blockIdx.y) {
+                if (!BF && (int64_t)(h + 1) * g.D <= n0 + NT * 32) {
+                    // this head's part of row k of W is in LDS already (exact fp32 values, fragment
+                    // order): D strided reads of global memory per product would cost more than
+                    // the whole staging
+                    const float* wk = reinterpret_cast<const float*>(frag) + ((size_t)t * NA * 64 + gk * 32) * 4 + e;
+#pragma unroll 8
+                    for (int d = 0; d < g.D; ++d) {
+                        const int n = h * g.D + d - (int)n0;
+                        v = fmaf(wk[((n >> 5) * 64 + (n & 31)) * 4], av[h * g.D + d], v);
+                    }
+                } else {
+                    const float* wrow = g.B + (int64_t)k * g.sbk + (int64_t)h * g.D * g.sbn;
+                    for (int d = 0; d < g.D; ++d) v = fmaf(wrow[d * g.sbn], av[h * g.D + d], v);
+                }
+            }
+            if (!BF) {
+                reinterpret_cast<float*>(frag)[(((size_t)t * NA + NT) * 64 + gk * 32 + col) * 4 + e] = v;
+            } else {
+                uint16_t* fh = reinterpret_cast<uint16_t*>(frag);
+                const uint32_t hi = f32_to_bf16_rne(v);
+                const size_t at = ((size_t)t * NA + NT) * 2 * 64 + gk * 32 + col;
+                fh[at * 8 + e] = (uint16_t)hi;
+                fh[(at + 64) * 8 + e] = (uint16_t)f32_to_bf16_rne(v - __uint_as_float(hi << 16));
+            }
+        }
+    }
+    __syncthreads();
+
+    if (tile >= n_tiles) return;
+    if constexpr (FUSE) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) arreg[x] = (g.op.ds && lane * 4 + x < g.K) ? g.op.a_r[lane * 4 + x] : 0.f;
+    }
+    // the last chunk, where K may end, is always one of the last chunks below
+    const int full = (g.chunks - 1) / (2 * PS) * (2 * PS);
 
     for (; tile < n_tiles; tile += stride) {
         float16_t acc[NA];
@@ -643,12 +674,15 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
             __builtin_amdgcn_wave_barrier();
         }
 
-        auto multiply = [&](const uint4& piece, int t) {
+        auto multiply = [&](const uint4& piece, int t, auto last) {
             const int k_first = t * kChunk + gq * (kChunk / 2);
-            const bool beyond = k_first >= g.K;
-            uint4 av = make_uint4(beyond ? 0u : piece.x, beyond ? 0u : piece.y, beyond ? 0u : piece.z,
-                                  beyond ? 0u : piece.w);
-            if (rest != 0 && k_first <= g.K && k_first > k_last) av = front_of_piece<TA>(av, rest);
+            uint4 av = piece;
+            if constexpr (decltype(last)::value) {
+                const bool beyond = k_first >= g.K;
+                if constexpr (RAG)
+                    if (k_first > k_last) av = front_of_piece<TA>(av, rest);
+                av = make_uint4(beyond ? 0u : av.x, beyond ? 0u : av.y, beyond ? 0u : av.z, beyond ? 0u : av.w);
+            }
             if constexpr (FUSE) {
                 if (!has) av = make_uint4(0u, 0u, 0u, 0u);
                 // a_r is zero beyond K, so a piece beyond the row stays zero
@@ -703,13 +737,13 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
             for (int u = 0; u < PS; ++u) b[u] = load_piece(rowp, t0 + PS + u);
             __builtin_amdgcn_sched_barrier(0);     // the loads stay ahead of the MFMAs
 #pragma unroll
-            for (int u = 0; u < PS; ++u) multiply(a[u], t0 + u);
+            for (int u = 0; u < PS; ++u) multiply(a[u], t0 + u, std::false_type{});
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < PS; ++u) a[u] = load_piece(rowp, t0 + 2 * PS + u);   // beyond the end: nobody reads it
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < PS; ++u) multiply(b[u], t0 + PS + u);
+            for (int u = 0; u < PS; ++u) multiply(b[u], t0 + PS + u, std::false_type{});
             __builtin_amdgcn_sched_barrier(0);
         }
         // the last chunks, fewer than two sets: the first set is loaded already
@@ -719,10 +753,10 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
         }
 #pragma unroll
         for (int u = 0; u < PS; ++u)
-            if (full + u < g.chunks) multiply(a[u], full + u);
+            if (full + u < g.chunks) multiply(a[u], full + u, std::true_type{});
 #pragma unroll
         for (int u = 0; u < PS; ++u)
-            if (full + PS + u < g.chunks) multiply(b[u], full + PS + u);
+            if (full + PS + u < g.chunks) multiply(b[u], full + PS + u, std::true_type{});
 
         // the next tile's first pieces travel while this one is stored
         const int64_t row0 = tile * 32;
@@ -841,21 +875,21 @@ bool plan_skinny(int K, int N, int dtype, int extra_tiles, SkinnyPlan* p)
     return p->slabs <= 4;
 }
 
-template <typename TA, typename TC, int NT, bool SC, bool FUSE = false>
+template <typename TA, typename TC, int NT, bool SC, bool FUSE, bool RAG>
 int launch_skinny_nt(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
 {
     int dev = 0;
     SAR_HIP(hipGetDevice(&dev));
     int n_cu = 0;
     SAR_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    SAR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_skinny<TA, TC, NT, SC, FUSE>),
+    SAR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_skinny<TA, TC, NT, SC, FUSE, RAG>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds));
     const int64_t tiles = (g.M + 31) / 32;
     // one workgroup per CU; two where registers (NT <= 4) and LDS leave room
     const int per_cu = (NT <= 4 && 2 * p.lds <= 150 * 1024) ? 2 : 1;
     const int64_t resident = std::max<int64_t>(1, (int64_t)n_cu * per_cu / p.slabs);
     dim3 grid((unsigned)std::max<int64_t>(1, std::min(tiles, resident)), p.slabs, 1);
-    k_gemm_skinny<TA, TC, NT, SC, FUSE><<<grid, kSkinnyThreads, p.lds, st>>>(g);
+    k_gemm_skinny<TA, TC, NT, SC, FUSE, RAG><<<grid, kSkinnyThreads, p.lds, st>>>(g);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
@@ -863,12 +897,20 @@ int launch_skinny_nt(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
 template <typename TA, typename TC, bool SC, bool FUSE = false>
 int launch_skinny(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
 {
-    switch (p.nt) {
-        case 1: return launch_skinny_nt<TA, TC, 1, SC, FUSE>(g, p, st);
-        case 2: return launch_skinny_nt<TA, TC, 2, SC, FUSE>(g, p, st);
-        case 4: return launch_skinny_nt<TA, TC, 4, SC, FUSE>(g, p, st);
-        default: return launch_skinny_nt<TA, TC, 8, SC, FUSE>(g, p, st);
-    }
+    auto with = [&](auto ragged) {
+        constexpr bool RAG = decltype(ragged)::value;
+        switch (p.nt) {
+            case 1: return launch_skinny_nt<TA, TC, 1, SC, FUSE, RAG>(g, p, st);
+            case 2: return launch_skinny_nt<TA, TC, 2, SC, FUSE, RAG>(g, p, st);
+            case 4: return launch_skinny_nt<TA, TC, 4, SC, FUSE, RAG>(g, p, st);
+        }
+        // (FUSE: not with eight accumulator tiles, see plan_takes_rows_op)
+        if constexpr (!FUSE) return launch_skinny_nt<TA, TC, 8, SC, FUSE, RAG>(g, p, st);
+        return sar::fail(SAR_ERR_STATE, "rows formed on the fly take at most four accumulator tiles");
+    };
+    if constexpr (!SC && !FUSE)
+        if (g.K % (16 / (int)sizeof(TA)) != 0) return with(std::true_type{});
+    return with(std::false_type{});
 }
 
 // Whether a plan can also form the rows of A on the fly (k_gemm_skinny's FUSE): the outputs must
@@ -1161,6 +1203,9 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
 // dW[k] += sum over slabs of partial[slab][k].  32 consecutive elements per
 // workgroup, eight threads per element taking every eighth slab; the eight
 // partial sums are added in a fixed order, so the result is reproducible.
+// Eight slabs are read at a time: a small dW has few workgroups, and with one
+// load in flight per thread they waited 64 times in a row (100 x 36 from 512
+// slabs: 18 us).
 __global__ __launch_bounds__(256) void k_sum_slabs(const float* __restrict__ partial, int n_slabs, int64_t count,
                                                    float* __restrict__ dW)
 {
@@ -1170,7 +1215,13 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const float* __restrict__ par
         const int64_t k = k0 + e;
         float s = 0.f;
         if (k < count)
-            for (int z = zl; z < n_slabs; z += 8) s += partial[(int64_t)z * count + k];
+            for (int z0 = zl; z0 < n_slabs; z0 += 64) {
+                float v[8];
+#pragma unroll
+                for (int x = 0; x < 8; ++x) v[x] = partial[(int64_t)std::min(z0 + 8 * x, n_slabs - 1) * count + k];
+#pragma unroll
+                for (int x = 0; x < 8; ++x) s = z0 + 8 * x < n_slabs ? s + v[x] : s;
+            }
         part[zl][e] = s;
         __syncthreads();
         if (zl == 0 && k < count) {
