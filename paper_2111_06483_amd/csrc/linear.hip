@@ -2,17 +2,15 @@
 // backward (what Z.backward(E) does in Alg. 2: dW = X^T dZ, dX = dZ W^T) on the
 // gfx950 matrix cores.  This is the one real contraction on the path.
 //
-// One tiled GEMM kernel C = A B serves the three products through strides.
-// Operands are widened to fp32 while being staged in LDS and multiplied with
-// V_MFMA_F32_32X32X2_F32 (fp32 in, fp32 accumulate), so fp32 configurations
-// keep fp32 accuracy; bf16-stored operands go through V_MFMA_F32_32X32X16_BF16
-// (see below).  Z = X W and dX = dZ W^T normally take the skinny kernel further
-// down (small operand resident in LDS, big operand straight into registers);
-// the tiled kernel remains for dW and for shapes the skinny one does not cover.
-// Workgroup tile 128 x 128 x 32, four wavefronts in a 2 x 2 grid,
-// each owning a 64 x 64 patch as 2 x 2 MFMA tiles (64 accumulator registers per
-// lane); the next tile is fetched into registers while the current one is
-// multiplied.
+// fp32 rows are multiplied with V_MFMA_F32_32X32X2_F32 (fp32 in, fp32 accumulate), so fp32
+// configurations keep fp32 accuracy; bf16-stored rows go through V_MFMA_F32_32X32X16_BF16:
+// the products are exact there, and the fp32 weight matrix is split into two bf16 terms,
+// W = hi + lo (+ an error below 2^-17 |W|), multiplied in two instructions, which is far
+// below the bf16 rounding of the stored result.
+//
+// Z = X W and dX = dZ W^T read their rows straight into registers.  Where the small operand
+// fits in LDS it stays there (k_gemm_skinny); where it does not it passes through LDS in
+// steps of the contraction (k_gemm_steps).  dW has a kernel of its own (k_dw).
 #include <algorithm>
 
 #include "gather_common.h"
@@ -21,11 +19,6 @@
 namespace {
 
 using namespace sar;
-
-constexpr int BM = 128, BN = 128, BK = 32;
-constexpr int kPad = 4;
-constexpr int kGemmThreads = 256;
-constexpr int kPerThread = BM * BK / kGemmThreads / 4;   // 4-element groups each thread stages per operand
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
@@ -38,281 +31,7 @@ __device__ inline float from_f32<float>(float v) { return v; }
 template <>
 __device__ inline bf16_t from_f32<bf16_t>(float v) { return bf16_t{(uint16_t)f32_to_bf16_rne(v)}; }
 
-// four consecutive elements, widened to fp32 (vector access when `vec`)
-template <typename T>
-__device__ inline void load4(const T* p, bool vec, int n_valid, float (&v)[4]);
-template <>
-__device__ inline void load4<float>(const float* p, bool vec, int n_valid, float (&v)[4])
-{
-    if (vec && n_valid == 4) {
-        const float4 x = *reinterpret_cast<const float4*>(p);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = k < n_valid ? p[k] : 0.f;
-    }
-}
-template <>
-__device__ inline void load4<bf16_t>(const bf16_t* p, bool vec, int n_valid, float (&v)[4])
-{
-    if (vec && n_valid == 4) {
-        const uint2 x = *reinterpret_cast<const uint2*>(p);
-        v[0] = __uint_as_float(x.x << 16);
-        v[1] = __uint_as_float(x.x & 0xffff0000u);
-        v[2] = __uint_as_float(x.y << 16);
-        v[3] = __uint_as_float(x.y & 0xffff0000u);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = k < n_valid ? bf16_to_f32(p[k]) : 0.f;
-    }
-}
-
-struct GemmArgs {
-    const void* A;
-    const void* B;
-    void* C;
-    int64_t M;        // rows of C
-    int N;            // cols of C
-    int64_t Kd;       // contraction length
-    int64_t lda;      // A(i,k) = A[i*lda + k]
-    int64_t ldb;      // B_K_FAST: B(k,j) = B[j*ldb + k]   else B(k,j) = B[k*ldb + j]
-    int64_t ldc;
-    int vec_a, vec_b; // 4-element groups of A / B are aligned and in one row
-};
-
-// One operand tile of TILE x BK (TILE = BM or BN) staged through registers:
-// each thread owns kPerThread groups of 4 elements that are consecutive in the
-// operand's contiguous dimension (k when K_FAST, else the tile dimension).
-template <typename T, bool K_FAST>
-struct Stage {
-    float v[kPerThread][4];
-    __device__ inline void fetch(const T* base, int64_t ld, int64_t x0, int64_t x_end, int64_t k0, int64_t k_end,
-                                 bool vec, int tid)
-    {
-#pragma unroll
-        for (int g = 0; g < kPerThread; ++g) {
-            const int e = g * kGemmThreads + tid;
-            if (K_FAST) {
-                const int kk = (e % (BK / 4)) * 4, x = e / (BK / 4);
-                const int64_t nk = k_end - (k0 + kk);
-                const int nv = (x0 + x < x_end) ? (int)(nk >= 4 ? 4 : (nk > 0 ? nk : 0)) : 0;
-                if (nv > 0)
-                    load4<T>(base + (x0 + x) * ld + k0 + kk, vec, nv, v[g]);
-                else
-                    v[g][0] = v[g][1] = v[g][2] = v[g][3] = 0.f;
-            } else {
-                const int x = (e % (BM / 4)) * 4, kk = e / (BM / 4);
-                const int64_t nx = x_end - (x0 + x);
-                const int nv = (k0 + kk < k_end) ? (int)(nx >= 4 ? 4 : (nx > 0 ? nx : 0)) : 0;
-                if (nv > 0)
-                    load4<T>(base + (k0 + kk) * ld + x0 + x, vec, nv, v[g]);
-                else
-                    v[g][0] = v[g][1] = v[g][2] = v[g][3] = 0.f;
-            }
-        }
-    }
-    __device__ inline void commit(float (*tile)[BM + kPad], int tid) const
-    {
-#pragma unroll
-        for (int g = 0; g < kPerThread; ++g) {
-            const int e = g * kGemmThreads + tid;
-            if (K_FAST) {
-                const int kk = (e % (BK / 4)) * 4, x = e / (BK / 4);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) tile[kk + c][x] = v[g][c];
-            } else {
-                const int x = (e % (BM / 4)) * 4, kk = e / (BM / 4);
-                *reinterpret_cast<float4*>(&tile[kk][x]) = make_float4(v[g][0], v[g][1], v[g][2], v[g][3]);
-            }
-        }
-    }
-};
-
-static_assert(BM == BN, "operand staging assumes square workgroup tiles");
-
-// A is contiguous along the contraction; B_K_FAST: so is B.
-template <typename TA, typename TB, typename TC, bool B_K_FAST>
-__global__ __launch_bounds__(kGemmThreads) void k_gemm(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(16))) float As[BK][BM + kPad];
-    __shared__ __attribute__((aligned(16))) float Bs[BK][BN + kPad];
-    const TA* A = static_cast<const TA*>(g.A);
-    const TB* B = static_cast<const TB*>(g.B);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int64_t n0 = (int64_t)blockIdx.y * BN;
-    const int64_t k_beg = 0, k_end = g.Kd;
-
-    float16_t acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-    Stage<TA, true> sa;
-    Stage<TB, B_K_FAST> sb;
-    if (k_beg < k_end) {
-        sa.fetch(A, g.lda, m0, g.M, k_beg, k_end, g.vec_a, tid);
-        sb.fetch(B, g.ldb, n0, g.N, k_beg, k_end, g.vec_b, tid);
-    }
-    for (int64_t k0 = k_beg; k0 < k_end; k0 += BK) {
-        sa.commit(As, tid);
-        sb.commit(Bs, tid);
-        __syncthreads();
-        // the next tile travels from HBM while this one is multiplied
-        if (k0 + BK < k_end) {
-            sa.fetch(A, g.lda, m0, g.M, k0 + BK, k_end, g.vec_a, tid);
-            sb.fetch(B, g.ldb, n0, g.N, k0 + BK, k_end, g.vec_b, tid);
-        }
-#pragma unroll
-        for (int ks = 0; ks < BK; ks += 2) {
-            const int kk = ks + (lane >> 5);
-            float a[2], b[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                a[x] = As[kk][wm * 64 + x * 32 + (lane & 31)];
-                b[x] = Bs[kk][wn * 64 + x * 32 + (lane & 31)];
-            }
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // lane holds column (lane % 32); register r holds row 8*(r/4) + 4*(lane/32) + r%4
-    TC* C = static_cast<TC*>(g.C);
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int64_t j = n0 + wn * 64 + y * 32 + (lane & 31);
-            if (j >= g.N) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = m0 + wm * 64 + x * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                if (i < g.M) C[i * g.ldc + j] = from_f32<TC>(acc[x][y][r]);
-            }
-        }
-}
-
-// ---- bf16-stored operands: bf16 MFMA --------------------------------------
-//
-// With bf16 storage the products are exact in a bf16 MFMA with fp32
-// accumulation, at several times the fp32 MFMA rate.  The fp32 weight matrix is
-// split into two bf16 terms, W = hi + lo (+ an error below 2^-17 |W|), and
-// multiplied in two instructions, which is far below the bf16 rounding of the
-// stored result.  Tiles are staged in LDS as bf16 with the contraction index
-// contiguous, the layout V_MFMA_F32_32X32X16_BF16 wants: lane l supplies
-// A[l%32][8*(l/32) .. +7] and B[8*(l/32) .. +7][l%32].
-
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-constexpr int kPadH = 8;
-
-template <bool K_FAST>
-__device__ inline void commit_bf16(const float (&v)[kPerThread][4], uint16_t (*hi)[BK + kPadH],
-                                   uint16_t (*lo)[BK + kPadH], int tid)
-{
-#pragma unroll
-    for (int g = 0; g < kPerThread; ++g) {
-        const int e = g * kGemmThreads + tid;
-        uint32_t h[4], l[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            h[c] = f32_to_bf16_rne(v[g][c]);
-            l[c] = lo ? f32_to_bf16_rne(v[g][c] - __uint_as_float(h[c] << 16)) : 0u;
-        }
-        if (K_FAST) {
-            const int kk = (e % (BK / 4)) * 4, x = e / (BK / 4);
-            *reinterpret_cast<uint2*>(&hi[x][kk]) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-            if (lo) *reinterpret_cast<uint2*>(&lo[x][kk]) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-        } else {
-            const int x = (e % (BM / 4)) * 4, kk = e / (BM / 4);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                hi[x + c][kk] = (uint16_t)h[c];
-                if (lo) lo[x + c][kk] = (uint16_t)l[c];
-            }
-        }
-    }
-}
-
-template <typename TA, typename TB, typename TC, bool B_K_FAST>
-__global__ __launch_bounds__(kGemmThreads) void k_gemm_bf16(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t As[BM][BK + kPadH];
-    __shared__ __attribute__((aligned(16))) uint16_t Bh[BN][BK + kPadH];
-    __shared__ __attribute__((aligned(16))) uint16_t Bl[BN][BK + kPadH];
-    const TA* A = static_cast<const TA*>(g.A);
-    const TB* B = static_cast<const TB*>(g.B);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int64_t n0 = (int64_t)blockIdx.y * BN;
-    const int64_t k_beg = 0, k_end = g.Kd;
-
-    float16_t acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-    Stage<TA, true> sa;
-    Stage<TB, B_K_FAST> sb;
-    if (k_beg < k_end) {
-        sa.fetch(A, g.lda, m0, g.M, k_beg, k_end, g.vec_a, tid);
-        sb.fetch(B, g.ldb, n0, g.N, k_beg, k_end, g.vec_b, tid);
-    }
-    for (int64_t k0 = k_beg; k0 < k_end; k0 += BK) {
-        commit_bf16<true>(sa.v, As, nullptr, tid);
-        commit_bf16<B_K_FAST>(sb.v, Bh, Bl, tid);
-        __syncthreads();
-        if (k0 + BK < k_end) {
-            sa.fetch(A, g.lda, m0, g.M, k0 + BK, k_end, g.vec_a, tid);
-            sb.fetch(B, g.ldb, n0, g.N, k0 + BK, k_end, g.vec_b, tid);
-        }
-#pragma unroll
-        for (int ks = 0; ks < BK; ks += 16) {
-            const int kk = ks + 8 * (lane >> 5);
-            bf16x8_t a[2], bh[2], bl[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                a[x] = *reinterpret_cast<const bf16x8_t*>(&As[wm * 64 + x * 32 + (lane & 31)][kk]);
-                bh[x] = *reinterpret_cast<const bf16x8_t*>(&Bh[wn * 64 + x * 32 + (lane & 31)][kk]);
-                bl[x] = *reinterpret_cast<const bf16x8_t*>(&Bl[wn * 64 + x * 32 + (lane & 31)][kk]);
-            }
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bh[y], acc[x][y], 0, 0, 0);
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bl[y], acc[x][y], 0, 0, 0);
-                }
-        }
-        __syncthreads();
-    }
-
-    TC* C = static_cast<TC*>(g.C);
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int64_t j = n0 + wn * 64 + y * 32 + (lane & 31);
-            if (j >= g.N) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = m0 + wm * 64 + x * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                if (i < g.M) C[i * g.ldc + j] = from_f32<TC>(acc[x][y][r]);
-            }
-        }
-}
 
 // ---- error rows that are never stored ---------------------------------------
 //
@@ -374,7 +93,7 @@ __device__ inline uint4 fuse_piece<bf16_t>(const uint4& base, float d, const flo
 //       B operands both take "their k" from the lane group, so any pairing of
 //       k with (step, group) is valid as long as both operands use the same).
 // bf16: a chunk is 16 values, one V_MFMA_F32_32X32X16_BF16 per bf16 half of the
-//       fp32 small operand (hi and lo, as above).
+//       fp32 small operand (hi and lo).
 
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = 64 * kSkinnyWaves;
@@ -922,6 +641,301 @@ bool plan_takes_rows_op(const SkinnyPlan& p, int K, int H, int dtype)
     return p.nt <= 4 && p.stage_off != 0 && K <= 256 && H <= 2 * kDsRegs && (size_t)(32 * H + 256) * 4 <= tile;
 }
 
+// ---- products whose small operand does not fit in LDS -----------------------
+//
+// The same two products for the wider layers (400 x 400 fp32 is 640 KB).  A wavefront keeps 32 rows of the
+// result, NT tiles of 32 columns wide, in registers and reads its rows of A straight from memory, 16
+// bytes per lane, a step of 32 contraction values ahead.  The small operand passes through LDS in the
+// same steps, in the order the fragments are consumed (one conflict-free 16-byte read per lane and
+// fragment); the next step's values travel while this one is multiplied and are written to the other
+// buffer after it, so there is one barrier per step, 64 to 128 matrix instructions of a wavefront.
+// The column tiles are dealt evenly to the slabs (400 columns: 7 + 6 tiles), because a 128-wide tiling
+// multiplies a quarter for nothing there; the slabs of the same rows are neighbours on one XCD, whose
+// L2 serves the rows the second time.
+//
+// fp32: a lane group holds values 8t+4g .. 8t+4g+3 of a chunk t; swapping the halves of register pairs
+//       turns them into the pairs (0,1) (2,3) (4,5) (6,7), so that the contraction runs in its natural order.
+// bf16: a chunk is 16 values, hi and lo multiplied in turn (see above).
+//
+// Bound by the matrix cores in fp32.  Measured before (128 x 128 tiles of both operands staged in LDS,
+// widened to fp32 there) and now, forward / dX: 600000 x 400 x 400 fp32 2650 / 2600 -> 1950 / 2010 us (117
+// TFLOP/s counting the 14 tiles), bf16 2554 / 1820 -> 787 / 787 us; 5000 x 400 x 400 bf16 54 / 37 -> 17 us.
+struct StepArgs {
+    const void* A;     // [M, K], row stride lda, contraction index contiguous
+    int64_t lda, M;
+    const float* B;    // B(k, n) = B[k * sbk + n * sbn]
+    int64_t sbk, sbn;
+    void* C;           // [M, N], row stride ldc
+    int64_t ldc;
+    int K, N, slabs;
+};
+
+constexpr int kStepWaves = 4;
+constexpr int kStepThreads = 64 * kStepWaves;
+constexpr int kStepRows = 32 * kStepWaves;
+constexpr int kStep = 32;   // contraction values per step
+
+// BK_FAST: the small operand's contiguous direction is the contraction (sbk == 1), otherwise its columns (sbn == 1)
+template <typename T, int NT, bool BK_FAST>
+__global__ __launch_bounds__(kStepThreads, 2) void k_gemm_steps(StepArgs g)
+{
+    constexpr bool BF = sizeof(T) == 2;
+    constexpr int kChunk = BF ? 16 : 8, kChunks = kStep / kChunk, kVec = 16 / (int)sizeof(T);
+    constexpr int kFrags = BF ? 2 : 1;                           // fragments per chunk and tile
+    constexpr int kItems = kChunks * NT * (BF ? 64 : 32);        // of 8 values of one column
+    constexpr int kPer = (kItems + kStepThreads - 1) / kStepThreads;
+    constexpr int kLds = NT * kFrags * 64 + 2;                   // units of a chunk
+    __shared__ uint4 frag[2][kChunks * kLds];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 31, gq = lane >> 5;
+    // blocks 8 apart share an XCD: the slabs of one row block
+    const int64_t row_block = (int64_t)(blockIdx.x / (8 * g.slabs)) * 8 + blockIdx.x % 8;
+    const int n0 = (int)(blockIdx.x / 8 % g.slabs) * NT * 32;
+    const int64_t row0 = row_block * kStepRows + wave * 32;
+    if (row_block * kStepRows >= g.M) return;
+    const T* row = static_cast<const T*>(g.A) + std::min<int64_t>(row0 + c, g.M - 1) * g.lda;
+    const int steps = (g.K + kStep - 1) / kStep;
+
+    const int k_last = g.K - kVec, rest = g.K % kVec;
+    auto load_a = [&](int step, uint4 (&a)[kChunks]) {
+#pragma unroll
+        for (int t = 0; t < kChunks; ++t) {
+            const int k = step * kStep + t * kChunk + gq * kVec;
+            a[t] = load16(row + min(k, k_last));
+        }
+    };
+    // item -> place in LDS, first contraction value in the step, column.  Neighbouring lanes take
+    // neighbouring memory: columns, or the four items of a column (128 bytes) where the contraction is
+    // the contiguous direction (a line per lane and load there cost a third of the time, 2008 against
+    // 2690 us; the two units between chunks keep the four on different banks)
+    auto item = [&](int u, int& at, int& kb, int& n) {
+        int f, l;
+        if (BK_FAST) {
+            const int piece = u & 3, col = u >> 2;
+            const int t = BF ? piece >> 1 : piece;
+            f = t * NT + (col >> 5);
+            l = (col & 31) + (BF ? (piece & 1) * 32 : 0);
+        } else {
+            f = BF ? u >> 6 : u >> 5;
+            l = BF ? u & 63 : u & 31;
+        }
+        const int t = f / NT;
+        kb = t * kChunk + (BF ? (l >> 5) * 8 : 0);
+        n = n0 + (f % NT) * 32 + (l & 31);
+        at = t * kLds + (f % NT) * kFrags * 64 + l;
+    };
+    // an item's byte offset from the step's first value; the step and the value's place are in the scalar base
+    uint32_t from[kPer];
+#pragma unroll
+    for (int x = 0; x < kPer; ++x) {
+        int at, kb, n;
+        item(min(tid + x * kStepThreads, kItems - 1), at, kb, n);
+        from[x] = (uint32_t)(kb * g.sbk + std::min<int64_t>(n, g.N - 1) * g.sbn) * 4u;
+    }
+    float bv[kPer][8];
+    auto load_b = [&](int step, auto last) {
+#pragma unroll
+        for (int x = 0; x < kPer; ++x) {
+            if (decltype(last)::value) {
+                int at, kb, n;
+                item(min(tid + x * kStepThreads, kItems - 1), at, kb, n);
+                const float* col = g.B + std::min<int64_t>(n, g.N - 1) * g.sbn;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) bv[x][j] = col[(int64_t)min(step * kStep + kb + j, g.K - 1) * g.sbk];
+            } else if (BK_FAST) {
+#pragma unroll
+                for (int j = 0; j < 8; j += 4) {
+                    const uint4 v = load16(reinterpret_cast<const char*>(g.B + step * kStep + j) + from[x]);
+                    bv[x][j] = __uint_as_float(v.x);
+                    bv[x][j + 1] = __uint_as_float(v.y);
+                    bv[x][j + 2] = __uint_as_float(v.z);
+                    bv[x][j + 3] = __uint_as_float(v.w);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    bv[x][j] = *reinterpret_cast<const float*>(
+                        reinterpret_cast<const char*>(g.B + (int64_t)(step * kStep + j) * g.sbk) + from[x]);
+            }
+        }
+    };
+    // (columns beyond N are another column's values: nothing of them is stored)
+    auto store_b = [&](int step, int buf, auto last) {
+#pragma unroll
+        for (int x = 0; x < kPer; ++x) {
+            const int u = tid + x * kStepThreads;
+            if (u >= kItems) break;
+            int at, kb, n;
+            item(u, at, kb, n);
+            kb += step * kStep;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = (!decltype(last)::value || kb + j < g.K) ? bv[x][j] : 0.f;
+            uint32_t p[4], q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (BF) {
+                    const uint32_t h0 = f32_to_bf16_rne(v[2 * j]), h1 = f32_to_bf16_rne(v[2 * j + 1]);
+                    p[j] = h0 | (h1 << 16);
+                    q[j] = f32_to_bf16_rne(v[2 * j] - __uint_as_float(h0 << 16)) |
+                           (f32_to_bf16_rne(v[2 * j + 1] - __uint_as_float(h1 << 16)) << 16);
+                } else {
+                    p[j] = __float_as_uint(v[2 * j]);          // lane group 0: even values
+                    q[j] = __float_as_uint(v[2 * j + 1]);      // lane group 1: odd values
+                }
+            }
+            frag[buf][at] = make_uint4(p[0], p[1], p[2], p[3]);
+            frag[buf][at + (BF ? 64 : 32)] = make_uint4(q[0], q[1], q[2], q[3]);
+        }
+    };
+
+    float16_t acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
+
+    auto multiply = [&](int buf, int t, const uint4& av) {
+        const uint4* fr = frag[buf] + t * kLds + lane;
+        if constexpr (BF) {
+            const bf16x8_t ax = __builtin_bit_cast(bf16x8_t, av);
+            // four tiles at a time, so that no instruction waits for the sums of the one before it
+#pragma unroll
+            for (int n4 = 0; n4 < NT; n4 += 4) {
+                uint4 w[2][4];
+#pragma unroll
+                for (int nt = n4; nt < NT && nt < n4 + 4; ++nt) {
+                    w[0][nt - n4] = fr[(2 * nt) * 64];
+                    w[1][nt - n4] = fr[(2 * nt + 1) * 64];
+                }
+#pragma unroll
+                for (int half = 0; half < 2; ++half)
+#pragma unroll
+                    for (int nt = n4; nt < NT && nt < n4 + 4; ++nt)
+                        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            ax, __builtin_bit_cast(bf16x8_t, w[half][nt - n4]), acc[nt], 0, 0, 0);
+            }
+        } else {
+            // (k0|k4) (k1|k5) -> (k0|k1) (k4|k5), and so for the other two
+            const auto lo = __builtin_amdgcn_permlane32_swap(av.x, av.y, false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(av.z, av.w, false, false);
+            const float k01 = __uint_as_float(lo[0]), k45 = __uint_as_float(lo[1]);
+            const float k23 = __uint_as_float(hi[0]), k67 = __uint_as_float(hi[1]);
+#pragma unroll
+            for (int n4 = 0; n4 < NT; n4 += 4) {
+                uint4 w[4];
+#pragma unroll
+                for (int nt = n4; nt < NT && nt < n4 + 4; ++nt) w[nt - n4] = fr[nt * 64];
+                auto pair = [&](float av2, auto value) {
+#pragma unroll
+                    for (int nt = n4; nt < NT && nt < n4 + 4; ++nt)
+                        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(av2, __uint_as_float(value(w[nt - n4])),
+                                                                       acc[nt], 0, 0, 0);
+                };
+                pair(k01, [](const uint4& v) { return v.x; });
+                pair(k23, [](const uint4& v) { return v.y; });
+                pair(k45, [](const uint4& v) { return v.z; });
+                pair(k67, [](const uint4& v) { return v.w; });
+            }
+        }
+    };
+
+    uint4 a[kChunks], next[kChunks];
+    if (g.K < kVec) {
+        T v[kVec] = {};
+#pragma unroll
+        for (int x = 0; x < kVec; ++x)
+            if (x < g.K) v[x] = row[x];
+#pragma unroll
+        for (int t = 0; t < kChunks; ++t) a[t] = __builtin_bit_cast(uint4, v);
+    } else {
+        load_a(0, a);
+    }
+    if (steps > 1) {
+        load_b(0, std::false_type{});
+        store_b(0, 0, std::false_type{});
+        __syncthreads();
+        for (int step = 0; step + 2 < steps; ++step) {
+            load_a(step + 1, next);
+            load_b(step + 1, std::false_type{});
+            __builtin_amdgcn_sched_barrier(0);     // the loads stay ahead of the MFMAs
+#pragma unroll
+            for (int t = 0; t < kChunks; ++t) multiply(step & 1, t, a[t]);
+            __builtin_amdgcn_sched_barrier(0);
+            store_b(step + 1, (step + 1) & 1, std::false_type{});
+#pragma unroll
+            for (int t = 0; t < kChunks; ++t) a[t] = next[t];
+            __syncthreads();
+        }
+        load_a(steps - 1, next);
+        load_b(steps - 1, std::true_type{});
+#pragma unroll
+        for (int t = 0; t < kChunks; ++t) multiply(steps & 1, t, a[t]);
+#pragma unroll
+        for (int t = 0; t < kChunks; ++t) a[t] = next[t];
+    } else {
+        load_b(0, std::true_type{});
+    }
+    store_b(steps - 1, (steps - 1) & 1, std::true_type{});
+    __syncthreads();
+    // the last step, where K ends
+#pragma unroll
+    for (int t = 0; t < kChunks; ++t) {
+        const int k0 = (steps - 1) * kStep + t * kChunk, k_first = k0 + gq * kVec;
+        if (k0 >= g.K) break;
+        uint4 av = a[t];
+        if (k_first > k_last && rest != 0 && g.K >= kVec) av = front_of_piece<T>(av, rest);
+        const bool beyond = k_first >= g.K;
+        av = make_uint4(beyond ? 0u : av.x, beyond ? 0u : av.y, beyond ? 0u : av.z, beyond ? 0u : av.w);
+        multiply((steps - 1) & 1, t, av);
+    }
+
+    // lane holds column c; register r holds row 8*(r/4) + 4*(lane/32) + r%4
+    T* C = static_cast<T*>(g.C);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int n = n0 + nt * 32 + c;
+        if (n >= g.N) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t i = row0 + 8 * (r / 4) + 4 * gq + (r % 4);
+            if (i < g.M) C[i * g.ldc + n] = from_f32<T>(acc[nt][r]);
+        }
+    }
+}
+
+// Column tiles per workgroup: at most eight (128 accumulator registers leave two wavefronts per
+// SIMD), the slabs as even as they come; with few rows two, so that more workgroups share the work.
+template <typename T>
+int launch_steps(StepArgs g, hipStream_t st)
+{
+    const int need = (g.N + 31) / 32;
+    const int64_t row_blocks = (g.M + kStepRows - 1) / kStepRows;
+    g.slabs = (need + 7) / 8;
+    int nt = (need + g.slabs - 1) / g.slabs;
+    if (nt <= 4) nt = nt <= 2 ? 2 : 4;
+    if (nt > 2 && row_blocks * g.slabs < 256) nt = row_blocks * ((need + 3) / 4) < 256 ? 2 : 4;
+    g.slabs = (need + nt - 1) / nt;
+    const unsigned grid = (unsigned)((row_blocks + 7) / 8 * 8 * g.slabs);
+    auto with = [&](auto bk_fast) {
+        constexpr bool BK = decltype(bk_fast)::value;
+        switch (nt) {
+            case 2: k_gemm_steps<T, 2, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+            case 4: k_gemm_steps<T, 4, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+            case 5: k_gemm_steps<T, 5, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+            case 6: k_gemm_steps<T, 6, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+            case 7: k_gemm_steps<T, 7, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+            default: k_gemm_steps<T, 8, BK><<<grid, kStepThreads, 0, st>>>(g); break;
+        }
+    };
+    if (g.sbk == 1)
+        with(std::true_type{});
+    else
+        with(std::false_type{});
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
 // ---- dW = X^T dZ: contraction over the rows ---------------------------------
 //
 // Here both operands have the contraction index (the node) as their slow
@@ -1241,16 +1255,10 @@ constexpr int kMaxSlabs = 512;
 // bytes, down to 32 rows: a step of few nodes would otherwise wait for a handful of workgroups.
 int slabs_for(int64_t n, int K, int F)
 {
-    const int64_t tiles = (int64_t)((K + BM - 1) / BM) * ((F + BN - 1) / BN);
+    const int64_t tiles = (int64_t)((K + 127) / 128) * ((F + 127) / 128);
     const int64_t want = std::min<int64_t>(kMaxSlabs, std::max<int64_t>(1, (1024 + tiles - 1) / tiles));
     const int64_t cheap = std::min(n / 32, n * (K + F) / (2 * (int64_t)K * F));
-    return (int)std::max<int64_t>(1, std::min(want, std::max(n / (4 * BK), cheap)));
-}
-
-// groups of 4 consecutive elements can be moved with one access: rows start aligned
-int vec_ok(const void* p, int64_t ld, int elem_bytes)
-{
-    return (reinterpret_cast<uintptr_t>(p) % (4 * elem_bytes) == 0) && (ld % 4 == 0);
+    return (int)std::max<int64_t>(1, std::min(want, std::max(n / 128, cheap)));
 }
 
 }  // namespace
@@ -1276,22 +1284,10 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     if (n == 0) return SAR_OK;
     SAR_CHECK_ARG(X && W && Z, "X, W or Z is null");
     hipStream_t st = sar::as_stream(stream);
-    GemmArgs g{};
-    g.A = X;
-    g.B = W;
-    g.C = Z;
-    g.M = n;
-    g.N = F;
-    g.Kd = K;
-    g.lda = K;
-    g.ldb = F;
-    g.ldc = F;
-    g.vec_a = vec_ok(X, K, dtype == SAR_F32 ? 4 : 2);
-    g.vec_b = vec_ok(W, F, 4);
     SkinnyPlan plan;
     const bool want_scores = a_score || a_score2;
-    // fp32 rows that are no whole number of pieces stay with the tiled kernel: the two take the
-    // contraction in different orders, and the scores' signs decide slopes
+    // fp32 rows that are no whole number of pieces take the stepwise kernel, whose contraction runs in its
+    // natural order, as it always did for them: the scores' signs decide slopes
     const bool rows_whole = dtype == SAR_BF16 || K % 4 == 0;
     // With fp32 rows the scores are two more columns of the product (z_h . a_h = x . (W_h a_h)),
     // equal to the scores of the stored rows up to fp32 rounding.  With bf16 rows they are taken
@@ -1312,12 +1308,8 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
         else
             SAR_TRY((launch_skinny<bf16_t, bf16_t, false>(sk, plan, st)));
     } else {
-        dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((F + BN - 1) / BN), 1);
-        if (dtype == SAR_F32)
-            k_gemm<float, float, float, false><<<grid, kGemmThreads, 0, st>>>(g);
-        else
-            k_gemm_bf16<bf16_t, float, bf16_t, false><<<grid, kGemmThreads, 0, st>>>(g);
-        SAR_LAUNCH_CHECK();
+        const StepArgs g{X, K, n, W, F, 1, Z, F, K, F, 0};
+        SAR_TRY(dtype == SAR_F32 ? launch_steps<float>(g, st) : launch_steps<bf16_t>(g, st));
     }
     // (one pass over the stored rows; with one vector the same vector rides along twice)
     if (a_score || a_score2) {
@@ -1424,22 +1416,9 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
         SAR_LAUNCH_CHECK();
     }
     if (dX) {
-        // dX[n,K] = dZ W^T : B(k=f, j=kcol) = W[kcol*F + f]
-        GemmArgs g{};
-        g.A = dZ;
-        g.B = W;
-        g.C = dX;
-        g.M = n;
-        g.N = K;
-        g.Kd = F;
-        g.lda = F;
-        g.ldb = F;
-        g.ldc = K;
-        g.vec_a = vec_ok(dZ, F, dtype == SAR_F32 ? 4 : 2);
-        g.vec_b = vec_ok(W, F, 4);
+        // dX[n,K] = dZ W^T : B(k = f, n = kcol) = W[kcol * F + f]
         SkinnyPlan plan;
         if (plan_skinny(F, K, dtype, 0, &plan)) {
-            // B(k = f, n = kcol) = W[kcol * F + f]
             SkinnyArgs sk{dZ, F, n, W, 1, F, dX, K, F, K, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                           plan.stage_off};
             if (op) {
@@ -1455,12 +1434,8 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
             }
         } else {
             if (op) return sar::fail(SAR_ERR_STATE, "rows formed on the fly need the skinny dX kernel");
-            dim3 grid((unsigned)((n + BM - 1) / BM), (unsigned)((K + BN - 1) / BN), 1);
-            if (dtype == SAR_F32)
-                k_gemm<float, float, float, true><<<grid, kGemmThreads, 0, st>>>(g);
-            else
-                k_gemm_bf16<bf16_t, float, bf16_t, true><<<grid, kGemmThreads, 0, st>>>(g);
-            SAR_LAUNCH_CHECK();
+            const StepArgs g{dZ, F, n, W, 1, F, dX, K, F, K, 0};
+            SAR_TRY(dtype == SAR_F32 ? launch_steps<float>(g, st) : launch_steps<bf16_t>(g, st));
         }
     }
     return SAR_OK;

@@ -12,10 +12,20 @@ f64 = lambda t: t.to(torch.float64).cpu().numpy()
 
 
 @pytest.mark.parametrize("K,F", [(3, 5), (7, 64), (9, 65), (32, 47), (33, 128), (61, 129), (100, 256), (129, 31),
-                                 (200, 257), (255, 40), (257, 1), (400, 400), (47, 511)])
+                                 (200, 257), (255, 40), (257, 1), (400, 400), (47, 511), (512, 512), (5, 300), (1, 700)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n", [1, 31, 700, 5003])
 def test_shapes(K, F, dtype, n):
+    check(K, F, dtype, n)
+
+
+@pytest.mark.parametrize("K,F", [(400, 300), (354, 353), (512, 224), (330, 289)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_wide_column_slabs_of_many_rows(K, F, dtype):
+    check(K, F, dtype, 20_011)
+
+
+def check(K, F, dtype, n):
     g = torch.Generator().manual_seed(n + 1000 * K + F)
     # one element past an allocation's start: no row is aligned to more than that
     off = lambda n, w: torch.randn(n * w + 1, generator=g).to(dtype).cuda()[1:].view(n, w)
