@@ -608,6 +608,14 @@ struct NodeLanes {
     // whether this lane (and not the one before it) speaks for its value x
     __device__ inline bool owns(int x) const { return !RAG || (x >= dup && x < width); }
     __device__ inline float head_sum(float v) const { return f256::group_all<LPH, f256::OpSum>(v); }
+    // The sum from the head's first lane to its last, one after the other; the last lane has it.
+    __device__ inline float head_sum_in_order(float v) const
+    {
+        float s = v;
+        for (int k = VEC; k < width; k += VEC)
+            s = __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x138 /* lane - 1 */, 0xf, 0xf, false)) + v;
+        return s;
+    }
     static __device__ inline float widen(float x) { return x; }
     static __device__ inline float widen(bf16_t x) { return __uint_as_float((uint32_t)x.bits << 16); }
     static __device__ inline void narrow(float* p, float v) { *p = v; }
@@ -625,6 +633,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__
                                                            float* __restrict__ score2)
 {
     const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
+    // A score's last bit decides on which side of LeakyReLU's kink an edge falls now and then, so heads of
+    // whole lanes that fill no power of two keep the order of addition that they have always had.
+    const bool in_order = !RAG && !is_pow2(D / VEC);
+    const int writer = in_order ? D / VEC - 1 : 0;
     float av[VEC] = {}, av2[VEC] = {};
     if (lm.on) {
         lm.load_vec(avec, av);
@@ -647,9 +659,9 @@ __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__
             c = fmaf(av[x], z[x], c);
             c2 = fmaf(av2[x], z[x], c2);
         }
-        c = lm.head_sum(c);
-        if (avec2) c2 = lm.head_sum(c2);
-        if (v < n && lm.on && lm.k_pos == 0) {
+        c = in_order ? lm.head_sum_in_order(c) : lm.head_sum(c);
+        if (avec2) c2 = in_order ? lm.head_sum_in_order(c2) : lm.head_sum(c2);
+        if (v < n && lm.on && lm.k_pos == writer) {
             score[v * ldh + lm.h] = c;
             if (avec2) score2[v * ldh + lm.h] = c2;
         }
