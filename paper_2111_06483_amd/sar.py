@@ -66,29 +66,38 @@ def lib() -> ctypes.CDLL:
             raise RuntimeError(
                 "%s is missing: build it with `python -m paper_2111_06483_amd.build` "
                 "(there is no fallback path)" % LIB_PATH)
-        _lib = ctypes.CDLL(LIB_PATH)
-        _lib.sar_last_error.restype = ctypes.c_char_p
-        for name in EXPORTS:
-            getattr(_lib, name)   # fail early if a symbol is missing
+        loaded = ctypes.CDLL(LIB_PATH)
+        for name, sig in _SIGNATURES.items():
+            getattr(loaded, name).argtypes = [_CTYPES[c] for c in sig]   # fails early if a symbol is missing
+        loaded.sar_last_error.restype = ctypes.c_char_p
+        _lib = loaded
     return _lib
 
 
-EXPORTS = [
-    "sar_last_error", "sar_version",
-    "sar_blocks_build", "sar_blocks_wrap", "sar_blocks_subset", "sar_blocks_info", "sar_blocks_get", "sar_blocks_singles",
-    "sar_blocks_degree", "sar_blocks_free",
-    "sar_spmm_block", "sar_spmm_end", "sar_spmm_all", "sar_act_bwd", "sar_spmm_bwd_block", "sar_spmm_bwd_all",
-    "sar_error_add",
-    "sar_gat_scores", "sar_gat_fwd_begin", "sar_gat_fwd_block", "sar_gat_fwd_end", "sar_gat_fwd_all",
-    "sar_gat_workspace_bytes", "sar_gat_bwd_begin", "sar_gat_bwd_block", "sar_gat_bwd_all", "sar_gat_bwd_end",
-    "sar_gat_bwd_end_noalloc",
-    "sar_linear_fwd", "sar_linear_bwd", "sar_linear_bwd_rows", "sar_linear_workspace_bytes",
-]
+# Parameter types of the entry points, declared once so that a call hands over plain Python values: p address,
+# i int, l int64_t, z size_t, f float.
+_SIGNATURES = {
+    "sar_last_error": "", "sar_version": "",
+    "sar_blocks_build": "ppilpliiipp", "sar_blocks_wrap": "ilpppipp", "sar_blocks_subset": "pplipp",
+    "sar_blocks_info": "ppp", "sar_blocks_get": "pip", "sar_blocks_singles": "pppppp", "sar_blocks_degree": "pp",
+    "sar_blocks_free": "p",
+    "sar_spmm_block": "pipiipp", "sar_spmm_end": "pippipilip", "sar_spmm_all": "ppiiipipp", "sar_act_bwd": "ppipilp",
+    "sar_spmm_bwd_block": "pipiiipp", "sar_spmm_bwd_all": "ppiiipp", "sar_error_add": "ppipilip",
+    "sar_gat_scores": "piliippp", "sar_gat_fwd_begin": "pppliip", "sar_gat_fwd_block": "pippppiiifpppp",
+    "sar_gat_fwd_end": "pppippiliip", "sar_gat_fwd_all": "pppppiiifippp", "sar_gat_workspace_bytes": "lliip",
+    "sar_gat_bwd_begin": "ppppipippliip", "sar_gat_bwd_block": "pipppppiiifpppppzp",
+    "sar_gat_bwd_all": "ppppppiiifpppppzp", "sar_gat_bwd_end": "pppppppiliipzp",
+    "sar_gat_bwd_end_noalloc": "pppppppiliip",
+    "sar_linear_fwd": "pppiliiiippppp", "sar_linear_bwd": "pppppiliipzp", "sar_linear_bwd_rows": "ppplppiipppilippzp",
+    "sar_linear_workspace_bytes": "liip",
+}
+_CTYPES = {"p": _vp, "i": _c_int, "l": _c_i64, "z": ctypes.c_size_t, "f": ctypes.c_float}
+EXPORTS = list(_SIGNATURES)
 
 
 def _same_shape(a: torch.Tensor, b: Optional[torch.Tensor]) -> None:
     """The C side takes one size for both: refuse a second tensor of another shape or dtype."""
-    if b is not None and (tuple(a.shape) != tuple(b.shape) or a.dtype != b.dtype):
+    if b is not None and (a.shape != b.shape or a.dtype != b.dtype):
         raise SarError(SAR_ERR_INVALID_ARG, "tensors of shape %s %s and %s %s must match"
                        % (tuple(a.shape), a.dtype, tuple(b.shape), b.dtype))
 
@@ -98,17 +107,28 @@ def _check(rc: int) -> None:
         raise SarError(rc, lib().sar_last_error().decode())
 
 
-def _ptr(t: Optional[torch.Tensor]) -> _vp:
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
-        return _vp(None)
+        return None
     assert t.is_contiguous(), "tensors passed to the library must be contiguous"
-    return _vp(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> _vp:
+def _bytes(t: torch.Tensor) -> int:
+    return t.numel() * t.element_size()
+
+
+# The address of the current stream without the Stream object around it, which took a third of the host
+# time of a short pass (2 of 12 us per call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream() -> Optional[int]:
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
     if torch.cuda.is_available():
-        return _vp(torch.cuda.current_stream().cuda_stream)
-    return _vp(None)
+        return torch.cuda.current_stream().cuda_stream
+    return None
 
 
 def dtype_code(dt: torch.dtype) -> int:
@@ -124,20 +144,20 @@ def _ptr_array(ts: Sequence[Optional[torch.Tensor]], what: str = "tensor", dtype
     """Host array of device pointers for the calls that take one tensor per block.  The C side
     reinterprets the memory, so every entry must be what the call assumes: on the device,
     contiguous, of `dtype`, and (when given) with `row_values` values per row."""
-    arr = (_vp * len(ts))()
+    ptrs = []
     for k, t in enumerate(ts):
         if t is None:
-            arr[k] = None
+            ptrs.append(None)
             continue
         if not t.is_cuda or not t.is_contiguous():
             raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] must be a contiguous device tensor" % (what, k))
         if dtype is not None and t.dtype != dtype:
             raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] is %s, the call needs %s" % (what, k, t.dtype, dtype))
-        if row_values is not None and t.numel() != t.shape[0] * row_values:
+        if row_values is not None and t.numel() != t.size(0) * row_values:
             raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] has %d values per row, the call needs %d"
-                           % (what, k, t.numel() // max(t.shape[0], 1), row_values))
-        arr[k] = t.data_ptr()
-    return arr
+                           % (what, k, t.numel() // max(t.size(0), 1), row_values))
+        ptrs.append(t.data_ptr())
+    return (_vp * len(ptrs))(*ptrs)
 
 
 class Blocks:
@@ -161,7 +181,7 @@ class Blocks:
 
     def view(self, q: int) -> BlockView:
         v = BlockView()
-        _check(lib().sar_blocks_get(self.handle, _c_int(q), ctypes.byref(v)))
+        _check(lib().sar_blocks_get(self.handle, q, ctypes.byref(v)))
         return v
 
     def n_src(self, q: int) -> int:
@@ -171,10 +191,13 @@ class Blocks:
 
     def check_rows(self, q: int, *tensors) -> None:
         """Host-side guard: per-source tensors of block q must have n_src rows."""
+        n = self._n_src.get(q)
+        if n is None:
+            n = self.n_src(q)
         for t in tensors:
-            if t is not None and t.shape[0] != self.n_src(q):
+            if t is not None and t.size(0) != n:
                 raise SarError(SAR_ERR_INVALID_ARG, "block %d has %d sources, tensor has %d rows"
-                               % (q, self.n_src(q), t.shape[0]))
+                               % (q, n, t.size(0)))
 
     def n_err_rows(self, q: int) -> int:
         """Rows of block q's dZ_q / dt_q: n_src, or n_t_rows on a SAR_BUILD_COMPACT handle."""
@@ -185,16 +208,19 @@ class Blocks:
         return self._n_err[q]
 
     def check_err_rows(self, q: int, *tensors) -> None:
+        n = self._n_err.get(q)
+        if n is None:
+            n = self._n_err[q] = self.n_err_rows(q)
         for t in tensors:
-            if t is not None and t.shape[0] != self.n_err_rows(q):
+            if t is not None and t.size(0) != n:
                 raise SarError(SAR_ERR_INVALID_ARG, "block %d's error has %d rows, tensor has %d"
-                               % (q, self.n_err_rows(q), t.shape[0]))
+                               % (q, n, t.size(0)))
 
     def check_dst(self, *tensors) -> None:
         for t in tensors:
-            if t is not None and t.shape[0] != self.n_dst:
+            if t is not None and t.size(0) != self.n_dst:
                 raise SarError(SAR_ERR_INVALID_ARG, "handle has %d destinations, tensor has %d rows"
-                               % (self.n_dst, t.shape[0]))
+                               % (self.n_dst, t.size(0)))
 
     def close(self) -> None:
         if self._h is not None:
@@ -236,8 +262,8 @@ def sar_blocks_build(src: torch.Tensor, dst: torch.Tensor, part: torch.Tensor, P
     assert src.dtype == dst.dtype and src.dtype in (torch.int32, torch.int64)
     assert part.dtype == torch.int32
     h = _vp(None)
-    _check(lib().sar_blocks_build(_ptr(src), _ptr(dst), _c_int(src.element_size()), _c_i64(src.numel()),
-                                  _ptr(part), _c_i64(part.numel()), _c_int(P), _c_int(p), _c_int(flags),
+    _check(lib().sar_blocks_build(_ptr(src), _ptr(dst), src.element_size(), src.numel(),
+                                  _ptr(part), part.numel(), P, p, flags,
                                   _stream(), ctypes.byref(h)))
     return Blocks(h, flags=flags)
 
@@ -248,8 +274,8 @@ def sar_blocks_wrap(n_dst: int, n_src: Sequence[int], indptr: Sequence[torch.Ten
     P = len(indptr)
     ns = (_c_i64 * P)(*[int(x) for x in n_src])
     h = _vp(None)
-    _check(lib().sar_blocks_wrap(_c_int(P), _c_i64(n_dst), ns, _ptr_array(indptr, "indptr", torch.int32),
-                                 _ptr_array(indices, "indices", torch.int32), _c_int(flags), _stream(),
+    _check(lib().sar_blocks_wrap(P, n_dst, ns, _ptr_array(indptr, "indptr", torch.int32),
+                                 _ptr_array(indices, "indices", torch.int32), flags, _stream(),
                                  ctypes.byref(h)))
     return Blocks(h, keep=(list(indptr), list(indices)), flags=flags)
 
@@ -259,7 +285,7 @@ def sar_blocks_subset(b: Blocks, dst_ids: torch.Tensor,
     if dst_ids.dtype != torch.int32 or dst_ids.dim() != 1 or not dst_ids.is_contiguous():
         raise SarError(SAR_ERR_INVALID_ARG, "dst_ids must be a contiguous 1-d int32 tensor")
     h = _vp(None)
-    _check(lib().sar_blocks_subset(b.handle, _ptr(dst_ids), _c_i64(dst_ids.numel()), _c_int(flags), _stream(),
+    _check(lib().sar_blocks_subset(b.handle, _ptr(dst_ids), dst_ids.numel(), flags, _stream(),
                                    ctypes.byref(h)))
     return Blocks(h, flags=flags)
 
@@ -293,15 +319,15 @@ def sar_blocks_degree(b: Blocks) -> torch.Tensor:
 def sar_spmm_block(b: Blocks, q: int, Zq: torch.Tensor, acc: torch.Tensor) -> None:
     b.check_rows(q, Zq)
     b.check_dst(acc)
-    _check(lib().sar_spmm_block(b.handle, _c_int(q), _ptr(Zq), _c_int(dtype_code(Zq.dtype)),
-                                _c_int(Zq.shape[-1]), _ptr(acc), _stream()))
+    _check(lib().sar_spmm_block(b.handle, q, _ptr(Zq), dtype_code(Zq.dtype),
+                                Zq.shape[-1], _ptr(acc), _stream()))
 
 
 def sar_spmm_end(deg: torch.Tensor, mean: bool, acc: torch.Tensor, out: torch.Tensor,
                  residual: Optional[torch.Tensor] = None, act: int = SAR_ACT_NONE) -> None:
     _same_shape(out, residual)
-    _check(lib().sar_spmm_end(_ptr(deg), _c_int(int(mean)), _ptr(acc), _ptr(residual), _c_int(act), _ptr(out),
-                              _c_int(dtype_code(out.dtype)), _c_i64(acc.shape[0]), _c_int(acc.shape[1]),
+    _check(lib().sar_spmm_end(_ptr(deg), int(mean), _ptr(acc), _ptr(residual), act, _ptr(out),
+                              dtype_code(out.dtype), acc.shape[0], acc.shape[1],
                               _stream()))
 
 
@@ -311,31 +337,31 @@ def sar_spmm_all(b: Blocks, Zq: Sequence[torch.Tensor], mean: bool, out: torch.T
         b.check_rows(q, Zq[q])
     b.check_dst(out)
     _same_shape(out, residual)
-    _check(lib().sar_spmm_all(b.handle, _ptr_array(Zq, "Zq", out.dtype, out.shape[-1]), _c_int(dtype_code(out.dtype)),
-                              _c_int(out.shape[-1]), _c_int(int(mean)), _ptr(residual), _c_int(act), _ptr(out),
+    _check(lib().sar_spmm_all(b.handle, _ptr_array(Zq, "Zq", out.dtype, out.shape[-1]), dtype_code(out.dtype),
+                              out.shape[-1], int(mean), _ptr(residual), act, _ptr(out),
                               _stream()))
 
 
 def sar_act_bwd(h: torch.Tensor, dH: torch.Tensor, act: int, G: torch.Tensor) -> None:
     _same_shape(h, dH)
     _same_shape(h, G)
-    _check(lib().sar_act_bwd(_ptr(h), _ptr(dH), _c_int(act), _ptr(G), _c_int(dtype_code(h.dtype)),
-                             _c_i64(h.numel()), _stream()))
+    _check(lib().sar_act_bwd(_ptr(h), _ptr(dH), act, _ptr(G), dtype_code(h.dtype),
+                             h.numel(), _stream()))
 
 
 def sar_spmm_bwd_block(b: Blocks, q: int, G: torch.Tensor, mean: bool, dZq: torch.Tensor) -> None:
     b.check_err_rows(q, dZq)
     b.check_dst(G)
-    _check(lib().sar_spmm_bwd_block(b.handle, _c_int(q), _ptr(G), _c_int(int(mean)),
-                                    _c_int(dtype_code(G.dtype)), _c_int(G.shape[-1]), _ptr(dZq), _stream()))
+    _check(lib().sar_spmm_bwd_block(b.handle, q, _ptr(G), int(mean),
+                                    dtype_code(G.dtype), G.shape[-1], _ptr(dZq), _stream()))
 
 
 def sar_spmm_bwd_all(b: Blocks, G: torch.Tensor, mean: bool, dZq: Sequence[torch.Tensor]) -> None:
     for q in range(b.P):
         b.check_err_rows(q, dZq[q])
     b.check_dst(G)
-    _check(lib().sar_spmm_bwd_all(b.handle, _ptr(G), _c_int(int(mean)), _c_int(dtype_code(G.dtype)),
-                                  _c_int(G.shape[-1]), _ptr_array(dZq, "dZq", G.dtype, G.shape[-1]), _stream()))
+    _check(lib().sar_spmm_bwd_all(b.handle, _ptr(G), int(mean), dtype_code(G.dtype),
+                                  G.shape[-1], _ptr_array(dZq, "dZq", G.dtype, G.shape[-1]), _stream()))
 
 
 def sar_error_add(Eq: Optional[torch.Tensor], t_rank: int, accumulate: bool, Ep: torch.Tensor) -> None:
@@ -344,21 +370,21 @@ def sar_error_add(Eq: Optional[torch.Tensor], t_rank: int, accumulate: bool, Ep:
     F = Ep.numel() // max(n, 1)
     if Eq is not None and (Eq.dtype != Ep.dtype or Eq.numel() != Eq.shape[0] * F):
         raise SarError(SAR_ERR_INVALID_ARG, "Eq and Ep must have the same row width and type")
-    _check(lib().sar_error_add(_ptr(Eq), _vp(t_rank), _c_int(int(accumulate)), _ptr(Ep), _c_int(dtype_code(Ep.dtype)),
-                               _c_i64(n), _c_int(F), _stream()))
+    _check(lib().sar_error_add(_ptr(Eq), t_rank, int(accumulate), _ptr(Ep), dtype_code(Ep.dtype),
+                               n, F, _stream()))
 
 
 # --------------------------------------------------------------------- GAT
 
 def sar_gat_scores(Z: torch.Tensor, a: torch.Tensor, score: torch.Tensor) -> None:
     H, D = a.shape
-    _check(lib().sar_gat_scores(_ptr(Z), _c_int(dtype_code(Z.dtype)), _c_i64(Z.shape[0]), _c_int(H), _c_int(D),
+    _check(lib().sar_gat_scores(_ptr(Z), dtype_code(Z.dtype), Z.shape[0], H, D,
                                 _ptr(a), _ptr(score), _stream()))
 
 
 def sar_gat_fwd_begin(m: torch.Tensor, l: torch.Tensor, acc: torch.Tensor) -> None:
     n, H, D = acc.shape
-    _check(lib().sar_gat_fwd_begin(_ptr(m), _ptr(l), _ptr(acc), _c_i64(n), _c_int(H), _c_int(D), _stream()))
+    _check(lib().sar_gat_fwd_begin(_ptr(m), _ptr(l), _ptr(acc), n, H, D, _stream()))
 
 
 def sar_gat_fwd_block(b: Blocks, q: int, Zq: torch.Tensor, s: torch.Tensor, tq: Optional[torch.Tensor],
@@ -367,16 +393,16 @@ def sar_gat_fwd_block(b: Blocks, q: int, Zq: torch.Tensor, s: torch.Tensor, tq: 
     _, H, D = acc.shape
     b.check_rows(q, Zq, tq)
     b.check_dst(s, m, l, acc)
-    _check(lib().sar_gat_fwd_block(b.handle, _c_int(q), _ptr(Zq), _ptr(s), _ptr(tq), _ptr(a_l),
-                                   _c_int(dtype_code(Zq.dtype)), _c_int(H), _c_int(D), ctypes.c_float(slope),
+    _check(lib().sar_gat_fwd_block(b.handle, q, _ptr(Zq), _ptr(s), _ptr(tq), _ptr(a_l),
+                                   dtype_code(Zq.dtype), H, D, slope,
                                    _ptr(m), _ptr(l), _ptr(acc), _stream()))
 
 
 def sar_gat_fwd_end(m: torch.Tensor, l: torch.Tensor, acc: torch.Tensor, out: torch.Tensor,
                     L: torch.Tensor, act: int = SAR_ACT_NONE) -> None:
     n, H, D = acc.shape
-    _check(lib().sar_gat_fwd_end(_ptr(m), _ptr(l), _ptr(acc), _c_int(act), _ptr(out), _ptr(L),
-                                 _c_int(dtype_code(out.dtype)), _c_i64(n), _c_int(H), _c_int(D), _stream()))
+    _check(lib().sar_gat_fwd_end(_ptr(m), _ptr(l), _ptr(acc), act, _ptr(out), _ptr(L),
+                                 dtype_code(out.dtype), n, H, D, _stream()))
 
 
 def sar_gat_fwd_all(b: Blocks, Zq: Sequence[torch.Tensor], s: torch.Tensor,
@@ -388,13 +414,13 @@ def sar_gat_fwd_all(b: Blocks, Zq: Sequence[torch.Tensor], s: torch.Tensor,
     b.check_dst(s, out, L)
     _check(lib().sar_gat_fwd_all(b.handle, _ptr_array(Zq, "Zq", out.dtype, H * D), _ptr(s),
                                  None if tq is None else _ptr_array(tq, "tq", torch.float32, H), _ptr(a_l),
-                                 _c_int(dtype_code(out.dtype)), _c_int(H), _c_int(D), ctypes.c_float(slope),
-                                 _c_int(act), _ptr(out), _ptr(L), _stream()))
+                                 dtype_code(out.dtype), H, D, slope,
+                                 act, _ptr(out), _ptr(L), _stream()))
 
 
 def sar_gat_workspace_bytes(n_dst: int, n_src_max: int, H: int, D: int) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().sar_gat_workspace_bytes(_c_i64(n_dst), _c_i64(n_src_max), _c_int(H), _c_int(D),
+    _check(lib().sar_gat_workspace_bytes(n_dst, n_src_max, H, D,
                                          ctypes.byref(out)))
     return out.value
 
@@ -405,9 +431,9 @@ def sar_gat_bwd_begin(G: torch.Tensor, out: torch.Tensor, s: torch.Tensor, L: to
     n, H, D = G.shape
     _same_shape(G, out)
     _same_shape(G, Gact)
-    _check(lib().sar_gat_bwd_begin(_ptr(G), _ptr(out), _ptr(s), _ptr(L), _c_int(act), _ptr(Gact),
-                                   _c_int(dtype_code(G.dtype)), _ptr(rec), _ptr(ds), _c_i64(n), _c_int(H),
-                                   _c_int(D), _stream()))
+    _check(lib().sar_gat_bwd_begin(_ptr(G), _ptr(out), _ptr(s), _ptr(L), act, _ptr(Gact),
+                                   dtype_code(G.dtype), _ptr(rec), _ptr(ds), n, H,
+                                   D, _stream()))
 
 
 def sar_gat_bwd_block(b: Blocks, q: int, Zq: torch.Tensor, G: torch.Tensor, tq: torch.Tensor,
@@ -418,10 +444,10 @@ def sar_gat_bwd_block(b: Blocks, q: int, Zq: torch.Tensor, G: torch.Tensor, tq: 
     b.check_rows(q, Zq, tq)
     b.check_err_rows(q, dZq, dtq)
     b.check_dst(G, rec, ds)
-    _check(lib().sar_gat_bwd_block(b.handle, _c_int(q), _ptr(Zq), _ptr(G), _ptr(tq), _ptr(rec), _ptr(a_l),
-                                   _c_int(dtype_code(G.dtype)), _c_int(H), _c_int(D), ctypes.c_float(slope),
+    _check(lib().sar_gat_bwd_block(b.handle, q, _ptr(Zq), _ptr(G), _ptr(tq), _ptr(rec), _ptr(a_l),
+                                   dtype_code(G.dtype), H, D, slope,
                                    _ptr(dZq), _ptr(dtq), _ptr(ds), _ptr(da_l), _ptr(work),
-                                   ctypes.c_size_t(work.numel() * work.element_size()), _stream()))
+                                   _bytes(work), _stream()))
 
 
 def sar_gat_bwd_all(b: Blocks, Zq: Sequence[torch.Tensor], G: torch.Tensor, tq: Sequence[torch.Tensor],
@@ -437,11 +463,11 @@ def sar_gat_bwd_all(b: Blocks, Zq: Sequence[torch.Tensor], G: torch.Tensor, tq: 
     _check(lib().sar_gat_bwd_all(b.handle, _ptr_array(Zq, "Zq", G.dtype, H * D), _ptr(G),
                                  None if tq is None else _ptr_array(tq, "tq", torch.float32, H),
                                  _ptr(rec), _ptr(a_l),
-                                 _c_int(dtype_code(G.dtype)), _c_int(H), _c_int(D), ctypes.c_float(slope),
+                                 dtype_code(G.dtype), H, D, slope,
                                  _ptr_array(dZq, "dZq", G.dtype, H * D),
                                  None if dtq is None else _ptr_array(dtq, "dtq", torch.float32, H),
                                  _ptr(ds), _ptr(da_l), _ptr(work),
-                                 ctypes.c_size_t(work.numel() * work.element_size()), _stream()))
+                                 _bytes(work), _stream()))
 
 
 def sar_gat_bwd_end(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor, dZadd: Optional[torch.Tensor],
@@ -450,25 +476,25 @@ def sar_gat_bwd_end(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor, dZa
     """dZadd_rank: device address of the local block's t_rank (BlockView.t_rank) when dZadd is compact.
     dZdst None: only da_r."""
     H, D = a_r.shape
-    _check(lib().sar_gat_bwd_end(_ptr(Zdst), _ptr(ds), _ptr(a_r), _ptr(dZadd), _vp(dZadd_rank), _ptr(dZdst), _ptr(da_r),
-                                 _c_int(dtype_code(Zdst.dtype)), _c_i64(Zdst.shape[0]), _c_int(H), _c_int(D),
-                                 _ptr(work), ctypes.c_size_t(work.numel() * work.element_size()), _stream()))
+    _check(lib().sar_gat_bwd_end(_ptr(Zdst), _ptr(ds), _ptr(a_r), _ptr(dZadd), dZadd_rank, _ptr(dZdst), _ptr(da_r),
+                                 dtype_code(Zdst.dtype), Zdst.shape[0], H, D,
+                                 _ptr(work), _bytes(work), _stream()))
 
 
 def sar_gat_bwd_end_noalloc(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor,
                             dZadd: Optional[torch.Tensor], dZdst: torch.Tensor, da_r: torch.Tensor,
                             dZadd_rank: Optional[int] = None) -> None:
     H, D = a_r.shape
-    _check(lib().sar_gat_bwd_end_noalloc(_ptr(Zdst), _ptr(ds), _ptr(a_r), _ptr(dZadd), _vp(dZadd_rank), _ptr(dZdst), _ptr(da_r),
-                                         _c_int(dtype_code(Zdst.dtype)), _c_i64(Zdst.shape[0]), _c_int(H),
-                                         _c_int(D), _stream()))
+    _check(lib().sar_gat_bwd_end_noalloc(_ptr(Zdst), _ptr(ds), _ptr(a_r), _ptr(dZadd), dZadd_rank, _ptr(dZdst), _ptr(da_r),
+                                         dtype_code(Zdst.dtype), Zdst.shape[0], H,
+                                         D, _stream()))
 
 
 # ------------------------------------------------------------------ linear
 
 def sar_linear_workspace_bytes(n: int, K: int, F: int) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().sar_linear_workspace_bytes(_c_i64(n), _c_int(K), _c_int(F), ctypes.byref(out)))
+    _check(lib().sar_linear_workspace_bytes(n, K, F, ctypes.byref(out)))
     return out.value
 
 
@@ -478,8 +504,8 @@ def sar_linear_fwd(X: torch.Tensor, W: torch.Tensor, Z: torch.Tensor,
     n, K = X.shape
     F = W.shape[1]
     H, D = (a_score.shape if a_score is not None else (0, 0))
-    _check(lib().sar_linear_fwd(_ptr(X), _ptr(W), _ptr(Z), _c_int(dtype_code(X.dtype)), _c_i64(n), _c_int(K),
-                                _c_int(F), _c_int(H), _c_int(D), _ptr(a_score), _ptr(score), _ptr(a_score2),
+    _check(lib().sar_linear_fwd(_ptr(X), _ptr(W), _ptr(Z), dtype_code(X.dtype), n, K,
+                                F, H, D, _ptr(a_score), _ptr(score), _ptr(a_score2),
                                 _ptr(score2), _stream()))
 
 
@@ -489,9 +515,9 @@ def sar_linear_bwd(X: Optional[torch.Tensor], dZ: torch.Tensor, W: Optional[torc
     n = dZ.shape[0]
     F = dZ.numel() // max(n, 1)
     K = X.shape[1] if X is not None else W.shape[0]
-    wb = 0 if work is None else work.numel() * work.element_size()
-    _check(lib().sar_linear_bwd(_ptr(X), _ptr(dZ), _ptr(W), _ptr(dW), _ptr(dX), _c_int(dtype_code(dZ.dtype)),
-                                _c_i64(n), _c_int(K), _c_int(F), _ptr(work), ctypes.c_size_t(wb), _stream()))
+    wb = 0 if work is None else _bytes(work)
+    _check(lib().sar_linear_bwd(_ptr(X), _ptr(dZ), _ptr(W), _ptr(dW), _ptr(dX), dtype_code(dZ.dtype),
+                                n, K, F, _ptr(work), wb, _stream()))
 
 
 def sar_linear_bwd_rows(X: Optional[torch.Tensor], E: Optional[torch.Tensor], E_rank: Optional[int],
@@ -502,7 +528,7 @@ def sar_linear_bwd_rows(X: Optional[torch.Tensor], E: Optional[torch.Tensor], E_
     """E_rank: device address of a t_rank array (BlockView.t_rank) when E is compact."""
     K = X.shape[1] if X is not None else W.shape[0]
     n_E = 0 if E is None else E.shape[0]
-    wb = 0 if work is None else work.numel() * work.element_size()
-    _check(lib().sar_linear_bwd_rows(_ptr(X), _ptr(E), _vp(E_rank), _c_i64(n_E), _ptr(ds), _ptr(a_r), _c_int(H),
-                                     _c_int(D), _ptr(W), _ptr(dW), _ptr(dX), _c_int(dtype_code(dtype)), _c_i64(n),
-                                     _c_int(K), _ptr(rows), _ptr(work), ctypes.c_size_t(wb), _stream()))
+    wb = 0 if work is None else _bytes(work)
+    _check(lib().sar_linear_bwd_rows(_ptr(X), _ptr(E), E_rank, n_E, _ptr(ds), _ptr(a_r), H,
+                                     D, _ptr(W), _ptr(dW), _ptr(dX), dtype_code(dtype), n,
+                                     K, _ptr(rows), _ptr(work), wb, _stream()))
