@@ -1207,43 +1207,43 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
     const f256::BwdTabs t = bwd_tabs(tabs);
     const f256::BwdP p = bwd_params(a);
     unsigned g_wide = 0, g_few = 0, g_single = 0;
-    if (a.n_wide > 0) {
-        if constexpr (SLOTS) {
-            auto wide = slots::k_gat_bwd_slots<T, LPH, ALL, RAG>;
-            static const int resident = resident_workgroups(wide);
-            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
-            wide<<<g_wide, kGatherThreads, 0, st>>>(t, p, n_slots);
-        } else {
-            auto wide = f256::k_gat_bwd_f256<T, LPH, B, ALL, true>;
-            static const int resident = resident_workgroups(wide);
-            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
-            wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
-        }
-        SAR_LAUNCH_CHECK();
-    }
     // The sources of one edge go destination-major where the handle lists them that way.  In the
     // work list they sit between the other few-edge sources and the ones without an edge, so the
-    // few-edges kernel takes the list in two pieces around them.
+    // few-edges part takes the list in two pieces around them.
     const int64_t n_edged = std::max(a.n_wide, std::min(a.n_rows, a.n_touched));
     const int64_t n_pulled = (!RAG && ALL && a.s_dst && a.n_single <= n_edged - a.n_wide) ? a.n_single : 0;
     const int64_t piece[2][2] = {{a.n_wide, n_pulled ? n_edged - n_pulled : a.n_rows}, {n_edged, n_pulled ? a.n_rows : n_edged}};
-    for (int k = 0; k < 2; ++k) {
-        const int64_t n = piece[k][1] - piece[k][0];
-        if (n <= 0) continue;
-        unsigned g = 0;
-        if constexpr (SLOTS) {
-            auto few = slots::k_gat_bwd_few_slots<T, LPH, ALL, RAG>;
-            static const int resident = resident_workgroups(few);
-            g = grid_of(n, (int64_t)n_slots * kWavesPerWG, resident);
-            few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few), n_slots);
-        } else {
-            auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
-            static const int resident = resident_workgroups(few);
-            g = grid_of(n, (int64_t)(B / 2) * kWavesPerWG, resident);
-            few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few));
+    if constexpr (SLOTS) {
+        auto kernel = slots::k_gat_bwd_slots<T, LPH, ALL, RAG>;
+        static const int resident = resident_workgroups(kernel);
+        if (a.n_wide > 0) g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
+        for (int k = 0; k < 2; ++k) {
+            const int64_t n = piece[k][1] - piece[k][0];
+            const unsigned wide = k == 0 ? g_wide : 0;
+            const unsigned g = n > 0 ? grid_of(n, (int64_t)n_slots * kWavesPerWG, resident) : 0;
+            if (wide + g == 0) continue;
+            kernel<<<wide + g, kGatherThreads, 0, st>>>(t, p, n_slots, (int)wide, piece[k][0], piece[k][1],
+                                                        (int)(k == 0 ? 0 : g_wide + g_few));
+            SAR_LAUNCH_CHECK();
+            g_few += g;
         }
-        SAR_LAUNCH_CHECK();
-        g_few += g;
+    } else {
+        auto wide = f256::k_gat_bwd_f256<T, LPH, B, ALL, true>;
+        auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
+        static const int resident_wide = resident_workgroups(wide), resident_few = resident_workgroups(few);
+        if (a.n_wide > 0) {
+            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
+            wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
+            SAR_LAUNCH_CHECK();
+        }
+        for (int k = 0; k < 2; ++k) {
+            const int64_t n = piece[k][1] - piece[k][0];
+            if (n <= 0) continue;
+            const unsigned g = grid_of(n, (int64_t)(B / 2) * kWavesPerWG, resident_few);
+            few<<<g, kGatherThreads, 0, st>>>(t, p, piece[k][0], piece[k][1], (int)(g_wide + g_few));
+            SAR_LAUNCH_CHECK();
+            g_few += g;
+        }
     }
     if constexpr (!RAG && ALL) {
         if (n_pulled > 0) {

@@ -308,7 +308,8 @@ __device__ inline void store_partial(float (&dal)[4], float (*part)[kWave][4], c
 // Sources of at least 8 edges: one wavefront each (a workgroup for the long ones), its slots taking
 // different edges.
 template <typename T, int LPH, bool ALL, bool RAG>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, BwdP a, int n_slots)
+__device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots, int block, int n_blocks,
+                                float* partial_row)
 {
     constexpr int B = kBatch<LPH>;
     __shared__ float part[kWavesPerWG][kWave][4];
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
         if (p.k_pos == 0 && tabs.dt[q]) tabs.dt[q][jo * a.ldh + p.h] = ac.dt;
     };
 
-    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+    for (int64_t r = block; r < a.n_long; r += n_blocks) {
         const uint32_t id = a.rows[r];
         const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
         BwdAcc4 ac;
@@ -430,8 +431,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
         }
         __syncthreads();
     }
-    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
+    for (int64_t r = a.n_long + (int64_t)block * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.rows[r]);
         const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
         BwdAcc4 ac;
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
         outputs(ac, q, j, zj);
     }
     __syncthreads();
-    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width, a.partial + (int64_t)blockIdx.x * f256::kF);
+    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width, partial_row);
 }
 
 // The other sources of the list (fewer than 8 edges, or none): every slot takes a source of its
@@ -448,8 +449,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, 
 // round of gathers (two of four where a head has only four lanes).  List entries are read three
 // rounds ahead, ranges and output rows two, destinations one.
 template <typename T, int LPH, bool ALL, bool RAG>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs tabs, BwdP a, int64_t r_begin,
-                                                                      int64_t r_end, int partial_row0, int n_slots)
+__device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, int64_t r_begin, int64_t r_end,
+                               int block, int n_blocks, float* partial_row)
 {
     constexpr int B = kBatch<LPH>;
     constexpr int kMost = 1 << kNarrowMaxClass;          // this kernel's sources have fewer edges
@@ -485,8 +486,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs ta
 
     struct Meta { int q, j, beg, cnt, jo; };
     struct Dst { int i[kRounds]; };
-    const int64_t stride = (int64_t)gridDim.x * kWavesPerWG * n_slots;
-    const int64_t w0 = r_begin + ((int64_t)blockIdx.x * kWavesPerWG + wave) * n_slots;   // slot 0's list position
+    const int64_t stride = (int64_t)n_blocks * kWavesPerWG * n_slots;
+    const int64_t w0 = r_begin + ((int64_t)block * kWavesPerWG + wave) * n_slots;   // slot 0's list position
     auto have = [&](int64_t w) { return p.live && w + p.slot < r_end; };
     auto load_id = [&](int64_t w) -> uint32_t { return have(w) ? a.rows[w + p.slot] : 0u; };
     auto load_meta = [&](uint32_t id, int64_t w) {
@@ -593,8 +594,25 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few_slots(BwdTabs ta
         m1 = m2;
         id2 = id3;
     }
-    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width,
-                            a.partial + ((int64_t)partial_row0 + blockIdx.x) * f256::kF);
+    store_partial<LPH, RAG>(dal, part, p, wave, n_slots, width, partial_row);
+}
+
+// One launch for both kinds of sources: the first n_wide workgroups share the wide ones (a.rows up to
+// a.n_rows, the long ones first), the others [r_begin, r_end) of the list.  They do not depend on each other,
+// and in a small call neither fills the chip: one after the other, the second waited for the first one's
+// longest row, and a launch costs as much as some of them take (4 heads x 16 over 4096 nodes: 23.4 + 5.6 -> 24.0
+// us; 16 blocks of 4 x 32, 75000 sources each: 37.4 + 31.1 -> 52.3 us a block).  Workgroup w leaves its part of da_l in
+// row partial_row0 + w.
+template <typename T, int LPH, bool ALL, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_slots(BwdTabs tabs, BwdP a, int n_slots, int n_wide,
+                                                                  int64_t r_begin, int64_t r_end, int partial_row0)
+{
+    float* const partial_row = a.partial + ((int64_t)partial_row0 + blockIdx.x) * f256::kF;
+    const int b = blockIdx.x;
+    if (b < n_wide)
+        bwd_wide<T, LPH, ALL, RAG>(tabs, a, n_slots, b, n_wide, partial_row);
+    else
+        bwd_few<T, LPH, ALL, RAG>(tabs, a, n_slots, r_begin, r_end, b - n_wide, (int)gridDim.x - n_wide, partial_row);
 }
 
 }  // namespace slots
