@@ -41,7 +41,16 @@
  *     over groups of heads, rows of the sum/mean calls (any F) over column ranges.
  *     The fastest kernels take head widths that are a multiple of 4 in layers of
  *     1, 2, 4, 8 heads or a multiple thereof (4 x 64, 8 x 32, 4 x 32, 2 x 100, ...);
- *     the results do not depend on which kernel a shape takes.
+ *     which kernel a shape takes changes results by the order of fp32 sums only.
+ *   - Score halves of the sources.  Where a call forms t_j = <a_l, z_j> itself
+ *     (tq NULL), every kernel that takes heads of at least 4 values four at a time
+ *     adds in one order, forward and backward: along each four values, then pairs
+ *     of fours, pairs of those and so on; a head that is no multiple of 4 ends in
+ *     a shorter four.  sar_gat_scores adds in that order too for fp32 heads of 4, 8,
+ *     16 ... values and, in both types, for widths that are no multiple of 4; for
+ *     the others its sums differ from those formed in flight by fp32 rounding.  An edge
+ *     whose score s_i + t_j is zero within rounding takes one slope of LeakyReLU
+ *     or the other with the last bit of t_j.
  *   - A destination with no in-edge at all has out = 0 and L = -inf, and
  *     contributes nothing to any gradient; the mean of an empty set is 0.
  *     A tensor without elements (n_dst = 0, or a block without sources) may be

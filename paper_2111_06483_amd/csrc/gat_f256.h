@@ -49,8 +49,8 @@ constexpr int kRowShr = 0x110;         // + n: lane r of a row of 16 reads lane 
 constexpr int kRowShl = 0x100;         // + n: lane r reads lane r + n
 constexpr int kQuadXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kQuadXor2 = 0x4E;        // quad_perm [2,3,0,1]
-constexpr int kRowHalfMirror = 0x141;
-constexpr int kRowRor4 = 0x124;
+constexpr int kRowHalfMirror = 0x141;  // lane r of 8 reads lane 7 - r
+constexpr int kRowMirror = 0x140;      // lane r of 16 reads lane 15 - r
 constexpr int kRowRor8 = 0x128;
 
 template <int PATTERN>
@@ -66,17 +66,19 @@ struct OpMax {
     static __device__ inline float f(float a, float b) { return fmaxf(a, b); }
 };
 
-// All-reduce over each group of LPH consecutive lanes (LPH = 1..64, power of two).
+// All-reduce over each group of LPH consecutive lanes (LPH = 1..64, power of two).  Every step pairs lanes
+// that read each other (a mirror image counts as lane ^ 4, lane ^ 8: the quads, and then the eights, hold
+// one value each by then), so every lane of the group ends with the SAME BITS, those of the sum by lane ^ 1,
+// lane ^ 2, lane ^ 4 ...  Rotations by 4 and 8 lanes would take as many instructions, but each quad would
+// add the four quads in an order of its own: lanes that store the same value, and the edges that different
+// lanes speak for, would differ in last bits.
 template <int LPH, typename Op>
 __device__ inline float group_all(float v)
 {
     if constexpr (LPH >= 2) v = Op::f(v, dpp<kQuadXor1>(v));
     if constexpr (LPH >= 4) v = Op::f(v, dpp<kQuadXor2>(v));
-    if constexpr (LPH == 8) v = Op::f(v, dpp<kRowHalfMirror>(v));
-    if constexpr (LPH >= 16) {
-        v = Op::f(v, dpp<kRowRor4>(v));
-        v = Op::f(v, dpp<kRowRor8>(v));
-    }
+    if constexpr (LPH >= 8) v = Op::f(v, dpp<kRowHalfMirror>(v));
+    if constexpr (LPH >= 16) v = Op::f(v, dpp<kRowMirror>(v));
     if constexpr (LPH >= 32) v = Op::f(v, swizzle<0x401F>(v));   // xor 16
     if constexpr (LPH >= 64) v = Op::f(v, __shfl_xor(v, 32));
     return v;
