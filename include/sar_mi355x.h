@@ -50,7 +50,7 @@
  *     16 ... values and, in both types, for widths that are no multiple of 4; for
  *     the others its sums differ from those formed in flight by fp32 rounding.  An edge
  *     whose score s_i + t_j is zero within rounding takes one slope of LeakyReLU
- *     or the other with the last bit of t_j.
+ *     or the other with the last bit of t_j; a score of exactly zero takes `slope`.
  *   - A destination with no in-edge at all has out = 0 and L = -inf, and
  *     contributes nothing to any gradient; the mean of an empty set is 0.
  *     A tensor without elements (n_dst = 0, or a block without sources) may be

@@ -421,12 +421,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd(BwdArgs tabs, BwdSca
         if (lm.on) r = Vec<T>::load(static_cast<const T*>(tabs.Z[q]) + (int64_t)j * a.ldz + lm.gl * VEC);
         Vec<T>::unpack(r, zj);
         if (tabs.t[q]) {
-            t2 = tabs.t[q][(int64_t)j * a.ldh + lm.h] * kLog2e;
+            t2 = f256::score_log2(tabs.t[q][(int64_t)j * a.ldh + lm.h]);
         } else {
             float c = 0.f;
 #pragma unroll
             for (int x = 0; x < VEC; ++x) c = fmaf(al[x], zj[x], c);
-            t2 = (pow2 ? group_sum_pow2(c, lm.lph) : group_sum_any(c, lm.head_first, lm.lph)) * kLog2e;
+            t2 = f256::score_log2(pow2 ? group_sum_pow2(c, lm.lph) : group_sum_any(c, lm.head_first, lm.lph));
         }
     };
     // dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j

@@ -235,6 +235,15 @@ struct Tabs {
 
 __device__ inline float leaky2(float u, float slope) { return u > 0.f ? u : slope * u; }
 
+// t_j in log2 units, rounded before it meets s_i in the backward kernels (never one multiply-add with the sum
+// that follows): the sum's sign chooses the slope, and it has to come out alike in every kernel.  A score of
+// exactly zero, s_i = -t_j, then is one here as well.
+__device__ inline float score_log2(float t)
+{
+#pragma clang fp contract(off)
+    return t * kLog2e;
+}
+
 // ------------------------------------------------------------------ forward
 
 struct FwdP {
@@ -555,12 +564,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         Row4<T>::unpack(load_lane<T, PAD>(static_cast<const T*>(tabs.Z[q]) + (int64_t)j * ld, foff, on), zj);
         float t2;
         if (tabs.t[q]) {
-            t2 = tabs.t[q][(int64_t)j * ldh + h] * kLog2e;
+            t2 = score_log2(tabs.t[q][(int64_t)j * ldh + h]);
         } else {   // t_j = <a_l, z_j> from the row this wavefront owns
             float c = al[0] * zj[0];
 #pragma unroll
             for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
-            t2 = group_all<LPH, OpSum>(c) * kLog2e;
+            t2 = score_log2(group_all<LPH, OpSum>(c));
         }
         const int32_t* ip = tabs.t_indptr[q];
         const int32_t* idx = tabs.t_indices[q];
@@ -757,14 +766,14 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
             t2[u] = 0.f;
             if (have[u]) {
                 if (s_t[q[u]]) {
-                    t2[u] = s_t[q[u]][(int64_t)j[u] * ldh + h] * kLog2e;
+                    t2[u] = score_log2(s_t[q[u]][(int64_t)j[u] * ldh + h]);
                 } else {   // t_j = <a_l, z_j> from the row this wavefront holds
                     float zj[4];
                     Row4<T>::unpack(zr[u], zj);
                     float c = al[0] * zj[0];
 #pragma unroll
                     for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
-                    t2[u] = group_all<LPH, OpSum>(c) * kLog2e;
+                    t2[u] = score_log2(group_all<LPH, OpSum>(c));
                 }
             }
         });
@@ -994,7 +1003,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
                 });
             }
             if (valid && s_t[my_q]) t_mine = s_t[my_q][(int64_t)(my_id & mask) * ldh + h];
-            const float u2 = rec.x + t_mine * kLog2e;
+            const float u2 = rec.x + score_log2(t_mine);
             const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
             const float de = alpha * (c_mine - rec.z);
             const float du = u2 > 0.f ? de : a.slope * de;

@@ -36,6 +36,7 @@ using f256::leaky2;
 using f256::OpMax;
 using f256::OpSum;
 using f256::Row4;
+using f256::score_log2;
 using f256::static_for;
 using f256::Tabs;
 
@@ -333,12 +334,12 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
         p.own_only(zj);
         float t2;
         if (tabs.t[q]) {
-            t2 = tabs.t[q][(int64_t)j * a.ldh + p.h] * kLog2e;
+            t2 = score_log2(tabs.t[q][(int64_t)j * a.ldh + p.h]);
         } else {   // t_j = <a_l, z_j>
             float c = al[0] * zj[0];
 #pragma unroll
             for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
-            t2 = group_all<LPH, OpSum>(c) * kLog2e;
+            t2 = score_log2(group_all<LPH, OpSum>(c));
         }
         const int32_t* idx = tabs.t_indices[q];
         const int beg = tabs.t_indptr[q][j], end = tabs.t_indptr[q][j + 1];
@@ -550,7 +551,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
                 for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
                 c = group_all<LPH, OpSum>(c);
                 if (mine && s_t[m0.q]) c = s_t[m0.q][(int64_t)m0.j * a.ldh + p.h];
-                t2 = c * kLog2e;
+                t2 = score_log2(c);
             }
             float c_mine = 0.f;
             static_for<B>([&](auto kk) {

@@ -1,12 +1,13 @@
-"""Last bits inside a head: lanes that hold one value of a head agree on it, and the source score halves
-that the kernels form in flight are those of sar_gat_scores."""
+"""Last bits inside a head: lanes that hold one value of a head agree on it, the source score halves that the
+kernels form in flight are those of sar_gat_scores, and a score of exactly zero is one in every kernel."""
 import numpy as np
 import pytest
 import torch
 
+from oracle import sar_oracle as orc
 from paper_2111_06483_amd import sar
 from tests import gpu_util as gu
-from tests.helpers import tiny_graph
+from tests.helpers import rel_err, tiny_graph
 
 pytestmark = pytest.mark.gpu
 SLOPE = 0.2
@@ -21,9 +22,10 @@ def blocks_and_parameters(H, D, flags=0):
     more = np.flatnonzero(part == 0)[rng.integers(0, 3, 2_000)]
     src, dst = np.concatenate([src, rng.integers(0, 1_500, 2_000)]), np.concatenate([dst, more])
     b = gu.build_blocks(src, dst, part, 2, 0, flags=sar.SAR_BUILD_TRANSPOSE | sar.SAR_BUILD_FUSED | flags)
+    want_b, _ = orc.build_blocks(src, dst, part, 2, 0)
     bound = np.sqrt(6.0 / (D + 1))
     a_l, a_r = (torch.from_numpy(rng.uniform(-bound, bound, (H, D)).astype(np.float32)).cuda() for _ in range(2))
-    return rng, b, a_l, a_r
+    return rng, b, want_b, a_l, a_r
 
 
 # 16, 32 and 64 lanes of 4 values, whole and ragged heads; the last lane of a ragged head opens a quad (33, 49),
@@ -34,7 +36,7 @@ def blocks_and_parameters(H, D, flags=0):
 @pytest.mark.parametrize("batched", [False, True])
 def test_lanes_of_a_head_agree(H, D, dtype, batched):
     """Rows and parameters that are constant along a head give results that are, bit for bit."""
-    rng, b, a_l, a_r = blocks_and_parameters(H, D)
+    rng, b, _, a_l, a_r = blocks_and_parameters(H, D)
     a_l = a_l[:, :1].expand(H, D).contiguous()
     row = lambda n: torch.from_numpy(rng.standard_normal((n, H, 1)).astype(np.float32)).to(dtype).cuda().expand(n, H, D).contiguous()
     Zs, G = [row(b.n_src(q)) for q in range(2)], row(b.n_dst)
@@ -55,7 +57,7 @@ def test_lanes_of_a_head_agree(H, D, dtype, batched):
 def test_scores_in_flight_are_those_of_the_scores_call(dtype, H, D, batched, singles):
     """With the same bits in t_j, shipped or formed in flight, every result but the atomically summed one has
     the same bits: the log-sum-exps, the errors and their score gradients take each edge's coefficient."""
-    rng, b, a_l, a_r = blocks_and_parameters(H, D, sar.SAR_BUILD_SINGLES if singles else sar.SAR_BUILD_NO_SINGLES)
+    rng, b, _, a_l, a_r = blocks_and_parameters(H, D, sar.SAR_BUILD_SINGLES if singles else sar.SAR_BUILD_NO_SINGLES)
     row = lambda n: torch.from_numpy(rng.standard_normal((n, H, D)).astype(np.float32)).to(dtype).cuda()
     Zs, G = [row(b.n_src(q)) for q in range(2)], row(b.n_dst)
     fwd = gu.gat_fwd_all if batched else gu.gat_fwd_stream
@@ -66,4 +68,38 @@ def test_scores_in_flight_are_those_of_the_scores_call(dtype, H, D, batched, sin
     for q in range(2):
         assert torch.equal(g[0].dts[q], g[1].dts[q]), q
         assert torch.equal(g[0].dZs[q], g[1].dZs[q]), q
+    b.close()
+
+
+# wide, few-edge and single-edge sources of every kernel family of the backward pass
+@pytest.mark.parametrize("dtype,H,D", [(torch.float32, 4, 64), (torch.bfloat16, 8, 32), (torch.float32, 2, 100),
+                                       (torch.bfloat16, 2, 128), (torch.float32, 4, 16), (torch.float32, 1, 47),
+                                       (torch.bfloat16, 2, 50), (torch.float32, 2, 3)])
+@pytest.mark.parametrize("batched,singles", [(False, False), (True, False), (True, True)])
+def test_a_score_of_exactly_zero_takes_the_slope(dtype, H, D, batched, singles):
+    """s_i = -t_j, bit for bit, for one in-edge of every destination.  (The derivative at zero is the slope's, the
+    oracle's too; no other score of these graphs is within rounding of zero, or the comparison would fail.)"""
+    rng, b, want_b, a_l, a_r = blocks_and_parameters(H, D, sar.SAR_BUILD_SINGLES if singles else sar.SAR_BUILD_NO_SINGLES)
+    row = lambda n: torch.from_numpy(rng.standard_normal((n, H, D)).astype(np.float32)).to(dtype).cuda()
+    Zs, G = [row(b.n_src(q)) for q in range(2)], row(b.n_dst)
+    s, ts = gu.gat_scores(Zs[0], Zs, a_l, a_r)
+    tied = 0
+    for q in (1, 0):                      # the last in-edge of every block, block 0's where a row has both
+        has = np.diff(want_b[q].indptr) > 0
+        last = want_b[q].indices[want_b[q].indptr[1:][has] - 1]
+        s[torch.from_numpy(has).cuda()] = -ts[q][torch.from_numpy(last).long().cuda()]
+        tied += has.sum()
+    assert tied > b.n_dst / 2
+    L, out = torch.empty((b.n_dst, H), device="cuda"), torch.empty((b.n_dst, H, D), dtype=dtype, device="cuda")
+    sar.sar_gat_fwd_all(b, Zs, s, ts, a_l, SLOPE, out, L)
+    fw = gu.GatOut(out, L, s, ts)
+    f64 = gu.host
+    want = orc.gat_bwd(want_b, f64(Zs[0]), [f64(z) for z in Zs], f64(G), f64(a_l), f64(a_r), SLOPE,
+                       orc.GatForward(f64(out), f64(L), f64(s), [f64(t) for t in ts]))
+    got = gu.gat_bwd(b, Zs[0], Zs, G, a_l, a_r, SLOPE, fw, batched)
+    tol = 1e-4 if dtype == torch.float32 else 2e-2
+    assert rel_err(f64(got.ds), want.ds) < 1e-4
+    for q in range(2):
+        assert rel_err(f64(got.dts[q]), want.dt[q]) < 1e-4, q
+        assert rel_err(f64(got.dZs[q]), want.dZs[q]) < tol, q
     b.close()
