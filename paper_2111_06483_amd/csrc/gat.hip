@@ -622,6 +622,14 @@ struct NodeLanes {
     static __device__ inline void narrow(bf16_t* p, float v) { p->bits = (uint16_t)f32_to_bf16_rne(v); }
 };
 
+// a0 z0 + a1 z1 + a2 z2 with every product rounded before it is added.
+__device__ inline float sum_of_three(const float* a, const float* z)
+{
+#pragma clang fp contract(off)
+    const float p0 = a[0] * z[0], p1 = a[1] * z[1], p2 = a[2] * z[2];
+    return p0 + p1 + p2;
+}
+
 // score[v,h] = <a[h], Z[v,h]>; one lane group per (node, head).  A second vector / output pair may
 // ride along (the two halves of the attention score from one pass over Z); avec2 = null: only the first.
 template <typename T, int VEC, int LPH, bool RAG>
@@ -658,6 +666,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__
         for (int x = 0; x < VEC; ++x) {
             c = fmaf(av[x], z[x], c);
             c2 = fmaf(av2[x], z[x], c2);
+        }
+        if constexpr (RAG && LPH == 1) {
+            if (D == 3) {                        // the aggregation kernels move such heads value by value
+                c = sum_of_three(av, z);
+                c2 = sum_of_three(av2, z);
+            }
         }
         c = in_order ? lm.head_sum_in_order(c) : lm.head_sum(c);
         if (avec2) c2 = in_order ? lm.head_sum_in_order(c2) : lm.head_sum(c2);

@@ -52,7 +52,7 @@ def test_lanes_of_a_head_agree(H, D, dtype, batched):
                                        (torch.float32, 8, 32), (torch.float32, 4, 16), (torch.float32, 8, 8)]
                          + [(dt, h, d) for dt in (torch.float32, torch.bfloat16)
                             for h, d in [(3, 33), (1, 34), (1, 47), (2, 50), (1, 63), (1, 66), (1, 126), (3, 23), (7, 9),
-                                         (2, 5)]])
+                                         (2, 5), (2, 3), (3, 2), (5, 1)]])
 @pytest.mark.parametrize("batched,singles", [(False, False), (True, False), (True, True)])
 def test_scores_in_flight_are_those_of_the_scores_call(dtype, H, D, batched, singles):
     """With the same bits in t_j, shipped or formed in flight, every result but the atomically summed one has
