@@ -664,6 +664,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__
         float c = 0.f, c2 = 0.f;
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
+            z[x] = lm.owns(x) ? z[x] : 0.f;      // not only a: an infinity the lane before owns is not 0 x inf here
             c = fmaf(av[x], z[x], c);
             c2 = fmaf(av2[x], z[x], c2);
         }

@@ -131,6 +131,7 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
                 constexpr int K = decltype(kk)::value;
                 float v[4];
                 Row4<T>::unpack(raw[K], v);
+                p.own_only(v);          // not only a_l: 0 x inf would be NaN where the lane before has inf
                 float c = al[0] * v[0];
 #pragma unroll
                 for (int x = 1; x < 4; ++x) c = fmaf(al[x], v[x], c);

@@ -13,14 +13,18 @@ pytestmark = pytest.mark.gpu
 SLOPE = 0.2
 
 
-def blocks_and_parameters(H, D, flags=0):
-    """Rows of 0 to some hundreds of edges; sources of one edge, of few and of many."""
+def blocks_and_parameters(H, D, flags=0, drop=None):
+    """Rows of 0 to some hundreds of edges; sources of one edge, of few and of many.  drop: leave out the edges of
+    this source of block 0."""
     rng = np.random.default_rng(H * 1000 + D)
     src, dst, part = tiny_graph(rng, 1_500, 12_000, 2, simple=False)
     hub = rng.random(src.size) < 0.3
     src, dst = np.where(hub, src % 40, src), np.where(hub, dst, dst)
     more = np.flatnonzero(part == 0)[rng.integers(0, 3, 2_000)]
     src, dst = np.concatenate([src, rng.integers(0, 1_500, 2_000)]), np.concatenate([dst, more])
+    if drop is not None:
+        keep = src != np.flatnonzero(part == 0)[drop]
+        src, dst = src[keep], dst[keep]
     b = gu.build_blocks(src, dst, part, 2, 0, flags=sar.SAR_BUILD_TRANSPOSE | sar.SAR_BUILD_FUSED | flags)
     want_b, _ = orc.build_blocks(src, dst, part, 2, 0)
     bound = np.sqrt(6.0 / (D + 1))
@@ -103,3 +107,33 @@ def test_a_score_of_exactly_zero_takes_the_slope(dtype, H, D, batched, singles):
         assert rel_err(f64(got.dts[q]), want.dt[q]) < 1e-4, q
         assert rel_err(f64(got.dZs[q]), want.dZs[q]) < tol, q
     b.close()
+
+
+# the infinity is a value that the last two lanes of a head both hold
+@pytest.mark.parametrize("H,D,at", [(1, 47, 43), (2, 50, 46), (1, 33, 30), (7, 9, 7), (2, 5, 1)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("fly", [False, True])
+def test_a_score_of_minus_infinity_weighs_nothing(H, D, at, dtype, batched, fly):
+    """A source whose score is -inf has weight zero: it spoils the column that holds the infinity (0 x inf) in the
+    rows that cite it and nothing else."""
+    rng, b, want_b, a_l, a_r = blocks_and_parameters(H, D)
+    _, without, _, _, _ = blocks_and_parameters(H, D, drop=7)
+    Zs = [torch.from_numpy(rng.standard_normal((b.n_src(q), H, D)).astype(np.float32)).to(dtype).cuda() for q in range(2)]
+    Zs[0][7, 0, at] = -np.inf * np.sign(a_l[0, at].item())
+    s, ts = gu.gat_scores(torch.zeros_like(Zs[0]), Zs, a_l, a_r)
+    assert ts[0][7, 0] == -np.inf
+    fwd = gu.gat_fwd_all if batched else gu.gat_fwd_stream
+    got, want = (fwd(h, torch.zeros_like(Zs[0]), Zs, a_l, a_r, SLOPE, fly=fly) for h in (b, without))
+    cited = torch.from_numpy(want_b[0].t_indices[want_b[0].t_indptr[7]:want_b[0].t_indptr[8]]).long().cuda()
+    others = torch.ones(b.n_dst, H, D, dtype=torch.bool, device="cuda")
+    others[cited, 0, at] = False
+    assert cited.numel() and got.out[cited, 0, at].isnan().all()
+    rest = got.out[:, 1:][cited] - want.out[:, 1:][cited]      # the other heads still weigh this source
+    others[cited, 1:] = False
+    tol = 1e-5 if dtype == torch.float32 else 1e-2
+    assert torch.isfinite(rest).all()
+    assert torch.allclose(got.out[others].float(), want.out[others].float(), rtol=tol, atol=tol)
+    assert torch.allclose(got.L[:, 0], want.L[:, 0], rtol=1e-5, atol=1e-5)
+    b.close()
+    without.close()
