@@ -609,13 +609,16 @@ int check_row_shape(int dtype, int F)
 
 // A wavefront covers 64 lane pieces of a row (1024 bytes; less where the row is so narrow that
 // lanes have to move 8, 4 or 2 bytes); wider rows are processed as several launches over column
-// ranges of about the same width, each seeing its slice of every row through the row stride.
+// ranges of about the same width, each seeing its slice of every row through the row stride.  No launch
+// is narrower than a piece: its one lane would reach back into the columns of the launch before it.  What is
+// left behind the last whole range (fp32 F = 16129: one value) takes a piece from that range instead.
 struct ColumnChunks {
     int n, width;   // launches and values per launch (the last launch may be narrower)
     size_t fb;
     int piece;      // values per lane: 16 bytes' worth; rows that are narrower, the largest piece that divides them
-    int first(int c) const { return c * width; }
-    int count(int c, int F) const { return std::min(width, F - c * width); }
+    int lent;       // values the last launch takes over from the one before it: a piece or none
+    int first(int c) const { return c * width - (c == n - 1 ? lent : 0); }
+    int count(int c, int F) const { return (c == n - 1 ? F : first(c + 1)) - first(c); }
 };
 
 ColumnChunks column_chunks(int dtype, int F)
@@ -627,6 +630,7 @@ ColumnChunks column_chunks(int dtype, int F)
     c.n = (F + 64 * c.piece - 1) / (64 * c.piece);
     c.width = ((F + c.n - 1) / c.n + c.piece - 1) / c.piece * c.piece;
     c.n = (F + c.width - 1) / c.width;
+    c.lent = c.n > 1 && F - (c.n - 1) * c.width < c.piece ? c.piece : 0;
     return c;
 }
 

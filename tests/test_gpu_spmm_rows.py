@@ -38,3 +38,27 @@ def test_rows(F, dtype, E):
             for got in (dZs[q], dZb[q]):
                 assert rel_err(f64(got), want_d[q][keep]) < tol, q
         b.close()
+
+
+# rows wider than a wavefront in launches of even width, the last of which would be left with one to three (fp32) or
+# one to seven (bf16) values, or just has a piece
+@pytest.mark.parametrize("dtype,F", [(torch.float32, 16129), (torch.float32, 16130), (torch.float32, 16131),
+                                     (torch.float32, 16132), (torch.float32, 16385), (torch.bfloat16, 32257),
+                                     (torch.bfloat16, 32263), (torch.bfloat16, 32264)])
+def test_last_column_range(dtype, F):
+    rng = np.random.default_rng(F)
+    src, dst, part = tiny_graph(rng, 60, 400, 2, simple=False)
+    want_b, _ = orc.build_blocks(src, dst, part, 2, 1)
+    b = gu.build_blocks(src, dst, part, 2, 1)
+    row = lambda n: torch.from_numpy(rng.standard_normal((n, F)).astype(np.float32)).to(dtype).cuda()
+    Zs, G = [row(w.n_src) for w in want_b], row(b.n_dst)
+    want = orc.spmm(want_b, [f64(z) for z in Zs], True)
+    tol = 1e-5 if dtype == torch.float32 else 1e-2
+    assert rel_err(f64(gu.spmm_stream(b, Zs, True)), want) < tol
+    assert rel_err(f64(gu.spmm_all(b, Zs, True)), want) < tol
+    want_d = orc.spmm_bwd(want_b, f64(G), True)
+    dZs = [torch.full_like(z, float("nan")) for z in Zs]
+    sar.sar_spmm_bwd_all(b, G, True, dZs)
+    for q in range(2):
+        assert rel_err(f64(dZs[q]), want_d[q]) < tol, q
+    b.close()
