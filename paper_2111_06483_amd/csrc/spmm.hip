@@ -85,19 +85,28 @@ struct RowLanes {
             Vec<T>::store(p, v);
         }
     }
-    static __device__ inline void load_acc(const float* p, float (&v)[VEC])
+    // p[x] += v[x], p being this lane's place in an fp32 row.  The last lane of a ragged row leaves out the values
+    // it shares with the lane before it: whether that lane has stored them when this one loads is not fixed.
+    __device__ inline void add_to(float* p, const float (&v)[VEC]) const
     {
-        if constexpr (RAG)
-            __builtin_memcpy(v, p, sizeof(v));
-        else
-            load_f32<VEC>(p, v);
-    }
-    static __device__ inline void store_acc(float* p, const float (&v)[VEC])
-    {
-        if constexpr (RAG)
-            __builtin_memcpy(p, v, sizeof(v));
-        else
-            store_f32<VEC>(p, v);
+        const int dup = RAG ? gl * VEC - off : 0;
+        if (dup == 0) {
+            float cur[VEC];
+            if constexpr (RAG)
+                __builtin_memcpy(cur, p, sizeof(cur));
+            else
+                load_f32<VEC>(p, cur);
+#pragma unroll
+            for (int x = 0; x < VEC; ++x) cur[x] += v[x];
+            if constexpr (RAG)
+                __builtin_memcpy(p, cur, sizeof(cur));
+            else
+                store_f32<VEC>(p, cur);
+        } else {
+#pragma unroll
+            for (int x = 1; x < VEC; ++x)
+                if (x >= dup) p[x] += v[x];
+        }
     }
 };
 
@@ -191,11 +200,7 @@ __device__ inline void finish_row(const float (&acc)[Vec<T>::N], const SpmmArgs&
     }
     const int64_t o = row * a.ld + lm.off;
     if constexpr (M == Mode::kBlock) {
-        float cur[VEC];
-        lm.load_acc(a.acc + o, cur);
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) cur[x] += acc[x];
-        lm.store_acc(a.acc + o, cur);
+        lm.add_to(a.acc + o, acc);
     } else {
         float v[VEC];
         float sc = 1.f;
@@ -464,11 +469,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllT
             }
             const int64_t o = (int64_t)m0.jo * a.ld + lm.off;
             if constexpr (M == Mode::kBlock) {
-                float cur[VEC];
-                lm.load_acc(a.acc + o, cur);
-#pragma unroll
-                for (int x = 0; x < VEC; ++x) cur[x] += acc[x];
-                lm.store_acc(a.acc + o, cur);
+                lm.add_to(a.acc + o, acc);
             } else {
                 lm.store(static_cast<T*>(ALLB ? s_out[m0.q] : a.out) + o, acc);
             }
