@@ -509,10 +509,11 @@ __global__ __launch_bounds__(256) void k_error_add(const T* __restrict__ Eq, con
     }
 }
 
-// Runs `...` with kG bound to the lanes of a row and kR to whether its last lane is shifted back.
-#define SAR_DISPATCH_LANES(T, F, ...)                                                          \
+// Runs `...` with kG bound to the lanes of a row and kR to whether its accesses are the unaligned ones: the
+// last lane is shifted back, or (a whole range of a row that is itself ragged) rows start anywhere.
+#define SAR_DISPATCH_LANES(T, F, ld, ...)                                                      \
     do {                                                                                       \
-        const bool ragged_ = (F) % Vec<T>::N != 0;                                             \
+        const bool ragged_ = (F) % Vec<T>::N != 0 || (ld) % Vec<T>::N != 0;                    \
         switch (lanes_for((F), Vec<T>::N)) {                                                   \
             case 4: { constexpr int kG = 4; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;         \
             case 8: { constexpr int kG = 8; SAR_RAGGED_OR_NOT(T, __VA_ARGS__); } break;         \
@@ -553,7 +554,7 @@ int launch_spmm(SpmmArgs a, const PtrTab& tab, int P, int64_t n_wide, hipStream_
     if constexpr (M != Mode::kAll) {
         const int64_t few = first_few<T>(a, n_wide), n = a.n_rows - few;
         if (n > 0) {
-            SAR_DISPATCH_LANES(T, a.F, {
+            SAR_DISPATCH_LANES(T, a.F, a.ld, {
                 auto fn = k_rows_few<T, (kG <= 16 ? kG : 16), M, false, kR>;
                 static const int resident = resident_workgroups(fn);
                 fn<<<few_grid<T>(a, n, resident), kGatherThreads, 0, st>>>(a, BwdAllTabs{}, few, a.n_rows);
@@ -566,7 +567,7 @@ int launch_spmm(SpmmArgs a, const PtrTab& tab, int P, int64_t n_wide, hipStream_
     }
     // every workgroup of the persistent grid has to start at once: with 2048 of them and room for 1792,
     // the backward pass over rows of 512 bf16 values took 1580 us instead of 1149
-    SAR_DISPATCH_LANES(T, a.F, {
+    SAR_DISPATCH_LANES(T, a.F, a.ld, {
         auto fn = k_spmm<T, kG, M, kR>;
         static const int resident = resident_workgroups(fn);
         fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(a, tab, P);
@@ -581,7 +582,7 @@ int launch_spmm_bwd_all(SpmmArgs a, const BwdAllTabs& tabs, int64_t n_wide, hipS
     if (a.n_rows == 0) return SAR_OK;
     const int64_t few = first_few<T>(a, n_wide), n = a.n_rows - few;
     if (n > 0) {
-        SAR_DISPATCH_LANES(T, a.F, {
+        SAR_DISPATCH_LANES(T, a.F, a.ld, {
             auto fn = k_rows_few<T, (kG <= 16 ? kG : 16), Mode::kBackward, true, kR>;
             static const int resident = resident_workgroups(fn);
             fn<<<few_grid<T>(a, n, resident), kGatherThreads, 0, st>>>(a, tabs, few, a.n_rows);
@@ -591,7 +592,7 @@ int launch_spmm_bwd_all(SpmmArgs a, const BwdAllTabs& tabs, int64_t n_wide, hipS
         a.n_long = std::min(a.n_long, few);
         if (few == 0) return SAR_OK;
     }
-    SAR_DISPATCH_LANES(T, a.F, {
+    SAR_DISPATCH_LANES(T, a.F, a.ld, {
         auto fn = k_spmm_bwd_all<T, kG, kR>;
         static const int resident = resident_workgroups(fn);
         fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(a, tabs);
