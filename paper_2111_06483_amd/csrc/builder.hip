@@ -107,8 +107,8 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(const int32_t* in, int64
 // by batch) would pay the driver for mapping and clearing them every time: up to 20 ms of a 25 ms
 // call where much memory had been freed before.  What a builder call or sar_blocks_free gives up is
 // therefore kept for the next call, at most kPoolMost bytes per device and nothing larger than a
-// quarter of that, and all of it is given back when the last handle on the device is freed (or
-// when the device runs out of memory).  Nothing enters the pool before the work that used it is done.
+// quarter of that, and all of it is given back when the last handle on the device is freed or when an
+// allocation made here fails.  Nothing enters the pool before the work that used it is done.
 class Pool {
 public:
     static constexpr size_t kPoolMost = (size_t)1 << 30;
@@ -141,9 +141,12 @@ public:
             std::lock_guard<std::mutex> lock(m_);
             auto& d = devices_[dev];
             if (d.bytes + size <= kPoolMost) {
-                d.idle.emplace(size, p);
-                d.bytes += size;
-                return;
+                try {
+                    d.idle.emplace(size, p);
+                    d.bytes += size;
+                    return;
+                } catch (const std::bad_alloc&) {   // no host memory for the entry: not kept
+                }
             }
         }
         (void)hipFree(p);
@@ -1720,10 +1723,13 @@ extern "C" int sar_blocks_build(const void* src, const void* dst, int idx_bytes,
     h->P = P;
     h->flags = flags;
     hipStream_t st = sar::as_stream(stream);
-    DeviceTemps tmp(st, h->device);
-    PairScratch scratch;
-    int rc = build_from_edges(h, src, dst, idx_bytes, E, part, N, P, p, tmp, scratch, st);
-    if (rc == SAR_OK) rc = derive(h, tmp, scratch, st);
+    auto body = [&]() -> int {       // the scratch goes back before a failed call's handle, the last one maybe, does
+        DeviceTemps tmp(st, h->device);
+        PairScratch scratch;
+        SAR_TRY(build_from_edges(h, src, dst, idx_bytes, E, part, N, P, p, tmp, scratch, st));
+        return derive(h, tmp, scratch, st);
+    };
+    int rc = body();
     if (rc != SAR_OK) {
         destroy(h);
         return rc;
