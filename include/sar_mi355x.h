@@ -227,8 +227,14 @@ int sar_blocks_singles(const sar_blocks_t* b, int64_t* n, const int32_t** dst, c
 /* *deg = device int32 [n_dst]: total in-degree |N(i)| over all blocks (Eq. 2). */
 int sar_blocks_degree(const sar_blocks_t* b, const int32_t** deg);
 
-/* Free the handle and everything the library allocated for it. */
+/* Free the handle and give up everything the library allocated for it.  While other handles live on
+ * the device the library keeps up to 1 GiB of what freed handles and finished builder calls gave
+ * up (in pieces of at most 256 MiB) for the next builder call; the last handle's end frees all of it. */
 int sar_blocks_free(sar_blocks_t* b);
+
+/* Free the device memory the library keeps for coming builder calls, on every device, for a program whose
+ * own allocations need it now.  Living handles are untouched.  Not during stream capture (it calls hipFree). */
+int sar_release_memory(void);
 
 /* ------------------------------------------------------- Eq. 2: sum / mean
  * Alg. 1 with m_{j->i} = z_j:  Acc_i += sum over the block's edges of z_j.

@@ -107,8 +107,9 @@ __global__ __launch_bounds__(kThreads) void k_tile_scan(const int32_t* in, int64
 // by batch) would pay the driver for mapping and clearing them every time: up to 20 ms of a 25 ms
 // call where much memory had been freed before.  What a builder call or sar_blocks_free gives up is
 // therefore kept for the next call, at most kPoolMost bytes per device and nothing larger than a
-// quarter of that, and all of it is given back when the last handle on the device is freed or when an
-// allocation made here fails.  Nothing enters the pool before the work that used it is done.
+// quarter of that, and all of it is given back when the last handle on the device is freed, when an
+// allocation made here fails, or by sar_release_memory.  Nothing enters the pool before the work that used it
+// is done.
 class Pool {
 public:
     static constexpr size_t kPoolMost = (size_t)1 << 30;
@@ -157,6 +158,11 @@ public:
         auto& d = devices_[dev];
         d.handles += by;
         if (d.handles <= 0) release(d);
+    }
+    void release_all()
+    {
+        std::lock_guard<std::mutex> lock(m_);
+        for (auto& d : devices_) release(d.second);
     }
 
 private:
@@ -1864,6 +1870,12 @@ extern "C" int sar_blocks_degree(const sar_blocks_t* b, const int32_t** deg)
 extern "C" int sar_blocks_free(sar_blocks_t* b)
 {
     destroy(b);
+    return SAR_OK;
+}
+
+extern "C" int sar_release_memory(void)
+{
+    pool().release_all();
     return SAR_OK;
 }
 

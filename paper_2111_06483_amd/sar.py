@@ -80,7 +80,7 @@ _SIGNATURES = {
     "sar_last_error": "", "sar_version": "",
     "sar_blocks_build": "ppilpliiipp", "sar_blocks_wrap": "ilpppipp", "sar_blocks_subset": "pplipp",
     "sar_blocks_info": "ppp", "sar_blocks_get": "pip", "sar_blocks_singles": "pppppp", "sar_blocks_degree": "pp",
-    "sar_blocks_free": "p",
+    "sar_blocks_free": "p", "sar_release_memory": "",
     "sar_spmm_block": "pipiipp", "sar_spmm_end": "pippipilip", "sar_spmm_all": "ppiiipipp", "sar_act_bwd": "ppipilp",
     "sar_spmm_bwd_block": "pipiiipp", "sar_spmm_bwd_all": "ppiiipp", "sar_error_add": "ppipilip",
     "sar_gat_scores": "piliippp", "sar_gat_fwd_begin": "pppliip", "sar_gat_fwd_block": "pippppiiifpppp",
@@ -312,6 +312,11 @@ def sar_blocks_degree(b: Blocks) -> torch.Tensor:
     p = _vp(None)
     _check(lib().sar_blocks_degree(b.handle, ctypes.byref(p)))
     return device_array(p.value, b.n_dst)
+
+
+def sar_release_memory() -> None:
+    """Free the device memory the library keeps for coming builder calls."""
+    _check(lib().sar_release_memory())
 
 
 # -------------------------------------------------------------------- spmm

@@ -1,4 +1,4 @@
-"""Device memory that the library keeps between builder calls: bounded by the handles' life."""
+"""Device memory that the library keeps between builder calls: bounded by the handles' life, given back on request."""
 import gc
 
 import pytest
@@ -35,3 +35,17 @@ def test_a_failed_build_of_the_only_handle_keeps_nothing():
     with pytest.raises(sar.SarError):
         sar.sar_blocks_build(src, dst, part, 1, 0, sar.SAR_BUILD_TRANSPOSE)
     assert before - free_bytes() < 4 * MB
+
+
+def test_idle_memory_is_released_on_request():
+    src, dst, part = edges(8_000_000, 100_000)
+    no_other_handle()
+    small = sar.sar_blocks_build(src[:1000], dst[:1000], part, 1, 0, 0)
+    before = free_bytes()
+    sar.sar_blocks_build(src, dst, part, 1, 0, sar.SAR_BUILD_TRANSPOSE).close()
+    kept = before - free_bytes()
+    assert 32 * MB < kept <= 1024 * MB                   # the closed handle's arrays, while `small` lives
+    sar.sar_release_memory()
+    assert before - free_bytes() < 4 * MB
+    assert sar.sar_blocks_degree(small) is not None      # the living handle is untouched
+    small.close()
