@@ -855,23 +855,47 @@ __global__ __launch_bounds__(kThreads) void k_make_indptr(const int32_t* __restr
     }
 }
 
-// The groups of the listed buckets (those too large for k_bucket_finish), gridDim.y workgroups a bucket.
+// The groups of the listed buckets (those too large for k_bucket_finish).  A bucket is kSortShares shares, share
+// c holding the groups at places c, c + kSortShares ... (a run of neighbouring keys, often long together, falls
+// into different shares), and the workgroups take share after share from *next: a bucket's long groups may be
+// one or all of its groups, so a fixed deal of shares to workgroups leaves most of them idle (1000 rows of 30
+// thousand edges, one to a bucket: build 35.5 ms when workgroup (x, y) took share y of every 32nd bucket,
+// 7.9 ms now; 100 rows of 300 thousand 160 and 77 ms).  Every workgroup ends when the shares have been taken.
+constexpr int kSortShares = 16;
 __global__ __launch_bounds__(kThreads) void k_sort_buckets(const int32_t* __restrict__ off, int32_t* __restrict__ data,
                                                            int w, Deal deal, int64_t n_keys,
                                                            const int32_t* __restrict__ big_list,
-                                                           const int* __restrict__ big_count)
+                                                           const int* __restrict__ big_count, int* __restrict__ next)
 {
+    constexpr int kMostPlaces = (1 << kMaxBucketBits) / kSortShares;
     __shared__ int32_t buf[kLdsSort];
-    const int n_list = *big_count;
-    for (int i = blockIdx.x; i < n_list; i += gridDim.x) {
-        for (int k = blockIdx.y; k < (1 << w); k += gridDim.y) {
-            const int64_t key = deal.key_at(big_list[i], k);
+    __shared__ int32_t first[kMostPlaces], length[kMostPlaces];
+    __shared__ int share, n_groups;
+    const int n_shares = *big_count * kSortShares;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            share = atomicAdd(next, 1);
+            n_groups = 0;
+        }
+        __syncthreads();
+        if (share >= n_shares) break;
+        const int b = big_list[share / kSortShares];
+        for (int k = share % kSortShares + (int)threadIdx.x * kSortShares; k < (1 << w); k += kThreads * kSortShares) {
+            const int64_t key = deal.key_at(b, k);
             if (key >= n_keys) continue;
             const int beg = off[key], len = off[key + 1] - beg;
             if (len <= 1) continue;
-            int32_t* g = data + beg;
+            const int at = atomicAdd(&n_groups, 1);
+            first[at] = beg;
+            length[at] = len;
+        }
+        __syncthreads();
+        const int n = n_groups;
+        for (int i = 0; i < n; ++i) {
+            const int len = length[i];
+            int32_t* g = data + first[i];
             const bool in_lds = len <= kLdsSort;
-            __syncthreads();
             if (in_lds) {
                 for (int t = threadIdx.x; t < len; t += kThreads) buf[t] = g[t];
             }
@@ -883,6 +907,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_buckets(const int32_t* __rest
             if (in_lds) {
                 for (int t = threadIdx.x; t < len; t += kThreads) g[t] = buf[t];
             }
+            __syncthreads();
         }
     }
 }
@@ -1240,9 +1265,9 @@ int finish_buckets(const BucketPlan& plan, const PairT* pairs, const int32_t* co
                    int32_t base, int32_t* off, int32_t* values, DeviceTemps& tmp, hipStream_t st)
 {
     int32_t* list = nullptr;
-    SAR_TRY(tmp.alloc(&list, plan.n_buckets() + 1));
-    int* count = list + plan.n_buckets();
-    SAR_HIP(hipMemsetAsync(count, 0, sizeof(int), st));
+    SAR_TRY(tmp.alloc(&list, plan.n_buckets() + 2));
+    int* count = list + plan.n_buckets();                // buckets listed, and shares of them taken
+    SAR_HIP(hipMemsetAsync(count, 0, 2 * sizeof(int), st));
     SAR_HIP(hipMemsetAsync(off + n_keys, 0, sizeof(int32_t), st));
     const size_t slots = ((size_t)1 << plan.w) * sizeof(int), lds = slots + kBucketCap * sizeof(int32_t);
     const Deal deal{plan.nb};
@@ -1254,8 +1279,8 @@ int finish_buckets(const BucketPlan& plan, const PairT* pairs, const int32_t* co
     k_bucket_finish<PairT><<<(unsigned)plan.n_buckets(), kBucketThreads, lds, st>>>(
         pairs, counts, plan.n_tiles, plan.w, deal, n_keys, vbits, off, values, list, count);
     SAR_LAUNCH_CHECK();
-    k_sort_buckets<<<dim3((unsigned)std::min(plan.n_buckets(), 32), 16), kThreads, 0, st>>>(off, values, plan.w, deal, n_keys,
-                                                                                            list, count);
+    k_sort_buckets<<<(unsigned)std::min(plan.n_buckets() * kSortShares, 1024), kThreads, 0, st>>>(
+        off, values, plan.w, deal, n_keys, list, count, count + 1);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }

@@ -46,3 +46,16 @@ def test_row_lengths(transposed, n_extra, idx_dtype):
     again = gu.build_blocks(src, dst, part, P, 0, idx_dtype=idx_dtype)     # on memory the first one gave up
     check(again, want)
     check(sub, orc.subset_blocks(want, ids)[0])
+
+
+def test_many_rows_too_long_for_a_bucket():
+    """More shares of listed buckets than the sort has workgroups, one long row in each bucket."""
+    rng = np.random.default_rng(6)
+    N, rows, each = 40_000, 100, 11_000
+    part = np.zeros(N, dtype=np.int32)
+    dst = np.repeat(rng.permutation(N)[:rows], each)
+    src = rng.integers(0, N, dst.size)
+    want, _ = orc.build_blocks(src, dst, part, 1, 0)
+    h = gu.build_blocks(src, dst, part, 1, 0)
+    check(h, want)
+    h.close()
