@@ -8,6 +8,8 @@ from oracle import sar_oracle as orc
 from paper_2111_06483_amd import sar
 from tests import gpu_util as gu
 from tests.helpers import rel_err
+from tests.test_gpu_layers import EPS, mask_ambiguous
+from tests.test_gpu_parity import TOL, gat_case
 
 pytestmark = pytest.mark.gpu
 SLOPE = 0.2
@@ -48,6 +50,31 @@ def test_slots_pass(H, D, E, hubs, dtype, batched):
     tol = 1e-4 if dtype == torch.float32 else 2e-2
     assert rel_err(f64(fw.out), wf.out) < tol
     g = gu.gat_bwd(b, Zs[0], Zs, G, a_l, a_r, SLOPE, fw, batched, fly=True)
+    for q in range(3):
+        assert rel_err(f64(g.dZs[q]), wb.dZs[q]) < tol, q
+        assert rel_err(f64(g.dts[q]), wb.dt[q]) < tol, q
+    for name in ("ds", "dZdst", "da_l", "da_r"):
+        assert rel_err(f64(getattr(g, name)), getattr(wb, name)) < tol, name
+    b.close()
+
+
+@pytest.mark.parametrize("H,D", [(1, 47), (2, 50), (3, 33), (7, 9), (2, 5), (5, 40), (4, 16)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batched", [False, True])
+def test_slots_pass_with_relu(H, D, dtype, batched):
+    """Elements whose aggregate is within the forward pass's error of zero get no error (see mask_ambiguous)."""
+    tol = TOL[dtype]
+    b, want_b, deg, Zdst, Zs, a_l, a_r, G = gat_case(52, 3_000, 40_000, 3, 0, H, D, dtype)
+    wz = [f64(z) for z in Zs]
+    wf = orc.gat_fwd(want_b, f64(Zdst), wz, f64(a_l), f64(a_r), SLOPE)
+    G, frac = mask_ambiguous(G.cpu(), wf.out, EPS[dtype] * np.sqrt(np.mean(np.concatenate(wz) ** 2)))
+    assert frac < 0.1
+    G = G.cuda()
+    wb = orc.gat_bwd(want_b, f64(Zdst), wz, orc.act_bwd(wf.out, f64(G), orc.ACT_RELU), f64(a_l), f64(a_r), SLOPE, wf)
+    fwd = gu.gat_fwd_all if batched else gu.gat_fwd_stream
+    fw = fwd(b, Zdst, Zs, a_l, a_r, SLOPE, fly=True, act=sar.SAR_ACT_RELU)
+    assert rel_err(f64(fw.out), orc.act_fwd(wf.out, orc.ACT_RELU)) < tol
+    g = gu.gat_bwd(b, Zdst, Zs, G, a_l, a_r, SLOPE, fw, batched, fly=True, act=sar.SAR_ACT_RELU)
     for q in range(3):
         assert rel_err(f64(g.dZs[q]), wb.dZs[q]) < tol, q
         assert rel_err(f64(g.dts[q]), wb.dt[q]) < tol, q
