@@ -876,11 +876,19 @@ int pow2_at_least(int x)
 //           bound by memory, not by lanes, so they cost little;
 //   slots   they need half of the groups or fewer, or the head width is no multiple of 4, or a head
 //           is four lanes (gat_slots.h): the groups left over take other edges.
-//   generic heads of 1 to 3 values, bf16 heads of more than 256, and in the forward pass heads of 4 or 8
-//           values (one or two lanes of 16 bytes: 8 x 8 bf16 229 us against 391 with the four lanes of a
-//           slots head; the slots' batches pay again in the backward pass, 703 us against 834) and bf16
-//           layers whose heads would fall into launches of different sizes (5 x 40 as 3 + 2: 965 us
-//           against 819 in one generic launch).
+//   generic heads of 1 to 3 values and bf16 heads of more than 256; in the forward pass also (times in us with
+//           the generic kernel and with the others, on a share of 7.3M edges with 24 a row | 7.4M with 6 a row):
+//           - more than 4 heads of 4 or 8 values.  Two lanes of 16 bytes hold such a head where a slots head
+//             has four: fp32 16 x 4 390/730 | 970/1228, 8 x 8 401/445 | 1001/855; bf16 8 x 8 310/400 |
+//             978/772, 16 x 8 421/733 | 1061/1230.  With up to 4 heads the slots' longer batches win: fp32
+//             4 x 4 241/232 | 813/579, 4 x 8 283/257 | 870/598, bf16 1 x 8 274/166 | 913/551.
+//           - bf16 layers of up to 512 values whose heads would fall into launches of different sizes,
+//             while one generic launch serves them well: rows of up to 256 values (32 lanes, two edges at a time:
+//             9 x 24 755/1148 | 1451/2236, 5 x 40 855/1038 | 1525/2052, 3 x 80 1149/1219 | 1849/2363), heads of
+//             up to 32 values (25 x 16 1273/1699 | 1985/2907, 15 x 32 1449/1423 | 2245/2604) and layers that
+//             would be three launches or more (7 x 72 2168/2572 | 3178/4994, 9 x 48 1785/1807 | 3514/3525,
+//             but 5 x 80 2235/1878 | 3243/3670).  Two launches are faster for the rest: 7 x 48 1704/1257 |
+//             2526/2422, 3 x 96 2416/1303 | 3442/2419, 3 x 120 2887/1444 | 4003/2671, 5 x 64 1422/1148 | 2147/2195.
 // In the forward pass the padded kernel also takes launches that leave up to 5/8 of the lanes idle:
 // it waits for memory there either way (4 x 32 fp32 on 7.4M edges: 603 us padded, 608 us with two
 // slots), while the backward pass gains from the slots (4 x 32: 1.9 and 6.5% of the whole step in
@@ -899,9 +907,9 @@ bool generic_layer(int dtype, int H, int D, bool forward)
 {
     if (D < 4 || D > 256) return true;
     if (!forward) return false;
-    if (D == 4 || D == 8) return true;
+    if (D == 4 || D == 8) return H > 4;
     const int n = (H + lane_groups(D) - 1) / lane_groups(D);
-    return dtype == SAR_BF16 && D % 8 == 0 && H % n != 0 && H * D <= 512;
+    return dtype == SAR_BF16 && D % 8 == 0 && H % n != 0 && H * D <= 512 && (H * D <= 256 || D <= 32 || n > 2);
 }
 
 LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, bool forward)

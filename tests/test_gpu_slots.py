@@ -9,7 +9,7 @@ from paper_2111_06483_amd import sar
 from tests import gpu_util as gu
 from tests.helpers import rel_err
 from tests.test_gpu_layers import EPS, mask_ambiguous
-from tests.test_gpu_parity import TOL, gat_case
+from tests.test_gpu_parity import TOL, check_fwd, gat_case
 
 pytestmark = pytest.mark.gpu
 SLOPE = 0.2
@@ -80,4 +80,19 @@ def test_slots_pass_with_relu(H, D, dtype, batched):
         assert rel_err(f64(g.dts[q]), wb.dt[q]) < tol, q
     for name in ("ds", "dZdst", "da_l", "da_r"):
         assert rel_err(f64(getattr(g, name)), getattr(wb, name)) < tol, name
+    b.close()
+
+
+# both sides of the lines between the generic forward kernel and the others, where a case above has none
+@pytest.mark.parametrize("dtype,H,D", [(dt, h, d) for dt in (torch.float32, torch.bfloat16)
+                                       for h, d in [(4, 4), (5, 4), (4, 8), (5, 8), (1, 8), (3, 4)]]
+                         + [(torch.bfloat16, 3, 80), (torch.bfloat16, 3, 96), (torch.bfloat16, 9, 32),
+                            (torch.bfloat16, 7, 40), (torch.bfloat16, 5, 80), (torch.bfloat16, 5, 64)])
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("fly", [False, True])
+def test_forward_at_the_lines_of_the_generic_kernel(dtype, H, D, batched, fly):
+    b, want_b, deg, Zdst, Zs, a_l, a_r, _ = gat_case(53, 3_000, 40_000, 3, 0, H, D, dtype)
+    want = orc.gat_fwd(want_b, f64(Zdst), [f64(z) for z in Zs], f64(a_l), f64(a_r), SLOPE)
+    got = (gu.gat_fwd_all if batched else gu.gat_fwd_stream)(b, Zdst, Zs, a_l, a_r, SLOPE, fly=fly)
+    check_fwd(got, want, deg, dtype)
     b.close()
