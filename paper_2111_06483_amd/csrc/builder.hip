@@ -202,6 +202,7 @@ struct DeviceTemps {
     {
         void* p = nullptr;
         const size_t size = Pool::round(std::max<int64_t>(count, 1) * sizeof(T));
+        ptrs.reserve(ptrs.size() + 1);      // before there is anything to lose
         SAR_TRY(pool().take(dev, &p, size));
         ptrs.emplace_back(p, size);
         *out = static_cast<T*>(p);
@@ -1202,6 +1203,7 @@ int own(sar_blocks* h, T** out, int64_t count)
 {
     void* p = nullptr;
     const size_t size = Pool::round(std::max<int64_t>(count, 1) * sizeof(T));
+    h->owned.reserve(h->owned.size() + 1);
     SAR_TRY(pool().take(h->device, &p, size));
     h->owned.emplace_back(p, size);
     *out = static_cast<T*>(p);
@@ -1722,6 +1724,17 @@ int new_handle(sar_blocks** out)
     return SAR_OK;
 }
 
+// What fn returns; a host allocation that fails in it becomes an error code instead of an exception at the C boundary.
+template <typename Fn>
+int guarded(Fn&& fn)
+{
+    try {
+        return fn();
+    } catch (const std::bad_alloc&) {
+        return sar::fail(SAR_ERR_HIP, "out of host memory");
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -1750,7 +1763,7 @@ extern "C" int sar_blocks_build(const void* src, const void* dst, int idx_bytes,
     if (N >= ((int64_t)1 << 31))
         return sar::fail(SAR_ERR_UNSUPPORTED, "N must be below 2^31 (32-bit node ids inside the handle)");
     sar_blocks* h = nullptr;
-    SAR_TRY(new_handle(&h));
+    SAR_TRY(guarded([&] { return new_handle(&h); }));
     h->P = P;
     h->flags = flags;
     hipStream_t st = sar::as_stream(stream);
@@ -1760,7 +1773,7 @@ extern "C" int sar_blocks_build(const void* src, const void* dst, int idx_bytes,
         SAR_TRY(build_from_edges(h, src, dst, idx_bytes, E, part, N, P, p, tmp, scratch, st));
         return derive(h, tmp, scratch, st);
     };
-    int rc = body();
+    int rc = guarded(body);
     if (rc != SAR_OK) {
         destroy(h);
         return rc;
@@ -1790,12 +1803,12 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
     SAR_CHECK_ARG(n_dst < ((int64_t)1 << 31), "n_dst must be below 2^31");
     hipStream_t st = sar::as_stream(stream);
     sar_blocks* h = nullptr;
-    SAR_TRY(new_handle(&h));
+    SAR_TRY(guarded([&] { return new_handle(&h); }));
     h->P = P;
     h->n_dst = n_dst;
     h->flags = flags;
-    h->blk.resize(P);
     auto body = [&]() -> int {
+        h->blk.resize(P);
         DeviceTemps tmp(st, h->device);
         PairScratch scratch;
         int* err_d = nullptr;
@@ -1833,7 +1846,7 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
         SAR_TRY(check_err_flag(err_d, st));
         return derive(h, tmp, scratch, st);
     };
-    int rc = body();
+    int rc = guarded(body);
     if (rc != SAR_OK) {
         destroy(h);
         return rc;
@@ -1915,12 +1928,12 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
     SAR_CHECK_ARG((flags & ~kKnownFlags) == 0, "unknown flags 0x%x", flags);
     hipStream_t st = sar::as_stream(stream);
     sar_blocks* h = nullptr;
-    SAR_TRY(new_handle(&h));
+    SAR_TRY(guarded([&] { return new_handle(&h); }));
     h->P = b->P;
     h->n_dst = n_sub;
     h->flags = flags;
-    h->blk.resize(b->P);
     auto body = [&]() -> int {
+        h->blk.resize(b->P);
         DeviceTemps tmp(st, h->device);
         PairScratch scratch;
         const int P = b->P;
@@ -1970,7 +1983,7 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
         }
         return derive(h, tmp, scratch, st);
     };
-    int rc = body();
+    int rc = guarded(body);
     if (rc != SAR_OK) {
         destroy(h);
         return rc;
