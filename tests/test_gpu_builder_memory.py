@@ -24,7 +24,7 @@ def free_bytes():
 
 def no_other_handle():
     gc.collect()
-    assert not [o for o in gc.get_objects() if isinstance(o, sar.Blocks) and o._h is not None]
+    assert not [o for o in gc.get_objects() if type(o) is sar.Blocks and o._h is not None]
 
 
 def test_a_failed_build_of_the_only_handle_keeps_nothing():
