@@ -873,6 +873,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_buckets(const int32_t* __rest
     __shared__ int32_t first[kMostPlaces], length[kMostPlaces];
     __shared__ int share, n_groups;
     const int n_shares = *big_count * kSortShares;
+    if (n_shares == 0) return;       // the usual case: no atomics then
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
