@@ -32,16 +32,17 @@
  *     all accumulation is fp32.
  *   - a_r multiplies the destination's z_i and a_l the source's z_j: the vector
  *     a of Eq. 3 is [a_r ; a_l] in the order the equation writes z_i || z_j.
- *   - Shapes.  A wavefront covers a head with 64 lanes that each move the largest
- *     piece of 16, 8, 4 (or, for bf16, 2) bytes that divides the head: every head
- *     width is accepted as long as the head fits 64 such lanes (any D up to 256 that
- *     is a multiple of 4; else fp32: D <= 128 for even D, D <= 64 for odd D; bf16:
- *     D <= 128 for even D, D <= 64 for odd D).  A wider head returns
- *     SAR_ERR_UNSUPPORTED.  Rows of several heads are processed as several launches
- *     over groups of heads, rows of the sum/mean calls (any F) over column ranges.
- *     The fastest kernels take head widths that are a multiple of 4 in layers of
- *     1, 2, 4, 8 heads or a multiple thereof (4 x 64, 8 x 32, 4 x 32, 2 x 100, ...);
- *     which kernel a shape takes changes results by the order of fp32 sums only.
+ *   - Shapes.  The attention calls accept every head width D that 64 lanes cover when
+ *     each moves the largest piece of 16, 8, 4 (or, for bf16, 2) bytes that divides the
+ *     head: fp32 D <= 256 if D is a multiple of 4, <= 128 if even, <= 64 if odd; bf16
+ *     D <= 512 if a multiple of 8, <= 256 if of 4, <= 128 if even, <= 64 if odd.  A wider
+ *     head returns SAR_ERR_UNSUPPORTED (sar_gat_scores takes any).  Layers of more heads
+ *     than a wavefront has room for are processed as several launches over groups of
+ *     heads, rows of the sum/mean calls (any F) over column ranges.  Heads of 4 to 256
+ *     values of any width have kernels that give a head the power of two of lanes that
+ *     covers it, four values a lane: whole rows where the heads fill the wavefront, further
+ *     edges in the lanes they leave.  Which kernel a shape takes changes results by the
+ *     order of fp32 sums only.
  *   - Score halves of the sources.  Where a call forms t_j = <a_l, z_j> itself
  *     (tq NULL), every kernel that takes heads of at least 4 values four at a time
  *     adds in one order, forward and backward: along each four values, then pairs

@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
 // (ids in the order of degree), and a bucket of the 1024 most frequent rows of that graph holds half a
 // million pairs (641 us for one workgroup, and 14 ms to sort its rows).
 // What the kernels now take on those 15.2M edges: pairs to buckets 218 + 222 us from the edge list (the
-// gathers of the nodes' codes) and 30 + 196 us from the CSR, keys 31, finish 374 each; of the last,
+// gathers of the nodes' codes) and 48 + 194 us from the CSR, keys 31, finish 374 each; of the last,
 // 140 us are the few hundred rows of more than 256 values and the rest the stores of short runs.
 
 constexpr int kBucketThreads = 512;

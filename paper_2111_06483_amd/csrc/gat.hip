@@ -641,8 +641,9 @@ __global__ __launch_bounds__(kGatherThreads) void k_scores(const T* __restrict__
                                                            float* __restrict__ score2)
 {
     const NodeLanes<T, VEC, LPH, RAG> lm(H, D);
-    // A score's last bit decides on which side of LeakyReLU's kink an edge falls now and then, so heads of
-    // whole lanes that fill no power of two keep the order of addition that they have always had.
+    // Heads of whole lanes that fill no power of two add lane after lane, the others pairwise.  (A score's last
+    // bit decides on which side of LeakyReLU's kink an edge within rounding of zero falls: a shape's order of
+    // addition is not to change.)
     const bool in_order = !RAG && !is_pow2(D / VEC);
     const int writer = in_order ? D / VEC - 1 : 0;
     float av[VEC] = {}, av2[VEC] = {};
