@@ -1,6 +1,6 @@
 """Parity of the HIP path (through the C ABI) with the CPU oracle, element by element.
 
-Tolerances (the benchmark spec): bit-exact for the block index; tensor-scale relative
+Tolerances: bit-exact for the block index; tensor-scale relative
 error max|a-b|/max|b| <= 1e-4 for fp32 tensors; <= 2e-2 for bf16-stored
 tensors with fp32 accumulation.  The oracle always runs in fp64 on the same
 (already rounded) inputs.
