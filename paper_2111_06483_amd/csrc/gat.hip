@@ -877,19 +877,22 @@ int pow2_at_least(int x)
 //           bound by memory, not by lanes, so they cost little;
 //   slots   they need half of the groups or fewer, or the head width is no multiple of 4, or a head
 //           is four lanes (gat_slots.h): the groups left over take other edges.
-//   generic heads of 1 to 3 values and bf16 heads of more than 256; in the forward pass also (times in us with
-//           the generic kernel and with the others, on a share of 7.3M edges with 24 a row | 7.4M with 6 a row):
-//           - more than 4 heads of 4 or 8 values.  Two lanes of 16 bytes hold such a head where a slots head
-//             has four: fp32 16 x 4 390/730 | 970/1228, 8 x 8 401/445 | 1001/855; bf16 8 x 8 310/400 |
-//             978/772, 16 x 8 421/733 | 1061/1230.  With up to 4 heads the slots' longer batches win: fp32
-//             4 x 4 241/232 | 813/579, 4 x 8 283/257 | 870/598, bf16 1 x 8 274/166 | 913/551.
-//           - bf16 layers of up to 512 values whose heads would fall into launches of different sizes,
-//             while one generic launch serves them well: rows of up to 256 values (32 lanes, two edges at a time:
-//             9 x 24 755/1148 | 1451/2236, 5 x 40 855/1038 | 1525/2052, 3 x 80 1149/1219 | 1849/2363), heads of
-//             up to 32 values (25 x 16 1273/1699 | 1985/2907, 15 x 32 1449/1423 | 2245/2604) and layers that
-//             would be three launches or more (7 x 72 2168/2572 | 3178/4994, 9 x 48 1785/1807 | 3514/3525,
-//             but 5 x 80 2235/1878 | 3243/3670).  Two launches are faster for the rest: 7 x 48 1704/1257 |
-//             2526/2422, 3 x 96 2416/1303 | 3442/2419, 3 x 120 2887/1444 | 4003/2671, 5 x 64 1422/1148 | 2147/2195.
+//   generic heads of 1 to 3 values and bf16 heads of more than 256; in the forward pass also layers of two
+//           kinds.  (Times in us, generic kernel/the others, of one call over all blocks on a share of 7.3M edges,
+//           24 a row, and on one of 7.4M, 6 a row; "shipped": with the sources' score halves given.)
+//           - heads of 4 or 8 values, which two lanes of 16 bytes hold where a slots head has four.  With score halves
+//             formed in flight up to 4 such heads are better off in the slots' longer batches: fp32 4 x 4
+//             241/232, 813/579, 4 x 8 283/257, 870/598, bf16 1 x 8 274/166, 913/551 (block by block 1 x 8 fp32
+//             1056/719, 4 x 4 989/706); more heads are not: fp32 16 x 4 390/730, 970/1228, 8 x 8 401/445,
+//             1001/855, bf16 16 x 8 421/733, 1061/1230.  Shipped, the generic kernel reads one value per head and
+//             edge with no sum to form: on 75 thousand rows of 29, fp32 4 x 8 96/136, bf16 4 x 4 74/133, 1 x 4 66/64.
+//           - bf16 layers of up to 512 values whose heads would fall into launches of different sizes, which one
+//             generic launch takes whole: shipped 5 x 64 988/1506, 7 x 48 1090/1667, 3 x 96 966/1522; block by block
+//             5 x 64 2272/2887; in flight 5 x 40 855/1038, 1525/2052, 9 x 24 755/1148, 1451/2236, 25 x 16 1273/1699,
+//             1985/2907, 7 x 72 2168/2572, 3178/4994.  In flight over all blocks two launches win where the
+//             generic kernel's row needs a whole wavefront and its heads a sum lane after lane (no power of
+//             two of lanes): 7 x 48 1704/1248, 2526/2388, 5 x 56 1797/1205, 2621/2325, 3 x 96 2416/1272, 3442/2378,
+//             3 x 120 2887/1418, 4003/2650; not 5 x 64 (1422/1148, 2147/2195) and 3 x 80 (1149/1219, 1849/2363).
 // In the forward pass the padded kernel also takes launches that leave up to 5/8 of the lanes idle:
 // it waits for memory there either way (4 x 32 fp32 on 7.4M edges: 603 us padded, 608 us with two
 // slots), while the backward pass gains from the slots (4 x 32: 1.9 and 6.5% of the whole step in
@@ -904,18 +907,24 @@ struct LaunchGeo {
 // Heads of width D a wavefront of the slots kernels (and of the padded ones) has lane groups for.
 int lane_groups(int D) { return 64 / std::max(4, pow2_at_least((D + 3) / 4)); }
 
-bool generic_layer(int dtype, int H, int D, bool forward)
+// What a launch is for: the forward pass with the sources' score halves given, or formed in flight for
+// one block or for all; or the backward pass.
+enum class Pass { kFwdShipped, kFwdBlock, kFwdAll, kBwd };
+Pass fwd_pass(bool shipped, bool all) { return shipped ? Pass::kFwdShipped : all ? Pass::kFwdAll : Pass::kFwdBlock; }
+
+bool generic_layer(int dtype, int H, int D, Pass pass)
 {
     if (D < 4 || D > 256) return true;
-    if (!forward) return false;
-    if (D == 4 || D == 8) return H > 4;
+    if (pass == Pass::kBwd) return false;
+    if (D == 4 || D == 8) return H > 4 || pass == Pass::kFwdShipped;
     const int n = (H + lane_groups(D) - 1) / lane_groups(D);
-    return dtype == SAR_BF16 && D % 8 == 0 && H % n != 0 && H * D <= 512 && (H * D <= 256 || D <= 32 || n > 2);
+    if (dtype != SAR_BF16 || D % 8 != 0 || H % n == 0 || H * D > 512) return false;
+    return pass != Pass::kFwdAll || n > 2 || H * D <= 256 || D <= 32 || is_pow2(D / 8);
 }
 
-LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, bool forward)
+LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, Pass pass)
 {
-    if (generic_layer(dtype, ldz / D, D, forward)) return LaunchGeo{Gather::kGeneric, 0, 0, false};
+    if (generic_layer(dtype, ldz / D, D, pass)) return LaunchGeo{Gather::kGeneric, 0, 0, false};
     const int lph = std::max(4, pow2_at_least((D + 3) / 4)), groups = 64 / lph;
     if (Hg * lph == 64 && D == 4 * lph && ldz == f256::kF) return LaunchGeo{Gather::kExact, lph, 1, false};
     int slots = 1;
@@ -923,7 +932,7 @@ LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, bool forward)
     if (D % 4 == 0) {
         const int padded = std::max(8, lph);
         if (slots == 1 && lph >= 8) return LaunchGeo{Gather::kPadded, lph, 1, false};
-        if (forward && Hg * padded <= 64 && Hg * (D / 4) * 8 >= 3 * 64) return LaunchGeo{Gather::kPadded, padded, 1, false};
+        if (pass != Pass::kBwd && Hg * padded <= 64 && Hg * (D / 4) * 8 >= 3 * 64) return LaunchGeo{Gather::kPadded, padded, 1, false};
     }
     return LaunchGeo{Gather::kSlots, lph, slots, D % 4 != 0};
 }
@@ -938,12 +947,12 @@ struct HeadGroups {
     int count(int g) const { return std::min(most, H - g * most); }
 };
 
-HeadGroups head_groups(int dtype, int H, int D, bool forward)
+HeadGroups head_groups(int dtype, int H, int D, Pass pass)
 {
     HeadGroups g;
     g.H = H;
     g.fb = dtype == SAR_F32 ? 4 : 2;
-    const int groups = generic_layer(dtype, H, D, forward) ? std::max(1, 64 * piece_for(dtype == SAR_F32, D) / D)
+    const int groups = generic_layer(dtype, H, D, pass) ? std::max(1, 64 * piece_for(dtype == SAR_F32, D) / D)
                                                            : lane_groups(D);
     g.n = (H + groups - 1) / groups;
     g.most = (H + g.n - 1) / g.n;
@@ -1186,7 +1195,7 @@ template <bool ALL>
 int launch_fwd(int dtype, const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int P, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, true);
+    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, fwd_pass(a.a_l == nullptr, ALL));
     if (geo.kind == Gather::kGeneric)
         SAR_DISPATCH_GENERIC(dtype, a.D, return (launch_fwd_generic<T, ALL>(a, zt, tt, P, st)));
     if (dtype == SAR_F32) return launch_fwd_fast<float, ALL>(a, zt, tt, geo, st);
@@ -1486,7 +1495,7 @@ template <bool ALL>
 int launch_bwd(int dtype, const BwdArgs& tabs, const BwdScalars& a, float* da_l, hipStream_t st)
 {
     if (a.n_rows == 0) return SAR_OK;
-    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, false);
+    const LaunchGeo geo = launch_geo(dtype, a.H, a.D, a.ldz, Pass::kBwd);
     if (geo.kind == Gather::kGeneric)
         SAR_DISPATCH_GENERIC_BWD(dtype, a.D, return (launch_bwd_generic<T, ALL>(tabs, a, da_l, st)));
     if (dtype == SAR_F32) return launch_bwd_fast<float, ALL>(tabs, a, geo, da_l, st);
@@ -1645,7 +1654,7 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     SAR_CHECK_ARG(Zq && s && m && l && acc, "a tensor argument is null");
     SAR_CHECK_ARG(tq || a_l, "either tq or a_l must be given");
     SAR_CHECK_ARG(aligned16(Zq) && aligned16(acc) && aligned16(a_l), "Zq, acc and a_l must be 16-byte aligned");
-    const HeadGroups hg = head_groups(dtype, H, D, true);
+    const HeadGroups hg = head_groups(dtype, H, D, fwd_pass(tq != nullptr, false));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         FwdArgs a{};
@@ -1712,7 +1721,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(aligned16(Zq[q]), "Zq[%d] must be 16-byte aligned", q);
     }
     hipStream_t st = sar::as_stream(stream);
-    const HeadGroups hg = head_groups(dtype, H, D, true);
+    const HeadGroups hg = head_groups(dtype, H, D, fwd_pass(tq != nullptr, true));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         PtrTab zt{}, tt{};
@@ -1834,7 +1843,7 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     SAR_CHECK_ARG(aligned16(Zq) && aligned16(dZq), "Zq and dZq must be 16-byte aligned");
     hipStream_t st = sar::as_stream(stream);
     DsTarget dst;
-    const HeadGroups hg = head_groups(dtype, H, D, false);
+    const HeadGroups hg = head_groups(dtype, H, D, Pass::kBwd);
     SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(k.hub, k.nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
@@ -1877,7 +1886,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(Zq[q] && (!tq || tq[q]) && dZq[q] && (!dtq || dtq[q]), "a tensor of block %d is null", q);
         SAR_CHECK_ARG(aligned16(Zq[q]) && aligned16(dZq[q]), "Zq[%d] and dZq[%d] must be 16-byte aligned", q, q);
     }
-    const HeadGroups hg = head_groups(dtype, H, D, false);
+    const HeadGroups hg = head_groups(dtype, H, D, Pass::kBwd);
     DsTarget dst;
     int64_t nnz = 0, hub = 0;     // a frequent destination is frequent in every block
     for (int q = 0; q < b->P; ++q) {

@@ -253,7 +253,7 @@ __device__ inline float group_sum_any(float v, int first, int width)
     return s;
 }
 
-__device__ inline bool is_pow2(int x) { return (x & (x - 1)) == 0; }
+__host__ __device__ inline bool is_pow2(int x) { return (x & (x - 1)) == 0; }
 
 // Geometry of one lane inside the row mapping.
 template <typename T, int G>
