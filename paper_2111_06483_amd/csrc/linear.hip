@@ -2,77 +2,26 @@
 // backward (what Z.backward(E) does in Alg. 2: dW = X^T dZ, dX = dZ W^T) on the
 // gfx950 matrix cores.  This is the one real contraction on the path.
 //
-// fp32 rows are multiplied with V_MFMA_F32_32X32X2_F32 (fp32 in, fp32 accumulate), so fp32
-// configurations keep fp32 accuracy; bf16-stored rows go through V_MFMA_F32_32X32X16_BF16:
+// fp32 rows are multiplied with V_MFMA_F32_32X32X2_F32 (fp32 in, fp32 accumulate) in the forward
+// product, whose last bits decide slopes and signs further on; the two products of the backward pass
+// go through the bf16 matrix cores in three pieces per value, which is both faster and closer to the
+// exact sums (linear_split.hip).  bf16-stored rows go through V_MFMA_F32_32X32X16_BF16:
 // the products are exact there, and the fp32 weight matrix is split into two bf16 terms,
 // W = hi + lo (+ an error below 2^-17 |W|), multiplied in two instructions, which is far
 // below the bf16 rounding of the stored result.
 //
 // Z = X W and dX = dZ W^T read their rows straight into registers.  Where the small operand
 // fits in LDS it stays there (k_gemm_skinny); where it does not it passes through LDS in
-// steps of the contraction (k_gemm_steps).  dW has a kernel of its own (k_dw).
+// steps of the contraction (k_gemm_steps).  dW of bf16 rows has a kernel of its own (k_dw).
 #include <algorithm>
 
-#include "gather_common.h"
+#include "linear_common.h"
+#include "linear_split.h"
 #include "sar_internal.h"
 
 namespace {
 
 using namespace sar;
-
-typedef float float16_t __attribute__((ext_vector_type(16)));
-
-__device__ inline float bf16_to_f32(bf16_t v) { return __uint_as_float((uint32_t)v.bits << 16); }
-
-template <typename T>
-__device__ inline T from_f32(float v);
-template <>
-__device__ inline float from_f32<float>(float v) { return v; }
-template <>
-__device__ inline bf16_t from_f32<bf16_t>(float v) { return bf16_t{(uint16_t)f32_to_bf16_rne(v)}; }
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-
-// ---- error rows that are never stored ---------------------------------------
-//
-// Z_p.backward(E_p) of Alg. 2 reads the worker's error E_p twice (dW = X^T E_p, dX = E_p W^T).
-// For the attention layer E_p = E_{p->p} + ds (x) a_r: the local block's error, stored compactly
-// (one row per touched source), plus a rank-one term per head.  Instead of writing that sum out
-// and reading it back twice, the two products can form each 16-byte piece of it where they load
-// the operand: piece(i, f..) = E[row of i][f..] (zero where E has no row for i) + ds[i, f/D] a_r[f..],
-// in fp32 and rounded to the storage type exactly as a stored E_p would have been.
-struct RowsOp {
-    const int32_t* rank;   // [n+1]: node i's row of E is rank[i], present iff rank[i+1] > rank[i]; null: row i
-    const float* ds;       // [n, H] or null (no rank-one term)
-    const float* a_r;      // [H*D]
-    int H, D;
-    int has_E;             // 0: E has no rows at all (or is null)
-};
-
-template <typename T>
-__device__ inline uint4 fuse_piece(const uint4& base, float d, const float* ar);
-template <>
-__device__ inline uint4 fuse_piece<float>(const uint4& base, float d, const float* ar)
-{
-    return make_uint4(__float_as_uint(fmaf(d, ar[0], __uint_as_float(base.x))),
-                      __float_as_uint(fmaf(d, ar[1], __uint_as_float(base.y))),
-                      __float_as_uint(fmaf(d, ar[2], __uint_as_float(base.z))),
-                      __float_as_uint(fmaf(d, ar[3], __uint_as_float(base.w))));
-}
-template <>
-__device__ inline uint4 fuse_piece<bf16_t>(const uint4& base, float d, const float* ar)
-{
-    float v[8];
-    Vec<bf16_t>::unpack(base, v);
-#pragma unroll
-    for (int x = 0; x < 8; ++x) v[x] = fmaf(d, ar[x], v[x]);
-    uint4 r;
-    r.x = pack2_bf16(v[0], v[1]);
-    r.y = pack2_bf16(v[2], v[3]);
-    r.z = pack2_bf16(v[4], v[5]);
-    r.w = pack2_bf16(v[6], v[7]);
-    return r;
-}
 
 // ---- skinny products: the small operand resident in LDS --------------------
 //
@@ -99,17 +48,6 @@ constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = 64 * kSkinnyWaves;
 constexpr size_t kSkinnyMaxLds = 160 * 1024;   // all of a CU's LDS: one workgroup per CU then
 
-// Any alignment (gfx950 takes unaligned vector accesses).
-struct __attribute__((packed, aligned(2))) U4Any {
-    uint32_t x, y, z, w;
-};
-__device__ inline uint4 load16(const void* p)
-{
-    const U4Any r = *static_cast<const U4Any*>(p);
-    return make_uint4(r.x, r.y, r.z, r.w);
-}
-__device__ inline void store16(void* p, const uint4& v) { *static_cast<U4Any*>(p) = U4Any{v.x, v.y, v.z, v.w}; }
-
 struct SkinnyArgs {
     const void* A;     // [M, K], row stride lda, contraction index contiguous
     int64_t lda, M;
@@ -132,31 +70,6 @@ struct SkinnyArgs {
     RowsOp op;         // FUSE only: how the rows of A are formed
 };
 
-
-// The last `rest` values of a 16-byte piece, moved to its front, zeros behind them.
-template <typename T>
-__device__ inline uint4 front_of_piece(const uint4& v, int rest);
-template <>
-__device__ inline uint4 front_of_piece<float>(const uint4& v, int rest)
-{
-    return rest == 3 ? make_uint4(v.y, v.z, v.w, 0u) : rest == 2 ? make_uint4(v.z, v.w, 0u, 0u) : make_uint4(v.w, 0u, 0u, 0u);
-}
-template <>
-__device__ inline uint4 front_of_piece<bf16_t>(const uint4& v, int rest)
-{
-    // down by 8 - rest halves: whole words first, then half a word
-    const int words = (8 - rest) >> 1;
-    uint32_t w[5] = {v.x, v.y, v.z, v.w, 0u}, o[4];
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const bool shift = s < words;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) w[k] = shift ? w[k + 1] : w[k];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = (rest & 1) ? (w[k] >> 16) | (w[k + 1] << 16) : w[k];
-    return make_uint4(o[0], o[1], o[2], o[3]);
-}
 
 // FUSE: the rows of A are not stored; each piece is formed where it is multiplied (RowsOp, K <= 256).
 // Between the epilogues a wavefront's staging tile is idle, so it holds what the pieces need: the
@@ -955,44 +868,29 @@ int launch_steps(StepArgs g, hipStream_t st)
 // of a row that is no whole number of them is read where the row ends and moved
 // to its front (RAG).
 //
-// What this measured, before (one 128 x 256 shape, no slab below 128 rows, a general tiled kernel for
-// other widths) and now: 64 x 64 over 4096 rows 31 -> 9.7 us, where every wavefront's four by two
-// tiles were multiplied though one in eight existed; bf16 254 x 200 over 30000 rows and other widths
-// off 16 bytes 28..59 -> 10..25 us.  The large products (fp32, 256 x 256 over 157000 rows, 404 us)
-// are as they were: bound by the fp32 matrix rate.  Two wavefronts per SIMD have to be asked for: with
-// the guarded and the unguarded row step both in it the compiler takes one (366 -> 415 us).
+// bf16 rows only: fp32 rows take k_dw_split.  What this measured, before (one 128 x 256 shape, no slab below 128 rows, a
+// general tiled kernel for other widths) and now: 254 x 200 over 30000 rows and other widths off 16 bytes 28..59 ->
+// 10..25 us.  Two wavefronts per SIMD have to be asked for: with the guarded and the unguarded row step both in it the
+// compiler takes one.
 
 constexpr int kDwKf = 128;
 
-template <typename T>
-struct DwShape;
-template <>
-struct DwShape<float> {
-    static constexpr int kRows = 16;          // rows per chunk
-    static constexpr int kPad = 32;           // LDS row strides: consecutive rows (the two lane groups)
-                                              // 32 banks apart
-    static constexpr int kVec = 4;            // elements per 16 bytes
-};
-template <>
-struct DwShape<bf16_t> {
-    static constexpr int kRows = 32;
-    static constexpr int kPad = 8;            // rows 8 apart (the two lane groups) 32 banks apart
-    static constexpr int kVec = 8;
-};
+constexpr int kDwRows = 32;          // rows per chunk
+constexpr int kDwPad = 8;            // LDS row strides: rows 8 apart (the two lane groups) 32 banks apart
+constexpr int kDwVec = 8;            // elements per 16 bytes
 
-template <typename T, bool FUSE, int NW, bool RAG>
-__global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T* __restrict__ dZ, RowsOp op,
-                                            float* __restrict__ partial, int64_t M, int K, int N,
+template <bool FUSE, int NW, bool RAG>
+__global__ __launch_bounds__(256, 2) void k_dw(const bf16_t* __restrict__ X, const bf16_t* __restrict__ dZ,
+                                            RowsOp op, float* __restrict__ partial, int64_t M, int K, int N,
                                             int64_t rows_per_slab)
 {
-    using S = DwShape<T>;
-    constexpr bool BF = sizeof(T) == 2;
-    constexpr int kXUnits = S::kRows * kDwKf / S::kVec / 256;   // 16-byte units per thread and chunk
-    constexpr int kDUnits = S::kRows * NW / S::kVec / 256;
-    constexpr int kXs = kDwKf + S::kPad, kDs = NW + S::kPad;
+    using T = bf16_t;
+    constexpr int kXUnits = kDwRows * kDwKf / kDwVec / 256;   // 16-byte units per thread and chunk
+    constexpr int kDUnits = kDwRows * NW / kDwVec / 256;
+    constexpr int kXs = kDwKf + kDwPad, kDs = NW + kDwPad;
     constexpr int kCols = NW / 64, kParts = NW == 256 ? 1 : 2, kKg = 4 / kCols / kParts, kKt = 4 / kKg;
-    __shared__ __attribute__((aligned(16))) T Xs[2][S::kRows][kXs];
-    __shared__ __attribute__((aligned(16))) T Ds[2][S::kRows][kDs];
+    __shared__ __attribute__((aligned(16))) T Xs[2][kDwRows][kXs];
+    __shared__ __attribute__((aligned(16))) T Ds[2][kDwRows][kDs];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, gq = lane >> 5;
     const int kf0 = blockIdx.z * kDwKf, n0 = blockIdx.y * NW;
@@ -1007,20 +905,20 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
     // where it is stored (commit); rows shorter than a unit are read value by value
     auto unit = [](const T* row, int col, int width) -> uint4 {
         if constexpr (RAG) {
-            if (width < S::kVec) {
-                T v[S::kVec] = {};
+            if (width < kDwVec) {
+                T v[kDwVec] = {};
 #pragma unroll
-                for (int x = 0; x < S::kVec; ++x)
+                for (int x = 0; x < kDwVec; ++x)
                     if (x < width) v[x] = row[x];
                 return __builtin_bit_cast(uint4, v);
             }
-            col = min(col, width - S::kVec);
+            col = min(col, width - kDwVec);
         }
         return load16(row + col);
     };
     auto placed = [](const uint4& v, int col, int width) -> uint4 {
         if constexpr (RAG) {
-            if (width > S::kVec && col < width && col + S::kVec > width) return front_of_piece<T>(v, width % S::kVec);
+            if (width > kDwVec && col < width && col + kDwVec > width) return front_of_piece<T>(v, width % kDwVec);
         }
         return v;
     };
@@ -1035,7 +933,7 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
         if constexpr (FUSE) {
 #pragma unroll
             for (int q = 0; q < kDUnits; ++q) {
-                const int u = tid + 256 * q, row = u / (NW / S::kVec);
+                const int u = tid + 256 * q, row = u / (NW / kDwVec);
                 const bool ok = op.rank != nullptr && m0 + row < m_end;
                 rk0[q] = ok ? op.rank[m0 + row] : 0;
                 rk1[q] = ok ? op.rank[m0 + row + 1] : 0;
@@ -1046,12 +944,12 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
         // a piece's values four by four: the first four of every piece, then (8-value pieces) the
         // last four, so that neighbouring lanes read neighbouring 16 bytes (no bank conflicts)
         for (int f = tid; f < NW; f += 256) {
-            const int piece = f / S::kVec, x = f % S::kVec;
+            const int piece = f / kDwVec, x = f % kDwVec;
             ars[(x / 4) * (NW / 2) + piece * 4 + (x % 4)] = (op.ds && n0 + f < N) ? op.a_r[n0 + f] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, col = (u % (NW / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, col = (u % (NW / kDwVec)) * kDwVec;
             hq[q] = n0 + col < N ? (n0 + col) / op.D : 0;
             dsv[q] = 0.f;
         }
@@ -1061,13 +959,13 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
     auto fetch = [&](int64_t m0) {
 #pragma unroll
         for (int q = 0; q < kXUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (kDwKf / S::kVec), col = (u % (kDwKf / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (kDwKf / kDwVec), col = (u % (kDwKf / kDwVec)) * kDwVec;
             const bool ok = m0 + row < m_end && kf0 + col < K;
             gx[q] = ok ? unit(X + (m0 + row) * K, kf0 + col, K) : make_uint4(0u, 0u, 0u, 0u);
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (NW / S::kVec), col = (u % (NW / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (NW / kDwVec), col = (u % (NW / kDwVec)) * kDwVec;
             const bool ok = m0 + row < m_end && n0 + col < N;
             if constexpr (FUSE) {
                 int64_t from = m0 + row;
@@ -1082,22 +980,22 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
                 gd[q] = ok ? unit(dZ + (m0 + row) * N, n0 + col, N) : make_uint4(0u, 0u, 0u, 0u);
             }
         }
-        fetch_rank(m0 + S::kRows);
+        fetch_rank(m0 + kDwRows);
     };
     auto commit = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < kXUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (kDwKf / S::kVec), col = (u % (kDwKf / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (kDwKf / kDwVec), col = (u % (kDwKf / kDwVec)) * kDwVec;
             *reinterpret_cast<uint4*>(&Xs[buf][row][col]) = placed(gx[q], kf0 + col, K);
         }
 #pragma unroll
         for (int q = 0; q < kDUnits; ++q) {
-            const int u = tid + 256 * q, row = u / (NW / S::kVec), col = (u % (NW / S::kVec)) * S::kVec;
+            const int u = tid + 256 * q, row = u / (NW / kDwVec), col = (u % (NW / kDwVec)) * kDwVec;
             if constexpr (FUSE) {
-                float arv[S::kVec];
+                float arv[kDwVec];
 #pragma unroll
-                for (int x = 0; x < S::kVec; x += 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(ars + (x / 4) * (NW / 2) + (col / S::kVec) * 4);
+                for (int x = 0; x < kDwVec; x += 4) {
+                    const float4 v = *reinterpret_cast<const float4*>(ars + (x / 4) * (NW / 2) + (col / kDwVec) * 4);
                     arv[x] = v.x; arv[x + 1] = v.y; arv[x + 2] = v.z; arv[x + 3] = v.w;
                 }
                 *reinterpret_cast<uint4*>(&Ds[buf][row][col]) = fuse_piece<T>(gd[q], dsv[q], arv);
@@ -1114,50 +1012,33 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-    constexpr int kStep = BF ? 16 : 2;   // rows per matrix instruction
+    constexpr int kStep = 16;   // rows per matrix instruction
     // one row step; ALL: every tile of this wavefront exists
     auto step = [&](int buf, int s, auto all) {
         constexpr bool ALL = decltype(all)::value;
-        if constexpr (BF) {
-            const uint16_t(*xs)[kXs] = reinterpret_cast<const uint16_t(*)[kXs]>(Xs[buf]);
-            const uint16_t(*ds)[kDs] = reinterpret_cast<const uint16_t(*)[kDs]>(Ds[buf]);
-            const int r0 = kStep * s + 8 * gq;
-            auto column = [&](auto tile, int col) -> bf16x8_t {
-                uint32_t w[4];
+        const uint16_t(*xs)[kXs] = reinterpret_cast<const uint16_t(*)[kXs]>(Xs[buf]);
+        const uint16_t(*ds)[kDs] = reinterpret_cast<const uint16_t(*)[kDs]>(Ds[buf]);
+        const int r0 = kStep * s + 8 * gq;
+        auto column = [&](auto tile, int col) -> bf16x8_t {
+            uint32_t w[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    w[e] = (uint32_t)tile[r0 + 2 * e][col] | ((uint32_t)tile[r0 + 2 * e + 1][col] << 16);
-                return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-            };
-            bf16x8_t b[2];
+            for (int e = 0; e < 4; ++e)
+                w[e] = (uint32_t)tile[r0 + 2 * e][col] | ((uint32_t)tile[r0 + 2 * e + 1][col] << 16);
+            return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+        };
+        bf16x8_t b[2];
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-                if (ALL || nt < nt_n) b[nt] = column(ds, 64 * cw + 32 * nt + c);
+        for (int nt = 0; nt < 2; ++nt)
+            if (ALL || nt < nt_n) b[nt] = column(ds, 64 * cw + 32 * nt + c);
 #pragma unroll
-            for (int kt = 0; kt < kKt; ++kt)
-                if (ALL || kt < kt_n) {
-                    const bf16x8_t a = column(xs, 32 * (kt * kKg + kg) + c);
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt)
-                        if (ALL || nt < nt_n)
-                            acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[nt], acc[kt][nt], 0, 0, 0);
-                }
-        } else {
-            const float(*xs)[kXs] = reinterpret_cast<const float(*)[kXs]>(Xs[buf]);
-            const float(*ds)[kDs] = reinterpret_cast<const float(*)[kDs]>(Ds[buf]);
-            const int r0 = kStep * s + gq;
-            float a[kKt], b[2];
-#pragma unroll
-            for (int kt = 0; kt < kKt; ++kt) a[kt] = xs[r0][32 * (kt * kKg + kg) + c];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) b[nt] = ds[r0][64 * cw + 32 * nt + c];
-#pragma unroll
-            for (int kt = 0; kt < kKt; ++kt)
+        for (int kt = 0; kt < kKt; ++kt)
+            if (ALL || kt < kt_n) {
+                const bf16x8_t a = column(xs, 32 * (kt * kKg + kg) + c);
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    if (ALL || (kt < kt_n && nt < nt_n))
-                        acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kt], b[nt], acc[kt][nt], 0, 0, 0);
-        }
+                    if (ALL || nt < nt_n)
+                        acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[nt], acc[kt][nt], 0, 0, 0);
+            }
     };
     const bool all = kt_n == kKt && nt_n == 2;
 
@@ -1167,15 +1048,15 @@ __global__ __launch_bounds__(256, 2) void k_dw(const T* __restrict__ X, const T*
     }
     __syncthreads();
     int buf = 0;
-    for (int64_t m0 = m_beg; m0 < m_end; m0 += S::kRows, buf ^= 1) {
-        const bool more = m0 + S::kRows < m_end;
-        if (more) fetch(m0 + S::kRows);
+    for (int64_t m0 = m_beg; m0 < m_end; m0 += kDwRows, buf ^= 1) {
+        const bool more = m0 + kDwRows < m_end;
+        if (more) fetch(m0 + kDwRows);
         if (all) {
 #pragma unroll
-            for (int s = 0; s < S::kRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::true_type{});
+            for (int s = 0; s < kDwRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::true_type{});
         } else {
 #pragma unroll
-            for (int s = 0; s < S::kRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::false_type{});
+            for (int s = 0; s < kDwRows / kStep / kParts; ++s) step(buf, s * kParts + part, std::false_type{});
         }
         if (more) commit(buf ^ 1);
         __syncthreads();
@@ -1324,8 +1205,8 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
 
 namespace {
 
-// Whether both products can form the rows `op` describes while they load them (k_dw and
-// k_gemm_skinny with FUSE): their aligned fast paths, a piece inside one head, the stand-in row
+// Whether both products can form the rows `op` describes while they load them (k_dw, k_dw_split,
+// k_gemm_skinny and k_dx_split with FUSE): their aligned fast paths, a piece inside one head, the stand-in row
 // readable.  dZ here is the stored part E (or the stand-in when there is none).
 bool rows_op_fusable(const void* X, const void* dZ, const RowsOp& op, void* dX, int dtype, int K, int F)
 {
@@ -1375,41 +1256,41 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
                     int64_t n, int K, int F, void* work, size_t work_bytes, hipStream_t st)
 {
     if (dW) {
-        const int slabs = slabs_for(n, K, F);
+        int slabs = slabs_for(n, K, F);
         const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
         SAR_CHECK_ARG(work != nullptr && work_bytes >= need, "work_bytes=%zu is below the %zu bytes required",
                       work_bytes, need);
         // dW[K,F] = X^T dZ, contraction over the n rows, split into slabs
-        const int chunk = dtype == SAR_F32 ? DwShape<float>::kRows : DwShape<bf16_t>::kRows;
-        const int64_t rows_per_slab = ((n + slabs - 1) / slabs + chunk - 1) / chunk * chunk;
-        auto launch = [&](auto kernel, int nw, const auto* x, const auto* dz) {
-            const dim3 grid((unsigned)slabs, (unsigned)((F + nw - 1) / nw), (unsigned)((K + kDwKf - 1) / kDwKf));
-            kernel<<<grid, 256, 0, st>>>(x, dz, op ? *op : RowsOp{}, static_cast<float*>(work), n, K, F,
-                                         rows_per_slab);
-        };
-        auto with = [&](auto fuse, auto ragged, const auto* x, const auto* dz) {
-            using T = std::remove_cv_t<std::remove_reference_t<decltype(*x)>>;
-            constexpr bool FUSE = decltype(fuse)::value, RAG = decltype(ragged)::value;
-            if (F <= 64)
-                launch(k_dw<T, FUSE, 64, RAG>, 64, x, dz);
-            else if (F <= 128)
-                launch(k_dw<T, FUSE, 128, RAG>, 128, x, dz);
-            else
-                launch(k_dw<T, FUSE, 256, RAG>, 256, x, dz);
-        };
-        auto typed = [&](const auto* x, const auto* dz, int vec) {
+        auto slabs_bf16 = [&]() -> int {
+            const int64_t rows_per_slab = ((n + slabs - 1) / slabs + kDwRows - 1) / kDwRows * kDwRows;
+            auto launch = [&](auto kernel, int nw) {
+                const dim3 grid((unsigned)slabs, (unsigned)((F + nw - 1) / nw), (unsigned)((K + kDwKf - 1) / kDwKf));
+                kernel<<<grid, 256, 0, st>>>(static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(dZ),
+                                             op ? *op : RowsOp{}, static_cast<float*>(work), n, K, F, rows_per_slab);
+            };
+            auto with = [&](auto fuse, auto ragged) {
+                constexpr bool FUSE = decltype(fuse)::value, RAG = decltype(ragged)::value;
+                if (F <= 64)
+                    launch(k_dw<FUSE, 64, RAG>, 64);
+                else if (F <= 128)
+                    launch(k_dw<FUSE, 128, RAG>, 128);
+                else
+                    launch(k_dw<FUSE, 256, RAG>, 256);
+            };
             if (op)   // (rows_op_fusable: whole units)
-                with(std::true_type{}, std::false_type{}, x, dz);
-            else if (K % vec == 0 && F % vec == 0)
-                with(std::false_type{}, std::false_type{}, x, dz);
+                with(std::true_type{}, std::false_type{});
+            else if (K % 8 == 0 && F % 8 == 0)
+                with(std::false_type{}, std::false_type{});
             else
-                with(std::false_type{}, std::true_type{}, x, dz);
+                with(std::false_type{}, std::true_type{});
+            SAR_LAUNCH_CHECK();
+            return SAR_OK;
         };
         if (dtype == SAR_F32)
-            typed(static_cast<const float*>(X), static_cast<const float*>(dZ), 4);
+            SAR_TRY(sar::split_dw(static_cast<const float*>(X), static_cast<const float*>(dZ), op,
+                                  static_cast<float*>(work), n, K, F, slabs, &slabs, st));
         else
-            typed(static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(dZ), 8);
-        SAR_LAUNCH_CHECK();
+            SAR_TRY(slabs_bf16());
         const int64_t count = (int64_t)K * F;
         k_sum_slabs<<<(unsigned)std::min<int64_t>((count + 31) / 32, 8192), 256, 0, st>>>(
             static_cast<const float*>(work), slabs, count, dW);
@@ -1418,7 +1299,9 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
     if (dX) {
         // dX[n,K] = dZ W^T : B(k = f, n = kcol) = W[kcol * F + f]
         SkinnyPlan plan;
-        if (plan_skinny(F, K, dtype, 0, &plan)) {
+        if (dtype == SAR_F32 && F > 16) {      // (shorter sums: not measured)
+            SAR_TRY(sar::split_dx(static_cast<const float*>(dZ), op, W, static_cast<float*>(dX), n, K, F, st));
+        } else if (plan_skinny(F, K, dtype, 0, &plan)) {
             SkinnyArgs sk{dZ, F, n, W, 1, F, dX, K, F, K, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                           plan.stage_off};
             if (op) {

@@ -1,0 +1,69 @@
+"""The backward products of fp32 layers as sums of bf16 pieces: their error against 64-bit sums at the edges of the
+tiles, and operands that have no such pieces (infinities, NaN, the largest finite values)."""
+import pytest
+import torch
+
+from paper_2111_06483_amd import sar
+
+pytestmark = pytest.mark.gpu
+
+
+def backward(X, dZ, W):
+    n, K = X.shape
+    F = dZ.shape[1]
+    work = torch.empty(max(1, sar.sar_linear_workspace_bytes(n, K, F) // 4), device="cuda")
+    dW = torch.zeros(K, F, device="cuda")
+    dX = torch.full((n, K), float("nan"), device="cuda")
+    sar.sar_linear_bwd(X, dZ, W, dW, dX, work)
+    return dW, dX
+
+
+def operands(n, K, F, seed):
+    g = torch.Generator().manual_seed(seed)
+    draw = lambda *shape: torch.randn(*shape, generator=g).cuda()
+    return draw(n, K), draw(n, F), draw(K, F)
+
+
+# Column tiles 2, 4, 5 .. 8 and two slabs of dX (K), one and several steps that end inside a piece (F), last row blocks of
+# 1, 127 and 128 rows, one slab of dW and many, its three widths, one chunk and chunks of fewer than 8 rows.
+@pytest.mark.parametrize("n,K,F", [(1, 40, 17), (33, 31, 47), (129, 64, 64), (255, 100, 65), (4100, 128, 130),
+                                   (30_000, 160, 100), (26_000, 190, 33), (26_011, 224, 257), (60_001, 256, 128),
+                                   (50_000, 300, 60)])
+def test_sums_against_64_bits(n, K, F):
+    """A result of L products carries the rounding of its 6 L / 16 additions, each below 2^-24 of the running sum (at most
+    the result's scale in its root mean square), and the left-out products, below 2^-23 of a product: sqrt(L) 2^-24 of
+    the result with room for the rows' own spread.  (Measured: 0.9e-7 to 3e-7 of the result.)"""
+    X, dZ, W = operands(n, K, F, seed=n + K)
+    dW, dX = backward(X, dZ, W)
+    for got, want, length in ((dX, dZ.double() @ W.double().T, F), (dW, X.double().T @ dZ.double(), n)):
+        err = float((got.double() - want).norm() / want.norm())
+        assert err < max(2.0, min(length, 1024) ** 0.5) * 2.0 ** -24, err
+
+
+def test_sums_of_many_rows_lean_to_no_side():
+    """The matrix cores cut small terms downwards; over a million rows the sums must not drift (the mean error of all
+    entries, which independent roundings bring to 1/64 of their size)."""
+    X, dZ, W = operands(1_000_000, 64, 64, seed=5)
+    dW, _ = backward(X, dZ, W)
+    d = dW.double() - X.double().T @ dZ.double()
+    assert abs(float(d.mean())) < 0.1 * float(d.std())
+
+
+@pytest.mark.parametrize("n,K,F", [(300, 100, 64), (2_000, 256, 100), (700, 61, 47)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+@pytest.mark.parametrize("where", ["X", "dZ", "W"])
+def test_values_without_pieces(n, K, F, value, where):
+    """One such value in an operand reaches the results it is a factor of, as in fp32 products, and no other."""
+    X, dZ, W = operands(n, K, F, seed=F)
+    if value == 3.4e38:                      # (beyond bf16's largest value; the products stay finite)
+        X, dZ, W = X * 0.01, dZ * 0.01, W * 0.01
+    row, col = n - 2, 19
+    {"X": X, "dZ": dZ, "W": W}[where][row if where != "W" else K - 1, col] = value
+    dW, dX = backward(X, dZ, W)
+    for got, want in ((dX, dZ.double() @ W.double().T), (dW, X.double().T @ dZ.double())):
+        finite = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(got), finite)
+        assert torch.equal(torch.isnan(got), torch.isnan(want))
+        assert torch.equal(got[torch.isinf(got)].sign().double(), want[torch.isinf(want)].sign())
+        w, e = want[finite], (got[finite].double() - want[finite]).abs()
+        assert (e <= 1e-5 * torch.maximum(w.abs(), w.abs().median())).all()
