@@ -1469,6 +1469,8 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         ClassLayout L = layout_from_hist(&hist[2 * P * C], 0, sar::kLongClassBlock);
         h->n_f_rows = L.n_rows;
         h->n_f_long = L.n_long;
+        for (int c = 1; c < C; ++c)
+            if (hist[2 * P * C + c]) h->f_longest = ((int64_t)1 << c) - 1;
         memcpy(&cursors[2 * P * C], L.start, sizeof(L.start));
     }
     if (transpose) {
@@ -1476,6 +1478,8 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         h->n_ft_rows = L.n_rows;
         h->n_ft_long = L.n_long;
         h->n_ft_wide = L.n_wide;
+        for (int c = 1; c < C; ++c)
+            if (all_hist[c]) h->ft_longest = ((int64_t)1 << c) - 1;
         memcpy(&cursors[(2 * P + 1) * C], L.start, sizeof(L.start));
     }
     SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));

@@ -23,6 +23,7 @@
 
 #include "gather_common.h"
 #include "gat_f256.h"
+#include "gat_slices.h"
 #include "gat_slots.h"
 #include "sar_internal.h"
 
@@ -326,6 +327,7 @@ struct BwdScalars {
     int ldz, ldh;               // node strides of feature rows / per-head arrays
     int tag_shift;
     float slope;
+    bool wide_done;             // the first n_wide list entries have been served (gat_slices.h)
 };
 
 template <int VEC>
@@ -1249,7 +1251,7 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
     if constexpr (SLOTS) {
         auto kernel = slots::k_gat_bwd_slots<T, LPH, ALL, RAG>;
         static const int resident = resident_workgroups(kernel);
-        if (a.n_wide > 0) g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
+        if (a.n_wide > 0 && !a.wide_done) g_wide = persistent_grid_for(p.n_rows, p.n_long, resident);
         for (int k = 0; k < 2; ++k) {
             const int64_t n = piece[k][1] - piece[k][0];
             const unsigned wide = k == 0 ? g_wide : 0;
@@ -1264,7 +1266,7 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
         auto wide = f256::k_gat_bwd_f256<T, LPH, B, ALL, true>;
         auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
         static const int resident_wide = resident_workgroups(wide), resident_few = resident_workgroups(few);
-        if (a.n_wide > 0) {
+        if (a.n_wide > 0 && !a.wide_done) {
             g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
             wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
             SAR_LAUNCH_CHECK();
@@ -1375,7 +1377,7 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
             SAR_LAUNCH_CHECK();
         }
     }
-    if (a.n_wide > 0) {
+    if (a.n_wide > 0 && !a.wide_done) {
         // sources with at least 8 edges: one wavefront (or workgroup) each
         g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
         wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
@@ -1547,6 +1549,13 @@ __global__ __launch_bounds__(256) void k_ds_sum(const float* __restrict__ copies
     }
 }
 
+// Scratch of a backward pass by head slices, behind the copies of ds: a record and a ds of every destination and head.
+// (A dense graph's destinations are few: none is set aside for more than these.)
+size_t slices_bytes(int64_t n_dst, int H)
+{
+    return n_dst * H <= (int64_t)1 << 20 ? (size_t)n_dst * H * 5 * sizeof(float) : 0;
+}
+
 // Where a backward call's atomics go: ds itself or zeroed copies of it in the caller's scratch.
 struct DsTarget {
     float* base;
@@ -1704,6 +1713,64 @@ extern "C" int sar_gat_fwd_end(const float* m, const float* l, const float* acc,
     return SAR_OK;
 }
 
+namespace {
+
+// Which passes over all blocks go by head slices (gat_slices.h).
+//
+// An XCD walks 512 wavefronts' rows together and fetches the slices of the table that these cite once per such sweep:
+// `uses` is how often it then uses a fetched slice (rows of `edges` edges together gathering from a table of `table` rows,
+// `sets` slices to a row of the table, `lanes` lanes to a slice).  It pays from two uses on, and where there are at least
+// four sweeps: with fewer the chip is not full (8 thousand nodes, 2 x 100, 100 edges a row, two sweeps: 54 us forward by
+// rows, 74 by slices; 10 thousand, 4 x 64, 50 edges: 61 / 100 backward).  No row may be far longer than the others: a
+// lane group walks it alone while the workgroup waits.
+bool even_rows(int64_t rows, int64_t edges, int64_t longest)
+{
+    return rows > 0 && edges > 0 && longest > 0 && longest * rows <= 4 * edges;
+}
+bool sets_for_xcds(int sets) { return sets == 1 || sets == 2 || sets == 4 || sets % slices::kXcds == 0; }
+bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
+{
+    const int parts = sets < slices::kXcds ? slices::kXcds / sets : 1;
+    const double sweeps = rows / (parts * 512.0 * (kWave / lanes)), uses = edges / (parts * std::max(sweeps, 1.0) * table);
+    return sweeps >= 4.0 && uses >= 2.0;
+}
+
+// Forward: heads of 32 to 128 fp32 values or 64 to 128 bf16 values (slices of 128 bytes, a cache line, and more: 64-byte
+// slices bring the neighbour's half along, 4 x 16 fp32 310 -> 440 us).  Times in us on uniform graphs, one worker of four
+// on 200 thousand nodes unless said otherwise, kernels of gat_f256.h / slices:
+//   - the head's slices of the whole table within 3 of an XCD's 4 MiB of L2 and at least 10 thousand wavefronts of work:
+//     no barriers.  20 thousand nodes, one worker, 8 x 32: 100 edges a row 215 / 134, 25 edges 63 / 40; 5 thousand
+//     nodes, 4 x 64, 50 edges (5 thousand wavefronts) 18.0 / 19.0;
+//   - else where sweeps pay.  8 x 32: 500 edges a row (10 uses) 3380 / 2170, 200 edges (4.1) 1370 /
+//     1045, 100 edges (2.05) 700 / 654, 50 edges (1.0) 358 / 384; 4 x 64 (5.1) 3366 / 2183, bf16 1632 / 1464; 4 x 100 (2.6)
+//     5850 / 4700; 1 x 128 (2.6) 1658 / 1302.
+enum class Slices { kNo, kFree, kSwept };
+Slices fwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D)
+{
+    if (D % 4 != 0 || D > 128 || D < (dtype == SAR_F32 ? 32 : 64) || !sets_for_xcds(H)) return Slices::kNo;
+    int64_t edges = 0, sources = 0;
+    for (int q = 0; q < b->P; ++q) {
+        edges += b->blk[q].nnz;
+        sources += b->blk[q].n_src;
+    }
+    if (!even_rows(b->n_dst, edges, b->f_longest)) return Slices::kNo;
+    const int lanes = slice_lanes(D);
+    if (sources * D * (dtype == SAR_F32 ? 4 : 2) <= 3 << 20)
+        return b->n_dst * H / (kWave / lanes) >= 10000 ? Slices::kFree : Slices::kNo;
+    return sweeps_pay(H, lanes, b->n_dst, edges, sources) ? Slices::kSwept : Slices::kNo;
+}
+
+// Backward: fp32 heads of 32, 64 or 128 values, in one or two slices of 128 values (the additions to ds), where sweeps
+// pay.  As above: 8 x 32 500 edges a row (2.6 uses) 3780 / 3355, 200 edges (1.0) 1585 / 1610; 4 x 64
+// (2.6) 3760 / 3370; 2 x 128 (2.6) 3690 / 3375; bf16 4 x 64 2000 / 2630.
+bool bwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D, int64_t edges)
+{
+    if (dtype != SAR_F32 || !(D == 32 || D == 64 || D == 128) || !(H * D == 128 || H * D == 256)) return false;
+    return even_rows(b->n_ft_wide, edges, b->ft_longest) && sweeps_pay(H * D / 128, 32, b->n_ft_wide, edges, b->n_dst);
+}
+
+}  // namespace
+
 extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, const float* s,
                                const float* const* tq, const float* a_l, int dtype, int H, int D, float slope,
                                int act, void* out, float* L, void* stream)
@@ -1721,6 +1788,30 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(aligned16(Zq[q]), "Zq[%d] must be 16-byte aligned", q);
     }
     hipStream_t st = sar::as_stream(stream);
+    const Slices sl = fwd_by_slices(b, dtype, H, D);
+    if (sl != Slices::kNo) {
+        f256::FwdP p{};
+        f256::Tabs tabs{};
+        for (int q = 0; q < b->P; ++q) {
+            tabs.Z[q] = Zq[q];
+            tabs.t[q] = tq ? tq[q] : nullptr;
+        }
+        p.indptr = b->f_indptr;
+        p.indices = b->f_indices;
+        p.rows = reinterpret_cast<const uint32_t*>(b->f_rows);
+        p.n_rows = b->n_dst;
+        p.s = s;
+        p.a_l = tq ? nullptr : a_l;
+        p.out = out;
+        p.L = L;
+        p.H = p.ldh = H;
+        p.D = D;
+        p.ld = H * D;
+        p.tag_shift = b->tag_shift;
+        p.slope = slope;
+        p.act = act;
+        return sar::fwd_slices(dtype, p, tabs, sl == Slices::kSwept, st);
+    }
     const HeadGroups hg = head_groups(dtype, H, D, fwd_pass(tq != nullptr, true));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
@@ -1757,7 +1848,7 @@ extern "C" int sar_gat_workspace_bytes(int64_t n_dst, int64_t n_src_max, int H, 
     SAR_CHECK_ARG(bytes != nullptr, "bytes is null");
     SAR_CHECK_ARG(n_dst >= 0 && n_src_max >= 0 && H > 0 && D > 0, "sizes must be non-negative, H and D positive");
     const int copies = ds_copies_for(n_dst, H);
-    *bytes = workspace_bytes(256) + (copies > 1 ? (size_t)copies * ds_copy_bytes(n_dst, H) : 0);
+    *bytes = workspace_bytes(256) + (copies > 1 ? (size_t)copies * ds_copy_bytes(n_dst, H) : 0) + slices_bytes(n_dst, H);
     return SAR_OK;
 }
 
@@ -1896,6 +1987,39 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
     SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(hub, nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
     int64_t n_src_all[SAR_MAX_BLOCKS];
     for (int q = 0; q < b->P; ++q) n_src_all[q] = b->blk[q].n_src;
+
+    // the sources of 8 edges and more by head slices, where that serves them better
+    const int copies = ds_copies_for(b->n_dst, H);
+    const size_t slices_at = workspace_bytes(256) + (copies > 1 ? (size_t)copies * ds_copy_bytes(b->n_dst, H) : 0);
+    const size_t slices_need = slices_bytes(b->n_dst, H);
+    const bool by_slices = slices_need > 0 && work_bytes >= slices_at + slices_need && bwd_by_slices(b, dtype, H, D, nnz);
+    if (by_slices) {
+        f256::BwdTabs tabs{};
+        for (int q = 0; q < b->P; ++q) {
+            const sar::Block& k = b->blk[q];
+            if (k.n_src == 0) continue;
+            tabs.t_indptr[q] = k.t_indptr;
+            tabs.t_indices[q] = k.t_indices;
+            tabs.Z[q] = Zq[q];
+            tabs.t[q] = tq ? tq[q] : nullptr;
+            tabs.dZ[q] = dZq[q];
+            tabs.dt[q] = dtq ? dtq[q] : nullptr;
+            tabs.rank[q] = (b->flags & SAR_BUILD_COMPACT) ? k.t_rank : nullptr;
+        }
+        f256::BwdP p{};
+        p.rows = b->ft_rows;
+        p.n_rows = b->n_ft_wide;
+        p.G = G;
+        p.rec = reinterpret_cast<const float4*>(rec);
+        p.a_l = a_l;
+        p.partial = static_cast<float*>(work);
+        p.H = p.ldh = H;
+        p.D = D;
+        p.ld = H * D;
+        p.tag_shift = b->tag_shift;
+        p.slope = slope;
+        SAR_TRY(sar::bwd_slices(p, tabs, b->n_dst, static_cast<char*>(work) + slices_at, ds, da_l, st));
+    }
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         BwdArgs tabs{};
@@ -1926,6 +2050,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.n_long = b->n_ft_long;
         a.tag_shift = b->tag_shift;
         fill_bwd_group(a, hg, g, H, D, G, rec, a_l, dst, work, slope);
+        a.wide_done = by_slices;
         SAR_TRY(launch_bwd<true>(dtype, tabs, a, da_l + f0, st));
     }
     return ds_end(dst, ds, st);

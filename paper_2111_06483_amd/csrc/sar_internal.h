@@ -95,11 +95,13 @@ struct sar_blocks {
     uint32_t* f_indices = nullptr; // [sum nnz]
     int32_t* f_rows = nullptr;     // destinations with deg > 0, longest class first
     int64_t n_f_rows = 0, n_f_long = 0;
+    int64_t f_longest = 0;         // no destination has more edges (one below a power of two); 0: not known
     int tag_shift = 0;
     // All-blocks source-side work list: (q << tag_shift) | local source id of
     // every source with an edge, longest class first.
     uint32_t* ft_rows = nullptr;
     int64_t n_ft_rows = 0, n_ft_long = 0, n_ft_wide = 0;
+    int64_t ft_longest = 0;        // no source has more edges in its block
     // The sources that have ONE edge in their block (the last n_single entries of ft_rows that
     // have an edge), listed in the order of that edge's destination: destination, tagged source,
     // row of the source in its block's error.  Null / 0 where the list was not built.

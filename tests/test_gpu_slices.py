@@ -1,0 +1,97 @@
+"""Dense graphs, whose all-blocks passes go by head slices (gat_slices.h): forward with and without barriers, backward, the
+heads and widths they take, rows that end inside a batch or have no edge, against the same layer block by block (the
+kernels of gat_f256.h and gat_slots.h, which the oracle tests hold; the source score halves are formed in the same order,
+so both sides choose the same slopes)."""
+import pytest
+import torch
+
+from paper_2111_06483_amd import sar
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(n_own, n_other, P, deg, H, D, dtype, seed, compact):
+    """Every destination but each 97th has about `deg` sources, uniform over P partitions (the first is the worker's)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    N = n_own + (P - 1) * n_other
+    part = torch.cat([torch.zeros(n_own, dtype=torch.int64), 1 + torch.arange((P - 1) * n_other) // max(n_other, 1)])
+    keep = torch.arange(n_own, device="cuda") % 97 != 3
+    keep[0] = False                                    # the first row of the index and the last one empty
+    keep[-1] = False
+    counts = (deg + torch.randint(-deg // 4, deg // 4 + 1, (n_own,), generator=g, device="cuda")) * keep
+    dst = torch.repeat_interleave(torch.arange(n_own, device="cuda"), counts)
+    src = torch.randint(0, N, (int(counts.sum()),), generator=g, device="cuda")
+    key = torch.unique(dst * N + src)
+    dst, src = key // N, key % N
+    flags = sar.SAR_BUILD_TRANSPOSE | sar.SAR_BUILD_FUSED | (sar.SAR_BUILD_COMPACT if compact else 0)
+    b = sar.sar_blocks_build(src, dst, part.to(torch.int32).cuda(), P, 0, flags)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    Zs = [(rnd(b.n_src(q), H, D)).to(dtype) for q in range(P)]
+    a_l, a_r = rnd(H, D) / D ** 0.5, rnd(H, D) / D ** 0.5
+    return b, Zs, a_l, a_r, rnd(n_own, H, D).to(dtype)
+
+
+def close(got, want, tol):
+    got, want = got.double(), want.double()
+    assert torch.equal(torch.isfinite(got), torch.isfinite(want))
+    ok = torch.isfinite(want)
+    scale = float(want[ok].abs().max())
+    assert float((got[ok] - want[ok]).abs().max()) <= tol * scale
+
+
+# (destinations, other sources, partitions, edges a row).  Barriers: tables beyond 3 MiB and four sweeps and more, in both
+# passes of the first four (backward: fp32) and in the forward pass of the next four; no barriers: the small tables behind.
+SHAPES = [(16_500, 16_500, 2, 90, 8, 32), (16_500, 16_500, 2, 90, 4, 64), (33_000, 5_000, 2, 90, 1, 128),
+          (16_900, 9_000, 3, 90, 2, 128), (17_000, 9_000, 2, 40, 2, 100), (16_390, 14_000, 2, 30, 4, 36),
+          (33_000, 400, 3, 80, 4, 32), (8_200, 8_000, 2, 40, 16, 64), (9_000, 300, 2, 30, 16, 40), (23_000, 500, 2, 9, 8, 32)]
+
+
+@pytest.mark.parametrize("n_own,n_other,P,deg,H,D", SHAPES)
+@pytest.mark.parametrize("dtype,shipped,relu,compact", [(torch.float32, False, False, True), (torch.float32, True, True, False),
+                                                        (torch.bfloat16, False, True, True)])
+def test_layer(n_own, n_other, P, deg, H, D, dtype, shipped, relu, compact):
+    b, Zs, a_l, a_r, G = layer(n_own, n_other, P, deg, H, D, dtype, seed=n_own + H, compact=compact)
+    act = sar.SAR_ACT_RELU if relu else sar.SAR_ACT_NONE
+    n, f32 = b.n_dst, torch.float32
+    tq = None
+    if shipped:
+        tq = [torch.empty(b.n_src(q), H, device="cuda") for q in range(P)]
+        for q in range(P):
+            sar.sar_gat_scores(Zs[q], a_l, tq[q])
+    s = torch.empty(n, H, device="cuda")
+    sar.sar_gat_scores(Zs[0], a_r, s)
+    out, L = torch.full((n, H, D), 7.0, device="cuda", dtype=dtype), torch.full((n, H), 7.0, device="cuda")
+    sar.sar_gat_fwd_all(b, Zs, s, tq, a_l, 0.2, out, L, act)
+    m, l, acc = torch.empty(n, H, device="cuda"), torch.empty(n, H, device="cuda"), torch.empty(n, H, D, device="cuda")
+    sar.sar_gat_fwd_begin(m, l, acc)
+    for q in range(P):
+        sar.sar_gat_fwd_block(b, q, Zs[q], s, None if tq is None else tq[q], a_l, 0.2, m, l, acc)
+    out2, L2 = torch.empty_like(out), torch.empty_like(L)
+    sar.sar_gat_fwd_end(m, l, acc, out2, L2, act)
+    # (fp32: sums of a hundred terms in another order; bf16: one rounding of the stored row)
+    close(out, out2, 2e-6 if dtype == f32 else 2.0 ** -8)
+    close(L, L2, 2e-6)
+    assert (out.reshape(n, -1)[0] == 0).all() and L[0].isneginf().all()
+
+    rec, ds0 = torch.empty(n, H, 4, device="cuda"), torch.empty(n, H, device="cuda")
+    Ga = torch.empty_like(G) if relu else None
+    sar.sar_gat_bwd_begin(G, out, s, L, rec, ds0, act, Ga)
+    Gb = Ga if relu else G
+    full = sar.sar_gat_workspace_bytes(n, max(b.n_src(q) for q in range(P)), H, D)
+    least = 4 * 2048 * 256 * 4
+    assert full > least
+    res = []
+    for size in (full, least):            # with the least scratch the pass takes its other way
+        dZ = [torch.full((b.n_err_rows(q), H, D), float("nan"), device="cuda", dtype=dtype) for q in range(P)]
+        dt = [torch.full((b.n_err_rows(q), H), float("nan"), device="cuda") for q in range(P)]
+        ds, da = torch.zeros(n, H, device="cuda"), torch.zeros(H, D, device="cuda")
+        work = torch.full((size // 4,), float("nan"), device="cuda")
+        sar.sar_gat_bwd_all(b, Zs, Gb, tq, rec, a_l, 0.2, dZ, dt, ds, da, work)
+        res.append((dZ, dt, ds, da))
+    for x, y in zip(res[0][0], res[1][0]):
+        close(x, y, 2e-6 if dtype == f32 else 2.0 ** -8)
+    for x, y in zip(res[0][1], res[1][1]):
+        close(x, y, 1e-5)
+    close(res[0][2], res[1][2], 1e-5)
+    close(res[0][3], res[1][3], 1e-5)
