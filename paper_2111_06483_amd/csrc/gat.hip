@@ -46,6 +46,7 @@ struct FwdArgs {
     const uint32_t* indices;
     const uint32_t* rows;
     int64_t n_rows, n_long;
+    int64_t n_wide;      // per-block call: rows of 8 edges and more, the head of the list
     const void* Z;       // per-block call: this block's source rows
     const float* t;      //                 and their score halves [n_src,H]; null: formed from a_l
     const float* a_l;    // [H,D], used only when the source score halves are not given
@@ -1076,24 +1077,44 @@ f256::Tabs fwd_tabs(const PtrTab& zt, const PtrTab& tt)
     return tabs;
 }
 
-template <typename T, int LPH, bool ALL, bool FLY, bool PAD>
+// A call over all blocks.
+template <typename T, int LPH, bool FLY, bool PAD>
 int launch_fwd_f256(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, hipStream_t st)
 {
     constexpr int B = LPH >= 8 ? 8 : 4;
-    auto fn = f256::k_gat_fwd_f256<T, LPH, B, ALL, FLY, PAD>;
+    auto fn = f256::k_gat_fwd_f256<T, LPH, B, FLY, PAD>;
     static const int resident = resident_workgroups(fn);
     fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt));
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
 
-template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
+template <typename T, int LPH, bool FLY, bool RAG>
 int launch_fwd_slots(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int n_slots, hipStream_t st)
 {
-    auto fn = slots::k_gat_fwd_slots<T, LPH, ALL, FLY, RAG>;
+    auto fn = slots::k_gat_fwd_slots<T, LPH, FLY, RAG>;
     static const int resident = resident_workgroups(fn);
     fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt),
                                                                                      n_slots);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
+// A call over one block: the rows of 8 edges and more and the others in one launch.
+template <typename T, int LPH, bool FLY, bool RAG, bool WHOLE, bool PAD>
+int launch_fwd_block(const FwdArgs& a, hipStream_t st)
+{
+    auto fn = slots::k_gat_fwd_block<T, LPH, FLY, RAG, WHOLE, PAD>;
+    static const int resident = resident_workgroups(fn);
+    f256::FwdP p = fwd_params(a);
+    p.n_rows = a.n_wide;
+    p.n_long = std::min(a.n_long, a.n_wide);
+    int n_slots = 1;
+    while (n_slots * 2 * a.H * LPH <= kWave) n_slots *= 2;
+    const int64_t few = a.n_rows - a.n_wide, per_wg = (int64_t)n_slots * kWavesPerWG;
+    const unsigned g_wide = a.n_wide > 0 ? persistent_grid_for(p.n_rows, p.n_long, resident) : 0;
+    const unsigned g_few = (unsigned)std::min<int64_t>((few + per_wg - 1) / per_wg, resident);
+    fn<<<g_wide + g_few, kGatherThreads, 0, st>>>(p, n_slots, (int)g_wide, a.n_wide, a.n_rows);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
@@ -1146,47 +1167,57 @@ int launch_fwd_generic(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, int
         }                                                               \
     } while (0)
 
-#define SAR_FWD_CASE(LAUNCH, LPH, FLAG, ...)                                                          \
-    case LPH:                                                                                         \
-        return a.a_l ? LAUNCH<T, LPH, ALL, true, FLAG>(a, zt, tt __VA_ARGS__, st)                     \
-                     : LAUNCH<T, LPH, ALL, false, FLAG>(a, zt, tt __VA_ARGS__, st)
+#define SAR_FWD_F256(LPH, PAD)                                                                                       \
+    case LPH:                                                                                                        \
+        if constexpr (ALL)                                                                                           \
+            return a.a_l ? launch_fwd_f256<T, LPH, true, PAD>(a, zt, tt, st) : launch_fwd_f256<T, LPH, false, PAD>(a, zt, tt, st); \
+        else                                                                                                         \
+            return a.a_l ? launch_fwd_block<T, LPH, true, false, true, PAD>(a, st)                                   \
+                         : launch_fwd_block<T, LPH, false, false, true, PAD>(a, st)
+#define SAR_FWD_SLOTS(LPH, RAG)                                                                                      \
+    case LPH:                                                                                                        \
+        if constexpr (ALL)                                                                                           \
+            return a.a_l ? launch_fwd_slots<T, LPH, true, RAG>(a, zt, tt, geo.n_slots, st)                           \
+                         : launch_fwd_slots<T, LPH, false, RAG>(a, zt, tt, geo.n_slots, st);                         \
+        else                                                                                                         \
+            return a.a_l ? launch_fwd_block<T, LPH, true, RAG, false, false>(a, st)                                  \
+                         : launch_fwd_block<T, LPH, false, RAG, false, false>(a, st)
 
 template <typename T, bool ALL>
 int launch_fwd_fast(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, const LaunchGeo& geo, hipStream_t st)
 {
-    const int ns = geo.n_slots;
     if (geo.kind == Gather::kExact) {
         switch (geo.lph) {
-            SAR_FWD_CASE(launch_fwd_f256, 4, false);
-            SAR_FWD_CASE(launch_fwd_f256, 8, false);
-            SAR_FWD_CASE(launch_fwd_f256, 16, false);
-            SAR_FWD_CASE(launch_fwd_f256, 32, false);
-            SAR_FWD_CASE(launch_fwd_f256, 64, false);
+            SAR_FWD_F256(4, false);
+            SAR_FWD_F256(8, false);
+            SAR_FWD_F256(16, false);
+            SAR_FWD_F256(32, false);
+            SAR_FWD_F256(64, false);
             default: break;
         }
     } else if (geo.kind == Gather::kPadded) {
         switch (geo.lph) {
-            SAR_FWD_CASE(launch_fwd_f256, 8, true);
-            SAR_FWD_CASE(launch_fwd_f256, 16, true);
-            SAR_FWD_CASE(launch_fwd_f256, 32, true);
-            SAR_FWD_CASE(launch_fwd_f256, 64, true);
+            SAR_FWD_F256(8, true);
+            SAR_FWD_F256(16, true);
+            SAR_FWD_F256(32, true);
+            SAR_FWD_F256(64, true);
             default: break;
         }
     } else if (geo.ragged) {
         switch (geo.lph) {
-            SAR_FWD_CASE(launch_fwd_slots, 4, true, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 8, true, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 16, true, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 32, true, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 64, true, , ns);
+            SAR_FWD_SLOTS(4, true);
+            SAR_FWD_SLOTS(8, true);
+            SAR_FWD_SLOTS(16, true);
+            SAR_FWD_SLOTS(32, true);
+            SAR_FWD_SLOTS(64, true);
             default: break;
         }
     } else {
         switch (geo.lph) {
-            SAR_FWD_CASE(launch_fwd_slots, 4, false, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 8, false, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 16, false, , ns);
-            SAR_FWD_CASE(launch_fwd_slots, 32, false, , ns);
+            SAR_FWD_SLOTS(4, false);
+            SAR_FWD_SLOTS(8, false);
+            SAR_FWD_SLOTS(16, false);
+            SAR_FWD_SLOTS(32, false);
             default: break;
         }
     }
@@ -1672,6 +1703,7 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.rows = reinterpret_cast<const uint32_t*>(k.rows);
         a.n_rows = k.n_rows;
         a.n_long = k.n_long;
+        a.n_wide = k.n_rows_wide;
         a.Z = shift(Zq, f0 * hg.fb);
         a.t = tq ? tq + h0 : nullptr;
         a.a_l = tq ? nullptr : a_l + f0;

@@ -340,8 +340,9 @@ __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const Tabs& t
     }
 }
 
+// The rows of the list, by workgroup `block` of `n_blocks`.
 template <typename T, int LPH, int B, bool ALL, bool FLY, bool PAD>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_f256(FwdP a, Tabs tabs)
+__device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int n_blocks)
 {
     static_assert(B <= LPH, "a sub-batch must fit a head group");
     __shared__ float part[kWavesPerWG][kWave][6];
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_f256(FwdP a, Tabs ta
     };
 
     // the long rows at the head of the list: the four wavefronts share the row
-    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+    for (int64_t r = block; r < a.n_long; r += n_blocks) {
         const int i = (int)a.rows[r];
         FwdState<LPH> st;
         init(st, i, wave == 0);
@@ -435,14 +436,20 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_f256(FwdP a, Tabs ta
         }
         __syncthreads();
     }
-    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
+    for (int64_t r = a.n_long + (int64_t)block * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         FwdState<LPH> st;
         init(st, i, true);
         edges(st, i, 0, 1);
         finish(st, i);
     }
+}
+
+template <typename T, int LPH, int B, bool FLY, bool PAD>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_f256(FwdP a, Tabs tabs)
+{
+    fwd_rows<T, LPH, B, true, FLY, PAD>(a, tabs, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ----------------------------------------------------------------- backward

@@ -177,8 +177,9 @@ __device__ inline void merge_into(State& st, float om, float ol, const float (&o
     st.m2 = mn;
 }
 
+// The rows of the list, by workgroup `block` of `n_blocks`.
 template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_slots(FwdP a, Tabs tabs, int n_slots)
+__device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int n_slots, int block, int n_blocks)
 {
     __shared__ float part[kWavesPerWG][kWave][6];
     __shared__ const void* s_Z[SAR_MAX_BLOCKS];
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_slots(FwdP a, Tabs t
     };
 
     // the long rows at the head of the list: the four wavefronts share the row
-    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+    for (int64_t r = block; r < a.n_long; r += n_blocks) {
         const int i = (int)a.rows[r];
         State st;
         init(st, i, wave == 0);
@@ -276,14 +277,153 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_slots(FwdP a, Tabs t
         }
         __syncthreads();
     }
-    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
+    for (int64_t r = a.n_long + (int64_t)block * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         State st;
         init(st, i, true);
         edges(st, i, 0, 1);
         finish(st, i);
     }
+}
+
+template <typename T, int LPH, bool FLY, bool RAG>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_slots(FwdP a, Tabs tabs, int n_slots)
+{
+    fwd_rows<T, LPH, true, FLY, RAG>(a, tabs, n_slots, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// Rows of fewer than 8 edges in the block of a per-block call: a P-way split leaves most rows two or three.  Every slot
+// takes a row of its own, lane k of each of its head groups speaking for the row's edge k, so a row is one round of
+// gathers (two of four where a head has only four lanes), and the carried state, read and written back, is most of what
+// a row moves.  A wavefront for such a row alone waited for its list entry, its range, its edges and its sources in turn;
+// here list entries are read three rounds ahead, ranges two, sources one.
+template <typename T, int LPH, bool FLY, bool RAG>
+__device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int64_t r_end, int block, int n_blocks)
+{
+    constexpr int B = kBatch<LPH>;
+    constexpr int kRounds = ((1 << kNarrowMaxClass) - 1 + B - 1) / B;
+    const Place<LPH, RAG> p(a.H, a.D, n_slots);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const T* Z = static_cast<const T*>(a.Z);
+    float al[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (FLY) {
+        if (p.on) load4_f32<RAG>(a.a_l + p.foff, al);
+        p.own_only(al);
+    }
+    struct Meta { int i, beg, cnt; };
+    struct Src { int j[kRounds]; };
+    const int64_t stride = (int64_t)n_blocks * kWavesPerWG * n_slots;
+    const int64_t w0 = r_begin + ((int64_t)block * kWavesPerWG + wave) * n_slots;   // slot 0's list position
+    auto have = [&](int64_t w) { return p.live && w + p.slot < r_end; };
+    auto load_id = [&](int64_t w) { return have(w) ? (int)a.rows[w + p.slot] : 0; };
+    auto load_meta = [&](int i, int64_t w) {
+        Meta m{0, 0, 0};
+        if (have(w)) {
+            m.i = i;
+            m.beg = a.indptr[i];
+            m.cnt = a.indptr[i + 1] - m.beg;
+        }
+        return m;
+    };
+    auto load_src = [&](const Meta& m) {
+        Src s;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int e = r * B + p.k_pos;
+            s.j[r] = (p.k_pos < B && e < m.cnt) ? (int)a.indices[m.beg + e] : 0;
+        }
+        return s;
+    };
+    int id2 = load_id(w0 + 2 * stride);
+    Meta m0 = load_meta(load_id(w0), w0), m1 = load_meta(load_id(w0 + stride), w0 + stride);
+    Src s0 = load_src(m0);
+    for (int64_t w = w0; w < r_end; w += stride) {
+        const Src s1 = load_src(m1);
+        const Meta m2 = load_meta(id2, w + 2 * stride);
+        const int id3 = load_id(w + 3 * stride);
+        const bool mine = have(w);
+        const int64_t i = m0.i;
+        State st{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
+        float s2 = 0.f;
+        if (mine) {
+            if (p.on) load4_f32<RAG>(a.acc + i * a.ld + p.foff, st.acc);
+            st.m2 = a.m[i * a.ldh + p.h] * kLog2e;
+            st.l = p.k_pos == 0 ? a.l[i * a.ldh + p.h] : 0.f;
+            s2 = a.s[i * a.ldh + p.h] * kLog2e;
+        }
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            if (__builtin_amdgcn_ballot_w64(m0.cnt > r * B) == 0) break;
+            typename Row4<T>::Raw raw[B];
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                raw[K] = typename Row4<T>::Raw{};
+                const int j = bcast_i<LPH, K>(s0.j[r]);
+                if (p.on && r * B + K < m0.cnt) raw[K] = load_raw<T, RAG>(Z + (int64_t)j * a.ld + p.foff);
+            });
+            const bool valid = p.live && p.k_pos < B && r * B + p.k_pos < m0.cnt;
+            float tv = 0.f;
+            if constexpr (FLY) {
+                static_for<B>([&](auto kk) {
+                    constexpr int K = decltype(kk)::value;
+                    float v[4];
+                    Row4<T>::unpack(raw[K], v);
+                    p.own_only(v);
+                    float c = al[0] * v[0];
+#pragma unroll
+                    for (int x = 1; x < 4; ++x) c = fmaf(al[x], v[x], c);
+                    c = group_all<LPH, OpSum>(c);
+                    tv = (p.k_pos == K) ? c : tv;
+                });
+            } else {
+                if (valid) tv = a.t[(int64_t)s0.j[r] * a.ldh + p.h];
+            }
+            const float e2 = valid ? leaky2(fmaf(tv, kLog2e, s2), a.slope) : -INFINITY;
+            const float mn = fmaxf(st.m2, group_all<LPH, OpMax>(e2)), ref = mn == -INFINITY ? 0.f : mn;
+            const float c = fast_exp2(st.m2 - ref);      // no edge yet: 0
+            const float pe = fast_exp2(e2 - ref);        // 0 for the lanes without an edge
+            st.l = st.l * c + pe;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) st.acc[x] *= c;
+            st.m2 = mn;
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                const float pk = group_bcast<LPH, K>(pe);
+                float v[4];
+                Row4<T>::unpack(raw[K], v);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) st.acc[x] = fmaf(pk, v[x], st.acc[x]);
+            });
+        }
+        const float l = group_all<LPH, OpSum>(st.l);
+        if (mine) {
+            if (p.on) store4<float, RAG>(a.acc + i * a.ld + p.foff, st.acc);
+            if (p.k_pos == 0) {
+                a.m[i * a.ldh + p.h] = st.m2 * kLn2;
+                a.l[i * a.ldh + p.h] = l;
+            }
+        }
+        m0 = m1;
+        s0 = s1;
+        m1 = m2;
+        id2 = id3;
+    }
+}
+
+// A per-block call: the first n_wide workgroups take the rows of 8 edges and more (a.rows up to a.n_rows; WHOLE: by
+// f256::fwd_rows, a wavefront's lanes on one edge of a row, otherwise by slots), the others [r_begin, r_end) of the list.
+template <typename T, int LPH, bool FLY, bool RAG, bool WHOLE, bool PAD>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_block(FwdP a, int n_slots, int n_wide, int64_t r_begin,
+                                                                  int64_t r_end)
+{
+    const Tabs none{};
+    if ((int)blockIdx.x >= n_wide)
+        fwd_few<T, LPH, FLY, RAG>(a, n_slots, r_begin, r_end, (int)blockIdx.x - n_wide, (int)gridDim.x - n_wide);
+    else if constexpr (WHOLE)
+        f256::fwd_rows<T, LPH, kBatch<LPH>, false, FLY, PAD>(a, none, (int)blockIdx.x, n_wide);
+    else
+        fwd_rows<T, LPH, false, FLY, RAG>(a, none, n_slots, (int)blockIdx.x, n_wide);
 }
 
 // ----------------------------------------------------------------- backward
