@@ -9,13 +9,13 @@ using namespace sar;
 
 // Workgroups that serve `rows` rows: a multiple of the XCDs.  With barriers there are as many as four times the CUs, so
 // that a CU takes another when its own ends (one runs at a time, by registers); without, as many as run at once.
-template <bool SYNC, typename Fn>
-unsigned grid_of(Fn fn, int64_t rows, int sets, int slots, int most)
+template <bool SYNC>
+unsigned grid_of(int resident, int64_t rows, int sets, int slots, int most)
 {
     const int parts = sets < slices::kXcds ? slices::kXcds / sets : 1;                 // XCDs that share a set's rows
     const int64_t per_wg = (int64_t)slices::kWaves<SYNC> * slots * parts;
     const int64_t want = (rows + per_wg - 1) / per_wg;
-    const int64_t enough = SYNC ? 1024 / slices::kXcds : resident_workgroups(fn) / slices::kXcds;
+    const int64_t enough = SYNC ? 1024 / slices::kXcds : resident / slices::kXcds;
     return (unsigned)(std::max<int64_t>(1, std::min<int64_t>({want, enough, most / slices::kXcds})) * slices::kXcds);
 }
 
@@ -23,7 +23,8 @@ template <typename T, int LPH, bool FLY, bool PAD, bool SYNC>
 int launch_fwd(const f256::FwdP& p, const f256::Tabs& tabs, hipStream_t st)
 {
     auto fn = slices::k_gat_fwd_slices<T, LPH, FLY, PAD, SYNC>;
-    const unsigned grid = grid_of<SYNC>(fn, p.n_rows, p.H, kWave / LPH, 1 << 20);
+    static const int resident = SYNC ? 0 : resident_workgroups(fn);
+    const unsigned grid = grid_of<SYNC>(resident, p.n_rows, p.H, kWave / LPH, 1 << 20);
     fn<<<grid, slices::kThreads<SYNC>, 0, st>>>(p, tabs);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
@@ -43,7 +44,7 @@ int launch_bwd(const f256::BwdP& p, const f256::BwdTabs& tabs, int64_t n_dst, vo
     const int sets = p.H / HS, each = sets < slices::kXcds ? 1 : sets / slices::kXcds, width = HS * p.D;
     // (room for 4 x 2048 partial rows of 256 values)
     const int most = 4 * kMaxPersistentWGs * 256 / (each * width);
-    const unsigned grid = grid_of<true>(fn, p.n_rows, sets, kWave / (LPH * HS), most);
+    const unsigned grid = grid_of<true>(0, p.n_rows, sets, kWave / (LPH * HS), most);
     fn<<<grid, slices::kThreads<true>, 0, st>>>(tabs, p, slices::SetP{rec, ds_sets, n_dst});
     SAR_LAUNCH_CHECK();
     slices::k_slices_da<<<(unsigned)(p.H * p.D), 256, 0, st>>>(p.partial, (int)(grid / slices::kXcds), sets, width, da_l);

@@ -124,6 +124,20 @@ def test_other_shapes_write_the_rows_first(dtype, H, D, K):
     assert torch.equal(rows, Ep.reshape(n, -1)) and torch.equal(dW2, dW1) and torch.equal(dX2, dX1)
 
 
+@pytest.mark.parametrize("dtype,H,D", [(torch.float32, 1, 47), (torch.bfloat16, 1, 47), (torch.float32, 1, 5),
+                                       (torch.bfloat16, 1, 5), (torch.bfloat16, 1, 9), (torch.float32, 3, 4)])
+@pytest.mark.parametrize("n,present,with_ds", [(1, None, True), (3001, 0.5, True), (3001, 0, True), (3001, 0.5, False),
+                                               (500000, 0.7, True)])
+def test_rows_of_any_width_are_written_in_pieces(dtype, H, D, n, present, with_ds):
+    """Rows that end within a piece of 16 bytes, rows shorter than one, more of them than the grid has threads: the
+    same values as the calls that store the rows."""
+    X, W, Z, ds, a_r, E, rank = make(dtype, H, D, 20, n, present, with_ds, seed=D + n)
+    Ep, dW1, dX1, da_r1, lwork = reference(X, W, Z, ds, a_r, E, rank, H, D)
+    rows = torch.full((n, H * D), float("nan"), dtype=dtype, device="cuda")
+    dW2, dX2 = fused(X, W, ds, a_r, E, rank, H, D, lwork, rows=rows)
+    assert torch.equal(rows, Ep.reshape(n, -1)) and torch.equal(dW2, dW1) and torch.equal(dX2, dX1)
+
+
 def test_no_stored_row_and_no_score_term_is_a_zero_error():
     n, H, D, K = 500, 4, 64, 100
     X, W, Z, ds, a_r, E, rank = make(torch.float32, H, D, K, n, 0.5, False, seed=3)
