@@ -1469,8 +1469,10 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         ClassLayout L = layout_from_hist(&hist[2 * P * C], 0, sar::kLongClassBlock);
         h->n_f_rows = L.n_rows;
         h->n_f_long = L.n_long;
-        for (int c = 1; c < C; ++c)
+        for (int c = 1; c < C; ++c) {
             if (hist[2 * P * C + c]) h->f_longest = ((int64_t)1 << c) - 1;
+            if (c >= sar::kHubClass) h->n_f_hub += hist[2 * P * C + c];
+        }
         memcpy(&cursors[2 * P * C], L.start, sizeof(L.start));
     }
     if (transpose) {

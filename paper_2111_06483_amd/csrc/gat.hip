@@ -46,6 +46,7 @@ struct FwdArgs {
     const uint32_t* indices;
     const uint32_t* rows;
     int64_t n_rows, n_long;
+    int64_t n_hub;       // call over all blocks: the first rows, where a large workgroup shares them (0: none does)
     int64_t n_wide;      // per-block call: rows of 8 edges and more, the head of the list
     const void* Z;       // per-block call: this block's source rows
     const float* t;      //                 and their score halves [n_src,H]; null: formed from a_l
@@ -1060,7 +1061,7 @@ f256::FwdP fwd_params(const FwdArgs& a)
 {
     f256::FwdP p{};
     p.indptr = a.indptr; p.indices = a.indices; p.rows = a.rows;
-    p.n_rows = a.n_rows; p.n_long = a.n_long;
+    p.n_rows = a.n_rows; p.n_long = a.n_long; p.n_hub = a.n_hub;
     p.Z = a.Z; p.t = a.t; p.a_l = a.a_l; p.s = a.s; p.m = a.m; p.l = a.l; p.acc = a.acc; p.out = a.out; p.L = a.L;
     p.H = a.H; p.tag_shift = a.tag_shift; p.slope = a.slope; p.act = a.act;
     p.ld = a.ldz; p.ldh = a.ldh; p.D = a.D;
@@ -1077,16 +1078,24 @@ f256::Tabs fwd_tabs(const PtrTab& zt, const PtrTab& tt)
     return tabs;
 }
 
+constexpr int kHubWaves = 12;
 // A call over all blocks.
+template <typename T, int LPH, bool FLY, bool PAD, int NW>
+int launch_fwd_waves(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, hipStream_t st)
+{
+    constexpr int B = LPH >= 8 ? 8 : 4;
+    auto fn = f256::k_gat_fwd_f256<T, LPH, B, FLY, PAD, NW>;
+    static const int resident = resident_workgroups(fn, NW * kWave);
+    fn<<<persistent_grid_for(a.n_rows, a.n_long, resident, NW), NW * kWave, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt));
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
+}
+
 template <typename T, int LPH, bool FLY, bool PAD>
 int launch_fwd_f256(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, hipStream_t st)
 {
-    constexpr int B = LPH >= 8 ? 8 : 4;
-    auto fn = f256::k_gat_fwd_f256<T, LPH, B, FLY, PAD>;
-    static const int resident = resident_workgroups(fn);
-    fn<<<persistent_grid_for(a.n_rows, a.n_long, resident), kGatherThreads, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt));
-    SAR_LAUNCH_CHECK();
-    return SAR_OK;
+    return a.n_hub > 0 ? launch_fwd_waves<T, LPH, FLY, PAD, kHubWaves>(a, zt, tt, st)
+                       : launch_fwd_waves<T, LPH, FLY, PAD, kWavesPerWG>(a, zt, tt, st);
 }
 
 template <typename T, int LPH, bool FLY, bool RAG>
@@ -1767,6 +1776,21 @@ bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
     return sweeps >= 4.0 && uses >= 2.0;
 }
 
+// Forward over all blocks by rows: how many rows at the head of the list all twelve wavefronts of a workgroup share (0:
+// workgroups of four).  A workgroup of four takes 32 edges of a row per round trip to memory, so a row of more edges than
+// its fair share (about 2048 of them run at once) decides when the launch ends.  Kernel times in us, four wavefronts /
+// twelve: a tenth of the destinations of a 2.45 M node power-law graph, 1.5 M edges, rows up to 2^14 edges, 4 x 64
+// bf16 473 / 276; 9 M edges, 8 x 32 bf16 with given scores 1169 / 1048.  Where the share is as long as the rows both take
+// the same: 20 M edges, 4 x 64 fp32, the whole layer 5770 to 5800 / 5800.  (Twelve for every long row instead of four:
+// 1215 for the second layer with sixteen, 1115 with eight, but 1 to 14 % more elsewhere.)
+int64_t shared_hubs(const sar_blocks_t* b)
+{
+    if (b->n_f_hub == 0) return 0;
+    int64_t edges = 0;
+    for (int q = 0; q < b->P; ++q) edges += b->blk[q].nnz;
+    return (b->f_longest + 1) / 2 * kMaxPersistentWGs >= edges ? b->n_f_hub : 0;
+}
+
 // Forward: heads of 32 to 128 fp32 values or 64 to 128 bf16 values (slices of 128 bytes, a cache line, and more: 64-byte
 // slices bring the neighbour's half along, 4 x 16 fp32 310 -> 440 us).  Times in us on uniform graphs, one worker of four
 // on 200 thousand nodes unless said otherwise, kernels of gat_f256.h / slices:
@@ -1858,6 +1882,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.rows = reinterpret_cast<const uint32_t*>(b->f_rows);
         a.n_rows = b->n_dst;   // the list ends with the destinations that have no in-edge: out = 0, L = -inf
         a.n_long = b->n_f_long;
+        a.n_hub = shared_hubs(b);
         a.s = s + h0;
         a.a_l = tq ? nullptr : a_l + f0;
         a.out = shift(out, f0 * hg.fb);

@@ -251,6 +251,7 @@ struct FwdP {
     const uint32_t* indices;
     const uint32_t* rows;
     int64_t n_rows, n_long;
+    int64_t n_hub;       // workgroups of more than four wavefronts: the rows that all of them share
     const void* Z;
     const float* t;      // source score halves, or null with FLY (formed from a_l and the gathered row)
     const float* a_l;
@@ -349,11 +350,11 @@ __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const Tabs& t
 }
 
 // The rows of the list, by workgroup `block` of `n_blocks`.
-template <typename T, int LPH, int B, bool ALL, bool FLY, bool PAD>
+template <typename T, int LPH, int B, bool ALL, bool FLY, bool PAD, int NW = kWavesPerWG>
 __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int n_blocks)
 {
     static_assert(B <= LPH, "a sub-batch must fit a head group");
-    __shared__ float part[kWavesPerWG][kWave][6];
+    __shared__ float part[NW][kWave][6];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // Padded geometry: a launch of fewer than 64/LPH heads leaves whole head groups without a head.
@@ -414,38 +415,54 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
         }
     };
 
-    // the long rows at the head of the list: the four wavefronts share the row
-    for (int64_t r = block; r < a.n_long; r += n_blocks) {
-        const int i = (int)a.rows[r];
-        FwdState<LPH> st;
-        init(st, i, wave == 0);
-        edges(st, i, wave, kWavesPerWG);
-        const float l = group_all<LPH, OpSum>(st.l);
+    // Rows at the head of the list are shared by a team of `team` wavefronts, each with every team-th 64 of its edges.
+    auto shared_rows = [&](auto team_c, int64_t r_begin, int64_t r_end) __attribute__((always_inline)) {
+        constexpr int team = decltype(team_c)::value, teams = NW / team;
+        const int lead = wave / team * team;
+        for (int64_t r0 = r_begin + (int64_t)block * teams; r0 < r_end; r0 += (int64_t)n_blocks * teams) {
+            const int64_t r = r0 + wave / team;
+            const bool have = teams == 1 || r < r_end;
+            FwdState<LPH> st;
+            int i = 0;
+            float l = 0.f;
+            if (have) {
+                i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
+                init(st, i, wave == lead);
+                edges(st, i, wave - lead, team);
+                l = group_all<LPH, OpSum>(st.l);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) part[wave][lane][x] = st.acc[x];
-        part[wave][lane][4] = st.m2;
-        part[wave][lane][5] = l;
-        __syncthreads();
-        if (wave == 0) {
-            float m2 = st.m2, lt = l;
-            for (int w = 1; w < kWavesPerWG; ++w) {
-                const float om = part[w][lane][4], ol = part[w][lane][5];
-                const float mn = fmaxf(m2, om);
-                const float ref = (mn == -INFINITY) ? 0.f : mn;
-                const float ca = fast_exp2(m2 - ref), cb = fast_exp2(om - ref);
-                lt = lt * ca + ol * cb;
-#pragma unroll
-                for (int x = 0; x < 4; ++x) st.acc[x] = st.acc[x] * ca + part[w][lane][x] * cb;
-                m2 = mn;
+                for (int x = 0; x < 4; ++x) part[wave][lane][x] = st.acc[x];
+                part[wave][lane][4] = st.m2;
+                part[wave][lane][5] = l;
             }
-            st.m2 = m2;
-            st.l = (k == 0) ? lt : 0.f;
-            finish(st, i);
+            __syncthreads();
+            if (have && wave == lead) {
+                float m2 = st.m2, lt = l;
+                for (int w = lead + 1; w < lead + team; ++w) {
+                    const float om = part[w][lane][4], ol = part[w][lane][5];
+                    const float mn = fmaxf(m2, om);
+                    const float ref = (mn == -INFINITY) ? 0.f : mn;
+                    const float ca = fast_exp2(m2 - ref), cb = fast_exp2(om - ref);
+                    lt = lt * ca + ol * cb;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) st.acc[x] = st.acc[x] * ca + part[w][lane][x] * cb;
+                    m2 = mn;
+                }
+                st.m2 = m2;
+                st.l = (k == 0) ? lt : 0.f;
+                finish(st, i);
+            }
+            __syncthreads();
         }
-        __syncthreads();
+    };
+    int64_t hubs = 0;
+    if constexpr (NW > kWavesPerWG) {
+        hubs = a.n_hub;
+        shared_rows(std::integral_constant<int, NW>{}, 0, hubs);
     }
-    const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
-    for (int64_t r = a.n_long + (int64_t)block * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long);
+    const int64_t n_waves = (int64_t)n_blocks * NW;
+    for (int64_t r = a.n_long + (int64_t)block * NW + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         FwdState<LPH> st;
         init(st, i, true);
@@ -454,10 +471,11 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
     }
 }
 
-template <typename T, int LPH, int B, bool FLY, bool PAD>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_fwd_f256(FwdP a, Tabs tabs)
+// NW: wavefronts of a workgroup.  Two workgroups of twelve fill a CU as far as six of four do, where registers let them.
+template <typename T, int LPH, int B, bool FLY, bool PAD, int NW>
+__global__ __launch_bounds__(NW * kWave, NW > kWavesPerWG ? 6 : 1) void k_gat_fwd_f256(FwdP a, Tabs tabs)
 {
-    fwd_rows<T, LPH, B, true, FLY, PAD>(a, tabs, (int)blockIdx.x, (int)gridDim.x);
+    fwd_rows<T, LPH, B, true, FLY, PAD, NW>(a, tabs, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ----------------------------------------------------------------- backward

@@ -328,7 +328,7 @@ inline int lanes_for(int F, int vec)
 // Workgroups that can be resident at once for kernel `fn` (persistent grids are
 // sized to this, so that every workgroup starts immediately).
 template <typename Fn>
-inline int resident_workgroups(Fn fn)
+inline int resident_workgroups(Fn fn, int threads = kGatherThreads)
 {
     static int n_cu = 0;
     if (n_cu == 0) {
@@ -338,14 +338,14 @@ inline int resident_workgroups(Fn fn)
         n_cu = prop.multiProcessorCount;
     }
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kGatherThreads, 0) != hipSuccess || per_cu <= 0)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0) != hipSuccess || per_cu <= 0)
         return kMaxPersistentWGs;
     return std::min(kMaxPersistentWGs, n_cu * per_cu);
 }
 
-inline unsigned persistent_grid_for(int64_t n_rows, int64_t n_long, int resident)
+inline unsigned persistent_grid_for(int64_t n_rows, int64_t n_long, int resident, int waves = kWavesPerWG)
 {
-    const int64_t want = n_long + (n_rows - n_long + kWavesPerWG - 1) / kWavesPerWG;
+    const int64_t want = n_long + (n_rows - n_long + waves - 1) / waves;
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, resident));
 }
 

@@ -47,6 +47,8 @@ constexpr int kLongRow = 512;
 constexpr int kLongClass = 10;       // 1 + log2(kLongRow)
 constexpr int kLongRowBlock = 128;
 constexpr int kLongClassBlock = 8;   // 1 + log2(kLongRowBlock)
+constexpr int kHubClass = 11;        // 1 + log2(kHubRow)
+constexpr int kHubRow = 1024;        // edges of a row that a large workgroup shares (forward pass over all blocks)
 constexpr int kNumClasses = 32;
 // Rows of fewer than 8 edges (degree classes 1..3, and the empty class 0) are
 // "narrow": the backward kernels process several of them per wavefront.  (Measured on the
@@ -95,6 +97,7 @@ struct sar_blocks {
     uint32_t* f_indices = nullptr; // [sum nnz]
     int32_t* f_rows = nullptr;     // destinations with deg > 0, longest class first
     int64_t n_f_rows = 0, n_f_long = 0;
+    int64_t n_f_hub = 0;           // of those, the rows of kHubRow edges and more
     int64_t f_longest = 0;         // no destination has more edges (one below a power of two); 0: not known
     int tag_shift = 0;
     // All-blocks source-side work list: (q << tag_shift) | local source id of
