@@ -1780,9 +1780,9 @@ bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
 // workgroups of four).  A workgroup of four takes 32 edges of a row per round trip to memory, so a row of more edges than
 // its fair share (about 2048 of them run at once) decides when the launch ends.  Kernel times in us, four wavefronts /
 // twelve: a tenth of the destinations of a 2.45 M node power-law graph, 1.5 M edges, rows up to 2^14 edges, 4 x 64
-// bf16 473 / 276; 9 M edges, 8 x 32 bf16 with given scores 1169 / 1048.  Where the share is as long as the rows both take
-// the same: 20 M edges, 4 x 64 fp32, the whole layer 5770 to 5800 / 5800.  (Twelve for every long row instead of four:
-// 1215 for the second layer with sixteen, 1115 with eight, but 1 to 14 % more elsewhere.)
+// bf16 473 / 276; 9 M edges, 8 x 32 bf16 with given scores 1169 / 1048.  Where a row is about as long as the share both take
+// the same: 15 M edges, 4 x 64 fp32, rows up to 2^14, whole layer 5770 to 5800 / 5800.  (Every long row by eight wavefronts
+// or by sixteen instead of teams of four, whole forward pass of the second: 1294 -> 1115 and 1215, but other layers 1 to 14 % slower.)
 int64_t shared_hubs(const sar_blocks_t* b)
 {
     if (b->n_f_hub == 0) return 0;
