@@ -520,12 +520,12 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
     const bool formed = FUSE && of_dz;
     uint4 ahead[8] = {};
     // FUSE: the lanes that share eight rows load their nine entries of the row map one each, a chunk ahead of the rows,
-    // and their ds one (row, head) each where there are lanes enough; what a lane needs it takes from the others
+    // and their ds in turn, kShare (row, head) at a time; what a lane needs it takes from the others
     constexpr int kShare = std::min(64, NW / 4);
+    constexpr int kDsOwn = FUSE ? 8 * kMaxRowsHeads / kShare : 1;
     const int rank_in = lane % kShare, share0 = lane - rank_in;
-    const bool ds_shared = FUSE && op.H * 8 <= kShare;
     int map = 0, absent = 0;      // absent: a bit for each of the eight rows that E does not have
-    float ds_one = 0.f, dsv[FUSE ? 8 : 1] = {}, ar[4];
+    float ds_own[kDsOwn] = {}, ar[4];
     if constexpr (FUSE)
 #pragma unroll
         for (int x = 0; x < 4; ++x) ar[x] = formed && op.ds ? op.a_r[from_col + x] : 0.f;
@@ -561,11 +561,11 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
             if constexpr (FUSE) {
                 if (formed) {
                     if (op.ds) {
-                        if (ds_shared)
-                            ds_one = op.ds[std::min<int64_t>(m + rank_in % 8, M - 1) * op.H + min(rank_in / 8, op.H - 1)];
-                        else
+                        const float* of_row = op.ds + std::min<int64_t>(m + rank_in % 8, M - 1) * op.H;
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) dsv[j] = op.ds[from[j] * op.H + head];
+                        for (int i = 0; i < kDsOwn; ++i)
+                            if (i == 0 || i * (kShare / 8) < op.H)
+                                ds_own[i] = of_row[min(i * (kShare / 8) + rank_in / 8, op.H - 1)];
                     }
                     if (op.rank) {
                         int rk[9];
@@ -594,10 +594,18 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
         if (!(of_dz || of_x)) return;
         // every other chunk with the sign of X turned over (see above)
         const float sign = of_x && (m0 & kDwRows) ? -1.f : 1.f;
+        float dsv[FUSE ? 8 : 1] = {};
         if constexpr (FUSE) {
-            if (formed && ds_shared) {
+            if (formed && op.ds) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) dsv[j] = op.ds ? __shfl(ds_one, share0 + head * 8 + j) : 0.f;
+                for (int i = 0; i < kDsOwn; ++i) {
+                    if (i > 0 && i * (kShare / 8) >= op.H) break;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float v = __shfl(ds_own[i], share0 + head * 8 % kShare + j);
+                        dsv[j] = i == 0 || head / (kShare / 8) == i ? v : dsv[j];
+                    }
+                }
             }
         }
         float v[4][8];

@@ -107,6 +107,12 @@ def test_rows_formed_in_the_products_equal_the_stored_rows(dtype, H, D, K, n, pr
     assert torch.equal(rows, Ep.reshape(n, -1)) and torch.equal(dW3, dW1) and torch.equal(dX3, dX1)
 
 
+@pytest.mark.parametrize("H,D,K", [(16, 4, 64), (9, 4, 40), (3, 12, 32), (5, 12, 64), (13, 8, 64), (9, 16, 100), (12, 20, 64)])
+def test_heads_that_lanes_hold_in_turns(H, D, K):
+    """dW's lanes share the ds of eight rows, 2, 4 or 8 heads at a time by the width of the rows: up to eight turns."""
+    test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, 3001, 0.6, True)
+
+
 @pytest.mark.parametrize("dtype,H,D,K", [(torch.float32, 3, 10, 100), (torch.float32, 4, 16, 256),
                                          (torch.bfloat16, 16, 16, 64), (torch.float32, 2, 200, 64),
                                          (torch.bfloat16, 4, 12, 32)])
