@@ -13,10 +13,10 @@
 // 6.0e-7 / 3.8e-7; values over ten orders of magnitude 7.8e-8 / 4.4e-8 .. 8.8e-7 / 6.3e-7.
 //
 // Infinities, NaN and finite values beyond bf16's largest (3.39e38) have no such sum: their pieces hold a NaN, so
-// every result they take part in is NaN.  A wavefront whose results hold a NaN forms them again with the fp32
-// instruction, from the operands themselves (k_gemm_split) or from pieces that carry such values whole (k_dw_split):
-// slower, with fp32's own results.  (Where a value is below 2^-109 its last pieces fall below bf16's smallest value
-// and are lost.)
+// every result they take part in is NaN.  Nor has a value below 2^-110, whose last bits are smaller than bf16's smallest
+// value.  Where results hold a NaN or operands such a small value (zero is none), a wavefront (k_dx_split) or a workgroup
+// (k_dw_split) forms its results again with the fp32 instruction from the operands themselves: slower, with fp32's own
+// results.
 #include <algorithm>
 
 #include "linear_common.h"
@@ -30,9 +30,7 @@ namespace {
 
 using namespace sar;
 
-// Eight values as three times eight bf16 values.  KEEP: values that have no such sum stay whole in the first piece
-// (infinities, NaN) or are cut instead of rounded there (finite ones), so that the three add up to the value.
-template <bool KEEP>
+// Eight values as three times eight bf16 values.
 __device__ inline void split8(const float (&v)[8], uint4 (&out)[3])
 {
     uint32_t p[3][4];
@@ -42,38 +40,25 @@ __device__ inline void split8(const float (&v)[8], uint4 (&out)[3])
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             p[t][j] = pack2_bf16(a, b);
-            if constexpr (KEEP) {
-                auto whole = [&](float x, uint32_t half) -> uint32_t {
-                    const uint32_t bits = __float_as_uint(x), size = bits & 0x7fffffffu;
-                    if (size > 0x7f800000u) return (bits >> 16) | 0x40u;            // stays a NaN
-                    return (half & 0x7fffu) == 0x7f80u ? bits >> 16 : half;         // infinity, or cut
-                };
-                p[t][j] = whole(a, p[t][j] & 0xffffu) | (whole(b, p[t][j] >> 16) << 16);
-            }
             if (t == 2) break;
-            const float a1 = __uint_as_float(p[t][j] << 16), b1 = __uint_as_float(p[t][j] & 0xffff0000u);
-            if constexpr (KEEP) {
-                a = __builtin_isfinite(a1) ? a - a1 : 0.f;
-                b = __builtin_isfinite(b1) ? b - b1 : 0.f;
-            } else {
-                a -= a1;
-                b -= b1;
-            }
+            a -= __uint_as_float(p[t][j] << 16);
+            b -= __uint_as_float(p[t][j] & 0xffff0000u);
         }
     }
 #pragma unroll
     for (int t = 0; t < 3; ++t) out[t] = make_uint4(p[t][0], p[t][1], p[t][2], p[t][3]);
 }
 
-// The eight values of three pieces that split8<true> made.
-__device__ inline void join8(const uint4 (&in)[3], float (&v)[8])
+// The smallest size met, zeros left out: twice its bits less one (zero: the largest number).
+constexpr uint32_t kLowBits = 2u * (17u << 23) - 1;      // of 2^-110
+__device__ inline uint32_t lowest(uint32_t low, const uint4& v)
 {
-    float part[3][8];
-#pragma unroll
-    for (int t = 0; t < 3; ++t) Vec<bf16_t>::unpack(in[t], part[t]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = (part[0][j] + part[1][j]) + part[2][j];
+    low = min(low, min(2u * v.x - 1u, 2u * v.y - 1u));
+    return min(low, min(2u * v.z - 1u, 2u * v.w - 1u));
 }
+// Before `next` is read: put off to where it is read itself, it keeps the values it is taken from in registers of their own
+// (dX of 8 tiles 212 -> 221 registers).
+__device__ inline void settle(uint32_t& low, float& next) { asm("" : "+v"(low), "+v"(next)); }
 
 constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 
@@ -208,6 +193,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         a[1] = load16(row + min(k + 4, k_last));
     };
     const float inv_D = FUSE ? 1.f / (float)g.op.D : 0.f;
+    uint32_t low = ~0u;          // the smallest size met in this row block
     // the eight values of a step's two pieces, zero beyond K
     auto values = [&](const uint4 (&a)[2], int step, bool has, float (&v)[8]) SAR_INLINE {
 #pragma unroll
@@ -227,11 +213,13 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
                 const float r4[4] = {ar.x, ar.y, ar.z, ar.w};
                 av = fuse_piece<float>(av, dsl[head * 32 + c], r4);
             }
+            low = lowest(low, av);
             v[4 * p] = __uint_as_float(av.x);
             v[4 * p + 1] = __uint_as_float(av.y);
             v[4 * p + 2] = __uint_as_float(av.z);
             v[4 * p + 3] = __uint_as_float(av.w);
         }
+        settle(low, v[0]);
     };
 
     // ---- the small operand: items of eight contraction values of one column
@@ -241,6 +229,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     const int item_k = (tid & 1) * 8, item_n = tid >> 1;            // (of the thread's first item; the next: 128 columns on)
     const int item_at = item_n / 32 * 192 + place(tid & 1, item_n & 31);
     uint4 bv[kPer][2];
+    uint32_t low_b = ~0u;        // the smallest size met (every row block takes the same values)
     auto load_b = [&](int step) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
@@ -250,7 +239,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         }
     };
     // (beyond K: other values of W, which meet zeros of A)
-    auto store_b = [&](int step, int buf) SAR_INLINE {
+    auto store_b = [&](int step, int buf, bool check) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
             if ((x + 1) * kThreads > NT * 64 && tid + x * kThreads >= NT * 64) break;
@@ -259,13 +248,14 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             for (int p = 0; p < 2; ++p) {
                 uint4 q = bv[x][p];
                 if (rest != 0 && step * kStep + item_k + 4 * p > k_last) q = front_of_piece<float>(q, rest);
+                if (check) low_b = lowest(low_b, q);
                 v[4 * p] = __uint_as_float(q.x);
                 v[4 * p + 1] = __uint_as_float(q.y);
                 v[4 * p + 2] = __uint_as_float(q.z);
                 v[4 * p + 3] = __uint_as_float(q.w);
             }
             uint4 piece[3];
-            split8<false>(v, piece);
+            split8(v, piece);
 #pragma unroll
             for (int t = 0; t < 3; ++t) frag[buf * kBuf + item_at + x * (kThreads / 64) * 192 + t * 64] = piece[t];
         }
@@ -327,12 +317,12 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     if constexpr (FUSE) {
         for (int k = tid; k < g.steps * kStep; k += kThreads) arl[k] = g.op.ds && k < g.K ? g.op.a_r[k] : 0.f;
     }
-    store_b(0, 0);
+    store_b(0, 0, true);
     __syncthreads();
 
     // ---- the steps
     int step = 0, buf = 0, ordinal = 0;
-    uint64_t again = 0;      // row blocks of this wavefront with a NaN (bit 63: the 64th and every later one)
+    uint64_t again = 0;      // row blocks of this wavefront to be redone (bit 63: the 64th and every later one)
     clear();
     auto turn = [&](uint4 (&cur)[2]) SAR_INLINE {
         const int after = step + 1 == g.steps ? 0 : step + 1;
@@ -345,7 +335,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         {
             float v[8];
             values(cur, step, has, v);
-            split8<false>(v, x);
+            split8(v, x);
         }
         fetch(cur);
         const uint4* fr = frag + buf * kBuf + place(gq, c);
@@ -362,13 +352,14 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             for (int i = 0; i < 3; ++i) w[i] = fr[((NT - 1) * 3 + i) * 64];
             multiply_split(x, w, acc[NT - 1]);
         }
-        store_b(after, buf ^ 1);
+        store_b(after, buf ^ 1, ordinal == 0);
         step = after;
         if (after == 0) {
-            bool nan = false;
+            bool redo = low < kLowBits;
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) nan |= any_nan(acc[nt]);
-            if (__any(nan)) again |= 1ull << min(ordinal, 63);
+            for (int nt = 0; nt < NT; ++nt) redo |= any_nan(acc[nt]);
+            if (__any(redo)) again |= 1ull << min(ordinal, 63);
+            low = ~0u;
             store_c(rb);
             rb += stride;
             ++ordinal;
@@ -384,8 +375,14 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         if (rb >= row_blocks) break;
     }
 
-    // ---- row blocks with a NaN, by the fp32 instruction (any pairing of k with instruction and lane group is valid as
-    // long as both operands use the same)
+    // ---- row blocks with a NaN or small operands, by the fp32 instruction (any pairing of k with instruction and lane group
+    // is valid as long as both operands use the same)
+    int* any_b = reinterpret_cast<int*>(split_lds);
+    if (tid == 0) *any_b = 0;
+    __syncthreads();
+    if (low_b < kLowBits) *any_b = 1;
+    __syncthreads();
+    if (*any_b) again = ~0ull;
     if (again == 0) return;
     rb -= stride * ordinal;
 #pragma unroll 1
@@ -590,8 +587,10 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
         }
         fetch_rank(m0 + kDwRows);
     };
+    uint32_t low = ~0u;           // the smallest size this thread has split
     auto commit = [&](int64_t m0, int buf, auto keep) SAR_INLINE {
         if (!(of_dz || of_x)) return;
+        constexpr bool KEEP = decltype(keep)::value;
         // every other chunk with the sign of X turned over (see above)
         const float sign = of_x && (m0 & kDwRows) ? -1.f : 1.f;
         float dsv[FUSE ? 8 : 1] = {};
@@ -620,11 +619,13 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
                 if (absent >> j & 1) r = make_uint4(0u, 0u, 0u, 0u);
                 if (formed) r = fuse_piece<float>(r, dsv[j], ar);
             }
+            if constexpr (!KEEP) low = lowest(low, r);
             v[0][j] = sign * __uint_as_float(r.x);
             v[1][j] = sign * __uint_as_float(r.y);
             v[2][j] = sign * __uint_as_float(r.z);
             v[3][j] = sign * __uint_as_float(r.w);
         }
+        settle(low, v[0][0]);
         if (left < 8) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -633,10 +634,19 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
         }
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
+            // (KEEP: the eight values themselves, in the places of the first two pieces)
             uint4 piece[3];
-            split8<decltype(keep)::value>(v[x], piece);
+            if constexpr (KEEP) {
 #pragma unroll
-            for (int t = 0; t < 3; ++t) dw_lds[buf * kBuf + t * kPlane + unit0 + (x ^ (col >> 3 & 3))] = piece[t];
+                for (int t = 0; t < 2; ++t)
+                    piece[t] = make_uint4(__float_as_uint(v[x][4 * t]), __float_as_uint(v[x][4 * t + 1]),
+                                          __float_as_uint(v[x][4 * t + 2]), __float_as_uint(v[x][4 * t + 3]));
+            } else {
+                split8(v[x], piece);
+            }
+#pragma unroll
+            for (int t = 0; t < (KEEP ? 2 : 3); ++t)
+                dw_lds[buf * kBuf + t * kPlane + unit0 + (x ^ (col >> 3 & 3))] = piece[t];
         }
     };
 
@@ -664,16 +674,16 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
 #pragma unroll
                 for (int nt = 0; nt < kNt; ++nt)
 #pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        float av[8], bv[8];
-                        join8(a[s], av);
-                        join8(b[nt][s], bv);
+                    for (int s = 0; s < 2; ++s)
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) av[j] *= sign;
+                        for (int t = 0; t < 2; ++t) {
+                            const uint4 x = a[s][t], y = b[nt][s][t];
+                            const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc[kt][nt], 0, 0, 0);
-                    }
+                            for (int j = 0; j < 4; ++j)
+                                acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                                    sign * __uint_as_float(xs[j]), __uint_as_float(ys[j]), acc[kt][nt], 0, 0, 0);
+                        }
             } else {
                 float16_t sum[kNt];
 #pragma unroll
@@ -727,14 +737,14 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
         }
     };
     slab(std::false_type{});
-    bool nan = false;
+    bool again = low < kLowBits;
 #pragma unroll
     for (int x = 0; x < kKt; ++x)
 #pragma unroll
-        for (int y = 0; y < kNt; ++y) nan |= any_nan(acc[x][y]);
+        for (int y = 0; y < kNt; ++y) again |= any_nan(acc[x][y]);
     if (tid == 0) redo = 0;
     __syncthreads();
-    if (nan) redo = 1;
+    if (again) redo = 1;
     __syncthreads();
     if (redo) slab(std::true_type{});
 

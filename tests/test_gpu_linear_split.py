@@ -67,3 +67,25 @@ def test_values_without_pieces(n, K, F, value, where):
         assert torch.equal(got[torch.isinf(got)].sign().double(), want[torch.isinf(want)].sign())
         w, e = want[finite], (got[finite].double() - want[finite]).abs()
         assert (e <= 1e-5 * torch.maximum(w.abs(), w.abs().median())).all()
+
+
+@pytest.mark.parametrize("n,K,F", [(300, 100, 64), (700, 61, 47), (26_000, 256, 40)])
+@pytest.mark.parametrize("exponent", [-111, -118, -126, -140])
+@pytest.mark.parametrize("where", ["X", "dZ", "W", "one value of dZ"])
+def test_small_values(n, K, F, exponent, where):
+    """Operands whose last bits lie below bf16's smallest value: as close as larger ones, but for the roundings of `length`
+    additions to fp32's smallest value, 2^-149, however small the result: each within half of it, 0.29 of it in the mean,
+    so sqrt(length) of it is 3.4 standard deviations of their walk.  (Measured with the fp32 instruction: 1.3e-7 of the
+    result down to 2^-126.)"""
+    X, dZ, W = operands(n, K, F, seed=F)
+    if where == "one value of dZ":
+        value = float(dZ[n - 2, 19])
+        dZ.zero_()
+        dZ[n - 2, 19] = value * 2.0 ** exponent
+    else:
+        {"X": X, "dZ": dZ, "W": W}[where].mul_(2.0 ** exponent)
+    dW, dX = backward(X, dZ, W)
+    for got, want, length in ((dX, dZ.double() @ W.double().T, F), (dW, X.double().T @ dZ.double(), n)):
+        root = max(2.0, min(length, 1024) ** 0.5)
+        err = float((got.double() - want).norm())
+        assert err < root * 2.0 ** -24 * float(want.norm()) + 2.0 ** -149 * (length * want.numel()) ** 0.5, err
