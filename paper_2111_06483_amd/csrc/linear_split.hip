@@ -14,7 +14,8 @@
 //
 // Infinities, NaN and finite values beyond bf16's largest (3.39e38) have no such sum: their pieces hold a NaN, so
 // every result they take part in is NaN.  Nor has a value below 2^-110, whose last bits are smaller than bf16's smallest
-// value.  Where results hold a NaN or operands such a small value (zero is none), a wavefront (k_dx_split) or a workgroup
+// value.  And pieces rounded up may carry a result that ends below fp32's largest value beyond it on the way.  Where results
+// hold a NaN or an infinity or operands such a small value (zero is none), a wavefront (k_dx_split) or a workgroup
 // (k_dw_split) forms its results again with the fp32 instruction from the operands themselves: slower, with fp32's own
 // results.
 #include <algorithm>
@@ -82,12 +83,13 @@ __device__ inline void multiply_split(const uint4 (&a)[3], const uint4 (&b0)[3],
     }
 }
 
-__device__ inline bool any_nan(const float16_t& v)
+// Whether an infinity or a NaN is among the results.
+__device__ inline bool not_finite(const float16_t& v)
 {
-    bool nan = false;
+    float zero[2] = {0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) nan |= __builtin_isunordered(v[r], v[r + 1]);
-    return nan;
+    for (int r = 0; r < 16; ++r) zero[r % 2] = fmaf(v[r], 0.f, zero[r % 2]);
+    return __builtin_isunordered(zero[0], zero[1]);
 }
 
 // ---- dX = dZ W^T ---------------------------------------------------------------
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         if (after == 0) {
             bool redo = low < kLowBits;
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) redo |= any_nan(acc[nt]);
+            for (int nt = 0; nt < NT; ++nt) redo |= not_finite(acc[nt]);
             if (__any(redo)) again |= 1ull << min(ordinal, 63);
             low = ~0u;
             store_c(rb);
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         if (rb >= row_blocks) break;
     }
 
-    // ---- row blocks with a NaN or small operands, by the fp32 instruction (any pairing of k with instruction and lane group
+    // ---- row blocks that are not finite or have small operands, by the fp32 instruction (any pairing of k with instruction and lane group
     // is valid as long as both operands use the same)
     int* any_b = reinterpret_cast<int*>(split_lds);
     if (tid == 0) *any_b = 0;
@@ -741,7 +743,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
 #pragma unroll
     for (int x = 0; x < kKt; ++x)
 #pragma unroll
-        for (int y = 0; y < kNt; ++y) again |= any_nan(acc[x][y]);
+        for (int y = 0; y < kNt; ++y) again |= not_finite(acc[x][y]);
     if (tid == 0) redo = 0;
     __syncthreads();
     if (again) redo = 1;

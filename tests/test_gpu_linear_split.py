@@ -89,3 +89,16 @@ def test_small_values(n, K, F, exponent, where):
         root = max(2.0, min(length, 1024) ** 0.5)
         err = float((got.double() - want).norm())
         assert err < root * 2.0 ** -24 * float(want.norm()) + 2.0 ** -149 * (length * want.numel()) ** 0.5, err
+
+
+@pytest.mark.parametrize("n,K,F", [(300, 100, 64), (700, 61, 47), (26_000, 256, 40)])
+@pytest.mark.parametrize("value", [1.7e38, -1.7e38])
+def test_results_near_the_largest_value(n, K, F, value):
+    """1.9963 rounds up to 2 in its first piece, and 2 x 1.7e38 to beyond 3.4028e38 before the other pieces bring it back."""
+    X, dZ, W = (torch.zeros_like(t) for t in operands(n, K, F, seed=1))
+    X[n - 2, 5], dZ[n - 2, 19], W[7, 19] = 1.9963, value * 1.0022, 1.9963
+    dW, dX = backward(X, dZ, W)
+    for got, want in ((dX, dZ.double() @ W.double().T), (dW, X.double().T @ dZ.double())):
+        assert float(want.abs().max()) > 3.39e38
+        # (one product: rounded once by the fp32 instruction)
+        assert float(((got.double() - want) / want.abs().max()).abs().max()) <= 2.0 ** -24
