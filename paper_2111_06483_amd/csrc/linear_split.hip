@@ -1,16 +1,12 @@
 // The fp32 products of the dense transform on the bf16 matrix cores.
 //
 // An fp32 value is the exact sum of three bf16 values, x = x1 + x2 + x3 (24 significant bits in pieces of 8, each
-// rounded to nearest), and the products of two such sums are exact in the matrix cores' fp32 sums.  Of the nine
+// rounded to nearest), and the product of two pieces is exact in fp32.  Of the nine
 // partial products x3 y2, x2 y3 and x3 y3 are left out (below 2^-23 of |x y|, of either sign); the other six are added
 // smallest first:
 //     x3 y1, x1 y3, x2 y2, x2 y1, x1 y2, x1 y1.
 // V_MFMA_F32_32X32X16_BF16 takes 16 contraction values where V_MFMA_F32_32X32X2_F32 takes 2, in half the cycles, so
-// six of them do in 192 cycles what the fp32 instruction does in 512; and a sum is rounded six times per 16 products
-// instead of sixteen times.  Measured error against 64-bit sums (2-norm over the result's; normal x normal; fp32
-// instruction / six bf16 ones): K = 16 7.4e-8 / 3.3e-8, 112 1.9e-7 / 1.5e-7, 256 2.9e-7 / 2.4e-7, 400 3.6e-7 /
-// 3.0e-7, 2048 8.0e-7 / 7.0e-7; uniform in [0,1) 6.2e-8 / 3.2e-8, 1.5e-7 / 1.2e-7, 2.2e-7 / 1.8e-7, 3.0e-7 / 2.4e-7,
-// 6.0e-7 / 3.8e-7; values over ten orders of magnitude 7.8e-8 / 4.4e-8 .. 8.8e-7 / 6.3e-7.
+// six of them do in 192 cycles what the fp32 instruction does in 512.  Errors stand at the kernels.
 //
 // Infinities, NaN and finite values beyond bf16's largest (3.39e38) have no such sum: their pieces hold a NaN, so
 // every result they take part in is NaN.  Nor has a value below 2^-110, whose last bits are smaller than bf16's smallest
@@ -63,24 +59,13 @@ __device__ inline void settle(uint32_t& low, float& next) { asm("" : "+v"(low), 
 
 constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 
-__device__ inline void multiply_split(const uint4 (&a)[3], const uint4 (&b)[3], float16_t& acc)
+__device__ inline void multiply_split(const uint4 (&a)[3], const uint4 (&b)[3], float16_t& sum)
 {
+    sum = float16_t{};
 #pragma unroll
     for (int t = 0; t < 6; ++t)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[kTerm[t][0]]),
-                                                      __builtin_bit_cast(bf16x8_t, b[kTerm[t][1]]), acc, 0, 0, 0);
-}
-
-// two results in turn, so that no instruction waits for the sum of the one before it
-__device__ inline void multiply_split(const uint4 (&a)[3], const uint4 (&b0)[3], const uint4 (&b1)[3], float16_t& acc0,
-                                      float16_t& acc1)
-{
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, a[kTerm[t][0]]);
-        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(bf16x8_t, b0[kTerm[t][1]]), acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(bf16x8_t, b1[kTerm[t][1]]), acc1, 0, 0, 0);
-    }
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[kTerm[t][0]]),
+                                                      __builtin_bit_cast(bf16x8_t, b[kTerm[t][1]]), sum, 0, 0, 0);
 }
 
 // Whether an infinity or a NaN is among the results.
@@ -102,13 +87,20 @@ __device__ inline bool not_finite(const float16_t& v)
 // row block, and the first steps of the next block travel while this one is stored.  Two to four workgroups per CU,
 // which do not wait for each other; the slabs of the same rows run on one XCD, whose L2 serves the rows again.
 //
+// The matrix cores cut a product's bits below the sum's instead of rounding them, always downwards.  Small terms added to a
+// long sum left errors of one sign: their mean was 0.06 to 0.14 of their standard deviation (normal values, 17 to 512
+// products a result; the fp32 instruction: 0.001), and up to 0.44 of it in a column of non-negative values, and the next
+// layer sums dX over all nodes.  So a step's 16 products are summed by themselves, small terms first, and added by vector
+// instructions, which round to nearest; and every other row and step takes A with the other sign.  Error against 64-bit
+// sums, fp32 instruction / here: 17 products 7.7e-8 / 4.2e-8, 64 1.5e-7 / 5.2e-8, 256 2.9e-7 / 8.4e-8, 400 3.6e-7 / 1.0e-7;
+// uniform in (0, 1) 6.5e-8 / 4.1e-8, 1.2e-7 / 4.1e-8, 2.2e-7 / 6.0e-8, 2.9e-7 / 7.6e-8.
+//
 // FUSE: the rows of A are formed where they are split (RowsOp).
 //
-// Bound by power in wide products (the matrix cores alone sustain 1.7 PFLOP/s of bf16 on random values; 306250 x 256 x
-// 256 is 0.24 Pflop there) and by memory latency in narrow ones.  dX against the fp32 instruction, plain / with formed
-// rows, us: 306250 rows 256 -> 256 340 / 359 -> 265 / 282, 256 -> 100 182..197 / 200 -> 157 / 162; 2450000 rows 400 ->
-// 400 7880 -> 4990; 75000 rows 128 -> 128 40 / 43 -> 24 / 31; 8000 rows 256 -> 256 33 / 37 -> 15 / 19; 100 rows 128 ->
-// 100 17 / 19 -> 9 / 12.  (Also measured: one workgroup of eight wavefronts per CU, of which four split before they
+// Bound by the matrix instructions of a wavefront and the vector instructions around them, which overlap in part, and by
+// memory latency in narrow products.  dX against the fp32 instruction, plain / with formed rows, us: 306250 rows 256 -> 256
+// 349 / 361 -> 290 / 303, 256 -> 100 183 / 196 -> 145 / 163; 2450000 rows 400 -> 400 7930 -> 5530; 75000 rows 128 -> 128
+// 40 / 42 -> 26 / 32; 8000 rows 256 -> 256 34 / 37 -> 18 / 22; 100 rows 128 -> 100 17 / 19 -> 10 / 13.  (Also measured: one workgroup of eight wavefronts per CU, of which four split before they
 // multiply and four after, the same within 5%, small products slower; steps of 32 values and results stored during the
 // next block's steps, 10 to 20% slower.)
 constexpr int kThreads = 256;
@@ -196,8 +188,8 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     };
     const float inv_D = FUSE ? 1.f / (float)g.op.D : 0.f;
     uint32_t low = ~0u;          // the smallest size met in this row block
-    // the eight values of a step's two pieces, zero beyond K
-    auto values = [&](const uint4 (&a)[2], int step, bool has, float (&v)[8]) SAR_INLINE {
+    // the eight values of a step's two pieces, zero beyond K; turned: a sign bit that they take over
+    auto values = [&](const uint4 (&a)[2], int step, bool has, uint32_t turned, float (&v)[8]) SAR_INLINE {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint4 av = a[p];
@@ -216,10 +208,10 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
                 av = fuse_piece<float>(av, dsl[head * 32 + c], r4);
             }
             low = lowest(low, av);
-            v[4 * p] = __uint_as_float(av.x);
-            v[4 * p + 1] = __uint_as_float(av.y);
-            v[4 * p + 2] = __uint_as_float(av.z);
-            v[4 * p + 3] = __uint_as_float(av.w);
+            v[4 * p] = __uint_as_float(av.x ^ turned);
+            v[4 * p + 1] = __uint_as_float(av.y ^ turned);
+            v[4 * p + 2] = __uint_as_float(av.z ^ turned);
+            v[4 * p + 3] = __uint_as_float(av.w ^ turned);
         }
         settle(low, v[0]);
     };
@@ -336,24 +328,34 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         uint4 x[3];
         {
             float v[8];
-            values(cur, step, has, v);
+            values(cur, step, has, (uint32_t)(c + step) << 31, v);
             split8(v, x);
         }
         fetch(cur);
         const uint4* fr = frag + buf * kBuf + place(gq, c);
+        const float sign = step % 2 ? -1.f : 1.f;
+        // A tile's 16 products are summed from zero and added to its results by vector instructions, where registers allow
+        // while the next tile's are multiplied.
+        constexpr int kSums = !FUSE && NT > 4 ? 2 : 1;
+        float16_t sum[kSums];
+        auto add = [&](int nt) SAR_INLINE {
 #pragma unroll
-        for (int nt = 0; nt + 1 < NT; nt += 2) {
-            uint4 w[2][3];
+            for (int r = 0; r < 16; ++r) {
+                float v = fmaf(r % 2 ? -sign : sign, sum[nt % kSums][r], acc[nt][r]);
+                asm("" : "+v"(v));      // (or the compiler puts off the additions of every tile to the step's end)
+                acc[nt][r] = v;
+            }
+        };
 #pragma unroll
-            for (int i = 0; i < 6; ++i) w[i / 3][i % 3] = fr[(nt * 3 + i) * 64];
-            multiply_split(x, w[0], w[1], acc[nt], acc[nt + 1]);
-        }
-        if constexpr (NT % 2 != 0) {
+        for (int nt = 0; nt < NT; ++nt) {
             uint4 w[3];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) w[i] = fr[((NT - 1) * 3 + i) * 64];
-            multiply_split(x, w, acc[NT - 1]);
+            for (int i = 0; i < 3; ++i) w[i] = fr[(nt * 3 + i) * 64];
+            multiply_split(x, w, sum[nt % kSums]);
+            if (nt >= kSums - 1) add(nt - (kSums - 1));
+            if (kSums == 2) __builtin_amdgcn_sched_barrier(0);
         }
+        if (kSums == 2) add(NT - 1);
         store_b(after, buf ^ 1, ordinal == 0);
         step = after;
         if (after == 0) {
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             uint4 piece[2];
             float v[8];
             load_a(row, s, piece);
-            values(piece, s, has, v);
+            values(piece, s, has, 0, v);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const int n = min(n0 + nt * 32 + c, g.N - 1);

@@ -49,6 +49,20 @@ def test_sums_of_many_rows_lean_to_no_side():
     assert abs(float(d.mean())) < 0.1 * float(d.std())
 
 
+@pytest.mark.parametrize("F", [17, 64, 256, 400])
+@pytest.mark.parametrize("kind", ["normal", "uniform"])
+def test_rows_of_errors_lean_to_no_side(F, kind):
+    """dX is the next layer's error and is summed over all nodes there: its mean error, over all of it and over each
+    column, is what independent roundings leave, 1/2500 and 1/316 of their size (ten and six of which are allowed)."""
+    X, dZ, W = operands(100_000, 64, F, seed=9)
+    if kind == "uniform":
+        dZ, W = (torch.special.ndtr(t) for t in (dZ, W))
+    _, dX = backward(X, dZ, W)
+    d = dX.double() - dZ.double() @ W.double().T
+    assert abs(float(d.mean())) < 10 / 2500 * float(d.std())
+    assert float((d.mean(0) / d.std(0)).abs().max()) < 6 / 316
+
+
 @pytest.mark.parametrize("n,K,F", [(300, 100, 64), (2_000, 256, 100), (700, 61, 47)])
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 @pytest.mark.parametrize("where", ["X", "dZ", "W"])
