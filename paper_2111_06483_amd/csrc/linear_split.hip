@@ -470,7 +470,9 @@ int split_tiles(int64_t M, int N, int most, int* slabs)
 // large ones, and the chunk's sum is added to the slab's by vector instructions, which round to nearest; and every other
 // chunk's X is taken with the other sign and its sum subtracted, so that what is cut falls on either side.  Error of dW
 // against 64-bit sums, fp32 instruction and here: 306250 rows 256 x 256 6.3e-7 / 1.9e-7, 2450000 rows 400 x 400 3.5e-6 /
-// 6.3e-7, 4096 rows 64 x 64 1.3e-7 / 0.9e-7, 1000 rows 100 x 256 2.2e-7 / 0.8e-7.
+// 6.3e-7, 4096 rows 64 x 64 1.3e-7 / 0.9e-7, 1000 rows 100 x 256 2.2e-7 / 0.8e-7; 64 x 64 of 1, 2, 3, 4, 8 rows 2.5e-8 / 3.5e-8,
+// 3.1e-8 / 3.4e-8, 3.9e-8 / 3.2e-8, 4.1e-8 / 3.2e-8, 4.8e-8 / 3.1e-8: a product's last addition is cut and not rounded, so one or
+// two rows stay with the fp32 instruction.  (A result whose other products are zeros is as far off as one of one row.)
 //
 // A chunk is on its way while the one before it is split and the one before that is multiplied.  Of the two wavefronts
 // of a SIMD one splits before it multiplies and the other after, so that the vector instructions of one run beside the
@@ -740,8 +742,9 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
             __syncthreads();
         }
     };
-    slab(std::false_type{});
-    bool again = low < kLowBits;
+    // (sums of one or two products: closer by the fp32 instruction, see above)
+    if (M > 2) slab(std::false_type{});
+    bool again = M <= 2 || low < kLowBits;
 #pragma unroll
     for (int x = 0; x < kKt; ++x)
 #pragma unroll

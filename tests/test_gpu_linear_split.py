@@ -40,6 +40,34 @@ def test_sums_against_64_bits(n, K, F):
         assert err < max(2.0, min(length, 1024) ** 0.5) * 2.0 ** -24, err
 
 
+@pytest.mark.parametrize("length", [1, 2, 3, 5, 9, 15, 16, 17, 31, 33, 100, 257, 400, 2000])
+@pytest.mark.parametrize("kind", ["normal", "uniform"])
+def test_no_further_off_than_the_fp32_instruction(length, kind):
+    """The forward product forms the same sums with the fp32 instruction: dW = (X^T) dZ over `length` rows and, from 17
+    products on, dX = dZ (W^T).  (One and two rows: the same instruction, so the same error but for the order of two.)"""
+    def pair(n, K, F):
+        X, dZ, W = operands(n, K, F, seed=length)
+        return (X, dZ, W) if kind == "normal" else tuple(torch.special.ndtr(t) for t in (X, dZ, W))
+
+    def off(got, want):
+        return float((got.double() - want).norm() / want.norm())
+
+    X, dZ, _ = pair(length, 200, 100)
+    dW, by_fp32 = torch.zeros(200, 100, device="cuda"), torch.empty(200, 100, device="cuda")
+    work = torch.empty(sar.sar_linear_workspace_bytes(length, 200, 100) // 4, device="cuda")
+    sar.sar_linear_bwd(X, dZ, None, dW, None, work)
+    sar.sar_linear_fwd(X.T.contiguous(), dZ, by_fp32)
+    want = X.double().T @ dZ.double()
+    assert off(dW, want) <= 1.02 * off(by_fp32, want)
+    if length > 16:
+        _, dZ, W = pair(3000, 100, length)
+        dX, by_fp32 = torch.empty(3000, 100, device="cuda"), torch.empty(3000, 100, device="cuda")
+        sar.sar_linear_bwd(None, dZ, W, None, dX, None)
+        sar.sar_linear_fwd(dZ, W.T.contiguous(), by_fp32)
+        want = dZ.double() @ W.double().T
+        assert off(dX, want) <= 1.02 * off(by_fp32, want)
+
+
 def test_sums_of_many_rows_lean_to_no_side():
     """The matrix cores cut small terms downwards; over a million rows the sums must not drift (the mean error of all
     entries, which independent roundings bring to 1/64 of their size)."""
