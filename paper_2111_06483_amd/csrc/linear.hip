@@ -1347,7 +1347,9 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
     if (dX) {
         // dX[n,K] = dZ W^T : B(k = f, n = kcol) = W[kcol * F + f]
         SkinnyPlan plan;
-        if (dtype == SAR_F32 && F > 16) {      // (shorter sums: not measured)
+        // (shorter sums: not measured; dX in the place of dZ: k_dx_split reads a row again after parts of dX are stored, for
+        // its other columns and for rows that are redone, k_gemm_skinny of one slab has read its rows by then)
+        if (dtype == SAR_F32 && F > 16 && dX != dZ) {
             SAR_TRY(sar::split_dx(static_cast<const float*>(dZ), op, W, static_cast<float*>(dX), n, K, F, st));
         } else if (plan_skinny(F, K, dtype, 0, &plan)) {
             SkinnyArgs sk{dZ, F, n, W, 1, F, dX, K, F, K, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,

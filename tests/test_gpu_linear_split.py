@@ -144,3 +144,19 @@ def test_results_near_the_largest_value(n, K, F, value):
         assert float(want.abs().max()) > 3.39e38
         # (one product: rounded once by the fp32 instruction)
         assert float(((got.double() - want) / want.abs().max()).abs().max()) <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,H,D", [(1, 4, 16), (1000, 4, 32), (3001, 5, 20), (40_000, 2, 64)])
+@pytest.mark.parametrize("formed", [False, True])
+def test_in_place(n, H, D, formed):
+    """dX written over dZ (at these widths): the kernel whose wavefronts read whole rows before they store any of them."""
+    F = H * D
+    X, dZ, W = operands(n, F, F, seed=n)
+    want = dZ.double() @ W.double().T
+    if formed:
+        ds, a_r = torch.randn(n, H, device="cuda"), torch.randn(H, D, device="cuda")
+        want = (dZ.double() + (ds.double()[:, :, None] * a_r.double()).reshape(n, F)) @ W.double().T
+        sar.sar_linear_bwd_rows(None, dZ, None, ds, a_r, H, D, W, None, dZ, n, torch.float32, None)
+    else:
+        sar.sar_linear_bwd(None, dZ, W, None, dZ, None)
+    assert float((dZ.double() - want).norm() / want.norm()) < F ** 0.5 * 2.0 ** -24
