@@ -72,6 +72,18 @@ __device__ inline bool go_on(bool left, int turn)
     return __builtin_amdgcn_ballot_w64(left) != 0;
 }
 
+// Edges behind a row's end (its last one again) hold zeros: weight 0 alone would turn an infinity of theirs into a NaN.
+// (Most batches have none: one test each.)
+template <int B, typename Raw>
+__device__ inline void zero_behind(Raw (&raw)[B], int left)
+{
+    if (__builtin_amdgcn_ballot_w64(left < B) == 0) return;
+    static_for<B>([&](auto kk) {
+        constexpr int K = decltype(kk)::value;
+        if (K >= left) raw[K] = Raw{};
+    });
+}
+
 template <int LPH, int K>
 __device__ inline uint32_t bcast_u(uint32_t v)
 {
@@ -127,6 +139,7 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
                                           (uint64_t)bcast_u<LPH, K>((uint32_t)(row >> 32)) << 32;
                     raw[K] = load_lane<T, PAD>(reinterpret_cast<const T*>(from), foff, on);
                 });
+                zero_behind(raw, len - e0);
                 const bool valid = k < B && e0 + k < len;
                 float tv = 0.f;
                 if constexpr (FLY) {
@@ -305,6 +318,7 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
                     constexpr int K = decltype(kk)::value;
                     raw[K] = load_lane<T, false>(Gp + (uint64_t)bcast_u<LPH, K>((uint32_t)mine) * (uint32_t)a.ld, 0, true);
                 });
+                zero_behind(raw, len - e0);
                 const bool valid = live && k < B && e0 + k < len;
                 const float4 rec = rec_of[(int64_t)mine * HS];
                 float c_mine = 0.f;

@@ -95,3 +95,49 @@ def test_layer(n_own, n_other, P, deg, H, D, dtype, shipped, relu, compact):
         close(x, y, 1e-5)
     close(res[0][2], res[1][2], 1e-5)
     close(res[0][3], res[1][3], 1e-5)
+
+
+@pytest.mark.parametrize("n_own,n_other,P,deg,H,D", [SHAPES[0], SHAPES[1], SHAPES[2], (17_000, 9_000, 2, 55, 2, 100),
+                                                        SHAPES[6], SHAPES[9]])
+def test_infinities_stay_with_their_edges(n_own, n_other, P, deg, H, D):
+    """An infinity in the last row that a destination (backward: a source) gathers, with longer rows beside it: the result
+    it belongs to is infinite and no result is NaN."""
+    b, Zs, a_l, a_r, G = layer(n_own, n_other, P, deg, H, D, torch.float32, seed=D, compact=False)
+    n, inf = b.n_dst, float("inf")
+    edges = []          # (destination, local source) by block
+    for q in range(P):
+        v = gu.view_arrays(b, q)
+        ip, ix = (torch.as_tensor(v[k]).long().cuda() for k in ("indptr", "indices"))
+        edges.append((torch.repeat_interleave(torch.arange(n, device="cuda"), ip[1:] - ip[:-1]), ix))
+    a_l, Zs, G = a_l.abs() + 0.01, [z.abs() + 0.01 for z in Zs], G.abs() + 0.01
+    tq = [torch.empty(b.n_src(q), H, device="cuda") for q in range(P)]
+    for q in range(P):
+        sar.sar_gat_scores(Zs[q], a_l, tq[q])
+    s = torch.zeros(n, H, device="cuda")
+    out, L = torch.empty(n, H, D, device="cuda"), torch.empty(n, H, device="cuda")
+    sar.sar_gat_fwd_all(b, Zs, s, tq, a_l, 0.2, out, L, sar.SAR_ACT_NONE)
+    rec, ds = torch.empty(n, H, 4, device="cuda"), torch.empty(n, H, device="cuda")
+    sar.sar_gat_bwd_begin(G, out, s, L, rec, ds)
+
+    dst, src = edges[P - 1]
+    last = int(src.max())
+    Zi = [z.clone() for z in Zs]
+    Zi[P - 1][last, 0, D - 1] = inf
+    out2 = torch.empty_like(out)
+    sar.sar_gat_fwd_all(b, Zi, s, tq, a_l, 0.2, out2, torch.empty_like(L), sar.SAR_ACT_NONE)
+    want = torch.isinf(out)
+    want[dst[src == last], 0, D - 1] = True
+    assert bool(want.any()) and torch.equal(out2 == inf, want) and not torch.isnan(out2).any()
+
+    if (n_own, n_other, P, deg, H, D) not in SHAPES[:4]:       # (the backward pass by other kernels)
+        return
+    i = max(int(d.max()) for d, _ in edges)
+    Gi = G.clone()
+    Gi[i, 0, 0] = inf
+    dZ = [torch.zeros(b.n_src(q), H, D, device="cuda") for q in range(P)]
+    work = torch.empty(sar.sar_gat_workspace_bytes(n, max(b.n_src(q) for q in range(P)), H, D) // 4, device="cuda")
+    sar.sar_gat_bwd_all(b, Zs, Gi, tq, rec, a_l, 0.2, dZ, None, ds, torch.zeros(H, D, device="cuda"), work)
+    for q in range(P):
+        want = torch.zeros(b.n_src(q), H, dtype=torch.bool, device="cuda")
+        want[edges[q][1][edges[q][0] == i], 0] = True
+        assert torch.equal((dZ[q] == inf).all(-1), want) and not torch.isnan(dZ[q]).any()
