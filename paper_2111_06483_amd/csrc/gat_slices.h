@@ -4,12 +4,13 @@
 // kernels of gat_f256.h take each of those reads from memory: the rows in use at a time do not fit in an XCD's 4 MiB of
 // L2.  Here workgroup b serves head b % 8, and workgroups are dealt to the eight XCDs in that order, so that an XCD's L2
 // holds slices of one head only; and a lane group of LPH = D/4 lanes owns a row of its own, so that 64/LPH rows a
-// wavefront, eight thousand an XCD with 32 lanes a row, are walked at a time.  Their edges are sorted by source and the
+// wavefront, a thousand an XCD with 32 lanes a row, are walked at a time.  Their edges are sorted by source and the
 // rows by number of edges, so at any time the rows of an XCD are at about the same place of the source list: they sweep
 // over it together, a slice is fetched once a sweep and the other rows that cite it find it in L2.
 // (Performance only: nothing depends on where a workgroup runs.)
 //
-// The arithmetic of a row is that of gat_f256.h, batch by batch and lane by lane: the results are the same bits.
+// The arithmetic of a row is that of gat_f256.h, batch by batch and lane by lane: the same bits where one wavefront walks
+// the row there (256 values, fewer edges than workgroups share).
 #pragma once
 
 #include "gat_f256.h"
@@ -197,7 +198,8 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
 
 // ------------------------------------------------------------------ backward, all blocks
 //
-// The sources of at least 8 edges, source by source as in k_gat_bwd_f256, a slice being HS heads of 128 values together.
+// The sources of at least 8 edges, source by source as in k_gat_bwd_f256, a slice being HS heads of 128 values together; one
+// or two slices to a row.
 // What is added to ds costs more than what is read here: the chip takes some 20 additions a nanosecond, one for every
 // edge and set of heads (one head of 32 values at a time, 8 sets: 5.1 ms for 25M edges, fp32 and bf16 alike, where the
 // rows take 2 ms), and a destination's record is a request to L2 of its own as well.  So slices are as wide as lets the
@@ -233,18 +235,16 @@ __global__ __launch_bounds__(256) void k_slices_end(const float* __restrict__ fr
     }
 }
 
-// da_l[set * width + f] += sum over the set's workgroups of partial[workgroup][f]; a workgroup's sets are `sets of it`
-// rows of partial, in the order it takes them
+// da_l[set * width + f] += sum over the set's workgroups of partial[workgroup][f]
 static __global__ __launch_bounds__(256) void k_slices_da(const float* __restrict__ partial, int n_wgs, int sets, int width,
                                                    float* __restrict__ da_l)
 {
     __shared__ float red[256];
-    const int set = blockIdx.x / width, f = blockIdx.x % width;
-    const int parts = sets < kXcds ? kXcds / sets : 1, each = sets < kXcds ? 1 : sets / kXcds;
+    const int set = blockIdx.x / width, f = blockIdx.x % width, parts = kXcds / sets;
     float s = 0.f;
     for (int w = threadIdx.x; w < n_wgs * parts; w += 256) {
-        const int wg = w / parts * kXcds + w % parts * min(sets, kXcds) + set % kXcds;
-        s += partial[((int64_t)wg * each + set / kXcds) * width + f];
+        const int wg = w / parts * kXcds + w % parts * sets + set;
+        s += partial[(int64_t)wg * width + f];
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -284,99 +284,96 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
     const int slot = lane / kLanes, hh = lane % kLanes / LPH, k = lane % LPH;
     const uint32_t mask = (1u << a.tag_shift) - 1u;
     const Unit<SYNC> u(a.H / HS);
-    for (int set = u.set, turn_of = 0; set < u.sets; set += kXcds, ++turn_of) {
-        const int h = set * HS + hh, foff = h * D + 4 * k;
-        const T* Gp = static_cast<const T*>(a.G) + foff;
-        const float4* rec_of = sp.rec + (int64_t)set * sp.n_dst * HS + hh;
-        float* ds_of = sp.ds + (int64_t)set * sp.n_dst * HS + hh;
-        float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4] = {0.f, 0.f, 0.f, 0.f};
-        load_f32<4>(a.a_l + foff, al);
-        int64_t r0 = u.first(wave, kSlots);
-        for (int64_t w0 = SYNC ? u.first(0, kSlots) : r0; w0 < a.n_rows; w0 += u.stride(kSlots), r0 += u.stride(kSlots)) {
-            const bool live = r0 + slot < a.n_rows;
-            const uint32_t id = a.rows[live ? r0 + slot : a.n_rows - 1];
-            const int q = (int)(id >> a.tag_shift), j = (int)(id & mask);
-            const int32_t* idx = s_ix[q];
-            const int beg = s_ip[q][j], len = s_ip[q][j + 1] - beg;      // (at least 8)
-            float zj[4];
-            Row4<T>::unpack(load_lane<T, false>(s_Z[q] + (int64_t)j * a.ld, foff, true), zj);
-            float t2;
-            if (s_t[q]) {
-                t2 = f256::score_log2(s_t[q][(int64_t)j * a.ldh + h]);
-            } else {
-                float c = al[0] * zj[0];
+    const int h = u.set * HS + hh, foff = h * D + 4 * k;
+    const T* Gp = static_cast<const T*>(a.G) + foff;
+    const float4* rec_of = sp.rec + (int64_t)u.set * sp.n_dst * HS + hh;
+    float* ds_of = sp.ds + (int64_t)u.set * sp.n_dst * HS + hh;
+    float al[4] = {0.f, 0.f, 0.f, 0.f}, dal[4] = {0.f, 0.f, 0.f, 0.f};
+    load_f32<4>(a.a_l + foff, al);
+    int64_t r0 = u.first(wave, kSlots);
+    for (int64_t w0 = SYNC ? u.first(0, kSlots) : r0; w0 < a.n_rows; w0 += u.stride(kSlots), r0 += u.stride(kSlots)) {
+        const bool live = r0 + slot < a.n_rows;
+        const uint32_t id = a.rows[live ? r0 + slot : a.n_rows - 1];
+        const int q = (int)(id >> a.tag_shift), j = (int)(id & mask);
+        const int32_t* idx = s_ix[q];
+        const int beg = s_ip[q][j], len = s_ip[q][j + 1] - beg;      // (at least 8)
+        float zj[4];
+        Row4<T>::unpack(load_lane<T, false>(s_Z[q] + (int64_t)j * a.ld, foff, true), zj);
+        float t2;
+        if (s_t[q]) {
+            t2 = f256::score_log2(s_t[q][(int64_t)j * a.ldh + h]);
+        } else {
+            float c = al[0] * zj[0];
 #pragma unroll
-                for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
-                t2 = f256::score_log2(group_all<LPH, OpSum>(c));
-            }
-            float dz[4] = {0.f, 0.f, 0.f, 0.f}, dt = 0.f;
-            int mine = idx[beg + min(k, len - 1)];
-            for (int e0 = 0, turn = 0; go_on<SYNC>(e0 < len, turn); e0 += B, ++turn) {
-                const int next = idx[beg + min(e0 + B + k, len - 1)];
-                typename Row4<T>::Raw raw[B];
-                static_for<B>([&](auto kk) {
-                    constexpr int K = decltype(kk)::value;
-                    raw[K] = load_lane<T, false>(Gp + (uint64_t)bcast_u<LPH, K>((uint32_t)mine) * (uint32_t)a.ld, 0, true);
-                });
-                zero_behind(raw, len - e0);
-                const bool valid = live && k < B && e0 + k < len;
-                const float4 rec = rec_of[(int64_t)mine * HS];
-                float c_mine = 0.f;
-                static_for<B>([&](auto kk) {
-                    constexpr int K = decltype(kk)::value;
-                    float g[4];
-                    Row4<T>::unpack(raw[K], g);
-                    float c = g[0] * zj[0];
-#pragma unroll
-                    for (int x = 1; x < 4; ++x) c = fmaf(g[x], zj[x], c);
-                    c = group_all<LPH, OpSum>(c);
-                    c_mine = k == K ? c : c_mine;
-                });
-                const float u2 = rec.x + t2;
-                const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
-                const float de = alpha * (c_mine - rec.z);
-                const float du = u2 > 0.f ? de : a.slope * de;
-                dt += valid ? du : 0.f;
-                if (valid) unsafeAtomicAdd(ds_of + (int64_t)mine * HS, du);
-                static_for<B>([&](auto kk) {
-                    constexpr int K = decltype(kk)::value;
-                    const float ak = group_bcast<LPH, K>(alpha);
-                    float g[4];
-                    Row4<T>::unpack(raw[K], g);
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) dz[x] = fmaf(ak, g[x], dz[x]);
-                });
-                mine = next;
-            }
-            // dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j
-            dt = group_all<LPH, OpSum>(dt);
-            if (live) {
-                float v[4];
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    v[x] = fmaf(dt, al[x], dz[x]);
-                    dal[x] = fmaf(dt, zj[x], dal[x]);
-                }
-                const int64_t jo = s_rank[q] ? s_rank[q][j] : j;
-                store_lane<T, false>(s_dZ[q] + jo * a.ld, foff, true, v);
-                if (k == 0 && s_dt[q]) s_dt[q][jo * a.ldh + h] = dt;
-            }
+            for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
+            t2 = f256::score_log2(group_all<LPH, OpSum>(c));
         }
-        // this workgroup's share of the set's da_l
-        __syncthreads();
+        float dz[4] = {0.f, 0.f, 0.f, 0.f}, dt = 0.f;
+        int mine = idx[beg + min(k, len - 1)];
+        for (int e0 = 0, turn = 0; go_on<SYNC>(e0 < len, turn); e0 += B, ++turn) {
+            const int next = idx[beg + min(e0 + B + k, len - 1)];
+            typename Row4<T>::Raw raw[B];
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                raw[K] = load_lane<T, false>(Gp + (uint64_t)bcast_u<LPH, K>((uint32_t)mine) * (uint32_t)a.ld, 0, true);
+            });
+            zero_behind(raw, len - e0);
+            const bool valid = live && k < B && e0 + k < len;
+            const float4 rec = rec_of[(int64_t)mine * HS];
+            float c_mine = 0.f;
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                float g[4];
+                Row4<T>::unpack(raw[K], g);
+                float c = g[0] * zj[0];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) part[wave][lane][x] = dal[x];
-        __syncthreads();
-        constexpr int width = HS * D;
-        const int each = u.sets < kXcds ? 1 : u.sets / kXcds;
-        if ((int)threadIdx.x < width) {
-            const int f = (int)threadIdx.x, from = f / D * LPH + f % D / 4, x = f % 4;
-            float s = 0.f;
-            for (int w = 0; w < kWaves<SYNC>; ++w)
+                for (int x = 1; x < 4; ++x) c = fmaf(g[x], zj[x], c);
+                c = group_all<LPH, OpSum>(c);
+                c_mine = k == K ? c : c_mine;
+            });
+            const float u2 = rec.x + t2;
+            const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
+            const float de = alpha * (c_mine - rec.z);
+            const float du = u2 > 0.f ? de : a.slope * de;
+            dt += valid ? du : 0.f;
+            if (valid) unsafeAtomicAdd(ds_of + (int64_t)mine * HS, du);
+            static_for<B>([&](auto kk) {
+                constexpr int K = decltype(kk)::value;
+                const float ak = group_bcast<LPH, K>(alpha);
+                float g[4];
+                Row4<T>::unpack(raw[K], g);
 #pragma unroll
-                for (int y = 0; y < kSlots; ++y) s += part[w][y * kLanes + from][x];
-            a.partial[((int64_t)blockIdx.x * each + turn_of) * width + f] = s;
+                for (int x = 0; x < 4; ++x) dz[x] = fmaf(ak, g[x], dz[x]);
+            });
+            mine = next;
         }
+        // dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j
+        dt = group_all<LPH, OpSum>(dt);
+        if (live) {
+            float v[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                v[x] = fmaf(dt, al[x], dz[x]);
+                dal[x] = fmaf(dt, zj[x], dal[x]);
+            }
+            const int64_t jo = s_rank[q] ? s_rank[q][j] : j;
+            store_lane<T, false>(s_dZ[q] + jo * a.ld, foff, true, v);
+            if (k == 0 && s_dt[q]) s_dt[q][jo * a.ldh + h] = dt;
+        }
+    }
+    // this workgroup's share of the set's da_l
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 4; ++x) part[wave][lane][x] = dal[x];
+    __syncthreads();
+    constexpr int width = HS * D;
+    if ((int)threadIdx.x < width) {
+        const int f = (int)threadIdx.x, from = f / D * LPH + f % D / 4, x = f % 4;
+        float s = 0.f;
+        for (int w = 0; w < kWaves<SYNC>; ++w)
+#pragma unroll
+            for (int y = 0; y < kSlots; ++y) s += part[w][y * kLanes + from][x];
+        a.partial[(int64_t)blockIdx.x * width + f] = s;
     }
 }
 

@@ -9,14 +9,15 @@ using namespace sar;
 
 // Workgroups that serve `rows` rows: a multiple of the XCDs.  With barriers there are as many as four times the CUs, so
 // that a CU takes another when its own ends (one runs at a time, by registers); without, as many as run at once.
+constexpr int kMostSynced = 1024;
 template <bool SYNC>
-unsigned grid_of(int resident, int64_t rows, int sets, int slots, int most)
+unsigned grid_of(int resident, int64_t rows, int sets, int slots)
 {
     const int parts = sets < slices::kXcds ? slices::kXcds / sets : 1;                 // XCDs that share a set's rows
     const int64_t per_wg = (int64_t)slices::kWaves<SYNC> * slots * parts;
     const int64_t want = (rows + per_wg - 1) / per_wg;
-    const int64_t enough = SYNC ? 1024 / slices::kXcds : resident / slices::kXcds;
-    return (unsigned)(std::max<int64_t>(1, std::min<int64_t>({want, enough, most / slices::kXcds})) * slices::kXcds);
+    const int64_t enough = (SYNC ? kMostSynced : resident) / slices::kXcds;
+    return (unsigned)(std::max<int64_t>(1, std::min<int64_t>(want, enough)) * slices::kXcds);
 }
 
 template <typename T, int LPH, bool FLY, bool PAD, bool SYNC>
@@ -24,7 +25,7 @@ int launch_fwd(const f256::FwdP& p, const f256::Tabs& tabs, hipStream_t st)
 {
     auto fn = slices::k_gat_fwd_slices<T, LPH, FLY, PAD, SYNC>;
     static const int resident = SYNC ? 0 : resident_workgroups(fn);
-    const unsigned grid = grid_of<SYNC>(resident, p.n_rows, p.H, kWave / LPH, 1 << 20);
+    const unsigned grid = grid_of<SYNC>(resident, p.n_rows, p.H, kWave / LPH);
     fn<<<grid, slices::kThreads<SYNC>, 0, st>>>(p, tabs);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
@@ -41,10 +42,9 @@ int launch_bwd(const f256::BwdP& p, const f256::BwdTabs& tabs, int64_t n_dst, vo
     float* ds_sets = reinterpret_cast<float*>(rec + total);
     slices::k_slices_begin<HS><<<g_all, 256, 0, st>>>(p.rec, rec, ds_sets, n_dst, p.H);
     SAR_LAUNCH_CHECK();
-    const int sets = p.H / HS, each = sets < slices::kXcds ? 1 : sets / slices::kXcds, width = HS * p.D;
-    // (room for 4 x 2048 partial rows of 256 values)
-    const int most = 4 * kMaxPersistentWGs * 256 / (each * width);
-    const unsigned grid = grid_of<true>(0, p.n_rows, sets, kWave / (LPH * HS), most);
+    const int sets = p.H / HS, width = HS * p.D;
+    static_assert(kMostSynced <= kMaxPersistentWGs, "a row of partial sums for every workgroup in the caller's scratch");
+    const unsigned grid = grid_of<true>(0, p.n_rows, sets, kWave / (LPH * HS));
     fn<<<grid, slices::kThreads<true>, 0, st>>>(tabs, p, slices::SetP{rec, ds_sets, n_dst});
     SAR_LAUNCH_CHECK();
     slices::k_slices_da<<<(unsigned)(p.H * p.D), 256, 0, st>>>(p.partial, (int)(grid / slices::kXcds), sets, width, da_l);

@@ -1280,9 +1280,9 @@ int rows_store(const void* E, const RowsOp& op, void* out, int dtype, int64_t n,
 {
     auto with = [&](auto row) {
         using T = decltype(row);
-        // a piece lies within one head; and over E itself a value is written once only
+        // a piece lies within one head
         const int vec = 16 / (int)sizeof(T);
-        const bool pieces = F >= vec && (!op.ds || op.H == 1 || op.D % vec == 0) && (F % vec == 0 || E != out);
+        const bool pieces = F >= vec && (!op.ds || op.H == 1 || op.D % vec == 0);
         const int64_t units = n * (pieces ? (F + vec - 1) / vec : F);
         const unsigned grid = (unsigned)std::min<int64_t>((units + 255) / 256, 16384);
         if (pieces)
