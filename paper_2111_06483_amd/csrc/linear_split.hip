@@ -791,6 +791,8 @@ namespace sar {
 int split_dx(const float* dZ, const RowsOp* op, const float* W, float* dX, int64_t n, int K, int F, hipStream_t st)
 {
     SplitArgs g{dZ, F, n, W, dX, K, F, K, (F + kStep - 1) / kStep, 0, op ? *op : RowsOp{}};
+    // (the second step is fetched before the first is multiplied: of the same rows)
+    if (g.steps < 2) return sar::fail(SAR_ERR_STATE, "the split product for dX takes more than %d columns", kStep);
     const int nt = split_tiles(n, K, op ? 6 : 8, &g.slabs);
     auto with = [&](auto fuse) {
         constexpr bool FUSE = decltype(fuse)::value;
