@@ -32,6 +32,14 @@ def layer(n_own, n_other, P, deg, H, D, dtype, seed, compact):
     return b, Zs, a_l, a_r, rnd(n_own, H, D).to(dtype)
 
 
+def kernels_of(call):
+    """Names of the kernels that a call launches."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.name for e in p.events())
+
+
 def close(got, want, tol):
     got, want = got.double(), want.double()
     assert torch.equal(torch.isfinite(got), torch.isfinite(want))
@@ -41,9 +49,10 @@ def close(got, want, tol):
 
 
 # (destinations, other sources, partitions, edges a row).  Barriers: tables beyond 3 MiB and four sweeps and more, in both
-# passes of the first four (backward: fp32) and in the forward pass of the next four; no barriers: the small tables behind.
+# passes of the first four and the seventh (backward: fp32) and in the forward pass of the other three; no barriers: the
+# small tables behind.
 SHAPES = [(16_500, 16_500, 2, 90, 8, 32), (16_500, 16_500, 2, 90, 4, 64), (33_000, 5_000, 2, 90, 1, 128),
-          (16_900, 9_000, 3, 90, 2, 128), (17_000, 9_000, 2, 40, 2, 100), (16_390, 14_000, 2, 30, 4, 36),
+          (16_900, 9_000, 3, 90, 2, 128), (17_000, 9_000, 2, 55, 2, 100), (16_390, 14_000, 2, 34, 4, 36),
           (33_000, 400, 3, 80, 4, 32), (8_200, 8_000, 2, 40, 16, 64), (9_000, 300, 2, 30, 16, 40), (23_000, 500, 2, 9, 8, 32)]
 
 
@@ -97,8 +106,73 @@ def test_layer(n_own, n_other, P, deg, H, D, dtype, shipped, relu, compact):
     close(res[0][3], res[1][3], 1e-5)
 
 
-@pytest.mark.parametrize("n_own,n_other,P,deg,H,D", [SHAPES[0], SHAPES[1], SHAPES[2], (17_000, 9_000, 2, 55, 2, 100),
-                                                        SHAPES[6], SHAPES[9]])
+@pytest.mark.parametrize("n_own,n_other,P,deg,H,D", SHAPES)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_which_kernels_run(n_own, n_other, P, deg, H, D, dtype):
+    """The shapes above reach what they are there for: forward slices with barriers (tables beyond 3 MiB) or without, and
+    backward slices where scratch is given for them."""
+    b, Zs, a_l, a_r, G = layer(n_own, n_other, P, deg, H, D, dtype, seed=1, compact=True)
+    n, f32 = b.n_dst, dtype == torch.float32
+    s = torch.zeros(n, H, device="cuda")
+    out, L = torch.empty(n, H, D, device="cuda", dtype=dtype), torch.empty(n, H, device="cuda")
+    names = kernels_of(lambda: sar.sar_gat_fwd_all(b, Zs, s, None, a_l, 0.2, out, L, sar.SAR_ACT_NONE))
+    index = SHAPES.index((n_own, n_other, P, deg, H, D))
+    if f32:
+        assert "k_gat_fwd_slices" in names and ("true>" in names) == (index < 8)
+    elif D < 64:
+        assert "k_gat_fwd_slices" not in names
+    rec, ds = torch.empty(n, H, 4, device="cuda"), torch.empty(n, H, device="cuda")
+    sar.sar_gat_bwd_begin(G, out, s, L, rec, ds)
+    dZ = [torch.empty(b.n_err_rows(q), H, D, device="cuda", dtype=dtype) for q in range(P)]
+    full = sar.sar_gat_workspace_bytes(n, max(b.n_src(q) for q in range(P)), H, D)
+    for size in (full, 4 * 2048 * 256 * 4):
+        work, da = torch.empty(size // 4, device="cuda"), torch.zeros(H, D, device="cuda")
+        names = kernels_of(lambda: sar.sar_gat_bwd_all(b, Zs, G, None, rec, a_l, 0.2, dZ, None, ds, da, work))
+        assert ("k_gat_bwd_slices" in names) == (f32 and index in (0, 1, 2, 3, 6) and size == full)
+
+
+@pytest.mark.parametrize("H,D,n_own", [(8, 32, 16_500), (4, 64, 16_500), (2, 64, 33_000), (2, 128, 16_500)])
+@pytest.mark.parametrize("flags", [0, sar.SAR_BUILD_COMPACT, sar.SAR_BUILD_COMPACT | sar.SAR_BUILD_SINGLES])
+@pytest.mark.parametrize("hub", [False, True])
+def test_sources_of_all_kinds(H, D, n_own, flags, hub):
+    """Sources of 70 or 100 edges by slices beside sources of 0, 1 and 2 to 7 edges by the other kernels of the same call, ds
+    summed in copies where one destination is cited by all: against the call whose scratch has no room for slices."""
+    g = torch.Generator(device="cuda").manual_seed(H * D + n_own)
+    kinds = [(n_own, 70 if n_own < 20_000 else 100)] + [(3000, k) for k in (0, 1, 1, 2, 3, 5, 7, 8, 9)]
+    counts = torch.cat([torch.full((n,), k, device="cuda") for n, k in kinds])
+    N = counts.numel()
+    src = torch.repeat_interleave(torch.arange(N, device="cuda"), counts)
+    dst = torch.randint(0, n_own, (src.numel(),), generator=g, device="cuda")
+    if hub:
+        dst[torch.cumsum(counts, 0)[counts > 1] - 1] = 17
+    key = torch.unique(dst * N + src)
+    part = torch.cat([torch.zeros(n_own, dtype=torch.int32), 1 + torch.arange(N - n_own, dtype=torch.int32) % 2])
+    b = sar.sar_blocks_build(key % N, key // N, part.cuda(), 3, 0, sar.SAR_BUILD_TRANSPOSE | sar.SAR_BUILD_FUSED | flags)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+    Zs = [rnd(b.n_src(q), H, D) for q in range(3)]
+    a_l, a_r, G, n = rnd(H, D) / D ** 0.5, rnd(H, D) / D ** 0.5, rnd(n_own, H, D), n_own
+    s, out, L = torch.empty(n, H, device="cuda"), torch.empty(n, H, D, device="cuda"), torch.empty(n, H, device="cuda")
+    sar.sar_gat_scores(Zs[0], a_r, s)
+    sar.sar_gat_fwd_all(b, Zs, s, None, a_l, 0.2, out, L, sar.SAR_ACT_NONE)
+    rec, ds0 = torch.empty(n, H, 4, device="cuda"), torch.empty(n, H, device="cuda")
+    sar.sar_gat_bwd_begin(G, out, s, L, rec, ds0)
+    full, res = sar.sar_gat_workspace_bytes(n, max(b.n_src(q) for q in range(3)), H, D), []
+    for size in (full, full - n * H * 20):
+        dZ = [torch.full((b.n_err_rows(q), H, D), float("nan"), device="cuda") for q in range(3)]
+        dt = [torch.full((b.n_err_rows(q), H), float("nan"), device="cuda") for q in range(3)]
+        ds, da = torch.zeros(n, H, device="cuda"), torch.zeros(H, D, device="cuda")
+        work = torch.full((size // 4,), float("nan"), device="cuda")
+        names = kernels_of(lambda: sar.sar_gat_bwd_all(b, Zs, G, None, rec, a_l, 0.2, dZ, dt, ds, da, work))
+        assert ("k_gat_bwd_slices" in names) == (size == full) and ("k_ds_sum" in names) == hub
+        res.append((dZ, dt, ds, da))
+    for x, y in zip(res[0][0] + res[0][1], res[1][0] + res[1][1]):
+        close(x, y, 1e-5)
+    # (17 of the hub's row: the sum of 40 thousand terms in another order)
+    close(res[0][2], res[1][2], 1e-5 if not hub else 40_000 ** 0.5 * 2.0 ** -24)
+    close(res[0][3], res[1][3], 1e-5)
+
+
+@pytest.mark.parametrize("n_own,n_other,P,deg,H,D", [SHAPES[0], SHAPES[1], SHAPES[2], SHAPES[4], SHAPES[6], SHAPES[9]])
 def test_infinities_stay_with_their_edges(n_own, n_other, P, deg, H, D):
     """An infinity in the last row that a destination (backward: a source) gathers, with longer rows beside it: the result
     it belongs to is infinite and no result is NaN."""
