@@ -1778,17 +1778,27 @@ bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
 
 // Forward over all blocks by rows: how many rows at the head of the list all twelve wavefronts of a workgroup share (0:
 // workgroups of four).  A workgroup of four takes 32 edges of a row per round trip to memory, so a row of more edges than
-// its fair share (about 2048 of them run at once) decides when the launch ends.  Kernel times in us, four wavefronts /
-// twelve: a tenth of the destinations of a 2.45 M node power-law graph, 1.5 M edges, rows up to 2^14 edges, 4 x 64
-// bf16 473 / 276; 9 M edges, 8 x 32 bf16 with given scores 1169 / 1048.  Where a row is about as long as the share both take
-// the same: 15 M edges, 4 x 64 fp32, rows up to 2^14, whole layer 5770 to 5800 / 5800.  (Every long row by eight wavefronts
-// or by sixteen instead of teams of four, whole forward pass of the second: 1294 -> 1115 and 1215, but other layers 1 to 14 % slower.)
-int64_t shared_hubs(const sar_blocks_t* b)
+// its fair share (about 2048 of them run at once) decides when the launch ends; workgroups of twelve fill a CU less evenly.
+// Times of twelve over four in turn on shares of power-law graphs, by how many shares the longest row has at least (from
+// its class) and how many rows have 1024 edges:
+//   - two shares or more: rows of 1 KiB with scores formed in flight (4 x 64, 2 x 128 fp32) 0.93 to 1.01, others 0.78 to
+//     0.96 (11 shares, 1.5 M edges: 501 -> 358 us, 4 x 64 bf16 434 -> 253);
+//   - one to two shares, 256 such rows (the CUs) and more: rows of 1 KiB with scores in flight 0.97 to 1.04, mostly slower
+//     (1.1 shares, 15 M edges 2186 / 2181 and 2155 / 2184 us; 1.9 shares, 9 M 1508 / 1546), with given ones 0.95 to 1.03,
+//     others 0.76 to 1.03 (8 x 32 bf16, 15 M edges 1202 -> 1081; 309 rows, 3.7 M edges 233 / 240);
+//   - one to two shares, 112 to 181 rows: 0.99 to 1.13 (1 x 128 fp32, 2.5 M edges 166 / 176);
+//   - less: 0.97 to 1.17 (4.0 M edges, 8 x 32 bf16 253 / 263).
+// The forms for padded layers spill a few registers at twelve wavefronts (20 to 32 bytes a lane) and are among these
+// figures; one workgroup of them per CU and no spills took 1.02 to 1.39 times as long as four wavefronts where this takes
+// 0.92 to 0.99.
+int64_t shared_hubs(const sar_blocks_t* b, size_t row_bytes, bool scores_given)
 {
     if (b->n_f_hub == 0) return 0;
     int64_t edges = 0;
     for (int q = 0; q < b->P; ++q) edges += b->blk[q].nnz;
-    return (b->f_longest + 1) / 2 * kMaxPersistentWGs >= edges ? b->n_f_hub : 0;
+    const int64_t reach = (b->f_longest + 1) / 2 * kMaxPersistentWGs;
+    const bool one_share = b->n_f_hub >= 256 && (row_bytes < 1024 || scores_given);
+    return reach >= (one_share ? edges : 2 * edges) ? b->n_f_hub : 0;
 }
 
 // Forward: heads of 32 to 128 fp32 values or 64 to 128 bf16 values (slices of 128 bytes, a cache line, and more: 64-byte
@@ -1882,12 +1892,12 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.rows = reinterpret_cast<const uint32_t*>(b->f_rows);
         a.n_rows = b->n_dst;   // the list ends with the destinations that have no in-edge: out = 0, L = -inf
         a.n_long = b->n_f_long;
-        a.n_hub = shared_hubs(b);
         a.s = s + h0;
         a.a_l = tq ? nullptr : a_l + f0;
         a.out = shift(out, f0 * hg.fb);
         a.L = L + h0;
         a.H = hg.count(g);
+        a.n_hub = shared_hubs(b, (size_t)a.H * D * hg.fb, tq != nullptr);
         a.D = D;
         a.F = a.H * D;
         a.ldz = H * D;

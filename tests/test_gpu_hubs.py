@@ -31,6 +31,24 @@ def check(got, want, tol):
     assert float((got.double() - want).abs().max()) <= tol * float(want.abs().max())
 
 
+@pytest.mark.parametrize("filler,few,many", [(0, 12, 12), (200_000, 4, 12)])
+def test_which_workgroups_share_rows(filler, few, many):
+    """400 rows of 1100 edges: far more than a workgroup's share of all edges, and one to two shares among 1.2 million others,
+    where rows of 1 KiB stay with workgroups of four wavefronts."""
+    counts = torch.cat([torch.full((400,), 1100), torch.full((filler,), 6)]).cuda()
+    n, g = counts.numel(), torch.Generator(device="cuda").manual_seed(1)
+    dst = torch.repeat_interleave(torch.arange(n, device="cuda"), counts)
+    src = torch.randint(0, n, (dst.numel(),), generator=g, device="cuda")
+    b = sar.sar_blocks_build(src, dst, torch.zeros(n, dtype=torch.int32, device="cuda"), 1, 0, sar.SAR_BUILD_FUSED)
+    for dtype, H, D, waves in ((torch.float32, 4, 64, few), (torch.bfloat16, 4, 64, many), (torch.float32, 2, 100, many)):
+        Z, a_l = torch.randn(n, H, D, generator=g, device="cuda").to(dtype), torch.randn(H, D, generator=g, device="cuda")
+        s, out, L = torch.randn(n, H, generator=g, device="cuda"), torch.empty_like(Z), torch.empty(n, H, device="cuda")
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+            sar.sar_gat_fwd_all(b, [Z], s, None, a_l, 0.2, out, L, sar.SAR_ACT_NONE)
+            torch.cuda.synchronize()
+        assert any("k_gat_fwd_f256" in e.name and ", %d>" % waves in e.name for e in p.events())
+
+
 @pytest.mark.parametrize("only_few", [False, True])
 @pytest.mark.parametrize("H,D", [(4, 64), (8, 32), (1, 256), (16, 16), (2, 96), (6, 40), (2, 100)])
 @pytest.mark.parametrize("dtype,shipped,relu", [(torch.float32, False, False), (torch.float32, True, True),
