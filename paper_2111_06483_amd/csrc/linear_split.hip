@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     const int item_k = (tid & 1) * 8, item_n = tid >> 1;            // (of the thread's first item; the next: 128 columns on)
     const int item_at = item_n / 32 * 192 + place(tid & 1, item_n & 31);
     uint4 bv[kPer][2];
-    uint32_t low_b = ~0u;        // the smallest size met (every row block takes the same values)
+    uint32_t low_b = ~0u;        // the smallest size met (every row block meets the same: a test for the first one costs more)
     auto load_b = [&](int step) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         }
     };
     // (beyond K: other values of W, which meet zeros of A)
-    auto store_b = [&](int step, int buf, bool check) SAR_INLINE {
+    auto store_b = [&](int step, int buf) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
             if ((x + 1) * kThreads > NT * 64 && tid + x * kThreads >= NT * 64) break;
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             for (int p = 0; p < 2; ++p) {
                 uint4 q = bv[x][p];
                 if (rest != 0 && step * kStep + item_k + 4 * p > k_last) q = front_of_piece<float>(q, rest);
-                if (check) low_b = lowest(low_b, q);
+                low_b = lowest(low_b, q);
                 v[4 * p] = __uint_as_float(q.x);
                 v[4 * p + 1] = __uint_as_float(q.y);
                 v[4 * p + 2] = __uint_as_float(q.z);
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     if constexpr (FUSE) {
         for (int k = tid; k < g.steps * kStep; k += kThreads) arl[k] = g.op.ds && k < g.K ? g.op.a_r[k] : 0.f;
     }
-    store_b(0, 0, true);
+    store_b(0, 0);
     __syncthreads();
 
     // ---- the steps
@@ -334,9 +334,10 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         fetch(cur);
         const uint4* fr = frag + buf * kBuf + place(gq, c);
         const float sign = step % 2 ? -1.f : 1.f;
-        // A tile's 16 products are summed from zero and added to its results by vector instructions, where registers allow
-        // while the next tile's are multiplied.
-        constexpr int kSums = !FUSE && NT > 4 ? 2 : 1;
+        // A tile's 16 products are summed from zero and added to its results by vector instructions: those of two tiles
+        // after the next step's values are split, of more, where registers allow, while the next tile's are multiplied.
+        constexpr bool kLate = NT == 2, kAhead = !FUSE && NT > 4;
+        constexpr int kSums = kLate || kAhead ? 2 : 1;
         float16_t sum[kSums];
         auto add = [&](int nt) SAR_INLINE {
 #pragma unroll
@@ -352,11 +353,15 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
 #pragma unroll
             for (int i = 0; i < 3; ++i) w[i] = fr[(nt * 3 + i) * 64];
             multiply_split(x, w, sum[nt % kSums]);
-            if (nt >= kSums - 1) add(nt - (kSums - 1));
-            if (kSums == 2) __builtin_amdgcn_sched_barrier(0);
+            if (!kLate && nt >= kSums - 1) add(nt - (kSums - 1));
+            if (kAhead) __builtin_amdgcn_sched_barrier(0);
         }
-        if (kSums == 2) add(NT - 1);
-        store_b(after, buf ^ 1, ordinal == 0);
+        if (kAhead) add(NT - 1);
+        store_b(after, buf ^ 1);
+        if (kLate) {
+            add(0);
+            add(1);
+        }
         step = after;
         if (after == 0) {
             bool redo = low < kLowBits;
