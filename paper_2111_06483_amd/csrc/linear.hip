@@ -1207,7 +1207,8 @@ namespace {
 
 // Whether both products can form the rows `op` describes while they load them (k_dw, k_dw_split,
 // k_gemm_skinny and k_dx_split with FUSE): their aligned fast paths, a piece inside one head, the stand-in row
-// readable.  dZ here is the stored part E (or the stand-in when there is none).
+// readable.  dZ here is the stored part E (or the stand-in when there is none).  (k_gemm_skinny's limits bind dX of fp32
+// rows too, which k_dx_split forms at any width: what a call without scratch for the rows refuses is as it was.)
 bool rows_op_fusable(const void* X, const void* dZ, const RowsOp& op, void* dX, int dtype, int K, int F)
 {
     const int elem = dtype == SAR_F32 ? 4 : 2, vec = 16 / elem;

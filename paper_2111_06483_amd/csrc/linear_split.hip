@@ -384,8 +384,8 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         if (rb >= row_blocks) break;
     }
 
-    // ---- row blocks that are not finite or have small operands, by the fp32 instruction (any pairing of k with instruction and lane group
-    // is valid as long as both operands use the same)
+    // ---- row blocks that are not finite or have small operands, by the fp32 instruction (any pairing of k with instruction
+    // and lane group is valid as long as both operands use the same)
     int* any_b = reinterpret_cast<int*>(split_lds);
     if (tid == 0) *any_b = 0;
     __syncthreads();
