@@ -97,10 +97,11 @@ __device__ inline bool not_finite(const float16_t& v)
 //
 // FUSE: the rows of A are formed where they are split (RowsOp).
 //
-// Bound by the matrix instructions of a wavefront and the vector instructions around them, which overlap in part, and by
-// memory latency in narrow products.  dX against the fp32 instruction, plain / with formed rows, us: 306250 rows 256 -> 256
-// 349 / 361 -> 290 / 303, 256 -> 100 183 / 196 -> 145 / 163; 2450000 rows 400 -> 400 7930 -> 5530; 75000 rows 128 -> 128
-// 40 / 42 -> 26 / 32; 8000 rows 256 -> 256 34 / 37 -> 18 / 22; 100 rows 128 -> 100 17 / 19 -> 10 / 13.  (Also measured: one workgroup of eight wavefronts per CU, of which four split before they
+// Bound by what a SIMD can issue: of its cycles at 306250 rows 256 -> 256, 1.8 GHz under this load, the matrix instructions
+// take 47% and the vector instructions (splitting, adding, checking) 52%, and the two wavefronts' overlap little; by memory
+// latency in narrow products.  dX against the fp32 instruction, plain / with formed rows, us: 306250 rows 256 -> 256
+// 351 / 362 -> 291 / 306, 256 -> 100 181 / 196 -> 145 / 163; 2450000 rows 400 -> 400 7950 -> 5700; 75000 rows 128 -> 128
+// 40 / 42 -> 26 / 32; 8000 rows 256 -> 256 33 / 37 -> 17 / 21; 100 rows 128 -> 100 17 / 19 -> 10 / 12.  (Also measured: one workgroup of eight wavefronts per CU, of which four split before they
 // multiply and four after, the same within 5%, small products slower; steps of 32 values and results stored during the
 // next block's steps, 10 to 20% slower.)
 constexpr int kThreads = 256;
@@ -482,9 +483,9 @@ int split_tiles(int64_t M, int N, int most, int* slabs)
 // A chunk is on its way while the one before it is split and the one before that is multiplied.  Of the two wavefronts
 // of a SIMD one splits before it multiplies and the other after, so that the vector instructions of one run beside the
 // matrix instructions of the other.  Measured against the fp32 instruction, plain / with formed rows, us: 306250 rows 100
-// x 256 184 / 207 -> 129 / 155, 256 x 256 345 / 387 -> 243 / 267; 2450000 rows 400 x 400 10550 -> 6800; 16384 rows 128 x
-// 256 33 / 37 -> 22 / 25; 4096 rows 64 x 64 9.8 / 10.7 -> 7.9 / 10.0.  Bound by the chunk's latency and, in wide products,
-// by power.
+// x 256 186 / 209 -> 136 / 145, 256 x 256 351 / 391 -> 259 / 267; 2450000 rows 400 x 400 10740 -> 6950; 8000 rows 256 x
+// 256 35 / 41 -> 23 / 26; 4096 rows 64 x 64 10.1 / 11.0 -> 8.6 / 10.5.  Bound by the chunk's latency and, in wide products,
+// by issue: matrix instructions 41 to 54%, vector instructions about as much of the cycles, at 1.7 to 1.8 GHz.
 constexpr int kDwThreads = 512;
 constexpr int kDwRows = 32;
 constexpr int kDwKf = 128;
@@ -681,6 +682,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
             uint4 a[2][3];
 #pragma unroll
             for (int s = 0; s < 2; ++s) fragment(buf, s, 32 * (kt * kKg + kg), a[s]);
+            float16_t sum[kNt] = {};
             if constexpr (decltype(keep)::value) {
 #pragma unroll
                 for (int nt = 0; nt < kNt; ++nt)
@@ -692,15 +694,10 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
                             const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
                             for (int j = 0; j < 4; ++j)
-                                acc[kt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                                    sign * __uint_as_float(xs[j]), __uint_as_float(ys[j]), acc[kt][nt], 0, 0, 0);
+                                sum[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(xs[j]),
+                                                                               __uint_as_float(ys[j]), sum[nt], 0, 0, 0);
                         }
             } else {
-                float16_t sum[kNt];
-#pragma unroll
-                for (int nt = 0; nt < kNt; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) sum[nt][r] = 0.f;
 #pragma unroll
                 for (int t = 0; t < 6; ++t)
 #pragma unroll
@@ -710,11 +707,11 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
                             sum[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                                 __builtin_bit_cast(bf16x8_t, a[s][kTerm[t][0]]),
                                 __builtin_bit_cast(bf16x8_t, b[nt][s][kTerm[t][1]]), sum[nt], 0, 0, 0);
-#pragma unroll
-                for (int nt = 0; nt < kNt; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[kt][nt][r] = fmaf(sign, sum[nt][r], acc[kt][nt][r]);
             }
+#pragma unroll
+            for (int nt = 0; nt < kNt; ++nt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[kt][nt][r] = fmaf(sign, sum[nt][r], acc[kt][nt][r]);
         }
     };
     auto slab = [&](auto keep) SAR_INLINE {
