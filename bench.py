@@ -505,14 +505,16 @@ def time_gat(args, torch, sar, synth, name, steps, warmup, full_report):
     # in stream mode the events bracket P launches; report per launch
     launches = 1 if args.mode == "all" else w.P
     fast = layer.F == 256
+    # every row long and no hubs: head slices (fp32 rows, the whole graph)
+    dense = name == "cfg5" and args.mode == "all" and args.scale == 1.0 and args.dst_frac == 1.0 and fb == 4
     # sources of one edge in their block that the backward call takes destination-major (exact geometry only)
     n_singles = sar.sar_blocks_n_singles(layer.blocks) if (fast and args.mode == "all") else 0
     calls = {
-        "gat_fwd": {"kernel": ("k_gat_fwd_f256, or k_gat_fwd_slices on dense graphs without hubs" if fast
+        "gat_fwd": {"kernel": (("k_gat_fwd_slices" if dense else "k_gat_fwd_f256") if fast
                                else "k_gat_fwd_f256 in its padded geometry, or k_gat_fwd, by shape")
                     + (" (all blocks)" if args.mode == "all" else " (per block)"),
                     "avg_ms": fwd_ms, "alg_bytes": alg["gat_fwd"]},
-        "gat_bwd": {"kernel": ("k_gat_bwd_f256, or k_gat_bwd_slices on dense graphs without hubs, + k_gat_bwd_few" if fast
+        "gat_bwd": {"kernel": (("k_gat_bwd_slices" if dense else "k_gat_bwd_f256") + " + k_gat_bwd_few" if fast
                                else "k_gat_bwd_f256 + k_gat_bwd_few in their padded geometry, or k_gat_bwd, by shape")
                     + (" + k_gat_bwd_single" if n_singles else "")
                     + ("" if layer.errors != "full" else " + k_bwd_zero_rows"),

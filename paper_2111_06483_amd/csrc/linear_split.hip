@@ -98,8 +98,8 @@ __device__ inline bool not_finite(const float16_t& v)
 // FUSE: the rows of A are formed where they are split (RowsOp).
 //
 // Bound by what a SIMD can issue: of its cycles at 306250 rows 256 -> 256, 1.8 GHz under this load, the matrix instructions
-// take 47% and the vector instructions (splitting, adding, checking) 52%, and the two wavefronts' overlap little; by memory
-// latency in narrow products.  dX against the fp32 instruction, plain / with formed rows, us: 306250 rows 256 -> 256
+// take 47% and the vector instructions (splitting, adding, checking) 46%, and they overlap little; by memory latency in
+// narrow products.  dX against the fp32 instruction, plain / with formed rows, us: 306250 rows 256 -> 256
 // 351 / 362 -> 291 / 306, 256 -> 100 181 / 196 -> 145 / 163; 2450000 rows 400 -> 400 7950 -> 5700; 75000 rows 128 -> 128
 // 40 / 42 -> 26 / 32; 8000 rows 256 -> 256 33 / 37 -> 17 / 21; 100 rows 128 -> 100 17 / 19 -> 10 / 12.  (Also measured: one workgroup of eight wavefronts per CU, of which four split before they
 // multiply and four after, the same within 5%, small products slower; steps of 32 values and results stored during the
@@ -485,7 +485,7 @@ int split_tiles(int64_t M, int N, int most, int* slabs)
 // matrix instructions of the other.  Measured against the fp32 instruction, plain / with formed rows, us: 306250 rows 100
 // x 256 186 / 209 -> 136 / 145, 256 x 256 351 / 391 -> 259 / 267; 2450000 rows 400 x 400 10740 -> 6950; 8000 rows 256 x
 // 256 35 / 41 -> 23 / 26; 4096 rows 64 x 64 10.1 / 11.0 -> 8.6 / 10.5.  Bound by the chunk's latency and, in wide products,
-// by issue: matrix instructions 41 to 54%, vector instructions about as much of the cycles, at 1.7 to 1.8 GHz.
+// by issue: matrix instructions take 41 to 52% of the cycles, vector instructions 45 to 47%, at 1.7 to 1.9 GHz.
 constexpr int kDwThreads = 512;
 constexpr int kDwRows = 32;
 constexpr int kDwKf = 128;
