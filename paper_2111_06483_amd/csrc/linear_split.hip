@@ -467,7 +467,7 @@ int split_tiles(int64_t M, int N, int most, int* slabs)
 // 16-byte unit to LDS: the transposed fragment, which the wavefronts read with one access per lane.  A unit's column is
 // exchanged within its group of four (column ^ (column / 8 % 4)), which puts the columns 4q + j of neighbouring lanes
 // and the neighbouring columns of a read alike on different banks.  One workgroup of eight wavefronts per CU; the output
-// tile is 128 x NW, 32 rows a chunk, double buffered, one barrier per chunk.  Rows are split into slabs over the grid;
+// tile is 128 x NW, 32 or 64 rows a chunk, double buffered, one barrier per chunk.  Rows are split into slabs over the grid;
 // k_sum_slabs adds the partial tiles in a fixed order.
 //
 // The matrix cores cut a product's bits below the sum's instead of rounding them, always downwards: five small terms
@@ -487,8 +487,12 @@ int split_tiles(int64_t M, int N, int most, int* slabs)
 // 256 35 / 41 -> 23 / 26; 4096 rows 64 x 64 10.1 / 11.0 -> 8.6 / 10.5.  Bound by the chunk's latency and, in wide products,
 // by issue: matrix instructions take 41 to 52% of the cycles, vector instructions 45 to 47%, at 1.7 to 1.9 GHz.
 constexpr int kDwThreads = 512;
-constexpr int kDwRows = 32;
+constexpr int kDwSum = 32;           // rows summed by themselves
 constexpr int kDwKf = 128;
+// Rows of a chunk.  The narrow tile takes twice as many: with 32 one workgroup per CU (formed rows, by registers) had 16 KB
+// on their way and waited for them (1000000 rows 64 x 64 formed 307 -> 158 us, stored, two workgroups per CU, 129 -> 137; 40000
+// rows 128 x 64 21.2 -> 18.8 and 18.7 -> 17.2).
+constexpr int dw_rows(int nw) { return nw == 64 ? 64 : 32; }
 
 template <bool FUSE, int NW, bool RAG>
 __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restrict__ X, const float* __restrict__ dZ,
@@ -500,7 +504,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
     constexpr int kCols = NW / 32 / kNt;      // wavefronts side by side
     constexpr int kKg = 8 / kCols;            // groups of kf-tiles
     constexpr int kKt = 4 / kKg;              // kf-tiles per wavefront
-    constexpr int kOct = kDwRows / 8;
+    constexpr int kRows = dw_rows(NW), kOct = kRows / 8;
     constexpr int kPlane = kOct * (kDwKf + NW);           // units of one piece of a chunk
     constexpr int kBuf = 3 * kPlane;
     extern __shared__ __attribute__((aligned(16))) uint4 dw_lds[];
@@ -517,8 +521,10 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
 
     // ---- staging: which eight rows of which four columns are this thread's
     // (whole wavefronts: the branches on it are uniform)
-    const bool of_dz = wave * 64 < NW, of_x = !of_dz && wave * 64 < NW + kDwKf;
-    const int u = of_dz ? tid : tid - NW, quads = of_dz ? NW / 4 : kDwKf / 4;
+    constexpr int kOfDz = NW / 4 * kOct, kOfX = kDwKf / 4 * kOct;
+    static_assert(kOfDz % 64 == 0 && kOfDz + kOfX <= kDwThreads, "");
+    const bool of_dz = wave * 64 < kOfDz, of_x = !of_dz && wave * 64 < kOfDz + kOfX;
+    const int u = of_dz ? tid : tid - kOfDz, quads = of_dz ? NW / 4 : kDwKf / 4;
     const int oct = u / quads, col = 4 * (u % quads);
     const int width = of_dz ? N : K, first = (of_dz ? n0 : kf0) + col;
     // (columns beyond the width are another column's values: nothing of them is stored)
@@ -597,14 +603,14 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
 #pragma unroll
             for (int j = 0; j < 8; ++j) ahead[j] = load_row(base + from[j] * width);
         }
-        fetch_rank(m0 + kDwRows);
+        fetch_rank(m0 + kRows);
     };
     uint32_t low = ~0u;           // the smallest size this thread has split
     auto commit = [&](int64_t m0, int buf, auto keep) SAR_INLINE {
         if (!(of_dz || of_x)) return;
         constexpr bool KEEP = decltype(keep)::value;
-        // every other chunk with the sign of X turned over (see above)
-        const float sign = of_x && (m0 & kDwRows) ? -1.f : 1.f;
+        // every other 32 rows with the sign of X turned over (see above)
+        const float sign = of_x && ((m0 + 8 * oct) & kDwSum) ? -1.f : 1.f;
         float dsv[FUSE ? 8 : 1] = {};
         if constexpr (FUSE) {
             if (formed && op.ds) {
@@ -669,19 +675,18 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
 #pragma unroll
         for (int t = 0; t < 3; ++t) w[t] = p[t * kPlane];
     };
-    auto multiply = [&](int buf, float sign, auto keep) SAR_INLINE {
-        if (!some) return;
+    auto multiply_32 = [&](int buf, int first, float sign, auto keep) SAR_INLINE {      // from the chunk's step `first` on
         uint4 b[kNt][2][3];
 #pragma unroll
         for (int nt = 0; nt < kNt; ++nt)
 #pragma unroll
-            for (int s = 0; s < 2; ++s) fragment(buf, s, kDwKf + 32 * (kNt * cw + nt), b[nt][s]);
+            for (int s = 0; s < 2; ++s) fragment(buf, first + s, kDwKf + 32 * (kNt * cw + nt), b[nt][s]);
 #pragma unroll
         for (int kt = 0; kt < kKt; ++kt) {
             if (kt >= kt_n) break;
             uint4 a[2][3];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) fragment(buf, s, 32 * (kt * kKg + kg), a[s]);
+            for (int s = 0; s < 2; ++s) fragment(buf, first + s, 32 * (kt * kKg + kg), a[s]);
             float16_t sum[kNt] = {};
             if constexpr (decltype(keep)::value) {
 #pragma unroll
@@ -714,6 +719,12 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
                 for (int r = 0; r < 16; ++r) acc[kt][nt][r] = fmaf(sign, sum[nt][r], acc[kt][nt][r]);
         }
     };
+    auto multiply = [&](int buf, int64_t m0, auto keep) SAR_INLINE {
+        if (!some) return;
+#pragma unroll
+        for (int part = 0; part < kRows / kDwSum; ++part)
+            multiply_32(buf, 2 * part, (m0 + part * kDwSum) & kDwSum ? -1.f : 1.f, keep);
+    };
     auto slab = [&](auto keep) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kKt; ++x)
@@ -725,21 +736,21 @@ __global__ __launch_bounds__(kDwThreads, 2) void k_dw_split(const float* __restr
             fetch_rank(m_beg);
             fetch(m_beg);
             commit(m_beg, 0, keep);
-            fetch(m_beg + kDwRows);
+            fetch(m_beg + kRows);
         }
         __syncthreads();
         int buf = 0;
-        for (int64_t m0 = m_beg; m0 < m_end; m0 += kDwRows, buf ^= 1) {
+        for (int64_t m0 = m_beg; m0 < m_end; m0 += kRows, buf ^= 1) {
             auto stage = [&]() SAR_INLINE {
-                if (m0 + kDwRows < m_end) {
-                    commit(m0 + kDwRows, buf ^ 1, keep);
-                    fetch(m0 + 2 * kDwRows);       // (beyond the end: the last row, used by nobody)
+                if (m0 + kRows < m_end) {
+                    commit(m0 + kRows, buf ^ 1, keep);
+                    fetch(m0 + 2 * kRows);         // (beyond the end: the last row, used by nobody)
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
             // (of a SIMD's two wavefronts one splits first, the other multiplies first)
             if (wave < kDwThreads / 128) stage();
-            multiply(buf, m0 & kDwRows ? -1.f : 1.f, keep);
+            multiply(buf, m0, keep);
             if (wave >= kDwThreads / 128) stage();
             __syncthreads();
         }
@@ -777,7 +788,7 @@ template <bool FUSE, int NW, bool RAG>
 int launch_dw(const float* X, const float* dZ, const RowsOp& op, float* partial, int64_t n, int K, int F, int slabs,
               int64_t rows_per_slab, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)2 * 3 * (kDwRows / 8) * (kDwKf + NW) * 16;
+    constexpr size_t lds = (size_t)2 * 3 * (dw_rows(NW) / 8) * (kDwKf + NW) * 16;
     SAR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dw_split<FUSE, NW, RAG>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const dim3 grid((unsigned)slabs, (unsigned)((F + NW - 1) / NW), (unsigned)((K + kDwKf - 1) / kDwKf));
@@ -815,14 +826,14 @@ int split_dw(const float* X, const float* dZ, const RowsOp* op, float* partial, 
 {
     const int nw = F <= 64 ? 64 : F <= 128 ? 128 : 256;
     const int64_t tiles = (int64_t)((F + nw - 1) / nw) * ((K + kDwKf - 1) / kDwKf);
-    // As many workgroups as run at once (two per CU with the narrowest tile of stored rows, else one) where all have the
-    // same work; where the last tiles are narrower twice as many, so that CUs that end early take another.  (Each writes
-    // a partial tile: 100000 rows 283 x 100 104 us with 341 slabs, 94 with 170; 150003 rows 256 x 47 62 with 512, 59 with
-    // 256; 40000 formed rows 64 x 36 26 with 512, 18 with 256.)
+    // As many workgroups as run at once, one per CU, where all have the same work; where the last tiles are narrower twice as
+    // many, so that CUs that end early take another.  (Each writes a partial tile: 100000 rows 283 x 100 104 us with 341
+    // slabs, 94 with 170; 40000 formed rows 64 x 36 26 with 512, 18 with 256.)  Stored and formed rows alike: their sums
+    // are to be the same bits.
     const bool even = (F % nw == 0 || F <= nw) && (K % kDwKf == 0 || K <= kDwKf);
-    const int64_t want = std::max<int64_t>(1, (even && (nw != 64 || op) ? 256 : 512) / tiles);
+    const int64_t want = std::max<int64_t>(1, (even ? 256 : 512) / tiles);
     *slabs = (int)std::min<int64_t>(want, most_slabs);
-    const int64_t rows = ((n + *slabs - 1) / *slabs + kDwRows - 1) / kDwRows * kDwRows;
+    const int64_t rows = ((n + *slabs - 1) / *slabs + kDwSum - 1) / kDwSum * kDwSum;
     auto with = [&](auto fuse, auto ragged) {
         constexpr bool FUSE = decltype(fuse)::value, RAG = decltype(ragged)::value;
         const RowsOp o = op ? *op : RowsOp{};

@@ -113,6 +113,12 @@ def test_heads_that_lanes_hold_in_turns(H, D, K):
     test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, 3001, 0.6, True)
 
 
+@pytest.mark.parametrize("H,D,K,n", [(4, 16, 64, 70_000), (1, 64, 128, 40_000), (3, 12, 32, 100_000), (8, 8, 100, 50_000)])
+def test_narrow_layers_of_many_rows(H, D, K, n):
+    """More rows than dW has slabs of 32: as many slabs whether the rows are stored or formed."""
+    test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, n, 0.6, True)
+
+
 @pytest.mark.parametrize("dtype,H,D,K", [(torch.float32, 3, 10, 100), (torch.float32, 4, 16, 256),
                                          (torch.bfloat16, 16, 16, 64), (torch.float32, 2, 200, 64),
                                          (torch.bfloat16, 4, 12, 32)])
