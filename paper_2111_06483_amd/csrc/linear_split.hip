@@ -224,7 +224,9 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
     const int item_k = (tid & 1) * 8, item_n = tid >> 1;            // (of the thread's first item; the next: 128 columns on)
     const int item_at = item_n / 32 * 192 + place(tid & 1, item_n & 31);
     uint4 bv[kPer][2];
-    uint32_t low_b = ~0u;        // the smallest size met (every row block meets the same: a test for the first one costs more)
+    uint32_t low_b[kPer];        // the smallest sizes met (every row block meets the same: a test for the first one costs more)
+#pragma unroll
+    for (int x = 0; x < kPer; ++x) low_b[x] = ~0u;
     auto load_b = [&](int step) SAR_INLINE {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             for (int p = 0; p < 2; ++p) {
                 uint4 q = bv[x][p];
                 if (rest != 0 && step * kStep + item_k + 4 * p > k_last) q = front_of_piece<float>(q, rest);
-                low_b = lowest(low_b, q);
+                low_b[x] = lowest(low_b[x], q);
                 v[4 * p] = __uint_as_float(q.x);
                 v[4 * p + 1] = __uint_as_float(q.y);
                 v[4 * p + 2] = __uint_as_float(q.z);
@@ -264,12 +266,12 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
     };
-    auto store_c = [&](int64_t b) SAR_INLINE {
+    auto store_c = [&](int64_t b, uint32_t tiles) SAR_INLINE {      // tiles: a bit for each that is stored
         const int64_t row0 = b * kBlockRows + wave * 32 + 4 * gq;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const int n = n0 + nt * 32 + c;
-            if (n >= g.N) continue;
+            if (n >= g.N || !(tiles >> nt & 1)) continue;
             float* to = g.C + row0 * g.ldc + n;
             if (row0 + 28 <= g.M) {
 #pragma unroll
@@ -280,6 +282,22 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
                     if (row0 + 8 * (r / 4) + (r % 4) < g.M) to[(int64_t)(8 * (r / 4) + (r % 4)) * g.ldc] = acc[nt][r];
             }
         }
+    };
+    // of a row block as stored: a bit for each tile that holds an infinity or a NaN
+    auto not_finite_stored = [&](int64_t b) SAR_INLINE -> uint32_t {
+        const int64_t row0 = b * kBlockRows + wave * 32 + 4 * gq;
+        uint32_t tiles = 0;
+#pragma unroll 1
+        for (int nt = 0; nt < NT; ++nt) {
+            const int n = n0 + nt * 32 + c;
+            float zero = 0.f;
+            for (int r = 0; r < 16; ++r) {
+                const int64_t i = row0 + 8 * (r / 4) + (r % 4);
+                if (n < g.N && i < g.M) zero = fmaf(g.C[i * g.ldc + n], 0.f, zero);
+            }
+            if (__any(__builtin_isunordered(zero, zero))) tiles |= 1u << nt;
+        }
+        return tiles;
     };
 
     // ---- first loads
@@ -370,7 +388,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
             for (int nt = 0; nt < NT; ++nt) redo |= not_finite(acc[nt]);
             if (__any(redo)) again |= 1ull << min(ordinal, 63);
             low = ~0u;
-            store_c(rb);
+            store_c(rb, ~0u);
             rb += stride;
             ++ordinal;
             clear();
@@ -385,19 +403,27 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
         if (rb >= row_blocks) break;
     }
 
-    // ---- row blocks that are not finite or have small operands, by the fp32 instruction (any pairing of k with instruction
-    // and lane group is valid as long as both operands use the same)
-    int* any_b = reinterpret_cast<int*>(split_lds);
-    if (tid == 0) *any_b = 0;
+    // ---- tiles of 32 x 32 that are not finite or have small operands, by the fp32 instruction (any pairing of k with
+    // instruction and lane group is valid as long as both operands use the same).  Which tiles these are does not depend on
+    // how many of them a workgroup has: formed and stored rows give the same bits.
+    int* low_cols = reinterpret_cast<int*>(split_lds);
+    if (tid < NT) low_cols[tid] = 0;
     __syncthreads();
-    if (low_b < kLowBits) *any_b = 1;
+#pragma unroll
+    for (int x = 0; x < kPer; ++x)
+        if (low_b[x] < kLowBits && wave + 4 * x < NT) low_cols[wave + 4 * x] = 1;
     __syncthreads();
-    if (*any_b) again = ~0ull;
-    if (again == 0) return;
+    uint32_t tiles_b = 0;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) tiles_b |= (uint32_t)low_cols[nt] << nt;
+    tiles_b = __builtin_amdgcn_readfirstlane(tiles_b);
+    if (again == 0 && tiles_b == 0) return;
     rb -= stride * ordinal;
 #pragma unroll 1
     for (int o = 0; o < ordinal; ++o, rb += stride) {
-        if (!(again >> min(o, 63) & 1)) continue;
+        if (!(again >> min(o, 63) & 1) && tiles_b == 0) continue;
+        const uint32_t tiles = tiles_b | not_finite_stored(rb);
+        low = ~0u;
         clear();
         if constexpr (FUSE) {
             rank_of(rb);
@@ -422,7 +448,7 @@ __global__ __launch_bounds__(kThreads, dx_waves(NT, FUSE)) void k_dx_split(Split
                 }
             }
         }
-        store_c(rb);
+        store_c(rb, __any(low < kLowBits) ? ~0u : tiles);
     }
 }
 

@@ -119,6 +119,20 @@ def test_narrow_layers_of_many_rows(H, D, K, n):
     test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, n, 0.6, True)
 
 
+@pytest.mark.parametrize("n", [200, 40_000])
+@pytest.mark.parametrize("where,value", [("W", float("inf")), ("W", 1e-36), ("E", float("nan")), ("E", 1e-36), ("ds", float("inf"))])
+def test_values_that_are_redone(n, where, value):
+    """Formed and stored rows are split into other column slabs (eight tiles of dX, at most four of formed rows): what is
+    redone for such a value, and with it the last bits, is the same."""
+    H, D, K = 4, 64, 256
+    X, W, Z, ds, a_r, E, rank = make(torch.float32, H, D, K, n, None, True, seed=n)
+    {"W": W[200, 70:71], "E": E.view(n, -1)[n // 2, 9:10], "ds": ds[n - 1, 3:4]}[where].fill_(value)
+    Ep, dW1, dX1, da_r1, lwork = reference(X, W, Z, ds, a_r, E, rank, H, D)
+    dW2, dX2 = fused(X, W, ds, a_r, E, rank, H, D, lwork)
+    for x, y in ((dX1, dX2), (dW1, dW2)):
+        assert torch.equal(torch.isnan(x), torch.isnan(y)) and torch.equal(x.nan_to_num(), y.nan_to_num())
+
+
 @pytest.mark.parametrize("dtype,H,D,K", [(torch.float32, 3, 10, 100), (torch.float32, 4, 16, 256),
                                          (torch.bfloat16, 16, 16, 64), (torch.float32, 2, 200, 64),
                                          (torch.bfloat16, 4, 12, 32)])
