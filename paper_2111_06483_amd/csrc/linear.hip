@@ -1299,6 +1299,17 @@ int rows_store(const void* E, const RowsOp& op, void* out, int dtype, int64_t n,
     return SAR_OK;
 }
 
+// Which fp32 dX goes by pieces (k_dx_split) and which by the fp32 instruction (k_gemm_skinny; stored and formed rows alike).
+// Sums of 16 and fewer: not measured.  Up to 32 columns are one tile of the two that k_dx_split takes: 17 to 37% slower (F
+// = 100 to 400, 250000 rows 16 columns 28 -> 36, 90 -> 120 us).  Up to 64 columns of rows that end within a line of memory are
+// read twice as they stream from memory, in steps of 64 bytes: 1000000 rows F = 100, 200, 400 175 -> 191, 259 -> 319, 476 -> 534
+// (whole lines, F = 128, 256: 201 -> 183, 336 -> 315; within reach of the 256 MiB cache, 250000 rows F = 100 47 -> 41).
+bool dx_by_split(int64_t n, int K, int F)
+{
+    if (F <= 16 || K <= 32) return false;
+    return !(K <= 64 && F > 64 && F % 32 != 0 && n * F * (int64_t)sizeof(float) > (int64_t)256 << 20);
+}
+
 // op == nullptr: dZ is the stored [n,F] operand.  Otherwise dZ is the stored part of the rows
 // `op` describes and both products form the rows as they load them.
 int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float* W, float* dW, void* dX, int dtype,
@@ -1348,9 +1359,9 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
     if (dX) {
         // dX[n,K] = dZ W^T : B(k = f, n = kcol) = W[kcol * F + f]
         SkinnyPlan plan;
-        // (shorter sums: not measured; dX in the place of dZ: k_dx_split reads a row again after parts of dX are stored, for
-        // its other columns and for rows that are redone, k_gemm_skinny of one slab has read its rows by then)
-        if (dtype == SAR_F32 && F > 16 && dX != dZ) {
+        // (dX in the place of dZ: k_dx_split reads a row again after parts of dX are stored, for its other columns and for
+        // rows that are redone, k_gemm_skinny of one slab has read its rows by then)
+        if (dtype == SAR_F32 && dx_by_split(n, K, F) && dX != dZ) {
             SAR_TRY(sar::split_dx(static_cast<const float*>(dZ), op, W, static_cast<float*>(dX), n, K, F, st));
         } else if (plan_skinny(F, K, dtype, 0, &plan)) {
             SkinnyArgs sk{dZ, F, n, W, 1, F, dX, K, F, K, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,

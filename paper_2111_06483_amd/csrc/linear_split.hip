@@ -852,12 +852,12 @@ int split_dw(const float* X, const float* dZ, const RowsOp* op, float* partial, 
 {
     const int nw = F <= 64 ? 64 : F <= 128 ? 128 : 256;
     const int64_t tiles = (int64_t)((F + nw - 1) / nw) * ((K + kDwKf - 1) / kDwKf);
-    // As many workgroups as run at once, one per CU, where all have the same work; where the last tiles are narrower twice as
-    // many, so that CUs that end early take another.  (Each writes a partial tile: 100000 rows 283 x 100 104 us with 341
-    // slabs, 94 with 170; 40000 formed rows 64 x 36 26 with 512, 18 with 256.)  Stored and formed rows alike: their sums
-    // are to be the same bits.
+    // As many workgroups as run at once, one per CU, where all have the same work and where output tiles are narrow; where the
+    // last of wider tiles are narrower twice as many, so that CUs that end early take another.  (Each writes a partial tile:
+    // 100000 rows 283 x 100 104 us with 341 slabs, 94 with 170; 40000 rows 203 x 64 30 with 512 over both tiles, 22 with 256,
+    // 250000 rows 94 and 87.)  Stored and formed rows alike: their sums are to be the same bits.
     const bool even = (F % nw == 0 || F <= nw) && (K % kDwKf == 0 || K <= kDwKf);
-    const int64_t want = std::max<int64_t>(1, (even ? 256 : 512) / tiles);
+    const int64_t want = std::max<int64_t>(1, (even || nw == 64 ? 256 : 512) / tiles);
     *slabs = (int)std::min<int64_t>(want, most_slabs);
     const int64_t rows = ((n + *slabs - 1) / *slabs + kDwSum - 1) / kDwSum * kDwSum;
     auto with = [&](auto fuse, auto ragged) {

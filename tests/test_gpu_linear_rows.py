@@ -113,9 +113,11 @@ def test_heads_that_lanes_hold_in_turns(H, D, K):
     test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, 3001, 0.6, True)
 
 
-@pytest.mark.parametrize("H,D,K,n", [(4, 16, 64, 70_000), (1, 64, 128, 40_000), (3, 12, 32, 100_000), (8, 8, 100, 50_000)])
-def test_narrow_layers_of_many_rows(H, D, K, n):
-    """More rows than dW has slabs of 32: as many slabs whether the rows are stored or formed."""
+@pytest.mark.parametrize("H,D,K,n", [(4, 16, 64, 70_000), (1, 64, 128, 40_000), (3, 12, 32, 100_000), (8, 8, 100, 50_000),
+                                     (4, 16, 36, 3001), (4, 16, 32, 3001), (5, 20, 64, 675_000)])
+def test_narrow_layers(H, D, K, n):
+    """More rows than dW has slabs of 32: as many slabs whether the rows are stored or formed.  And both sides of the lines
+    at which dX goes by the fp32 instruction: 32 columns, up to 64 of rows beyond 256 MiB that end within a line."""
     test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, n, 0.6, True)
 
 
