@@ -1781,27 +1781,28 @@ bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
 
 // Forward over all blocks by rows: how many rows at the head of the list all twelve wavefronts of a workgroup share (0:
 // workgroups of four).  A workgroup of four takes 32 edges of a row per round trip to memory, so a row of more edges than
-// its fair share (about 2048 of them run at once) decides when the launch ends; workgroups of twelve fill a CU less evenly.
-// Times of twelve over four in turn on shares of power-law graphs, by how many shares the longest row has at least (from
-// its class) and how many rows have 1024 edges:
-//   - two shares or more: rows of 1 KiB with scores formed in flight (4 x 64, 2 x 128 fp32) 0.93 to 1.01, others 0.78 to
-//     0.96 (11 shares, 1.5 M edges: 501 -> 358 us, 4 x 64 bf16 434 -> 253);
-//   - one to two shares, 256 such rows (the CUs) and more: rows of 1 KiB with scores in flight 0.97 to 1.04, mostly slower
-//     (1.1 shares, 15 M edges 2186 / 2181 and 2155 / 2184 us; 1.9 shares, 9 M 1508 / 1546), with given ones 0.95 to 1.03,
-//     others 0.76 to 1.03 (8 x 32 bf16, 15 M edges 1202 -> 1081; 309 rows, 3.7 M edges 233 / 240);
-//   - one to two shares, 112 to 181 rows: 0.99 to 1.13 (1 x 128 fp32, 2.5 M edges 166 / 176);
-//   - less: 0.97 to 1.17 (4.0 M edges, 8 x 32 bf16 253 / 263).
-// The forms for padded layers spill a few registers at twelve wavefronts (20 to 32 bytes a lane) and are among these
-// figures; one workgroup of them per CU and no spills took 1.02 to 1.39 times as long as four wavefronts where this takes
-// 0.92 to 0.99.
+// its fair share (about 2048 of them run at once) decides when the launch ends.  Workgroups of twelve hold 24 wavefronts on a
+// CU instead of 32, and a row of a few times their 768 edges is soon over either way.  Times of twelve over four in turn on
+// 2600 shares of power-law graphs (20 thousand to 16 million edges, 2 to 100 a row, twelve layers), where the longest row has
+// at least a share:
+//   - 4096 edges and more: 0.82 in the mean, 0.96 at the 90th percentile, 1.05 at most (1.5 M edges, rows up to 10143, 4 x 64
+//     fp32 501 -> 358 us, bf16 434 -> 253; 9 M edges, 8 x 32 bf16 with given scores 1162 -> 1029);
+//   - 2048 to 4095 (the class is what is known): 0.95; with 96 such rows of 1024 edges and more and a share and a half 0.9, 1.13
+//     at most;
+//   - 1024 to 2047: 1.08 to 1.41, most on small graphs (0.2 M edges 84 -> 114 us);
+//   - rows of 1 KiB with scores formed in flight (4 x 64, 2 x 128 fp32): 1.00 up to two shares (15 M edges 2186 / 2181 and 2155
+//     / 2184 us), 0.87 to 0.96 beyond.
+// Less than a share: 1.02.  The forms for padded layers spill a few registers at twelve wavefronts (20 to 32 bytes a lane) and
+// are among these figures; one workgroup of them per CU and no spills took 1.02 to 1.39 times as long as four wavefronts
+// where this takes 0.92 to 0.99.
 int64_t shared_hubs(const sar_blocks_t* b, size_t row_bytes, bool scores_given)
 {
-    if (b->n_f_hub == 0) return 0;
+    const int64_t longest = (b->f_longest + 1) / 2;      // at least
+    if (longest < 2048 || (longest < 4096 && b->n_f_hub < 96)) return 0;
     int64_t edges = 0;
     for (int q = 0; q < b->P; ++q) edges += b->blk[q].nnz;
-    const int64_t reach = (b->f_longest + 1) / 2 * kMaxPersistentWGs;
-    const bool one_share = b->n_f_hub >= 256 && (row_bytes < 1024 || scores_given);
-    return reach >= (one_share ? edges : 2 * edges) ? b->n_f_hub : 0;
+    const double least = row_bytes >= 1024 && !scores_given ? 2.0 : longest < 4096 ? 1.5 : 1.0;
+    return (double)longest * kMaxPersistentWGs >= least * (double)edges ? b->n_f_hub : 0;
 }
 
 // Forward: heads of 32 to 128 fp32 values or 64 to 128 bf16 values (slices of 128 bytes, a cache line, and more: 64-byte

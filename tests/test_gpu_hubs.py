@@ -17,7 +17,7 @@ TOL = 8 * (9000 / 4) ** 0.5 * 2.0 ** -24
 
 def graph(seed, only_few):
     g = torch.Generator().manual_seed(seed)
-    lengths = [5, 0, 3000, 1] if only_few else LENGTHS + [3] * 40
+    lengths = [5, 0, 5000, 1] if only_few else LENGTHS + [3] * 40
     dst = torch.cat([torch.full((n,), i, dtype=torch.int64) for i, n in enumerate(lengths)])
     src = torch.cat([torch.randperm(N, generator=g)[:n] for n in lengths])
     own = len(lengths)
@@ -31,13 +31,15 @@ def check(got, want, tol):
     assert float((got.double() - want).abs().max()) <= tol * float(want.abs().max())
 
 
-@pytest.mark.parametrize("filler,few,many", [(0, 12, 12), (200_000, 4, 12)])
-def test_which_workgroups_share_rows(filler, few, many):
-    """400 rows of 1100 edges: far more than a workgroup's share of all edges, and one to two shares among 1.2 million others,
-    where rows of 1 KiB stay with workgroups of four wavefronts."""
-    counts = torch.cat([torch.full((400,), 1100), torch.full((filler,), 6)]).cuda()
+@pytest.mark.parametrize("rows,length,filler,few,many", [(400, 2100, 0, 12, 12), (400, 2100, 300_000, 4, 12),
+                                                         (60, 2100, 0, 4, 4), (2, 4200, 0, 12, 12), (400, 1100, 0, 4, 4)])
+def test_which_workgroups_share_rows(rows, length, filler, few, many):
+    """Rows far longer than a workgroup's share of all edges and of one to two shares (there rows of 1 KiB stay with workgroups
+    of four wavefronts); too few of 2048 edges, two of 4096, and none as long as that."""
+    counts = torch.cat([torch.full((rows,), length), torch.full((filler,), 6)]).cuda()
     n, g = counts.numel(), torch.Generator(device="cuda").manual_seed(1)
-    dst = torch.repeat_interleave(torch.arange(n, device="cuda"), counts)
+    n += 5000               # (sources enough)
+    dst = torch.repeat_interleave(torch.arange(n - 5000, device="cuda"), counts)
     src = torch.randint(0, n, (dst.numel(),), generator=g, device="cuda")
     b = sar.sar_blocks_build(src, dst, torch.zeros(n, dtype=torch.int32, device="cuda"), 1, 0, sar.SAR_BUILD_FUSED)
     for dtype, H, D, waves in ((torch.float32, 4, 64, few), (torch.bfloat16, 4, 64, many), (torch.float32, 2, 100, many)):
