@@ -1772,11 +1772,11 @@ bool even_rows(int64_t rows, int64_t edges, int64_t longest)
     return rows > 0 && edges > 0 && longest > 0 && longest * rows <= 4 * edges;
 }
 bool sets_for_xcds(int sets) { return sets == 1 || sets == 2 || sets == 4 || sets % slices::kXcds == 0; }
-bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table)
+bool sweeps_pay(int sets, int lanes, int64_t rows, int64_t edges, int64_t table, double least_uses)
 {
     const int parts = sets < slices::kXcds ? slices::kXcds / sets : 1;
     const double sweeps = rows / (parts * 512.0 * (kWave / lanes)), uses = edges / (parts * std::max(sweeps, 1.0) * table);
-    return sweeps >= 4.0 && uses >= 2.0;
+    return sweeps >= 4.0 && uses >= least_uses;
 }
 
 // Forward over all blocks by rows: how many rows at the head of the list all twelve wavefronts of a workgroup share (0:
@@ -1806,16 +1806,20 @@ int64_t shared_hubs(const sar_blocks_t* b, size_t row_bytes, bool scores_given)
 }
 
 // Forward: heads of 32 to 128 fp32 values or 64 to 128 bf16 values (slices of 128 bytes, a cache line, and more: 64-byte
-// slices bring the neighbour's half along, 4 x 16 fp32 310 -> 440 us).  Times in us on uniform graphs, one worker of four
-// on 200 thousand nodes unless said otherwise, kernels of gat_f256.h / slices:
+// slices bring the neighbour's half along, 4 x 16 fp32 310 -> 440 us).  Tables that mostly stay in the L2s anyway gain
+// nothing, and `whole`, the bytes of all sources' rows, says which.  Times of slices over rows on 7600 uniform graphs (6 to
+// 370 thousand nodes, 16 to 500 edges a row, 1 to 16 blocks, 13 layers; mean, 90th percentile, most):
 //   - the head's slices of the whole table within 3 of an XCD's 4 MiB of L2 and at least 10 thousand wavefronts of work:
-//     no barriers.  20 thousand nodes, one worker, 8 x 32: 100 edges a row 215 / 134, 25 edges 63 / 40; 5 thousand
-//     nodes, 4 x 64, 50 edges (5 thousand wavefronts) 18.0 / 19.0;
-//   - else where sweeps pay.  8 x 32: 500 edges a row (10 uses) 3380 / 2170, 200 edges (4.1) 1370 /
-//     1045, 100 edges (2.05) 700 / 654, 50 edges (1.0) 358 / 384; 4 x 64 (5.1) 3366 / 2183, bf16 1632 / 1464; 4 x 100 (2.6)
-//     5850 / 4700; 1 x 128 (2.6) 1658 / 1302.
+//     no barriers.  fp32 from 12 MiB on 0.70, 0.83, 0.92 (20 thousand nodes, 8 x 32, 100 edges a row 215 -> 134 us), 8 to 12
+//     MiB 0.8, 1.1, 1.2; bf16 1.05, 1.09, 1.27;
+//   - else where sweeps pay.  fp32 from 20 MiB on 0.71, 0.89, 1.12 (50 thousand destinations of 200 thousand nodes, 8 x 32,
+//     500 edges 3380 -> 2170 us, 100 edges, two uses, 700 -> 654), 12 to 20 MiB 0.9, 1.26, 1.5.  bf16 of one head 0.7, 0.8,
+//     0.8; of several from 96 MiB on 0.93, 0.98, 0.98, 48 to 96 MiB 1.02, 1.1, 1.2, less 1.1 to 1.6;
+//   - scores given, whose gathers cost each head a line more: fp32 from 24 MiB on 0.75, 0.90, 1.13, bf16 from 16 MiB on 0.84,
+//     1.01, 1.25.  Where all eight XCDs gather another head's (8 heads and more) from five uses on; with two to three they
+//     take 1.13 (12 M edges, 150 thousand nodes 1840 -> 2430 us).
 enum class Slices { kNo, kFree, kSwept };
-Slices fwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D)
+Slices fwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D, bool scores_given)
 {
     if (D % 4 != 0 || D > 128 || D < (dtype == SAR_F32 ? 32 : 64) || !sets_for_xcds(H)) return Slices::kNo;
     int64_t edges = 0, sources = 0;
@@ -1824,19 +1828,27 @@ Slices fwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D)
         sources += b->blk[q].n_src;
     }
     if (!even_rows(b->n_dst, edges, b->f_longest)) return Slices::kNo;
+    const bool f32 = dtype == SAR_F32;
     const int lanes = slice_lanes(D);
-    if (sources * D * (dtype == SAR_F32 ? 4 : 2) <= 3 << 20)
-        return b->n_dst * H / (kWave / lanes) >= 10000 ? Slices::kFree : Slices::kNo;
-    return sweeps_pay(H, lanes, b->n_dst, edges, sources) ? Slices::kSwept : Slices::kNo;
+    const int64_t slice = sources * D * (f32 ? 4 : 2), whole = slice * H;
+    if (slice <= 3 << 20)
+        return f32 && whole >= 12 << 20 && b->n_dst * H / (kWave / lanes) >= 10000 ? Slices::kFree : Slices::kNo;
+    const int64_t least = scores_given ? (f32 ? 24 : 16) : f32 ? 20 : H > 1 ? 96 : 0;
+    if (whole < least << 20) return Slices::kNo;
+    return sweeps_pay(H, lanes, b->n_dst, edges, sources, scores_given && H >= slices::kXcds ? 5.0 : 2.0) ? Slices::kSwept
+                                                                                                     : Slices::kNo;
 }
 
-// Backward: fp32 heads of 32, 64 or 128 values, in one or two slices of 128 values (the additions to ds), where sweeps
-// pay.  As above: 8 x 32 500 edges a row (2.6 uses) 3780 / 3355, 200 edges (1.0) 1585 / 1610; 4 x 64
-// (2.6) 3760 / 3370; 2 x 128 (2.6) 3690 / 3375; bf16 4 x 64 2000 / 2630.
+// Backward: fp32 heads of 32, 64 or 128 values, in one or two slices of 128 values (the additions to ds), where sweeps pay
+// and G is 28 MiB and more: on 3500 such graphs 0.87, 0.95, 1.07 of the time by rows (50 thousand destinations of 200
+// thousand nodes, 8 x 32, 500 edges a row 3780 -> 3170 us); 16 to 24 MiB 1.02, 1.2, 1.5, less than 8 MiB 1.35 to 1.8.  bf16 4
+// x 64 2000 / 2630.
 bool bwd_by_slices(const sar_blocks_t* b, int dtype, int H, int D, int64_t edges)
 {
     if (dtype != SAR_F32 || !(D == 32 || D == 64 || D == 128) || !(H * D == 128 || H * D == 256)) return false;
-    return even_rows(b->n_ft_wide, edges, b->ft_longest) && sweeps_pay(H * D / 128, 32, b->n_ft_wide, edges, b->n_dst);
+    if (b->n_dst * H * D * (int64_t)sizeof(float) < 28 << 20) return false;
+    return even_rows(b->n_ft_wide, edges, b->ft_longest) &&
+           sweeps_pay(H * D / 128, 32, b->n_ft_wide, edges, b->n_dst, 2.0);
 }
 
 }  // namespace
@@ -1858,7 +1870,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         SAR_CHECK_ARG(aligned16(Zq[q]), "Zq[%d] must be 16-byte aligned", q);
     }
     hipStream_t st = sar::as_stream(stream);
-    const Slices sl = fwd_by_slices(b, dtype, H, D);
+    const Slices sl = fwd_by_slices(b, dtype, H, D, tq != nullptr);
     if (sl != Slices::kNo) {
         f256::FwdP p{};
         f256::Tabs tabs{};
