@@ -1085,7 +1085,11 @@ int launch_fwd_waves(const FwdArgs& a, const PtrTab& zt, const PtrTab& tt, hipSt
 {
     constexpr int B = LPH >= 8 ? 8 : 4;
     auto fn = f256::k_gat_fwd_f256<T, LPH, B, FLY, PAD, NW>;
-    static const int resident = resident_workgroups(fn, NW * kWave);
+    // Formed scores of 4 or 8 heads and 1 KiB rows: registers let eight workgroups of four run on a CU, but seven are
+    // faster (1 M rows of 2 edges, 4 heads of 64: 594 us with eight, 498 with seven; 100 thousand rows of 40, some of
+    // them thousands long: 459 and 450).  The others lose by it (2 M edges to rows of bf16, given scores: 354 and 370).
+    constexpr bool seven = NW == kWavesPerWG && FLY && !PAD && sizeof(T) == 4 && (LPH == 8 || LPH == 16);
+    static const int resident = std::min(resident_workgroups(fn, NW * kWave), seven ? kMaxPersistentWGs / 8 * 7 : kMaxPersistentWGs);
     fn<<<persistent_grid_for(a.n_rows, a.n_long, resident, NW), NW * kWave, 0, st>>>(fwd_params(a), fwd_tabs(zt, tt));
     SAR_LAUNCH_CHECK();
     return SAR_OK;
