@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsar_mi355x.so")
-SOURCES = ["builder.hip", "spmm.hip", "gat.hip", "gat_slices.hip", "linear.hip", "linear_split.hip"]
+SOURCES = ["builder.hip", "spmm.hip", "gat.hip", "gat_slices.hip", "linear.hip", "linear_split.hip", "linear_few.hip"]
 BENCH_LIB = os.path.join(HERE, "libsar_bench.so")
 BENCH_SOURCES = ["probe.hip"]
 

@@ -12,10 +12,12 @@
 //
 // Z = X W and dX = dZ W^T read their rows straight into registers.  Where the small operand
 // fits in LDS it stays there (k_gemm_skinny); where it does not it passes through LDS in
-// steps of the contraction (k_gemm_steps).  dW of bf16 rows has a kernel of its own (k_dw).
+// steps of the contraction (k_gemm_steps).  dW of bf16 rows has a kernel of its own (k_dw).  Few rows
+// go another way (linear_few.hip).
 #include <algorithm>
 
 #include "linear_common.h"
+#include "linear_few.h"
 #include "linear_split.h"
 #include "sar_internal.h"
 
@@ -1129,6 +1131,13 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const float* __restrict__ par
     }
 }
 
+// Whether two operands share no memory (the kernels of few rows read an operand again after parts of the result are stored).
+bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return !a || !b || x + a_bytes <= y || y + b_bytes <= x;
+}
+
 constexpr int kMaxSlabs = 512;
 
 // How many slabs of rows dW is split into: as many as fill the chip (1024 workgroups), each of at
@@ -1175,13 +1184,20 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     // from the STORED (rounded) rows in one pass afterwards: every later step reads those rows,
     // and a score of the unrounded sums differs from theirs by up to the storage rounding, which
     // is enough to move LeakyReLU's kink for about one edge in a thousand.
+    const size_t elem = dtype == SAR_F32 ? 4 : 2;
+    const bool alone = apart(X, (size_t)n * K * elem, Z, (size_t)n * F * elem);
     if (want_scores && dtype == SAR_F32 && 2 * H <= 32 && rows_whole && plan_skinny(K, F, dtype, 1, &plan)) {
+        if (alone && sar::few_rows(dtype, n, K, F, true, plan.nt))
+            return sar::few_fwd(dtype, {X, n, W, Z, K, F, a_score, a_score2, score, score2, H, D}, false, st);
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, a_score, a_score2, score, score2, H, D,
                       plan.stage_off};
         SAR_TRY((launch_skinny<float, float, true>(sk, plan, st)));
         return SAR_OK;
     }
-    if (rows_whole && plan_skinny(K, F, dtype, 0, &plan)) {
+    const bool natural = !(rows_whole && plan_skinny(K, F, dtype, 0, &plan));
+    if (alone && sar::few_rows(dtype, n, K, F, false, natural ? 2 : plan.nt)) {
+        SAR_TRY(sar::few_fwd(dtype, {X, n, W, Z, K, F, nullptr, nullptr, nullptr, nullptr, 0, 0}, natural, st));
+    } else if (!natural) {
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                       plan.stage_off};
         if (dtype == SAR_F32)
@@ -1315,6 +1331,29 @@ bool dx_by_split(int64_t n, int K, int F)
 int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float* W, float* dW, void* dX, int dtype,
                     int64_t n, int K, int F, void* work, size_t work_bytes, hipStream_t st)
 {
+    auto add_slabs = [&](int slabs) -> int {
+        const int64_t count = (int64_t)K * F;
+        k_sum_slabs<<<(unsigned)std::min<int64_t>((count + 31) / 32, 8192), 256, 0, st>>>(
+            static_cast<const float*>(work), slabs, count, dW);
+        SAR_LAUNCH_CHECK();
+        return SAR_OK;
+    };
+    const size_t elem = dtype == SAR_F32 ? 4 : 2;
+    if (sar::few_rows_bwd(dtype, n, K, F) && apart(dX, (size_t)n * K * elem, dZ, (size_t)n * F * elem) &&
+        (!dW || apart(dX, (size_t)n * K * elem, X, (size_t)n * K * elem))) {
+        if (dW) {
+            const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
+            SAR_CHECK_ARG(work != nullptr && work_bytes >= need, "work_bytes=%zu is below the %zu bytes required",
+                          work_bytes, need);
+        }
+        SkinnyPlan plan;
+        const bool split = dtype == SAR_F32 && dx_by_split(n, K, F);
+        const bool natural = !split && !plan_skinny(F, K, dtype, 0, &plan);
+        int slabs = 0;
+        SAR_TRY(sar::few_bwd(dtype, {X, dZ, W, dW, dX, static_cast<float*>(work), n, K, F, slabs_for(n, K, F), split, natural},
+                             op, &slabs, st));
+        return slabs > 0 ? add_slabs(slabs) : SAR_OK;
+    }
     if (dW) {
         int slabs = slabs_for(n, K, F);
         const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
@@ -1351,10 +1390,7 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
                                   static_cast<float*>(work), n, K, F, slabs, &slabs, st));
         else
             SAR_TRY(slabs_bf16());
-        const int64_t count = (int64_t)K * F;
-        k_sum_slabs<<<(unsigned)std::min<int64_t>((count + 31) / 32, 8192), 256, 0, st>>>(
-            static_cast<const float*>(work), slabs, count, dW);
-        SAR_LAUNCH_CHECK();
+        SAR_TRY(add_slabs(slabs));
     }
     if (dX) {
         // dX[n,K] = dZ W^T : B(k = f, n = kcol) = W[kcol * F + f]

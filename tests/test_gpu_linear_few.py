@@ -1,0 +1,94 @@
+"""The transform of few rows against the kernels that many rows take: a row's results do not depend on how many rows
+a call has, so the first rows of a large call are the reference, bit for bit."""
+import pytest
+import torch
+
+from paper_2111_06483_amd import sar
+
+pytestmark = pytest.mark.gpu
+MANY = 60_000       # beyond the lines of every width below
+
+# tiles of one column to several, contractions that end inside a piece, a chunk, a ring of chunks; heads of any width
+SHAPES = [(64, 4, 16), (36, 1, 33), (100, 4, 64), (128, 3, 20), (256, 8, 32), (255, 1, 47), (72, 2, 50), (300, 5, 12), (21, 1, 130)]
+
+
+def layer(K, H, D, dtype):
+    g = torch.Generator(device="cuda").manual_seed(K * 1000 + H * D)
+    draw = lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+    return (draw(MANY, K).to(dtype), draw(MANY, H * D).to(dtype), draw(K, H * D) / K ** 0.5, draw(H, D), draw(H, D),
+            draw(MANY, H))
+
+
+@pytest.mark.parametrize("K,H,D", SHAPES)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("scores", [0, 1, 2])
+def test_forward(K, H, D, dtype, scores):
+    X, _, W, a, b, _ = layer(K, H, D, dtype)
+
+    def run(n):
+        Z = torch.empty(n, H * D, dtype=dtype, device="cuda")
+        s, t = torch.empty(n, H, device="cuda"), torch.empty(n, H, device="cuda")
+        second = (b, t) if scores == 2 else (None, None)
+        sar.sar_linear_fwd(X[:n], W, Z, *((a, s) if scores else (None, None)), *second)
+        return [Z, s, t][: 1 + scores]
+
+    want = run(MANY)
+    for n in (1, 32, 33, 127, 1000):
+        for got, many in zip(run(n), want):
+            assert torch.equal(got, many[:n])
+
+
+@pytest.mark.parametrize("K,H,D", SHAPES)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("formed", [False, True])
+def test_backward(K, H, D, dtype, formed):
+    X, E, W, a, _, ds = layer(K, H, D, dtype)
+    F = H * D
+
+    def run(n):
+        work = torch.empty(max(1, sar.sar_linear_workspace_bytes(n, K, F) // 4), device="cuda")
+        dW, dX = torch.ones(K, F, device="cuda"), torch.empty(n, K, dtype=dtype, device="cuda")
+        if not formed:
+            sar.sar_linear_bwd(X[:n], E[:n], W, dW, dX, work)
+            return dW, dX, E[:n].double()
+        # every third row has no stored part
+        has = torch.arange(n, device="cuda") % 3 != 1
+        rank = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+        rank[1:] = torch.cumsum(has, 0)
+        stored = E[:n][has].contiguous()
+        sar.sar_linear_bwd_rows(X[:n], stored, rank.data_ptr(), ds[:n].contiguous(), a, H, D, W, dW, dX, n, dtype, work)
+        rows = torch.where(has[:, None], E[:n], 0).double() + (ds[:n, :, None].double() * a.double()).reshape(n, F)
+        return dW, dX, rows.to(dtype).double()
+
+    try:
+        _, want, _ = run(MANY)
+    except sar.SarError as e:
+        assert formed and e.code == sar.SAR_ERR_UNSUPPORTED      # (the same shapes are refused for any number of rows)
+        with pytest.raises(sar.SarError):
+            run(100)
+        return
+    # (n, groups of 32 rows: one, one for each wavefront, one slab, several)
+    for n in (1, 2, 31, 128, 129, 640, 641, 1500):
+        dW, dX, rows = run(n)
+        assert torch.equal(dX, want[:n])
+        exact = 1.0 + X[:n].double().T @ rows
+        # a sum of n products: n^1/2 roundings of the running sum, below 2^-24 of its scale each, and (bf16) those of the
+        # formed rows, which 64 bits round to the other neighbour where fp32's multiply-add is within its rounding of a tie
+        tol = max(2.0, n ** 0.5) * 2.0 ** -24 + (2.0 ** -9 * 0.1 if formed and dtype == torch.bfloat16 else 0.0)
+        assert float((dW.double() - exact).norm() / exact.norm()) < tol
+
+
+def test_result_over_an_operand():
+    """Z over X and dX over dZ go the other kernels' way: a tile's rows are read again after others are stored."""
+    X = torch.randn(500, 64, device="cuda")
+    W = torch.randn(64, 64, device="cuda") / 8
+    Z, dX = torch.empty_like(X), torch.empty_like(X)
+    sar.sar_linear_fwd(X, W, Z)
+    sar.sar_linear_bwd(None, X, W, None, dX, None)
+    A, B = X.clone(), X.clone()
+    sar.sar_linear_fwd(A, W, A)
+    sar.sar_linear_bwd(None, B, W, None, B, None)
+    assert torch.equal(A, Z)
+    want = X.double() @ W.double().T
+    assert float((B.double() - want).norm() / want.norm()) < 8 * 2.0 ** -24
+    assert float((dX.double() - want).norm() / want.norm()) < 8 * 2.0 ** -24
