@@ -690,17 +690,17 @@ __device__ inline void dw_tile(const DwArgs& g, const RowsOp& op, int slab, int 
     }
 }
 
-// The workgroups of dW (none or dw_groups), then those of dX (none or x_groups times its column tiles).
+// The workgroups of dX (x_groups times its column tiles, or none), whose chains are the longer ones, then those of dW.
 template <typename T, bool SPLIT, bool NAT, bool FUSE, bool TAIL>
-__global__ __launch_bounds__(kThreads, 2) void k_few_bwd(FewArgs g, DwArgs w, RowsOp op, int dw_groups, int x_groups)
+__global__ __launch_bounds__(kThreads, 2) void k_few_bwd(FewArgs g, DwArgs w, RowsOp op, int dx_blocks, int x_groups)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if ((int)blockIdx.x < dw_groups) {
+    const int b = (int)blockIdx.x;
+    if (b >= dx_blocks) {
         __shared__ float part[kWaves - 1][16][64];
-        const int n_tiles = (w.F + 31) / 32, k_tiles = (w.K + 31) / 32, id = (int)blockIdx.x;
+        const int n_tiles = (w.F + 31) / 32, k_tiles = (w.K + 31) / 32, id = b - dx_blocks;
         return dw_tile<T, FUSE>(w, op, id / (n_tiles * k_tiles), id / n_tiles % k_tiles * 32, id % n_tiles * 32, wave, part);
     }
-    const int b = (int)blockIdx.x - dw_groups;
     const int64_t tile = (int64_t)(b % x_groups) * kWaves + wave;
     if (tile * 32 >= g.M) return;
     const int n0 = b / x_groups * 32;
@@ -746,12 +746,13 @@ template <typename T>
 int launch_bwd(const FewArgs& g, const DwArgs& w, const FewBwd& b, const RowsOp* op, hipStream_t st)
 {
     constexpr int kChunk = 32 / (int)sizeof(T);
-    const int dw_groups = b.dW ? w.slabs * ((w.F + 31) / 32) * ((w.K + 31) / 32) : 0;
+    const int dw_blocks = b.dW ? w.slabs * ((w.F + 31) / 32) * ((w.K + 31) / 32) : 0;
     const int x_groups = (int)((g.M + 32 * kWaves - 1) / (32 * kWaves));
-    const unsigned grid = (unsigned)(dw_groups + (b.dX ? x_groups * ((g.N + 31) / 32) : 0));
+    const int dx_blocks = b.dX ? x_groups * ((g.N + 31) / 32) : 0;
+    const unsigned grid = (unsigned)(dx_blocks + dw_blocks);
     const RowsOp o = op ? *op : RowsOp{};
     auto go = [&](auto kernel) -> int {
-        kernel<<<grid, kThreads, 0, st>>>(g, w, o, dw_groups, x_groups);
+        kernel<<<grid, kThreads, 0, st>>>(g, w, o, dx_blocks, x_groups);
         SAR_LAUNCH_CHECK();
         return SAR_OK;
     };
@@ -796,14 +797,14 @@ int few_fwd(int dtype, const FewArgs& g, bool natural, hipStream_t st)
 }
 
 // (dX tiles as above; dW of as many rows has its own.)  us, the kernels for many rows / this one, dX and dW with the slabs' sum:
-// fp32, formed rows, 64 -> 64 100 rows 18.8 / 7.2, 5000 20.0 / 9.3, 20000 23.8 / 22.5; 256 -> 256 500 43.8 / 14.7, 5000 46.1 /
-// 42.9, 10000 53.9 / 65.0; 128 -> 256 2000 41.4 / 20.8, 10000 46.2 / 47.3; stored rows, 256 -> 64 2000 16.8 / 9.7, 10000 23.5 /
-// 23.6.  bf16, formed rows, 256 -> 256 500 44.7 / 11.3, 10000 51.5 / 50.5, 20000 58.6 / 80.6; stored, 100 -> 256 2000 39.9 / 12.1,
-// 20000 45.8 / 32.9; 256 -> 64 10000 28.1 / 21.2.
+// fp32, formed rows, 64 -> 64 200 rows 18.8 / 8.8, 5000 20.1 / 9.2; 256 -> 256 600 41.0 / 17.8, 2500 43.5 / 23.3, 5000 45.9 /
+// 43.3; 128 -> 256 2500 41.8 / 20.2, 10000 46.7 / 45.0; stored rows, 256 -> 256 2500 38.2 / 19.0, 10000 49.3 / 49.1.  bf16, formed
+// rows, 256 -> 256 600 42.9 / 15.3, 5000 47.7 / 32.3, 10000 51.5 / 55.9; 128 -> 256 10000 48.1 / 33.7; stored, 100 -> 256 2500
+// 40.2 / 13.1, 10000 43.9 / 22.4.  (dX before dW in the grid and dW on half of the chip: 1300 rows 256 -> 256 24.5 -> 18.6.)
 bool few_rows_bwd(int dtype, int64_t n, int K, int F)
 {
     if (F < (dtype == SAR_F32 ? 4 : 8) || !small_operands(n, K, F)) return false;
-    return (n + 31) / 32 * ((K + 31) / 32) <= (dtype == SAR_F32 ? 1280 : 2560);
+    return (n + 31) / 32 * ((K + 31) / 32) <= (dtype == SAR_F32 ? 1280 : 2048);
 }
 
 int few_bwd(int dtype, const FewBwd& b, const RowsOp* op, int* slabs, hipStream_t st)
@@ -813,8 +814,8 @@ int few_bwd(int dtype, const FewBwd& b, const RowsOp* op, int* slabs, hipStream_
     *slabs = 0;
     if (b.dW) {
         const int64_t tiles = (int64_t)((b.K + 31) / 32) * ((b.F + 31) / 32), groups = (b.n + kGroup - 1) / kGroup;
-        // (up to five groups a wavefront are sooner done than a launch that adds slabs up)
-        const int64_t want = groups <= 5 * kWaves ? 1 : std::max<int64_t>(1, 512 / tiles);
+        // (two groups a wavefront are sooner done than a launch that adds slabs up; beside dX, half of the chip)
+        const int64_t want = groups <= 2 * kWaves ? 1 : std::max<int64_t>(1, (b.dX ? 256 : 512) / tiles);
         const int64_t s = std::min<int64_t>({want, (int64_t)b.most_slabs, (groups + kWaves - 1) / kWaves});
         w.groups = (int)((groups + s - 1) / s);
         w.slabs = (int)((groups + w.groups - 1) / w.groups);
