@@ -92,6 +92,52 @@ __device__ inline int bcast_i(int v)
     return __float_as_int(group_bcast<LPH, K>(__int_as_float(v)));
 }
 
+// The places of a batch that some slot of the wavefront has an edge for, in three groups [0, G1), [G1, G2), [G2, END) that
+// are skipped whole where none has.  Rows that end inside a batch are most of what these kernels see: of a batch of eight
+// a row of 8 edges fills two places with four slots and four with two, a source of one edge fills one, and an empty place
+// costs some fourteen instructions (its sum over the head, its weight's way back, its multiply-adds).  Without them, and
+// with the registers that the shorter live ranges free (112 -> 89: five wavefronts per SIMD instead of four), backward
+// kernels of 1 x 47 fp32 on 7.4M edges 541 -> 480 us, 4 x 32 on 75000 sources of 136 thousand edges 52 -> 47.
+template <int B, int G1, int G2, int END>
+struct Places {
+    bool any, more, most;     // uniform: some slot has an edge in group 0, 1, 2
+    template <int FROM, int TO, int R, typename F>
+    static __device__ inline void run(F& f)
+    {
+        constexpr int lo = FROM > R * B ? FROM - R * B : 0, hi = TO < R * B + B ? TO - R * B : B;
+        if constexpr (lo < hi)
+            static_for<hi - lo>([&](auto k) { f(std::integral_constant<int, lo + decltype(k)::value>{}); });
+    }
+    // f(K) for the places R * B + K of round R
+    template <int R, typename F>
+    __device__ inline void each(F f) const
+    {
+        run<0, G1, R>(f);
+        if (more) run<G1, G2, R>(f);
+        if (most) run<G2, END, R>(f);
+    }
+};
+
+// Rows of fewer than 8 edges, one per slot: the lists hold them by degree class (4 to 7 edges, 2 or 3, one, none), so the
+// rows of a wavefront are of one class but at the borders.
+template <int B>
+using FewPlaces = Places<B, 1, 3, 7>;
+template <int B>
+__device__ inline FewPlaces<B> few_places(int cnt)
+{
+    return {__builtin_amdgcn_ballot_w64(cnt > 0) != 0, __builtin_amdgcn_ballot_w64(cnt > 1) != 0,
+            __builtin_amdgcn_ballot_w64(cnt > 3) != 0};
+}
+
+// Batches of one row, `left` edges from the batch's first on, dealt to the slots in turn.
+template <int B>
+using RowPlaces = Places<B, 2, 4, 8>;
+template <int B>
+__device__ inline RowPlaces<B> row_places(int left, int n_slots)
+{
+    return {true, left > 2 * n_slots, left > 4 * n_slots};
+}
+
 // Adds the slots' values to slot 0 (n_slots a power of two; the other slots are left with junk).
 __device__ inline float sum_slots(float v, int lane, int n_slots, int width)
 {
@@ -114,7 +160,8 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
     for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {
         typename Row4<T>::Raw raw[B];
-        static_for<B>([&](auto kk) {
+        const RowPlaces<B> some = row_places<B>(cnt - k0, n_slots);
+        some.template each<0>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
             raw[K] = typename Row4<T>::Raw{};
             if (k0 + K * n_slots < cnt) {          // uniform: some slot has an edge here
@@ -128,7 +175,7 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
         const bool valid = p.live && p.k_pos < B && my_e < cnt;
         float tv = 0.f;
         if constexpr (FLY) {
-            static_for<B>([&](auto kk) {
+            some.template each<0>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 float v[4];
                 Row4<T>::unpack(raw[K], v);
@@ -156,7 +203,7 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
         }
         const float pe = fast_exp2(e2 - (st.m2 == -INFINITY ? 0.f : st.m2));   // 0 for the lanes without an edge
         st.l += pe;
-        static_for<B>([&](auto kk) {
+        some.template each<0>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
             const float pk = group_bcast<LPH, K>(pe);
             float v[4];
@@ -346,17 +393,18 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
         const int64_t i = m0.i;
         State st{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
         float s2 = 0.f;
+        const FewPlaces<B> some = few_places<B>(m0.cnt);
         if (mine) {
             if (p.on) load4_f32<RAG>(a.acc + i * a.ld + p.foff, st.acc);
             st.m2 = a.m[i * a.ldh + p.h] * kLog2e;
             st.l = p.k_pos == 0 ? a.l[i * a.ldh + p.h] : 0.f;
             s2 = a.s[i * a.ldh + p.h] * kLog2e;
         }
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            if (__builtin_amdgcn_ballot_w64(m0.cnt > r * B) == 0) break;
+        static_for<kRounds>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            if (!(r == 0 ? some.any : some.most)) return;
             typename Row4<T>::Raw raw[B];
-            static_for<B>([&](auto kk) {
+            some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 raw[K] = typename Row4<T>::Raw{};
                 const int j = bcast_i<LPH, K>(s0.j[r]);
@@ -365,7 +413,7 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
             const bool valid = p.live && p.k_pos < B && r * B + p.k_pos < m0.cnt;
             float tv = 0.f;
             if constexpr (FLY) {
-                static_for<B>([&](auto kk) {
+                some.template each<r>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     float v[4];
                     Row4<T>::unpack(raw[K], v);
@@ -387,7 +435,7 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
 #pragma unroll
             for (int x = 0; x < 4; ++x) st.acc[x] *= c;
             st.m2 = mn;
-            static_for<B>([&](auto kk) {
+            some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 const float pk = group_bcast<LPH, K>(pe);
                 float v[4];
@@ -395,7 +443,7 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
 #pragma unroll
                 for (int x = 0; x < 4; ++x) st.acc[x] = fmaf(pk, v[x], st.acc[x]);
             });
-        }
+        });
         const float l = group_all<LPH, OpSum>(st.l);
         if (mine) {
             if (p.on) store4<float, RAG>(a.acc + i * a.ld + p.foff, st.acc);
@@ -493,20 +541,23 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
             const int mine = (p.lane < cnt) ? idx[cb + p.lane] : 0;
             for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {
                 typename Row4<T>::Raw raw[B];
-                static_for<B>([&](auto kk) {
+                const RowPlaces<B> some = row_places<B>(cnt - k0, n_slots);
+                int e0 = k0 + p.slot;
+                asm("" : "+v"(e0));
+                some.template each<0>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     raw[K] = typename Row4<T>::Raw{};
                     if (k0 + K * n_slots < cnt) {
-                        const int i = __shfl(mine, min(k0 + K * n_slots + p.slot, cnt - 1));
+                        const int i = __shfl(mine, min(e0 + K * n_slots, cnt - 1));
                         if (p.on) raw[K] = load_raw<T, RAG>(Gp + (int64_t)i * a.ld + p.foff);
                     }
                 });
-                const int my_e = k0 + p.k_pos * n_slots + p.slot;
+                const int my_e = e0 + p.k_pos * n_slots;
                 const bool valid = p.live && p.k_pos < B && my_e < cnt;
                 const int my_i = __shfl(mine, valid ? my_e : 0);
                 const float4 rec = a.rec[(int64_t)my_i * a.ldh + p.h];
                 float c_mine = 0.f;
-                static_for<B>([&](auto kk) {
+                some.template each<0>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     float g[4];
                     Row4<T>::unpack(raw[K], g);
@@ -522,7 +573,7 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
                 const float du = u2 > 0.f ? de : a.slope * de;
                 ac.dt += du;
                 if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
-                static_for<B>([&](auto kk) {
+                some.template each<0>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     const float ak = group_bcast<LPH, K>(alpha);
                     float g[4];
@@ -663,20 +714,20 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
         const Meta m2 = load_meta(id2, w + 2 * stride);
         const uint32_t id3 = load_id(w + 3 * stride);
         const bool mine = have(w);
+        const FewPlaces<B> some = few_places<B>(m0.cnt);
         float zj[4];
         {
             typename Row4<T>::Raw zr{};
-            if (mine && p.on) zr = load_raw<T, RAG>(static_cast<const T*>(s_Z[m0.q]) + (int64_t)m0.j * a.ld + p.foff);
+            if (m0.cnt > 0 && p.on) zr = load_raw<T, RAG>(static_cast<const T*>(s_Z[m0.q]) + (int64_t)m0.j * a.ld + p.foff);
             Row4<T>::unpack(zr, zj);
             p.own_only(zj);
         }
         float dz[4] = {0.f, 0.f, 0.f, 0.f}, dt = 0.f, t2 = 0.f;
-        bool have_t = false;
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            if (__builtin_amdgcn_ballot_w64(m0.cnt > r * B) == 0) break;
+        static_for<kRounds>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            if (!(r == 0 ? some.any : some.most)) return;
             typename Row4<T>::Raw raw[B];
-            static_for<B>([&](auto kk) {
+            some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 raw[K] = typename Row4<T>::Raw{};
                 const int i = bcast_i<LPH, K>(d0.i[r]);
@@ -686,8 +737,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
             const int my_i = d0.i[r];
             float4 rec = make_float4(0.f, INFINITY, 0.f, 0.f);   // L = +inf gives alpha = 0
             if (valid) rec = a.rec[(int64_t)my_i * a.ldh + p.h];
-            if (!have_t) {
-                have_t = true;
+            if constexpr (r == 0) {
                 float c = al[0] * zj[0];
 #pragma unroll
                 for (int x = 1; x < 4; ++x) c = fmaf(al[x], zj[x], c);
@@ -696,7 +746,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
                 t2 = score_log2(c);
             }
             float c_mine = 0.f;
-            static_for<B>([&](auto kk) {
+            some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 float g[4];
                 Row4<T>::unpack(raw[K], g);
@@ -712,7 +762,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
             const float du = u2 > 0.f ? de : a.slope * de;
             dt += du;
             if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
-            static_for<B>([&](auto kk) {
+            some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 const float ak = group_bcast<LPH, K>(alpha);
                 float g[4];
@@ -720,7 +770,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
 #pragma unroll
                 for (int x = 0; x < 4; ++x) dz[x] = fmaf(ak, g[x], dz[x]);
             });
-        }
+        });
         dt = group_all<LPH, OpSum>(dt);
         if (mine) {
             float v[4];

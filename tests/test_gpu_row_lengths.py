@@ -1,0 +1,77 @@
+"""Rows and sources of every length at which a kernel changes how it walks them: batches that end early, rows of fewer
+than 8 edges of mixed lengths in a wavefront, rows that wavefronts share and how their shares are cut."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sar_oracle as orc
+from paper_2111_06483_amd import sar
+from tests import gpu_util as gu
+from tests.helpers import rel_err
+
+pytestmark = pytest.mark.gpu
+SLOPE = 0.2
+f64 = lambda t: t.to(torch.float64).cpu().numpy()
+LENGTHS = [*range(0, 10)] * 4 + [15, 16, 17, 24, 31, 32, 33, 40, 63, 64, 65, 71, 127, 128, 129, 130, 159, 160, 161, 191,
+                                 192, 193, 255, 256, 257, 263, 300, 511, 512, 513, 777]
+
+
+def graph(seed):
+    """Block 0 holds a destination of every length, block 1 a source of every length (to the same destinations)."""
+    rng = np.random.default_rng(seed)
+    n = 500
+    part = np.arange(2 * n, dtype=np.int32) % 2
+    own, other = np.flatnonzero(part == 0), np.flatnonzero(part == 1)
+    lengths = np.array(LENGTHS)
+    dst = np.concatenate([np.repeat(rng.permutation(own)[:lengths.size], lengths), rng.choice(own, lengths.sum())])
+    src = np.concatenate([rng.choice(own, lengths.sum()), np.repeat(rng.permutation(other)[:lengths.size], lengths)])
+    return rng, src, dst, part
+
+
+# one to sixteen slots, heads of 4 to 64 lanes, whole, ragged and padded; the generic kernel
+@pytest.mark.parametrize("H,D", [(4, 16), (1, 47), (4, 32), (1, 16), (2, 8), (3, 12), (5, 40), (2, 50), (4, 64), (8, 32),
+                                 (1, 256), (2, 100), (3, 3)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("fly", [False, True])
+def test_attention_rows(H, D, dtype, batched, fly):
+    rng, src, dst, part = graph(H * 100 + D)
+    want_b, _ = orc.build_blocks(src, dst, part, 2, 0)
+    b = gu.build_blocks(src, dst, part, 2, 0)
+    row = lambda n: torch.from_numpy(rng.standard_normal((n, H, D)).astype(np.float32)).to(dtype).cuda()
+    Zs, G = [row(w.n_src) for w in want_b], row(b.n_dst)
+    bound = np.sqrt(6.0 / (D + 1))
+    a_l, a_r = (torch.from_numpy(rng.uniform(-bound, bound, (H, D)).astype(np.float32)).cuda() for _ in range(2))
+    wz = [f64(z) for z in Zs]
+    wf = orc.gat_fwd(want_b, wz[0], wz, f64(a_l), f64(a_r), SLOPE)
+    wb = orc.gat_bwd(want_b, wz[0], wz, f64(G), f64(a_l), f64(a_r), SLOPE, wf)
+    fw = (gu.gat_fwd_all if batched else gu.gat_fwd_stream)(b, Zs[0], Zs, a_l, a_r, SLOPE, fly=fly)
+    tol = 1e-4 if dtype == torch.float32 else 2e-2
+    assert rel_err(f64(fw.out), wf.out) < tol
+    g = gu.gat_bwd(b, Zs[0], Zs, G, a_l, a_r, SLOPE, fw, batched, fly=fly)
+    for q in range(2):
+        assert rel_err(f64(g.dZs[q]), wb.dZs[q]) < tol, q
+        assert rel_err(f64(g.dts[q]), wb.dt[q]) < tol, q
+    for name in ("ds", "da_l", "da_r"):
+        assert rel_err(f64(getattr(g, name)), getattr(wb, name)) < tol, name
+    b.close()
+
+
+@pytest.mark.parametrize("F", [8, 47, 100, 256])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_mean_rows(F, dtype):
+    rng, src, dst, part = graph(F)
+    want_b, _ = orc.build_blocks(src, dst, part, 2, 0)
+    b = gu.build_blocks(src, dst, part, 2, 0)
+    row = lambda n: torch.from_numpy(rng.standard_normal((n, F)).astype(np.float32)).to(dtype).cuda()
+    Zs, G = [row(w.n_src) for w in want_b], row(b.n_dst)
+    tol = 1e-5 if dtype == torch.float32 else 1e-2
+    want = orc.spmm(want_b, [f64(z) for z in Zs], True)
+    assert rel_err(f64(gu.spmm_stream(b, Zs, True)), want) < tol
+    assert rel_err(f64(gu.spmm_all(b, Zs, True)), want) < tol
+    want_d = orc.spmm_bwd(want_b, f64(G), True)
+    dZs = [torch.full_like(z, float("nan")) for z in Zs]
+    sar.sar_spmm_bwd_all(b, G, True, dZs)
+    for q in range(2):
+        assert rel_err(f64(dZs[q]), want_d[q]) < tol, q
+    b.close()
