@@ -998,7 +998,7 @@ __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, in
 }
 
 struct ClassLayout {
-    int64_t n_rows = 0, n_long = 0, n_wide = 0;
+    int64_t n_rows = 0, n_long = 0, n_shared = 0, n_wide = 0;
     int start[sar::kNumClasses];
 };
 
@@ -1018,9 +1018,28 @@ int pick_long_class(const int* hist, int floor_class)
     return sar::kLongClass;
 }
 
-ClassLayout layout_from_hist(const int* hist, int64_t offset, int floor_class)
+// Degree class from which a launch over the list shares rows among four wavefronts: that of the long rows, and in a short
+// launch a lower one.  A wavefront takes eight edges per round trip to memory, so a row of more edges than a wavefront's
+// even share of the launch (4096 of them run at once) is what the launch waits for: with 136 thousand edges in a block, 33 a
+// wavefront, the rows of 8 edges and more alone took 38 of the 42 us of its forward launch, rows of 64 to 127 edges 8 to 16
+// round trips each; with those of 32 and more shared, evenly cut, 30 us.  A graph of 4096 nodes and 64 thousand edges, 4 heads of 16: forward
+// 16.0 -> 10.9, backward 22.5 -> 16.0 us.  (In launches of millions of edges sharing costs: 47 bf16 values, 6 M edges, rows from
+// 32 on shared, backward 3 to 9% slower.)  At most 1024 rows: each takes a workgroup, and about as many run at once.
+int shared_class(const int* hist, int64_t edges, int long_class)
 {
-    const int long_class = pick_long_class(hist, floor_class);
+    int c = sar::kSharedClassLeast;
+    while (c < long_class && ((int64_t)1 << (c - 1)) < edges / 4096) ++c;
+    for (; c < sar::kLongClassBlock && c < long_class; ++c) {
+        int64_t n = 0;
+        for (int k = c; k < sar::kNumClasses; ++k) n += hist[k];
+        if (n <= 1024) return c;
+    }
+    return long_class;
+}
+
+ClassLayout layout_from_hist(const int* hist, int64_t offset, int floor_class, int64_t edges)
+{
+    const int long_class = pick_long_class(hist, floor_class), shared = shared_class(hist, edges, long_class);
     ClassLayout L;
     int64_t run = offset;
     for (int c = sar::kNumClasses - 1; c >= 1; --c) {
@@ -1028,6 +1047,7 @@ ClassLayout layout_from_hist(const int* hist, int64_t offset, int floor_class)
         run += hist[c];
         L.n_rows += hist[c];
         if (c >= long_class) L.n_long += hist[c];
+        if (c >= shared) L.n_shared += hist[c];
         if (c > sar::kNarrowMaxClass) L.n_wide += hist[c];
     }
     L.start[0] = (int)run;
@@ -1443,9 +1463,10 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     for (int q = 0; q < P; ++q) {
         Block& b = h->blk[q];
         const int* row_hist = &hist[q * C];
-        ClassLayout L = layout_from_hist(row_hist, 0, sar::kLongClassBlock);
+        ClassLayout L = layout_from_hist(row_hist, 0, sar::kLongClassBlock, b.nnz);
         b.n_rows = L.n_rows;
         b.n_long = L.n_long;
+        b.n_shared = L.n_shared;
         b.n_rows_wide = L.n_wide;
         for (int c = 1; c < C; ++c)
             if (row_hist[c]) b.hub = (int64_t)1 << (c - 1);
@@ -1455,9 +1476,10 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         rows_at += L.n_rows;
         if (transpose) {
             const int* s_hist = &hist[(P + q) * C];
-            ClassLayout S = layout_from_hist(s_hist, 0, sar::kLongClassBlock);
+            ClassLayout S = layout_from_hist(s_hist, 0, sar::kLongClassBlock, b.nnz);
             b.n_t_rows = S.n_rows;
             b.n_t_long = S.n_long;
+            b.n_t_shared = S.n_shared;
             b.n_t_wide = S.n_wide;
             memcpy(&cursors[(P + q) * C], S.start, sizeof(S.start));
             b.touched = touched_all + t_rows_at;
@@ -1466,9 +1488,9 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         }
     }
     if (fused) {
-        ClassLayout L = layout_from_hist(&hist[2 * P * C], 0, sar::kLongClassBlock);
+        ClassLayout L = layout_from_hist(&hist[2 * P * C], 0, sar::kLongClassBlock, nnz_total);
         h->n_f_rows = L.n_rows;
-        h->n_f_long = L.n_long;
+        h->n_f_shared = L.n_shared;
         for (int c = 1; c < C; ++c) {
             if (hist[2 * P * C + c]) h->f_longest = ((int64_t)1 << c) - 1;
             if (c >= sar::kHubClass) h->n_f_hub += hist[2 * P * C + c];
@@ -1476,9 +1498,9 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         memcpy(&cursors[2 * P * C], L.start, sizeof(L.start));
     }
     if (transpose) {
-        ClassLayout L = layout_from_hist(all_hist, 0, sar::kLongClassBlock);
+        ClassLayout L = layout_from_hist(all_hist, 0, sar::kLongClassBlock, nnz_total);
         h->n_ft_rows = L.n_rows;
-        h->n_ft_long = L.n_long;
+        h->n_ft_shared = L.n_shared;
         h->n_ft_wide = L.n_wide;
         for (int c = 1; c < C; ++c)
             if (all_hist[c]) h->ft_longest = ((int64_t)1 << c) - 1;

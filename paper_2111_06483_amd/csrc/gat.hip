@@ -94,19 +94,20 @@ __device__ inline void state_merge(SoftState<VEC>& st, float om2, float ol, cons
     st.m2 = mn;
 }
 
-// Folds the edges idx[beg,end) into st; this wavefront takes the 64-edge
-// chunks chunk0, chunk0+stride, ...  s2 is the destination score half of this
+// Folds the edges idx[beg,end) into st; this wavefront takes share `share`
+// of `shares` of them.  s2 is the destination score half of this
 // lane's head in log2 units.
 template <typename T, int G, bool ALL>
 __device__ inline void fwd_edges(SoftState<Vec<T>::N>& st, const FwdArgs& a, const void* const* ztab,
-                                 const float* const* ttab, int beg, int end, int chunk0, int stride,
+                                 const float* const* ttab, int beg, int end, int share, int shares,
                                  const LaneMap<T, G>& lm, float s2, const float (&al)[Vec<T>::N], bool fly,
                                  bool pow2)
 {
     constexpr int VEC = Vec<T>::N;
     constexpr int SLOTS = kWave / G;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
-    for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+    if (shares > 1) row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += kWave) {
         const int cnt = min(kWave, end - cb);
         const uint32_t mine = (lm.lane < cnt) ? a.indices[cb + lm.lane] : 0u;
         for (int k0 = 0; k0 < cnt; k0 += SLOTS * kU) {
@@ -341,13 +342,14 @@ struct BwdAcc {
 // Edges (destinations) idx[beg,end) of one source row.
 template <typename T, int G>
 __device__ inline void bwd_edges(BwdAcc<Vec<T>::N>& ac, const BwdScalars& a, const int32_t* idx, int beg,
-                                 int end, int chunk0, int stride, const LaneMap<T, G>& lm,
+                                 int end, int share, int shares, const LaneMap<T, G>& lm,
                                  const float (&zj)[Vec<T>::N], float t2, bool pow2)
 {
     constexpr int VEC = Vec<T>::N;
     constexpr int SLOTS = kWave / G;
     const T* Gp = static_cast<const T*>(a.G);
-    for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+    if (shares > 1) row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += kWave) {
         const int cnt = min(kWave, end - cb);
         const int mine = (lm.lane < cnt) ? idx[cb + lm.lane] : 0;
         for (int k0 = 0; k0 < cnt; k0 += SLOTS * kU) {
@@ -1718,7 +1720,7 @@ extern "C" int sar_gat_fwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.indices = reinterpret_cast<const uint32_t*>(k.indices);
         a.rows = reinterpret_cast<const uint32_t*>(k.rows);
         a.n_rows = k.n_rows;
-        a.n_long = k.n_long;
+        a.n_long = k.n_shared;
         a.n_wide = k.n_rows_wide;
         a.Z = shift(Zq, f0 * hg.fb);
         a.t = tq ? tq + h0 : nullptr;
@@ -1911,7 +1913,7 @@ extern "C" int sar_gat_fwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.indices = b->f_indices;
         a.rows = reinterpret_cast<const uint32_t*>(b->f_rows);
         a.n_rows = b->n_dst;   // the list ends with the destinations that have no in-edge: out = 0, L = -inf
-        a.n_long = b->n_f_long;
+        a.n_long = b->n_f_shared;
         a.s = s + h0;
         a.a_l = tq ? nullptr : a_l + f0;
         a.out = shift(out, f0 * hg.fb);
@@ -2037,7 +2039,7 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
         a.rows = reinterpret_cast<const uint32_t*>(k.t_rows);
         // sources without edges come last and get dZ = 0, dt = 0, unless the handle skips them
         a.n_rows = sar::skips_untouched(b->flags) ? k.n_t_rows : k.n_src;
-        a.n_long = k.n_t_long;
+        a.n_long = k.n_t_shared;
         a.n_wide = k.n_t_wide;
         a.n_touched = k.n_t_rows;
         a.n_src_host = &k.n_src;
@@ -2134,7 +2136,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         a.s_row = b->s_row;
         a.n_src_host = n_src_all;
         a.n_blocks = b->P;
-        a.n_long = b->n_ft_long;
+        a.n_long = b->n_ft_shared;
         a.tag_shift = b->tag_shift;
         fill_bwd_group(a, hg, g, H, D, G, rec, a_l, dst, work, slope);
         a.wide_done = by_slices;

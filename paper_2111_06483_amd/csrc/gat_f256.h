@@ -405,17 +405,18 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
             }
         }
     };
-    auto edges = [&](FwdState<LPH>& st, int i, int chunk0, int stride) {
+    auto edges = [&](FwdState<LPH>& st, int i, int share, int shares) {
         const float s2 = a.s[(int64_t)i * ldh + h] * kLog2e;
-        const int beg = a.indptr[i], end = a.indptr[i + 1];
-        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+        int beg = a.indptr[i], end = a.indptr[i + 1];
+        if (shares > 1) row_share(beg, end, share, shares);
+        for (int cb = beg; cb < end; cb += kWave) {
             const int cnt = min(kWave, end - cb);
             const uint32_t mine = (lane < cnt) ? a.indices[cb + lane] : 0u;
             fwd_chunk<T, LPH, B, ALL, FLY, PAD>(st, a, tabs, mine, cnt, foff, on, h, k, s2, al);
         }
     };
 
-    // Rows at the head of the list are shared by a team of `team` wavefronts, each with every team-th 64 of its edges.
+    // Rows at the head of the list are shared by a team of `team` wavefronts, each with its share of the edges.
     auto shared_rows = [&](auto team_c, int64_t r_begin, int64_t r_end) __attribute__((always_inline)) {
         constexpr int team = decltype(team_c)::value, teams = NW / team;
         const int lead = wave / team * team;
@@ -593,7 +594,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
 #pragma unroll
     for (int x = 0; x < 4; ++x) dal[x] = 0.f;
 
-    auto edges = [&](BwdAcc4& ac, int q, int j, int chunk0, int stride, float (&zj)[4]) {
+    auto edges = [&](BwdAcc4& ac, int q, int j, int share, int shares, float (&zj)[4]) {
         Row4<T>::unpack(load_lane<T, PAD>(static_cast<const T*>(tabs.Z[q]) + (int64_t)j * ld, foff, on), zj);
         float t2;
         if (tabs.t[q]) {
@@ -606,11 +607,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         }
         const int32_t* ip = tabs.t_indptr[q];
         const int32_t* idx = tabs.t_indices[q];
-        const int beg = ip[j], end = ip[j + 1];
+        int beg = ip[j], end = ip[j + 1];
+        if (shares > 1) row_share(beg, end, share, shares);
 #pragma unroll
         for (int x = 0; x < 4; ++x) ac.dz[x] = 0.f;
         ac.dt = 0.f;
-        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+        for (int cb = beg; cb < end; cb += kWave) {
             const int cnt = min(kWave, end - cb);
             const int mine = (lane < cnt) ? idx[cb + lane] : 0;
             bwd_chunk<T, LPH, B, PAD>(ac, a, ds, mine, cnt, foff, on, h, k, zj, t2);

@@ -261,10 +261,11 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int n_slots, in
             }
         }
     };
-    auto edges = [&](State& st, int i, int chunk0, int stride) {
+    auto edges = [&](State& st, int i, int share, int shares) {
         const float s2 = a.s[(int64_t)i * a.ldh + p.h] * kLog2e;
-        const int beg = a.indptr[i], end = a.indptr[i + 1];
-        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+        int beg = a.indptr[i], end = a.indptr[i + 1];
+        if (shares > 1) row_share(beg, end, share, shares);
+        for (int cb = beg; cb < end; cb += kWave) {
             const int cnt = min(kWave, end - cb);
             const uint32_t mine = (p.lane < cnt) ? a.indices[cb + p.lane] : 0u;
             fwd_chunk<T, LPH, ALL, FLY, RAG>(st, a, s_Z, s_t, mine, cnt, n_slots, p, s2, al);
@@ -517,7 +518,7 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
 #pragma unroll
     for (int x = 0; x < 4; ++x) dal[x] = 0.f;
 
-    auto edges = [&](BwdAcc4& ac, int q, int j, int chunk0, int stride, float (&zj)[4]) {
+    auto edges = [&](BwdAcc4& ac, int q, int j, int share, int shares, float (&zj)[4]) {
         typename Row4<T>::Raw zr{};
         if (p.on) zr = load_raw<T, RAG>(static_cast<const T*>(tabs.Z[q]) + (int64_t)j * a.ld + p.foff);
         Row4<T>::unpack(zr, zj);
@@ -532,11 +533,12 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
             t2 = score_log2(group_all<LPH, OpSum>(c));
         }
         const int32_t* idx = tabs.t_indices[q];
-        const int beg = tabs.t_indptr[q][j], end = tabs.t_indptr[q][j + 1];
+        int beg = tabs.t_indptr[q][j], end = tabs.t_indptr[q][j + 1];
+        if (shares > 1) row_share(beg, end, share, shares);
 #pragma unroll
         for (int x = 0; x < 4; ++x) ac.dz[x] = 0.f;
         ac.dt = 0.f;
-        for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+        for (int cb = beg; cb < end; cb += kWave) {
             const int cnt = min(kWave, end - cb);
             const int mine = (p.lane < cnt) ? idx[cb + p.lane] : 0;
             for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {

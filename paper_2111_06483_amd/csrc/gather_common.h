@@ -25,6 +25,15 @@ constexpr int kGatherThreads = 256;          // 4 wavefronts per workgroup
 constexpr int kWavesPerWG = kGatherThreads / kWave;
 constexpr int kMaxPersistentWGs = 256 * 8;   // 256 CUs x 8 resident workgroups
 
+// Part `part` of `parts` of a long row's edges [beg, end): even shares in whole eights.  (Dealt out 64 at a time, a row of
+// 130 edges was 64 + 64 + 2 to four wavefronts; such a row at the head of the list is what a short launch waits for.)
+__device__ inline void row_share(int& beg, int& end, int part, int parts)
+{
+    const int per = (end - beg + 8 * parts - 1) / (8 * parts) * 8;
+    beg = min(beg + part * per, end);
+    end = min(beg + per, end);
+}
+
 template <typename T>
 struct Vec;
 

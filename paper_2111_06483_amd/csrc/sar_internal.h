@@ -40,13 +40,15 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 // so that it coincides with a degree-class boundary.
 // Rows the four wavefronts of a workgroup share: those of at least 128, 256 or 512 edges, the
 // lowest of the three that leaves them a small minority of their list (chosen per list when it
-// is built).  A 300-edge row at the head of one wavefront's share otherwise decides when a
-// launch ends (a per-block launch is a dozen rows per wavefront); where nearly all rows are that
-// long there is nothing to balance, and sharing them would only add merges.
+// is built), in short launches of 32 or 64 (`shared_class`, builder.hip).  A 300-edge row at the
+// head of one wavefront's share otherwise decides when a launch ends (a per-block launch is a dozen
+// rows per wavefront); where nearly all rows are that long there is nothing to balance, and sharing
+// them would only add merges.
 constexpr int kLongRow = 512;
 constexpr int kLongClass = 10;       // 1 + log2(kLongRow)
 constexpr int kLongRowBlock = 128;
 constexpr int kLongClassBlock = 8;   // 1 + log2(kLongRowBlock)
+constexpr int kSharedClassLeast = 6; // 1 + log2 of the shortest row that is shared
 constexpr int kHubClass = 11;        // 1 + log2(kHubRow)
 constexpr int kHubRow = 1024;        // edges of a row that a large workgroup shares (forward pass over all blocks)
 constexpr int kNumClasses = 32;
@@ -65,6 +67,7 @@ struct Block {
     int32_t* t_indices = nullptr;
     int32_t* rows = nullptr;
     int64_t n_rows = 0, n_long = 0;
+    int64_t n_shared = 0, n_t_shared = 0;                // rows and sources at the lists' heads that four wavefronts share
     int32_t* t_rows = nullptr;
     int64_t hub = 0;                                     // edges of the most frequent destination, rounded down to a power of two
     int64_t n_rows_wide = 0;                             // destination rows with >= 8 edges (head of `rows`)
@@ -96,14 +99,14 @@ struct sar_blocks {
     int32_t* f_indptr = nullptr;   // [n_dst+1]
     uint32_t* f_indices = nullptr; // [sum nnz]
     int32_t* f_rows = nullptr;     // destinations with deg > 0, longest class first
-    int64_t n_f_rows = 0, n_f_long = 0;
+    int64_t n_f_rows = 0, n_f_shared = 0;
     int64_t n_f_hub = 0;           // of those, the rows of kHubRow edges and more
     int64_t f_longest = 0;         // no destination has more edges (one below a power of two); 0: not known
     int tag_shift = 0;
     // All-blocks source-side work list: (q << tag_shift) | local source id of
     // every source with an edge, longest class first.
     uint32_t* ft_rows = nullptr;
-    int64_t n_ft_rows = 0, n_ft_long = 0, n_ft_wide = 0;
+    int64_t n_ft_rows = 0, n_ft_shared = 0, n_ft_wide = 0;
     int64_t ft_longest = 0;        // no source has more edges in its block
     // The sources that have ONE edge in their block (the last n_single entries of ft_rows that
     // have an edge), listed in the order of that edge's destination: destination, tagged source,

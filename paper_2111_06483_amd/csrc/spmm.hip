@@ -157,18 +157,19 @@ __device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, con
     }
 }
 
-// Adds the rows listed in idx[beg,end) into acc.  The wavefront takes the
-// 64-edge chunks chunk0, chunk0+stride, ...  Eight edges per lane group are in flight while there are
+// Adds the rows listed in idx[beg,end) into acc; the wavefront takes share
+// `share` of `shares` of them.  Eight edges per lane group are in flight while there are
 // as many (forward, 7.4M edges: bf16 rows of 512 values 1208 us with four, 1099 with eight), then four.
 // The backward pass over wide rows stays with four: a source has 12 edges on average and its wavefront
 // waits for the chain in front of them, so what counts is how many wavefronts are resident (the same
 // rows: 1149 us with four, 1257 with eight and their registers).
 template <typename T, int G, Mode M, bool RAG>
 __device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab,
-                                int beg, int end, int chunk0, int stride, const RowLanes<T, G, RAG>& lm)
+                                int beg, int end, int share, int shares, const RowLanes<T, G, RAG>& lm)
 {
     constexpr int SLOTS = kWave / G;
-    for (int cb = beg + chunk0 * kWave; cb < end; cb += stride * kWave) {
+    if (shares > 1) row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += kWave) {
         const int cnt = min(kWave, end - cb);
         const uint32_t mine = (lm.lane < cnt) ? a.indices[cb + lm.lane] : 0u;
         int k0 = 0;
@@ -662,7 +663,7 @@ extern "C" int sar_spmm_block(const sar_blocks_t* b, int q, const void* Zq, int 
     a.indices = reinterpret_cast<const uint32_t*>(k.indices);
     a.rows = reinterpret_cast<const uint32_t*>(k.rows);
     a.n_rows = k.n_rows;
-    a.n_long = k.n_long;
+    a.n_long = k.n_shared;
     a.ld = F;
     PtrTab tab{};
     const ColumnChunks cc = column_chunks(dtype, F);
@@ -749,7 +750,7 @@ extern "C" int sar_spmm_all(const sar_blocks_t* b, const void* const* Zq, int dt
     a.indices = b->f_indices;
     a.rows = reinterpret_cast<const uint32_t*>(b->f_rows);
     a.n_rows = b->n_dst;   // destinations without in-edges come last in the list and get 0
-    a.n_long = b->n_f_long;
+    a.n_long = b->n_f_shared;
     a.deg = b->deg;
     a.ld = F;
     a.tag_shift = b->tag_shift;
@@ -787,7 +788,7 @@ extern "C" int sar_spmm_bwd_block(const sar_blocks_t* b, int q, const void* G, i
     // sources without edges come last in the list and get 0, unless the handle skips them
     a.n_rows = sar::skips_untouched(b->flags) ? k.n_t_rows : k.n_src;
     a.out_rank = (b->flags & SAR_BUILD_COMPACT) ? k.t_rank : nullptr;
-    a.n_long = k.n_t_long;
+    a.n_long = k.n_t_shared;
     a.deg = b->deg;
     a.ld = F;
     a.mean = mean;
@@ -825,7 +826,7 @@ extern "C" int sar_spmm_bwd_all(const sar_blocks_t* b, const void* G, int mean, 
     SpmmArgs a{};
     a.rows = b->ft_rows;
     a.n_rows = sar::skips_untouched(b->flags) ? b->n_ft_rows : n_src_total;
-    a.n_long = b->n_ft_long;
+    a.n_long = b->n_ft_shared;
     a.deg = b->deg;
     a.ld = F;
     a.mean = mean;
