@@ -324,8 +324,8 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
 // (ids in the order of degree), and a bucket of the 1024 most frequent rows of that graph holds half a
 // million pairs (641 us for one workgroup, and 14 ms to sort its rows).
 // What the kernels now take on those 15.2M edges: pairs to buckets 218 + 222 us from the edge list (the
-// gathers of the nodes' codes) and 48 + 194 us from the CSR, keys 31, finish 374 each; of the last,
-// 140 us are the few hundred rows of more than 256 values and the rest the stores of short runs.
+// gathers of the nodes' codes) and 48 + 194 us from the CSR, keys 31, finish 173 each.  The last was 372 us, three quarters
+// of it instructions: groups of up to 8 values now take 8 lanes instead of 16, those of 17 to 256 a network in registers.
 
 constexpr int kBucketThreads = 512;
 constexpr int kRunBits = 2;             // runs of four keys
@@ -608,6 +608,19 @@ __device__ inline void bitonic(int32_t* a, int len, int tid, int nt, Sync&& sync
     }
 }
 
+// The value of lane ^ M.
+template <int M>
+__device__ inline uint32_t lane_xor(uint32_t x)
+{
+    constexpr int kDpp = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 3 ? 0x1B : M == 7 ? 0x141 : M == 8 ? 0x128 : M == 15 ? 0x140 : 0;
+    if constexpr (kDpp != 0)      // quad_perm, row_half_mirror, row_ror:8, row_mirror
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDpp, 0xf, 0xf, false);
+    else if constexpr (M < 32)
+        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (M << 10) | 0x1f);
+    else
+        return (uint32_t)__shfl_xor((int)x, M);
+}
+
 // Values among the 16 of a DPP row that sort before this lane's (equal ones by lane).
 template <int J>
 __device__ inline int rank16_step(int32_t x, int l)
@@ -622,36 +635,79 @@ __device__ inline int rank16_step(int32_t x, int l)
 }
 __device__ inline int rank16(int32_t x, int l) { return rank16_step<15>(x, l); }
 
-// Ascending order of a[0, len), len <= 64 N, by one wavefront: every value goes to the place that the
-// count of the values before it gives it -- smaller ones, and equal ones at lower indexes: for values
-// x at index i and y at j, y goes first if y < x + (j < i).
-template <int N>
-__device__ inline void rank_sort_wave(int32_t* a, int len, int lane)
+// Values among the 8 of half a DPP row that sort before this lane's.  A lane's partner is lane ^ m, and of equal values the
+// one at the lower lane goes first: it is the partner where the lane has m's highest bit.
+__device__ inline int rank8(uint32_t x, int l)
 {
-    int32_t x[N];
-    int rank[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        x[r] = a[min(r * 64 + lane, len - 1)];
-        rank[r] = 0;
-    }
-#pragma unroll
-    for (int b = 0; b < N; ++b) {
-        const int n = min(64, len - b * 64);
-#pragma unroll 4
-        for (int j = 0; j < n; ++j) {
-            const int32_t y = a[b * 64 + j];
+    const uint32_t b1 = x + (l & 1), b2 = x + (l >> 1 & 1), b4 = x + (l >> 2 & 1);
+    const uint32_t far = lane_xor<7>(x);
+    return (lane_xor<1>(x) < b1) + (lane_xor<2>(x) < b2) + (lane_xor<3>(x) < b2) + (far < b4) + (lane_xor<1>(far) < b4) +
+           (lane_xor<2>(far) < b4) + (lane_xor<3>(far) < b4);
+}
+
+// Steps of a bitonic network over 64 N values, lane l holding values N l to N l + N - 1, in which every comparator is
+// ascending: value i meets i ^ (K - 1), then i ^ K/4, i ^ K/8 ... 1.
+template <int N, int J>
+__device__ inline void bitonic_halves(int32_t (&x)[N], int lane)
+{
+    if constexpr (J >= 1) {
+        if constexpr (J >= N) {
 #pragma unroll
             for (int r = 0; r < N; ++r) {
-                const int32_t bound = b < r ? x[r] + 1 : b > r ? x[r] : x[r] + (j < lane ? 1 : 0);
-                rank[r] += y < bound ? 1 : 0;
+                const int32_t y = (int32_t)lane_xor<J / N>((uint32_t)x[r]);
+                x[r] = (lane & (J / N)) ? max(x[r], y) : min(x[r], y);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                if (!(r & J)) {
+                    const int32_t lo = min(x[r], x[r | J]);
+                    x[r | J] = max(x[r], x[r | J]);
+                    x[r] = lo;
+                }
+        }
+        bitonic_halves<N, J / 2>(x, lane);
+    }
+}
+template <int N, int K>
+__device__ inline void bitonic_steps(int32_t (&x)[N], int lane)
+{
+    if constexpr (K > 2) bitonic_steps<N, K / 2>(x, lane);
+    if constexpr (K > N) {
+        constexpr int M = K / N - 1;
+        int32_t y[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) y[r] = (int32_t)lane_xor<M>((uint32_t)x[N - 1 - r]);
+#pragma unroll
+        for (int r = 0; r < N; ++r) x[r] = (lane & ((M + 1) / 2)) ? max(x[r], y[r]) : min(x[r], y[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const int o = r ^ (K - 1);
+            if (r < o) {
+                const int32_t lo = min(x[r], x[o]);
+                x[o] = max(x[r], x[o]);
+                x[r] = lo;
             }
         }
     }
+    bitonic_halves<N, K / 4>(x, lane);
+}
+
+// Ascending order of a[0, len), len <= 64 N, by one wavefront, in registers: 256 values are 36 steps, 15 of them
+// inside a lane, of the others' exchanges two thirds DPP; under two instructions a value.  (Counting for every value the ones before it reads the group from LDS once per
+// value: 13 instructions for each of 256 values, and the long groups were most of what the kernel below issued.)
+template <int N>
+__device__ inline void sort_wave(int32_t* a, int len, int lane)
+{
+    int32_t x[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) x[r] = lane * N + r < len ? a[lane * N + r] : 0x7fffffff;
+    bitonic_steps<N, 64 * N>(x, lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reads stay ahead of the writes
 #pragma unroll
     for (int r = 0; r < N; ++r)
-        if (r * 64 + lane < len) a[rank[r]] = x[r];
+        if (lane * N + r < len) a[lane * N + r] = x[r];
 }
 
 // Ascending order of a[0, len) in LDS by a workgroup of THREADS, len <= kMergeSort: wavefronts sort
@@ -664,7 +720,7 @@ __device__ inline void merge_sort(int32_t* a, int len)
     constexpr int kPer = kMergeSort / THREADS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int c = wave * kWaveSort; c < len; c += THREADS / 64 * kWaveSort)
-        rank_sort_wave<kWaveSort / 64>(a + c, min(kWaveSort, len - c), lane);
+        sort_wave<kWaveSort / 64>(a + c, min(kWaveSort, len - c), lane);
     __syncthreads();
     for (int width = kWaveSort; width < len; width *= 2) {
         int32_t x[kPer];
@@ -731,7 +787,8 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_finish(const PairT* _
     constexpr int kRunLanes = 16;
     extern __shared__ int bucket_lds[];
     __shared__ int wave_sum[kWaves];
-    __shared__ int n_listed, n_big;
+    __shared__ int n_small, n_listed, n_big;
+    __shared__ uint16_t small[kBucketCap / (kRankLanes / 2 + 1) + 1];
     __shared__ uint16_t listed[kBucketCap / kRankLanes];
     __shared__ uint16_t big[kBucketCap / kWaveSort];
     const int n_slots = 1 << w;
@@ -754,7 +811,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_finish(const PairT* _
         if (threadIdx.x == 0) big_list[atomicAdd(big_count, 1)] = b;
         return;
     }
-    if (threadIdx.x == 0) n_listed = n_big = 0;
+    if (threadIdx.x == 0) n_small = n_listed = n_big = 0;
     for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) {
         const int64_t key = deal.key_at(b, k);
         cnt[k] = key < n_keys ? off[key + 1] - off[key] : 0;
@@ -786,37 +843,54 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_finish(const PairT* _
     }
     __syncthreads();
     // each group's start is its cursor; afterwards it is the group's end
-    for (int e = threadIdx.x; e < n; e += kBucketThreads) {
-        const PairT x = pairs[beg + e];
-        vals[atomicAdd(&cnt[(int)(x >> vbits)], 1)] = (int32_t)(x & vmask);
+    constexpr int kAhead = 8;
+    for (int e0 = threadIdx.x; e0 < n; e0 += kBucketThreads * kAhead) {
+        PairT x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) x[u] = pairs[beg + min(e0 + u * kBucketThreads, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (e0 + u * kBucketThreads < n) vals[atomicAdd(&cnt[(int)(x[u] >> vbits)], 1)] = (int32_t)(x[u] & vmask);
     }
     __syncthreads();
-    // Groups of up to 16 values: a DPP row of 16 lanes each, a lane's value goes to the place that the
-    // count of smaller ones gives it; the others' values come by rotation, without LDS.
-    for (int k0 = threadIdx.x / kRankLanes; k0 < n_slots; k0 += kBucketThreads / kRankLanes) {
-        const int s = k0 ? cnt[k0 - 1] : 0, len = cnt[k0] - s, l = threadIdx.x % kRankLanes;
-        if (len > kWaveSort) {
-            if (l == 0) big[atomicAdd(&n_big, 1)] = (uint16_t)k0;
-        } else if (len > kRankLanes) {
-            if (l == 0) listed[atomicAdd(&n_listed, 1)] = (uint16_t)k0;
+    // Groups of up to 8 values, most of them: 8 lanes each, a lane's value goes to the place that the count of the values
+    // before it gives it; the others' values come by DPP, without LDS.
+    for (int k0 = threadIdx.x / 8; k0 < n_slots; k0 += kBucketThreads / 8) {
+        const int s = k0 ? cnt[k0 - 1] : 0, len = cnt[k0] - s, l = threadIdx.x % 8;
+        if (len > 8) {
+            if (l != 0) continue;
+            if (len > kWaveSort)
+                big[atomicAdd(&n_big, 1)] = (uint16_t)k0;
+            else if (len > kRankLanes)
+                listed[atomicAdd(&n_listed, 1)] = (uint16_t)k0;
+            else
+                small[atomicAdd(&n_small, 1)] = (uint16_t)k0;
         } else if (len > 1) {
-            const int32_t x = l < len ? vals[s + l] : 0x7fffffff;
-            const int rank = rank16(x, l);
+            const uint32_t x = l < len ? (uint32_t)vals[s + l] : 0x7fffffffu;
+            const int rank = rank8(x, l);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reads stay ahead of the writes
-            if (l < len) vals[s + rank] = x;
+            if (l < len) vals[s + rank] = (int32_t)x;
         }
     }
     __syncthreads();
+    // up to 16: a DPP row each
+    for (int i = threadIdx.x / kRankLanes; i < n_small; i += kBucketThreads / kRankLanes) {
+        const int k = small[i], s = k ? cnt[k - 1] : 0, len = cnt[k] - s, l = threadIdx.x % kRankLanes;
+        const int32_t x = l < len ? vals[s + l] : 0x7fffffff;
+        const int rank = rank16(x, l);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (l < len) vals[s + rank] = x;
+    }
     // up to 256: a wavefront each, one to four values to a lane
     for (int i = wave; i < n_listed; i += kWaves) {
         const int k = __builtin_amdgcn_readfirstlane(listed[i]);
         const int s = k ? cnt[k - 1] : 0, len = __builtin_amdgcn_readfirstlane(cnt[k] - s);
         if (len <= 64)
-            rank_sort_wave<1>(vals + s, len, lane);
+            sort_wave<1>(vals + s, len, lane);
         else if (len <= 128)
-            rank_sort_wave<2>(vals + s, len, lane);
+            sort_wave<2>(vals + s, len, lane);
         else
-            rank_sort_wave<4>(vals + s, len, lane);
+            sort_wave<4>(vals + s, len, lane);
     }
     __syncthreads();
     for (int i = 0; i < n_big; ++i) {
@@ -958,7 +1032,10 @@ __global__ __launch_bounds__(kThreads) void k_class_hist(ListIn in, Lists l, int
 }
 
 // cursor[c] starts at the first slot of class c; value written = r | tag.
-// Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.
+// Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.  A workgroup takes 2048 rows to
+// one request to the cursors, which share a cache line and are served one request after the other (2.4 million rows: 256 rows
+// to a request 50 us, 2048 15).
+constexpr int kPlacePer = 8, kPlaceRows = kThreads * kPlacePer;
 __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, int tag_shift, int* __restrict__ cursors,
                                                           uint32_t* __restrict__ out_all)
 {
@@ -970,30 +1047,39 @@ __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, in
     uint32_t* out = l == Lists::kRows ? in.blk[blockIdx.y].rows : l == Lists::kSources ? in.blk[blockIdx.y].t_rows : out_all;
     const uint32_t tag = l == Lists::kAllSources ? (uint32_t)blockIdx.y << tag_shift : 0u;
     const int lane = threadIdx.x & 63;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t r0 = (int64_t)blockIdx.x * kThreads; r0 < n; r0 += stride) {
+    const int64_t stride = (int64_t)gridDim.x * kPlaceRows;
+    for (int64_t r0 = (int64_t)blockIdx.x * kPlaceRows; r0 < n; r0 += stride) {
+        __syncthreads();
         if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
         __syncthreads();
-        const int64_t r = r0 + threadIdx.x;
-        int c = r < n ? degree_class(off[r + 1] - off[r]) : -1;
-        if (c == 0 && l == Lists::kRows) c = -1;
-        int local = 0;
-        unsigned long long todo = __ballot(c >= 0);
-        while (todo) {
-            const int first = __ffsll((long long)todo) - 1;
-            const unsigned long long same = __ballot(c == __shfl(c, first));
-            int start = 0;
-            if (lane == first) start = atomicAdd(&h[c], __popcll(same));
-            start = __shfl(start, first);
-            if ((same >> lane) & 1) local = start + __popcll(same & ((1ull << lane) - 1ull));
-            todo &= ~same;
+        int c[kPlacePer], local[kPlacePer];
+#pragma unroll
+        for (int j = 0; j < kPlacePer; ++j) {
+            const int64_t r = r0 + j * kThreads + threadIdx.x;
+            c[j] = r < n ? degree_class(off[r + 1] - off[r]) : -1;
+            if (c[j] == 0 && l == Lists::kRows) c[j] = -1;
+        }
+#pragma unroll
+        for (int j = 0; j < kPlacePer; ++j) {
+            local[j] = 0;
+            unsigned long long todo = __ballot(c[j] >= 0);
+            while (todo) {
+                const int first = __ffsll((long long)todo) - 1;
+                const unsigned long long same = __ballot(c[j] == __shfl(c[j], first));
+                int start = 0;
+                if (lane == first) start = atomicAdd(&h[c[j]], __popcll(same));
+                start = __shfl(start, first);
+                if ((same >> lane) & 1) local[j] = start + __popcll(same & ((1ull << lane) - 1ull));
+                todo &= ~same;
+            }
         }
         __syncthreads();
         if (threadIdx.x < sar::kNumClasses && h[threadIdx.x])
             base[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]);
         __syncthreads();
-        if (c >= 0) out[base[c] + local] = (uint32_t)r | tag;
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPlacePer; ++j)
+            if (c[j] >= 0) out[base[c[j]] + local[j]] = (uint32_t)(r0 + j * kThreads + threadIdx.x) | tag;
     }
 }
 
@@ -1389,6 +1475,8 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     ListIn in{blk_d, h->f_indptr, n_dst};
     const dim3 g_rows(grid_for(n_dst, kThreads, std::max(1, 4096 / P)), P), g_all(grid_for(n_dst, kThreads, 4096), 1);
     const dim3 g_src(grid_for(n_src_max + 1, kThreads, std::max(1, 4096 / P)), P);
+    const dim3 g_place_rows(grid_for(n_dst, kPlaceRows), P), g_place_all(grid_for(n_dst, kPlaceRows), 1);
+    const dim3 g_place_src(grid_for(n_src_max, kPlaceRows), P);
     k_class_hist<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, rows_hist);
     SAR_LAUNCH_CHECK();
 
@@ -1508,18 +1596,18 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     }
     SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
     SAR_HIP(hipMemcpyAsync(hist_d, cursors.data(), n_hist * sizeof(int), hipMemcpyHostToDevice, st));
-    k_class_place<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, rows_hist, nullptr);
+    k_class_place<<<g_place_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, rows_hist, nullptr);
     SAR_LAUNCH_CHECK();
     if (fused) {
-        k_class_place<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, 0, all_rows_hist,
+        k_class_place<<<g_place_all, kThreads, 0, st>>>(in, Lists::kAllRows, 0, all_rows_hist,
                                                   reinterpret_cast<uint32_t*>(h->f_rows));
         SAR_LAUNCH_CHECK();
     }
     int32_t placed = 0;
     if (transpose) {
-        k_class_place<<<g_src, kThreads, 0, st>>>(in, Lists::kSources, 0, src_hist, nullptr);
+        k_class_place<<<g_place_src, kThreads, 0, st>>>(in, Lists::kSources, 0, src_hist, nullptr);
         SAR_LAUNCH_CHECK();
-        k_class_place<<<g_src, kThreads, 0, st>>>(in, Lists::kAllSources, h->tag_shift, hist_d + (2 * P + 1) * C, h->ft_rows);
+        k_class_place<<<g_place_src, kThreads, 0, st>>>(in, Lists::kAllSources, h->tag_shift, hist_d + (2 * P + 1) * C, h->ft_rows);
         SAR_LAUNCH_CHECK();
 
         // ---- the sources of one edge, listed from their destinations' side (all-blocks backward):
