@@ -258,12 +258,13 @@ __global__ __launch_bounds__(kThreads) void k_part_tile_count(const int32_t* __r
     if ((int)threadIdx.x < P) tile_counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = hist[threadIdx.x];
 }
 
-// code[v] = (partition of v << tag_shift) | number of nodes u < v in the same partition.
+// code[v] = (partition of v << tag_shift) | number of nodes u < v in the same partition; owner[v] = the partition.
 __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restrict__ part, int64_t N,
                                                         int P, int64_t n_tiles,
                                                         const int32_t* __restrict__ tile_base, int tag_shift,
-                                                        uint32_t* __restrict__ code)
+                                                        uint32_t* __restrict__ code, uint8_t* __restrict__ owner)
 {
+    static_assert(SAR_MAX_PARTS <= 256, "a partition fits a byte");
     constexpr int kRounds = kPartTile / kThreads;
     constexpr int kChunks = kPartTile / 64;
     __shared__ int cnt[kChunks][SAR_MAX_PARTS];
@@ -305,6 +306,7 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
         for (int c = 0; c < chunk; ++c) pre += cnt[c][pv[r]];
         const int64_t col = (int64_t)pv[r] * n_tiles;
         code[v] = ((uint32_t)pv[r] << tag_shift) | (uint32_t)(tile_base[col + blockIdx.x] - tile_base[col] + pre + rank[r]);
+        owner[v] = (uint8_t)pv[r];
     }
 }
 
@@ -323,8 +325,9 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
 // The keys are dealt to the buckets in runs of four: neighbouring keys are often frequent together
 // (ids in the order of degree), and a bucket of the 1024 most frequent rows of that graph holds half a
 // million pairs (641 us for one workgroup, and 14 ms to sort its rows).
-// What the kernels now take on those 15.2M edges: pairs to buckets 218 + 222 us from the edge list (the
-// gathers of the nodes' codes) and 48 + 194 us from the CSR, keys 31, finish 173 each.  The last was 372 us, three quarters
+// What the kernels now take on those 15.2M edges: pairs to buckets 153 + 194 us from the edge list (the
+// gathers of the nodes' partitions and codes; one edge a thread at a time 216 + 217) and 31 + 120 us from the CSR, keys
+// 29, finish 170 each.  The last was 372 us, three quarters
 // of it instructions: groups of up to 8 values now take 8 lanes instead of 16, those of 17 to 256 a network in registers.
 
 constexpr int kBucketThreads = 512;
@@ -370,8 +373,8 @@ BucketPlan plan_buckets(int64_t n_keys, int64_t n_items)
     while (((int64_t)1 << (b.nb + kMaxBucketBits)) < n_keys) ++b.nb;
     b.w = kRunBits;
     while (((int64_t)1 << (b.nb + b.w)) < n_keys) ++b.w;
-    // about a thousand tiles, fewer where the counts would not fit
-    const int64_t tiles = std::min<int64_t>(1024, std::max<int64_t>(1, kMaxBucketCounts >> b.nb));
+    // about 512 tiles, fewer where the counts would not fit
+    const int64_t tiles = std::min<int64_t>(512, std::max<int64_t>(1, kMaxBucketCounts >> b.nb));
     b.tile = std::max<int64_t>(1, (n_items + tiles - 1) / tiles);
     b.tile = (b.tile + kBucketSub - 1) / kBucketSub * kBucketSub;
     b.n_tiles = std::max<int64_t>(1, (n_items + b.tile - 1) / b.tile);
@@ -393,24 +396,49 @@ struct EdgeSource {
     const IdxT* src;
     const IdxT* dst;
     const uint32_t* code;
+    const uint8_t* owner;    // the partition alone
     int64_t E, N, n_dst;
     int p, tag_shift;
     int* err;
-    __device__ inline bool get(int64_t e, int64_t& key, uint32_t& value) const
+    // Edges e, e + step ... e + (U - 1) step (below end): which are kept, their keys and, with VALUES, their values.  The
+    // gathers of the codes wait for memory (10 MB of them for 2.4 million nodes do not stay in a 4 MB L2), so U edges' are
+    // under way at once; without VALUES a source is only asked for its partition, a byte a node, which stays there.
+    template <int U, bool VALUES>
+    __device__ inline void get(int64_t e, int64_t step, int64_t end, bool (&have)[U], int64_t (&key)[U], uint32_t (&value)[U]) const
     {
-        const int64_t d = (int64_t)dst[e], s = (int64_t)src[e];
-        if (d < 0 || d >= N || s < 0 || s >= N) {
-            atomicOr(err, 2);
-            return false;
+        int64_t d[U], s[U];
+        uint32_t cd[U], cs[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = min(e + u * step, E - 1);
+            d[u] = (int64_t)dst[at];
+            s[u] = (int64_t)src[at];
         }
-        const uint32_t cd = code[d];
-        if ((int)(cd >> tag_shift) != p) return false;
-        const uint32_t cs = code[s], mask = (1u << tag_shift) - 1u;
-        key = (int64_t)(cs >> tag_shift) * n_dst + (int64_t)(cd & mask);
-        value = cs & mask;
-        return true;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            have[u] = e + u * step < end;
+            if (have[u] && (d[u] < 0 || d[u] >= N || s[u] < 0 || s[u] >= N)) {
+                atomicOr(err, 2);
+                have[u] = false;
+            }
+            cd[u] = have[u] ? code[d[u]] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            have[u] = have[u] && (int)(cd[u] >> tag_shift) == p;
+            cs[u] = 0;
+            if (have[u]) cs[u] = VALUES ? code[s[u]] : (uint32_t)owner[s[u]];
+        }
+        const uint32_t mask = (1u << tag_shift) - 1u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            key[u] = (int64_t)(VALUES ? cs[u] >> tag_shift : cs[u]) * n_dst + (int64_t)(cd[u] & mask);
+            value[u] = cs[u] & mask;
+        }
     }
 };
+
+constexpr int kEdgesAhead = 4;
 
 template <typename Src>
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t tile, int64_t n_tiles, int64_t key0,
@@ -424,13 +452,18 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t
     __syncthreads();
     const int64_t beg = (int64_t)blockIdx.x * tile, end = min(in.E, beg + tile);
     unsigned long long mine = 0;
-    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
-        int64_t key;
-        uint32_t value;
-        if (!in.get(e, key, value)) continue;
-        ++mine;
-        key -= key0;
-        if (key >= 0 && key < n_keys) atomicAdd(&bucket_hist[deal.bucket(key)], 1);
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads * kEdgesAhead) {
+        bool have[kEdgesAhead];
+        int64_t key[kEdgesAhead];
+        uint32_t value[kEdgesAhead];
+        in.template get<kEdgesAhead, false>(e, kBucketThreads, end, have, key, value);
+#pragma unroll
+        for (int u = 0; u < kEdgesAhead; ++u) {
+            if (!have[u]) continue;
+            ++mine;
+            key[u] -= key0;
+            if (key[u] >= 0 && key[u] < n_keys) atomicAdd(&bucket_hist[deal.bucket(key[u])], 1);
+        }
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
@@ -453,13 +486,17 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Src in, int64
         bucket_cursor[b] = offsets[(int64_t)b * n_tiles + blockIdx.x];
     __syncthreads();
     const int64_t beg = (int64_t)blockIdx.x * tile, end = min(in.E, beg + tile);
-    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
-        int64_t key;
-        uint32_t value;
-        if (!in.get(e, key, value)) continue;
-        key -= key0;
-        if (key < 0 || key >= n_keys) continue;
-        pairs[atomicAdd(&bucket_cursor[deal.bucket(key)], 1)] = make_pair<PairT>(deal.place(key), value, vbits);
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads * kEdgesAhead) {
+        bool have[kEdgesAhead];
+        int64_t key[kEdgesAhead];
+        uint32_t value[kEdgesAhead];
+        in.template get<kEdgesAhead, true>(e, kBucketThreads, end, have, key, value);
+#pragma unroll
+        for (int u = 0; u < kEdgesAhead; ++u) {
+            key[u] -= key0;
+            if (!have[u] || key[u] < 0 || key[u] >= n_keys) continue;
+            pairs[atomicAdd(&bucket_cursor[deal.bucket(key[u])], 1)] = make_pair<PairT>(deal.place(key[u]), value[u], vbits);
+        }
     }
 }
 
@@ -501,16 +538,82 @@ __global__ __launch_bounds__(kBucketThreads) void k_block_count(const BlkDev* __
     const BlkDev& B = blk[block_of_tile(blk, P, blockIdx.x)];
     const int64_t beg = ((int64_t)blockIdx.x - B.tile0) * tile, end = min(B.nnz, beg + tile);
     const int64_t first = B.coff - key0;
-    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads) {
-        const int64_t key = first + B.indices[e];
-        if (key >= 0 && key < n_keys) atomicAdd(&bucket_hist[deal.bucket(key)], 1);
+    for (int64_t e = beg + threadIdx.x; e < end; e += kBucketThreads * kEdgesAhead) {
+        int32_t j[kEdgesAhead];
+#pragma unroll
+        for (int u = 0; u < kEdgesAhead; ++u) j[u] = B.indices[min(e + u * kBucketThreads, end - 1)];
+#pragma unroll
+        for (int u = 0; u < kEdgesAhead; ++u) {
+            const int64_t key = first + j[u];
+            if (e + u * kBucketThreads < end && key >= 0 && key < n_keys) atomicAdd(&bucket_hist[deal.bucket(key)], 1);
+        }
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
 }
 
-// The destination of an edge is the row whose range holds it: the rows that start inside the 2048
+// The destination of an edge is the row whose range holds it: the rows that start inside the SUB
 // edges at hand mark their first edge, and a running maximum over the marks names every edge's row.
+// row[k] becomes the row of edge beg + threadIdx.x * kPer + k.  `known` is the row of edge beg - 1 where the workgroup
+// has just had it, else -1; it becomes that of the last edge.
+template <int THREADS, int SUB>
+__device__ inline void rows_of_edges(const BlkDev& B, int64_t n_dst, int64_t beg, int n, int& known, int* mark,
+                                     int (&row)[SUB / THREADS])
+{
+    constexpr int kPer = SUB / THREADS, kWaves = THREADS / 64;
+    __shared__ int wave_max[kWaves];
+    __shared__ int first_row;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();
+    if (known < 0 && wave == 0) {
+        // the last row that starts at or before `beg`, 64 tries a round (in 32 bits: of 64-bit uniform values the compiler
+        // selected the new `lo` by the condition code of another instruction)
+        uint32_t lo = 0, hi = (uint32_t)n_dst - 1u;
+        const int32_t at = (int32_t)beg;
+        while (lo < hi) {
+            const uint32_t step = (hi - lo) / 64 + 1;
+            const uint32_t c = (uint32_t)__popcll(__ballot(B.indptr[lo + min((lane + 1) * step, hi - lo)] <= at));
+            const uint32_t from = min(c * step, hi - lo);
+            hi = lo + min((c + 1) * step - 1, hi - lo);
+            lo += from;
+        }
+        if (lane == 0) first_row = (int)lo;
+    }
+    for (int k = threadIdx.x; k < SUB; k += THREADS) mark[k] = 0;
+    __syncthreads();
+    const int r0 = known < 0 ? first_row : known;
+    for (int64_t r = r0 + 1 + threadIdx.x; r < n_dst; r += THREADS) {
+        const int64_t at = B.indptr[r] - beg;
+        if (at >= n) break;
+        atomicMax(&mark[at], (int)(r - r0));
+    }
+    __syncthreads();
+    int run = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        run = max(run, mark[threadIdx.x * kPer + k]);
+        row[k] = run;
+    }
+    int incl = run;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl = max(incl, x);
+    }
+    if (lane == 63) wave_max[wave] = incl;
+    __syncthreads();
+    int before = __shfl_up(incl, 1);
+    if (lane == 0) before = 0;
+    for (int k = 0; k < wave; ++k) before = max(before, wave_max[k]);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        row[k] = r0 + max(before, row[k]);
+        if ((int)threadIdx.x * kPer + k == n - 1) first_row = row[k];
+    }
+    __syncthreads();
+    known = first_row;
+}
+
 template <typename PairT>
 __global__ __launch_bounds__(kBucketThreads) void k_block_scatter(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
                                                                   int64_t tile, int64_t n_tiles, int64_t key0,
@@ -519,67 +622,128 @@ __global__ __launch_bounds__(kBucketThreads) void k_block_scatter(const BlkDev* 
                                                                   PairT* __restrict__ pairs)
 {
     constexpr int kPer = kBucketSub / kBucketThreads;
-    constexpr int kWaves = kBucketThreads / 64;
     extern __shared__ int bucket_cursor[];
     __shared__ int mark[kBucketSub];
-    __shared__ int wave_max[kWaves];
-    __shared__ int first_row;
     const int n_buckets = 1 << deal.nb;
     for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads)
         bucket_cursor[b] = offsets[(int64_t)b * n_tiles + blockIdx.x];
     const BlkDev& B = blk[block_of_tile(blk, P, blockIdx.x)];
     const int64_t t_beg = ((int64_t)blockIdx.x - B.tile0) * tile, t_end = min(B.nnz, t_beg + tile);
     const int64_t first = B.coff - key0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int known = -1;
     for (int64_t beg = t_beg; beg < t_end; beg += kBucketSub) {
         const int n = (int)min((int64_t)kBucketSub, t_end - beg);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int64_t lo = 0, hi = n_dst - 1;      // the last row that starts at or before `beg`
-            while (lo < hi) {
-                const int64_t mid = (lo + hi + 1) / 2;
-                if (B.indptr[mid] <= beg)
-                    lo = mid;
-                else
-                    hi = mid - 1;
-            }
-            first_row = (int)lo;
-        }
-        for (int k = threadIdx.x; k < kBucketSub; k += kBucketThreads) mark[k] = 0;
-        __syncthreads();
-        const int r0 = first_row;
-        for (int64_t r = r0 + 1 + threadIdx.x; r < n_dst; r += kBucketThreads) {
-            const int64_t at = B.indptr[r] - beg;
-            if (at >= n) break;
-            atomicMax(&mark[at], (int)(r - r0));
-        }
-        __syncthreads();
-        int v[kPer], run = 0;
+        int row[kPer];
+        rows_of_edges<kBucketThreads, kBucketSub>(B, n_dst, beg, n, known, mark, row);
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            run = max(run, mark[threadIdx.x * kPer + k]);
-            v[k] = run;
-        }
-        int incl = run;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int x = __shfl_up(incl, o);
-            if (lane >= o) incl = max(incl, x);
-        }
-        if (lane == 63) wave_max[wave] = incl;
-        __syncthreads();
-        int before = __shfl_up(incl, 1);
-        if (lane == 0) before = 0;
-        for (int k = 0; k < wave; ++k) before = max(before, wave_max[k]);
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) mark[threadIdx.x * kPer + k] = max(before, v[k]);
+        for (int k = 0; k < kPer; ++k) mark[threadIdx.x * kPer + k] = row[k];
         __syncthreads();
         for (int k = threadIdx.x; k < n; k += kBucketThreads) {
             const int64_t key = first + B.indices[beg + k];
             if (key < 0 || key >= n_keys) continue;
             pairs[atomicAdd(&bucket_cursor[deal.bucket(key)], 1)] =
-                make_pair<PairT>(deal.place(key), (uint32_t)(r0 + mark[k]), vbits);
+                make_pair<PairT>(deal.place(key), (uint32_t)mark[k], vbits);
         }
+    }
+}
+
+// The same for 32-bit pairs and up to 2^kStagedBits buckets: 16 thousand pairs are put in the order of their buckets in
+// LDS first, so that neighbouring lanes write neighbouring pairs.  A pair at a time, a wavefront's store went to 64
+// different cache lines of which it wrote four bytes each (15.2M pairs: 13M requests beyond the L2s, 187 us; staged 120, half as
+// many pairs at a time by two workgroups on a CU 133).
+constexpr int kStageThreads = 1024, kStageSub = 4096, kStage = 4 * kStageSub, kStagedBits = 12;
+constexpr size_t kStagedLds = (2 * ((size_t)1 << kStagedBits) + kStage + kStage / 2) * sizeof(int);
+__global__ __launch_bounds__(kStageThreads) void k_block_scatter_staged(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
+                                                                        int64_t tile, int64_t n_tiles, int64_t key0,
+                                                                        int64_t n_keys, Deal deal, int vbits,
+                                                                        const int32_t* __restrict__ offsets,
+                                                                        uint32_t* __restrict__ pairs)
+{
+    constexpr int kPer = kStageSub / kStageThreads, kSubs = kStage / kStageSub, kWaves = kStageThreads / 64;
+    constexpr int kMine = ((1 << kStagedBits) + kStageThreads - 1) / kStageThreads;    // buckets a thread sums up
+    extern __shared__ int staged_lds[];
+    __shared__ int wave_sum[kWaves];
+    int* const start = staged_lds;                                     // pairs of a bucket, then its first place here
+    int* const at = start + (1 << kStagedBits);                        // its next place in `pairs`, less `start`
+    uint32_t* const stage = (uint32_t*)(at + (1 << kStagedBits));      // first the marks of the rows
+    uint16_t* const owner = (uint16_t*)(stage + kStage);               // the bucket of a staged pair
+    const int n_buckets = 1 << deal.nb, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const BlkDev& B = blk[block_of_tile(blk, P, blockIdx.x)];
+    const int64_t t_beg = ((int64_t)blockIdx.x - B.tile0) * tile, t_end = min(B.nnz, t_beg + tile);
+    const int64_t first = B.coff - key0;
+    int next[kMine];                                                   // of the thread's own buckets
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int b = threadIdx.x * kMine + k;
+        next[k] = b < n_buckets ? offsets[(int64_t)b * n_tiles + blockIdx.x] : 0;
+    }
+    int known = -1;
+    for (int64_t beg = t_beg; beg < t_end; beg += kStage) {
+        for (int b = threadIdx.x; b < n_buckets; b += kStageThreads) start[b] = 0;
+        uint32_t pair[kSubs * kPer], meta[kSubs * kPer];               // meta: bucket | rank in the stage's bucket << 12
+#pragma unroll
+        for (int sub = 0; sub < kSubs; ++sub) {
+            const int64_t sb = beg + sub * kStageSub;
+            const int n = (int)max((int64_t)0, min((int64_t)kStageSub, t_end - sb));
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) meta[sub * kPer + k] = ~0u;
+            if (n == 0) continue;                                      // the same for the whole workgroup
+            int row[kPer];
+            int32_t j[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) j[k] = B.indices[sb + min((int)threadIdx.x * kPer + k, n - 1)];
+            rows_of_edges<kStageThreads, kStageSub>(B, n_dst, sb, n, known, (int*)stage, row);
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int64_t key = first + j[k];
+                if ((int)threadIdx.x * kPer + k >= n || key < 0 || key >= n_keys) continue;
+                const int b = deal.bucket(key);
+                pair[sub * kPer + k] = make_pair<uint32_t>(deal.place(key), (uint32_t)row[k], vbits);
+                meta[sub * kPer + k] = (uint32_t)b | (uint32_t)atomicAdd(&start[b], 1) << kStagedBits;
+            }
+        }
+        __syncthreads();
+        int count[kMine], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kMine; ++k) {
+            const int b = threadIdx.x * kMine + k;
+            count[k] = b < n_buckets ? start[b] : 0;
+            sum += count[k];
+        }
+        int incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(incl, o);
+            if (lane >= o) incl += x;
+        }
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        int run = incl - sum, total = 0;
+        for (int k = 0; k < kWaves; ++k) {
+            if (k < wave) run += wave_sum[k];
+            total += wave_sum[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kMine; ++k) {
+            const int b = threadIdx.x * kMine + k;
+            if (b < n_buckets) {
+                start[b] = run;
+                at[b] = next[k] - run;
+            }
+            run += count[k];
+            next[k] += count[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSubs * kPer; ++k) {
+            if (meta[k] == ~0u) continue;
+            const int b = (int)(meta[k] & ((1u << kStagedBits) - 1u)), to = start[b] + (int)(meta[k] >> kStagedBits);
+            stage[to] = pair[k];
+            owner[to] = (uint16_t)b;
+        }
+        __syncthreads();
+        for (int k = threadIdx.x; k < total; k += kStageThreads) pairs[at[owner[k]] + k] = stage[k];
+        __syncthreads();
     }
 }
 
@@ -1516,9 +1680,15 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
             SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
             auto place = [&](auto* pairs) -> int {
                 using PairT = std::remove_pointer_t<decltype(pairs)>;
-                SAR_TRY(allow_lds(k_block_scatter<PairT>, lds));
-                k_block_scatter<PairT><<<(unsigned)tiles, kBucketThreads, lds, st>>>(
-                    blk_d, P, n_dst, pass.tile, tiles, key0, nk, deal, vbits, counts, pairs);
+                if (sizeof(PairT) == 4 && pass.nb <= kStagedBits) {
+                    SAR_TRY(allow_lds(k_block_scatter_staged, kStagedLds));
+                    k_block_scatter_staged<<<(unsigned)tiles, kStageThreads, kStagedLds, st>>>(
+                        blk_d, P, n_dst, pass.tile, tiles, key0, nk, deal, vbits, counts, (uint32_t*)pairs);
+                } else {
+                    SAR_TRY(allow_lds(k_block_scatter<PairT>, lds));
+                    k_block_scatter<PairT><<<(unsigned)tiles, kBucketThreads, lds, st>>>(
+                        blk_d, P, n_dst, pass.tile, tiles, key0, nk, deal, vbits, counts, pairs);
+                }
                 SAR_LAUNCH_CHECK();
                 return finish_buckets<PairT>(pass, pairs, counts, nk, vbits, base, col_off + key0, t_indices_all, tmp, st);
             };
@@ -1673,8 +1843,10 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
     const int64_t n_tiles = std::max<int64_t>(1, (N + kPartTile - 1) / kPartTile);
     int32_t* tile_counts = nullptr;
     uint32_t* code = nullptr;
+    uint8_t* owner = nullptr;
     SAR_TRY(tmp.alloc(&tile_counts, (int64_t)P * n_tiles + 1));
     SAR_TRY(tmp.alloc(&code, N));
+    SAR_TRY(tmp.alloc(&owner, N));
     SAR_HIP(hipMemsetAsync(tile_counts + (int64_t)P * n_tiles, 0, sizeof(int32_t), st));
     k_part_tile_count<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, err_d);
     SAR_LAUNCH_CHECK();
@@ -1692,7 +1864,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
         n_src_max = std::max(n_src_max, h->blk[q].n_src);
     }
     SAR_TRY(set_tag_shift(h, n_src_max));
-    k_local_ids<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, h->tag_shift, code);
+    k_local_ids<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, h->tag_shift, code, owner);
     SAR_LAUNCH_CHECK();
 
     // 2. the kept edges grouped by (block, destination)
@@ -1752,9 +1924,9 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
     };
     if (E > 0) {
         if (idx_bytes == 4)
-            SAR_TRY(group(EdgeSource<int32_t>{(const int32_t*)src, (const int32_t*)dst, code, E, N, n_dst, p, h->tag_shift, err_d}));
+            SAR_TRY(group(EdgeSource<int32_t>{(const int32_t*)src, (const int32_t*)dst, code, owner, E, N, n_dst, p, h->tag_shift, err_d}));
         else
-            SAR_TRY(group(EdgeSource<int64_t>{(const int64_t*)src, (const int64_t*)dst, code, E, N, n_dst, p, h->tag_shift, err_d}));
+            SAR_TRY(group(EdgeSource<int64_t>{(const int64_t*)src, (const int64_t*)dst, code, owner, E, N, n_dst, p, h->tag_shift, err_d}));
     }
     if (E == 0 || n_rows_all == 0) {
         SAR_HIP(hipMemsetAsync(row_off, 0, (n_rows_all + 1) * sizeof(int32_t), st));
