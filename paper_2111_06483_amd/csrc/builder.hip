@@ -256,6 +256,7 @@ __global__ __launch_bounds__(kThreads) void k_part_tile_count(const int32_t* __r
     }
     __syncthreads();
     if ((int)threadIdx.x < P) tile_counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = hist[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) tile_counts[(int64_t)P * n_tiles] = 0;      // closes the scan
 }
 
 // code[v] = (partition of v << tag_shift) | number of nodes u < v in the same partition; owner[v] = the partition.
@@ -467,6 +468,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
+    if (blockIdx.x == 0 && threadIdx.x == 0) counts[(int64_t)n_buckets * n_tiles] = 0;      // closes the scan
     // edges kept for this worker, in 64 bits: the 32-bit offsets that follow must not wrap
     if (kept) {
         for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
@@ -550,6 +552,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_block_count(const BlkDev* __
     }
     __syncthreads();
     for (int b = threadIdx.x; b < n_buckets; b += kBucketThreads) counts[(int64_t)b * n_tiles + blockIdx.x] = bucket_hist[b];
+    if (blockIdx.x == 0 && threadIdx.x == 0) counts[(int64_t)n_buckets * n_tiles] = 0;      // closes the scan
 }
 
 // The destination of an edge is the row whose range holds it: the rows that start inside the SUB
@@ -916,15 +919,17 @@ __device__ inline void merge_sort(int32_t* a, int len)
     }
 }
 
-// off[key] = pairs of the key, for every key of the pass: a workgroup per bucket.
+// off[key] = pairs of the key, for every key of the pass: a workgroup per bucket.  off[n_keys] and the counters
+// of the buckets too large for LDS start at 0.
 template <typename PairT>
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_keys(const PairT* __restrict__ pairs,
                                                                 const int32_t* __restrict__ offsets, int64_t n_tiles,
                                                                 int w, Deal deal, int64_t n_keys, int vbits,
-                                                                int32_t* __restrict__ off)
+                                                                int32_t* __restrict__ off, int* __restrict__ big_count)
 {
     extern __shared__ int bucket_lds[];
     const int n_slots = 1 << w, b = blockIdx.x;
+    if (b == 0 && threadIdx.x == 0) big_count[0] = big_count[1] = off[n_keys] = 0;
     for (int k = threadIdx.x; k < n_slots; k += kBucketThreads) bucket_lds[k] = 0;
     __syncthreads();
     const int beg = offsets[(int64_t)b * n_tiles], end = offsets[(int64_t)(b + 1) * n_tiles];
@@ -1371,7 +1376,10 @@ __global__ __launch_bounds__(kThreads) void k_source_offsets(const BlkDev* __res
     for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k <= B.n_src; k += (int64_t)gridDim.x * kThreads) {
         const int32_t o = off[B.coff + k];
         B.t_indptr[k] = o - (int32_t)B.nnz0;
-        if (k < B.n_src) flags[B.coff + k] = off[B.coff + k + 1] > o ? 1 : 0;
+        if (k < B.n_src)
+            flags[B.coff + k] = off[B.coff + k + 1] > o ? 1 : 0;
+        else if (blockIdx.y == gridDim.y - 1)
+            flags[B.coff + k] = 0;           // closes the scan
     }
 }
 
@@ -1391,8 +1399,9 @@ __global__ __launch_bounds__(kThreads) void k_source_ranks(const BlkDev* __restr
 // ------------------------------------------------- all-blocks (fused) index
 
 __global__ __launch_bounds__(kThreads) void k_total_degree(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
-                                                           int32_t* __restrict__ deg)
+                                                           int32_t* __restrict__ deg, int* __restrict__ hist, int n_hist)
 {
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_hist; i += (int64_t)gridDim.x * kThreads) hist[i] = 0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i <= n_dst;
          i += (int64_t)gridDim.x * kThreads) {
         int d = 0;
@@ -1402,13 +1411,16 @@ __global__ __launch_bounds__(kThreads) void k_total_degree(const BlkDev* __restr
     }
 }
 
-// Row i of the all-blocks index: its sources block after block, tagged with the block.  A
-// wavefront takes a row: lane q reads block q's range of the row, then 8 lanes copy a block's
-// (usually short) range, eight blocks at a time.
-__global__ __launch_bounds__(kThreads) void k_fused_copy(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
+// Rows of the all-blocks index: a row's sources block after block, tagged with the block.  A wavefront takes `rows` rows
+// from as many parts of the list (neighbouring rows are often long together), as many as have a lane each for every block, 4 at
+// most: a lane reads its block's range of its row, then 8 lanes copy a range, 32 ranges of one turn under way at once, and
+// the whole wavefront the ranges of more than 64.  (One row at a time, 8 lanes to a range of any length: 306 thousand rows
+// of 50 in 8 blocks, up to 11 thousand in one, 94 us, now 56.)
+__global__ __launch_bounds__(kThreads) void k_fused_copy(const BlkDev* __restrict__ blk, int P, int rows, int64_t n_dst,
                                                          const int32_t* __restrict__ f_indptr, int tag_shift,
                                                          uint32_t* __restrict__ f_indices)
 {
+    constexpr int kTurn = 4;
     __shared__ const int32_t* s_indices[SAR_MAX_BLOCKS];
     __shared__ const int32_t* s_indptr[SAR_MAX_BLOCKS];
     if ((int)threadIdx.x < P) {
@@ -1416,27 +1428,56 @@ __global__ __launch_bounds__(kThreads) void k_fused_copy(const BlkDev* __restric
         s_indptr[threadIdx.x] = blk[threadIdx.x].indptr;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
-    for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6; i < n_dst;
-         i += ((int64_t)gridDim.x * kThreads) >> 6) {
-        int beg = 0, len = 0;
-        if (lane < P) {
-            beg = s_indptr[lane][i];
-            len = s_indptr[lane][i + 1] - beg;
+    const int lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3, ranges = rows * P;
+    const int my_row = lane / P, my_q = lane - my_row * P;
+    const int64_t part = (n_dst + rows - 1) / rows, step = ((int64_t)gridDim.x * kThreads) >> 6;
+    for (int64_t i0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6; i0 < part; i0 += step) {
+        const int64_t i = i0 + my_row * part;
+        int beg = 0, len = 0, pos = 0;
+        if (lane < ranges && i < n_dst) {
+            beg = s_indptr[my_q][i];
+            len = s_indptr[my_q][i + 1] - beg;
+            pos = f_indptr[i];
         }
-        int at = len;                          // exclusive sum of the blocks' lengths
+        int at = len;                          // sum of the row's lengths up to this block's
         for (int o = 1; o < P; o <<= 1) {
             const int x = __shfl_up(at, o);
-            if (lane >= o) at += x;
+            if (my_q >= o) at += x;
         }
-        at -= len;
-        const int64_t pos = f_indptr[i];
-        for (int q0 = 0; q0 < P; q0 += 8) {
-            const int q = q0 + grp;            // P <= 64: a lane of the wavefront
-            const int b = __shfl(beg, q), n = __shfl(len, q), a = __shfl(at, q);
-            if (q < P)
-                for (int e = sub; e < n; e += 8)
-                    f_indices[pos + a + e] = (uint32_t)s_indices[q][b + e] | ((uint32_t)q << tag_shift);
+        at += pos - len;
+        constexpr int kLong = 64;
+        for (uint64_t todo = __ballot(len > kLong); todo; todo &= todo - 1) {
+            const int r = __ffsll((long long)todo) - 1;
+            const int b = __shfl(beg, r), n = __shfl(len, r), a = __shfl(at, r), q = __shfl(my_q, r);
+            const int32_t* const from = s_indices[q] + b;
+            for (int e0 = lane; e0 < n; e0 += 64 * kTurn) {
+                uint32_t x[kTurn];
+#pragma unroll
+                for (int u = 0; u < kTurn; ++u) x[u] = (uint32_t)from[min(e0 + 64 * u, n - 1)];
+#pragma unroll
+                for (int u = 0; u < kTurn; ++u)
+                    if (e0 + 64 * u < n) f_indices[a + e0 + 64 * u] = x[u] | ((uint32_t)q << tag_shift);
+            }
+        }
+        for (int r0 = 0; r0 < ranges; r0 += 8 * kTurn) {
+            int b[kTurn], n[kTurn], a[kTurn], q[kTurn];
+            uint32_t x[kTurn];
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                const int r = r0 + u * 8 + grp, from = min(r, 63);
+                b[u] = __shfl(beg, from);
+                n[u] = __shfl(len, from);
+                a[u] = __shfl(at, from);
+                q[u] = __shfl(my_q, from);
+                if (r >= ranges || n[u] > kLong) n[u] = 0;
+                if (sub < n[u]) x[u] = (uint32_t)s_indices[q[u]][b[u] + sub];
+            }
+#pragma unroll
+            for (int u = 0; u < kTurn; ++u) {
+                const uint32_t tag = (uint32_t)q[u] << tag_shift;
+                if (sub < n[u]) f_indices[a[u] + sub] = x[u] | tag;
+                for (int e = sub + 8; e < n[u]; e += 8) f_indices[a[u] + e] = (uint32_t)s_indices[q[u]][b[u] + e] | tag;
+            }
         }
     }
 }
@@ -1540,12 +1581,10 @@ int finish_buckets(const BucketPlan& plan, const PairT* pairs, const int32_t* co
     int32_t* list = nullptr;
     SAR_TRY(tmp.alloc(&list, plan.n_buckets() + 2));
     int* count = list + plan.n_buckets();                // buckets listed, and shares of them taken
-    SAR_HIP(hipMemsetAsync(count, 0, 2 * sizeof(int), st));
-    SAR_HIP(hipMemsetAsync(off + n_keys, 0, sizeof(int32_t), st));
     const size_t slots = ((size_t)1 << plan.w) * sizeof(int), lds = slots + kBucketCap * sizeof(int32_t);
     const Deal deal{plan.nb};
     k_bucket_keys<PairT><<<(unsigned)plan.n_buckets(), kBucketThreads, slots, st>>>(pairs, counts, plan.n_tiles, plan.w,
-                                                                                   deal, n_keys, vbits, off);
+                                                                                   deal, n_keys, vbits, off, count);
     SAR_LAUNCH_CHECK();
     SAR_TRY(exclusive_scan(off, off, n_keys + 1, st, tmp, base));
     SAR_TRY(allow_lds(k_bucket_finish<PairT>, lds));
@@ -1629,12 +1668,11 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
 
     // total in-degree |N(i)|, and its class histograms: the blocks' rows, their sources, all rows
-    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg);
-    SAR_LAUNCH_CHECK();
     int* hist_d = nullptr;
     const int C = sar::kNumClasses, n_hist = (2 * P + 2) * C;
     SAR_TRY(tmp.alloc(&hist_d, n_hist));
-    SAR_HIP(hipMemsetAsync(hist_d, 0, n_hist * sizeof(int), st));
+    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg, hist_d, n_hist);
+    SAR_LAUNCH_CHECK();
     int *rows_hist = hist_d, *src_hist = hist_d + P * C, *all_rows_hist = hist_d + 2 * P * C;
     ListIn in{blk_d, h->f_indptr, n_dst};
     const dim3 g_rows(grid_for(n_dst, kThreads, std::max(1, 4096 / P)), P), g_all(grid_for(n_dst, kThreads, 4096), 1);
@@ -1647,7 +1685,9 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     // ---- all-blocks destination-major index
     if (fused) {
         SAR_TRY(exclusive_scan(h->deg, h->f_indptr, n_dst + 1, st, tmp));
-        k_fused_copy<<<grid_for(n_dst * 64), kThreads, 0, st>>>(blk_d, P, n_dst, h->f_indptr, h->tag_shift, h->f_indices);
+        const int rows = std::min(4, 64 / P);       // P <= 64
+        k_fused_copy<<<grid_for((n_dst + rows - 1) / rows * 64), kThreads, 0, st>>>(blk_d, P, rows, n_dst, h->f_indptr,
+                                                                                    h->tag_shift, h->f_indices);
         SAR_LAUNCH_CHECK();
         k_class_hist<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, all_rows_hist);
         SAR_LAUNCH_CHECK();
@@ -1672,7 +1712,6 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
             const int64_t n_counts = (int64_t)pass.n_buckets() * tiles + 1;
             const size_t lds = pass.n_buckets() * sizeof(int);
             const Deal deal{pass.nb};
-            SAR_HIP(hipMemsetAsync(counts + n_counts - 1, 0, sizeof(int32_t), st));
             SAR_TRY(allow_lds(k_block_count, lds));
             k_block_count<<<(unsigned)tiles, kBucketThreads, lds, st>>>(blk_d, P, pass.tile, tiles, key0, nk, deal,
                                                                         counts);
@@ -1702,7 +1741,6 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         }
         // per-block offsets (from 0), the classes of the sources, ranks of the touched ones
         SAR_TRY(tmp.alloc(&pos, n_src_total + 1));
-        SAR_HIP(hipMemsetAsync(pos + n_src_total, 0, sizeof(int32_t), st));
         k_source_offsets<<<g_src, kThreads, 0, st>>>(blk_d, col_off, pos);
         SAR_LAUNCH_CHECK();
         k_class_hist<<<g_src, kThreads, 0, st>>>(in, Lists::kSources, src_hist);
@@ -1847,7 +1885,6 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
     SAR_TRY(tmp.alloc(&tile_counts, (int64_t)P * n_tiles + 1));
     SAR_TRY(tmp.alloc(&code, N));
     SAR_TRY(tmp.alloc(&owner, N));
-    SAR_HIP(hipMemsetAsync(tile_counts + (int64_t)P * n_tiles, 0, sizeof(int32_t), st));
     k_part_tile_count<<<(unsigned)n_tiles, kThreads, 0, st>>>(part, N, P, n_tiles, tile_counts, err_d);
     SAR_LAUNCH_CHECK();
     SAR_TRY(exclusive_scan(tile_counts, tile_counts, (int64_t)P * n_tiles + 1, st, tmp));
@@ -1886,7 +1923,6 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
             const int64_t n_counts = (int64_t)plan.n_buckets() * plan.n_tiles + 1;
             const size_t lds = plan.n_buckets() * sizeof(int);
             const Deal deal{plan.nb};
-            SAR_HIP(hipMemsetAsync(counts + n_counts - 1, 0, sizeof(int32_t), st));
             SAR_TRY(allow_lds(k_bucket_count<decltype(in)>, lds));
             k_bucket_count<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(in, plan.tile, plan.n_tiles, key0, nk, deal,
                                                                                 counts, first ? kept_d : nullptr);
