@@ -106,8 +106,8 @@ __device__ inline void fwd_edges(SoftState<Vec<T>::N>& st, const FwdArgs& a, con
     constexpr int VEC = Vec<T>::N;
     constexpr int SLOTS = kWave / G;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
-    if (shares > 1) row_share(beg, end, share, shares);
-    for (int cb = beg; cb < end; cb += kWave) {
+    const int step = row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += step) {
         const int cnt = min(kWave, end - cb);
         const uint32_t mine = (lm.lane < cnt) ? a.indices[cb + lm.lane] : 0u;
         for (int k0 = 0; k0 < cnt; k0 += SLOTS * kU) {
@@ -348,8 +348,8 @@ __device__ inline void bwd_edges(BwdAcc<Vec<T>::N>& ac, const BwdScalars& a, con
     constexpr int VEC = Vec<T>::N;
     constexpr int SLOTS = kWave / G;
     const T* Gp = static_cast<const T*>(a.G);
-    if (shares > 1) row_share(beg, end, share, shares);
-    for (int cb = beg; cb < end; cb += kWave) {
+    const int step = row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += step) {
         const int cnt = min(kWave, end - cb);
         const int mine = (lm.lane < cnt) ? idx[cb + lm.lane] : 0;
         for (int k0 = 0; k0 < cnt; k0 += SLOTS * kU) {

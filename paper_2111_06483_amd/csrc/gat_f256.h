@@ -408,8 +408,8 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
     auto edges = [&](FwdState<LPH>& st, int i, int share, int shares) {
         const float s2 = a.s[(int64_t)i * ldh + h] * kLog2e;
         int beg = a.indptr[i], end = a.indptr[i + 1];
-        if (shares > 1) row_share(beg, end, share, shares);
-        for (int cb = beg; cb < end; cb += kWave) {
+        const int step = row_share(beg, end, share, shares);
+        for (int cb = beg; cb < end; cb += step) {
             const int cnt = min(kWave, end - cb);
             const uint32_t mine = (lane < cnt) ? a.indices[cb + lane] : 0u;
             fwd_chunk<T, LPH, B, ALL, FLY, PAD>(st, a, tabs, mine, cnt, foff, on, h, k, s2, al);
@@ -608,11 +608,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         const int32_t* ip = tabs.t_indptr[q];
         const int32_t* idx = tabs.t_indices[q];
         int beg = ip[j], end = ip[j + 1];
-        if (shares > 1) row_share(beg, end, share, shares);
+        const int step = row_share(beg, end, share, shares);
 #pragma unroll
         for (int x = 0; x < 4; ++x) ac.dz[x] = 0.f;
         ac.dt = 0.f;
-        for (int cb = beg; cb < end; cb += kWave) {
+        for (int cb = beg; cb < end; cb += step) {
             const int cnt = min(kWave, end - cb);
             const int mine = (lane < cnt) ? idx[cb + lane] : 0;
             bwd_chunk<T, LPH, B, PAD>(ac, a, ds, mine, cnt, foff, on, h, k, zj, t2);

@@ -264,8 +264,8 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int n_slots, in
     auto edges = [&](State& st, int i, int share, int shares) {
         const float s2 = a.s[(int64_t)i * a.ldh + p.h] * kLog2e;
         int beg = a.indptr[i], end = a.indptr[i + 1];
-        if (shares > 1) row_share(beg, end, share, shares);
-        for (int cb = beg; cb < end; cb += kWave) {
+        const int step = row_share(beg, end, share, shares);
+        for (int cb = beg; cb < end; cb += step) {
             const int cnt = min(kWave, end - cb);
             const uint32_t mine = (p.lane < cnt) ? a.indices[cb + p.lane] : 0u;
             fwd_chunk<T, LPH, ALL, FLY, RAG>(st, a, s_Z, s_t, mine, cnt, n_slots, p, s2, al);
@@ -534,11 +534,11 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
         }
         const int32_t* idx = tabs.t_indices[q];
         int beg = tabs.t_indptr[q][j], end = tabs.t_indptr[q][j + 1];
-        if (shares > 1) row_share(beg, end, share, shares);
+        const int step = row_share(beg, end, share, shares);
 #pragma unroll
         for (int x = 0; x < 4; ++x) ac.dz[x] = 0.f;
         ac.dt = 0.f;
-        for (int cb = beg; cb < end; cb += kWave) {
+        for (int cb = beg; cb < end; cb += step) {
             const int cnt = min(kWave, end - cb);
             const int mine = (p.lane < cnt) ? idx[cb + p.lane] : 0;
             for (int k0 = 0; k0 < cnt; k0 += B * n_slots) {

@@ -168,8 +168,8 @@ __device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, cons
                                 int beg, int end, int share, int shares, const RowLanes<T, G, RAG>& lm)
 {
     constexpr int SLOTS = kWave / G;
-    if (shares > 1) row_share(beg, end, share, shares);
-    for (int cb = beg; cb < end; cb += kWave) {
+    const int step = row_share(beg, end, share, shares);
+    for (int cb = beg; cb < end; cb += step) {
         const int cnt = min(kWave, end - cb);
         const uint32_t mine = (lm.lane < cnt) ? a.indices[cb + lm.lane] : 0u;
         int k0 = 0;

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 SLOPE = 0.2
 f64 = lambda t: t.to(torch.float64).cpu().numpy()
 LENGTHS = [*range(0, 10)] * 4 + [15, 16, 17, 24, 31, 32, 33, 40, 63, 64, 65, 71, 127, 128, 129, 130, 159, 160, 161, 191,
-                                 192, 193, 255, 256, 257, 263, 300, 511, 512, 513, 777]
+                                 192, 193, 255, 256, 257, 263, 300, 511, 512, 513, 777, 1023, 1024, 1025, 1290]
 
 
 def graph(seed):
