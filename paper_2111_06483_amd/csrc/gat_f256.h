@@ -52,11 +52,24 @@ constexpr int kQuadXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kRowHalfMirror = 0x141;  // lane r of 8 reads lane 7 - r
 constexpr int kRowMirror = 0x140;      // lane r of 16 reads lane 15 - r
 constexpr int kRowRor8 = 0x128;
+constexpr int kQuadReverse = 0x1B;     // quad_perm [3,2,1,0]
+constexpr int kRowNewBcast = 0x150;    // + n: every lane of a row of 16 reads the row's lane n
 
-template <int PATTERN>
-__device__ inline float swizzle(float v)
+// Of each 32 lanes, the value of the lane at this one's place in the lower row of 16, and in the upper row; and the same of
+// the lower and upper 32.  (v_permlane16_swap, v_permlane32_swap of a value with itself: vector instructions, where
+// ds_swizzle and ds_bpermute queue up for the LDS crossbar and are waited for.)
+struct Pair {
+    float lo, hi;
+};
+__device__ inline Pair rows_of_32(float v)
 {
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), PATTERN));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ inline Pair halves_of_64(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
 struct OpSum {
@@ -79,22 +92,56 @@ __device__ inline float group_all(float v)
     if constexpr (LPH >= 4) v = Op::f(v, dpp<kQuadXor2>(v));
     if constexpr (LPH >= 8) v = Op::f(v, dpp<kRowHalfMirror>(v));
     if constexpr (LPH >= 16) v = Op::f(v, dpp<kRowMirror>(v));
-    if constexpr (LPH >= 32) v = Op::f(v, swizzle<0x401F>(v));   // xor 16
-    if constexpr (LPH >= 64) v = Op::f(v, __shfl_xor(v, 32));
+    if constexpr (LPH >= 32) {
+        const Pair p = rows_of_32(v);
+        v = Op::f(p.lo, p.hi);
+    }
+    if constexpr (LPH >= 64) {
+        const Pair p = halves_of_64(v);
+        v = Op::f(p.lo, p.hi);
+    }
     return v;
 }
 
-// Value held by lane K of the caller's head group, delivered to the whole group.
-template <int LPH, int K>
-__device__ inline float group_bcast(float v)
-{
-    if constexpr (LPH >= 64) {
-        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), K));
-    } else {
-        constexpr int kAnd = (LPH >= 32) ? 0x00 : (0x1F & ~(LPH - 1));
-        return swizzle<(K << 5) | kAnd>(v);
+// A value of every lane of a head group, made ready to be handed to the whole group lane by lane: of<K>() is lane K's (K < 16).
+// DPP: one vector instruction each (a scalar where the group is the wavefront), after three for groups of 8 lanes and one
+// for 32.  Otherwise ds_swizzle, which leaves the vector units alone: measured (us, ds_swizzle / DPP), 8 lanes by head slices 25 M
+// edges forward 2283 / 2249, by rows 201 M edges of bf16 9610 / 9730; 16 lanes 1.5 M edges of bf16, a long row deciding, 276 /
+// 282; 32 lanes 122 M edges of 4 x 100 backward 36400 / 35700.
+template <int LPH, bool DPP = LPH == 4 || LPH == 32>
+struct Spread {
+    int lo, hi;
+    __device__ inline explicit Spread(int v) : lo(v), hi(v)
+    {
+        if constexpr (DPP && LPH == 8) {     // lo: the lower quad's values in both quads, hi: the upper quad's
+            const int m = dpp_i<kRowHalfMirror>(v);
+            lo = __builtin_amdgcn_update_dpp(v, m, kQuadReverse, 0xf, 0xa, false);
+            hi = __builtin_amdgcn_update_dpp(v, m, kQuadReverse, 0xf, 0x5, false);
+        } else if constexpr (DPP && LPH == 32) {
+            lo = __float_as_int(rows_of_32(__int_as_float(v)).lo);
+        }
     }
-}
+    __device__ inline explicit Spread(uint32_t v) : Spread((int)v) {}
+    __device__ inline explicit Spread(float v) : Spread(__float_as_int(v)) {}
+    template <int K>
+    __device__ inline int of_int() const
+    {
+        static_assert(K < LPH && K < 16, "a lane of the group's first row");
+        if constexpr (LPH == 64)
+            return __builtin_amdgcn_readlane(lo, K);
+        else if constexpr (!DPP)
+            return __builtin_amdgcn_ds_swizzle(lo, K << 5 | (0x1f & ~(LPH - 1)));
+        else if constexpr (LPH <= 8)
+            return __builtin_amdgcn_mov_dpp(K < 4 ? lo : hi, K % 4 * 0x55, 0xf, 0xf, true);     // quad_perm [K,K,K,K]
+        else
+            return __builtin_amdgcn_mov_dpp(lo, kRowNewBcast + K, 0xf, 0xf, true);
+    }
+    template <int K>
+    __device__ inline float of() const
+    {
+        return __int_as_float(of_int<K>());
+    }
+};
 
 // Sums of 8 per-lane values over each group of LPH consecutive lanes, one sum per lane: the lane
 // at position k of its group (k % 8 for LPH > 8) returns the group's sum of c[k % 8].  Eight
@@ -105,7 +152,6 @@ __device__ inline float group_bcast(float v)
 // (bf16 4 x 128 and 2 x 256: 3 to 10% per pass); within 16 lanes the eight independent DPP chains
 // of the separate all-reductions are as fast or faster.
 constexpr int kScatterSumsFrom = 32;
-constexpr int kQuadReverse = 0x1B;     // quad_perm [3,2,1,0]
 template <int LPH>
 __device__ inline float group_sums8(const float (&c)[8])
 {
@@ -127,8 +173,14 @@ __device__ inline float group_sums8(const float (&c)[8])
     // lane ^ 4 = the mirror image within 8 lanes (lane ^ 7) of the quad's reverse (lane ^ 3)
     float v = mine + dpp<kQuadReverse>(dpp<kRowHalfMirror>(send));
     if constexpr (LPH >= 16) v += dpp<kRowRor8>(v);
-    if constexpr (LPH >= 32) v += swizzle<0x401F>(v);   // xor 16
-    if constexpr (LPH >= 64) v += __shfl_xor(v, 32);
+    if constexpr (LPH >= 32) {
+        const Pair p = rows_of_32(v);
+        v = p.lo + p.hi;
+    }
+    if constexpr (LPH >= 64) {
+        const Pair p = halves_of_64(v);
+        v = p.lo + p.hi;
+    }
     return v;
 }
 
@@ -339,8 +391,9 @@ __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const Tabs& t
         }
         const float p = fast_exp2(e2 - st.m2);        // 0 for the lanes without an edge
         st.l += p;
+        const Spread<LPH> ps(p);
         static_for<B>([&](auto kk) {
-            const float pk = group_bcast<LPH, decltype(kk)::value>(p);
+            const float pk = ps.template of<decltype(kk)::value>();
             float v[4];
             Row4<T>::unpack(raw[decltype(kk)::value], v);
 #pragma unroll
@@ -560,8 +613,9 @@ __device__ inline void bwd_chunk(BwdAcc4& ac, const BwdP& a, float* ds, int mine
         const float du = u2 > 0.f ? de : a.slope * de;
         ac.dt += du;
         if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, du);
+        const Spread<LPH> as(alpha);
         static_for<B>([&](auto kk) {
-            const float ak = group_bcast<LPH, decltype(kk)::value>(alpha);
+            const float ak = as.template of<decltype(kk)::value>();
             float g[4];
             Row4<T>::unpack(raw[decltype(kk)::value], g);
 #pragma unroll
@@ -869,9 +923,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
             const float du = u2 > 0.f ? de : a.slope * de;
             dt_mine += du;
             if (my_ok) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, du);
+            const Spread<LPH> as(alpha);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                const float ak = group_bcast<LPH, K>(alpha);
+                const float ak = as.template of<K>();
                 float g[4];
                 Row4<T>::unpack(raw[K], g);
 #pragma unroll
@@ -880,10 +935,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
         }
 
         // ---- dZ_q[j] = sum alpha G + dt a_l ; dt_q[j] = dt ; da_l += dt z_j
+        const Spread<LPH> dts(dt_mine);
         static_for<S>([&](auto uu) {
             constexpr int u = decltype(uu)::value;
             float dt = 0.f;
-            static_for<R>([&](auto rr) { dt += group_bcast<LPH, u * R + decltype(rr)::value>(dt_mine); });
+            static_for<R>([&](auto rr) { dt += dts.template of<u * R + decltype(rr)::value>(); });
             if (have[u]) {
                 float v[4], zj[4];
                 Row4<T>::unpack(zr[u], zj);
@@ -1060,10 +1116,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
                 const int next = dpp_i<kRowShl + 1>(seg);
                 if (valid && (k == B - 1 || next != seg)) unsafeAtomicAdd(ds + (int64_t)my_i * ldh + h, run);
             }
+            const Spread<LPH> as(alpha), us(du);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                const float ak = group_bcast<LPH, K>(alpha);
-                const float dk = group_bcast<LPH, K>(du);
+                const float ak = as.template of<K>();
+                const float dk = us.template of<K>();
                 float g[4], z[4], v[4];
                 Row4<T>::unpack(rg[K], g);
                 Row4<T>::unpack(rz[K], z);

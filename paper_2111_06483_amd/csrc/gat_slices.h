@@ -21,12 +21,12 @@ namespace slices {
 using f256::dpp;
 using f256::FwdP;
 using f256::group_all;
-using f256::group_bcast;
 using f256::leaky2;
 using f256::load_lane;
 using f256::OpMax;
 using f256::OpSum;
 using f256::Row4;
+using f256::Spread;
 using f256::static_for;
 using f256::store_lane;
 using f256::Tabs;
@@ -86,12 +86,6 @@ __device__ inline void zero_behind(Raw (&raw)[B], int left)
     });
 }
 
-template <int LPH, int K>
-__device__ inline uint32_t bcast_u(uint32_t v)
-{
-    return (uint32_t)__float_as_int(group_bcast<LPH, K>(__int_as_float((int)v)));
-}
-
 // ------------------------------------------------------------------ forward, all blocks
 
 template <typename T, int LPH, bool FLY, bool PAD, bool SYNC>
@@ -136,10 +130,11 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
                 const int64_t at = (int64_t)(mine & mask);
                 const uint64_t row = reinterpret_cast<uint64_t>(s_Z[mine >> a.tag_shift] + at * a.ld);
                 typename Row4<T>::Raw raw[B];
+                const Spread<LPH, LPH <= 32> lo((uint32_t)row), hi((uint32_t)(row >> 32));
                 static_for<B>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
-                    const uint64_t from = (uint64_t)bcast_u<LPH, K>((uint32_t)row) |
-                                          (uint64_t)bcast_u<LPH, K>((uint32_t)(row >> 32)) << 32;
+                    const uint64_t from = (uint64_t)(uint32_t)lo.template of_int<K>() |
+                                          (uint64_t)(uint32_t)hi.template of_int<K>() << 32;
                     raw[K] = load_lane<T, PAD>(reinterpret_cast<const T*>(from), foff, on);
                 });
                 zero_behind(raw, len - e0);
@@ -171,9 +166,10 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
                 }
                 const float p = fast_exp2(e2 - m2);
                 l += p;
+                const Spread<LPH, LPH <= 32> ps(p);
                 static_for<B>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
-                    const float pk = group_bcast<LPH, K>(p);
+                    const float pk = ps.template of<K>();
                     float v[4];
                     Row4<T>::unpack(raw[K], v);
 #pragma unroll
@@ -315,9 +311,10 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
             if (e0 >= len) continue;
             const int next = idx[beg + min(e0 + B + k, len - 1)];
             typename Row4<T>::Raw raw[B];
+            const Spread<LPH, LPH <= 32> ids(mine);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                raw[K] = load_lane<T, false>(Gp + (uint64_t)bcast_u<LPH, K>((uint32_t)mine) * (uint32_t)a.ld, 0, true);
+                raw[K] = load_lane<T, false>(Gp + (uint64_t)(uint32_t)ids.template of_int<K>() * (uint32_t)a.ld, 0, true);
             });
             zero_behind(raw, len - e0);
             const bool valid = live && k < B && e0 + k < len;
@@ -339,9 +336,10 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
             const float du = u2 > 0.f ? de : a.slope * de;
             dt += valid ? du : 0.f;
             if (valid) unsafeAtomicAdd(ds_of + (int64_t)mine * HS, du);
+            const Spread<LPH, LPH <= 32> as(alpha);
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                const float ak = group_bcast<LPH, K>(alpha);
+                const float ak = as.template of<K>();
                 float g[4];
                 Row4<T>::unpack(raw[K], g);
 #pragma unroll

@@ -32,12 +32,12 @@ using f256::BwdP;
 using f256::BwdTabs;
 using f256::FwdP;
 using f256::group_all;
-using f256::group_bcast;
 using f256::leaky2;
 using f256::OpMax;
 using f256::OpSum;
 using f256::Row4;
 using f256::score_log2;
+using f256::Spread;
 using f256::static_for;
 using f256::Tabs;
 
@@ -83,13 +83,6 @@ template <bool ANY>
 __device__ inline void load4_f32(const float* p, float (&v)[4])
 {
     Row4<float>::unpack(load_raw<float, ANY>(p), v);
-}
-
-// Value of lane K of the caller's head group.
-template <int LPH, int K>
-__device__ inline int bcast_i(int v)
-{
-    return __float_as_int(group_bcast<LPH, K>(__int_as_float(v)));
 }
 
 // The places of a batch that some slot of the wavefront has an edge for, in three groups [0, G1), [G1, G2), [G2, END) that
@@ -203,9 +196,10 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
         }
         const float pe = fast_exp2(e2 - (st.m2 == -INFINITY ? 0.f : st.m2));   // 0 for the lanes without an edge
         st.l += pe;
+        const Spread<LPH> ps(pe);
         some.template each<0>([&](auto kk) {
             constexpr int K = decltype(kk)::value;
-            const float pk = group_bcast<LPH, K>(pe);
+            const float pk = ps.template of<K>();
             float v[4];
             Row4<T>::unpack(raw[K], v);
 #pragma unroll
@@ -405,10 +399,11 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
             constexpr int r = decltype(rr)::value;
             if (!(r == 0 ? some.any : some.most)) return;
             typename Row4<T>::Raw raw[B];
+            const Spread<LPH> js(s0.j[r]);
             some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 raw[K] = typename Row4<T>::Raw{};
-                const int j = bcast_i<LPH, K>(s0.j[r]);
+                const int j = js.template of_int<K>();
                 if (p.on && r * B + K < m0.cnt) raw[K] = load_raw<T, RAG>(Z + (int64_t)j * a.ld + p.foff);
             });
             const bool valid = p.live && p.k_pos < B && r * B + p.k_pos < m0.cnt;
@@ -436,9 +431,10 @@ __device__ inline void fwd_few(const FwdP& a, int n_slots, int64_t r_begin, int6
 #pragma unroll
             for (int x = 0; x < 4; ++x) st.acc[x] *= c;
             st.m2 = mn;
+            const Spread<LPH> ps(pe);
             some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                const float pk = group_bcast<LPH, K>(pe);
+                const float pk = ps.template of<K>();
                 float v[4];
                 Row4<T>::unpack(raw[K], v);
 #pragma unroll
@@ -575,9 +571,10 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
                 const float du = u2 > 0.f ? de : a.slope * de;
                 ac.dt += du;
                 if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
+                const Spread<LPH> as(alpha);
                 some.template each<0>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
-                    const float ak = group_bcast<LPH, K>(alpha);
+                    const float ak = as.template of<K>();
                     float g[4];
                     Row4<T>::unpack(raw[K], g);
 #pragma unroll
@@ -729,10 +726,11 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
             constexpr int r = decltype(rr)::value;
             if (!(r == 0 ? some.any : some.most)) return;
             typename Row4<T>::Raw raw[B];
+            const Spread<LPH> is(d0.i[r]);
             some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
                 raw[K] = typename Row4<T>::Raw{};
-                const int i = bcast_i<LPH, K>(d0.i[r]);
+                const int i = is.template of_int<K>();
                 if (p.on && r * B + K < m0.cnt) raw[K] = load_raw<T, RAG>(Gp + (int64_t)i * a.ld + p.foff);
             });
             const bool valid = p.live && p.k_pos < B && r * B + p.k_pos < m0.cnt;
@@ -764,9 +762,10 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
             const float du = u2 > 0.f ? de : a.slope * de;
             dt += du;
             if (valid) unsafeAtomicAdd(ds + (int64_t)my_i * a.ldh + p.h, du);
+            const Spread<LPH> as(alpha);
             some.template each<r>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
-                const float ak = group_bcast<LPH, K>(alpha);
+                const float ak = as.template of<K>();
                 float g[4];
                 Row4<T>::unpack(raw[K], g);
 #pragma unroll
