@@ -899,10 +899,9 @@ int pow2_at_least(int x)
 //             generic kernel's row needs a whole wavefront and its heads a sum lane after lane (no power of
 //             two of lanes): 7 x 48 1704/1248, 2526/2388, 5 x 56 1797/1205, 2621/2325, 3 x 96 2416/1272, 3442/2378,
 //             3 x 120 2887/1418, 4003/2650; not 5 x 64 (1422/1148, 2147/2195) and 3 x 80 (1149/1219, 1849/2363).
-// In the forward pass the padded kernel also takes launches that leave up to 5/8 of the lanes idle:
-// it waits for memory there either way (4 x 32 fp32 on 7.4M edges: 603 us padded, 608 us with two
-// slots), while the backward pass gains from the slots (4 x 32: 1.9 and 6.5% of the whole step in
-// fp32 and bf16).
+// (Where two slots fit, the padded kernel reads as fast on large graphs, 4 x 32 fp32 on 7.4M edges 603 us and 608, but a long
+// row takes it twice as many round trips: 1 x 128 bf16, 2.2M edges, given scores 237 us and 176 with slots, 4 x 32 bf16 on 2000
+// rows of 88 33.9 and 26.0, block by block on 136 thousand edges 29 and 25.)
 enum class Gather { kGeneric, kExact, kPadded, kSlots };
 struct LaunchGeo {
     Gather kind;
@@ -936,9 +935,7 @@ LaunchGeo launch_geo(int dtype, int Hg, int D, int ldz, Pass pass)
     int slots = 1;
     while (slots * 2 * Hg <= groups) slots *= 2;
     if (D % 4 == 0) {
-        const int padded = std::max(8, lph);
         if (slots == 1 && lph >= 8) return LaunchGeo{Gather::kPadded, lph, 1, false};
-        if (pass != Pass::kBwd && Hg * padded <= 64 && Hg * (D / 4) * 8 >= 3 * 64) return LaunchGeo{Gather::kPadded, padded, 1, false};
     }
     return LaunchGeo{Gather::kSlots, lph, slots, D % 4 != 0};
 }
