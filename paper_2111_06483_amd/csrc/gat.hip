@@ -531,21 +531,67 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd(BwdArgs tabs, BwdSca
     }
 }
 
-// out[f] += sum_w partial[w][f]
-__global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict__ partial, int n_part,
-                                                         int F, float* __restrict__ out)
+// out(x) += sum_w partial[w ld + x] for the COLS values x of a workgroup: eight rows' loads a thread under way at a time,
+// then the wavefronts' sums, one barrier.
+template <int COLS, typename Out>
+__device__ inline void add_columns(const float* __restrict__ partial, int n_part, int64_t ld, Out out)
 {
-    __shared__ float red[256];
-    const int f = blockIdx.x;
-    float s = 0.f;
-    for (int w = threadIdx.x; w < n_part; w += 256) s += partial[(int64_t)w * F + f];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    __shared__ float red[kWavesPerWG][COLS];
+    float sum[COLS] = {};
+    float* const to = threadIdx.x < COLS ? out((int)threadIdx.x) : nullptr;
+    const float was = to ? *to : 0.f;
+    constexpr int kRows = 8;
+    for (int w0 = threadIdx.x; w0 < n_part; w0 += 256 * kRows) {
+        float v[kRows][COLS];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int w = w0 + 256 * r;
+#pragma unroll
+            for (int x = 0; x < COLS; ++x) v[r][x] = 0.f;
+            if (w >= n_part) continue;
+            if constexpr (COLS == 4)
+                load_f32<4>(partial + w * ld, v[r]);
+            else
+                v[r][0] = partial[w * ld];
+        }
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int x = 0; x < COLS; ++x) sum[x] += v[r][x];
     }
-    if (threadIdx.x == 0) out[f] += red[0];
+#pragma unroll
+    for (int x = 0; x < COLS; ++x) {
+        const float s = f256::group_all<kWave, f256::OpSum>(sum[x]);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave][x] = s;
+    }
+    __syncthreads();
+    if (!to) return;
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesPerWG; ++w) s += red[w][threadIdx.x];
+    *to = was + s;
+}
+
+// Columns a workgroup sums: a cache line of four wanted bytes a row is nothing while the rows are few (243 of them, 128
+// columns 3.8 us, by fours 2.6), and beyond that the chip wants the workgroups (2048 rows, 256 columns: 8.5 us by fours 9).
+constexpr int kFewPartials = 512;
+
+// out[f] += sum_w partial[w][f]
+template <int COLS>
+__global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict__ partial, int n_part, int F,
+                                                         float* __restrict__ out)
+{
+    const int f0 = blockIdx.x * COLS;
+    add_columns<COLS>(partial + f0, n_part, F, [&](int x) { return out + f0 + x; });
+}
+int reduce_partials(const float* partial, int n_part, int F, float* out, hipStream_t st)
+{
+    if (F % 4 == 0 && n_part <= kFewPartials)      // (rows of whole 16 bytes: the scratch is aligned)
+        k_reduce_partials<4><<<F / 4, 256, 0, st>>>(partial, n_part, F, out);
+    else
+        k_reduce_partials<1><<<F, 256, 0, st>>>(partial, n_part, F, out);
+    SAR_LAUNCH_CHECK();
+    return SAR_OK;
 }
 
 // ---------------------------------------------------------------- node-wise
@@ -833,14 +879,19 @@ __global__ __launch_bounds__(kGatherThreads) void k_bwd_end(const T* __restrict_
 #pragma unroll
     for (int x = 0; x < VEC; ++x) part[wave][lm.lane][x] = dar[x];
     __syncthreads();
-    if (wave == 0 && lm.slot == 0 && lm.on) {
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) {
-            float s = 0.f;
-            for (int w = 0; w < kWavesPerWG; ++w)
-                for (int sl = 0; sl < lm.n_slots; ++sl) s += part[w][sl * H * LPH + lm.lane][x];
-            if (lm.owns(x)) partial[(int64_t)blockIdx.x * (H * D) + lm.foff + x] = s;
+    // a thread per value of a node's lanes: a wavefront that summed its slots' values one after the other waited for LDS 128
+    // times (4 heads of 32 bf16 values on a thousand nodes: the kernel 9.8 us, now 3.9)
+    const int lanes = H * LPH;
+    for (int t = threadIdx.x; t < lanes * VEC; t += kGatherThreads) {
+        const int l = t / VEC, x = t % VEC, first = VEC * (l % LPH);
+        const int off = RAG ? max(0, min(first, D - VEC)) : first;      // as in NodeLanes
+        if (first >= D || off + x < first || off + x >= D) continue;
+        float s = 0.f;
+        for (int w = 0; w < kWavesPerWG; ++w) {
+#pragma unroll 4
+            for (int sl = 0; sl < lm.n_slots; ++sl) s += part[w][sl * lanes + l][x];
         }
+        partial[(int64_t)blockIdx.x * (H * D) + l / LPH * D + off + x] = s;
     }
 }
 
@@ -1340,22 +1391,16 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
 // da_l[h*D + off(k) + x] += sum_w partial[w][(h*LPH + k)*4 + x]: the padded and the slots kernels
 // leave their partial sums in lane order (256 per workgroup).  off(k) = 4k, or D - 4 for the last
 // lane of a ragged head; the values such a lane shares with the one before it are that one's.
+template <int COLS>
 __global__ __launch_bounds__(256) void k_reduce_partials_padded(const float* __restrict__ partial, int n_part,
                                                                 int lph, int H, int D, float* __restrict__ out)
 {
-    __shared__ float red[256];
-    const int slot = blockIdx.x, lane = slot >> 2, x = slot & 3;
-    const int h = lane / lph, k = lane % lph, off = min(4 * k, D - 4);
-    if (h >= H || 4 * k >= D || off + x < 4 * k) return;
-    float s = 0.f;
-    for (int w = threadIdx.x; w < n_part; w += 256) s += partial[(int64_t)w * 256 + slot];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[h * D + off + x] += red[0];
+    const int slot = blockIdx.x * COLS, lane = slot / 4, h = lane / lph, k = lane % lph, off = min(4 * k, D - 4);
+    if (h >= H || 4 * k >= D) return;
+    add_columns<COLS>(partial + slot, n_part, 256, [&](int c) -> float* {
+        const int x = slot % 4 + c;
+        return off + x < 4 * k ? nullptr : out + h * D + off + x;
+    });
 }
 
 // The sources without an edge in their block (the tail of the work list): their rows of dZ_q and
@@ -1467,9 +1512,7 @@ int launch_bwd_fast(const BwdArgs& tabs, const BwdScalars& a, const LaunchGeo& g
             case 32: SAR_TRY((launch_bwd_f256<T, 32, ALL>(tabs, a, &grid, st))); break;
             default: SAR_TRY((launch_bwd_f256<T, 64, ALL>(tabs, a, &grid, st))); break;
         }
-        k_reduce_partials<<<a.F, 256, 0, st>>>(a.partial, (int)grid, a.F, da_l);
-        SAR_LAUNCH_CHECK();
-        return SAR_OK;
+        return reduce_partials(a.partial, (int)grid, a.F, da_l, st);
     }
     if (geo.kind == Gather::kPadded) {
         switch (geo.lph) {
@@ -1497,7 +1540,10 @@ int launch_bwd_fast(const BwdArgs& tabs, const BwdScalars& a, const LaunchGeo& g
             default: return sar::fail(SAR_ERR_STATE, "no backward kernel for %d heads of %d values", a.H, a.D);
         }
     }
-    k_reduce_partials_padded<<<256, 256, 0, st>>>(a.partial, (int)grid, geo.lph, a.H, a.D, da_l);
+    if ((int)grid <= kFewPartials)
+        k_reduce_partials_padded<4><<<256 / 4, 256, 0, st>>>(a.partial, (int)grid, geo.lph, a.H, a.D, da_l);
+    else
+        k_reduce_partials_padded<1><<<256, 256, 0, st>>>(a.partial, (int)grid, geo.lph, a.H, a.D, da_l);
     SAR_LAUNCH_CHECK();
     return SAR_OK;
 }
@@ -1508,9 +1554,7 @@ int launch_bwd_generic(const BwdArgs& tabs, const BwdScalars& a, float* da_l, hi
     const unsigned grid = persistent_grid(a.n_rows, a.n_long);
     SAR_DISPATCH_G(T, a.F, (k_gat_bwd<T, kG, ALL><<<grid, kGatherThreads, 0, st>>>(tabs, a)));
     SAR_LAUNCH_CHECK();
-    k_reduce_partials<<<a.F, 256, 0, st>>>(a.partial, (int)grid, a.F, da_l);
-    SAR_LAUNCH_CHECK();
-    return SAR_OK;
+    return reduce_partials(a.partial, (int)grid, a.F, da_l, st);
 }
 
 // The generic backward kernel's row types: heads of 1 to 3 values, bf16 heads of more than 256.
@@ -2190,8 +2234,7 @@ int bwd_end_impl(const void* Zdst, const float* ds, const float* a_r, const void
                                           dZadd ? static_cast<const T*>(dZadd) + f0 : nullptr, dZadd_rank,
                                           dZdst ? static_cast<T*>(dZdst) + f0 : nullptr, partial, n_dst, Hg, D, H * D, H)));
         SAR_LAUNCH_CHECK();
-        k_reduce_partials<<<Fg, 256, 0, st>>>(partial, (int)grid, Fg, da_r + f0);
-        SAR_LAUNCH_CHECK();
+        SAR_TRY(reduce_partials(partial, (int)grid, Fg, da_r + f0, st));
     }
     return SAR_OK;
 }
