@@ -1610,14 +1610,20 @@ int ds_copies_for(int64_t n_dst, int H)
     const size_t bytes = (size_t)n_dst * H * sizeof(float);
     return bytes == 0 || bytes > 2 * kDsSmall ? 1 : bytes > kDsSmall ? 8 : 16;
 }
-// Whether a call of nnz edges, hub of them into its most frequent destination, waits for the line that
-// destination is on: its additions (as if the line's other destinations were as frequent) against the
-// two extra launches and against the time the call's rows take at 6 TB/s.
-bool ds_contended(int64_t hub, int64_t nnz, int H, int D, size_t fb)
+// Whether a call of nnz edges to n_dst destinations, hub of them to the most frequent one, waits for ds: the additions to the
+// line that destination is on, as if the line's other destinations were as frequent; or where the lines are few, those to every
+// line, some 16 ns each there (262 destinations of 290 edges, 4 heads: 2300 a line and launch, the wide kernel 45 us without
+// copies and 15 with).
+// Copies are two more launches, 5 us of a small ds and 12 of 2.5 MB.  Steps of 3700 layers over power-law and uniform
+// graphs (77 to 160 thousand destinations, 1 to 16 blocks, fourteen shapes): 11% longer than with the better of the two where
+// copies are never taken, 1.8% always, 1.1% by the first line drawn at 20 us alone, 0.5% by both; worst 3.1, 1.11, 1.8 and
+// 1.19 times.  Block by block, 712 layers: 2.8, 10.5, 1.1, 0.5%.
+bool ds_contended(int64_t hub, int64_t nnz, int64_t n_dst, int H, int D, size_t fb)
 {
     const double line_us = 0.004 * (double)hub * std::max(1, 32 / H);
     const double rows_us = (double)nnz * H * D * fb / 6e6;
-    return line_us > 20.0 && line_us > 0.15 * rows_us;
+    const double to_a_line = (double)nnz / std::max(1.0, (double)n_dst * H * sizeof(float) / 128.0);
+    return (line_us > 10.0 && line_us > 0.05 * rows_us) || (to_a_line > 800.0 && 0.016 * to_a_line > 0.3 * rows_us);
 }
 size_t ds_copy_bytes(int64_t n_dst, int H) { return ((size_t)n_dst * H * sizeof(float) + 255) / 256 * 256; }
 
@@ -2065,7 +2071,7 @@ extern "C" int sar_gat_bwd_block(const sar_blocks_t* b, int q, const void* Zq, c
     hipStream_t st = sar::as_stream(stream);
     DsTarget dst;
     const HeadGroups hg = head_groups(dtype, H, D, Pass::kBwd);
-    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(k.hub, k.nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
+    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(k.hub, k.nnz, b->n_dst, H, D, hg.fb), H, ds, work, work_bytes, st));
     for (int g = 0; g < hg.n; ++g) {
         const size_t h0 = (size_t)hg.first(g), f0 = h0 * D;
         BwdArgs tabs{};
@@ -2114,7 +2120,7 @@ extern "C" int sar_gat_bwd_all(const sar_blocks_t* b, const void* const* Zq, con
         nnz += b->blk[q].nnz;
         hub += b->blk[q].hub;
     }
-    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(hub, nnz, H, D, hg.fb), H, ds, work, work_bytes, st));
+    SAR_TRY(ds_begin(dst, b->n_dst, ds_contended(hub, nnz, b->n_dst, H, D, hg.fb), H, ds, work, work_bytes, st));
     int64_t n_src_all[SAR_MAX_BLOCKS];
     for (int q = 0; q < b->P; ++q) n_src_all[q] = b->blk[q].n_src;
 
