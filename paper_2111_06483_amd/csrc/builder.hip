@@ -152,17 +152,53 @@ public:
         }
         (void)hipFree(p);
     }
+    // A page of pinned host memory for what a call's kernels report to the host and what it sends them: through pageable
+    // memory every copy waits for the stream (15.2M edges: twelve copies, the build 1534 us and now 1431).  At most kHostPages idle ones.
+    static constexpr size_t kHostPage = 192 << 10;
+    static constexpr size_t kHostPages = 4;
+    int take_host(void** out)
+    {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            if (!host_.empty()) {
+                *out = host_.back();
+                host_.pop_back();
+                return SAR_OK;
+            }
+        }
+        SAR_HIP(hipHostMalloc(out, kHostPage, hipHostMallocPortable));
+        return SAR_OK;
+    }
+    void give_host(void* p)
+    {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            if (host_.size() < kHostPages) {
+                try {
+                    host_.push_back(p);
+                    return;
+                } catch (const std::bad_alloc&) {
+                }
+            }
+        }
+        (void)hipHostFree(p);
+    }
     void count_handle(int dev, int by)
     {
         std::lock_guard<std::mutex> lock(m_);
         auto& d = devices_[dev];
         d.handles += by;
-        if (d.handles <= 0) release(d);
+        if (d.handles > 0) return;
+        release(d);
+        for (auto& e : devices_)
+            if (e.second.handles > 0) return;
+        release_host();
     }
     void release_all()
     {
         std::lock_guard<std::mutex> lock(m_);
         for (auto& d : devices_) release(d.second);
+        release_host();
     }
 
 private:
@@ -177,8 +213,14 @@ private:
         d.idle.clear();
         d.bytes = 0;
     }
+    void release_host()
+    {
+        for (void* p : host_) (void)hipHostFree(p);
+        host_.clear();
+    }
     std::mutex m_;
     std::map<int, Device> devices_;
+    std::vector<void*> host_;
 };
 
 Pool& pool()
@@ -193,9 +235,17 @@ struct DeviceTemps {
     DeviceTemps(const DeviceTemps&) = delete;
     ~DeviceTemps()
     {
-        if (ptrs.empty()) return;
+        if (ptrs.empty() && !page) return;
         (void)hipStreamSynchronize(st);
         for (auto& p : ptrs) pool().give(dev, p.first, p.second);
+        if (page) pool().give_host(page);
+    }
+    // the call's page of pinned memory: what the device reports first, then `up` bytes to send
+    int host(void** out, size_t up = 0)
+    {
+        if (!page) SAR_TRY(pool().take_host(&page));
+        *out = static_cast<char*>(page) + up;
+        return SAR_OK;
     }
     template <typename T>
     int alloc(T** out, int64_t count)
@@ -210,6 +260,7 @@ struct DeviceTemps {
     }
     hipStream_t st;
     int dev;
+    void* page = nullptr;
     std::vector<std::pair<void*, size_t>> ptrs;
 };
 
@@ -1079,11 +1130,12 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_finish(const PairT* _
     }
 }
 
-// out[k] = in[k * step] for k in [0, n]
-__global__ __launch_bounds__(kThreads) void k_every(const int32_t* __restrict__ in, int64_t step, int n,
-                                                    int32_t* __restrict__ out)
+// A call's report to the host: flags[0..3] (or zeros), then in[k * step] for k in [0, n).
+__global__ __launch_bounds__(kThreads) void k_report(const int32_t* __restrict__ in, int64_t step, int n,
+                                                     const int* __restrict__ flags, int32_t* __restrict__ out)
 {
-    for (int k = threadIdx.x; k <= n; k += kThreads) out[k] = in[k * step];
+    if (threadIdx.x < 4) out[threadIdx.x] = flags ? flags[threadIdx.x] : 0;
+    for (int k = threadIdx.x; k < n; k += kThreads) out[4 + k] = in[k * step];
 }
 
 // indptr of block q out of the offsets of all blocks' rows
@@ -1546,14 +1598,31 @@ int allow_lds(Fn fn, size_t bytes)
     return SAR_OK;
 }
 
-// host[k] = in[k * step] for k in [0, P]; the stream has to be waited for before they are read.
-int read_every(const int32_t* in, int64_t step, int P, int32_t* host, DeviceTemps& tmp, hipStream_t st)
+// Where things stand in a call's pinned page: the newest report, the blocks, the lists' cursors.
+constexpr size_t kReportBytes = (4 + (2 * SAR_MAX_PARTS + 2) * sar::kNumClasses + 15) / 16 * 16 * sizeof(int32_t);
+constexpr size_t kBlkBytes = SAR_MAX_PARTS * sizeof(BlkDev);
+static_assert(2 * kReportBytes + kBlkBytes <= Pool::kHostPage && kReportBytes % alignof(BlkDev) == 0, "");
+
+// Has the stream report flags[0..3] and in[k * step], k < n; without `wait` the stream has to be waited for before `*report` is read.
+int send_report(const int32_t* in, int64_t step, int n, const int* flags, bool wait, const int32_t** report,
+                DeviceTemps& tmp, hipStream_t st)
 {
-    int32_t* dev = nullptr;
-    SAR_TRY(tmp.alloc(&dev, P + 1));
-    k_every<<<1, kThreads, 0, st>>>(in, step, P, dev);
+    void* page = nullptr;
+    SAR_TRY(tmp.host(&page));
+    k_report<<<1, kThreads, 0, st>>>(in, step, n, flags, static_cast<int32_t*>(page));
     SAR_LAUNCH_CHECK();
-    SAR_HIP(hipMemcpyAsync(host, dev, (P + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    if (wait) SAR_HIP(hipStreamSynchronize(st));
+    *report = static_cast<const int32_t*>(page);
+    return SAR_OK;
+}
+
+int check_flags(int err)
+{
+    if (err & 1) return sar::fail(SAR_ERR_INVALID_ARG, "part[] holds a value outside [0,P)");
+    if (err & 2) return sar::fail(SAR_ERR_INVALID_ARG, "edge list holds a node id outside [0,N)");
+    if (err & 4) return sar::fail(SAR_ERR_INVALID_ARG, "indices[] holds a column outside [0,n_src)");
+    if (err & 8) return sar::fail(SAR_ERR_INVALID_ARG, "indptr[] is not non-decreasing");
+    if (err & 16) return sar::fail(SAR_ERR_INVALID_ARG, "dst_ids[] holds a row outside [0,n_dst)");
     return SAR_OK;
 }
 
@@ -1647,7 +1716,9 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     }
 
     const BucketPlan plan = plan_buckets(std::min(kKeysPerPass, std::max<int64_t>(n_src_total, 1)), nnz_total);
-    std::vector<BlkDev> blk(P);
+    void* page = nullptr;
+    SAR_TRY(tmp.host(&page, kReportBytes));
+    BlkDev* const blk = static_cast<BlkDev*>(page);
     int64_t coff = 0, nnz0 = 0, tiles = 0;
     for (int q = 0; q < P; ++q) {
         Block& b = h->blk[q];
@@ -1665,7 +1736,7 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     }
     BlkDev* blk_d = nullptr;
     SAR_TRY(tmp.alloc(&blk_d, P));
-    SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+    SAR_HIP(hipMemcpyAsync(blk_d, blk, P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
 
     // total in-degree |N(i)|, and its class histograms: the blocks' rows, their sources, all rows
     int* hist_d = nullptr;
@@ -1751,9 +1822,12 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     }
 
     // ---- launch lists, longest class first
-    std::vector<int> hist(n_hist), cursors(n_hist, 0);
-    SAR_HIP(hipMemcpyAsync(hist.data(), hist_d, n_hist * sizeof(int), hipMemcpyDeviceToHost, st));
-    SAR_HIP(hipStreamSynchronize(st));
+    const int32_t* report = nullptr;
+    SAR_TRY(send_report(hist_d, 1, n_hist, nullptr, true, &report, tmp, st));
+    const std::vector<int> hist(report + 4, report + 4 + n_hist);
+    SAR_TRY(tmp.host(&page, kReportBytes + kBlkBytes));
+    int* const cursors = static_cast<int*>(page);
+    std::fill(cursors, cursors + n_hist, 0);
     int64_t rows_at = 0, t_rows_at = 0;
     int all_hist[sar::kNumClasses] = {0};
     for (int q = 0; q < P; ++q) {
@@ -1802,8 +1876,8 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
             if (all_hist[c]) h->ft_longest = ((int64_t)1 << c) - 1;
         memcpy(&cursors[(2 * P + 1) * C], L.start, sizeof(L.start));
     }
-    SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
-    SAR_HIP(hipMemcpyAsync(hist_d, cursors.data(), n_hist * sizeof(int), hipMemcpyHostToDevice, st));
+    SAR_HIP(hipMemcpyAsync(blk_d, blk, P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
+    SAR_HIP(hipMemcpyAsync(hist_d, cursors, n_hist * sizeof(int), hipMemcpyHostToDevice, st));
     k_class_place<<<g_place_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, rows_hist, nullptr);
     SAR_LAUNCH_CHECK();
     if (fused) {
@@ -1811,7 +1885,6 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
                                                   reinterpret_cast<uint32_t*>(h->f_rows));
         SAR_LAUNCH_CHECK();
     }
-    int32_t placed = 0;
     if (transpose) {
         k_class_place<<<g_place_src, kThreads, 0, st>>>(in, Lists::kSources, 0, src_hist, nullptr);
         SAR_LAUNCH_CHECK();
@@ -1842,7 +1915,7 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
                                                               s_cnt, nullptr, 0, nullptr, nullptr, nullptr);
             SAR_LAUNCH_CHECK();
             SAR_TRY(exclusive_scan(s_cnt, s_off, n_dst + 1, st, tmp));
-            SAR_HIP(hipMemcpyAsync(&placed, s_off + n_dst, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+            SAR_TRY(send_report(s_off + n_dst, 1, 1, nullptr, false, &report, tmp, st));
             k_single_list<true><<<g_list, kThreads, 0, st>>>(stabs, h->f_indptr, h->f_indices, n_dst, h->tag_shift,
                                                              nullptr, s_off, n_single, h->s_dst, h->s_src, h->s_row);
             SAR_LAUNCH_CHECK();
@@ -1850,22 +1923,9 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         }
     }
     SAR_HIP(hipStreamSynchronize(st));
-    if (h->n_single > 0 && placed != h->n_single)
-        return sar::fail(SAR_ERR_STATE, "the all-blocks index lists %d sources of one edge, the transposes %lld", placed,
+    if (h->n_single > 0 && report[4] != h->n_single)
+        return sar::fail(SAR_ERR_STATE, "the all-blocks index lists %d sources of one edge, the transposes %lld", report[4],
                          (long long)h->n_single);
-    return SAR_OK;
-}
-
-int check_err_flag(int* err_d, hipStream_t st)
-{
-    int err = 0;
-    SAR_HIP(hipMemcpyAsync(&err, err_d, sizeof(int), hipMemcpyDeviceToHost, st));
-    SAR_HIP(hipStreamSynchronize(st));
-    if (err & 1) return sar::fail(SAR_ERR_INVALID_ARG, "part[] holds a value outside [0,P)");
-    if (err & 2) return sar::fail(SAR_ERR_INVALID_ARG, "edge list holds a node id outside [0,N)");
-    if (err & 4) return sar::fail(SAR_ERR_INVALID_ARG, "indices[] holds a column outside [0,n_src)");
-    if (err & 8) return sar::fail(SAR_ERR_INVALID_ARG, "indptr[] is not non-decreasing");
-    if (err & 16) return sar::fail(SAR_ERR_INVALID_ARG, "dst_ids[] holds a row outside [0,n_dst)");
     return SAR_OK;
 }
 
@@ -1874,7 +1934,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
 {
     int* err_d = nullptr;
     SAR_TRY(tmp.alloc(&err_d, 4));
-    unsigned long long* kept_d = reinterpret_cast<unsigned long long*>(err_d + 2);
+    unsigned long long* kept_d = reinterpret_cast<unsigned long long*>(err_d + 2);     // reported with the flags
     SAR_HIP(hipMemsetAsync(err_d, 0, 4 * sizeof(int), st));
 
     // 1. rank of every node inside its partition
@@ -1889,8 +1949,10 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
     SAR_LAUNCH_CHECK();
     SAR_TRY(exclusive_scan(tile_counts, tile_counts, (int64_t)P * n_tiles + 1, st, tmp));
     std::vector<int32_t> part_first(P + 1);
-    SAR_TRY(read_every(tile_counts, n_tiles, P, part_first.data(), tmp, st));
-    SAR_TRY(check_err_flag(err_d, st));
+    const int32_t* report = nullptr;
+    SAR_TRY(send_report(tile_counts, n_tiles, P + 1, err_d, true, &report, tmp, st));
+    SAR_TRY(check_flags(report[0]));
+    std::copy(report + 4, report + 5 + P, part_first.begin());
     const int64_t n_dst = part_first[p + 1] - part_first[p];
     h->n_dst = n_dst;
     h->blk.resize(P);
@@ -1930,8 +1992,9 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
             SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
             if (first) {
                 unsigned long long kept = 0;
-                SAR_HIP(hipMemcpyAsync(&kept, kept_d, sizeof(kept), hipMemcpyDeviceToHost, st));
-                SAR_TRY(check_err_flag(err_d, st));
+                SAR_TRY(send_report(nullptr, 0, 0, err_d, true, &report, tmp, st));
+                SAR_TRY(check_flags(report[0]));
+                memcpy(&kept, report + 2, sizeof(kept));
                 if (kept >= (1ull << 31))
                     return sar::fail(SAR_ERR_UNSUPPORTED,
                                      "worker %d's share holds %llu in-edges; a handle holds fewer than 2^31", p, kept);
@@ -1972,8 +2035,8 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
     SAR_LAUNCH_CHECK();
     std::vector<int32_t> block_first(P + 1, 0);
     if (n_dst > 0) {
-        SAR_TRY(read_every(row_off, n_dst, P, block_first.data(), tmp, st));
-        SAR_HIP(hipStreamSynchronize(st));
+        SAR_TRY(send_report(row_off, n_dst, P + 1, nullptr, true, &report, tmp, st));
+        std::copy(report + 4, report + 5 + P, block_first.begin());
     }
     for (int q = 0; q < P; ++q) {
         h->blk[q].nnz = block_first[q + 1] - block_first[q];
@@ -2139,10 +2202,10 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
         int* err_d = nullptr;
         int32_t* ends_d = nullptr;
         BlkDev* blk_d = nullptr;
-        SAR_TRY(tmp.alloc(&err_d, 1));
+        SAR_TRY(tmp.alloc(&err_d, 4));
         SAR_TRY(tmp.alloc(&ends_d, 2 * P));
         SAR_TRY(tmp.alloc(&blk_d, P));
-        SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
+        SAR_HIP(hipMemsetAsync(err_d, 0, 4 * sizeof(int), st));
         std::vector<BlkDev> blk(P);
         std::vector<int32_t> ends(2 * P);
         for (int q = 0; q < P; ++q) {
@@ -2168,7 +2231,9 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
         SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
         k_check_columns<<<dim3(grid_for(most, kThreads, std::max(1, 4096 / P)), P), kThreads, 0, st>>>(blk_d, n_dst, err_d);
         SAR_LAUNCH_CHECK();
-        SAR_TRY(check_err_flag(err_d, st));
+        const int32_t* report = nullptr;
+        SAR_TRY(send_report(nullptr, 0, 0, err_d, true, &report, tmp, st));
+        SAR_TRY(check_flags(report[0]));
         return derive(h, tmp, scratch, st);
     };
     int rc = guarded(body);
@@ -2266,7 +2331,7 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
         int* err_d = nullptr;
         BlkDev* blk_d = nullptr;
         int32_t *row_off = nullptr, *indptr_all = nullptr, *indices_all = nullptr;
-        SAR_TRY(tmp.alloc(&err_d, 1));
+        SAR_TRY(tmp.alloc(&err_d, 4));
         SAR_TRY(tmp.alloc(&blk_d, P));
         SAR_TRY(tmp.alloc(&row_off, n_rows_all + 1));
         SAR_TRY(own(h, &indptr_all, (int64_t)P * (n_sub + 1)));
@@ -2278,7 +2343,7 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
             blk[q] = BlkDev{from.indptr, from.indices, from.n_src, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
         }
         SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
-        SAR_HIP(hipMemsetAsync(err_d, 0, sizeof(int), st));
+        SAR_HIP(hipMemsetAsync(err_d, 0, 4 * sizeof(int), st));
         SAR_HIP(hipMemsetAsync(row_off + n_rows_all, 0, sizeof(int32_t), st));
         std::vector<int32_t> block_first(P + 1, 0);
         if (n_sub > 0) {
@@ -2286,9 +2351,11 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
                 blk_d, dst_ids, n_sub, b->n_dst, row_off, err_d);
             SAR_LAUNCH_CHECK();
             SAR_TRY(exclusive_scan(row_off, row_off, n_rows_all + 1, st, tmp));
-            SAR_TRY(read_every(row_off, n_sub, P, block_first.data(), tmp, st));
         }
-        SAR_TRY(check_err_flag(err_d, st));      // synchronises; ids are in range beyond this point
+        const int32_t* report = nullptr;
+        SAR_TRY(send_report(row_off, n_sub, n_sub > 0 ? P + 1 : 0, err_d, true, &report, tmp, st));
+        SAR_TRY(check_flags(report[0]));         // ids are in range beyond this point
+        if (n_sub > 0) std::copy(report + 4, report + 5 + P, block_first.begin());
         // the offsets are 32-bit: repeated ids may list more edges than the handle they come from
         for (int q = 0; q < P; ++q)
             if (block_first[q + 1] < block_first[q])
