@@ -2,11 +2,9 @@
 // G_{p,q} (Sec. 3.2 of the paper), plus the derived indexes the aggregation
 // kernels launch from: the source-major transpose of every block, degree-class
 // ordered row lists, the sorted touched-source list and the all-blocks row
-// index.  Integer work only.  Every array whose content is part of the
-// contract (indptr, indices, t_indptr, t_indices, deg, touched) is bit-exact
-// and independent of scheduling: rows are filled through atomic cursors and
-// then sorted.  Only the order inside a degree class of the launch lists is
-// left to the scheduler.
+// index.  Integer work only.  Every array is bit-exact and independent of
+// scheduling: rows are filled through atomic cursors and then sorted, and the
+// launch lists hold the rows of a degree class in their own order.
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
@@ -1213,12 +1211,30 @@ __global__ __launch_bounds__(kThreads) void k_sort_buckets(const int32_t* __rest
 
 __device__ inline int degree_class(int len) { return len <= 0 ? 0 : 32 - __clz(len); }
 
-// hist[y][class] over the rows of offset array y: the blocks' own, their transposes', or one given array.
+// The launch lists: the blocks' own rows, their sources, the rows of all blocks, the sources of all blocks.
 enum class Lists { kRows, kSources, kAllRows, kAllSources };
+constexpr int kPlacePer = 8, kPlaceRows = kThreads * kPlacePer;      // rows of a tile
+// Rows of a tile in every class, [class][tile] for each list one after another (the sources of all blocks: [class][block][tile]),
+// and, scanned, how many of the list's class stand before them.
 struct ListIn {
     const BlkDev* blk;
     const int32_t* off;      // kAllRows: the all-blocks row offsets
     int64_t n_dst;
+    int P;
+    int64_t t_rows, t_src;   // tiles of a block's rows and sources
+    bool fused;
+    __host__ __device__ inline int64_t first_src() const { return P * sar::kNumClasses * t_rows; }
+    __host__ __device__ inline int64_t first_all_rows() const { return first_src() + P * sar::kNumClasses * t_src; }
+    __host__ __device__ inline int64_t first_all_src() const { return first_all_rows() + (fused ? sar::kNumClasses * t_rows : 0); }
+    __host__ __device__ inline int64_t size() const { return first_all_src() + P * sar::kNumClasses * t_src; }
+    // where the counts of class c of list l (of block q) start, and how many there are
+    __host__ __device__ inline int64_t counts(Lists l, int q, int c, int64_t& tiles) const
+    {
+        tiles = l == Lists::kAllSources ? P * t_src : l == Lists::kSources ? t_src : t_rows;
+        const int64_t first = l == Lists::kRows ? 0 : l == Lists::kSources ? first_src() : l == Lists::kAllRows ? first_all_rows() : first_all_src();
+        const bool by_block = l == Lists::kRows || l == Lists::kSources;
+        return first + ((by_block ? (int64_t)q * sar::kNumClasses : 0) + c) * tiles;
+    }
     __device__ inline const int32_t* offsets(Lists l, int y, int64_t& n) const
     {
         const bool sources = l == Lists::kSources || l == Lists::kAllSources;
@@ -1227,81 +1243,106 @@ struct ListIn {
     }
 };
 
-__global__ __launch_bounds__(kThreads) void k_class_hist(ListIn in, Lists l, int* __restrict__ hist_all)
+// The classes of a tile's rows: class c[j] and place at[j] among the tile's rows of the class, in the rows' order, of row
+// tile * kPlaceRows + j * kThreads + threadIdx.x (-1: no row); cnt[class] = rows of the class in the tile.
+__device__ inline void tile_classes(const int32_t* off, int64_t n, int64_t tile, int (&c)[kPlacePer], int (&at)[kPlacePer],
+                                    int* cnt)
 {
-    __shared__ int h[sar::kNumClasses];
-    if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
+    constexpr int kChunks = kPlacePer * kThreads / 64;
+    __shared__ int chunk[kChunks][sar::kNumClasses];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int k = threadIdx.x; k < kChunks * sar::kNumClasses; k += kThreads) (&chunk[0][0])[k] = 0;
+#pragma unroll
+    for (int j = 0; j < kPlacePer; ++j) {
+        const int64_t r = tile * kPlaceRows + j * kThreads + threadIdx.x;
+        c[j] = r < n ? degree_class(off[r + 1] - off[r]) : -1;
+    }
     __syncthreads();
-    int64_t n;
-    const int32_t* off = in.offsets(l, blockIdx.y, n);
-    // most rows of a block fall into a few classes: the lanes of a class count themselves together
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t r0 = (int64_t)blockIdx.x * kThreads; r0 < n; r0 += stride) {
-        const int64_t r = r0 + threadIdx.x;
-        const int c = r < n ? degree_class(off[r + 1] - off[r]) : -1;
-        unsigned long long todo = __ballot(c >= 0);
+#pragma unroll
+    for (int j = 0; j < kPlacePer; ++j) {
+        at[j] = 0;
+        unsigned long long todo = __ballot(c[j] >= 0);
         while (todo) {
-            const int first = __ffsll((long long)todo) - 1;
-            const unsigned long long same = __ballot(c == __shfl(c, first));
-            if ((int)(threadIdx.x & 63) == first) atomicAdd(&h[c], __popcll(same));
+            const int first = __ffsll((long long)todo) - 1, of = __shfl(c[j], first);
+            const unsigned long long same = __ballot(c[j] == of);
+            if (c[j] == of) at[j] = __popcll(same & ((1ull << lane) - 1ull));
+            if (lane == first) chunk[j * (kThreads / 64) + wave][of] = __popcll(same);
             todo &= ~same;
         }
     }
     __syncthreads();
-    int* hist = hist_all + blockIdx.y * sar::kNumClasses;
-    if (threadIdx.x < sar::kNumClasses && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x < sar::kNumClasses) {
+        int run = 0;
+#pragma unroll 8
+        for (int k = 0; k < kChunks; ++k) {
+            const int x = chunk[k][threadIdx.x];
+            chunk[k][threadIdx.x] = run;
+            run += x;
+        }
+        cnt[threadIdx.x] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPlacePer; ++j)
+        if (c[j] >= 0) at[j] += chunk[j * (kThreads / 64) + wave][c[j]];
 }
 
-// cursor[c] starts at the first slot of class c; value written = r | tag.
-// Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.  A workgroup takes 2048 rows to
-// one request to the cursors, which share a cache line and are served one request after the other (2.4 million rows: 256 rows
-// to a request 50 us, 2048 15).
-constexpr int kPlacePer = 8, kPlaceRows = kThreads * kPlacePer;
-__global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, int tag_shift, int* __restrict__ cursors,
-                                                          uint32_t* __restrict__ out_all)
+__global__ __launch_bounds__(kThreads) void k_class_count(ListIn in, Lists l, int32_t* __restrict__ counts)
 {
-    __shared__ int h[sar::kNumClasses];
-    __shared__ int base[sar::kNumClasses];
-    int64_t n;
+    __shared__ int cnt[sar::kNumClasses];
+    int64_t n, tiles;
     const int32_t* off = in.offsets(l, blockIdx.y, n);
-    int* cursor = cursors + (l == Lists::kRows || l == Lists::kSources ? blockIdx.y * sar::kNumClasses : 0);
+    int c[kPlacePer], at[kPlacePer];
+    tile_classes(off, n, blockIdx.x, c, at, cnt);
+    __syncthreads();
+    if (threadIdx.x < sar::kNumClasses) {
+        const int64_t of = in.counts(l, blockIdx.y, threadIdx.x, tiles);
+        counts[of + blockIdx.x] = cnt[threadIdx.x];
+        if (l == Lists::kSources) counts[in.counts(Lists::kAllSources, 0, threadIdx.x, tiles) + blockIdx.y * in.t_src + blockIdx.x] = cnt[threadIdx.x];
+    }
+    if (l == Lists::kRows && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) counts[in.size()] = 0;
+}
+
+// hist[list][class] out of the scanned counts (differences of 32-bit sums): the blocks' rows, their sources, all rows, all sources
+__global__ __launch_bounds__(kThreads) void k_class_totals(ListIn in, bool sources, const int32_t* __restrict__ counts,
+                                                           int32_t* __restrict__ hist)
+{
+    for (int k = threadIdx.x; k < (2 * in.P + 2) * sar::kNumClasses; k += kThreads) {
+        const int y = k / sar::kNumClasses, c = k % sar::kNumClasses;
+        const Lists l = y < in.P ? Lists::kRows : y < 2 * in.P ? Lists::kSources : y == 2 * in.P ? Lists::kAllRows : Lists::kAllSources;
+        const bool there = l == Lists::kRows || (l == Lists::kAllRows ? in.fused : sources);
+        int64_t tiles;
+        const int64_t of = in.counts(l, y % in.P, c, tiles);
+        hist[k] = there ? (int32_t)((uint32_t)counts[of + tiles] - (uint32_t)counts[of]) : 0;
+    }
+}
+
+// start[class] is the first place of the class in the list; value written = r | tag.  Rows stand by class, in a class in their
+// own order: the same lists from every build.  Where ids follow degrees the longest rows stand in front; the kernels deal the
+// rows after the shared ones from behind (1.5 M edges, rows of up to 10 thousand, forward pass: 219 us; dealt from the front 287,
+// and 267 with the rows in the order in which workgroups came to take places for 256 at a time).  Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.
+__global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, int tag_shift, const int* __restrict__ starts,
+                                                          const int32_t* __restrict__ counts, uint32_t* __restrict__ out_all)
+{
+    __shared__ int cnt[sar::kNumClasses];
+    __shared__ int base[sar::kNumClasses];
+    int64_t n, tiles;
+    const int32_t* off = in.offsets(l, blockIdx.y, n);
+    const int* start = starts + (l == Lists::kRows || l == Lists::kSources ? blockIdx.y * sar::kNumClasses : 0);
     uint32_t* out = l == Lists::kRows ? in.blk[blockIdx.y].rows : l == Lists::kSources ? in.blk[blockIdx.y].t_rows : out_all;
     const uint32_t tag = l == Lists::kAllSources ? (uint32_t)blockIdx.y << tag_shift : 0u;
-    const int lane = threadIdx.x & 63;
-    const int64_t stride = (int64_t)gridDim.x * kPlaceRows;
-    for (int64_t r0 = (int64_t)blockIdx.x * kPlaceRows; r0 < n; r0 += stride) {
-        __syncthreads();
-        if (threadIdx.x < sar::kNumClasses) h[threadIdx.x] = 0;
-        __syncthreads();
-        int c[kPlacePer], local[kPlacePer];
-#pragma unroll
-        for (int j = 0; j < kPlacePer; ++j) {
-            const int64_t r = r0 + j * kThreads + threadIdx.x;
-            c[j] = r < n ? degree_class(off[r + 1] - off[r]) : -1;
-            if (c[j] == 0 && l == Lists::kRows) c[j] = -1;
-        }
-#pragma unroll
-        for (int j = 0; j < kPlacePer; ++j) {
-            local[j] = 0;
-            unsigned long long todo = __ballot(c[j] >= 0);
-            while (todo) {
-                const int first = __ffsll((long long)todo) - 1;
-                const unsigned long long same = __ballot(c[j] == __shfl(c[j], first));
-                int start = 0;
-                if (lane == first) start = atomicAdd(&h[c[j]], __popcll(same));
-                start = __shfl(start, first);
-                if ((same >> lane) & 1) local[j] = start + __popcll(same & ((1ull << lane) - 1ull));
-                todo &= ~same;
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < sar::kNumClasses && h[threadIdx.x])
-            base[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], h[threadIdx.x]);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kPlacePer; ++j)
-            if (c[j] >= 0) out[base[c[j]] + local[j]] = (uint32_t)(r0 + j * kThreads + threadIdx.x) | tag;
+    int c[kPlacePer], at[kPlacePer];
+    tile_classes(off, n, blockIdx.x, c, at, cnt);
+    if (threadIdx.x < sar::kNumClasses) {
+        const int64_t of = in.counts(l, blockIdx.y, threadIdx.x, tiles);
+        const int64_t tile = l == Lists::kAllSources ? blockIdx.y * in.t_src + blockIdx.x : blockIdx.x;
+        base[threadIdx.x] = start[threadIdx.x] + (int32_t)((uint32_t)counts[of + tile] - (uint32_t)counts[of]);
     }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPlacePer; ++j)
+        if (c[j] > 0 || (c[j] == 0 && l != Lists::kRows))
+            out[base[c[j]] + at[j]] = (uint32_t)((int64_t)blockIdx.x * kPlaceRows + j * kThreads + threadIdx.x) | tag;
 }
 
 struct ClassLayout {
@@ -1451,9 +1492,8 @@ __global__ __launch_bounds__(kThreads) void k_source_ranks(const BlkDev* __restr
 // ------------------------------------------------- all-blocks (fused) index
 
 __global__ __launch_bounds__(kThreads) void k_total_degree(const BlkDev* __restrict__ blk, int P, int64_t n_dst,
-                                                           int32_t* __restrict__ deg, int* __restrict__ hist, int n_hist)
+                                                           int32_t* __restrict__ deg)
 {
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_hist; i += (int64_t)gridDim.x * kThreads) hist[i] = 0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i <= n_dst;
          i += (int64_t)gridDim.x * kThreads) {
         int d = 0;
@@ -1738,20 +1778,24 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     SAR_TRY(tmp.alloc(&blk_d, P));
     SAR_HIP(hipMemcpyAsync(blk_d, blk, P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
 
-    // total in-degree |N(i)|, and its class histograms: the blocks' rows, their sources, all rows
-    int* hist_d = nullptr;
+    // total in-degree |N(i)|, and the tiles' rows by class
     const int C = sar::kNumClasses, n_hist = (2 * P + 2) * C;
-    SAR_TRY(tmp.alloc(&hist_d, n_hist));
-    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg, hist_d, n_hist);
+    int *starts_d = nullptr, *class_counts = nullptr;
+    ListIn in{blk_d, h->f_indptr, n_dst, P, (n_dst + kPlaceRows - 1) / kPlaceRows,
+              transpose ? (n_src_max + kPlaceRows - 1) / kPlaceRows : 0, fused};
+    SAR_TRY(tmp.alloc(&starts_d, n_hist));
+    SAR_TRY(tmp.alloc(&class_counts, in.size() + 1));
+    k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg);
     SAR_LAUNCH_CHECK();
-    int *rows_hist = hist_d, *src_hist = hist_d + P * C, *all_rows_hist = hist_d + 2 * P * C;
-    ListIn in{blk_d, h->f_indptr, n_dst};
-    const dim3 g_rows(grid_for(n_dst, kThreads, std::max(1, 4096 / P)), P), g_all(grid_for(n_dst, kThreads, 4096), 1);
+    const dim3 g_rows((unsigned)std::max<int64_t>(1, in.t_rows), P), g_all(g_rows.x, 1), g_tiles((unsigned)std::max<int64_t>(1, in.t_src), P);
     const dim3 g_src(grid_for(n_src_max + 1, kThreads, std::max(1, 4096 / P)), P);
-    const dim3 g_place_rows(grid_for(n_dst, kPlaceRows), P), g_place_all(grid_for(n_dst, kPlaceRows), 1);
-    const dim3 g_place_src(grid_for(n_src_max, kPlaceRows), P);
-    k_class_hist<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, rows_hist);
-    SAR_LAUNCH_CHECK();
+    const bool lists = n_dst > 0, src_lists = transpose && n_src_max > 0;
+    if (lists) {
+        k_class_count<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, class_counts);
+        SAR_LAUNCH_CHECK();
+    } else {
+        SAR_HIP(hipMemsetAsync(class_counts + in.size(), 0, sizeof(int32_t), st));
+    }
 
     // ---- all-blocks destination-major index
     if (fused) {
@@ -1760,8 +1804,10 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         k_fused_copy<<<grid_for((n_dst + rows - 1) / rows * 64), kThreads, 0, st>>>(blk_d, P, rows, n_dst, h->f_indptr,
                                                                                     h->tag_shift, h->f_indices);
         SAR_LAUNCH_CHECK();
-        k_class_hist<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, all_rows_hist);
-        SAR_LAUNCH_CHECK();
+        if (lists) {
+            k_class_count<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, class_counts);
+            SAR_LAUNCH_CHECK();
+        }
     }
 
     // ---- source-major transpose of every block
@@ -1814,17 +1860,23 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         SAR_TRY(tmp.alloc(&pos, n_src_total + 1));
         k_source_offsets<<<g_src, kThreads, 0, st>>>(blk_d, col_off, pos);
         SAR_LAUNCH_CHECK();
-        k_class_hist<<<g_src, kThreads, 0, st>>>(in, Lists::kSources, src_hist);
-        SAR_LAUNCH_CHECK();
+        if (src_lists) {
+            k_class_count<<<g_tiles, kThreads, 0, st>>>(in, Lists::kSources, class_counts);
+            SAR_LAUNCH_CHECK();
+        }
         SAR_TRY(exclusive_scan(pos, pos, n_src_total + 1, st, tmp));
         k_source_ranks<<<g_src, kThreads, 0, st>>>(blk_d, pos, touched_all);
         SAR_LAUNCH_CHECK();
     }
 
     // ---- launch lists, longest class first
-    const int32_t* report = nullptr;
-    SAR_TRY(send_report(hist_d, 1, n_hist, nullptr, true, &report, tmp, st));
-    const std::vector<int> hist(report + 4, report + 4 + n_hist);
+    SAR_TRY(exclusive_scan(class_counts, class_counts, in.size() + 1, st, tmp));
+    SAR_TRY(tmp.host(&page));
+    const int32_t* report = static_cast<const int32_t*>(page);
+    k_class_totals<<<1, kThreads, 0, st>>>(in, transpose, class_counts, static_cast<int32_t*>(page));
+    SAR_LAUNCH_CHECK();
+    SAR_HIP(hipStreamSynchronize(st));
+    const std::vector<int> hist(report, report + n_hist);
     SAR_TRY(tmp.host(&page, kReportBytes + kBlkBytes));
     int* const cursors = static_cast<int*>(page);
     std::fill(cursors, cursors + n_hist, 0);
@@ -1877,19 +1929,24 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
         memcpy(&cursors[(2 * P + 1) * C], L.start, sizeof(L.start));
     }
     SAR_HIP(hipMemcpyAsync(blk_d, blk, P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
-    SAR_HIP(hipMemcpyAsync(hist_d, cursors, n_hist * sizeof(int), hipMemcpyHostToDevice, st));
-    k_class_place<<<g_place_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, rows_hist, nullptr);
-    SAR_LAUNCH_CHECK();
-    if (fused) {
-        k_class_place<<<g_place_all, kThreads, 0, st>>>(in, Lists::kAllRows, 0, all_rows_hist,
+    SAR_HIP(hipMemcpyAsync(starts_d, cursors, n_hist * sizeof(int), hipMemcpyHostToDevice, st));
+    if (lists) {
+        k_class_place<<<g_rows, kThreads, 0, st>>>(in, Lists::kRows, 0, starts_d, class_counts, nullptr);
+        SAR_LAUNCH_CHECK();
+    }
+    if (fused && lists) {
+        k_class_place<<<g_all, kThreads, 0, st>>>(in, Lists::kAllRows, 0, starts_d + 2 * P * C, class_counts,
                                                   reinterpret_cast<uint32_t*>(h->f_rows));
         SAR_LAUNCH_CHECK();
     }
     if (transpose) {
-        k_class_place<<<g_place_src, kThreads, 0, st>>>(in, Lists::kSources, 0, src_hist, nullptr);
-        SAR_LAUNCH_CHECK();
-        k_class_place<<<g_place_src, kThreads, 0, st>>>(in, Lists::kAllSources, h->tag_shift, hist_d + (2 * P + 1) * C, h->ft_rows);
-        SAR_LAUNCH_CHECK();
+        if (src_lists) {
+            k_class_place<<<g_tiles, kThreads, 0, st>>>(in, Lists::kSources, 0, starts_d + P * C, class_counts, nullptr);
+            SAR_LAUNCH_CHECK();
+            k_class_place<<<g_tiles, kThreads, 0, st>>>(in, Lists::kAllSources, h->tag_shift, starts_d + (2 * P + 1) * C,
+                                                        class_counts, h->ft_rows);
+            SAR_LAUNCH_CHECK();
+        }
 
         // ---- the sources of one edge, listed from their destinations' side (all-blocks backward):
         // built where they carry at least an eighth of the edges, or on request

@@ -470,10 +470,10 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
     };
 
     // Rows at the head of the list are shared by a team of `team` wavefronts, each with its share of the edges.
-    auto shared_rows = [&](auto team_c, int64_t r_begin, int64_t r_end) __attribute__((always_inline)) {
+    auto shared_rows = [&](auto team_c, int64_t r_begin, int64_t r_end, int64_t place) __attribute__((always_inline)) {
         constexpr int team = decltype(team_c)::value, teams = NW / team;
         const int lead = wave / team * team;
-        for (int64_t r0 = r_begin + (int64_t)block * teams; r0 < r_end; r0 += (int64_t)n_blocks * teams) {
+        for (int64_t r0 = r_begin + place * teams; r0 < r_end; r0 += (int64_t)n_blocks * teams) {
             const int64_t r = r0 + wave / team;
             const bool have = teams == 1 || r < r_end;
             FwdState<LPH> st;
@@ -512,11 +512,11 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
     int64_t hubs = 0;
     if constexpr (NW > kWavesPerWG) {
         hubs = a.n_hub;
-        shared_rows(std::integral_constant<int, NW>{}, 0, hubs);
+        shared_rows(std::integral_constant<int, NW>{}, 0, hubs, block);
     }
-    shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long);
+    shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long, hubs > 0 ? from_behind(block, n_blocks) : block);
     const int64_t n_waves = (int64_t)n_blocks * NW;
-    for (int64_t r = a.n_long + (int64_t)block * NW + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(block, n_blocks) * NW + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         FwdState<LPH> st;
         init(st, i, true);
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + (int64_t)blockIdx.x * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.rows[r]);
         const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
         BwdAcc4 ac;

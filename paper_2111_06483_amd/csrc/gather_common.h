@@ -25,6 +25,11 @@ constexpr int kGatherThreads = 256;          // 4 wavefronts per workgroup
 constexpr int kWavesPerWG = kGatherThreads / kWave;
 constexpr int kMaxPersistentWGs = 256 * 8;   // 256 CUs x 8 resident workgroups
 
+// A workgroup's place among those that take the rows after the shared ones: the last first.  Lists go from long rows to short
+// ones, so the workgroups that had the longest of the shared rows would have the longest of the others as well (forward,
+// 4 x 64 bf16, 1.5 M edges 287 us dealt from the front, 219 from behind; 8 x 32 bf16, 9 M edges, given scores 1055 and 965).
+__device__ inline int64_t from_behind(int64_t block, int64_t n_blocks) { return n_blocks - 1 - block; }
+
 // Part `part` of `parts` of a row's edges [beg, end): the part's first 64 edges start at beg, and the value returned is how far
 // on the next 64 do.  Even shares in whole eights; dealt out 64 at a time a row of 130 edges was 64 + 64 + 2 to four
 // wavefronts, and such a row at the head of the list is what a short launch waits for.  Rows of 512 edges

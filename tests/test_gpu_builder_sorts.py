@@ -20,7 +20,9 @@ def check(src, dst, part, P):
         for rows, ptr in ((v["rows"], w.indptr), (v["t_rows"], w.t_indptr)):
             deg = np.diff(ptr)
             assert sorted(rows.tolist()) == np.flatnonzero(deg > 0).tolist()
-            assert np.all(np.diff(np.floor(np.log2(deg[rows]))) <= 0)
+            cls = np.floor(np.log2(deg[rows]))
+            assert np.all(np.diff(cls) <= 0)
+            assert np.all(np.diff(rows)[np.diff(cls) == 0] > 0)      # in a class by id
     b.close()
 
 
