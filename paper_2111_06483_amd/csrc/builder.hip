@@ -375,9 +375,9 @@ __global__ __launch_bounds__(kThreads) void k_local_ids(const int32_t* __restric
 // The keys are dealt to the buckets in runs of four: neighbouring keys are often frequent together
 // (ids in the order of degree), and a bucket of the 1024 most frequent rows of that graph holds half a
 // million pairs (641 us for one workgroup, and 14 ms to sort its rows).
-// What the kernels now take on those 15.2M edges: pairs to buckets 153 + 194 us from the edge list (the
-// gathers of the nodes' partitions and codes; one edge a thread at a time 216 + 217) and 31 + 120 us from the CSR, keys
-// 29, finish 170 each.  The last was 372 us, three quarters
+// What the kernels now take on those 15.2M edges: pairs to buckets 198 + 70 us from the edge list (the first gathers the
+// nodes' codes, the second reads what it left; each for itself, one edge a thread at a time, 216 + 217) and 31 + 120 us from the
+// CSR, keys 29, finish 170 each.  The last was 372 us, three quarters
 // of it instructions: groups of up to 8 values now take 8 lanes instead of 16, those of 17 to 256 a network in registers.
 
 constexpr int kBucketThreads = 512;
@@ -488,13 +488,36 @@ struct EdgeSource {
     }
 };
 
+// The same edges as the counting pass left them: (key, value), key ~0 where the edge is not kept.  Where all keys are one
+// pass and they fit 1 GiB, the scatter reads these 8 bytes instead of the edge list, and gathers no codes (15.2M edges: count
+// and scatter 153 + 194 us, so 198 + 70).
+struct StoredEdges {
+    const uint2* edges;
+    int64_t E;
+    template <int U, bool VALUES>
+    __device__ inline void get(int64_t e, int64_t step, int64_t end, bool (&have)[U], int64_t (&key)[U], uint32_t (&value)[U]) const
+    {
+        uint2 x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = edges[min(e + u * step, E - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            have[u] = e + u * step < end && x[u].x != ~0u;
+            key[u] = x[u].x;
+            value[u] = x[u].y;
+        }
+    }
+};
+constexpr int64_t kMostStored = (int64_t)1 << 27;
+
 constexpr int kEdgesAhead = 4;
 
-template <typename Src>
+template <typename Src, bool STORE>
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t tile, int64_t n_tiles, int64_t key0,
                                                                  int64_t n_keys, Deal deal,
                                                                  int32_t* __restrict__ counts,
-                                                                 unsigned long long* __restrict__ kept)
+                                                                 unsigned long long* __restrict__ kept,
+                                                                 uint2* __restrict__ stored)
 {
     extern __shared__ int bucket_hist[];
     const int n_buckets = 1 << deal.nb;
@@ -506,9 +529,13 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Src in, int64_t
         bool have[kEdgesAhead];
         int64_t key[kEdgesAhead];
         uint32_t value[kEdgesAhead];
-        in.template get<kEdgesAhead, false>(e, kBucketThreads, end, have, key, value);
+        in.template get<kEdgesAhead, STORE>(e, kBucketThreads, end, have, key, value);
 #pragma unroll
         for (int u = 0; u < kEdgesAhead; ++u) {
+            if constexpr (STORE) {
+                if (e + u * kBucketThreads < end)
+                    stored[e + u * kBucketThreads] = have[u] ? make_uint2((uint32_t)key[u], value[u]) : make_uint2(~0u, 0u);
+            }
             if (!have[u]) continue;
             ++mine;
             key[u] -= key0;
@@ -2035,6 +2062,8 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
         const bool narrow = plan.w + vbits <= 32;
         int32_t* counts = nullptr;
         SAR_TRY(tmp.alloc(&counts, (int64_t)plan.n_buckets() * plan.n_tiles + 1));
+        uint2* stored = nullptr;
+        if (n_rows_all <= kKeysPerPass && E <= kMostStored && tmp.alloc(&stored, E) != SAR_OK) stored = nullptr;   // (no room: without)
         int32_t base = 0;
         for (int64_t key0 = 0; key0 < std::max<int64_t>(n_rows_all, 1); key0 += kKeysPerPass) {
             const int64_t nk = std::min(kKeysPerPass, n_rows_all - key0);
@@ -2042,10 +2071,15 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
             const int64_t n_counts = (int64_t)plan.n_buckets() * plan.n_tiles + 1;
             const size_t lds = plan.n_buckets() * sizeof(int);
             const Deal deal{plan.nb};
-            SAR_TRY(allow_lds(k_bucket_count<decltype(in)>, lds));
-            k_bucket_count<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(in, plan.tile, plan.n_tiles, key0, nk, deal,
-                                                                                counts, first ? kept_d : nullptr);
-            SAR_LAUNCH_CHECK();
+            auto count = [&](auto store) -> int {
+                auto fn = k_bucket_count<decltype(in), decltype(store)::value>;
+                SAR_TRY(allow_lds(fn, lds));
+                fn<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(in, plan.tile, plan.n_tiles, key0, nk, deal, counts,
+                                                                        first ? kept_d : nullptr, stored);
+                SAR_LAUNCH_CHECK();
+                return SAR_OK;
+            };
+            SAR_TRY(stored ? count(std::true_type{}) : count(std::false_type{}));
             SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
             if (first) {
                 unsigned long long kept = 0;
@@ -2062,10 +2096,15 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
             }
             auto place = [&](auto* pairs) -> int {
                 using PairT = std::remove_pointer_t<decltype(pairs)>;
-                SAR_TRY(allow_lds(k_bucket_scatter<decltype(in), PairT>, lds));
-                k_bucket_scatter<decltype(in), PairT><<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(
-                    in, plan.tile, plan.n_tiles, key0, nk, deal, vbits, counts, pairs);
-                SAR_LAUNCH_CHECK();
+                auto scatter = [&](auto from) -> int {
+                    auto fn = k_bucket_scatter<decltype(from), PairT>;
+                    SAR_TRY(allow_lds(fn, lds));
+                    fn<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(from, plan.tile, plan.n_tiles, key0, nk, deal,
+                                                                            vbits, counts, pairs);
+                    SAR_LAUNCH_CHECK();
+                    return SAR_OK;
+                };
+                SAR_TRY(stored ? scatter(StoredEdges{stored, E}) : scatter(in));
                 return finish_buckets<PairT>(plan, pairs, counts, nk, vbits, base, row_off + key0, indices_all, tmp, st);
             };
             SAR_TRY(narrow ? place(static_cast<uint32_t*>(scratch.pairs)) : place(static_cast<uint64_t*>(scratch.pairs)));
