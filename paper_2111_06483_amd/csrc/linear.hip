@@ -1331,6 +1331,7 @@ bool dx_by_split(int64_t n, int K, int F)
 int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float* W, float* dW, void* dX, int dtype,
                     int64_t n, int K, int F, void* work, size_t work_bytes, hipStream_t st)
 {
+    if (!dW && !dX) return SAR_OK;       // (an empty grid is refused by the runtime)
     auto add_slabs = [&](int slabs) -> int {
         const int64_t count = (int64_t)K * F;
         k_sum_slabs<<<(unsigned)std::min<int64_t>((count + 31) / 32, 8192), 256, 0, st>>>(

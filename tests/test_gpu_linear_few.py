@@ -78,6 +78,18 @@ def test_backward(K, H, D, dtype, formed):
         assert float((dW.double() - exact).norm() / exact.norm()) < tol
 
 
+@pytest.mark.parametrize("n", [1, 100, MANY])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_neither_product_wanted(n, dtype):
+    """dW and dX may each be left out, so may both, for any number of rows; `rows` is written all the same."""
+    X, E, W, a, _, ds = layer(64, 4, 16, dtype)
+    sar.sar_linear_bwd(X[:n], E[:n], W, None, None, None)
+    sar.sar_linear_bwd_rows(X[:n], E[:n], None, ds[:n], a, 4, 16, W, None, None, n, dtype, None)
+    rows = torch.full((n, 64), float("nan"), dtype=dtype, device="cuda")
+    sar.sar_linear_bwd_rows(X[:n], E[:n], None, None, None, 4, 16, W, None, None, n, dtype, None, rows=rows)
+    assert torch.equal(rows, E[:n])
+
+
 def test_result_over_an_operand():
     """Z over X and dX over dZ go the other kernels' way: a tile's rows are read again after others are stored."""
     X = torch.randn(500, 64, device="cuda")
