@@ -119,6 +119,12 @@ public:
     }
     int take(int dev, void** out, size_t size)       // dev: the current device; size as round() gives it
     {
+        const hipError_t e = try_take(dev, out, size);
+        return e == hipSuccess ? SAR_OK
+                               : sar::fail(SAR_ERR_HIP, "hipMalloc of %zu bytes failed: %s", size, hipGetErrorString(e));
+    }
+    hipError_t try_take(int dev, void** out, size_t size)      // no error is left behind, here or with the runtime
+    {
         std::lock_guard<std::mutex> lock(m_);
         auto& d = devices_[dev];
         auto it = d.idle.lower_bound(size);
@@ -126,13 +132,15 @@ public:
             *out = it->second;
             d.bytes -= it->first;
             d.idle.erase(it);
-            return SAR_OK;
+            return hipSuccess;
         }
-        if (hipMalloc(out, size) == hipSuccess) return SAR_OK;
+        hipError_t e = hipMalloc(out, size);
+        if (e == hipSuccess) return e;
         (void)hipGetLastError();
         release(d);
-        SAR_HIP(hipMalloc(out, size));
-        return SAR_OK;
+        e = hipMalloc(out, size);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
     }
     void give(int dev, void* p, size_t size)         // memory of `dev` that nothing in flight uses any more
     {
@@ -233,6 +241,7 @@ struct DeviceTemps {
     DeviceTemps(const DeviceTemps&) = delete;
     ~DeviceTemps()
     {
+        drop_spare();
         if (ptrs.empty() && !page) return;
         (void)hipStreamSynchronize(st);
         for (auto& p : ptrs) pool().give(dev, p.first, p.second);
@@ -251,14 +260,37 @@ struct DeviceTemps {
         void* p = nullptr;
         const size_t size = Pool::round(std::max<int64_t>(count, 1) * sizeof(T));
         ptrs.reserve(ptrs.size() + 1);      // before there is anything to lose
-        SAR_TRY(pool().take(dev, &p, size));
+        SAR_TRY(or_without_spare([&] { return pool().take(dev, &p, size); }));
         ptrs.emplace_back(p, size);
         *out = static_cast<T*>(p);
         return SAR_OK;
     }
+    // Scratch that the call can do without (`spare`, null where there is no room): it makes way for whatever else is asked for.
+    void alloc_spare(size_t bytes)
+    {
+        spare_bytes = Pool::round(bytes);
+        if (pool().try_take(dev, &spare, spare_bytes) != hipSuccess) spare = nullptr;
+    }
+    void drop_spare()
+    {
+        if (!spare) return;
+        (void)hipStreamSynchronize(st);
+        pool().give(dev, spare, spare_bytes);
+        spare = nullptr;
+    }
+    template <typename Fn>
+    int or_without_spare(Fn&& take)
+    {
+        const int rc = take();
+        if (rc == SAR_OK || !spare) return rc;
+        drop_spare();
+        return take();
+    }
     hipStream_t st;
     int dev;
     void* page = nullptr;
+    void* spare = nullptr;
+    size_t spare_bytes = 0;
     std::vector<std::pair<void*, size_t>> ptrs;
 };
 
@@ -489,7 +521,7 @@ struct EdgeSource {
 };
 
 // The same edges as the counting pass left them: (key, value), key ~0 where the edge is not kept.  Where all keys are one
-// pass and they fit 1 GiB, the scatter reads these 8 bytes instead of the edge list, and gathers no codes (15.2M edges: count
+// pass, they fit 1 GiB and nothing else needs the room, the scatter reads these 8 bytes instead of the edge list, and gathers no codes (15.2M edges: count
 // and scatter 153 + 194 us, so 198 + 70).
 struct StoredEdges {
     const uint2* edges;
@@ -2062,8 +2094,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
         const bool narrow = plan.w + vbits <= 32;
         int32_t* counts = nullptr;
         SAR_TRY(tmp.alloc(&counts, (int64_t)plan.n_buckets() * plan.n_tiles + 1));
-        uint2* stored = nullptr;
-        if (n_rows_all <= kKeysPerPass && E <= kMostStored && tmp.alloc(&stored, E) != SAR_OK) stored = nullptr;   // (no room: without)
+        if (n_rows_all <= kKeysPerPass && E <= kMostStored) tmp.alloc_spare((size_t)E * sizeof(uint2));
         int32_t base = 0;
         for (int64_t key0 = 0; key0 < std::max<int64_t>(n_rows_all, 1); key0 += kKeysPerPass) {
             const int64_t nk = std::min(kKeysPerPass, n_rows_all - key0);
@@ -2075,11 +2106,11 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
                 auto fn = k_bucket_count<decltype(in), decltype(store)::value>;
                 SAR_TRY(allow_lds(fn, lds));
                 fn<<<(unsigned)plan.n_tiles, kBucketThreads, lds, st>>>(in, plan.tile, plan.n_tiles, key0, nk, deal, counts,
-                                                                        first ? kept_d : nullptr, stored);
+                                                                        first ? kept_d : nullptr, static_cast<uint2*>(tmp.spare));
                 SAR_LAUNCH_CHECK();
                 return SAR_OK;
             };
-            SAR_TRY(stored ? count(std::true_type{}) : count(std::false_type{}));
+            SAR_TRY(tmp.spare ? count(std::true_type{}) : count(std::false_type{}));
             SAR_TRY(exclusive_scan(counts, counts, n_counts, st, tmp));
             if (first) {
                 unsigned long long kept = 0;
@@ -2090,7 +2121,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
                     return sar::fail(SAR_ERR_UNSUPPORTED,
                                      "worker %d's share holds %llu in-edges; a handle holds fewer than 2^31", p, kept);
                 nnz_total = (int64_t)kept;
-                SAR_TRY(own(h, &indices_all, nnz_total));
+                SAR_TRY(tmp.or_without_spare([&] { return own(h, &indices_all, nnz_total); }));
                 SAR_TRY(scratch.take(tmp, (size_t)nnz_total * (narrow ? 4 : 8)));
                 if (n_rows_all == 0) break;
             }
@@ -2104,7 +2135,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
                     SAR_LAUNCH_CHECK();
                     return SAR_OK;
                 };
-                SAR_TRY(stored ? scatter(StoredEdges{stored, E}) : scatter(in));
+                SAR_TRY(tmp.spare ? scatter(StoredEdges{static_cast<const uint2*>(tmp.spare), E}) : scatter(in));
                 return finish_buckets<PairT>(plan, pairs, counts, nk, vbits, base, row_off + key0, indices_all, tmp, st);
             };
             SAR_TRY(narrow ? place(static_cast<uint32_t*>(scratch.pairs)) : place(static_cast<uint64_t*>(scratch.pairs)));
@@ -2134,6 +2165,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
         SAR_TRY(send_report(row_off, n_dst, P + 1, nullptr, true, &report, tmp, st));
         std::copy(report + 4, report + 5 + P, block_first.begin());
     }
+    tmp.drop_spare();      // (its readers are done: the handle's other arrays may take its room)
     for (int q = 0; q < P; ++q) {
         h->blk[q].nnz = block_first[q + 1] - block_first[q];
         h->blk[q].indptr = indptr_all + (int64_t)q * (n_dst + 1);

@@ -14,12 +14,15 @@ namespace sar {
 // Records the message for sar_last_error() and returns `code`.
 int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 
+// (The runtime keeps the error of a failed call until it is asked for: left there, the next launch would seem to have failed.)
 #define SAR_HIP(expr)                                                                   \
     do {                                                                                \
         hipError_t sar_e_ = (expr);                                                     \
-        if (sar_e_ != hipSuccess)                                                       \
+        if (sar_e_ != hipSuccess) {                                                     \
+            (void)hipGetLastError();                                                    \
             return ::sar::fail(SAR_ERR_HIP, "%s failed: %s", #expr,                     \
                                hipGetErrorString(sar_e_));                              \
+        }                                                                               \
     } while (0)
 
 #define SAR_CHECK_ARG(cond, ...)                                                        \
