@@ -649,7 +649,8 @@ struct BlkDev {
     const int32_t* indices;
     int64_t n_src, coff;     // sources of the block, and of the blocks before it
     int64_t nnz, nnz0;       // edges of the block, and of the blocks before it
-    int64_t tile0;           // first tile of the block (k_block_count / k_block_scatter)
+    int64_t tile0;           // first tile of the block's edges (k_block_count / k_block_scatter)
+    int64_t s_tile0;         // first tile of its sources in the launch lists' counts
     uint32_t* rows;          // launch lists
     uint32_t* t_rows;
     int32_t* t_indptr;
@@ -657,12 +658,13 @@ struct BlkDev {
 };
 
 // The edges of all blocks as pairs (coff[q] + source, destination): a tile lies inside one block.
+template <int64_t BlkDev::*FIRST = &BlkDev::tile0>
 __device__ inline int block_of_tile(const BlkDev* blk, int P, int64_t tile)
 {
     int lo = 0, hi = P - 1;      // the last block that starts at or before the tile and has tiles
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        if (blk[mid].tile0 <= tile)
+        if (blk[mid].*FIRST <= tile)
             lo = mid;
         else
             hi = mid - 1;
@@ -1306,26 +1308,38 @@ __device__ inline int degree_class(int len) { return len <= 0 ? 0 : 32 - __clz(l
 // The launch lists: the blocks' own rows, their sources, the rows of all blocks, the sources of all blocks.
 enum class Lists { kRows, kSources, kAllRows, kAllSources };
 constexpr int kPlacePer = 8, kPlaceRows = kThreads * kPlacePer;      // rows of a tile
-// Rows of a tile in every class, [class][tile] for each list one after another (the sources of all blocks: [class][block][tile]),
-// and, scanned, how many of the list's class stand before them.
+// Rows of a tile in every class, [class][tile] for each list one after another (the sources of all blocks: [class][block][tile];
+// a block has the tiles of its own sources), and, scanned, how many of the list's class stand before them.
 struct ListIn {
     const BlkDev* blk;
     const int32_t* off;      // kAllRows: the all-blocks row offsets
     int64_t n_dst;
     int P;
-    int64_t t_rows, t_src;   // tiles of a block's rows and sources
+    int64_t t_rows, t_src;   // tiles of a block's rows, and of all blocks' sources
     bool fused;
     __host__ __device__ inline int64_t first_src() const { return P * sar::kNumClasses * t_rows; }
-    __host__ __device__ inline int64_t first_all_rows() const { return first_src() + P * sar::kNumClasses * t_src; }
+    __host__ __device__ inline int64_t first_all_rows() const { return first_src() + sar::kNumClasses * t_src; }
     __host__ __device__ inline int64_t first_all_src() const { return first_all_rows() + (fused ? sar::kNumClasses * t_rows : 0); }
-    __host__ __device__ inline int64_t size() const { return first_all_src() + P * sar::kNumClasses * t_src; }
+    __host__ __device__ inline int64_t size() const { return first_all_src() + sar::kNumClasses * t_src; }
     // where the counts of class c of list l (of block q) start, and how many there are
-    __host__ __device__ inline int64_t counts(Lists l, int q, int c, int64_t& tiles) const
+    __device__ inline int64_t counts(Lists l, int q, int c, int64_t& tiles) const
     {
-        tiles = l == Lists::kAllSources ? P * t_src : l == Lists::kSources ? t_src : t_rows;
-        const int64_t first = l == Lists::kRows ? 0 : l == Lists::kSources ? first_src() : l == Lists::kAllRows ? first_all_rows() : first_all_src();
-        const bool by_block = l == Lists::kRows || l == Lists::kSources;
-        return first + ((by_block ? (int64_t)q * sar::kNumClasses : 0) + c) * tiles;
+        if (l == Lists::kSources) {
+            tiles = (q + 1 < P ? blk[q + 1].s_tile0 : t_src) - blk[q].s_tile0;
+            return first_src() + blk[q].s_tile0 * sar::kNumClasses + c * tiles;
+        }
+        tiles = l == Lists::kAllSources ? t_src : t_rows;
+        const int64_t first = l == Lists::kRows ? (int64_t)q * sar::kNumClasses * t_rows : l == Lists::kAllRows ? first_all_rows() : first_all_src();
+        return first + c * tiles;
+    }
+    // a workgroup's block and its tile there: the blocks' rows (tile, block), all others by the tile
+    __device__ inline void place(Lists l, int& q, int64_t& tile) const
+    {
+        q = (int)blockIdx.y;
+        tile = blockIdx.x;
+        if (l == Lists::kRows || l == Lists::kAllRows) return;
+        q = block_of_tile<&BlkDev::s_tile0>(blk, P, tile);
+        tile -= blk[q].s_tile0;
     }
     __device__ inline const int32_t* offsets(Lists l, int y, int64_t& n) const
     {
@@ -1382,15 +1396,16 @@ __device__ inline void tile_classes(const int32_t* off, int64_t n, int64_t tile,
 __global__ __launch_bounds__(kThreads) void k_class_count(ListIn in, Lists l, int32_t* __restrict__ counts)
 {
     __shared__ int cnt[sar::kNumClasses];
-    int64_t n, tiles;
-    const int32_t* off = in.offsets(l, blockIdx.y, n);
+    int64_t n, tiles, tile;
+    int q;
+    in.place(l, q, tile);
+    const int32_t* off = in.offsets(l, q, n);
     int c[kPlacePer], at[kPlacePer];
-    tile_classes(off, n, blockIdx.x, c, at, cnt);
+    tile_classes(off, n, tile, c, at, cnt);
     __syncthreads();
     if (threadIdx.x < sar::kNumClasses) {
-        const int64_t of = in.counts(l, blockIdx.y, threadIdx.x, tiles);
-        counts[of + blockIdx.x] = cnt[threadIdx.x];
-        if (l == Lists::kSources) counts[in.counts(Lists::kAllSources, 0, threadIdx.x, tiles) + blockIdx.y * in.t_src + blockIdx.x] = cnt[threadIdx.x];
+        counts[in.counts(l, q, threadIdx.x, tiles) + tile] = cnt[threadIdx.x];
+        if (l == Lists::kSources) counts[in.counts(Lists::kAllSources, 0, threadIdx.x, tiles) + blockIdx.x] = cnt[threadIdx.x];
     }
     if (l == Lists::kRows && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) counts[in.size()] = 0;
 }
@@ -1418,23 +1433,24 @@ __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, in
 {
     __shared__ int cnt[sar::kNumClasses];
     __shared__ int base[sar::kNumClasses];
-    int64_t n, tiles;
-    const int32_t* off = in.offsets(l, blockIdx.y, n);
-    const int* start = starts + (l == Lists::kRows || l == Lists::kSources ? blockIdx.y * sar::kNumClasses : 0);
-    uint32_t* out = l == Lists::kRows ? in.blk[blockIdx.y].rows : l == Lists::kSources ? in.blk[blockIdx.y].t_rows : out_all;
-    const uint32_t tag = l == Lists::kAllSources ? (uint32_t)blockIdx.y << tag_shift : 0u;
+    int64_t n, tiles, tile;
+    int q;
+    in.place(l, q, tile);
+    const int32_t* off = in.offsets(l, q, n);
+    const int* start = starts + (l == Lists::kRows || l == Lists::kSources ? q * sar::kNumClasses : 0);
+    uint32_t* out = l == Lists::kRows ? in.blk[q].rows : l == Lists::kSources ? in.blk[q].t_rows : out_all;
+    const uint32_t tag = l == Lists::kAllSources ? (uint32_t)q << tag_shift : 0u;
     int c[kPlacePer], at[kPlacePer];
-    tile_classes(off, n, blockIdx.x, c, at, cnt);
+    tile_classes(off, n, tile, c, at, cnt);
     if (threadIdx.x < sar::kNumClasses) {
-        const int64_t of = in.counts(l, blockIdx.y, threadIdx.x, tiles);
-        const int64_t tile = l == Lists::kAllSources ? blockIdx.y * in.t_src + blockIdx.x : blockIdx.x;
-        base[threadIdx.x] = start[threadIdx.x] + (int32_t)((uint32_t)counts[of + tile] - (uint32_t)counts[of]);
+        const int64_t of = in.counts(l, q, threadIdx.x, tiles), mine = l == Lists::kAllSources ? (int64_t)blockIdx.x : tile;
+        base[threadIdx.x] = start[threadIdx.x] + (int32_t)((uint32_t)counts[of + mine] - (uint32_t)counts[of]);
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kPlacePer; ++j)
         if (c[j] > 0 || (c[j] == 0 && l != Lists::kRows))
-            out[base[c[j]] + at[j]] = (uint32_t)((int64_t)blockIdx.x * kPlaceRows + j * kThreads + threadIdx.x) | tag;
+            out[base[c[j]] + at[j]] = (uint32_t)(tile * kPlaceRows + j * kThreads + threadIdx.x) | tag;
 }
 
 struct ClassLayout {
@@ -1851,7 +1867,7 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     void* page = nullptr;
     SAR_TRY(tmp.host(&page, kReportBytes));
     BlkDev* const blk = static_cast<BlkDev*>(page);
-    int64_t coff = 0, nnz0 = 0, tiles = 0;
+    int64_t coff = 0, nnz0 = 0, tiles = 0, s_tiles = 0;
     for (int q = 0; q < P; ++q) {
         Block& b = h->blk[q];
         if (transpose) {
@@ -1860,18 +1876,18 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
             b.t_indices = t_indices_all + nnz0;
             b.t_rows = t_rows_all + coff;
         }
-        blk[q] = BlkDev{b.indptr, b.indices, b.n_src, coff, b.nnz, nnz0, tiles, nullptr,
+        blk[q] = BlkDev{b.indptr, b.indices, b.n_src, coff, b.nnz, nnz0, tiles, s_tiles, nullptr,
                         reinterpret_cast<uint32_t*>(b.t_rows), b.t_indptr, b.t_rank};
         coff += b.n_src;
         nnz0 += b.nnz;
         tiles += (b.nnz + plan.tile - 1) / plan.tile;
+        if (transpose) s_tiles += (b.n_src + kPlaceRows - 1) / kPlaceRows;
     }
     BlkDev* blk_d = nullptr;
     const int C = sar::kNumClasses, n_hist = (2 * P + 2) * C;
     int *starts_d = nullptr, *class_counts = nullptr;
     int32_t *col_off = nullptr, *counts = nullptr, *pos = nullptr;      // (the transpose's)
-    ListIn in{nullptr, h->f_indptr, n_dst, P, (n_dst + kPlaceRows - 1) / kPlaceRows,
-              transpose ? (n_src_max + kPlaceRows - 1) / kPlaceRows : 0, fused};
+    ListIn in{nullptr, h->f_indptr, n_dst, P, (n_dst + kPlaceRows - 1) / kPlaceRows, s_tiles, fused};
     SAR_TRY(tmp.alloc_parts({tmp.part(&blk_d, P), tmp.part(&starts_d, n_hist), tmp.part(&class_counts, in.size() + 1),
                              tmp.part(&col_off, transpose ? n_src_total + 1 : 0), tmp.part(&pos, transpose ? n_src_total + 1 : 0),
                              tmp.part(&counts, transpose ? (int64_t)plan.n_buckets() * std::max<int64_t>(tiles, 1) + 1 : 0)}));
@@ -1881,7 +1897,7 @@ int derive(sar_blocks* h, DeviceTemps& tmp, PairScratch& scratch, hipStream_t st
     // total in-degree |N(i)|, and the tiles' rows by class
     k_total_degree<<<grid_for(n_dst + 1), kThreads, 0, st>>>(blk_d, P, n_dst, h->deg);
     SAR_LAUNCH_CHECK();
-    const dim3 g_rows((unsigned)std::max<int64_t>(1, in.t_rows), P), g_all(g_rows.x, 1), g_tiles((unsigned)std::max<int64_t>(1, in.t_src), P);
+    const dim3 g_rows((unsigned)std::max<int64_t>(1, in.t_rows), P), g_all(g_rows.x, 1), g_tiles((unsigned)std::max<int64_t>(1, in.t_src), 1);
     const dim3 g_src(grid_for(n_src_max + 1, kThreads, std::max(1, 4096 / P)), P);
     const bool lists = n_dst > 0, src_lists = transpose && n_src_max > 0;
     if (lists) {
@@ -2370,7 +2386,7 @@ extern "C" int sar_blocks_wrap(int P, int64_t n_dst, const int64_t* n_src, const
             b.n_src = n_src[q];
             b.indptr = indptr[q];
             b.indices = indices[q];
-            blk[q] = BlkDev{indptr[q], indices[q], n_src[q], 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
+            blk[q] = BlkDev{indptr[q], indices[q], n_src[q], 0, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
         }
         SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
         k_block_ends<<<1, kThreads, 0, st>>>(blk_d, P, n_dst, ends_d);
@@ -2496,7 +2512,7 @@ extern "C" int sar_blocks_subset(const sar_blocks_t* b, const int32_t* dst_ids, 
             const Block& from = b->blk[q];
             h->blk[q].n_dst = n_sub;
             h->blk[q].n_src = from.n_src;
-            blk[q] = BlkDev{from.indptr, from.indices, from.n_src, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
+            blk[q] = BlkDev{from.indptr, from.indices, from.n_src, 0, 0, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
         }
         SAR_HIP(hipMemcpyAsync(blk_d, blk.data(), P * sizeof(BlkDev), hipMemcpyHostToDevice, st));
         SAR_HIP(hipMemsetAsync(err_d, 0, 4 * sizeof(int), st));

@@ -47,3 +47,14 @@ def test_lists_of_many_rows(n):
     part = (np.arange(2 * n) % 2).astype(np.int32)
     dst = 2 * rng.integers(0, n, 3 * n)
     check(rng.integers(0, 2 * n, dst.size), dst, part, 2)
+
+
+@pytest.mark.parametrize("sizes", [[6_000, 0, 1, 4_096, 0, 0, 2_049, 1], [1, 0, 9_000], [0, 0, 5, 2_048], [3] * 60 + [20_000]])
+def test_lists_of_blocks_of_any_size(sizes):
+    """Blocks of no source, of one, of whole and broken tiles, the destinations' own among them."""
+    rng = np.random.default_rng(len(sizes))
+    part = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    N, mine = part.size, np.flatnonzero(part == part[-1])
+    part = (part - part[-1]) % len(sizes)                     # the last block's nodes are partition 0
+    dst = mine[rng.integers(0, mine.size, 2 * N)]
+    check(rng.integers(0, N, dst.size), dst, part.astype(np.int32), len(sizes))
