@@ -104,3 +104,20 @@ def test_result_over_an_operand():
     want = X.double() @ W.double().T
     assert float((B.double() - want).norm() / want.norm()) < 8 * 2.0 ** -24
     assert float((dX.double() - want).norm() / want.norm()) < 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,K,F,dtype", [(8192, 256, 512, torch.bfloat16), (16384, 128, 400, torch.bfloat16), (2560, 512, 384, torch.float32),
+                                         (20480, 64, 256, torch.float32), (1500, 256, 256, torch.bfloat16)])
+@pytest.mark.parametrize("alone", [True, False])
+def test_weight_gradients_of_long_slabs(n, K, F, dtype, alone):
+    """Many columns leave few slabs, of hundreds of rows for a wavefront.  Normal operands: a result is of size n^1/2, and so is
+    a partial sum of m rows of size m^1/2; eight sums of 32 rows, up to eight of those and four wavefronts' and eight slabs'
+    sums are some 17 n of squares in all, each rounded by 0.42 of 2^-24 in the mean: 1.7 2^-24 of the result (measured: 1.7)."""
+    g = torch.Generator(device="cuda").manual_seed(n + K)
+    X, dZ = (torch.randn(n, w, device="cuda", generator=g).to(dtype) for w in (K, F))
+    W = torch.randn(K, F, device="cuda", generator=g)
+    work = torch.empty(sar.sar_linear_workspace_bytes(n, K, F) // 4, device="cuda")
+    dW, dX = torch.zeros(K, F, device="cuda"), None if alone else torch.empty_like(X)
+    sar.sar_linear_bwd(X, dZ, None if alone else W, dW, dX, work)
+    want = X.double().T @ dZ.double()
+    assert float((dW.double() - want).norm() / want.norm()) < 2.0 * 2.0 ** -24
