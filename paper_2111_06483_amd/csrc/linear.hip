@@ -1135,7 +1135,7 @@ __global__ __launch_bounds__(256) void k_sum_slabs(const float* __restrict__ par
 bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes)
 {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return !a || !b || x + a_bytes <= y || y + b_bytes <= x;
+    return !a || !b || !a_bytes || !b_bytes || x + a_bytes <= y || y + b_bytes <= x;
 }
 
 constexpr int kMaxSlabs = 512;
@@ -1327,8 +1327,8 @@ bool dx_by_split(int64_t n, int K, int F)
 }
 
 // op == nullptr: dZ is the stored [n,F] operand.  Otherwise dZ is the stored part of the rows
-// `op` describes and both products form the rows as they load them.
-int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float* W, float* dW, void* dX, int dtype,
+// `op` describes and both products form the rows as they load them.  dZ_rows: its rows, 0 for a stand-in of which no value counts.
+int linear_bwd_impl(const void* X, const void* dZ, int64_t dZ_rows, const RowsOp* op, const float* W, float* dW, void* dX, int dtype,
                     int64_t n, int K, int F, void* work, size_t work_bytes, hipStream_t st)
 {
     if (!dW && !dX) return SAR_OK;       // (an empty grid is refused by the runtime)
@@ -1340,7 +1340,7 @@ int linear_bwd_impl(const void* X, const void* dZ, const RowsOp* op, const float
         return SAR_OK;
     };
     const size_t elem = dtype == SAR_F32 ? 4 : 2;
-    if (sar::few_rows_bwd(dtype, n, K, F) && apart(dX, (size_t)n * K * elem, dZ, (size_t)n * F * elem) &&
+    if (sar::few_rows_bwd(dtype, n, K, F) && apart(dX, (size_t)n * K * elem, dZ, (size_t)dZ_rows * F * elem) &&
         (!dW || apart(dX, (size_t)n * K * elem, X, (size_t)n * K * elem))) {
         if (dW) {
             const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
@@ -1440,7 +1440,7 @@ extern "C" int sar_linear_bwd(const void* X, const void* dZ, const float* W, flo
         SAR_CHECK_ARG(work != nullptr && work_bytes >= need, "work_bytes=%zu is below the %zu bytes required",
                       work_bytes, need);
     }
-    return linear_bwd_impl(X, dZ, nullptr, W, dW, dX, dtype, n, K, F, work, work_bytes, sar::as_stream(stream));
+    return linear_bwd_impl(X, dZ, n, nullptr, W, dW, dX, dtype, n, K, F, work, work_bytes, sar::as_stream(stream));
 }
 
 extern "C" int sar_linear_bwd_rows(const void* X, const void* E, const int32_t* E_rank, int64_t n_E,
@@ -1477,11 +1477,11 @@ extern "C" int sar_linear_bwd_rows(const void* X, const void* E, const int32_t* 
     // where no row is stored the kernels still need an address they may read a row from
     const void* stored = op.has_E ? E : static_cast<const void*>(a_r ? a_r : ds);
     if (!rows && rows_op_fusable(X, stored, op, dX, dtype, K, F))
-        return linear_bwd_impl(X, stored, &op, W, dW, dX, dtype, n, K, F, work, work_bytes, st);
+        return linear_bwd_impl(X, stored, op.has_E ? n_E : 0, &op, W, dW, dX, dtype, n, K, F, work, work_bytes, st);
     if (!rows)
         return sar::fail(SAR_ERR_UNSUPPORTED,
                          "this shape (K=%d, H=%d, D=%d) cannot form the error rows inside the products: pass `rows`, "
                          "[n,F] values of scratch, and they are written out first", K, H, D);
     SAR_TRY(rows_store(E, op, rows, dtype, n, F, st));
-    return linear_bwd_impl(X, rows, nullptr, W, dW, dX, dtype, n, K, F, work, work_bytes, st);
+    return linear_bwd_impl(X, rows, n, nullptr, W, dW, dX, dtype, n, K, F, work, work_bytes, st);
 }

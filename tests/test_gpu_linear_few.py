@@ -121,3 +121,26 @@ def test_weight_gradients_of_long_slabs(n, K, F, dtype, alone):
     sar.sar_linear_bwd(X, dZ, None if alone else W, dW, dX, work)
     want = X.double().T @ dZ.double()
     assert float((dW.double() - want).norm() / want.norm()) < 2.0 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("stored", [0, 40])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_results_do_not_depend_on_where_operands_lie(stored, dtype):
+    """dX right behind the few stored rows of a compact E, or behind a_r where no row is stored: the same bits as far off."""
+    n, K, H, D = 1500, 64, 4, 16
+    F = H * D
+    X, E, W, a, _, ds = layer(K, H, D, dtype)
+    rank = torch.arange(n + 1, dtype=torch.int32, device="cuda").clamp(max=stored)
+    near = torch.empty(F + (stored * F + n * K), device="cuda")      # (fp32 words: room for either type)
+    near[:F] = a.reshape(-1)
+    values = near[F:].view(dtype)
+    values[:stored * F] = E[:stored].reshape(-1)
+    got = []
+    for dX, e, a_r in ((torch.empty(n, K, dtype=dtype, device="cuda"), E[:stored].contiguous(), a),
+                       (values[stored * F:stored * F + n * K].view(n, K), values[:stored * F].view(stored, F), near[:F].view(H, D))):
+        work = torch.empty(sar.sar_linear_workspace_bytes(n, K, F) // 4, device="cuda")
+        dW = torch.zeros(K, F, device="cuda")
+        sar.sar_linear_bwd_rows(X[:n], e if stored else None, rank.data_ptr() if stored else None, ds[:n], a_r, H, D, W, dW, dX, n,
+                                dtype, work)
+        got.append((dW, dX.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
