@@ -176,13 +176,11 @@ int sar_version(void);
  *              the handle), else SAR_ERR_UNSUPPORTED.
  *   part       [N] partition of every node, each in [0,P)
  *   P <= SAR_MAX_PARTS (<= SAR_MAX_BLOCKS with SAR_BUILD_FUSED), N < 2^31.
- * The CSR arrays, their transposes, the degrees and the touched lists / ranks are
- * integer work and bit-exact: they do not depend on thread scheduling.  The launch
- * lists (rows, t_rows) are filled through atomic cursors, so the order of the rows
- * INSIDE a degree class differs from build to build; that order decides which
- * workgroup sums which rows into the partial sums of da_l / da_r, whose last bits
- * are therefore reproducible for one handle, not across handles built from the same
- * edges (ds is order-dependent through its atomics in any case).
+ * The CSR arrays, their transposes, the degrees, the touched lists / ranks and the
+ * launch lists (rows, t_rows: by degree class, inside a class in the rows' own order)
+ * are integer work and bit-exact: they do not depend on thread scheduling.  So the
+ * partial sums of da_l / da_r, whose order follows the lists, are the same for every
+ * handle built from the same edges (ds is order-dependent through its atomics).
  * *out is a new handle the caller frees with sar_blocks_free. */
 int sar_blocks_build(const void* src, const void* dst, int idx_bytes, int64_t E,
                      const int32_t* part, int64_t N, int P, int p, int flags, void* stream,
@@ -230,11 +228,14 @@ int sar_blocks_degree(const sar_blocks_t* b, const int32_t** deg);
 
 /* Free the handle and give up everything the library allocated for it.  While other handles live on
  * the device the library keeps up to 1 GiB of what freed handles and finished builder calls gave
- * up (in pieces of at most 256 MiB) for the next builder call; the last handle's end frees all of it. */
+ * up (in pieces of at most 256 MiB) for the next builder call; the end of the device's last handle frees all
+ * of it.  Builder calls also keep up to four pages of 192 KiB of pinned host memory, which the end of the last
+ * handle on any device frees.  Not during stream capture (it calls hipFree and hipHostFree). */
 int sar_blocks_free(sar_blocks_t* b);
 
-/* Free the device memory the library keeps for coming builder calls, on every device, for a program whose
- * own allocations need it now.  Living handles are untouched.  Not during stream capture (it calls hipFree). */
+/* Free the device memory the library keeps for coming builder calls, on every device, and the pinned pages,
+ * for a program whose own allocations need it now.  Living handles are untouched.  Not during stream capture (it
+ * calls hipFree and hipHostFree). */
 int sar_release_memory(void);
 
 /* ------------------------------------------------------- Eq. 2: sum / mean
