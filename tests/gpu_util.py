@@ -17,6 +17,14 @@ from paper_2111_06483_amd import sar
 DEV = "cuda"
 
 
+def kernels_of(fn) -> str:
+    """Names of the kernels that fn() runs, one a line."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return "\n".join(e.name for e in p.events())
+
+
 def dev(a, dtype=None) -> torch.Tensor:
     t = torch.as_tensor(np.ascontiguousarray(a))
     if dtype is not None:

@@ -4,9 +4,10 @@ import pytest
 import torch
 
 from paper_2111_06483_amd import sar
+from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
-MANY = 60_000       # beyond the lines of every width below
+MANY = 70_000       # beyond the lines of every width below
 
 # tiles of one column to several, contractions that end inside a piece, a chunk, a ring of chunks; heads of any width
 SHAPES = [(64, 4, 16), (36, 1, 33), (100, 4, 64), (128, 3, 20), (256, 8, 32), (255, 1, 47), (72, 2, 50), (300, 5, 12), (21, 1, 130)]
@@ -32,6 +33,7 @@ def test_forward(K, H, D, dtype, scores):
         sar.sar_linear_fwd(X[:n], W, Z, *((a, s) if scores else (None, None)), *second)
         return [Z, s, t][: 1 + scores]
 
+    assert "k_few" not in gu.kernels_of(lambda: run(MANY)) and "k_few" in gu.kernels_of(lambda: run(1000))
     want = run(MANY)
     for n in (1, 32, 33, 127, 1000):
         for got, many in zip(run(n), want):
@@ -67,10 +69,15 @@ def test_backward(K, H, D, dtype, formed):
         with pytest.raises(sar.SarError):
             run(100)
         return
+    assert "k_few" not in gu.kernels_of(lambda: run(MANY)) and "k_few" in gu.kernels_of(lambda: run(1500))
     # (n, groups of 32 rows: one, one for each wavefront, one slab, several)
     for n in (1, 2, 31, 128, 129, 640, 641, 1500):
         dW, dX, rows = run(n)
         assert torch.equal(dX, want[:n])
+        # (F products, as above; bf16: the stored result's rounding, 2^-8 of a value at most, and those of the formed rows)
+        back = rows @ W.double().T
+        off = max(2.0, F ** 0.5) * 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8 * (1.1 if formed else 1.0)
+        assert float((dX.double() - back).norm() / back.norm()) < off
         exact = 1.0 + X[:n].double().T @ rows
         # a sum of n products: n^1/2 roundings of the running sum, below 2^-24 of its scale each, and (bf16) those of the
         # formed rows, which 64 bits round to the other neighbour where fp32's multiply-add is within its rounding of a tie
@@ -144,3 +151,24 @@ def test_results_do_not_depend_on_where_operands_lie(stored, dtype):
                                 dtype, work)
         got.append((dW, dX.clone()))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("K,H,D", [(64, 4, 16), (100, 4, 64), (72, 2, 50)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("where", ["X", "E", "W"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38, 2.0 ** -111, 2.0 ** -126])
+def test_values_that_are_not_split(K, H, D, dtype, where, value):
+    """Infinities, NaN, values beyond bf16's largest and below its smallest piece: Z and dX as of many rows, bit for bit.
+    (Whole tiles of 32 rows: fp32 dX is formed by another instruction for all rows of a tile in which one overflows.)"""
+    X, E, W, _, _, _ = layer(K, H, D, dtype)
+    {"X": X[70, 5:6], "E": E[70, 9:10], "W": W[11, 40:41]}[where].fill_(value)
+
+    def run(n):
+        Z, dX = torch.empty(n, H * D, dtype=dtype, device="cuda"), torch.empty(n, K, dtype=dtype, device="cuda")
+        sar.sar_linear_fwd(X[:n], W, Z)
+        sar.sar_linear_bwd(None, E[:n], W, None, dX, None)
+        return Z, dX
+
+    for few, many in zip(run(96), run(MANY)):
+        assert torch.equal(torch.isnan(few), torch.isnan(many[:96]))
+        assert torch.equal(few.float().nan_to_num(7.0, 1.0, -1.0), many[:96].float().nan_to_num(7.0, 1.0, -1.0))

@@ -108,13 +108,16 @@ def test_rows_formed_in_the_products_equal_the_stored_rows(dtype, H, D, K, n, pr
 
 
 @pytest.mark.parametrize("H,D,K", [(16, 4, 64), (9, 4, 40), (3, 12, 32), (5, 12, 64), (13, 8, 64), (9, 16, 100), (12, 20, 64)])
-def test_heads_that_lanes_hold_in_turns(H, D, K):
-    """dW's lanes share the ds of eight rows, 2, 4 or 8 heads at a time by the width of the rows: up to eight turns."""
-    test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, 3001, 0.6, True)
+@pytest.mark.parametrize("n", [3001, 42_001])
+def test_heads_that_lanes_hold_in_turns(H, D, K, n):
+    """dW's lanes share the ds of eight rows, 2, 4 or 8 heads at a time by the width of the rows: up to eight turns.  (3001
+    rows: the kernel of few rows, whose lanes hold one head each.)"""
+    test_rows_formed_in_the_products_equal_the_stored_rows(torch.float32, H, D, K, n, 0.6, True)
 
 
 @pytest.mark.parametrize("H,D,K,n", [(4, 16, 64, 70_000), (1, 64, 128, 40_000), (3, 12, 32, 100_000), (8, 8, 100, 50_000),
-                                     (4, 16, 36, 3001), (4, 16, 32, 3001), (5, 20, 64, 675_000)])
+                                     (4, 16, 36, 3001), (4, 16, 32, 3001), (4, 16, 36, 42_001), (4, 16, 32, 42_001),
+                                     (5, 20, 64, 675_000)])
 def test_narrow_layers(H, D, K, n):
     """More rows than dW has slabs of 32: as many slabs whether the rows are stored or formed.  And both sides of the lines
     at which dX goes by the fp32 instruction: 32 columns, up to 64 of rows beyond 256 MiB that end within a line."""

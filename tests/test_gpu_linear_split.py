@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2111_06483_amd import sar
+from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
@@ -40,7 +41,7 @@ def test_sums_against_64_bits(n, K, F):
         assert err < max(2.0, min(length, 1024) ** 0.5) * 2.0 ** -24, err
 
 
-@pytest.mark.parametrize("length", [1, 2, 3, 5, 9, 15, 16, 17, 31, 33, 100, 257, 400, 2000])
+@pytest.mark.parametrize("length", [1, 2, 3, 5, 9, 15, 16, 17, 31, 33, 100, 257, 400, 2000, 6000])
 @pytest.mark.parametrize("kind", ["normal", "uniform"])
 def test_no_further_off_than_the_fp32_instruction(length, kind):
     """The forward product forms the same sums with the fp32 instruction: dW = (X^T) dZ over `length` rows and, from 17
@@ -59,9 +60,9 @@ def test_no_further_off_than_the_fp32_instruction(length, kind):
     sar.sar_linear_fwd(X.T.contiguous(), dZ, by_fp32)
     want = X.double().T @ dZ.double()
     assert off(dW, want) <= 1.02 * off(by_fp32, want)
-    if length > 16:
-        _, dZ, W = pair(3000, 100, length)
-        dX, by_fp32 = torch.empty(3000, 100, device="cuda"), torch.empty(3000, 100, device="cuda")
+    for n in (3000, 12_000) if length > 16 else ():      # (few rows and many)
+        _, dZ, W = pair(n, 100, length)
+        dX, by_fp32 = torch.empty(n, 100, device="cuda"), torch.empty(n, 100, device="cuda")
         sar.sar_linear_bwd(None, dZ, W, None, dX, None)
         sar.sar_linear_fwd(dZ, W.T.contiguous(), by_fp32)
         want = dZ.double() @ W.double().T
@@ -91,7 +92,8 @@ def test_rows_of_errors_lean_to_no_side(F, kind):
     assert float((d.mean(0) / d.std(0)).abs().max()) < 6 / 316
 
 
-@pytest.mark.parametrize("n,K,F", [(300, 100, 64), (2_000, 256, 100), (700, 61, 47)])
+@pytest.mark.parametrize("n,K,F", [(300, 100, 64), (2_000, 256, 100), (700, 61, 47),
+                                   (12_000, 100, 64), (6_000, 256, 100), (21_000, 61, 47)])
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 @pytest.mark.parametrize("where", ["X", "dZ", "W"])
 def test_values_without_pieces(n, K, F, value, where):
@@ -160,3 +162,10 @@ def test_in_place(n, H, D, formed):
     else:
         sar.sar_linear_bwd(None, dZ, W, None, dZ, None)
     assert float((dZ.double() - want).norm() / want.norm()) < F ** 0.5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,K,F", [(12_000, 100, 64), (6_000, 256, 100), (21_000, 61, 47), (6_000, 200, 100), (26_000, 256, 40)])
+def test_sizes_above_that_many_rows_take(n, K, F):
+    X, dZ, W = operands(n, K, F, seed=3)
+    names = gu.kernels_of(lambda: backward(X, dZ, W))
+    assert "k_dx_split" in names and "k_dw_split" in names
