@@ -554,8 +554,8 @@ struct EdgeSource {
 };
 
 // The same edges as the counting pass left them: (key, value), key ~0 where the edge is not kept.  Where all keys are one
-// pass, they fit 1 GiB and nothing else needs the room, the scatter reads these 8 bytes instead of the edge list, and gathers no codes (15.2M edges: count
-// and scatter 153 + 194 us, so 198 + 70).
+// pass, they fit 1 GiB and nothing else needs the room, the scatter reads these 8 bytes instead of the edge list, and gathers no
+// codes (15.2M edges: count and scatter 153 + 194 us, so 198 + 70).
 struct StoredEdges {
     const uint2* edges;
     int64_t E;
@@ -1005,8 +1005,9 @@ __device__ inline void bitonic_steps(int32_t (&x)[N], int lane)
 }
 
 // Ascending order of a[0, len), len <= 64 N, by one wavefront, in registers: 256 values are 36 steps, 15 of them
-// inside a lane, of the others' exchanges two thirds DPP; under two instructions a value.  (Counting for every value the ones before it reads the group from LDS once per
-// value: 13 instructions for each of 256 values, and the long groups were most of what the kernel below issued.)
+// inside a lane, of the others' exchanges two thirds DPP; under two instructions a value.  (Counting for every value the ones
+// before it reads the group from LDS once per value: 13 instructions for each of 256 values, and the long groups were most of
+// what the kernel below issued.)
 template <int N>
 __device__ inline void sort_wave(int32_t* a, int len, int lane)
 {
@@ -1427,7 +1428,8 @@ __global__ __launch_bounds__(kThreads) void k_class_totals(ListIn in, bool sourc
 // start[class] is the first place of the class in the list; value written = r | tag.  Rows stand by class, in a class in their
 // own order: the same lists from every build.  Where ids follow degrees the longest rows stand in front; the kernels deal the
 // rows after the shared ones from behind (1.5 M edges, rows of up to 10 thousand, forward pass: 219 us; dealt from the front 287,
-// and 267 with the rows in the order in which workgroups came to take places for 256 at a time).  Rows without edges (class 0) are listed last, in the blocks' own row lists not at all.
+// and 267 with the rows in the order in which workgroups came to take places for 256 at a time).  Rows without edges (class 0)
+// are listed last, in the blocks' own row lists not at all.
 __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, int tag_shift, const int* __restrict__ starts,
                                                           const int32_t* __restrict__ counts, uint32_t* __restrict__ out_all)
 {

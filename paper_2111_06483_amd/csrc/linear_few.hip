@@ -3,10 +3,10 @@
 // The kernels of linear.hip and linear_split.hip lay the small operand out in LDS for workgroups that walk over many rows.
 // Where there are only a few hundred or thousand rows that layout is most of the time: 462 rows 256 x 256 with scores
 // took 40 us, of which the products of a wavefront are 17 (five tiles one after the other on 30 of 256 CUs) and the
-// staging the rest; now 19, of which the score columns are more than half (8.8 without).  Here a wavefront has one tile of 32 x 32 results and reads both operands' fragments straight from
-// memory, several chunks ahead, without LDS or a barrier: as many wavefronts as there are tiles, each a chain of a
-// few microseconds.  The second reader of a row or column finds it in L1 or L2.  The two backward products of a call are one
-// launch.
+// staging the rest; now 19, of which the score columns are more than half (8.8 without).  Here a wavefront has one tile of
+// 32 x 32 results and reads both operands' fragments straight from memory, several chunks ahead, without LDS or a barrier: as
+// many wavefronts as there are tiles, each a chain of a few microseconds.  The second reader of a row or column finds it in
+// L1 or L2.  The two backward products of a call are one launch.
 //
 // Z and dX are the same sums in the same order as in the kernels named beside each function, bit for bit; dW has the same terms in
 // an order of its own.
