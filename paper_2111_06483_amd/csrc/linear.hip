@@ -1340,19 +1340,19 @@ int linear_bwd_impl(const void* X, const void* dZ, int64_t dZ_rows, const RowsOp
         return SAR_OK;
     };
     const size_t elem = dtype == SAR_F32 ? 4 : 2;
-    if (sar::few_rows_bwd(dtype, n, K, F) && apart(dX, (size_t)n * K * elem, dZ, (size_t)dZ_rows * F * elem) &&
+    SkinnyPlan few_plan;
+    const bool few_split = dtype == SAR_F32 && dx_by_split(n, K, F);
+    const sar::FewBwd few{X, dZ, W, dW, dX, static_cast<float*>(work), n, K, F, slabs_for(n, K, F), few_split,
+                          !few_split && !plan_skinny(F, K, dtype, 0, &few_plan)};
+    if (sar::few_rows_bwd(dtype, few, op != nullptr) && apart(dX, (size_t)n * K * elem, dZ, (size_t)dZ_rows * F * elem) &&
         (!dW || apart(dX, (size_t)n * K * elem, X, (size_t)n * K * elem))) {
         if (dW) {
             const size_t need = (size_t)slabs_for(n, K, F) * K * F * sizeof(float);
             SAR_CHECK_ARG(work != nullptr && work_bytes >= need, "work_bytes=%zu is below the %zu bytes required",
                           work_bytes, need);
         }
-        SkinnyPlan plan;
-        const bool split = dtype == SAR_F32 && dx_by_split(n, K, F);
-        const bool natural = !split && !plan_skinny(F, K, dtype, 0, &plan);
         int slabs = 0;
-        SAR_TRY(sar::few_bwd(dtype, {X, dZ, W, dW, dX, static_cast<float*>(work), n, K, F, slabs_for(n, K, F), split, natural},
-                             op, &slabs, st));
+        SAR_TRY(sar::few_bwd(dtype, few, op, &slabs, st));
         return slabs > 0 ? add_slabs(slabs) : SAR_OK;
     }
     if (dW) {

@@ -39,7 +39,8 @@ struct FewBwd {
     int K, F, most_slabs;
     bool split, natural;
 };
-bool few_rows_bwd(int dtype, int64_t n, int K, int F);
+// Whether the kernels of few rows take the call (formed: its rows are, by RowsOp).
+bool few_rows_bwd(int dtype, const FewBwd& b, bool formed);
 // slabs: partial sums of dW in work that are to be added up; 0: dW is complete.
 int few_bwd(int dtype, const FewBwd& b, const RowsOp* op, int* slabs, hipStream_t st);
 

@@ -790,19 +790,29 @@ static bool small_operands(int64_t n, int K, int F)
     return n * std::max(K, F) < (1 << 30) && (int64_t)K * F < (1 << 28);
 }
 
-// The lines are drawn by tiles of 32 x 32, of which 1024 are one wavefront per SIMD.  The other kernel's wavefronts form `wide`
-// tiles one after the other, so it takes the longer the more these are while the chip has room for all of them side by side;
-// with more tiles than that, reading both operands from memory for each costs more than staging one of them.  us, the other
-// kernel / this one: fp32 with scores, 64 -> 64 (wide 2) 2000 rows 10.1 / 7.4, 20000 17.8 / 9.2; 256 -> 64 (2) 10000 rows
-// 26.0 / 14.5, 20000 26.6 / 24.5; 256 -> 256 (4) 100 rows 39.5 / 18.8, 5000 41.7 / 20.4, 10000 41.9 / 39.7, 20000 59.8 / 67.2;
-// 100 -> 256 (8) 5000 32.1 / 11.8, 10000 32.7 / 21.3, 20000 34.0 / 37.3.  Without: 256 -> 256 500 23.8 / 8.8, 5000 24.8 / 17.8,
-// 10000 25.4 / 27.4; 128 -> 256 (8) 10000 26.3 / 18.0, 20000 27.4 / 27.5.  bf16: 256 -> 256 (4) 500 12.7 / 6.1, 5000 13.7 /
-// 9.8, 10000 14.0 / 15.5; 256 -> 64 (2) 10000 7.8 / 6.4, 20000 8.2 / 9.9.
+// Workgroups of four tiles of 32 x 32: 256 of them are one wavefront per SIMD.
+static int64_t workgroups(int64_t n, int N) { return (n + 32 * kWaves - 1) / (32 * kWaves) * ((N + 31) / 32); }
+
+// The lines are drawn by workgroups.  The other kernel's wavefronts form `wide` tiles one after the other, so it takes the longer
+// the more these are while the chip has room for all of them side by side; with more tiles than that, reading both operands
+// from memory for each costs more than staging one of them.  us, the other kernel / this one: fp32 with scores, 64 -> 64 (wide 2)
+// 2000 rows 10.1 / 7.4, 20000 17.8 / 9.2; 256 -> 64 (2) 10000 rows 26.0 / 14.5, 20000 26.6 / 24.5; 256 -> 256 (4) 100 rows
+// 39.5 / 18.8, 5000 41.7 / 20.4, 10000 41.9 / 39.7, 20000 59.8 / 67.2; 100 -> 256 (8) 5000 32.1 / 11.8, 10000 32.7 / 21.3, 20000
+// 34.0 / 37.3.  Without: 256 -> 256 500 23.8 / 8.8, 5000 24.8 / 17.8, 10000 25.4 / 27.4; 128 -> 256 (8) 10000 26.3 / 18.0, 20000
+// 27.4 / 27.5.  bf16: 256 -> 256 (4) 500 12.7 / 6.1, 5000 13.7 / 9.8, 10000 14.0 / 15.5; 256 -> 64 (2) 10000 7.8 / 6.4, 20000 8.2 /
+// 9.9.  By workgroups and not tiles: a few beyond 256 wait for a round of their own (512 -> 400, bf16 2432 rows 13.6 / 10.0, 2496
+// rows 13.9 / 16.0).  A long contraction is one chain here, and where the other kernel has few tiles as well that one's loads
+// are the wider: 1024 -> 128 and fewer, fp32 27 / 29, bf16 12 / 16.5 (-> 256: 22.5 / 16.3); bf16 of one column tile 512 -> 16
+// 7.7 / 9.9, 256 -> 16 6.4 / 7.1 and, from 8000 rows on, 9.4 / 7.2 (32 -> 16: 4.6 / 4.1 from the fewest on).
 bool few_rows(int dtype, int64_t n, int K, int N, bool scores, int wide)
 {
-    if (K < (dtype == SAR_F32 ? 4 : 8) || !small_operands(n, K, N)) return false;
+    const bool f32 = dtype == SAR_F32;
+    if (K < (f32 ? 4 : 8) || !small_operands(n, K, N)) return false;
     if (scores && (N < 4 || score_lds(K, N) > 160 * 1024)) return false;
-    return (n + 31) / 32 * ((N + 31) / 32) <= (scores ? 320 * (wide + 1) : 512 * wide);
+    const int64_t w = workgroups(n, N);
+    if (K > 512 && N <= 128) return false;
+    if (!f32 && N <= 32 && K > 64 && (w < 64 || K > 256)) return false;
+    return w <= (scores ? 80 * (wide + 1) : 128 * wide);
 }
 
 int few_fwd(int dtype, const FewArgs& g, bool natural, hipStream_t st)
@@ -810,15 +820,55 @@ int few_fwd(int dtype, const FewArgs& g, bool natural, hipStream_t st)
     return dtype == SAR_F32 ? launch_fwd<float>(g, natural, st) : launch_fwd<bf16_t>(g, natural, st);
 }
 
-// (dX tiles as above; dW of as many rows has its own.)  us, the kernels for many rows / this one, dX and dW with the slabs' sum:
-// fp32, formed rows, 64 -> 64 200 rows 18.8 / 8.8, 5000 20.1 / 9.2; 256 -> 256 600 41.0 / 17.8, 2500 43.5 / 23.3, 5000 45.9 /
-// 43.3; 128 -> 256 2500 41.8 / 20.2, 10000 46.7 / 45.0; stored rows, 256 -> 256 2500 38.2 / 19.0, 10000 49.3 / 49.1.  bf16, formed
-// rows, 256 -> 256 600 42.9 / 15.3, 5000 47.7 / 32.3, 10000 51.5 / 55.9; 128 -> 256 10000 48.1 / 33.7; stored, 100 -> 256 2500
-// 40.2 / 13.1, 10000 43.9 / 22.4.  (dX before dW in the grid and dW on half of the chip: 1300 rows 256 -> 256 24.5 -> 18.6.)
-bool few_rows_bwd(int dtype, int64_t n, int K, int F)
+// Partial sums of dW, and the groups of rows of one.
+struct DwPlan {
+    int slabs, groups;
+    int chain() const { return (groups + kWaves - 1) / kWaves; }      // of a wavefront
+};
+static DwPlan plan_dw(int64_t n, int K, int F, bool dX, int most_slabs)
 {
-    if (F < (dtype == SAR_F32 ? 4 : 8) || !small_operands(n, K, F)) return false;
-    return (n + 31) / 32 * ((K + 31) / 32) <= (dtype == SAR_F32 ? 1280 : 2048);
+    const int64_t tiles = (int64_t)((K + 31) / 32) * ((F + 31) / 32), groups = (n + kGroup - 1) / kGroup;
+    // (two groups a wavefront are sooner done than a launch that adds slabs up; beside dX, half of the chip)
+    const int64_t want = groups <= 2 * kWaves ? 1 : std::max<int64_t>(1, (dX ? 256 : 512) / tiles);
+    const int64_t s = std::min<int64_t>({want, (int64_t)most_slabs, (groups + kWaves - 1) / kWaves});
+    const int64_t per = (groups + s - 1) / s;
+    return {(int)((groups + per - 1) / per), (int)per};
+}
+
+// us, the kernels for many rows / this one.  Both products, with the slabs' sum (dX by its workgroups as above, dW of as many
+// rows beside it): fp32, formed rows, 64 -> 64 200 rows 18.8 / 8.8, 5000 20.1 / 9.2; 256 -> 256 600 41.0 / 17.8, 2500 43.5 / 23.3,
+// 5000 45.9 / 43.3; 128 -> 256 2500 41.8 / 20.2, 10000 46.7 / 45.0; stored rows, 256 -> 256 2500 38.2 / 19.0, 10000 49.3 / 49.1.
+// bf16, formed rows, 256 -> 256 600 42.9 / 15.3, 5000 47.7 / 32.3, 10000 51.5 / 55.9; 128 -> 256 10000 48.1 / 33.7; stored, 100 ->
+// 256 2500 40.2 / 13.1, 10000 43.9 / 22.4.  (dX before dW in the grid and dW on half of the chip: 1300 rows 256 -> 256 24.5 -> 18.6.)
+// From 512 columns of dZ on beyond one wavefront per SIMD two share it on long chains: bf16 128 -> 2048 16384 rows 91 / 165, 8192 52 /
+// 44; fp32 100 -> 512 10240 52 / 60.
+// dX alone: the other kernel has the chip to itself too.  fp32 64 -> 128 20480 rows 11.4 / 14.4, 15360 10.9 / 8.6; bf16 512 ->
+// 256 4096 23.8 / 17.1, 64 -> 256 32768 14.3 / 17.5, 16384 13.1 / 9.7; where that kernel passes W through LDS in steps (natural) it
+// has as many wavefronts: 1024 -> 256 2048 rows 10.4 / 17.1, 1024 9.7 / 9.7, 512 -> 512 2432 13.8 / 26.3, 1400 13.9 / 14.7.  Chains
+// of more than 512 values only where they fill the SIMDs: 64 -> 1024 16384 26.0 / 25.8, 3200 21.1 / 25.2, 64 -> 2048 52.8 / 46.2,
+// 39.7 / 45.9.  One column tile: the other kernel has no tiles to go through one after the other.  fp32 32 -> 128 10240 rows 10.7 /
+// 8.6, 4096 7.7 / 8.6; bf16 16384 8.9 / 7.0, 65536 10.8 / 11.5, 6500 6.1 / 7.0; 32 -> 512 16384 12.9 / 15.2; formed rows cost that
+// one a staging of ds for every row (fp32 32 -> 256 4096 14.2 / 12.5, bf16 65536 20.6 / 19.5).
+// dW alone by the groups of 32 rows that a wavefront sums up: eight cost as much as there (fp32 64 -> 512 15360 rows 21.0 / 22.2, 100
+// -> 1024 10240, twenty, 33 / 48; bf16 64 -> 512 16384 19 / 15, 32 -> 512 49152, twelve, 22.2 / 26.3, 256 -> 1024 2848, twelve,
+// 27 / 19).
+bool few_rows_bwd(int dtype, const FewBwd& b, bool formed)
+{
+    const bool f32 = dtype == SAR_F32;
+    const int K = b.K, F = b.F;
+    if (F < (f32 ? 4 : 8) || !small_operands(b.n, K, F)) return false;
+    const int64_t w = workgroups(b.n, K), one = 256, most = f32 ? 320 : 512;
+    if (b.dX && b.dW) return w <= (F <= (f32 ? 256 : 400) ? most : one);
+    if (b.dW) return w <= most && plan_dw(b.n, K, F, false, b.most_slabs).chain() <= (!f32 && K > 64 ? 12 : 8);
+    if (K <= 32 && F > 32) {
+        if (formed) return w <= most;
+        if (F > 1024) return w <= one && (f32 || K <= 16);
+        return w >= 64 && w <= (F < 64 && !f32 ? most : one) && (f32 || F <= 400);
+    }
+    if (f32) return w <= (F <= 32 ? most : one);
+    if (F <= 128) return w <= most;
+    if (F <= 400) return w <= (K > 64 && !b.natural ? most : one);
+    return w <= one && !b.natural && (F <= 512 || w > 192);
 }
 
 int few_bwd(int dtype, const FewBwd& b, const RowsOp* op, int* slabs, hipStream_t st)
@@ -827,12 +877,9 @@ int few_bwd(int dtype, const FewBwd& b, const RowsOp* op, int* slabs, hipStream_
     DwArgs w{b.X, b.dZ, b.work, b.n, 0, b.K, b.F, 0};
     *slabs = 0;
     if (b.dW) {
-        const int64_t tiles = (int64_t)((b.K + 31) / 32) * ((b.F + 31) / 32), groups = (b.n + kGroup - 1) / kGroup;
-        // (two groups a wavefront are sooner done than a launch that adds slabs up; beside dX, half of the chip)
-        const int64_t want = groups <= 2 * kWaves ? 1 : std::max<int64_t>(1, (b.dX ? 256 : 512) / tiles);
-        const int64_t s = std::min<int64_t>({want, (int64_t)b.most_slabs, (groups + kWaves - 1) / kWaves});
-        w.groups = (int)((groups + s - 1) / s);
-        w.slabs = (int)((groups + w.groups - 1) / w.groups);
+        const DwPlan p = plan_dw(b.n, b.K, b.F, b.dX != nullptr, b.most_slabs);
+        w.groups = p.groups;
+        w.slabs = p.slabs;
         if (w.slabs == 1)
             w.out = b.dW;
         else

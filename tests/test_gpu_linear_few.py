@@ -114,7 +114,8 @@ def test_result_over_an_operand():
 
 
 @pytest.mark.parametrize("n,K,F,dtype", [(8192, 256, 512, torch.bfloat16), (16384, 128, 400, torch.bfloat16), (2560, 512, 384, torch.float32),
-                                         (20480, 64, 256, torch.float32), (1500, 256, 256, torch.bfloat16)])
+                                         (20480, 64, 256, torch.float32), (1500, 256, 256, torch.bfloat16), (8192, 128, 2048, torch.bfloat16),
+                                         (8192, 256, 400, torch.bfloat16), (2048, 512, 1024, torch.float32), (2560, 512, 256, torch.float32)])
 @pytest.mark.parametrize("alone", [True, False])
 def test_weight_gradients_of_long_slabs(n, K, F, dtype, alone):
     """Many columns leave few slabs, of hundreds of rows for a wavefront.  Normal operands: a result is of size n^1/2, and so is
@@ -169,6 +170,51 @@ def test_values_that_are_not_split(K, H, D, dtype, where, value):
         sar.sar_linear_bwd(None, E[:n], W, None, dX, None)
         return Z, dX
 
+    assert "k_few" in gu.kernels_of(lambda: run(96)) and "k_few" not in gu.kernels_of(lambda: run(MANY))
     for few, many in zip(run(96), run(MANY)):
         assert torch.equal(torch.isnan(few), torch.isnan(many[:96]))
         assert torch.equal(few.float().nan_to_num(7.0, 1.0, -1.0), many[:96].float().nan_to_num(7.0, 1.0, -1.0))
+
+
+LINES = [  # rows, K, F, what is wanted, taken by the kernels of few rows; lines by dZ's columns and by the products wanted
+    (torch.float32, 10_240, 128, 256, "both", True), (torch.float32, 10_240, 128, 260, "both", False),
+    (torch.float32, 8_192, 128, 260, "both", True), (torch.bfloat16, 8_192, 256, 400, "both", True),
+    (torch.bfloat16, 8_192, 256, 408, "both", False), (torch.bfloat16, 4_096, 256, 408, "both", True),
+    (torch.float32, 10_240, 128, 32, "dX", True), (torch.float32, 10_240, 128, 36, "dX", False),
+    (torch.float32, 8_192, 128, 36, "dX", True), (torch.float32, 8_192, 32, 36, "dX", True),
+    (torch.float32, 8_000, 32, 36, "dX", False), (torch.float32, 100, 32, 32, "dX", True),
+    (torch.float32, 100, 32, 1_028, "dX", True), (torch.bfloat16, 65_536, 32, 63, "dX", True),
+    (torch.bfloat16, 65_536, 32, 64, "dX", False), (torch.bfloat16, 32_768, 32, 400, "dX", True),
+    (torch.bfloat16, 32_768, 32, 408, "dX", False), (torch.bfloat16, 100, 16, 1_032, "dX", True),
+    (torch.bfloat16, 8_192, 256, 128, "dX", True), (torch.bfloat16, 16_384, 128, 136, "dX", True),
+    (torch.bfloat16, 32_768, 64, 136, "dX", False), (torch.bfloat16, 16_384, 64, 136, "dX", True),
+    (torch.bfloat16, 2_048, 1_024, 256, "dX", False), (torch.bfloat16, 16_384, 64, 520, "dX", True),
+    (torch.bfloat16, 12_288, 64, 520, "dX", False), (torch.bfloat16, 6_500, 64, 512, "dX", True),
+    (torch.float32, 20_480, 64, 256, "dW", True), (torch.float32, 10_240, 128, 400, "dW", False),
+    (torch.bfloat16, 49_152, 32, 400, "dW", False), (torch.bfloat16, 2_848, 256, 1_024, "dW", True),
+    (torch.float32, 1_000, 516, 128, "Z", False), (torch.float32, 1_000, 516, 130, "Z", True),
+    (torch.bfloat16, 1_000, 520, 128, "Z", False), (torch.bfloat16, 1_000, 512, 128, "Z", True),
+    (torch.bfloat16, 8_192, 256, 32, "Z", True), (torch.bfloat16, 8_000, 256, 32, "Z", False),
+    (torch.bfloat16, 8_192, 264, 32, "Z", False), (torch.bfloat16, 100, 64, 32, "Z", True),
+    (torch.bfloat16, 2_432, 512, 400, "Z", True), (torch.bfloat16, 2_496, 512, 400, "Z", False)]
+
+
+@pytest.mark.parametrize("dtype,n,K,F,what,few", LINES)
+def test_both_sides_of_a_line(dtype, n, K, F, what, few):
+    g = torch.Generator(device="cuda").manual_seed(n + K + F)
+    draw = lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+    X, dZ, W = draw(n, K).to(dtype), draw(n, F).to(dtype), draw(K, F) / K ** 0.5
+    Z, dX, dW = torch.empty_like(dZ), torch.empty_like(X), torch.zeros(K, F, device="cuda")
+    work = torch.empty(sar.sar_linear_workspace_bytes(n, K, F) // 4, device="cuda")
+    x, d, w = X.double(), dZ.double(), W.double()
+    if what == "Z":
+        run, results = lambda: sar.sar_linear_fwd(X, W, Z), [(Z, x @ w, K)]
+    else:
+        run = lambda: sar.sar_linear_bwd(X, dZ, W, None if what == "dX" else dW, None if what == "dW" else dX, work)
+        results = [(dX, d @ w.T, F)] * (what != "dW") + [(dW, x.T @ d, n)] * (what != "dX")
+    assert ("k_few" in gu.kernels_of(run)) == few
+    dW.zero_()
+    run()
+    for got, want, length in results:      # (stored bf16: half a unit of the value; sums as above, at most 32 rows' and their sums')
+        tol = 2.0 ** -8 if got.dtype == torch.bfloat16 else max(2.0, min(length, 1024) ** 0.5) * 2.0 ** -24
+        assert float((got.double() - want).norm() / want.norm()) < tol
