@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd(FwdArgs a, PtrTab zt
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = (int)a.rows[r];
         const float s2 = a.s[(int64_t)i * a.ldh + lm.h] * kLog2e;
         SoftState<VEC> st;
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd(BwdArgs tabs, BwdSca
     // the first two links (and the output row) of the NEXT source are read while this one is
     // processed, the list entry of the one after that as well.
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave;
+    int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave;
     struct Ahead {
         uint32_t id;
         int beg, end;

@@ -514,9 +514,9 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
         hubs = a.n_hub;
         shared_rows(std::integral_constant<int, NW>{}, 0, hubs, block);
     }
-    shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long, hubs > 0 ? from_behind(block, n_blocks) : block);
+    shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long, from_behind(hubs, block, n_blocks));
     const int64_t n_waves = (int64_t)n_blocks * NW;
-    for (int64_t r = a.n_long + from_behind(block, n_blocks) * NW + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, block, n_blocks) * NW + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         FwdState<LPH> st;
         init(st, i, true);
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.rows[r]);
         const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
         BwdAcc4 ac;

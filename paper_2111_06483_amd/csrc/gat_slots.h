@@ -320,7 +320,7 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int n_slots, in
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(block, n_blocks) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, block, n_blocks) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
         State st;
         init(st, i, true);
@@ -625,7 +625,7 @@ __device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int n_slots,
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(block, n_blocks) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, block, n_blocks) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.rows[r]);
         const int q = ALL ? (int)(id >> a.tag_shift) : 0, j = (int)(id & mask);
         BwdAcc4 ac;

@@ -28,7 +28,13 @@ constexpr int kMaxPersistentWGs = 256 * 8;   // 256 CUs x 8 resident workgroups
 // A workgroup's place among those that take the rows after the shared ones: the last first.  Lists go from long rows to short
 // ones, so the workgroups that had the longest of the shared rows would have the longest of the others as well (forward,
 // 4 x 64 bf16, 1.5 M edges 287 us dealt from the front, 219 from behind; 8 x 32 bf16, 9 M edges, given scores 1055 and 965).
-__device__ inline int64_t from_behind(int64_t block, int64_t n_blocks) { return n_blocks - 1 - block; }
+// Where no row is shared there is nothing to balance, and the workgroups that start last would have one row more (uniform
+// graphs, steps of GraphSage layers: 60 thousand nodes of 35 edges, 200 bf16 values 308 us from behind, 303 from the front, 200
+// thousand of 60, 128 fp32 589 and 582; attention 8 x 32 bf16, 100 thousand of 20, 553 and 547).
+__device__ inline int64_t from_behind(int64_t n_shared, int64_t block, int64_t n_blocks)
+{
+    return n_shared > 0 ? n_blocks - 1 - block : block;
+}
 
 // Part `part` of `parts` of a row's edges [beg, end): the part's first 64 edges start at beg, and the value returned is how far
 // on the next 64 do.  Even shares in whole eights; dealt out 64 at a time a row of 130 edges was 64 + 64 + 2 to four

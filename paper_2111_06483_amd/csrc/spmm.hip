@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab,
     }
     // remaining rows: one wavefront each
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         const int i = (int)a.rows[r];
         float acc[VEC] = {};
         add_rows<T, G, M, RAG>(acc, a, ztab, a.indptr[i], a.indptr[i + 1], 0, 1, lm);
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_spmm_bwd_all(SpmmArgs a, Bwd
         __syncthreads();
     }
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
+    for (int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows; r += n_waves) {
         SpmmArgs la = a;
         const int j = locate(r, la);
         float acc[VEC] = {};
