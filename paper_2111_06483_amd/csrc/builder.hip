@@ -159,6 +159,13 @@ public:
         }
         (void)hipFree(p);
     }
+    // Whether memory of that size is kept once the builder call that uses it gives it up, and not handed to the driver then or
+    // with the call's own handle.
+    bool keeps(int dev, size_t size)
+    {
+        std::lock_guard<std::mutex> lock(m_);
+        return size <= kPoolMost / 4 && devices_[dev].handles > 1;
+    }
     // A page of pinned host memory for what a call's kernels report to the host and what it sends them: through pageable
     // memory every copy waits for the stream (15.2M edges: twelve copies, the build 1534 us and now 1431).  At most kHostPages idle ones.
     static constexpr size_t kHostPage = 192 << 10;
@@ -268,7 +275,7 @@ struct DeviceTemps {
     }
     // Several arrays as one piece, where the pool keeps pieces of that size.  A program that frees its only handle gives
     // every piece back to the driver, 240 us each once the few ten MB that the runtime holds on to are full (2.4 million nodes, 8
-    // million edges of which an eighth is kept, built and freed: 7.8 ms with a piece for every array, now 6.8).
+    // million edges of which an eighth is kept, built and freed: 7.8 ms with a piece for every array, 6.8 with these).
     struct Part {
         void** out;
         size_t bytes;
@@ -298,11 +305,12 @@ struct DeviceTemps {
     {
         return {reinterpret_cast<void**>(out), (size_t)std::max<int64_t>(count, 1) * sizeof(T)};
     }
-    // Scratch that the call can do without (`spare`, null where there is no room): it makes way for whatever else is asked for.
+    // Scratch that the call can do without (`spare`, null where there is no room or the pool would not keep it): it makes way for
+    // whatever else is asked for.
     void alloc_spare(size_t bytes)
     {
         spare_bytes = Pool::round(bytes);
-        if (pool().try_take(dev, &spare, spare_bytes) != hipSuccess) spare = nullptr;
+        if (!pool().keeps(dev, spare_bytes) || pool().try_take(dev, &spare, spare_bytes) != hipSuccess) spare = nullptr;
     }
     void drop_spare()
     {
@@ -554,8 +562,11 @@ struct EdgeSource {
 };
 
 // The same edges as the counting pass left them: (key, value), key ~0 where the edge is not kept.  Where all keys are one
-// pass, they fit 1 GiB and nothing else needs the room, the scatter reads these 8 bytes instead of the edge list, and gathers no
-// codes (15.2M edges: count and scatter 153 + 194 us, so 198 + 70).
+// pass, the pool keeps the memory and nothing else needs the room, the scatter reads these 8 bytes instead of the edge list, and
+// gathers no codes (15.2M edges: count and scatter 153 + 194 us, so 198 + 70).  That is some 15% of a build, and less than what the
+// driver takes for memory that is not kept: the only handle built and freed, of 8 million edges an eighth kept, 4.6 ms with and
+// 1.7 without, all of 2 million 1.8 and 0.9; beside other handles, from more than 256 MiB on (33 million edges), 100 million 17 to 75
+// ms from run to run and 15.6, of 60 million an eighth 3.3 to 4.4 and 3.9.
 struct StoredEdges {
     const uint2* edges;
     int64_t E;
@@ -573,7 +584,6 @@ struct StoredEdges {
         }
     }
 };
-constexpr int64_t kMostStored = (int64_t)1 << 27;
 
 constexpr int kEdgesAhead = 4;
 
@@ -2140,7 +2150,7 @@ int build_from_edges(sar_blocks* h, const void* src, const void* dst, int idx_by
         const bool narrow = plan.w + vbits <= 32;
         int32_t* counts = nullptr;
         SAR_TRY(tmp.alloc(&counts, (int64_t)plan.n_buckets() * plan.n_tiles + 1));
-        if (n_rows_all <= kKeysPerPass && E <= kMostStored) tmp.alloc_spare((size_t)E * sizeof(uint2));
+        if (n_rows_all <= kKeysPerPass) tmp.alloc_spare((size_t)E * sizeof(uint2));
         int32_t base = 0;
         for (int64_t key0 = 0; key0 < std::max<int64_t>(n_rows_all, 1); key0 += kKeysPerPass) {
             const int64_t nk = std::min(kKeysPerPass, n_rows_all - key0);

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2111_06483_amd import sar
+from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 MB = 1 << 20
@@ -22,9 +23,9 @@ def free_bytes():
     return torch.cuda.mem_get_info()[0]
 
 
-def no_other_handle():
+def no_other_handle(but=None):
     gc.collect()
-    assert not [o for o in gc.get_objects() if type(o) is sar.Blocks and o._h is not None]
+    assert not [o for o in gc.get_objects() if type(o) is sar.Blocks and o._h is not None and o is not but]
 
 
 def test_a_failed_build_of_the_only_handle_keeps_nothing():
@@ -62,10 +63,13 @@ def index_arrays(b):
 
 
 class Full:
-    """All of the device's memory but what room() leaves."""
+    """All of the device's memory but what room() leaves, and one handle."""
+
+    def __init__(self, handle):
+        self.handle = handle
 
     def __enter__(self):
-        no_other_handle()
+        no_other_handle(self.handle)
         sar.sar_release_memory()
         torch.cuda.empty_cache()
         self.last = None
@@ -98,7 +102,7 @@ class Full:
 def test_builds_with_little_room():
     """24 Mi edges: 192 MiB of what the counting pass may leave for the scatter, and 96 each of sources, pairs and derived
     indexes.  Memory that only speeds a build up is done without, and the arrays are the same; a build that does not fit
-    says so and leaves no error for the next one."""
+    says so and leaves no error for the next one.  (Beside a handle that lives: a device's only one leaves nothing.)"""
     fused = sar.SAR_BUILD_TRANSPOSE | sar.SAR_BUILD_FUSED
     src, dst, part = edges(24 * MB, 100_000)
     small = src.to(torch.int32), dst.to(torch.int32)
@@ -109,7 +113,8 @@ def test_builds_with_little_room():
         b = sar.sar_blocks_build(src, dst, part, P, 0, flags)
         cases.append((P, flags, room, part, index_arrays(b)))
         b.close()
-    with Full() as full:
+    living = sar.sar_blocks_build(src[:1000], dst[:1000], part, 1, 0, 0)
+    with Full(living) as full:
         for P, flags, room, part, want in cases:
             for s, d in ((src, dst), small):
                 full.room(room)
@@ -125,6 +130,32 @@ def test_builds_with_little_room():
             sar.sar_blocks_build(src, dst, part, 1, 0, 0)
         assert "hipMalloc" in str(e.value)
         sar.sar_blocks_build(src[:1000], dst[:1000], part, 1, 0, 0).close()
+    living.close()
+
+
+def test_edges_are_stored_where_the_memory_is_kept():
+    """A device's only handle, or edges of more than 256 MiB in (key, value) pairs of 8 bytes: the memory would go to the driver
+    and come from it again, which takes longer than gathering twice.  Both ways to the same arrays."""
+    no_other_handle()
+    most = 32 * MB                                        # edges
+    src, dst, part = edges(most + 1, 100_000)
+    part = torch.arange(100_000, device="cuda", dtype=torch.int32) % 16
+    arrays = []
+    for E, alive, stored in ((200_001, False, False), (200_001, True, True), (most, False, False), (most, True, True),
+                             (most + 1, True, False)):
+        other = sar.sar_blocks_build(src[:1000], dst[:1000], part, 16, 0, 0) if alive else None
+
+        def build():
+            b = sar.sar_blocks_build(src[:E], dst[:E], part, 16, 0, sar.SAR_BUILD_TRANSPOSE)
+            arrays.append(index_arrays(b))
+            b.close()
+
+        names = [n for n in gu.kernels_of(build).split("\n") if "k_bucket_scatter" in n]
+        assert len(names) == 1 and ("StoredEdges" in names[0]) == stored, (E, alive, names)
+        if other:
+            other.close()
+    for x, y in (arrays[0:2], arrays[2:4]):
+        assert all(torch.equal(a, b) for a, b in zip(x, y))
 
 
 def test_keys_in_several_passes():
