@@ -17,6 +17,7 @@
 #include <utility>
 #include <vector>
 
+#include "global_ptr.h"
 #include "sar_internal.h"
 
 namespace sar {
@@ -655,16 +656,16 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Src in, int64
 
 // What the builder's kernels need of every block, in device memory.
 struct BlkDev {
-    const int32_t* indptr;
-    const int32_t* indices;
+    sar::GlobalPtr<const int32_t> indptr;
+    sar::GlobalPtr<const int32_t> indices;
     int64_t n_src, coff;     // sources of the block, and of the blocks before it
     int64_t nnz, nnz0;       // edges of the block, and of the blocks before it
     int64_t tile0;           // first tile of the block's edges (k_block_count / k_block_scatter)
     int64_t s_tile0;         // first tile of its sources in the launch lists' counts
-    uint32_t* rows;          // launch lists
-    uint32_t* t_rows;
-    int32_t* t_indptr;
-    int32_t* t_rank;
+    sar::GlobalPtr<uint32_t> rows;          // launch lists
+    sar::GlobalPtr<uint32_t> t_rows;
+    sar::GlobalPtr<int32_t> t_indptr;
+    sar::GlobalPtr<int32_t> t_rank;
 };
 
 // The edges of all blocks as pairs (coff[q] + source, destination): a tile lies inside one block.
@@ -1450,7 +1451,7 @@ __global__ __launch_bounds__(kThreads) void k_class_place(ListIn in, Lists l, in
     in.place(l, q, tile);
     const int32_t* off = in.offsets(l, q, n);
     const int* start = starts + (l == Lists::kRows || l == Lists::kSources ? q * sar::kNumClasses : 0);
-    uint32_t* out = l == Lists::kRows ? in.blk[q].rows : l == Lists::kSources ? in.blk[q].t_rows : out_all;
+    uint32_t* out = l == Lists::kRows ? in.blk[q].rows.as<uint32_t>() : l == Lists::kSources ? in.blk[q].t_rows.as<uint32_t>() : out_all;
     const uint32_t tag = l == Lists::kAllSources ? (uint32_t)q << tag_shift : 0u;
     int c[kPlacePer], at[kPlacePer];
     tile_classes(off, n, tile, c, at, cnt);
@@ -1541,8 +1542,8 @@ __global__ __launch_bounds__(kThreads) void k_single_list(SingleTabs tabs, const
                                                           int64_t n_single, int32_t* __restrict__ s_dst,
                                                           uint32_t* __restrict__ s_src, int32_t* __restrict__ s_row)
 {
-    __shared__ const int32_t* ip[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* rk[SAR_MAX_BLOCKS];
+    __shared__ sar::GlobalPtr<const int32_t> ip[SAR_MAX_BLOCKS];
+    __shared__ sar::GlobalPtr<const int32_t> rk[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         ip[threadIdx.x] = tabs.t_indptr[threadIdx.x];
         rk[threadIdx.x] = tabs.t_rank[threadIdx.x];
@@ -1633,8 +1634,8 @@ __global__ __launch_bounds__(kThreads) void k_fused_copy(const BlkDev* __restric
                                                          uint32_t* __restrict__ f_indices)
 {
     constexpr int kTurn = 4;
-    __shared__ const int32_t* s_indices[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_indptr[SAR_MAX_BLOCKS];
+    __shared__ sar::GlobalPtr<const int32_t> s_indices[SAR_MAX_BLOCKS];
+    __shared__ sar::GlobalPtr<const int32_t> s_indptr[SAR_MAX_BLOCKS];
     if ((int)threadIdx.x < P) {
         s_indices[threadIdx.x] = blk[threadIdx.x].indices;
         s_indptr[threadIdx.x] = blk[threadIdx.x].indptr;

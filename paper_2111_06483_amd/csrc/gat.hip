@@ -98,8 +98,8 @@ __device__ inline void state_merge(SoftState<VEC>& st, float om2, float ol, cons
 // of `shares` of them.  s2 is the destination score half of this
 // lane's head in log2 units.
 template <typename T, int G, bool ALL>
-__device__ inline void fwd_edges(SoftState<Vec<T>::N>& st, const FwdArgs& a, const void* const* ztab,
-                                 const float* const* ttab, int beg, int end, int share, int shares,
+__device__ inline void fwd_edges(SoftState<Vec<T>::N>& st, const FwdArgs& a, const GlobalPtr<const void>* ztab,
+                                 const GlobalPtr<const float>* ttab, int beg, int end, int share, int shares,
                                  const LaneMap<T, G>& lm, float s2, const float (&al)[Vec<T>::N], bool fly,
                                  bool pow2)
 {
@@ -126,7 +126,7 @@ __device__ inline void fwd_edges(SoftState<Vec<T>::N>& st, const FwdArgs& a, con
                     const T* zb;
                     const float* tb;
                     if constexpr (ALL) {
-                        zb = static_cast<const T*>(ztab[id >> a.tag_shift]);
+                        zb = ztab[id >> a.tag_shift].template as<const T>();
                         tb = ttab[id >> a.tag_shift];
                     } else {
                         zb = static_cast<const T*>(a.Z);
@@ -224,8 +224,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_fwd(FwdArgs a, PtrTab zt
                                                             int P)
 {
     constexpr int VEC = Vec<T>::N;
-    __shared__ const void* ztab[SAR_MAX_BLOCKS];
-    __shared__ const float* ttab[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> ztab[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> ttab[SAR_MAX_BLOCKS];
     __shared__ float part_acc[kWavesPerWG][G][VEC];
     __shared__ float part_ml[kWavesPerWG][G][2];
     if constexpr (ALL) {
@@ -1410,8 +1410,8 @@ __global__ __launch_bounds__(256) void k_bwd_zero_rows(f256::BwdTabs tabs, const
                                                        int64_t r_begin, int64_t r_end, int H, int tag_shift)
 {
     constexpr int kPieces = f256::kF * (int)sizeof(T) / 16;   // 16-byte pieces of a row
-    __shared__ void* s_dZ[SAR_MAX_BLOCKS];
-    __shared__ float* s_dt[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<void> s_dZ[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<float> s_dt[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_dZ[threadIdx.x] = tabs.dZ[threadIdx.x];
         s_dt[threadIdx.x] = tabs.dt[threadIdx.x];
@@ -1424,7 +1424,7 @@ __global__ __launch_bounds__(256) void k_bwd_zero_rows(f256::BwdTabs tabs, const
         const int piece = (int)(p % kPieces);
         const int q = ALL ? (int)(id >> tag_shift) : 0;
         const int64_t j = (int64_t)(id & mask);
-        reinterpret_cast<uint4*>(static_cast<T*>(s_dZ[q]) + j * f256::kF)[piece] = make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint4*>(s_dZ[q].template as<T>() + j * f256::kF)[piece] = make_uint4(0u, 0u, 0u, 0u);
         if (piece < H && s_dt[q]) s_dt[q][j * H + piece] = 0.f;
     }
 }

@@ -763,13 +763,13 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
     static_assert(S * kAhead <= kWave, "one lane per (source, edge read ahead)");
     static_assert((1 << kNarrowMaxClass) <= kAhead, "this kernel's sources have fewer than kAhead edges");
     __shared__ float part[kWavesPerWG][kWave][4];
-    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
-    __shared__ void* s_dZ[SAR_MAX_BLOCKS];
-    __shared__ float* s_dt[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ix[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<void> s_dZ[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<float> s_dt[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ip[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ix[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_rank[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
         s_t[threadIdx.x] = tabs.t[threadIdx.x];
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
             jo[u] = __builtin_amdgcn_readlane(m0.jo, u * kAhead);
             rounds = max(rounds, end[u] - beg[u]);
             zr[u] = typename Row4<T>::Raw{};
-            if (have[u]) zr[u] = load_lane<T, PAD>(static_cast<const T*>(s_Z[q[u]]) + (int64_t)j[u] * ld, foff, on);
+            if (have[u]) zr[u] = load_lane<T, PAD>(s_Z[q[u]].template as<const T>() + (int64_t)j[u] * ld, foff, on);
         });
         float t2[S], dz[S][4];
         static_for<S>([&](auto uu) {
@@ -948,7 +948,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
                     v[x] = fmaf(dt, al[x], dz[u][x]);
                     dal[x] = fmaf(dt, zj[x], dal[x]);
                 }
-                store_lane<T, PAD>(static_cast<T*>(s_dZ[q[u]]) + (int64_t)jo[u] * ld, foff, on, v);
+                store_lane<T, PAD>(s_dZ[q[u]].template as<T>() + (int64_t)jo[u] * ld, foff, on, v);
                 if (k == 0 && s_dt[q[u]]) s_dt[q[u]][(int64_t)jo[u] * ldh + h] = dt;
             }
         });
@@ -998,10 +998,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
     constexpr int B = LPH >= 8 ? 8 : 4;
     static_assert(B <= LPH, "a sub-batch must fit a head group");
     __shared__ float part[kWavesPerWG][kWave][4];
-    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
-    __shared__ void* s_dZ[SAR_MAX_BLOCKS];
-    __shared__ float* s_dt[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<void> s_dZ[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<float> s_dt[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
         s_t[threadIdx.x] = tabs.t[threadIdx.x];
@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
                 q[K] = (int)(id >> a.tag_shift);
                 row[K] = __builtin_amdgcn_readlane(cur.row, e);
                 rg[K] = load_lane<T, PAD>(Gp + (int64_t)i * ld, foff, on);
-                rz[K] = load_lane<T, PAD>(static_cast<const T*>(s_Z[q[K]]) + (int64_t)(id & mask) * ld, foff, on);
+                rz[K] = load_lane<T, PAD>(s_Z[q[K]].template as<const T>() + (int64_t)(id & mask) * ld, foff, on);
             });
             // lane k speaks for slot k
             const bool valid = k < nb;
@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
                     v[x] = fmaf(dk, al[x], ak * g[x]);
                     dal[x] = fmaf(dk, z[x], dal[x]);
                 }
-                if (K < nb) store_lane<T, PAD>(static_cast<T*>(s_dZ[q[K]]) + (int64_t)row[K] * ld, foff, on, v);
+                if (K < nb) store_lane<T, PAD>(s_dZ[q[K]].template as<T>() + (int64_t)row[K] * ld, foff, on, v);
             });
         }
         cur = nxt;

@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
 {
     constexpr int B = kBatch, kSlots = kWave / LPH;
     static_assert(B <= LPH, "a batch must fit a head group");
-    __shared__ const T* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const T> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_Z[threadIdx.x] = static_cast<const T*>(tabs.Z[threadIdx.x]);
         s_t[threadIdx.x] = tabs.t[threadIdx.x];
@@ -128,14 +128,14 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
                 if (e0 >= len) continue;          // (the rows beside this one go on)
                 const uint32_t next = a.indices[beg + min(e0 + B + k, last)];
                 const int64_t at = (int64_t)(mine & mask);
-                const uint64_t row = reinterpret_cast<uint64_t>(s_Z[mine >> a.tag_shift] + at * a.ld);
+                const uint64_t row = s_Z[mine >> a.tag_shift].bits + (uint64_t)(at * a.ld) * sizeof(T);
                 typename Row4<T>::Raw raw[B];
                 const Spread<LPH, LPH <= 32> lo((uint32_t)row), hi((uint32_t)(row >> 32));
                 static_for<B>([&](auto kk) {
                     constexpr int K = decltype(kk)::value;
                     const uint64_t from = (uint64_t)(uint32_t)lo.template of_int<K>() |
                                           (uint64_t)(uint32_t)hi.template of_int<K>() << 32;
-                    raw[K] = load_lane<T, PAD>(reinterpret_cast<const T*>(from), foff, on);
+                    raw[K] = load_lane<T, PAD>(GlobalPtr<const T>::at(from), foff, on);
                 });
                 zero_behind(raw, len - e0);
                 const bool valid = k < B && e0 + k < len;
@@ -260,13 +260,13 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
     constexpr bool SYNC = true;
     static_assert(B <= LPH && kLanes <= kWave, "a batch must fit a head group");
     __shared__ float part[kWaves<SYNC>][kWave][4];
-    __shared__ const T* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
-    __shared__ T* s_dZ[SAR_MAX_BLOCKS];
-    __shared__ float* s_dt[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ix[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const T> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<T> s_dZ[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<float> s_dt[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ip[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ix[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_rank[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_Z[threadIdx.x] = static_cast<const T*>(tabs.Z[threadIdx.x]);
         s_t[threadIdx.x] = tabs.t[threadIdx.x];

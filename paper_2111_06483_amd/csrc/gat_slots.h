@@ -145,7 +145,7 @@ struct State {
 };
 
 template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
-__device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_Z, const float* const* s_t,
+__device__ inline void fwd_chunk(State& st, const FwdP& a, const GlobalPtr<const void>* s_Z, const GlobalPtr<const float>* s_t,
                                  uint32_t mine, int cnt, int n_slots, const Place<LPH, RAG>& p, float s2,
                                  const float (&al)[4])
 {
@@ -159,7 +159,7 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
             raw[K] = typename Row4<T>::Raw{};
             if (k0 + K * n_slots < cnt) {          // uniform: some slot has an edge here
                 const uint32_t id = (uint32_t)__shfl((int)mine, min(k0 + K * n_slots + p.slot, cnt - 1));
-                const T* zb = static_cast<const T*>(ALL ? s_Z[id >> a.tag_shift] : a.Z);
+                const T* zb = ALL ? s_Z[id >> a.tag_shift].template as<const T>() : static_cast<const T*>(a.Z);
                 if (p.on) raw[K] = load_raw<T, RAG>(zb + (int64_t)(id & mask) * a.ld + p.foff);
             }
         });
@@ -181,7 +181,7 @@ __device__ inline void fwd_chunk(State& st, const FwdP& a, const void* const* s_
             });
         } else {
             const uint32_t my = (uint32_t)__shfl((int)mine, valid ? my_e : 0);
-            const float* tb = ALL ? s_t[my >> a.tag_shift] : a.t;
+            const float* tb = ALL ? s_t[my >> a.tag_shift].template as<const float>() : a.t;
             tv = tb[(int64_t)(my & mask) * a.ldh + p.h];
         }
         const float e2 = valid ? leaky2(fmaf(tv, kLog2e, s2), a.slope) : -INFINITY;
@@ -223,8 +223,8 @@ template <typename T, int LPH, bool ALL, bool FLY, bool RAG>
 __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int n_slots, int block, int n_blocks)
 {
     __shared__ float part[kWavesPerWG][kWave][6];
-    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
     if constexpr (ALL) {
         if (threadIdx.x < SAR_MAX_BLOCKS) {
             s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
@@ -649,13 +649,13 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
     constexpr int kMost = 1 << kNarrowMaxClass;          // this kernel's sources have fewer edges
     constexpr int kRounds = (kMost - 1 + B - 1) / B;
     __shared__ float part[kWavesPerWG][kWave][4];
-    __shared__ const void* s_Z[SAR_MAX_BLOCKS];
-    __shared__ const float* s_t[SAR_MAX_BLOCKS];
-    __shared__ void* s_dZ[SAR_MAX_BLOCKS];
-    __shared__ float* s_dt[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_ix[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> s_Z[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const float> s_t[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<void> s_dZ[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<float> s_dt[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ip[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ix[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_rank[SAR_MAX_BLOCKS];
     if (threadIdx.x < SAR_MAX_BLOCKS) {
         s_Z[threadIdx.x] = tabs.Z[threadIdx.x];
         s_t[threadIdx.x] = tabs.t[threadIdx.x];
@@ -717,7 +717,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
         float zj[4];
         {
             typename Row4<T>::Raw zr{};
-            if (m0.cnt > 0 && p.on) zr = load_raw<T, RAG>(static_cast<const T*>(s_Z[m0.q]) + (int64_t)m0.j * a.ld + p.foff);
+            if (m0.cnt > 0 && p.on) zr = load_raw<T, RAG>(s_Z[m0.q].template as<const T>() + (int64_t)m0.j * a.ld + p.foff);
             Row4<T>::unpack(zr, zj);
             p.own_only(zj);
         }
@@ -780,7 +780,7 @@ __device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int n_slots, 
                 v[x] = fmaf(dt, al[x], dz[x]);
                 dal[x] = fmaf(dt, zj[x], dal[x]);
             }
-            if (p.on) store4<T, RAG>(static_cast<T*>(s_dZ[m0.q]) + (int64_t)m0.jo * a.ld + p.foff, v);
+            if (p.on) store4<T, RAG>(s_dZ[m0.q].template as<T>() + (int64_t)m0.jo * a.ld + p.foff, v);
             if (p.k_pos == 0 && s_dt[m0.q]) s_dt[m0.q][(int64_t)m0.jo * a.ldh + p.h] = dt;
         }
         m0 = m1;

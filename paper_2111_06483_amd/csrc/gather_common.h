@@ -14,6 +14,8 @@
 
 #include <algorithm>
 
+#include "global_ptr.h"
+
 namespace sar {
 
 struct bf16_t {

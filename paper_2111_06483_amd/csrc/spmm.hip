@@ -114,7 +114,7 @@ struct RowLanes {
 // Adds the rows of KU edges per lane group into acc: edges k0 + k SLOTS + slot of the chunk whose
 // ids the lanes hold in `mine`.  FULL: all of them are below cnt.
 template <typename T, int G, Mode M, bool RAG, int KU, bool FULL>
-__device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab, uint32_t mine,
+__device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, const GlobalPtr<const void>* ztab, uint32_t mine,
                                  int k0, int cnt, const RowLanes<T, G, RAG>& lm)
 {
     constexpr int VEC = Vec<T>::N;
@@ -133,7 +133,7 @@ __device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, con
             const uint32_t j = id & mask;
             const T* base;
             if constexpr (M == Mode::kAll)
-                base = static_cast<const T*>(ztab[id >> a.tag_shift]);
+                base = ztab[id >> a.tag_shift].template as<const T>();
             else
                 base = static_cast<const T*>(a.Z);
             raw[k] = lm.load(base + (int64_t)j * a.ld + lm.off);
@@ -164,7 +164,7 @@ __device__ inline void add_batch(float (&acc)[Vec<T>::N], const SpmmArgs& a, con
 // waits for the chain in front of them, so what counts is how many wavefronts are resident (the same
 // rows: 1149 us with four, 1257 with eight and their registers).
 template <typename T, int G, Mode M, bool RAG>
-__device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, const void* const* ztab,
+__device__ inline void add_rows(float (&acc)[Vec<T>::N], const SpmmArgs& a, const GlobalPtr<const void>* ztab,
                                 int beg, int end, int share, int shares, const RowLanes<T, G, RAG>& lm)
 {
     constexpr int SLOTS = kWave / G;
@@ -231,7 +231,7 @@ template <typename T, int G, Mode M, bool RAG>
 __global__ __launch_bounds__(kGatherThreads) void k_spmm(SpmmArgs a, PtrTab tab, int P)
 {
     constexpr int VEC = Vec<T>::N;
-    __shared__ const void* ztab[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const void> ztab[SAR_MAX_BLOCKS];
     __shared__ float part[kWavesPerWG][G][VEC];
     if constexpr (M == Mode::kAll) {
         if ((int)threadIdx.x < P) ztab[threadIdx.x] = tab.p[threadIdx.x];
@@ -393,10 +393,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllT
     constexpr int SLOTS = kWave / G;
     constexpr int kMost = (1 << sar::kNarrowMaxClass) - 1;
     constexpr int kHold = (kMost + G - 1) / G;          // ids a lane holds
-    __shared__ const int32_t* s_ip[SAR_MAX_BLOCKS];
-    __shared__ const uint32_t* s_ix[SAR_MAX_BLOCKS];
-    __shared__ void* s_out[SAR_MAX_BLOCKS];
-    __shared__ const int32_t* s_rank[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_ip[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const uint32_t> s_ix[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<void> s_out[SAR_MAX_BLOCKS];
+    __shared__ GlobalPtr<const int32_t> s_rank[SAR_MAX_BLOCKS];
     if constexpr (ALLB) {
         if (threadIdx.x < SAR_MAX_BLOCKS) {
             s_ip[threadIdx.x] = tabs.t_indptr[threadIdx.x];
@@ -418,12 +418,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllT
         if (r < r_end) {
             m.q = ALLB ? (int)(id >> a.tag_shift) : 0;
             m.j = (int)(id & mask);
-            const int32_t* ip = ALLB ? s_ip[m.q] : a.indptr;
+            const int32_t* ip = ALLB ? s_ip[m.q].template as<const int32_t>() : a.indptr;
             m.beg = ip[m.j];
             m.cnt = ip[m.j + 1] - m.beg;
             m.jo = m.j;
             if constexpr (M == Mode::kBackward) {
-                const int32_t* rank = ALLB ? s_rank[m.q] : a.out_rank;
+                const int32_t* rank = ALLB ? s_rank[m.q].template as<const int32_t>() : a.out_rank;
                 if (rank) m.jo = rank[m.j];
             }
         }
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllT
 #pragma unroll
         for (int k = 0; k < kHold; ++k) {
             const int e = k * G + lm.gl;
-            d.v[k] = e < m.cnt ? (ALLB ? s_ix[m.q] : a.indices)[m.beg + e] : 0u;
+            d.v[k] = e < m.cnt ? (ALLB ? s_ix[m.q].template as<const uint32_t>() : a.indices)[m.beg + e] : 0u;
         }
         return d;
     };
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_rows_few(SpmmArgs a, BwdAllT
             if constexpr (M == Mode::kBlock) {
                 lm.add_to(a.acc + o, acc);
             } else {
-                lm.store(static_cast<T*>(ALLB ? s_out[m0.q] : a.out) + o, acc);
+                lm.store((ALLB ? s_out[m0.q].template as<T>() : static_cast<T*>(a.out)) + o, acc);
             }
         }
         m0 = m1;
