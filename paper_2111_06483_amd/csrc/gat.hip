@@ -1327,6 +1327,19 @@ unsigned grid_of(int64_t items, int64_t per_wg, int resident)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + per_wg - 1) / per_wg, resident));
 }
 
+// Workgroups of the wide kernel.  Its fp32 form fills the memory's queues with two workgroups a CU (eight wavefronts with eight
+// rows of 1 KiB each under way, 64 KiB; 7 TB/s over 2 us are 55), and more of them only push the frequent destinations' rows out
+// of L2: 15 M edges, 4 x 64, 1577 us with five a CU, 1555 with three, 1508 with two; 122 M edges, 4 x 100, 36.4, 36.3
+// and 36.1 ms.  Launches in which a wavefront has few sources want them all the same (4 x 64 over 0.7 M edges 38 us, with two a
+// CU 41; 2 x 100 over 1 M 66 and 71), and so do bf16 rows (201 M edges 5.4 and 5.7 ms; 8 M 611 and 795 us).
+template <typename T>
+unsigned wide_grid(const f256::BwdP& p, int resident)
+{
+    constexpr int kTwoPerCu = kMaxPersistentWGs / 4;
+    const bool many = sizeof(T) == 4 && p.n_rows >= (int64_t)kTwoPerCu * kWavesPerWG * kWave;
+    return persistent_grid_for(p.n_rows, p.n_long, many ? std::min(resident, kTwoPerCu) : resident);
+}
+
 // The padded and the slots kernels.  The few-edges kernels also take the sources without an edge
 // at the end of the list (they write their zero rows).
 template <typename T, int LPH, bool ALL, bool SLOTS, bool RAG>
@@ -1361,7 +1374,7 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
         auto few = f256::k_gat_bwd_few<T, LPH, ALL, true>;
         static const int resident_wide = resident_workgroups(wide), resident_few = resident_workgroups(few);
         if (a.n_wide > 0 && !a.wide_done) {
-            g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
+            g_wide = wide_grid<T>(p, resident_wide);
             wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
             SAR_LAUNCH_CHECK();
         }
@@ -1467,7 +1480,7 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
     }
     if (a.n_wide > 0 && !a.wide_done) {
         // sources with at least 8 edges: one wavefront (or workgroup) each
-        g_wide = persistent_grid_for(p.n_rows, p.n_long, resident_wide);
+        g_wide = wide_grid<T>(p, resident_wide);
         wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
         SAR_LAUNCH_CHECK();
     }

@@ -137,6 +137,7 @@ __global__ __launch_bounds__(kThreads<SYNC>) void k_gat_fwd_slices(FwdP a, Tabs 
                                           (uint64_t)(uint32_t)hi.template of_int<K>() << 32;
                     raw[K] = load_lane<T, PAD>(GlobalPtr<const T>::at(from), foff, on);
                 });
+                loads_sent();
                 zero_behind(raw, len - e0);
                 const bool valid = k < B && e0 + k < len;
                 float tv = 0.f;
@@ -316,9 +317,10 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
                 constexpr int K = decltype(kk)::value;
                 raw[K] = load_lane<T, false>(Gp + (uint64_t)(uint32_t)ids.template of_int<K>() * (uint32_t)a.ld, 0, true);
             });
+            const float4 rec = rec_of[(int64_t)mine * HS];
+            loads_sent();
             zero_behind(raw, len - e0);
             const bool valid = live && k < B && e0 + k < len;
-            const float4 rec = rec_of[(int64_t)mine * HS];
             float c_mine = 0.f;
             static_for<B>([&](auto kk) {
                 constexpr int K = decltype(kk)::value;
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(kThreads<true>) void k_gat_bwd_slices(f256::BwdTabs
                 c_mine = k == K ? c : c_mine;
             });
             const float u2 = rec.x + t2;
-            const float alpha = valid ? fast_exp2(leaky2(u2, a.slope) - rec.y) : 0.f;
+            const float alpha = f256::alpha_if(valid, u2, a.slope, rec.y);
             const float de = alpha * (c_mine - rec.z);
             const float du = u2 > 0.f ? de : a.slope * de;
             dt += valid ? du : 0.f;
