@@ -339,8 +339,9 @@ struct FwdState {
 // edges' rows, all at once, and a batch takes them from there: looked up edge by edge in the launch's table, every row's
 // load waited for a scalar load of its own.
 template <typename T, int LPH, int B, bool ALL, bool FLY, bool PAD>
-__device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const GlobalPtr<const void>* s_Z, const GlobalPtr<const float>* s_t,
-                                 uint32_t mine, int cnt, int foff, bool on, int h, int k, float s2, const float (&al)[4])
+__device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const GlobalPtr<const void>* s_Z,
+                                 const GlobalPtr<const float>* s_t, uint32_t mine, int cnt, int foff, bool on, int h, int k,
+                                 float s2, const float (&al)[4])
 {
     const int ld = PAD ? a.ld : kF, ldh = PAD ? a.ldh : a.H;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
@@ -642,8 +643,8 @@ struct BwdAcc4 {
 };
 
 template <typename T, int LPH, int B, bool PAD>
-__device__ inline void bwd_chunk(BwdAcc4& ac, DsLater& later, const BwdP& a, float* ds, int mine, int cnt, int foff, bool on, int h, int k,
-                                 const float (&zj)[4], float t2)
+__device__ inline void bwd_chunk(BwdAcc4& ac, DsLater& later, const BwdP& a, float* ds, int mine, int cnt, int foff, bool on,
+                                 int h, int k, const float (&zj)[4], float t2)
 {
     const int ld = PAD ? a.ld : kF, ldh = PAD ? a.ldh : a.H;
     const T* Gp = static_cast<const T*>(a.G);

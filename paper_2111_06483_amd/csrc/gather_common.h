@@ -57,8 +57,8 @@ __device__ inline int row_share(int& beg, int& end, int part, int parts)
 }
 
 // What stands behind it uses none of the loads before it until all of them are sent.  (The compiler's scheduler may put the
-// first value's use between the loads, and a wavefront then waits for one row before it asks for the others: bf16 4 x 64, forward, 229 us
-for 189.)
+// first value's use between the loads, and a wavefront then waits for one row before it asks for the others: bf16 4 x 64,
+// forward, 229 us for 189.)
 __device__ inline void loads_sent() { __builtin_amdgcn_sched_barrier(0); }
 
 template <typename T>
