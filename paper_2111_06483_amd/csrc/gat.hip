@@ -1340,6 +1340,17 @@ unsigned wide_grid(const f256::BwdP& p, int resident)
     return persistent_grid_for(p.n_rows, p.n_long, many ? std::min(resident, kTwoPerCu) : resident);
 }
 
+// The list of single-edge sources: a wavefront takes 64 entries at a time, eight after the other by eight, where that many
+// are there for each; of a short list it takes 32, 16 or 8, down to one round for every wavefront the chip holds (20 thousand
+// entries, 64 at a time by 320 wavefronts: 20 us; 8 at a time by 2500: 6 us).
+f256::SingleP single_list(const BwdScalars& a, int64_t n, int resident, unsigned& grid)
+{
+    f256::SingleP s{a.s_dst, a.s_src, a.s_row, n, kWave};
+    while (s.per > 8 && n < (int64_t)resident * kWavesPerWG * s.per) s.per /= 2;
+    grid = grid_of(n, (int64_t)s.per * kWavesPerWG, resident);
+    return s;
+}
+
 // The padded and the slots kernels.  The few-edges kernels also take the sources without an edge
 // at the end of the list (they write their zero rows).
 template <typename T, int LPH, bool ALL, bool SLOTS, bool RAG>
@@ -1391,8 +1402,7 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
         if (n_pulled > 0) {
             auto single = f256::k_gat_bwd_single<T, LPH, true>;
             static const int resident = resident_workgroups(single);
-            const f256::SingleP sp{a.s_dst, a.s_src, a.s_row, n_pulled};
-            g_single = grid_of(n_pulled, (int64_t)kWave * kWavesPerWG, resident);
+            const f256::SingleP sp = single_list(a, n_pulled, resident, g_single);
             single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
             SAR_LAUNCH_CHECK();
         }
@@ -1493,9 +1503,7 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
         SAR_LAUNCH_CHECK();
     }
     if (n_pulled > 0) {
-        const f256::SingleP sp{a.s_dst, a.s_src, a.s_row, n_pulled};
-        const int64_t per_wg = (int64_t)kWave * kWavesPerWG;
-        g_single = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_pulled + per_wg - 1) / per_wg, resident_single));
+        const f256::SingleP sp = single_list(a, n_pulled, resident_single, g_single);
         single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
         SAR_LAUNCH_CHECK();
     }

@@ -1119,6 +1119,7 @@ struct SingleP {
     const uint32_t* src;   // [n] its source, tagged with the block
     const int32_t* row;    // [n] row of the source in its block's dZ_q / dt_q
     int64_t n;
+    int per;               // entries a wavefront takes at a time, at most 64
 };
 
 template <typename T, int LPH, bool PAD>
@@ -1157,21 +1158,21 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
 #pragma unroll
     for (int x = 0; x < 4; ++x) dal[x] = 0.f;
 
-    // a wavefront takes 64 entries at a time, one per lane; the next 64 travel meanwhile
-    const int64_t n_chunks = (s.n + kWave - 1) / kWave;
+    // a wavefront takes `per` entries at a time, one per lane; the next ones travel meanwhile
+    const int64_t n_chunks = (s.n + s.per - 1) / s.per;
     const int64_t stride = (int64_t)gridDim.x * kWavesPerWG;
     struct Entry { int i; uint32_t id; int row; };
     auto load_entries = [&](int64_t c) {
         Entry e{0, 0u, 0};
-        const int64_t at = c * kWave + lane;
-        if (c < n_chunks && at < s.n) e = Entry{s.dst[at], s.src[at], s.row[at]};
+        const int64_t at = c * s.per + lane;
+        if (c < n_chunks && lane < s.per && at < s.n) e = Entry{s.dst[at], s.src[at], s.row[at]};
         return e;
     };
     int64_t c = (int64_t)blockIdx.x * kWavesPerWG + wave;
     Entry cur = load_entries(c);
     for (; c < n_chunks; c += stride) {
         const Entry nxt = load_entries(c + stride);
-        const int cnt = (int)min((int64_t)kWave, s.n - c * kWave);
+        const int cnt = (int)min((int64_t)s.per, s.n - c * s.per);
         for (int k0 = 0; k0 < cnt; k0 += B) {
             const int nb = min(B, cnt - k0);
             int q[B], row[B];
