@@ -1,10 +1,11 @@
-"""Build libsar_mi355x.so (the product) and libsar_bench.so (bench.py's bandwidth probes) from
-csrc/ with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Build libsar_mi355x.so (the product), _binding.so (the Python side of its hot calls) and libsar_bench.so
+(bench.py's bandwidth probes) from csrc/ with hipcc for gfx950 (cross-compiles without a GPU)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +14,8 @@ LIB = os.path.join(HERE, "libsar_mi355x.so")
 SOURCES = ["builder.hip", "spmm.hip", "gat.hip", "gat_slices.hip", "linear.hip", "linear_split.hip", "linear_few.hip"]
 BENCH_LIB = os.path.join(HERE, "libsar_bench.so")
 BENCH_SOURCES = ["probe.hip"]
+BINDING = os.path.join(HERE, "_binding.so")
+BINDING_SOURCE = "binding.cpp"
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
@@ -20,6 +23,20 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
 ]
+
+
+def binding_flags():
+    """The binding is host code that reads torch's tensors: compiled against the installed torch's headers."""
+    from torch.utils import cpp_extension
+    return ["-O2", "-std=c++17", "-fPIC", "-w", "-DUSE_ROCM", "-isystem", sysconfig.get_paths()["include"],
+            *[f for path in cpp_extension.include_paths() for f in ("-isystem", path)]]
+
+
+def binding_link_flags():
+    """Linked against the library beside it; torch's own are loaded by the time it is imported."""
+    from torch.utils import cpp_extension
+    return ["-L" + HERE, "-lsar_mi355x", "-Wl,-rpath,$ORIGIN",
+            *["-L" + path for path in cpp_extension.library_paths()], "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
 def _hipcc() -> str:
@@ -36,8 +53,9 @@ def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
 
     def compile_one(src: str) -> str:
-        obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
+        flags = binding_flags() if src == BINDING_SOURCE else HIPCC_FLAGS
+        cmd = [hipcc, *flags, "-c", os.path.join(CSRC, src), "-o", obj]
         res = subprocess.run(cmd, capture_output=True, text=True)
         noise = "packed-fp32-ops"
         err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
@@ -47,18 +65,19 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    def link(objs, lib):
+    def link(objs, lib, flags=()):
         tmp = lib + ".%d.tmp" % os.getpid()
-        res = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs],
+        res = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs, *flags],
                              capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("link failed:\n" + res.stderr)
         os.replace(tmp, lib)
 
     with ThreadPoolExecutor(max_workers=5) as pool:
-        objs = list(pool.map(compile_one, SOURCES + BENCH_SOURCES))
+        objs = list(pool.map(compile_one, SOURCES + BENCH_SOURCES + [BINDING_SOURCE]))
     link(objs[:len(SOURCES)], LIB)
-    link(objs[len(SOURCES):], BENCH_LIB)
+    link(objs[len(SOURCES):-1], BENCH_LIB)
+    link(objs[-1:], BINDING, binding_link_flags())
     return LIB
 
 

@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libsar_mi355x.so: same names as include/sar_mi355x.h.
+"""Thin binding over libsar_mi355x.so: same names as include/sar_mi355x.h.  The calls of a step go through _binding.so, which
+checks their tensors and hands them over; handles are built, and the rarer calls made, over ctypes.
 
 Argument marshalling only -- every step of the path runs in the library's HIP
 kernels.  torch is used for device memory (``tensor.data_ptr()``) and for the
@@ -74,6 +75,23 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The loaded binding of the hot calls; raises if it has not been built."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise RuntimeError("_binding.so does not load (%s): build it with `python -m paper_2111_06483_amd.build` "
+                               "(there is no fallback path)" % e) from e
+        _native = _binding
+    return _native
+
+
 # Parameter types of the entry points, declared once so that a call hands over plain Python values: p address,
 # i int, l int64_t, z size_t, f float.
 _SIGNATURES = {
@@ -114,10 +132,6 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
-def _bytes(t: torch.Tensor) -> int:
-    return t.numel() * t.element_size()
-
-
 # The address of the current stream without the Stream object around it, which took a third of the host
 # time of a short pass (2 of 12 us per call).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -139,11 +153,9 @@ def dtype_code(dt: torch.dtype) -> int:
     raise SarError(SAR_ERR_UNSUPPORTED, "dtype %s" % dt)
 
 
-def _ptr_array(ts: Sequence[Optional[torch.Tensor]], what: str = "tensor", dtype: Optional[torch.dtype] = None,
-               row_values: Optional[int] = None):
-    """Host array of device pointers for the calls that take one tensor per block.  The C side
-    reinterprets the memory, so every entry must be what the call assumes: on the device,
-    contiguous, of `dtype`, and (when given) with `row_values` values per row."""
+def _ptr_array(ts: Sequence[Optional[torch.Tensor]], what: str, dtype: torch.dtype):
+    """Host array of device pointers, one per block.  The C side reinterprets the memory, so every
+    entry must be what the call assumes: on the device, contiguous, of `dtype`."""
     ptrs = []
     for k, t in enumerate(ts):
         if t is None:
@@ -151,11 +163,8 @@ def _ptr_array(ts: Sequence[Optional[torch.Tensor]], what: str = "tensor", dtype
             continue
         if not t.is_cuda or not t.is_contiguous():
             raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] must be a contiguous device tensor" % (what, k))
-        if dtype is not None and t.dtype != dtype:
+        if t.dtype != dtype:
             raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] is %s, the call needs %s" % (what, k, t.dtype, dtype))
-        if row_values is not None and t.numel() != t.size(0) * row_values:
-            raise SarError(SAR_ERR_INVALID_ARG, "%s[%d] has %d values per row, the call needs %d"
-                           % (what, k, t.numel() // max(t.size(0), 1), row_values))
         ptrs.append(t.data_ptr())
     return (_vp * len(ptrs))(*ptrs)
 
@@ -165,6 +174,7 @@ class Blocks:
 
     def __init__(self, handle: _vp, keep=(), flags: int = 0):
         self._h = handle
+        self._addr = handle.value
         self._keep = keep   # tensors borrowed by a wrapped handle
         self.flags = flags
         self._n_src = {}
@@ -225,7 +235,7 @@ class Blocks:
     def close(self) -> None:
         if self._h is not None:
             lib().sar_blocks_free(self._h)
-            self._h = None
+            self._h = self._addr = None
 
     def __del__(self):
         try:
@@ -338,20 +348,11 @@ def sar_spmm_end(deg: torch.Tensor, mean: bool, acc: torch.Tensor, out: torch.Te
 
 def sar_spmm_all(b: Blocks, Zq: Sequence[torch.Tensor], mean: bool, out: torch.Tensor,
                  residual: Optional[torch.Tensor] = None, act: int = SAR_ACT_NONE) -> None:
-    for q in range(b.P):
-        b.check_rows(q, Zq[q])
-    b.check_dst(out)
-    _same_shape(out, residual)
-    _check(lib().sar_spmm_all(b.handle, _ptr_array(Zq, "Zq", out.dtype, out.shape[-1]), dtype_code(out.dtype),
-                              out.shape[-1], int(mean), _ptr(residual), act, _ptr(out),
-                              _stream()))
+    native().spmm_all(b, Zq, mean, out, residual, act)
 
 
 def sar_act_bwd(h: torch.Tensor, dH: torch.Tensor, act: int, G: torch.Tensor) -> None:
-    _same_shape(h, dH)
-    _same_shape(h, G)
-    _check(lib().sar_act_bwd(_ptr(h), _ptr(dH), act, _ptr(G), dtype_code(h.dtype),
-                             h.numel(), _stream()))
+    native().act_bwd(h, dH, act, G)
 
 
 def sar_spmm_bwd_block(b: Blocks, q: int, G: torch.Tensor, mean: bool, dZq: torch.Tensor) -> None:
@@ -362,65 +363,39 @@ def sar_spmm_bwd_block(b: Blocks, q: int, G: torch.Tensor, mean: bool, dZq: torc
 
 
 def sar_spmm_bwd_all(b: Blocks, G: torch.Tensor, mean: bool, dZq: Sequence[torch.Tensor]) -> None:
-    for q in range(b.P):
-        b.check_err_rows(q, dZq[q])
-    b.check_dst(G)
-    _check(lib().sar_spmm_bwd_all(b.handle, _ptr(G), int(mean), dtype_code(G.dtype),
-                                  G.shape[-1], _ptr_array(dZq, "dZq", G.dtype, G.shape[-1]), _stream()))
+    native().spmm_bwd_all(b, G, mean, dZq)
 
 
 def sar_error_add(Eq: Optional[torch.Tensor], t_rank: int, accumulate: bool, Ep: torch.Tensor) -> None:
     """t_rank: device address of the block's t_rank array (BlockView.t_rank)."""
-    n = Ep.shape[0]
-    F = Ep.numel() // max(n, 1)
-    if Eq is not None and (Eq.dtype != Ep.dtype or Eq.numel() != Eq.shape[0] * F):
-        raise SarError(SAR_ERR_INVALID_ARG, "Eq and Ep must have the same row width and type")
-    _check(lib().sar_error_add(_ptr(Eq), t_rank, int(accumulate), _ptr(Ep), dtype_code(Ep.dtype),
-                               n, F, _stream()))
+    native().error_add(Eq, t_rank, accumulate, Ep)
 
 
 # --------------------------------------------------------------------- GAT
 
 def sar_gat_scores(Z: torch.Tensor, a: torch.Tensor, score: torch.Tensor) -> None:
-    H, D = a.shape
-    _check(lib().sar_gat_scores(_ptr(Z), dtype_code(Z.dtype), Z.shape[0], H, D,
-                                _ptr(a), _ptr(score), _stream()))
+    native().gat_scores(Z, a, score)
 
 
 def sar_gat_fwd_begin(m: torch.Tensor, l: torch.Tensor, acc: torch.Tensor) -> None:
-    n, H, D = acc.shape
-    _check(lib().sar_gat_fwd_begin(_ptr(m), _ptr(l), _ptr(acc), n, H, D, _stream()))
+    native().gat_fwd_begin(m, l, acc)
 
 
 def sar_gat_fwd_block(b: Blocks, q: int, Zq: torch.Tensor, s: torch.Tensor, tq: Optional[torch.Tensor],
                       a_l: Optional[torch.Tensor], slope: float,
                       m: torch.Tensor, l: torch.Tensor, acc: torch.Tensor) -> None:
-    _, H, D = acc.shape
-    b.check_rows(q, Zq, tq)
-    b.check_dst(s, m, l, acc)
-    _check(lib().sar_gat_fwd_block(b.handle, q, _ptr(Zq), _ptr(s), _ptr(tq), _ptr(a_l),
-                                   dtype_code(Zq.dtype), H, D, slope,
-                                   _ptr(m), _ptr(l), _ptr(acc), _stream()))
+    native().gat_fwd_block(b, q, Zq, s, tq, a_l, slope, m, l, acc)
 
 
 def sar_gat_fwd_end(m: torch.Tensor, l: torch.Tensor, acc: torch.Tensor, out: torch.Tensor,
                     L: torch.Tensor, act: int = SAR_ACT_NONE) -> None:
-    n, H, D = acc.shape
-    _check(lib().sar_gat_fwd_end(_ptr(m), _ptr(l), _ptr(acc), act, _ptr(out), _ptr(L),
-                                 dtype_code(out.dtype), n, H, D, _stream()))
+    native().gat_fwd_end(m, l, acc, out, L, act)
 
 
 def sar_gat_fwd_all(b: Blocks, Zq: Sequence[torch.Tensor], s: torch.Tensor,
                     tq: Optional[Sequence[torch.Tensor]], a_l: Optional[torch.Tensor],
                     slope: float, out: torch.Tensor, L: torch.Tensor, act: int = SAR_ACT_NONE) -> None:
-    _, H, D = out.shape
-    for q in range(b.P):
-        b.check_rows(q, Zq[q], None if tq is None else tq[q])
-    b.check_dst(s, out, L)
-    _check(lib().sar_gat_fwd_all(b.handle, _ptr_array(Zq, "Zq", out.dtype, H * D), _ptr(s),
-                                 None if tq is None else _ptr_array(tq, "tq", torch.float32, H), _ptr(a_l),
-                                 dtype_code(out.dtype), H, D, slope,
-                                 act, _ptr(out), _ptr(L), _stream()))
+    native().gat_fwd_all(b, Zq, s, tq, a_l, slope, out, L, act)
 
 
 def sar_gat_workspace_bytes(n_dst: int, n_src_max: int, H: int, D: int) -> int:
@@ -433,26 +408,14 @@ def sar_gat_workspace_bytes(n_dst: int, n_src_max: int, H: int, D: int) -> int:
 def sar_gat_bwd_begin(G: torch.Tensor, out: torch.Tensor, s: torch.Tensor, L: torch.Tensor,
                       rec: torch.Tensor, ds: torch.Tensor, act: int = SAR_ACT_NONE,
                       Gact: Optional[torch.Tensor] = None) -> None:
-    n, H, D = G.shape
-    _same_shape(G, out)
-    _same_shape(G, Gact)
-    _check(lib().sar_gat_bwd_begin(_ptr(G), _ptr(out), _ptr(s), _ptr(L), act, _ptr(Gact),
-                                   dtype_code(G.dtype), _ptr(rec), _ptr(ds), n, H,
-                                   D, _stream()))
+    native().gat_bwd_begin(G, out, s, L, rec, ds, act, Gact)
 
 
 def sar_gat_bwd_block(b: Blocks, q: int, Zq: torch.Tensor, G: torch.Tensor, tq: torch.Tensor,
                       rec: torch.Tensor, a_l: torch.Tensor, slope: float, dZq: torch.Tensor,
                       dtq: Optional[torch.Tensor], ds: torch.Tensor, da_l: torch.Tensor, work: torch.Tensor) -> None:
     """dtq None: the per-source sums dt_q are not written (dZq and da_l contain them already)."""
-    H, D = a_l.shape
-    b.check_rows(q, Zq, tq)
-    b.check_err_rows(q, dZq, dtq)
-    b.check_dst(G, rec, ds)
-    _check(lib().sar_gat_bwd_block(b.handle, q, _ptr(Zq), _ptr(G), _ptr(tq), _ptr(rec), _ptr(a_l),
-                                   dtype_code(G.dtype), H, D, slope,
-                                   _ptr(dZq), _ptr(dtq), _ptr(ds), _ptr(da_l), _ptr(work),
-                                   _bytes(work), _stream()))
+    native().gat_bwd_block(b, q, Zq, G, tq, rec, a_l, slope, dZq, dtq, ds, da_l, work)
 
 
 def sar_gat_bwd_all(b: Blocks, Zq: Sequence[torch.Tensor], G: torch.Tensor, tq: Sequence[torch.Tensor],
@@ -460,19 +423,7 @@ def sar_gat_bwd_all(b: Blocks, Zq: Sequence[torch.Tensor], G: torch.Tensor, tq: 
                     dtq: Optional[Sequence[torch.Tensor]], ds: torch.Tensor, da_l: torch.Tensor,
                     work: torch.Tensor) -> None:
     """dtq None: the per-source sums dt_q are not written (dZq and da_l contain them already)."""
-    H, D = a_l.shape
-    for q in range(b.P):
-        b.check_rows(q, Zq[q], None if tq is None else tq[q])
-        b.check_err_rows(q, dZq[q], None if dtq is None else dtq[q])
-    b.check_dst(G, rec, ds)
-    _check(lib().sar_gat_bwd_all(b.handle, _ptr_array(Zq, "Zq", G.dtype, H * D), _ptr(G),
-                                 None if tq is None else _ptr_array(tq, "tq", torch.float32, H),
-                                 _ptr(rec), _ptr(a_l),
-                                 dtype_code(G.dtype), H, D, slope,
-                                 _ptr_array(dZq, "dZq", G.dtype, H * D),
-                                 None if dtq is None else _ptr_array(dtq, "dtq", torch.float32, H),
-                                 _ptr(ds), _ptr(da_l), _ptr(work),
-                                 _bytes(work), _stream()))
+    native().gat_bwd_all(b, Zq, G, tq, rec, a_l, slope, dZq, dtq, ds, da_l, work)
 
 
 def sar_gat_bwd_end(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor, dZadd: Optional[torch.Tensor],
@@ -480,10 +431,7 @@ def sar_gat_bwd_end(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor, dZa
                     dZadd_rank: Optional[int] = None) -> None:
     """dZadd_rank: device address of the local block's t_rank (BlockView.t_rank) when dZadd is compact.
     dZdst None: only da_r."""
-    H, D = a_r.shape
-    _check(lib().sar_gat_bwd_end(_ptr(Zdst), _ptr(ds), _ptr(a_r), _ptr(dZadd), dZadd_rank, _ptr(dZdst), _ptr(da_r),
-                                 dtype_code(Zdst.dtype), Zdst.shape[0], H, D,
-                                 _ptr(work), _bytes(work), _stream()))
+    native().gat_bwd_end(Zdst, ds, a_r, dZadd, dZdst, da_r, work, dZadd_rank)
 
 
 def sar_gat_bwd_end_noalloc(Zdst: torch.Tensor, ds: torch.Tensor, a_r: torch.Tensor,
@@ -506,23 +454,13 @@ def sar_linear_workspace_bytes(n: int, K: int, F: int) -> int:
 def sar_linear_fwd(X: torch.Tensor, W: torch.Tensor, Z: torch.Tensor,
                    a_score: Optional[torch.Tensor] = None, score: Optional[torch.Tensor] = None,
                    a_score2: Optional[torch.Tensor] = None, score2: Optional[torch.Tensor] = None) -> None:
-    n, K = X.shape
-    F = W.shape[1]
-    H, D = (a_score.shape if a_score is not None else (0, 0))
-    _check(lib().sar_linear_fwd(_ptr(X), _ptr(W), _ptr(Z), dtype_code(X.dtype), n, K,
-                                F, H, D, _ptr(a_score), _ptr(score), _ptr(a_score2),
-                                _ptr(score2), _stream()))
+    native().linear_fwd(X, W, Z, a_score, score, a_score2, score2)
 
 
 def sar_linear_bwd(X: Optional[torch.Tensor], dZ: torch.Tensor, W: Optional[torch.Tensor],
                    dW: Optional[torch.Tensor], dX: Optional[torch.Tensor],
                    work: Optional[torch.Tensor]) -> None:
-    n = dZ.shape[0]
-    F = dZ.numel() // max(n, 1)
-    K = X.shape[1] if X is not None else W.shape[0]
-    wb = 0 if work is None else _bytes(work)
-    _check(lib().sar_linear_bwd(_ptr(X), _ptr(dZ), _ptr(W), _ptr(dW), _ptr(dX), dtype_code(dZ.dtype),
-                                n, K, F, _ptr(work), wb, _stream()))
+    native().linear_bwd(X, dZ, W, dW, dX, work)
 
 
 def sar_linear_bwd_rows(X: Optional[torch.Tensor], E: Optional[torch.Tensor], E_rank: Optional[int],
@@ -531,9 +469,4 @@ def sar_linear_bwd_rows(X: Optional[torch.Tensor], E: Optional[torch.Tensor], E_
                         n: int, dtype: torch.dtype, work: Optional[torch.Tensor],
                         rows: Optional[torch.Tensor] = None) -> None:
     """E_rank: device address of a t_rank array (BlockView.t_rank) when E is compact."""
-    K = X.shape[1] if X is not None else W.shape[0]
-    n_E = 0 if E is None else E.shape[0]
-    wb = 0 if work is None else _bytes(work)
-    _check(lib().sar_linear_bwd_rows(_ptr(X), _ptr(E), E_rank, n_E, _ptr(ds), _ptr(a_r), H,
-                                     D, _ptr(W), _ptr(dW), _ptr(dX), dtype_code(dtype), n,
-                                     K, _ptr(rows), _ptr(work), wb, _stream()))
+    native().linear_bwd_rows(X, E, E_rank, ds, a_r, H, D, W, dW, dX, n, dtype_code(dtype), work, rows)

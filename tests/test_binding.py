@@ -1,0 +1,86 @@
+"""What the binding of the hot calls refuses before anything reaches a device (tensors in host memory serve for that)."""
+import pytest
+import torch
+
+from paper_2111_06483_amd import sar
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    sar.native()
+
+
+def freed():
+    import ctypes
+    b = sar.Blocks.__new__(sar.Blocks)
+    b._h, b._addr, b.flags = None, None, 0
+    return b
+
+
+def test_shapes_and_types_that_must_match():
+    h = torch.zeros(4, 8)
+    for other in (torch.zeros(8, 4), torch.zeros(4, 8, dtype=torch.bfloat16)):
+        with pytest.raises(sar.SarError) as e:
+            sar.sar_act_bwd(h, other, sar.SAR_ACT_RELU, torch.zeros(4, 8))
+        assert e.value.code == sar.SAR_ERR_INVALID_ARG and "must match" in str(e.value)
+        assert "(4, 8) torch.float32" in str(e.value) and str(other.dtype) in str(e.value)
+
+
+def test_types_the_library_has_not():
+    z = torch.zeros(4, 2, 8, dtype=torch.float16)
+    with pytest.raises(sar.SarError) as e:
+        sar.sar_gat_scores(z, torch.zeros(2, 8), torch.zeros(4, 2))
+    assert e.value.code == sar.SAR_ERR_UNSUPPORTED and "torch.float16" in str(e.value)
+
+
+def test_tensors_that_are_no_plain_memory():
+    with pytest.raises(AssertionError, match="contiguous"):
+        sar.sar_gat_scores(torch.zeros(2, 8, 4).transpose(1, 2), torch.zeros(4, 8), torch.zeros(2, 4))
+    with pytest.raises(TypeError):
+        sar.sar_gat_scores([1.0], torch.zeros(2, 8), torch.zeros(4, 2))
+    with pytest.raises(ValueError):
+        sar.sar_gat_fwd_begin(torch.zeros(4, 2), torch.zeros(4, 2), torch.zeros(4, 16))
+    with pytest.raises(TypeError):
+        sar.sar_act_bwd(torch.zeros(4), torch.zeros(4), None, torch.zeros(4))
+
+
+def test_a_freed_handle():
+    for call in (lambda b: sar.sar_spmm_all(b, [], True, torch.zeros(4, 8)),
+                 lambda b: sar.sar_spmm_bwd_all(b, torch.zeros(4, 8), True, []),
+                 lambda b: sar.sar_gat_fwd_all(b, [], torch.zeros(4, 1), None, torch.zeros(1, 8), 0.2, torch.zeros(4, 1, 8),
+                                               torch.zeros(4, 1))):
+        with pytest.raises(sar.SarError) as e:
+            call(freed())
+        assert e.value.code == sar.SAR_ERR_STATE and "freed" in str(e.value)
+
+
+def test_errors_of_the_library_come_through():
+    with pytest.raises(sar.SarError) as e:      # a head wider than a wavefront
+        sar.sar_gat_fwd_end(torch.zeros(4, 1), torch.zeros(4, 1), torch.zeros(4, 1, 512), torch.zeros(4, 1, 512),
+                            torch.zeros(4, 1))
+    assert e.value.code == sar.SAR_ERR_UNSUPPORTED and "64 lanes" in str(e.value)
+
+
+def test_nothing_to_do_with_no_row():
+    sar.sar_linear_fwd(torch.zeros(0, 4), torch.zeros(4, 8), torch.zeros(0, 8))
+    sar.sar_gat_scores(torch.zeros(0, 2, 8), a=torch.zeros(2, 8), score=torch.zeros(0, 2))
+
+
+@pytest.mark.gpu
+def test_lists_of_blocks():
+    """One tensor per block: missing, of another type, another width, another height, on the host."""
+    part = torch.tensor([0, 1, 0, 1], dtype=torch.int32, device="cuda")
+    src, dst = torch.tensor([0, 1, 3], device="cuda"), torch.tensor([2, 0, 0], device="cuda")
+    b = sar.sar_blocks_build(src, dst, part, 2, 0)
+    out, f32 = torch.zeros(2, 8, device="cuda"), dict(device="cuda")
+    good = [torch.ones(2, 8, **f32), torch.ones(2, 8, **f32)]
+    sar.sar_spmm_all(b, tuple(good), False, out=out)
+    assert out.sum().item() == 24.0
+    for bad, text in ((torch.ones(2, 8, dtype=torch.bfloat16, **f32), "torch.bfloat16"), (torch.ones(2, 4, **f32), "4 values"),
+                      (torch.ones(3, 8, **f32), "2 sources"), (torch.ones(2, 8), "device tensor"),
+                      (torch.ones(8, 2, **f32).t(), "contiguous")):
+        with pytest.raises(sar.SarError, match=text):
+            sar.sar_spmm_all(b, [good[0], bad], False, out)
+    with pytest.raises(IndexError):
+        sar.sar_spmm_all(b, good[:1], False, out)
+    b.close()
