@@ -11,7 +11,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsar_mi355x.so")
-SOURCES = ["builder.hip", "spmm.hip", "gat.hip", "gat_slices.hip", "linear.hip", "linear_split.hip", "linear_few.hip"]
+SOURCES = ["builder.hip", "spmm.hip", "gat.hip", "gat_slices.hip", "gat_joint_f32.hip", "gat_joint_bf16.hip", "linear.hip",
+           "linear_split.hip", "linear_few.hip"]
 BENCH_LIB = os.path.join(HERE, "libsar_bench.so")
 BENCH_SOURCES = ["probe.hip"]
 BINDING = os.path.join(HERE, "_binding.so")
@@ -73,7 +74,7 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("link failed:\n" + res.stderr)
         os.replace(tmp, lib)
 
-    with ThreadPoolExecutor(max_workers=5) as pool:
+    with ThreadPoolExecutor(max_workers=8) as pool:
         objs = list(pool.map(compile_one, SOURCES + BENCH_SOURCES + [BINDING_SOURCE]))
     link(objs[:len(SOURCES)], LIB)
     link(objs[len(SOURCES):-1], BENCH_LIB)

@@ -24,6 +24,7 @@
 #include "gather_common.h"
 #include "gat_f256.h"
 #include "gat_slices.h"
+#include "gat_joint.h"
 #include "gat_slots.h"
 #include "sar_internal.h"
 
@@ -1322,11 +1323,6 @@ f256::BwdP bwd_params(const BwdScalars& a)
     return p;
 }
 
-unsigned grid_of(int64_t items, int64_t per_wg, int resident)
-{
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + per_wg - 1) / per_wg, resident));
-}
-
 // Workgroups of the wide kernel.  Its fp32 form fills the memory's queues with two workgroups a CU (eight wavefronts with eight
 // rows of 1 KiB each under way, 64 KiB; 7 TB/s over 2 us are 55), and more of them only push the frequent destinations' rows out
 // of L2: 15 M edges, 4 x 64, 1577 us with five a CU, 1555 with three, 1508 with two; 122 M edges, 4 x 100, 36.4, 36.3
@@ -1338,17 +1334,6 @@ unsigned wide_grid(const f256::BwdP& p, int resident)
     constexpr int kTwoPerCu = kMaxPersistentWGs / 4;
     const bool many = sizeof(T) == 4 && p.n_rows >= (int64_t)kTwoPerCu * kWavesPerWG * kWave;
     return persistent_grid_for(p.n_rows, p.n_long, many ? std::min(resident, kTwoPerCu) : resident);
-}
-
-// The list of single-edge sources: a wavefront takes 64 entries at a time, eight after the other by eight, where that many
-// are there for each; of a short list it takes 32, 16 or 8, down to one round for every wavefront the chip holds (20 thousand
-// entries, 64 at a time by 320 wavefronts: 20 us; 8 at a time by 2500: 6 us).
-f256::SingleP single_list(const BwdScalars& a, int64_t n, int resident, unsigned& grid)
-{
-    f256::SingleP s{a.s_dst, a.s_src, a.s_row, n, kWave};
-    while (s.per > 8 && n < (int64_t)resident * kWavesPerWG * s.per) s.per /= 2;
-    grid = grid_of(n, (int64_t)s.per * kWavesPerWG, resident);
-    return s;
 }
 
 // The padded and the slots kernels.  The few-edges kernels also take the sources without an edge
@@ -1366,6 +1351,15 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
     const int64_t n_edged = std::max(a.n_wide, std::min(a.n_rows, a.n_touched));
     const int64_t n_pulled = (!RAG && ALL && a.s_dst && a.n_single <= n_edged - a.n_wide) ? a.n_single : 0;
     const int64_t piece[2][2] = {{a.n_wide, n_pulled ? n_edged - n_pulled : a.n_rows}, {n_edged, n_pulled ? a.n_rows : n_edged}};
+    if (!a.wide_done && (!SLOTS || n_pulled > 0)) {       // (the slots kernel takes both kinds of sources as it is)
+        constexpr joint::Lanes lanes = SLOTS ? joint::Lanes::kSlots : joint::Lanes::kPadded;
+        const joint::Work w{{{piece[0][0], piece[0][1]}, {piece[1][0], piece[1][1]}}, {a.s_dst, a.s_src, a.s_row, n_pulled, 0},
+                            n_slots, LPH, lanes, ALL};
+        int grid = 0;
+        SAR_TRY(sar::bwd_joint(sizeof(T) == 4 ? SAR_F32 : SAR_BF16, t, p, w, &grid, st));
+        *grid_out = (unsigned)grid;
+        if (grid > 0) return SAR_OK;
+    }
     if constexpr (SLOTS) {
         auto kernel = slots::k_gat_bwd_slots<T, LPH, ALL, RAG>;
         static const int resident = resident_workgroups(kernel);
@@ -1402,7 +1396,7 @@ int launch_bwd_padded(const BwdArgs& tabs, const BwdScalars& a, int n_slots, uns
         if (n_pulled > 0) {
             auto single = f256::k_gat_bwd_single<T, LPH, true>;
             static const int resident = resident_workgroups(single);
-            const f256::SingleP sp = single_list(a, n_pulled, resident, g_single);
+            const f256::SingleP sp = single_list({a.s_dst, a.s_src, a.s_row, n_pulled, 0}, resident, g_single);
             single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
             SAR_LAUNCH_CHECK();
         }
@@ -1488,13 +1482,19 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
             SAR_LAUNCH_CHECK();
         }
     }
-    if (a.n_wide > 0 && !a.wide_done) {
+    int g_joint = 0;
+    if (!a.wide_done) {
+        const joint::Work w{{{a.n_wide, n_few_end}, {0, 0}}, {a.s_dst, a.s_src, a.s_row, n_pulled, 0}, 1, LPH,
+                            joint::Lanes::kExact, ALL};
+        SAR_TRY(sar::bwd_joint(sizeof(T) == 4 ? SAR_F32 : SAR_BF16, t, p, w, &g_joint, st));
+    }
+    if (g_joint == 0 && a.n_wide > 0 && !a.wide_done) {
         // sources with at least 8 edges: one wavefront (or workgroup) each
         g_wide = wide_grid<T>(p, resident_wide);
         wide<<<g_wide, kGatherThreads, 0, st>>>(t, p);
         SAR_LAUNCH_CHECK();
     }
-    if (n_few_end > a.n_wide) {
+    if (g_joint == 0 && n_few_end > a.n_wide) {
         // the other sources with edges, several per wavefront
         const int64_t n = n_few_end - a.n_wide;
         const int64_t per_wg = (int64_t)kPerWave * kWavesPerWG;
@@ -1502,8 +1502,8 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
         few<<<g_few, kGatherThreads, 0, st>>>(t, p, a.n_wide, n_few_end, (int)g_wide);
         SAR_LAUNCH_CHECK();
     }
-    if (n_pulled > 0) {
-        const f256::SingleP sp = single_list(a, n_pulled, resident_single, g_single);
+    if (g_joint == 0 && n_pulled > 0) {
+        const f256::SingleP sp = single_list({a.s_dst, a.s_src, a.s_row, n_pulled, 0}, resident_single, g_single);
         single<<<g_single, kGatherThreads, 0, st>>>(t, p, sp, (int)(g_wide + g_few));
         SAR_LAUNCH_CHECK();
     }
@@ -1514,7 +1514,7 @@ int launch_bwd_f256(const BwdArgs& tabs, const BwdScalars& a, unsigned* grid_out
                                                        a.tag_shift);
         SAR_LAUNCH_CHECK();
     }
-    *grid_out = g_wide + g_few + g_single;
+    *grid_out = g_joint + g_wide + g_few + g_single;
     return SAR_OK;
 }
 

@@ -697,8 +697,9 @@ __device__ inline void bwd_chunk(BwdAcc4& ac, DsLater& later, const BwdP& a, flo
     }
 }
 
+// The wide sources, by workgroup `block` of `n_blocks`; its share of da_l goes to partial_row.
 template <typename T, int LPH, int B, bool ALL, bool PAD>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, BwdP a)
+__device__ inline void bwd_wide(const BwdTabs& tabs, const BwdP& a, int block, int n_blocks, float* partial_row)
 {
     static_assert(B <= LPH, "a sub-batch must fit a head group");
     __shared__ float part[kWavesPerWG][kWave][5];
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
         if (k == 0 && s_dt[q]) s_dt[q][jo * ldh + h] = dt;
     };
 
-    for (int64_t r = blockIdx.x; r < a.n_long; r += gridDim.x) {
+    for (int64_t r = block; r < a.n_long; r += n_blocks) {
         const Src x = source(a.rows[r]);
         BwdAcc4 ac;
         float zj[4];
@@ -823,8 +824,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
     // The other sources, 64 of a wavefront's at a time: lane u looks up the u-th, and its own row and first destinations are
     // read while the source before it is taken.  (With the record read at once and the additions sent late, 40 layers of 6 us to
     // 36 ms: 13% shorter on average, up to 34; 2 x 100 bf16 block by block 167 -> 111 us, 4 x 64 bf16 over 3 M edges 238 -> 213.)
-    const int64_t n_waves = (int64_t)gridDim.x * kWavesPerWG;
-    for (int64_t r = a.n_long + from_behind(a.n_long, blockIdx.x, gridDim.x) * kWavesPerWG + wave; r < a.n_rows;
+    const int64_t n_waves = (int64_t)n_blocks * kWavesPerWG;
+    for (int64_t r = a.n_long + from_behind(a.n_long, block, n_blocks) * kWavesPerWG + wave; r < a.n_rows;
          r += n_waves * kWave) {
         const bool have = r + lane * n_waves < a.n_rows;
         const int count = __builtin_popcountll(__builtin_amdgcn_ballot_w64(have));
@@ -861,8 +862,14 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
             for (int w = 0; w < kWavesPerWG; ++w) s += part[w][lane][x];
             v[x] = s;
         }
-        store_f32<4>(a.partial + (int64_t)blockIdx.x * kF + lane * 4, v);
+        store_f32<4>(partial_row + lane * 4, v);
     }
+}
+
+template <typename T, int LPH, int B, bool ALL, bool PAD>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, BwdP a)
+{
+    bwd_wide<T, LPH, B, ALL, PAD>(tabs, a, (int)blockIdx.x, (int)gridDim.x, a.partial + (int64_t)blockIdx.x * kF);
 }
 
 // ------------------------------------------- backward, rows of few edges
@@ -881,8 +888,8 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_f256(BwdTabs tabs, B
 // destination of its edge e.  List entries are read three groups ahead, ranges two, and
 // destinations one, so that a group starts with its row gathers and no dependent chain.
 template <typename T, int LPH, bool ALL, bool PAD>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, BwdP a, int64_t r_begin, int64_t r_end,
-                                                                int partial_row0)
+__device__ inline void bwd_few(const BwdTabs& tabs, const BwdP& a, int64_t r_begin, int64_t r_end, int block, int n_blocks,
+                               float* partial_row)
 {
     constexpr int B = LPH >= 8 ? 8 : 4;   // gather slots per round
     constexpr int R = 2;                  // slots per source
@@ -930,7 +937,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
     // ---- the lanes' read-ahead of list entries, ranges and destinations
     const bool meta_lane = lane < S * kAhead;
     const int mu = lane / kAhead, me = lane % kAhead;
-    const int64_t stride = (int64_t)gridDim.x * kWavesPerWG * S;
+    const int64_t stride = (int64_t)n_blocks * kWavesPerWG * S;
     struct Range { int q, j, beg, end, jo; };
     auto valid = [&](int64_t g) { return meta_lane && g + mu < r_end; };
     auto load_id = [&](int64_t g) -> uint32_t { return valid(g) ? a.rows[g + mu] : 0u; };
@@ -948,7 +955,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
     };
     auto load_dst = [&](const Range& m, int64_t g) { return (valid(g) && me < m.end - m.beg) ? s_ix[m.q][m.beg + me] : 0; };
 
-    int64_t g0 = r_begin + ((int64_t)blockIdx.x * kWavesPerWG + wave) * S;
+    int64_t g0 = r_begin + ((int64_t)block * kWavesPerWG + wave) * S;
     uint32_t id2 = load_id(g0 + 2 * stride);
     Range m0 = load_range(load_id(g0), g0), m1 = load_range(load_id(g0 + stride), g0 + stride);
     int dst0 = load_dst(m0, g0);
@@ -1099,8 +1106,16 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, Bw
             for (int w = 0; w < kWavesPerWG; ++w) s += part[w][lane][x];
             v[x] = s;
         }
-        store_f32<4>(a.partial + ((int64_t)partial_row0 + blockIdx.x) * kF + lane * 4, v);
+        store_f32<4>(partial_row + lane * 4, v);
     }
+}
+
+template <typename T, int LPH, bool ALL, bool PAD>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_few(BwdTabs tabs, BwdP a, int64_t r_begin, int64_t r_end,
+                                                                int partial_row0)
+{
+    bwd_few<T, LPH, ALL, PAD>(tabs, a, r_begin, r_end, (int)blockIdx.x, (int)gridDim.x,
+                              a.partial + ((int64_t)partial_row0 + blockIdx.x) * kF);
 }
 
 // ------------------------------------------- backward, sources of one edge
@@ -1123,7 +1138,8 @@ struct SingleP {
 };
 
 template <typename T, int LPH, bool PAD>
-__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs, BwdP a, SingleP s, int partial_row0)
+__device__ inline void bwd_single(const BwdTabs& tabs, const BwdP& a, const SingleP& s, int block, int n_blocks,
+                                  float* partial_row)
 {
     constexpr int B = LPH >= 8 ? 8 : 4;
     static_assert(B <= LPH, "a sub-batch must fit a head group");
@@ -1160,7 +1176,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
 
     // a wavefront takes `per` entries at a time, one per lane; the next ones travel meanwhile
     const int64_t n_chunks = (s.n + s.per - 1) / s.per;
-    const int64_t stride = (int64_t)gridDim.x * kWavesPerWG;
+    const int64_t stride = (int64_t)n_blocks * kWavesPerWG;
     struct Entry { int i; uint32_t id; int row; };
     auto load_entries = [&](int64_t c) {
         Entry e{0, 0u, 0};
@@ -1168,7 +1184,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
         if (c < n_chunks && lane < s.per && at < s.n) e = Entry{s.dst[at], s.src[at], s.row[at]};
         return e;
     };
-    int64_t c = (int64_t)blockIdx.x * kWavesPerWG + wave;
+    int64_t c = (int64_t)block * kWavesPerWG + wave;
     Entry cur = load_entries(c);
     for (; c < n_chunks; c += stride) {
         const Entry nxt = load_entries(c + stride);
@@ -1278,8 +1294,15 @@ __global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs,
             for (int w = 0; w < kWavesPerWG; ++w) sum += part[w][lane][x];
             v[x] = sum;
         }
-        store_f32<4>(a.partial + ((int64_t)partial_row0 + blockIdx.x) * kF + lane * 4, v);
+        store_f32<4>(partial_row + lane * 4, v);
     }
+}
+
+template <typename T, int LPH, bool PAD>
+__global__ __launch_bounds__(kGatherThreads) void k_gat_bwd_single(BwdTabs tabs, BwdP a, SingleP s, int partial_row0)
+{
+    bwd_single<T, LPH, PAD>(tabs, a, s, (int)blockIdx.x, (int)gridDim.x,
+                            a.partial + ((int64_t)partial_row0 + blockIdx.x) * kF);
 }
 
 }  // namespace f256
