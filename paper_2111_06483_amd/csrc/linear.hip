@@ -70,8 +70,22 @@ struct SkinnyArgs {
     // are stored as whole 64- or 128-byte row segments, or 0 to store element-wise
     int stage_off;
     RowsOp op;         // FUSE only: how the rows of A are formed
+    int vec_off = 0;   // Scores::kRows: byte offset in LDS of the columns' values of a1 and of a2
 };
 
+// kTile: as one more accumulator tile, from the unrounded sums.  kRows: from the rows as they are stored.
+enum class Scores { kNone, kTile, kRows };
+
+
+// Sums over lanes of four, the same bits in each.
+__device__ inline float add_xor2(float v)
+{
+    return v + __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x4E /* lane ^ 2 */, 0xf, 0xf, true));
+}
+__device__ inline float quad_sum(float v)
+{
+    return add_xor2(v + __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0xB1 /* lane ^ 1 */, 0xf, 0xf, true)));
+}
 
 // FUSE: the rows of A are not stored; each piece is formed where it is multiplied (RowsOp, K <= 256).
 // Between the epilogues a wavefront's staging tile is idle, so it holds what the pieces need: the
@@ -79,12 +93,18 @@ struct SkinnyArgs {
 // tile ahead (the map two), like the first pieces of its rows.
 constexpr int kDsRegs = 8;   // 32 rows x H <= 16 heads of ds, 64 lanes
 
+// Scores::kRows (bf16, heads of 32, 64 or 128 values): on their way through the staging tile four lanes hold a row's 32
+// values of a tile, eight each, as they would in a pass over the stored rows (k_scores in gat.hip).  They form the same sums in
+// the same order (a head's tiles are added pairwise, as that pass adds its lanes), so the bits are those of that pass.
+//
 // RAG: K is no whole number of pieces.
-template <typename TA, typename TC, int NT, bool SC, bool FUSE, bool RAG>
+template <typename TA, typename TC, int NT, Scores S, bool FUSE, bool RAG>
 __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
 {
-    static_assert(!(SC && FUSE), "the fused operand is that of dX = E W^T, which has no score columns");
+    constexpr bool SC = S == Scores::kTile, SR = S == Scores::kRows;
+    static_assert(!((SC || SR) && FUSE), "the fused operand is that of dX = E W^T, which has no scores");
     static_assert(!(RAG && (FUSE || SC)), "");
+    static_assert(!SR || sizeof(TC) == 2, "");
     constexpr int NA = NT + (SC ? 1 : 0);   // accumulator tiles: NT of the product, one of scores
     extern __shared__ __attribute__((aligned(16))) unsigned char skinny_lds[];
     constexpr bool BF = sizeof(TA) == 2;
@@ -161,8 +181,9 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
     // The loads of a set are issued together, ahead of the other set's MFMAs, and are first
     // needed a whole set later.  (The compiler waits for every load in flight, not for the oldest,
     // wherever stores may be in flight too, so a deeper ring of single loads gains nothing.)
-    // chunks per set: about 2000 MFMA cycles of one wavefront either way (two where registers run out)
-    constexpr int PS = (BF && !(SC && NT == 8)) ? 4 : 2;
+    // chunks per set: about 2000 MFMA cycles of one wavefront either way (two where registers run out: with four and scores of
+    // the stored rows four are spilled, 3.5 M rows of 128 to 256 712 us instead of 696)
+    constexpr int PS = (BF && !((SC || SR) && NT == 8)) ? 4 : 2;
     uint4 a[PS], b[PS];
     const TA* rowp;
     if constexpr (FUSE) {
@@ -278,6 +299,14 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
                 fh[at * 8 + e] = (uint16_t)hi;
                 fh[(at + 64) * 8 + e] = (uint16_t)f32_to_bf16_rne(v - __uint_as_float(hi << 16));
             }
+        }
+    }
+    float* const vecs = reinterpret_cast<float*>(skinny_lds + g.vec_off);
+    if constexpr (SR) {
+        for (int x = tid; x < 2 * NT * 32; x += kSkinnyThreads) {
+            const float* const from = x < NT * 32 ? g.a1 : g.a2;
+            const int64_t n = n0 + x % (NT * 32);
+            vecs[x] = from && n < g.N ? from[n] : 0.f;
         }
     }
     __syncthreads();
@@ -416,8 +445,19 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
             constexpr int kPieces = 32 / kPer;                // pieces per tile row
             constexpr int kRows = 64 / kPieces;               // tile rows per store instruction
             TC* stg = reinterpret_cast<TC*>(skinny_lds + g.stage_off + wave * (32 * 32 * (int)sizeof(TC)));
+            // Scores::kRows: of a row's four lanes lane j keeps the sums of vector j % 2 over the tiles 2k + j / 2
+            float sums[(NT + 1) / 2][32 / kRows] = {};
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
+                float av1[kPer], av2[kPer];
+                if constexpr (SR) {
+                    const float* const at = vecs + nt * 32 + lane % kPieces * kPer;
+#pragma unroll
+                    for (int x = 0; x < kPer; ++x) {
+                        av1[x] = at[x];
+                        av2[x] = at[NT * 32 + x];
+                    }
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     stg[(8 * (r / 4) + 4 * gq + (r % 4)) * 32 + c] = from_f32<TC>(acc[nt][r]);
@@ -427,6 +467,20 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
                     const int row = pass * kRows + lane / kPieces, piece = lane % kPieces;
                     const TC* from = stg + row * 32 + piece * kPer;
                     const int64_t i = row0 + row, n = n0 + nt * 32 + piece * kPer;
+                    if constexpr (SR) {
+                        float z[kPer], c1 = 0.f, c2 = 0.f;
+                        Vec<TC>::unpack(*reinterpret_cast<const uint4*>(from), z);
+#pragma unroll
+                        for (int x = 0; x < kPer; ++x) {
+                            c1 = fmaf(av1[x], z[x], c1);
+                            c2 = fmaf(av2[x], z[x], c2);
+                        }
+                        c1 = quad_sum(c1);
+                        c2 = quad_sum(c2);
+                        const float own = (lane & 1) ? c2 : c1;
+                        sums[nt / 2][pass] = (nt & 1) && (lane & 2) == 0 ? sums[nt / 2][pass] : own;
+                        asm volatile("" : "+v"(sums[nt / 2][pass]));     // formed here, not behind the last tile
+                    }
                     if (i < g.M) {
                         if (n + kPer <= g.N) {
                             store16(C + i * g.ldc + n, *reinterpret_cast<const uint4*>(from));
@@ -436,6 +490,52 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_gemm_skinny(SkinnyArgs g)
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
+                if constexpr (SR) __builtin_amdgcn_sched_barrier(0);     // one tile's values of the vectors at a time
+            }
+            if constexpr (SR) {
+                // the slab's heads, [32 rows][heads] of each vector, leave through the staging tile as whole lines
+                const int tiles = g.D >> 5, heads = NT / tiles;      // (powers of two, whole heads: scores_with_rows)
+                const int lg = 31 - __clz(heads);
+                float* const turn = reinterpret_cast<float*>(stg);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                int late = lane;
+                asm volatile("" : "+v"(late));     // (addresses formed here, not kept across the products)
+                const int vec = late & 1, odd = (late >> 1) & 1;
+#pragma unroll
+                for (int pass = 0; pass < 32 / kRows; ++pass) {
+                    const int row = pass * kRows + late / kPieces;
+                    float* const to = turn + ((vec * 32 + row) << lg);
+                    if (tiles == 1) {
+#pragma unroll
+                        for (int k = 0; k < (NT + 1) / 2; ++k)
+                            if (2 * k + odd < NT) to[2 * k + odd] = sums[k][pass];
+                    } else if constexpr (NT >= 2) {
+#pragma unroll
+                        for (int k = 0; k < NT / 2; ++k) sums[k][pass] = add_xor2(sums[k][pass]);
+                        if (tiles == 2) {
+#pragma unroll
+                            for (int k = 0; k < NT / 2; ++k)
+                                if (!odd) to[k] = sums[k][pass];
+                        } else if constexpr (NT >= 4) {
+#pragma unroll
+                            for (int k = 0; k < NT / 4; ++k)
+                                if (!odd) to[k] = sums[2 * k][pass] + sums[2 * k + 1][pass];
+                        }
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int h0 = (int)(n0 / g.D);
+                for (int x = late; x < 32 << lg; x += 64) {
+                    const int64_t i = row0 + (x >> lg);
+                    const int h = h0 + (x & (heads - 1));
+                    if (i < g.M && h < g.H) {
+                        if (g.s1) g.s1[i * g.H + h] = turn[x];
+                        if (g.s2) g.s2[i * g.H + h] = turn[(32 << lg) + x];
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
         } else {
 #pragma unroll
@@ -509,7 +609,7 @@ bool plan_skinny(int K, int N, int dtype, int extra_tiles, SkinnyPlan* p)
     return p->slabs <= 4;
 }
 
-template <typename TA, typename TC, int NT, bool SC, bool FUSE, bool RAG>
+template <typename TA, typename TC, int NT, Scores SC, bool FUSE, bool RAG>
 int launch_skinny_nt(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
 {
     int dev = 0;
@@ -528,7 +628,7 @@ int launch_skinny_nt(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
     return SAR_OK;
 }
 
-template <typename TA, typename TC, bool SC, bool FUSE = false>
+template <typename TA, typename TC, Scores SC = Scores::kNone, bool FUSE = false>
 int launch_skinny(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
 {
     auto with = [&](auto ragged) {
@@ -542,7 +642,7 @@ int launch_skinny(const SkinnyArgs& g, const SkinnyPlan& p, hipStream_t st)
         if constexpr (!FUSE) return launch_skinny_nt<TA, TC, 8, SC, FUSE, RAG>(g, p, st);
         return sar::fail(SAR_ERR_STATE, "rows formed on the fly take at most four accumulator tiles");
     };
-    if constexpr (!SC && !FUSE)
+    if constexpr (SC != Scores::kTile && !FUSE)
         if (g.K % (16 / (int)sizeof(TA)) != 0) return with(std::true_type{});
     return with(std::false_type{});
 }
@@ -554,6 +654,18 @@ bool plan_takes_rows_op(const SkinnyPlan& p, int K, int H, int dtype)
     const size_t tile = 32 * 32 * (dtype == SAR_F32 ? 4 : 2);
     // (with eight accumulator tiles the registers are spoken for)
     return p.nt <= 4 && p.stage_off != 0 && K <= 256 && H <= 2 * kDsRegs && (size_t)(32 * H + 256) * 4 <= tile;
+}
+
+// Which scores of stored bf16 rows are formed where the rows leave (Scores::kRows): heads of whole staging tiles, a power of
+// two of them, that no slab of columns divides (the sums are the pass's own there: an eighth of a wavefront's pieces to a lane), and
+// room for the slab's values of both vectors.  The others are a pass over the stored rows, which costs a read of all of them.  (Bound by
+// memory; us, product and pass / together: 3.5 M rows of 128 to 8 x 32 565 + 443 / 696, 313 thousand 71 + 39 / 87, 31 thousand of 256
+// to 4 x 64 27 + 19 / 24.)
+size_t row_score_bytes(const SkinnyPlan& p) { return (size_t)2 * p.nt * 32 * sizeof(float); }
+bool scores_with_rows(int D, const SkinnyPlan& p)
+{
+    return (D == 32 || D == 64 || D == 128) && p.nt * 32 % D == 0 && p.stage_off != 0 &&
+           p.lds + row_score_bytes(p) <= kSkinnyMaxLds;
 }
 
 // ---- products whose small operand does not fit in LDS -----------------------
@@ -1181,9 +1293,10 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     const bool rows_whole = dtype == SAR_BF16 || K % 4 == 0;
     // With fp32 rows the scores are two more columns of the product (z_h . a_h = x . (W_h a_h)),
     // equal to the scores of the stored rows up to fp32 rounding.  With bf16 rows they are taken
-    // from the STORED (rounded) rows in one pass afterwards: every later step reads those rows,
+    // from the STORED (rounded) rows: every later step reads those rows,
     // and a score of the unrounded sums differs from theirs by up to the storage rounding, which
-    // is enough to move LeakyReLU's kink for about one edge in a thousand.
+    // is enough to move LeakyReLU's kink for about one edge in a thousand.  (Where the shape allows it they
+    // are taken as the rows leave: scores_with_rows.)
     const size_t elem = dtype == SAR_F32 ? 4 : 2;
     const bool alone = apart(X, (size_t)n * K * elem, Z, (size_t)n * F * elem);
     if (want_scores && dtype == SAR_F32 && 2 * H <= 32 && rows_whole && plan_skinny(K, F, dtype, 1, &plan)) {
@@ -1191,7 +1304,7 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
             return sar::few_fwd(dtype, {X, n, W, Z, K, F, a_score, a_score2, score, score2, H, D}, false, st);
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, a_score, a_score2, score, score2, H, D,
                       plan.stage_off};
-        SAR_TRY((launch_skinny<float, float, true>(sk, plan, st)));
+        SAR_TRY((launch_skinny<float, float, Scores::kTile>(sk, plan, st)));
         return SAR_OK;
     }
     const bool natural = !(rows_whole && plan_skinny(K, F, dtype, 0, &plan));
@@ -1200,10 +1313,22 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
     } else if (!natural) {
         SkinnyArgs sk{X, K, n, W, F, 1, Z, F, K, F, plan.chunks, nullptr, nullptr, nullptr, nullptr, 0, 0,
                       plan.stage_off};
-        if (dtype == SAR_F32)
-            SAR_TRY((launch_skinny<float, float, false>(sk, plan, st)));
-        else
-            SAR_TRY((launch_skinny<bf16_t, bf16_t, false>(sk, plan, st)));
+        if (dtype == SAR_F32) {
+            SAR_TRY((launch_skinny<float, float>(sk, plan, st)));
+        } else if (want_scores && (uintptr_t)Z % 16 == 0 && scores_with_rows(D, plan)) {
+            sk.a1 = a_score;
+            sk.a2 = a_score2;
+            sk.s1 = score;
+            sk.s2 = score2;
+            sk.H = H;
+            sk.D = D;
+            sk.vec_off = (int)plan.lds;
+            plan.lds += row_score_bytes(plan);
+            SAR_TRY((launch_skinny<bf16_t, bf16_t, Scores::kRows>(sk, plan, st)));
+            return SAR_OK;
+        } else {
+            SAR_TRY((launch_skinny<bf16_t, bf16_t>(sk, plan, st)));
+        }
     } else {
         const StepArgs g{X, K, n, W, F, 1, Z, F, K, F, 0};
         SAR_TRY(dtype == SAR_F32 ? launch_steps<float>(g, st) : launch_steps<bf16_t>(g, st));
@@ -1406,13 +1531,13 @@ int linear_bwd_impl(const void* X, const void* dZ, int64_t dZ_rows, const RowsOp
             if (op) {
                 sk.op = *op;
                 if (dtype == SAR_F32)
-                    SAR_TRY((launch_skinny<float, float, false, true>(sk, plan, st)));
+                    SAR_TRY((launch_skinny<float, float, Scores::kNone, true>(sk, plan, st)));
                 else
-                    SAR_TRY((launch_skinny<bf16_t, bf16_t, false, true>(sk, plan, st)));
+                    SAR_TRY((launch_skinny<bf16_t, bf16_t, Scores::kNone, true>(sk, plan, st)));
             } else if (dtype == SAR_F32) {
-                SAR_TRY((launch_skinny<float, float, false>(sk, plan, st)));
+                SAR_TRY((launch_skinny<float, float>(sk, plan, st)));
             } else {
-                SAR_TRY((launch_skinny<bf16_t, bf16_t, false>(sk, plan, st)));
+                SAR_TRY((launch_skinny<bf16_t, bf16_t>(sk, plan, st)));
             }
         } else {
             if (op) return sar::fail(SAR_ERR_STATE, "rows formed on the fly need the skinny dX kernel");
