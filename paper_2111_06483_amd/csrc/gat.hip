@@ -1093,10 +1093,21 @@ unsigned persistent_grid(int64_t n_rows, int64_t n_long)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, kMaxPersistentWGs));
 }
 
-unsigned nodewise_grid(int64_t n, int slots)
+unsigned nodewise_grid(int64_t n, int slots, int64_t most = kMaxPersistentWGs)
 {
     const int64_t waves = (n + slots - 1) / slots;
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + kWavesPerWG - 1) / kWavesPerWG, kMaxPersistentWGs));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + kWavesPerWG - 1) / kWavesPerWG, most));
+}
+
+// k_bwd_begin reads two arrays and keeps nothing from row to row, so a wavefront may as well take its rows once, by workgroups that
+// come in the rows' order: walked by a resident grid the rows under way lie far apart, which memory answers more slowly.  Where
+// the two fit the 256 MiB memory-side cache the resident grid is the faster one, by what starting workgroups costs.  (us, resident / once:
+// bf16 8 x 32 3.5 M rows 893 / 748, fp32 4 x 100 2.5 M 985 / 919 twice, 4 x 64 306 thousand 124 / 118; 4 x 32 75 thousand 22.3 / 23.5, bf16
+// 4 x 64 31 thousand 10.5 / 11.1.  The next rows read ahead by a resident grid: 1008, 1079, 137.)
+int64_t begin_grid_most(int64_t n, int H, int D, int fb)
+{
+    constexpr int64_t kOnce = 1 << 22;      // (a launch counts its threads in 32 bits)
+    return 2 * n * H * D * fb > ((int64_t)256 << 20) ? kOnce : kMaxPersistentWGs;
 }
 
 #define SAR_DISPATCH_G(T, F, CALL)                                                   \
@@ -2027,7 +2038,7 @@ extern "C" int sar_gat_bwd_begin(const void* G, const void* out, const float* s,
         const void* Gg = shift(G, f0 * geo.hg.fb);
         const void* og = shift(out, f0 * geo.hg.fb);
         float4* recg = reinterpret_cast<float4*>(rec) + h0;
-        const unsigned grid = nodewise_grid(n_dst, geo.slots(g));
+        const unsigned grid = nodewise_grid(n_dst, geo.slots(g), begin_grid_most(n_dst, H, D, geo.hg.fb));
         SAR_DISPATCH_NODE(dtype, geo, (k_bwd_begin<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
                                           static_cast<const T*>(Gg), static_cast<const T*>(og), s + h0, L + h0, recg,
                                           ds + h0, n_dst, geo.hg.count(g), D, H * D, H, act,
