@@ -35,7 +35,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ("gat.hip", "gat_f256.h", "gat_slices.h", "gat_slices.hip", "gat_slots.h", "gather_common.h", "spmm.hip")
+KERNEL_SOURCES = ("gat.hip", "gat_f256.h", "gat_joint.h", "gat_joint_launch.h", "gat_slices.h", "gat_slices.hip", "gat_slots.h",
+                  "gather_common.h", "global_ptr.h", "spmm.hip")
 
 
 def parse():
