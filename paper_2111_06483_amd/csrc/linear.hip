@@ -657,8 +657,8 @@ bool plan_takes_rows_op(const SkinnyPlan& p, int K, int H, int dtype)
 }
 
 // Which scores of stored bf16 rows are formed where the rows leave (Scores::kRows): heads of whole staging tiles, a power of
-// two of them, that no slab of columns divides (the sums are the pass's own there: an eighth of a wavefront's pieces to a lane), and
-// room for the slab's values of both vectors.  The others are a pass over the stored rows, which costs a read of all of them.  (Bound by
+// two of them, that no slab of columns divides (a lane then holds eight values of one head, as a lane of the pass does, and the sums are the
+// pass's own), and room for the slab's values of both vectors.  The others are a pass over the stored rows, which costs a read of all of them.  (Bound by
 // memory; us, product and pass / together: 3.5 M rows of 128 to 8 x 32 565 + 443 / 696, 313 thousand 71 + 39 / 87, 31 thousand of 256
 // to 4 x 64 27 + 19 / 24.)
 size_t row_score_bytes(const SkinnyPlan& p) { return (size_t)2 * p.nt * 32 * sizeof(float); }
