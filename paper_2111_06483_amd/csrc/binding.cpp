@@ -22,26 +22,28 @@ namespace {
 // A Python error is set.
 struct Raised {};
 
-PyObject* sar_module()
-{
-    PyObject* m = PyImport_ImportModule("paper_2111_06483_amd.sar");
-    if (!m) throw Raised{};
-    return m;
-}
+// What the library, or a check here, refuses: sar.SarError with this code and text.
+struct Refused {
+    int code;
+    std::string text;
+};
 
-[[noreturn]] void raise_sar(int code, const std::string& text)
+[[noreturn]] void raise_sar(int code, const std::string& text) { throw Refused{code, text}; }
+
+// SarError is that of the package this module was imported as a part of, whatever its name.
+void set_error(PyObject* self, const Refused& r)
 {
-    PyObject* m = sar_module();
-    PyObject* type = PyObject_GetAttrString(m, "SarError");
-    Py_DECREF(m);
-    if (!type) throw Raised{};
-    PyObject* e = PyObject_CallFunction(type, "is", code, text.c_str());
-    if (e) {
-        PyErr_SetObject(type, e);
-        Py_DECREF(e);
-    }
-    Py_DECREF(type);
-    throw Raised{};
+    const char* own = PyModule_GetName(self);
+    if (!own) return;
+    std::string name(own);
+    name.erase(name.rfind('.') + 1);
+    PyObject* m = PyImport_ImportModule((name + "sar").c_str());
+    PyObject* type = m ? PyObject_GetAttrString(m, "SarError") : nullptr;
+    PyObject* e = type ? PyObject_CallFunction(type, "is", r.code, r.text.c_str()) : nullptr;
+    if (e) PyErr_SetObject(type, e);
+    Py_XDECREF(e);
+    Py_XDECREF(type);
+    Py_XDECREF(m);
 }
 
 [[noreturn]] void refuse(const char* fmt, ...) __attribute__((format(printf, 1, 2)));
@@ -170,26 +172,25 @@ void unpack_sizes(const at::Tensor& t, int64_t (&out)[N])
     for (int d = 0; d < N; ++d) out[d] = t.size(d);
 }
 
-// The stream work is sent to: torch's current one; the device's own before torch has set up the device.
+// torch.cuda.<what>()
+PyObject* cuda(const char* what)
+{
+    PyObject* m = PyImport_ImportModule("torch.cuda");
+    PyObject* r = m ? PyObject_CallMethod(m, what, nullptr) : nullptr;
+    Py_XDECREF(m);
+    if (!r) throw Raised{};
+    Py_DECREF(r);                    // (True, False, or an object that is not looked at)
+    return r;
+}
+
+// The stream work is sent to: torch's current one, which sets up the device where nothing has; null where there is none.
 void* stream()
 {
     static bool ready = false;       // torch.cuda.is_initialized() does not go back
     if (!ready) {
-        PyObject* m = PyImport_ImportModule("torch.cuda");
-        PyObject* r = m ? PyObject_CallMethod(m, "is_initialized", nullptr) : nullptr;
-        Py_XDECREF(m);
-        if (!r) throw Raised{};
-        const bool is = r == Py_True;
-        Py_DECREF(r);
-        if (!is) {
-            PyObject* s = sar_module();
-            PyObject* v = PyObject_CallMethod(s, "_stream", nullptr);
-            Py_DECREF(s);
-            if (!v) throw Raised{};
-            void* p = v == Py_None ? nullptr : PyLong_AsVoidPtr(v);
-            Py_DECREF(v);
-            if (PyErr_Occurred()) throw Raised{};
-            return p;
+        if (cuda("is_initialized") != Py_True) {
+            if (cuda("is_available") != Py_True) return nullptr;
+            cuda("current_stream");
         }
         ready = true;
     }
@@ -307,7 +308,7 @@ void call(F&& f)
 }
 
 template <int N, typename F>
-PyObject* entry(PyObject* const* a, Py_ssize_t n, F&& f)
+PyObject* entry(PyObject* self, PyObject* const* a, Py_ssize_t n, F&& f)
 {
     HANDLE_TH_ERRORS
     if (n != N) {
@@ -318,12 +319,15 @@ PyObject* entry(PyObject* const* a, Py_ssize_t n, F&& f)
         f(a);
     } catch (const Raised&) {
         return nullptr;
+    } catch (const Refused& r) {
+        set_error(self, r);
+        return nullptr;
     }
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
 #define SAR_CALL(name, n_args) \
-    PyObject* name(PyObject*, PyObject* const* args, Py_ssize_t n) { return entry<n_args>(args, n, [](PyObject* const* a) {
+    PyObject* name(PyObject* self, PyObject* const* args, Py_ssize_t n) { return entry<n_args>(self, args, n, [](PyObject* const* a) {
 #define SAR_CALL_END }); }
 
 // b, Zq, mean, out, residual, act

@@ -84,3 +84,34 @@ def test_lists_of_blocks():
     with pytest.raises(IndexError):
         sar.sar_spmm_all(b, good[:1], False, out)
     b.close()
+
+
+def in_a_copy(tmp_path, name, code):
+    """Runs `code` in a fresh interpreter where a copy of the built package is importable as `name` and nothing else of it is."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    home = tmp_path / name
+    home.mkdir()
+    for f in os.listdir(os.path.dirname(sar.__file__)):
+        if f.endswith((".py", ".so")):
+            shutil.copy(os.path.join(os.path.dirname(sar.__file__), f), home / f)
+    return subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True,
+                          env={k: v for k, v in os.environ.items() if k != "PYTHONPATH"})
+
+
+def test_errors_are_of_the_package_the_binding_belongs_to(tmp_path):
+    r = in_a_copy(tmp_path, "under_another_name", """
+import torch
+from under_another_name import sar
+try:
+    sar.sar_act_bwd(torch.zeros(4, 8), torch.zeros(8, 4), 0, torch.zeros(4, 8))
+except sar.SarError as e:
+    assert e.code == sar.SAR_ERR_INVALID_ARG and "must match" in str(e), e
+else:
+    raise AssertionError("not refused")
+import sys
+assert "paper_2111_06483_amd" not in sys.modules
+""")
+    assert r.returncode == 0, r.stderr
