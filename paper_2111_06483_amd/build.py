@@ -26,10 +26,16 @@ HIPCC_FLAGS = [
 ]
 
 
+def binding_for() -> str:
+    """The interpreter and the torch whose objects the binding reads by their headers' layout."""
+    import torch
+    return "python %d.%d, torch %s %s" % (*sys.version_info[:2], torch.__version__, torch.version.git_version)
+
+
 def binding_flags():
     """The binding is host code that reads torch's tensors: compiled against the installed torch's headers."""
     from torch.utils import cpp_extension
-    return ["-O2", "-std=c++17", "-fPIC", "-w", "-DUSE_ROCM", "-isystem", sysconfig.get_paths()["include"],
+    return ["-O2", '-DSAR_BUILT_FOR="%s"' % binding_for(), "-std=c++17", "-fPIC", "-w", "-DUSE_ROCM", "-isystem", sysconfig.get_paths()["include"],
             *[f for path in cpp_extension.include_paths() for f in ("-isystem", path)]]
 
 

@@ -79,15 +79,18 @@ _native = None
 
 
 def native():
-    """The loaded binding of the hot calls; raises if it has not been built."""
+    """The loaded binding of the hot calls; raises if it has not been built, or not for this interpreter and torch."""
     global _native
     if _native is None:
         lib()
+        how = "build it with `python -m paper_2111_06483_amd.build` (there is no fallback path)"
         try:
-            from . import _binding
+            from . import _binding, build
         except ImportError as e:
-            raise RuntimeError("_binding.so does not load (%s): build it with `python -m paper_2111_06483_amd.build` "
-                               "(there is no fallback path)" % e) from e
+            raise RuntimeError("_binding.so does not load (%s): %s" % (e, how)) from e
+        built_for, here = getattr(_binding, "built_for", "another version"), build.binding_for()
+        if built_for != here:
+            raise RuntimeError("_binding.so reads tensors by the headers of %s, and this is %s: %s" % (built_for, here, how))
         _native = _binding
     return _native
 

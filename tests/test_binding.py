@@ -115,3 +115,23 @@ import sys
 assert "paper_2111_06483_amd" not in sys.modules
 """)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("changed", ["torch.__version__ = '2.11.0'", "torch.version.git_version = '0' * 40",
+                                     "sys.version_info = (3, 99) + sys.version_info[2:]"])
+def test_a_binding_built_for_another_torch_or_interpreter(changed):
+    import os
+    import subprocess
+    import sys
+    r = subprocess.run([sys.executable, "-c", """
+import sys, torch
+from paper_2111_06483_amd import sar
+%s
+try:
+    sar.sar_gat_scores(torch.zeros(0, 2, 8), torch.zeros(2, 8), torch.zeros(0, 2))
+except RuntimeError as e:
+    assert "_binding.so" in str(e) and "build" in str(e), e
+else:
+    raise AssertionError("taken")
+""" % changed], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
