@@ -67,7 +67,8 @@ void check(int rc)
 const at::Tensor& tensor(PyObject* o)
 {
     if (!THPVariable_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "expected a tensor, got %s", Py_TYPE(o)->tp_name);
+        // (None has none of a tensor's attributes, and says so)
+        PyErr_Format(o == Py_None ? PyExc_AttributeError : PyExc_TypeError, "expected a tensor, got %s", Py_TYPE(o)->tp_name);
         throw Raised{};
     }
     return THPVariable_Unpack(o);
@@ -139,10 +140,10 @@ int dtype_code(at::ScalarType t)
     raise_sar(SAR_ERR_UNSUPPORTED, "dtype " + type_name(t));
 }
 
-size_t bytes_of(PyObject* o)
-{
-    return o == Py_None ? 0 : tensor(o).numel() * tensor(o).element_size();
-}
+size_t bytes_of(PyObject* o) { return tensor(o).numel() * tensor(o).element_size(); }
+
+// ... of scratch that a call may do without
+size_t bytes_if(PyObject* o) { return o == Py_None ? 0 : bytes_of(o); }
 
 std::string shape_text(const at::Tensor& t)
 {
@@ -570,7 +571,7 @@ SAR_CALL(linear_bwd, 6)
     void *const x = ptr(a[0]), *const dz = ptr_of(dZ), *const dx = ptr(a[4]), *const work = ptr(a[5]), *const st = stream();
     float *const w = ptr<float>(a[2]), *const dw = ptr<float>(a[3]);
     const int dt = dtype_code(dZ.scalar_type());
-    const size_t wb = bytes_of(a[5]);
+    const size_t wb = bytes_if(a[5]);
     call([&] { return sar_linear_bwd(x, dz, w, dw, dx, dt, rows, (int)K, (int)F, work, wb, st); });
 SAR_CALL_END
 
@@ -582,7 +583,7 @@ SAR_CALL(linear_bwd_rows, 14)
     float *const ds = ptr<float>(a[3]), *const ar = ptr<float>(a[4]), *const w = ptr<float>(a[7]), *const dw = ptr<float>(a[8]);
     const int H = (int)integer(a[5]), D = (int)integer(a[6]), dt = (int)integer(a[11]);
     void* const st = stream();
-    const size_t wb = bytes_of(a[12]);
+    const size_t wb = bytes_if(a[12]);
     call([&] {
         return sar_linear_bwd_rows(x, e, rank, n_E, ds, ar, H, D, w, dw, dx, dt, n_rows, (int)K, rows, work, wb, st);
     });

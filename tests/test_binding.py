@@ -44,6 +44,20 @@ def test_tensors_that_are_no_plain_memory():
         sar.sar_act_bwd(torch.zeros(4), torch.zeros(4), None, torch.zeros(4))
 
 
+def test_none_for_a_tensor_that_a_call_needs():
+    z, a, v = torch.zeros(4, 2, 8), torch.zeros(2, 8), torch.zeros(4, 2)
+    for call in (lambda: sar.sar_gat_scores(None, a, v), lambda: sar.sar_gat_scores(z, None, v),
+                 lambda: sar.sar_gat_fwd_begin(v, v, None), lambda: sar.sar_gat_fwd_end(v, v, z, None, v),
+                 lambda: sar.sar_gat_bwd_begin(None, z, v, v, torch.zeros(4, 2, 4), v),
+                 lambda: sar.sar_gat_bwd_end(z, v, a, None, None, a, None),       # (scratch, which the call cannot do without)
+                 lambda: sar.sar_gat_bwd_end(None, v, a, None, None, a, v), lambda: sar.sar_error_add(None, None, False, None),
+                 lambda: sar.sar_linear_fwd(None, a, v), lambda: sar.sar_linear_fwd(v, None, v),
+                 lambda: sar.sar_linear_bwd(v, None, a, None, None, None),
+                 lambda: sar.sar_act_bwd(None, v, sar.SAR_ACT_RELU, v)):
+        with pytest.raises(AttributeError):
+            call()
+
+
 def test_a_freed_handle():
     for call in (lambda b: sar.sar_spmm_all(b, [], True, torch.zeros(4, 8)),
                  lambda b: sar.sar_spmm_bwd_all(b, torch.zeros(4, 8), True, []),
