@@ -259,6 +259,11 @@ struct List {
     ~List() { Py_XDECREF(items); }
     void open(PyObject* seq)
     {
+        // by position: a set has no order, and an iterator is at its end after one look
+        if (!PySequence_Check(seq) && !THPVariable_Check(seq)) {
+            PyErr_Format(PyExc_TypeError, "expected one tensor per block, got %s", Py_TYPE(seq)->tp_name);
+            throw Raised{};
+        }
         items = PySequence_Fast(seq, "expected one tensor per block");
         if (!items) throw Raised{};
     }

@@ -100,6 +100,21 @@ def test_lists_of_blocks():
     b.close()
 
 
+@pytest.mark.gpu
+def test_lists_of_blocks_are_by_position():
+    part = torch.tensor([0, 1, 0, 1], dtype=torch.int32, device="cuda")
+    b = sar.sar_blocks_build(torch.tensor([0, 1, 3], device="cuda"), torch.tensor([2, 0, 0], device="cuda"), part, 2, 0)
+    out, Z = torch.zeros(2, 8, device="cuda"), torch.ones(2, 2, 8, device="cuda")
+    for good in (list(Z), tuple(Z), Z):                  # (one tensor of all blocks' rows is its own list)
+        out.zero_()
+        sar.sar_spmm_all(b, good, False, out)
+        assert out.sum().item() == 24.0
+    for bad in (set(Z), iter(Z), (z for z in Z), None, 3):
+        with pytest.raises(TypeError):
+            sar.sar_spmm_all(b, bad, False, out)
+    b.close()
+
+
 def in_a_copy(tmp_path, name, code):
     """Runs `code` in a fresh interpreter where a copy of the built package is importable as `name` and nothing else of it is."""
     import os
