@@ -1308,6 +1308,11 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
         return SAR_OK;
     }
     const bool natural = !(rows_whole && plan_skinny(K, F, dtype, 0, &plan));
+    // scores written over X or W, which a caller may be done with, wait until all rows are formed
+    auto clear = [&](const float* s) {
+        const size_t bytes = (size_t)n * H * sizeof(float);
+        return !s || (apart(X, (size_t)n * K * elem, s, bytes) && apart(W, (size_t)K * F * sizeof(float), s, bytes));
+    };
     if (alone && sar::few_rows(dtype, n, K, F, false, natural ? 2 : plan.nt)) {
         SAR_TRY(sar::few_fwd(dtype, {X, n, W, Z, K, F, nullptr, nullptr, nullptr, nullptr, 0, 0}, natural, st));
     } else if (!natural) {
@@ -1315,7 +1320,7 @@ extern "C" int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype,
                       plan.stage_off};
         if (dtype == SAR_F32) {
             SAR_TRY((launch_skinny<float, float>(sk, plan, st)));
-        } else if (want_scores && (uintptr_t)Z % 16 == 0 && scores_with_rows(D, plan)) {
+        } else if (want_scores && (uintptr_t)Z % 16 == 0 && scores_with_rows(D, plan) && clear(score) && clear(score2)) {
             sk.a1 = a_score;
             sk.a2 = a_score2;
             sk.s1 = score;

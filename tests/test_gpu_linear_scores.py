@@ -44,3 +44,28 @@ def test_scores_of_many_rows(H, D, K, n):
         assert torch.equal(torch.isfinite(s), torch.isfinite(w))
     sar.sar_linear_fwd(X, W, Z, a2, one)                  # one vector alone
     assert torch.equal(bits(one)[finite], bits(w2)[finite])
+
+
+@pytest.mark.parametrize("over", ["first", "last", "weights"])
+@pytest.mark.parametrize("second", [False, True])
+def test_scores_over_an_operand(over, second):
+    """Scores may lie over the inputs or the weights: rows and scores are those of a call with memory of their own."""
+    n, K, H, D = 70_001, 128, 8, 32
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(n, K, generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn(K, H * D, generator=g, device="cuda") / K ** 0.5
+    a1, a2 = (torch.randn(H, D, generator=g, device="cuda") for _ in range(2))
+    want, w1, w2 = torch.empty(n, H * D, dtype=torch.bfloat16, device="cuda"), *(torch.empty(n, H, device="cuda") for _ in range(2))
+    sar.sar_linear_fwd(X, W, want, a1, w1, a2, w2)
+    Z, own = torch.empty_like(want), torch.empty(n, H, device="cuda")
+    if over == "weights":
+        room = torch.zeros(n * H, device="cuda")
+        room[:W.numel()] = W.flatten()
+        W, shared = room[:W.numel()].view(K, H * D), room.view(n, H)
+    else:
+        flat = X.flatten().view(torch.float32)
+        shared = (flat[:n * H] if over == "first" else flat[-n * H:]).view(n, H)
+    sar.sar_linear_fwd(X, W, Z, a1, own if second else shared, a2, shared if second else own)
+    assert torch.equal(Z, want)
+    s1, s2 = (own, shared) if second else (shared, own)
+    assert torch.equal(s1, w1) and torch.equal(s2, w2)
