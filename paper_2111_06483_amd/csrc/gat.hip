@@ -1100,14 +1100,22 @@ unsigned nodewise_grid(int64_t n, int slots, int64_t most = kMaxPersistentWGs)
 }
 
 // k_bwd_begin reads two arrays and keeps nothing from row to row, so a wavefront may as well take its rows once, by workgroups that
-// come in the rows' order: walked by a resident grid the rows under way lie far apart, which memory answers more slowly.  Where
-// the two fit the 256 MiB memory-side cache the resident grid is the faster one, by what starting workgroups costs.  (us, resident / once:
-// bf16 8 x 32 3.5 M rows 893 / 748, fp32 4 x 100 2.5 M 985 / 919 twice, 4 x 64 306 thousand 124 / 118; 4 x 32 75 thousand 22.3 / 23.5, bf16
-// 4 x 64 31 thousand 10.5 / 11.1.  The next rows read ahead by a resident grid: 1008, 1079, 137.)
-int64_t begin_grid_most(int64_t n, int H, int D, int fb)
+// come in the rows' order: walked by a resident grid the rows under way lie far apart, which memory answers more slowly.  Against it
+// stands what starting workgroups costs.  That decides for a launch whose two arrays fit the 256 MiB memory-side cache, for wavefronts that
+// move little at a time, and for rows of unaligned pieces.
+// fp32 4 x 64, us, resident / once: arrays of 160 MiB 30 / 32 where the call before has read them, 65 / 63 where they are in no cache; 260
+// MiB 47 / 49, 99 / 96; 320 MiB 69 / 67, 115 / 107; 1500 MiB 322 / 292, 374 / 334; 5000 MiB 1159 / 958, 1201 / 1009.
+// Once / resident by the bytes a wavefront moves at a time, least and most of 320 and 1500 MiB, cached and not:
+//   856 to 1216  1.13 1.33  (bf16 2 x 100, 4 x 20, 5 x 40, 3 x 12, 4 x 12)        1264 to 1320  0.99 1.09  (2 x 36, 3 x 24)
+//   1504         0.98 1.06  (4 x 20)             1628 to 1656  0.92 1.03  (1 x 200, 1 x 48, 2 x 100, 1 x 100)
+//   1704         0.93 1.02  (3 x 32, bf16 3 x 64)       1860 0.86 0.99  (3 x 12)       2160 0.88 0.98  (4 x 64)       2816 0.83 0.87  (bf16 8 x 4)
+//   unaligned, 280 and 1200 MiB: fp32 1 x 47 (1616) 0.97 1.12, bf16 (864) 1.29 1.34
+int64_t begin_grid_most(int64_t n, const NodeGeo& geo, int g, int D)
 {
     constexpr int64_t kOnce = 1 << 22;      // (a launch counts its threads in 32 bits)
-    return 2 * n * H * D * fb > ((int64_t)256 << 20) ? kOnce : kMaxPersistentWGs;
+    const int64_t heads = geo.hg.count(g), rows = 2 * heads * D * geo.hg.fb;
+    const int64_t moved = geo.slots(g) * (rows + heads * 28);     // with a record of 16 bytes, s, L and ds
+    return !geo.ragged && moved >= 1600 && n * rows > ((int64_t)320 << 20) ? kOnce : kMaxPersistentWGs;
 }
 
 #define SAR_DISPATCH_G(T, F, CALL)                                                   \
@@ -2038,7 +2046,7 @@ extern "C" int sar_gat_bwd_begin(const void* G, const void* out, const float* s,
         const void* Gg = shift(G, f0 * geo.hg.fb);
         const void* og = shift(out, f0 * geo.hg.fb);
         float4* recg = reinterpret_cast<float4*>(rec) + h0;
-        const unsigned grid = nodewise_grid(n_dst, geo.slots(g), begin_grid_most(n_dst, H, D, geo.hg.fb));
+        const unsigned grid = nodewise_grid(n_dst, geo.slots(g), begin_grid_most(n_dst, geo, g, D));
         SAR_DISPATCH_NODE(dtype, geo, (k_bwd_begin<T, kV, kL, kR><<<grid, kGatherThreads, 0, st>>>(
                                           static_cast<const T*>(Gg), static_cast<const T*>(og), s + h0, L + h0, recg,
                                           ds + h0, n_dst, geo.hg.count(g), D, H * D, H, act,

@@ -25,6 +25,22 @@ def kernels_of(fn) -> str:
     return "\n".join(e.name for e in p.events())
 
 
+def launches_of(fn):
+    """(kernel's name, its workgroups) for every kernel that fn() runs."""
+    import json
+    import os
+    import tempfile
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    with tempfile.TemporaryDirectory() as d:
+        trace = os.path.join(d, "trace.json")
+        p.export_chrome_trace(trace)
+        with open(trace) as f:
+            events = json.load(f)["traceEvents"]
+    return [(e["name"], int(np.prod(e["args"]["grid"]))) for e in events if e.get("cat") == "kernel"]
+
+
 def dev(a, dtype=None) -> torch.Tensor:
     t = torch.as_tensor(np.ascontiguousarray(a))
     if dtype is not None:

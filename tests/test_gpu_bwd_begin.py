@@ -33,3 +33,30 @@ def test_records(n, H, D, dtype, act):
     assert ((rec[..., 2].double() - want).abs() <= room).all()
     for k, t in ((0, s), (1, L)):
         assert ((rec[..., k].double() - t.double() / math.log(2.0)).abs() <= t.double().abs() * 2.0 ** -21).all()
+
+
+# arrays beyond the memory-side cache: wavefronts that move little at a time and rows of unaligned pieces stay with a resident grid,
+# as arrays do that a part of fits it; the size counts launch by launch where heads are shared among several
+@pytest.mark.parametrize("mib,H,D,dtype,once", [
+    (400, 2, 100, torch.bfloat16, False), (1200, 2, 100, torch.bfloat16, False), (400, 1, 47, torch.bfloat16, False),
+    (1200, 1, 47, torch.float32, False), (400, 5, 40, torch.bfloat16, False), (400, 4, 20, torch.float32, False),
+    (280, 4, 64, torch.float32, False), (400, 4, 64, torch.float32, True), (400, 8, 32, torch.bfloat16, True),
+    (400, 3, 12, torch.float32, True), (400, 2, 100, torch.float32, True), (400, 8, 4, torch.bfloat16, True),
+    (500, 4, 100, torch.float32, False), (1000, 4, 100, torch.float32, True)])
+def test_which_rows_are_taken_once(mib, H, D, dtype, once):
+    from tests import gpu_util as gu
+    n = (mib << 20) // (2 * H * D * (4 if dtype == torch.float32 else 2))
+    G, out, s, L = (torch.ones(n, *shape, device="cuda") for shape in ((H, D), (H, D), (H,), (H,)))
+    G, out = G.to(dtype), out.to(dtype)
+    rec, ds = torch.empty(n, H, 4, device="cuda"), torch.empty(n, H, device="cuda")
+    grids = [wgs for name, wgs in gu.launches_of(lambda: sar.sar_gat_bwd_begin(G, out, s, L, rec, ds)) if "k_bwd_begin" in name]
+    assert grids and all((g > 2048) == once for g in grids), grids
+
+
+# beyond the size: the last wavefront full, with one row, and with some of its slots
+@pytest.mark.parametrize("n,H,D,dtype", [(163_841, 4, 64, torch.float32), (330_003, 8, 32, torch.bfloat16),
+                                         (1_200_001, 3, 12, torch.float32), (220_001, 4, 100, torch.float32),
+                                         (2_700_000, 8, 4, torch.bfloat16)])
+@pytest.mark.parametrize("act", [sar.SAR_ACT_NONE, sar.SAR_ACT_RELU])
+def test_records_of_rows_taken_once(n, H, D, dtype, act):
+    test_records(n, H, D, dtype, act)
