@@ -2,9 +2,13 @@
 //
 // Sources of 8 edges and more, the others, and those of one edge have kernels of their own, which do not depend on each other.
 // In a small call none of them fills the chip, and each is a launch and a chain of loads of 5 to 10 us.  Here their workgroups
-// are one launch where all of them are resident at once; beyond that the kernels run one after the other, each with the registers
-// it needs.  (Kernels one after the other / together, us: 8 x 32 over 12 thousand edges 27 / 14, 2 x 100 over 60 thousand 26 / 14, 5
-// x 40 of two launches over 100 thousand 64 / 19; a step of 2 x 100 over 15 thousand nodes in 9 blocks 74 / 63.)
+// are one launch where there are two parts at least and all workgroups that they ask for are resident at once; beyond that the kernels
+// run one after the other, each with the registers it needs.  (Kernels one after the other / together, us: 8 x 32 over 12 thousand
+// edges 27 / 14, 2 x 100 over 60 thousand 26 / 14, 5 x 40 of two launches over 100 thousand 64 / 19; a step of 2 x 100 over 15 thousand
+// nodes in 9 blocks 74 / 63.)  Parts that go round lose by it, and so does a part alone: this kernel holds three or four workgroups
+// a CU, the others up to seven, and gives single-edge sources half the chip.  (800 wide sources and 1600 of three edges beside single-edge ones,
+// bf16 4 x 64: 65 thousand 36 / 31, 131 thousand 47 / 47, 262 thousand 81 / 94, 2 million 465 / 597; fp32 8 x 32 49 / 40, 80 / 83, 144 / 137,
+// 878 / 906.  Sources of three edges alone, bf16 4 x 64: 30 thousand 26 / 28, 300 thousand 143 / 158, 2 million 859 / 976.)
 #pragma once
 
 #include "gat_slots.h"

@@ -22,19 +22,21 @@ int launch(const f256::BwdTabs& t, const f256::BwdP& p, Work w, int* grid, hipSt
     static const int resident = resident_workgroups(kernel);
     const int64_t per_wg = (int64_t)(SLOTS ? w.n_slots : (LPH >= 8 ? 8 : 4) / 2) * kWavesPerWG;
     Grid g{};
-    if (p.n_rows > 0) g.wide = (int)persistent_grid_for(p.n_rows, p.n_long, resident);
+    // (a part that would go round asks for more workgroups than there are)
+    if (p.n_rows > 0) g.wide = (int)persistent_grid_for(p.n_rows, p.n_long, resident + 1);
     for (int k = 0; k < 2; ++k) {
         const int64_t n = w.piece[k][1] - w.piece[k][0];
-        if (n > 0) g.few[k] = (int)grid_of(n, per_wg, resident);
+        if (n > 0) g.few[k] = (int)grid_of(n, per_wg, resident + 1);
     }
     if (w.single.n > 0) {
         unsigned n = 0;
+        const int64_t once = (int64_t)(resident / 2) * kWavesPerWG * kWave;
         w.single = single_list(w.single, resident / 2, n);
-        g.single = (int)n;
+        g.single = w.single.n > once ? resident + 1 : (int)n;
     }
     *grid = 0;
-    const int total = g.total();
-    if (total == 0 || total > resident) return SAR_OK;
+    const int total = g.total(), parts = (g.wide > 0) + (g.few[0] > 0) + (g.few[1] > 0) + (g.single > 0);
+    if (parts < 2 || total > resident) return SAR_OK;
     kernel<<<(unsigned)total, kGatherThreads, 0, st>>>(t, p, w, g);
     SAR_LAUNCH_CHECK();
     *grid = total;

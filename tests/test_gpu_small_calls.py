@@ -80,3 +80,92 @@ def test_one_launch_and_several(dtype, H, D, flags, compact, per_block):
     assert rel_err(f64(ds), wb.ds) < tol
     assert rel_err(f64(da_l), wb.da_l) < tol
     b.close()
+
+
+class Call:
+    """A backward call's tensors for edges (src, dst) with unit-variance rows."""
+
+    def __init__(self, src, dst, part, P, H, D, dtype, flags=0, seed=2):
+        self.b = gu.build_blocks(src, dst, part, P, 0, flags=3 | flags)
+        self.P, self.H, self.D, self.dtype, n = P, H, D, dtype, self.b.n_dst
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        randn = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+        self.Zs = [randn(self.b.n_src(q), H, D).to(dtype) for q in range(P)]
+        self.a_l, self.a_r = randn(H, D) / D ** 0.5, randn(H, D) / D ** 0.5
+        self.fw = gu.gat_fwd_all(self.b, self.Zs[0], self.Zs, self.a_l, self.a_r, SLOPE)
+        self.G = randn(n, H, D).to(dtype)
+        self.rec = torch.empty((n, H, 4), device="cuda")
+        self.work = torch.empty(sar.sar_gat_workspace_bytes(n, 0, H, D) // 4, device="cuda")
+
+    def run(self, batched=True):
+        empty = lambda *shape, dtype=torch.float32: torch.full(shape, float("nan"), dtype=dtype, device="cuda")
+        ds, da_l = empty(self.b.n_dst, self.H), torch.zeros((self.H, self.D), device="cuda")
+        rows = [self.b.n_err_rows(q) for q in range(self.P)]
+        dZs = [empty(r, self.H, self.D, dtype=self.dtype) for r in rows]
+        dts = [empty(r, self.H) for r in rows]
+        sar.sar_gat_bwd_begin(self.G, self.fw.out, self.fw.s, self.fw.L, self.rec, ds)
+
+        def backward():
+            if batched:
+                sar.sar_gat_bwd_all(self.b, self.Zs, self.G, None, self.rec, self.a_l, SLOPE, dZs, dts, ds, da_l, self.work)
+                return
+            for q in range(self.P):
+                sar.sar_gat_bwd_block(self.b, q, self.Zs[q], self.G, None, self.rec, self.a_l, SLOPE, dZs[q], dts[q], ds, da_l,
+                                      self.work)
+
+        return gu.kernels_of(backward), dZs + dts + [ds, da_l]
+
+
+SEPARATE = ("k_gat_bwd_f256", "k_gat_bwd_few", "k_gat_bwd_single", "k_gat_bwd_slots")
+
+
+@pytest.mark.parametrize("dtype,H,D", [(torch.float32, 8, 32), (torch.bfloat16, 4, 64), (torch.bfloat16, 2, 100),
+                                       (torch.float32, 3, 64), (torch.bfloat16, 4, 16)])
+@pytest.mark.parametrize("batched", [True, False])
+@pytest.mark.parametrize("per_block", [40, 700, 24000])
+def test_which_calls_are_one_launch(dtype, H, D, batched, per_block):
+    """Small calls, all blocks and block by block, are one launch where the kernels are several; larger ones are not.  All give
+    what the other form of the call gives."""
+    src, dst, part, _ = graph(5, 150, per_block, 3)
+    c = Call(src, dst, part, 3, H, D, dtype, sar.SAR_BUILD_SINGLES)
+    kernels, got = c.run(batched)
+    _, want = c.run(not batched)
+    for g, w in zip(got, want):
+        assert rel_err(g.double().cpu().numpy(), w.double().cpu().numpy()) < TOL[dtype]
+    slots = D == 16
+    joint = per_block < 24000 and (batched or not slots)      # (block by block the slots are one launch as it is)
+    assert ("k_gat_bwd_joint" in kernels) == joint
+    # (block by block, the local block has sources of two edges only, which is one kernel)
+    assert any(k in kernels for k in SEPARATE) == (not joint or not batched)
+    c.b.close()
+
+
+def test_slots_without_a_list_of_singles_are_one_launch_as_they_are():
+    src, dst, part, _ = graph(5, 150, 700, 3)
+    c = Call(src, dst, part, 3, 4, 32, torch.float32, sar.SAR_BUILD_NO_SINGLES)
+    kernels, _ = c.run()
+    assert "k_gat_bwd_joint" not in kernels and "k_gat_bwd_slots" in kernels
+    c.b.close()
+
+
+@pytest.mark.parametrize("dtype,H,D", [(torch.float32, 8, 32), (torch.bfloat16, 4, 64), (torch.float32, 3, 64)])
+@pytest.mark.parametrize("wide,few,single", [(60, 0, 0), (9000, 0, 0), (0, 60, 0), (0, 40000, 0), (0, 0, 300), (40, 60, 30000),
+                                             (40, 60, 140_000), (9000, 60, 300)])
+def test_parts_alone_and_parts_that_go_round(dtype, H, D, wide, few, single):
+    """One launch only for two parts and more, none of which goes round its workgroups."""
+    n_dst = 2000
+    k = np.concatenate([np.full(wide, 12), np.full(few, 3), np.full(single, 1)])
+    n = len(k)
+    at = np.arange(k.sum()) - np.repeat(np.cumsum(k) - k, k)
+    rng = np.random.default_rng(8)
+    src = np.repeat(np.arange(n_dst, n_dst + n), k)
+    dst = (np.repeat(rng.integers(0, n_dst, n), k) + 7 * at) % n_dst
+    part = np.concatenate([np.zeros(n_dst, np.int32), np.ones(n, np.int32)])
+    c = Call(src, dst, part, 2, H, D, dtype, sar.SAR_BUILD_SINGLES | sar.SAR_BUILD_COMPACT)      # (no rows for sources without an edge)
+    kernels, got = c.run()
+    assert ("k_gat_bwd_joint" in kernels) == ((wide, few, single) == (40, 60, 30000))
+    _, want = c.run(batched=False)
+    for g, w in zip(got, want):
+        if w.numel():
+            assert rel_err(g.double().cpu().numpy(), w.double().cpu().numpy()) < TOL[dtype]
+    c.b.close()
