@@ -335,8 +335,8 @@ struct FwdState {
     float acc[4];   // running numerator for the lane's 4 features
 };
 
-// One 64-edge chunk position `mine`(lane) holds; folds edges [0,cnt) of it.  The lanes look up the addresses of their
-// edges' rows, all at once, and a batch takes them from there: looked up edge by edge in the launch's table, every row's
+// One 64-edge chunk position `mine`(lane) holds; folds edges [0,cnt) of it.  Over all blocks the lanes look up the addresses of
+// their edges' rows, all at once, and a batch takes them from there: looked up edge by edge in the launch's table, every row's
 // load waited for a scalar load of its own.
 template <typename T, int LPH, int B, bool ALL, bool FLY, bool PAD>
 __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const GlobalPtr<const void>* s_Z,
@@ -345,8 +345,8 @@ __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const GlobalP
 {
     const int ld = PAD ? a.ld : kF, ldh = PAD ? a.ldh : a.H;
     const uint32_t mask = ALL ? ((1u << a.tag_shift) - 1u) : 0xffffffffu;
-    const uint64_t row = (ALL ? s_Z[mine >> a.tag_shift].bits : reinterpret_cast<uint64_t>(a.Z)) +
-                         (uint64_t)(mine & mask) * (uint32_t)(ld * (int)sizeof(T));
+    uint64_t row = 0;
+    if constexpr (ALL) row = s_Z[mine >> a.tag_shift].bits + (uint64_t)(mine & mask) * (uint32_t)(ld * (int)sizeof(T));
     // Shipped scores: lane k of every head group reads its edge's, a batch ahead, so that the weights are ready when
     // the rows arrive (8 heads of 32 bf16 values, 9 M edges: the kernel 1231 -> 1169 us).
     auto shipped = [&](int k0) {
@@ -362,7 +362,12 @@ __device__ inline void fwd_chunk(FwdState<LPH>& st, const FwdP& a, const GlobalP
         typename Row4<T>::Raw raw[B];
         static_for<B>([&](auto kk) {
             const int e = k0 + min((int)decltype(kk)::value, nb - 1);
-            raw[decltype(kk)::value] = load_lane<T, PAD>(GlobalPtr<const T>::at(readlane64(row, e)), foff, on);
+            const T* z;
+            if constexpr (ALL)
+                z = GlobalPtr<const T>::at(readlane64(row, e));
+            else
+                z = static_cast<const T*>(a.Z) + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, e) * ld;
+            raw[decltype(kk)::value] = load_lane<T, PAD>(z, foff, on);
         });
         loads_sent();
         // scores: lane k of every head group takes edge k0+k
@@ -539,6 +544,20 @@ __device__ inline void fwd_rows(const FwdP& a, const Tabs& tabs, int block, int 
     }
     shared_rows(std::integral_constant<int, kWavesPerWG>{}, hubs, a.n_long, from_behind(hubs, block, n_blocks));
     const int64_t n_waves = (int64_t)n_blocks * NW;
+    if constexpr (!ALL) {
+        // Block by block most of a row is its state, read and written, and the rows are taken one by one.  (As below: bf16 4 x 64 and 8 x
+        // 32, 8 blocks of 15 M edges in all, 2103 -> 2230 us, 16 blocks of 0.4 M 274 -> 291; fp32 there 312 -> 328.)
+        for (int64_t r = a.n_long + from_behind(a.n_long, block, n_blocks) * NW + wave; r < a.n_rows; r += n_waves) {
+            const int i = __builtin_amdgcn_readfirstlane((int)a.rows[r]);
+            FwdState<LPH> st;
+            init(st, i, true);
+            const int beg = a.indptr[i], end = a.indptr[i + 1];
+            const float s = a.s[(int64_t)i * ldh + h];
+            edges(st, beg, end, kWave, edges_at(beg, end), s * kLog2e);
+            finish(st, i);
+        }
+        return;
+    }
     // The other rows, 64 of a wavefront's at a time: lane u reads what there is to know of the u-th (its place in the index),
     // so that a row does not wait for its list entry and then for its range; its first edges and its score half are read while
     // the row before it is folded.  What binds small and middling launches is this chain of loads, not the bytes.  (With the
