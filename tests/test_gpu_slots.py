@@ -96,3 +96,35 @@ def test_forward_at_the_lines_of_the_generic_kernel(dtype, H, D, batched, fly):
     got = (gu.gat_fwd_all if batched else gu.gat_fwd_stream)(b, Zdst, Zs, a_l, a_r, SLOPE, fly=fly)
     check_fwd(got, want, deg, dtype)
     b.close()
+
+
+@pytest.mark.parametrize("dtype,H,D,ship", [(torch.float32, 1, 47, False), (torch.bfloat16, 4, 16, False), (torch.float32, 4, 16, True)])
+def test_wavefronts_with_more_rows_than_lanes(dtype, H, D, ship):
+    """More short rows than the resident wavefronts have lanes, so that every one looks its rows up more than once, behind a few
+    rows that four wavefronts share; against sums in 64 bits on the device."""
+    N, deg, hubs = 700_000, 3, 5
+    g = torch.Generator(device="cuda").manual_seed(D)
+    own = torch.arange(N, device="cuda")
+    src = torch.cat([(own * deg + 7919 * k) % N for k in range(deg)] + [torch.arange(0, N, 53, device="cuda")] * hubs)
+    dst = torch.cat([own] * deg + [torch.full(((N + 52) // 53,), 1000 * k + 17, device="cuda") for k in range(hubs)])
+    key = torch.unique(dst * N + src)
+    src, dst = key % N, key // N
+    b = sar.sar_blocks_build(src, dst, torch.zeros(N, dtype=torch.int32, device="cuda"), 1, 0)
+    Z = torch.randn(N, H, D, generator=g, device="cuda").to(dtype)
+    a_l, s = torch.randn(H, D, generator=g, device="cuda") / D ** 0.5, torch.randn(N, H, generator=g, device="cuda")
+    t = torch.empty(N, H, device="cuda")
+    sar.sar_gat_scores(Z, a_l, t)
+    out, L = torch.full((N, H, D), float("nan"), dtype=dtype, device="cuda"), torch.full((N, H), float("nan"), device="cuda")
+    sar.sar_gat_fwd_all(b, [Z], s, [t] if ship else None, a_l, 0.2, out, L)
+    Zd, e = Z.double(), s.double()[dst] + (Z.double() * a_l.double()).sum(2)[src]
+    e = torch.where(e > 0, e, 0.2 * e)
+    top = torch.full((N, H), -float("inf"), dtype=torch.float64, device="cuda")
+    top.scatter_reduce_(0, dst[:, None].expand(-1, H), e, "amax")
+    w = torch.exp(e - top[dst])
+    l = torch.zeros(N, H, dtype=torch.float64, device="cuda").index_add_(0, dst, w)
+    want = torch.zeros(N, H, D, dtype=torch.float64, device="cuda").index_add_(0, dst, w[..., None] * Zd[src]) / l[..., None]
+    # a weight's exponent is off by a few units of the scores' last place; bf16 results are rounded once
+    tol = 1e-4 if dtype == torch.float32 else 2e-2
+    assert ((out.double() - want).abs() <= tol * want.abs().amax()).all()
+    assert ((L.double() - (top + l.log())).abs() <= 1e-4).all()
+    b.close()
