@@ -46,6 +46,34 @@ def test_scores_of_many_rows(H, D, K, n):
     assert torch.equal(bits(one)[finite], bits(w2)[finite])
 
 
+# at the limits: weights that leave just room for the vectors' values beside them, or not; one slab of columns and several
+@pytest.mark.parametrize("K,H,D,with_rows", [(256, 16, 32, True), (256, 8, 64, True), (256, 4, 128, True), (256, 9, 64, False),
+                                             (256, 5, 128, False), (131, 4, 32, True), (131, 2, 64, True), (131, 8, 32, False),
+                                             (131, 4, 64, False), (131, 3, 128, False), (512, 4, 64, True), (1024, 1, 32, True)])
+@pytest.mark.parametrize("both", [False, True])
+def test_which_scores_leave_with_the_rows(K, H, D, with_rows, both):
+    n = 70_001
+    X, W = torch.randn(n, K, device="cuda").to(torch.bfloat16), torch.randn(K, H * D, device="cuda")
+    a, s, w = torch.randn(H, D, device="cuda"), torch.empty(n, H, device="cuda"), torch.empty(n, H, device="cuda")
+    Z = torch.empty(n, H * D, dtype=torch.bfloat16, device="cuda")
+    other = (a.neg(), torch.empty_like(s)) if both else ()
+    kernels = gu.kernels_of(lambda: sar.sar_linear_fwd(X, W, Z, a, s, *other))
+    assert ("k_scores" not in kernels) == with_rows
+    sar.sar_gat_scores(Z.view(n, H, D), a, w)
+    assert torch.equal(s, w) and (not both or torch.equal(other[1], -w))
+
+
+def test_rows_that_begin_off_a_piece_are_refused_with_scores():
+    """As by the pass over the stored rows, which reads them in 16-byte pieces."""
+    n, K, H, D = 70_001, 64, 4, 64
+    X, W = torch.randn(n, K, device="cuda").to(torch.bfloat16), torch.randn(K, H * D, device="cuda")
+    Z = torch.empty(n * H * D + 4, dtype=torch.bfloat16, device="cuda")[4:].view(n, H * D)
+    a, s = torch.randn(H, D, device="cuda"), torch.empty(n, H, device="cuda")
+    with pytest.raises(sar.SarError, match="16-byte aligned") as e:
+        sar.sar_linear_fwd(X, W, Z, a, s)
+    assert e.value.code == sar.SAR_ERR_INVALID_ARG
+
+
 @pytest.mark.parametrize("over", ["first", "last", "weights"])
 @pytest.mark.parametrize("second", [False, True])
 def test_scores_over_an_operand(over, second):
