@@ -1101,11 +1101,12 @@ unsigned nodewise_grid(int64_t n, int slots, int64_t most = kMaxPersistentWGs)
 
 // k_bwd_begin reads two arrays and keeps nothing from row to row, so a wavefront may as well take its rows once, by workgroups that
 // come in the rows' order: walked by a resident grid the rows under way lie far apart, which memory answers more slowly.  Against it
-// stands what starting workgroups costs.  That decides for a launch whose two arrays fit the 256 MiB memory-side cache, for wavefronts that
-// move little at a time, and for rows of unaligned pieces.
-// fp32 4 x 64, us, resident / once: arrays of 160 MiB 30 / 32 where the call before has read them, 65 / 63 where they are in no cache; 260
-// MiB 47 / 49, 99 / 96; 320 MiB 69 / 67, 115 / 107; 1500 MiB 322 / 292, 374 / 334; 5000 MiB 1159 / 958, 1201 / 1009.
-// Once / resident by the bytes a wavefront moves at a time, least and most of 320 and 1500 MiB, cached and not:
+// stands what starting workgroups costs.  That decides for a launch that moves little more than fits the 256 MiB memory-side cache, for
+// wavefronts that move little at a time, and for rows of unaligned pieces.
+// Bytes are counted with the records, s, L and ds.  us, resident / once, where the call before has read the arrays and where they are in
+// no cache: fp32 4 x 64, 169 MiB 30 / 32, 65 / 63; 295 MiB 54 / 56, 103 / 99; 337 MiB 69 / 67, 115 / 107; 1580 MiB 322 / 292, 374 / 334; bf16 8 x 32,
+// 195 MiB 33 / 35, 70 / 67; 292 MiB 54 / 52, 102 / 94; 341 MiB 71 / 67, 112 / 104; fp32 8 x 8, 230 MiB 36 / 38, 81 / 75; 345 MiB 69 / 65, 109 / 99.
+// Once / resident by the bytes a wavefront moves at a time, least and most for arrays of 320 and 1500 MiB, cached and not:
 //   856 to 1216  1.13 1.33  (bf16 2 x 100, 4 x 20, 5 x 40, 3 x 12, 4 x 12)        1264 to 1320  0.99 1.09  (2 x 36, 3 x 24)
 //   1504         0.98 1.06  (4 x 20)             1628 to 1656  0.92 1.03  (1 x 200, 1 x 48, 2 x 100, 1 x 100)
 //   1704         0.93 1.02  (3 x 32, bf16 3 x 64)       1860 0.86 0.99  (3 x 12)       2160 0.88 0.98  (4 x 64)       2816 0.83 0.87  (bf16 8 x 4)
@@ -1113,9 +1114,8 @@ unsigned nodewise_grid(int64_t n, int slots, int64_t most = kMaxPersistentWGs)
 int64_t begin_grid_most(int64_t n, const NodeGeo& geo, int g, int D)
 {
     constexpr int64_t kOnce = 1 << 22;      // (a launch counts its threads in 32 bits)
-    const int64_t heads = geo.hg.count(g), rows = 2 * heads * D * geo.hg.fb;
-    const int64_t moved = geo.slots(g) * (rows + heads * 28);     // with a record of 16 bytes, s, L and ds
-    return !geo.ragged && moved >= 1600 && n * rows > ((int64_t)320 << 20) ? kOnce : kMaxPersistentWGs;
+    const int64_t heads = geo.hg.count(g), moved = heads * (2 * D * (int64_t)geo.hg.fb + 28);
+    return !geo.ragged && geo.slots(g) * moved >= 1600 && n * moved > ((int64_t)336 << 20) ? kOnce : kMaxPersistentWGs;
 }
 
 #define SAR_DISPATCH_G(T, F, CALL)                                                   \

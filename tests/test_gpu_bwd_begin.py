@@ -36,11 +36,12 @@ def test_records(n, H, D, dtype, act):
 
 
 # arrays beyond the memory-side cache: wavefronts that move little at a time and rows of unaligned pieces stay with a resident grid,
-# as arrays do that a part of fits it; the size counts launch by launch where heads are shared among several
+# as arrays do that a part of fits it; records count, and launch by launch where heads are shared among several
 @pytest.mark.parametrize("mib,H,D,dtype,once", [
     (400, 2, 100, torch.bfloat16, False), (1200, 2, 100, torch.bfloat16, False), (400, 1, 47, torch.bfloat16, False),
     (1200, 1, 47, torch.float32, False), (400, 5, 40, torch.bfloat16, False), (400, 4, 20, torch.float32, False),
-    (280, 4, 64, torch.float32, False), (400, 4, 64, torch.float32, True), (400, 8, 32, torch.bfloat16, True),
+    (280, 4, 64, torch.float32, False), (280, 8, 32, torch.bfloat16, True), (200, 8, 8, torch.float32, False),
+    (240, 8, 8, torch.float32, True), (400, 4, 64, torch.float32, True), (400, 8, 32, torch.bfloat16, True),
     (400, 3, 12, torch.float32, True), (400, 2, 100, torch.float32, True), (400, 8, 4, torch.bfloat16, True),
     (500, 4, 100, torch.float32, False), (1000, 4, 100, torch.float32, True)])
 def test_which_rows_are_taken_once(mib, H, D, dtype, once):
