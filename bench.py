@@ -35,8 +35,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ("gat.hip", "gat_f256.h", "gat_joint.h", "gat_joint_launch.h", "gat_slices.h", "gat_slices.hip", "gat_slots.h",
-                  "gather_common.h", "global_ptr.h", "spmm.hip")
+KERNEL_SOURCES = ("gat.hip", "gat_f256.h", "gat_joint.h", "gat_joint_bf16.hip", "gat_joint_f32.hip", "gat_joint_launch.h",
+                  "gat_slices.h", "gat_slices.hip", "gat_slots.h", "gather_common.h", "global_ptr.h", "spmm.hip")
 
 
 def parse():
@@ -516,8 +516,9 @@ def time_gat(args, torch, sar, synth, name, steps, warmup, full_report):
                     + (" (all blocks)" if args.mode == "all" else " (per block)"),
                     "avg_ms": fwd_ms, "alg_bytes": alg["gat_fwd"]},
         "gat_bwd": {"kernel": (("k_gat_bwd_slices" if dense else "k_gat_bwd_f256") + " + k_gat_bwd_few" if fast
-                               else "k_gat_bwd_f256 + k_gat_bwd_few in their padded geometry, or k_gat_bwd, by shape")
+                               else "k_gat_bwd_f256 + k_gat_bwd_few in their padded geometry, k_gat_bwd_slots or k_gat_bwd, by shape")
                     + (" + k_gat_bwd_single" if n_singles else "")
+                    + (", or k_gat_bwd_joint in their place where the call is small" if not dense else "")
                     + ("" if layer.errors != "full" else " + k_bwd_zero_rows"),
                     "single_edge_sources_destination_major": n_singles,
                     "avg_ms": bwd_ms, "alg_bytes": alg["gat_bwd"],
