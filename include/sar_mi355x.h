@@ -416,8 +416,10 @@ int sar_gat_bwd_end_noalloc(const void* Zdst, const float* ds, const float* a_r,
 
 /* Z[n,F] = X[n,K] W[K,F]; X, Z of `dtype`, W fp32 row-major.  When a_score is
  * non-null (fp32 [H,D], F = H*D) also writes score[v,h] = <a_score[h], Z[v,h]>
- * from the fp32 accumulators (fp32 [n,H]); a second pair (a_score2, score2)
- * may be given as well.  Pass H = D = 0 and null pointers for no scores. */
+ * (fp32 [n,H]): of fp32 rows from the accumulators, equal to the scores of the
+ * stored rows up to fp32 rounding; of bf16 rows from the rows as they are stored,
+ * rounded.  A second pair (a_score2, score2) may be given as well.  Pass
+ * H = D = 0 and null pointers for no scores. */
 int sar_linear_fwd(const void* X, const float* W, void* Z, int dtype, int64_t n, int K, int F,
                    int H, int D, const float* a_score, float* score, const float* a_score2,
                    float* score2, void* stream);

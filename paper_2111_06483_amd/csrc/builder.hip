@@ -365,7 +365,8 @@ struct DeviceTemps {
 // Up to so many tiles every workgroup adds up the sums of the tiles before its own, 16 loads a thread at most, and a scan is two
 // launches; beyond that the sums are scanned by a pass of their own.  (A build of 15 million edges in 8 blocks has eight scans of up to
 // 1.2 million values, bound by launches and their chains of loads: 16 launches of 6.5 us for the scans and 8 of 5.6 for the sums, now 8 of
-// 5.0 and 8 of 4.2; the whole build 1340 -> 1260 us.)
+// 5.0 and 8 of 4.2; the whole build 1340 -> 1260 us.  The scans of a build over N nodes, sums by a pass of their own / added up by every
+// workgroup, us: N of 0.5 million 93 / 65, 2 million 110 / 78, 4 million (1954 tiles) 127 / 95, 8 million (3907 tiles) 204 / 135.)
 constexpr int64_t kScanOnce = 4096;
 
 // out[k] = base + sum of in[0..k) for k in [0,n); in may equal out.

@@ -10,7 +10,7 @@ namespace sar {
 // pointer, the compiler cannot tell what it points to and reads through it by FLAT instructions: their answers count in two
 // counters and come in no order, so that a wavefront waits for all it has under way before it uses the first of them, and
 // every address is a register pair that is tested for LDS.  (Kernel times over 140 steps of 10 us to 90 ms, geometric means: the
-// sum's forward kernel 3% shorter by GLOBAL instructions, single-edge sources 3%, the generic attention kernel 2%, others 0 to 2%.) 
+// sum's forward kernel 3% shorter by GLOBAL instructions, single-edge sources 3%, the generic attention kernel 2%, others 0 to 2%.)
 template <typename T>
 struct GlobalPtr {
     uint64_t bits;
