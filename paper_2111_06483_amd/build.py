@@ -80,11 +80,13 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("link failed:\n" + res.stderr)
         os.replace(tmp, lib)
 
+    # (the libraries know nothing of torch: they are built where the binding cannot be, too)
     with ThreadPoolExecutor(max_workers=8) as pool:
-        objs = list(pool.map(compile_one, SOURCES + BENCH_SOURCES + [BINDING_SOURCE]))
+        binding = pool.submit(compile_one, BINDING_SOURCE)
+        objs = list(pool.map(compile_one, SOURCES + BENCH_SOURCES))
     link(objs[:len(SOURCES)], LIB)
-    link(objs[len(SOURCES):-1], BENCH_LIB)
-    link(objs[-1:], BINDING, binding_link_flags())
+    link(objs[len(SOURCES):], BENCH_LIB)
+    link([binding.result()], BINDING, binding_link_flags())
     return LIB
 
 

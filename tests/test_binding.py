@@ -164,3 +164,24 @@ else:
     raise AssertionError("taken")
 """ % changed], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_the_libraries_are_built_where_the_binding_cannot_be(tmp_path, monkeypatch):
+    import subprocess
+    from paper_2111_06483_amd import build
+
+    def no_torch():
+        raise ImportError("No module named 'torch'")
+
+    def compiler(cmd, **kwargs):
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    for name in ("LIB", "BENCH_LIB", "BINDING"):
+        monkeypatch.setattr(build, name, str(tmp_path / name))
+    monkeypatch.setattr(build, "binding_flags", no_torch)
+    monkeypatch.setattr(build.subprocess, "run", compiler)
+    with pytest.raises(ImportError):
+        build.build()
+    assert (tmp_path / "LIB").exists() and (tmp_path / "BENCH_LIB").exists() and not (tmp_path / "BINDING").exists()
