@@ -1348,9 +1348,10 @@ f256::BwdP bwd_params(const BwdScalars& a)
 // and 36.1 ms.  Launches in which a wavefront has few sources want them all the same (4 x 64 over 0.7 M edges 38 us, with two a
 // CU 41; 2 x 100 over 1 M 66 and 71), and so do bf16 rows (201 M edges 5.4 and 5.7 ms; 8 M 611 and 795 us), and shorter
 // rows, of which two workgroups have too little under way.  (The call, two a CU / all, two power-law and two uniform graphs of 8 to 21 M
-// edges, by bytes of a row in a launch: 432, 6 x 36, 1.04 to 1.07; 576, 3 x 48 and 4 x 36, 0.97 to 1.04; 640, 4 x 40, 1.00 to 1.04;
-// 672, 3 x 56, 0.95 to 1.00; 704 to 736, 0.95 to 1.01; 768, 1 x 192 to 4 x 48, 0.94 to 1.03, six of sixteen up to 0.99 and two above
-// 1.01; 896 and 960, 0.97 to 1.00; 1024, 0.98 to 0.99, and 16 x 16, with four rows under way, 0.99 to 1.01.)
+// edges, by bytes of a row in a launch: 432, 6 x 36, 1.04 to 1.07; 480 and 320, 5 x 40, 1.02 to 1.03; 576, 3 x 48 and 4 x 36, 0.97 to 1.04;
+// 640, 4 x 40, 1.00 to 1.04; 640 and 320, 3 x 80, 0.98 to 1.00; 672, 3 x 56, 0.95 to 1.00; 704 to 736, 0.95 to 1.01; 768, 1 x 192 to
+// 4 x 48, 0.94 to 1.03, six of sixteen up to 0.99 and two above 1.01; 896, 4 x 56, 0.97 to 0.99; 1024, 0.98 to 0.99, and 16 x 16, with
+// four rows under way, 0.99 to 1.01.)
 template <typename T>
 unsigned wide_grid(const f256::BwdP& p, int resident)
 {
